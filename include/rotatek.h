@@ -145,8 +145,9 @@ typedef struct {
     float* mu;           /* [B,H_kv,d]    per-head channel mean of the fitted Keys             */
     float* delta_mu;     /* [B,H_kv,d]    mu - R_r R_r^T mu  (Alg. 1 step 15)                   */
     float* cov;          /* optional [B,H_kv,d,d]: the un-weighted scatter of Alg. 1 step 3     */
-    int32_t* sweeps;     /* optional [B,H_kv] (int32): Jacobi sweeps the eigensolver used; 20 (its limit)
-                          * means that the off-diagonal norm was still above 2e-8 ||C_q||_F: not converged */
+    int32_t* sweeps;     /* optional [B,H_kv] (int32): 0 for a C_q that was diagonal as it came (off-diagonal
+                          * norm at most 2e-8 ||C_q||_F), 1 for one solved directly, else the sweeps of the
+                          * Jacobi iteration; 20 (its limit) means that it did not converge */
 } rk_fit_out;
 
 /* ---- context ------------------------------------------------------------- */
@@ -166,9 +167,9 @@ rk_status rk_validate_layout(const rk_layout* L);
 rk_status rk_cache_bytes(const rk_layout* L, size_t* k_packed_bytes, size_t* v_cache_bytes);
 
 /* Bytes of workspace rk_fit_rotation / rk_fit_subspace need for at most max_tokens rows per sequence
- * (0 for an invalid layout or max_tokens outside 0..RK_MAX_TOKENS).  At least 1.3 MB per (b, h_kv):
- * the eigensolver records its rotations there (up to 20 sweeps) after the covariance partials,
- * 64 KB per 2048 rows, are no longer needed. */
+ * (0 for an invalid layout or max_tokens outside 0..RK_MAX_TOKENS).  At least 0.3 MB per (b, h_kv):
+ * the eigensolver keeps its reflections and vectors there after the covariance partials, 64 KB per
+ * 512 rows, are no longer needed. */
 size_t rk_fit_workspace_size(const rk_layout* L, int32_t max_tokens);
 /* Bytes of workspace rk_decode_attn needs (depends on batch, heads, max_seq_len). */
 size_t rk_decode_workspace_size(const rk_ctx* ctx, const rk_layout* L);
@@ -194,8 +195,11 @@ rk_status rk_stream_read(rk_ctx* ctx, const void* src, size_t bytes, void* strea
  * C_q ("Query-Weighted PCA": R = eigenvectors of C_q); rank of every
  * eigenvalue (descending, ties -> lower column) -> mask, keep_idx, R_r;
  * delta_mu (step 15).  n_b = 0 gives mu = 0, C = 0 (R = I).
- * The eigensolver is a parallel Jacobi iteration that stops when the off-diagonal
- * Frobenius norm is at most 2e-8 ||C_q||_F, or after 20 sweeps (see `sweeps`).
+ * The eigensolver works in double: Householder reduction to a tridiagonal matrix,
+ * multisection, vectors by twisted factorisation.  A matrix whose vectors fail the
+ * solver's own checks, and every matrix under RK_OPT_FORCE_GENERIC, is solved by
+ * a parallel Jacobi iteration that stops when the off-diagonal Frobenius norm is
+ * at most 2e-8 ||C_q||_F, or after 20 sweeps (see `sweeps`).
  * Errors: INVALID_ARG (NULL required pointer, bad strides/sizes), UNSUPPORTED,
  * WORKSPACE, HIP.                                                             */
 rk_status rk_fit_rotation(rk_ctx* ctx, const rk_layout* L, const rk_rows* keys,

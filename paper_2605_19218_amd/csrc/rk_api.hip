@@ -98,20 +98,20 @@ RowsDev to_dev(const rk_rows* r)
 
 int cov_chunks(int max_tokens) { int n = (max_tokens + COV_CHUNK - 1) / COV_CHUNK; return n < 1 ? 1 : n; }
 
-// The covariance partials are dead once the covariance is reduced: the eigensolver's recorded
-// rotations reuse their space (the region is sized for the larger of the two).
-struct FitWs { size_t part_S, part_sum, cov, sweeps, total; };
+// The covariance partials are dead once the covariance is reduced: the eigensolver's
+// scratch reuses their space (the region is sized for the larger of the two).
+struct FitWs { size_t part_S, part_sum, cov, status, total; };
 FitWs fit_ws(const rk_layout* L, int max_tokens)
 {
     size_t U = (size_t)L->batch * L->n_kv_heads, nc = (size_t)cov_chunks(max_tokens);
     FitWs w;
     w.part_S = 0;
     size_t first = U * nc * D * D * sizeof(float);
-    if (first < eig_rotation_bytes(U)) first = eig_rotation_bytes(U);
+    if (first < eig_scratch_bytes(U)) first = eig_scratch_bytes(U);
     w.part_sum = align_up(w.part_S + first, 256);
     w.cov = align_up(w.part_sum + U * nc * D * sizeof(float), 256);
-    w.sweeps = align_up(w.cov + U * D * D * sizeof(float), 256);
-    w.total = align_up(w.sweeps + U * sizeof(int32_t), 256);
+    w.status = align_up(w.cov + U * D * D * sizeof(float), 256);
+    w.total = align_up(w.status + 2 * U * sizeof(int32_t), 256);
     return w;
 }
 
@@ -394,8 +394,8 @@ rk_status rk_fit_rotation(rk_ctx* ctx, const rk_layout* L, const rk_rows* keys, 
     e = launch_cov_finalize(rows, B, Hkv, nc, (flags & RK_FIT_CENTER) != 0, ct == cov_chunk_tokens(RK_BF16, true),
                             part_S, part_sum, cov, out->mu, st);
     if (e != hipSuccess) return hip_fail(ctx, e, "covariance reduction launch");
-    e = launch_eig(U, cov, sigma, out->mu, L->keep, out->R, out->eigvals, out->mask, out->keep_idx, out->R_r,
-                   out->delta_mu, out->sweeps, ws + w.part_S, (int32_t*)(ws + w.sweeps), st);
+    e = launch_eig(ctx->force_generic != 0, U, cov, sigma, out->mu, L->keep, out->R, out->eigvals, out->mask, out->keep_idx, out->R_r,
+                   out->delta_mu, out->sweeps, ws + w.part_S, (int32_t*)(ws + w.status), st);
     if (e != hipSuccess) return hip_fail(ctx, e, "eigensolver launch");
     return RK_OK;
 }

@@ -40,6 +40,14 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_wave_barrier();
 }
 
+// Work-group barrier for data that goes through LDS only: __syncthreads() would also wait until the global stores
+// issued so far are acknowledged, a round trip to the L2 in every step of a loop that stores a row per step.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // Device view of rk_rows (see rotatek.h).
 struct RowsDev {
     const void* data;

@@ -1,0 +1,1081 @@
+// All eigenpairs of the query-weighted scatter C_q = (sigma sigma^T) .* C of every (b, h_kv) (step 5 of Alg. 1,
+// Eq. 4, and the "Query-Weighted PCA" of Sec. 3.2), then rank, keep-mask, R_r and delta_mu (steps 14-16).
+//
+// Four launches, all arithmetic in double:
+//   eig_tridiag      C_q = Q T Q^T by Householder reflections, one work-group per matrix, C_q in registers
+//   eig_tri_vectors  eigenvalues of T by multisection, vectors of T by twisted factorisation, whole chip
+//   eig_orth_back    one Newton-Schulz step on the vectors of T, then R = Q Z, whole chip
+//   eig_finish       rank, mask, keep_idx, R_r, delta_mu; solves the (rare) matrices that the first three
+//                    leave alone by parallel Jacobi
+// The fp64 vector rate of this part equals its unpacked fp32 rate, so double costs registers and LDS width only; it
+// buys vectors that need no iteration over the whole matrix.  A sweep of Jacobi is 127 dependent rounds on one compute
+// unit and 8-10 sweeps are needed; the reduction is 126 dependent steps in all, and everything behind it is independent
+// per eigenpair.  Measured (32 / 512 matrices): 102 + 36 + 28 + 10 us / 214 + 334 + 546 us against 756 us / 2.3 ms of the
+// parallel Jacobi that solved every matrix before, with eigenvalues to their fp32 rounding (1e-7 of the spectrum
+// against 8e-7).
+#include "rk_kernels.hpp"
+
+namespace rk {
+
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// ---------------------------------------------------------------------------
+// Scratch of one matrix (doubles).  A "spread" row of 128 numbers holds element j at eig_spread(j): the eight elements
+// j = s + 16 m of lane s of a group of 16 are four pairs, and a pair of all 16 lanes is 256 contiguous bytes, so that a
+// lane group reads or writes its row with four conflict-free 16-byte accesses.
+constexpr int EIGW_V = 0;                          // [126][128] Householder vectors, spread rows
+constexpr int EIGW_Z = EIGW_V + (D - 2) * D;       // [128][128] vectors of T, row c = column c of the result
+constexpr int EIGW_DE = EIGW_Z + D * D;            // [128] pairs (d_i, e_{i-1}^2) of the scaled T
+constexpr int EIGW_E = EIGW_DE + 2 * D;            // [128] e_i (e_127 unused)
+constexpr int EIGW_TAU = EIGW_E + D;               // [128] H_k = I - tau_k v_k v_k^T
+constexpr int EIGW_SCALE = EIGW_TAU + D;           // C_q = scale * (Q T Q^T)
+constexpr int EIGW_TOTAL = EIGW_SCALE + 2;
+
+size_t eig_scratch_bytes(size_t U) { return U * EIGW_TOTAL * sizeof(double); }
+
+__host__ __device__ constexpr int eig_spread(int j) { return (((j >> 5) * 16 + (j & 15)) << 1) | ((j >> 4) & 1); }
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v)
+{
+    int lo = __double2loint(v), hi = __double2hiint(v);
+    lo = __builtin_amdgcn_mov_dpp(lo, CTRL, 0xf, 0xf, true);
+    hi = __builtin_amdgcn_mov_dpp(hi, CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+// sum over each aligned group of 16 lanes, the same bits in all of them
+__device__ __forceinline__ double row16_sum_f64(double v)
+{
+    v += dpp_f64<0xB1>(v);       // quad_perm [1, 0, 3, 2]
+    v += dpp_f64<0x4E>(v);       // quad_perm [2, 3, 0, 1]
+    v += dpp_f64<0x141>(v);      // row_half_mirror
+    v += dpp_f64<0x140>(v);      // row_mirror
+    return v;
+}
+// 1 / x: hardware estimate and two Newton steps
+__device__ __forceinline__ double rcp_f64(double x)
+{
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(r, fma(-x, r, 1.0), r);
+    return fma(r, fma(-x, r, 1.0), r);
+}
+
+// ---------------------------------------------------------------------------
+// Householder reduction, one 512-thread work-group per matrix.  Thread (rg, cg) = (tid / 16, tid % 16) holds rows
+// rg + 32 i and columns cg + 16 m: the active part shrinks evenly over the threads, and a row lies in the 16
+// consecutive lanes of a group, where sums are lane permutations.  A step has two barriers:
+//   v_k is in LDS; every group forms p = A v on its rows                 -> LDS, barrier
+//   w = p - (tau v^T p / 2) v, A -= tau (v w^T + w v^T); the wave that owns row k + 1 updates that row first, makes the
+//   next reflection from it and publishes it before it goes on          -> LDS, barrier
+// What bounds a step is its dependent chain (two LDS round trips, three lane-group sums, a square root, two barriers).
+// Tried: 1024 threads of 2 x 8 elements (119 us for 32 matrices: twice the sums and LDS reads per element); A v from A x
+// and the column k + 1, every wave taking the square root for itself off the chain (138 us: the second vector and the
+// redundant sums cost more LDS and issue than the chain saves).
+// status[2 u]: 1 for a matrix left to Jacobi (already diagonal to its threshold, zero, or not finite), else 0; status
+// [2 u + 1] is cleared for the two kernels behind, which set it when a vector fails its check (they read the first flag
+// only: the second may change while they run).
+constexpr int TRI_THREADS = 512, TRI_ROWS = 4;
+
+struct TriShared {
+    double vs[2][D];                    // spread: v of this step and of the next
+    double ps[D];                       // spread: A v
+    double d[D], e[D], tau[D];
+    double red[2][TRI_THREADS / 64];
+};
+
+// The reflection that clears row kn right of its first off-diagonal element, made by the wave that owns the row:
+// H = I - tau v v^T, v = x + sign(x_first) |x| e_first, tau = 1 / (|x|^2 + |x_first| |x|).
+template <int KB>
+__device__ __forceinline__ void tri_publish(const double (&row)[8], int kn, TriShared& S, int rg, int cg)
+{
+    double x[8];
+    double s0 = 0.0, s1 = 0.0;
+    const bool own = rg == (kn & 31);
+    const int lead = kn + 1;
+    const double xl = KB < 7 && (lead >> 4) > KB ? row[KB < 7 ? KB + 1 : KB] : row[KB];
+    const int src = 16 * (kn & 3) + (lead & 15);
+    const double first = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(xl), src),
+                                          __builtin_amdgcn_readlane(__double2loint(xl), src));
+#pragma unroll
+    for (int m = KB; m < 8; ++m) {
+        x[m] = m > KB + 1 || cg + 16 * m > lead ? row[m] : 0.0;
+        if (m & 1) s1 = fma(x[m], x[m], s1);
+        else s0 = fma(x[m], x[m], s0);
+    }
+    const double sig = row16_sum_f64(s0 + s1);
+    const double h = fma(first, first, sig);
+    // |x| = h / sqrt(h): hardware estimate and one third-order step
+    const double y = __builtin_amdgcn_rsq(h), t = h * y, r = fma(-t, y, 1.0);
+    const double nrm = fma(t * r, fma(r, 0.375, 0.5), t);
+    const bool act = sig > 1e-36;                                // else nothing to clear at double precision: H = I
+    const double vl = !act ? 0.0 : first >= 0.0 ? first + nrm : first - nrm;      // (|x| is NaN for x = 0)
+    if (own) {
+        double* vb = S.vs[kn & 1];
+#pragma unroll
+        for (int q = KB >> 1; q < 4; ++q) {
+            f64x2 v2;
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                const int m = 2 * q + b;
+                v2[b] = m < KB ? 0.0 : (m <= KB + 1 && cg + 16 * m == lead ? vl : x[m < KB ? KB : m]);
+            }
+            *(f64x2*)(vb + (q * 16 + cg) * 2) = v2;
+        }
+        if (cg == (kn & 15)) {                                   // (this lane also holds the diagonal element)
+            S.tau[kn] = act ? rcp_f64(fma(fabs(first), nrm, h)) : 0.0;
+            S.e[kn] = act ? (first >= 0.0 ? -nrm : nrm) : first;
+            S.d[kn] = KB < 7 && (kn >> 4) > KB ? row[KB < 7 ? KB + 1 : KB] : row[KB];
+        }
+    }
+}
+
+// Steps 16 KB .. 16 KB + 15: column blocks m < KB are finished, and so are row places i < KB / 2.
+template <int KB>
+__device__ __forceinline__ void tri_block(double (&a)[TRI_ROWS][8], TriShared& S, double* __restrict__ Vg, int rg, int cg,
+                                          int wave)
+{
+    constexpr int R0 = KB >> 1, NR = TRI_ROWS - R0;
+    const int k1 = min(16 * KB + 16, D - 2);
+#pragma unroll 1
+    for (int k = 16 * KB; k < k1; ++k) {
+        const bool live = 96 + 4 * wave + 3 > k;                // wave-uniform: some row of this wave is still active
+        double v[8], vi[TRI_ROWS], tau = 0.0;
+        if (live) {
+            const double* vb = S.vs[k & 1];
+#pragma unroll
+            for (int q = KB >> 1; q < 4; ++q) {
+                const f64x2 t = *(const f64x2*)(vb + (q * 16 + cg) * 2);
+                v[2 * q] = t.x;
+                v[2 * q + 1] = t.y;
+            }
+            double p[TRI_ROWS];
+#pragma unroll
+            for (int i = 0; i < TRI_ROWS; ++i) {
+                double s0 = 0.0, s1 = 0.0;
+                if (i >= R0) {
+#pragma unroll
+                    for (int m = KB; m < 8; ++m) {
+                        if (m & 1) s1 = fma(a[i][m], v[m], s1);
+                        else s0 = fma(a[i][m], v[m], s0);
+                    }
+                }
+                p[i] = s0 + s1;
+            }
+            // sums over the 16 lanes; with several rows the first steps halve the rows a lane carries
+            // instead of adding all of them everywhere
+            double t;
+            int row;
+            if constexpr (NR >= 3) {
+                const bool b3 = (cg & 8) != 0, b2 = (cg & 4) != 0;
+                double t0 = b3 ? p[2] : p[0], t1 = b3 ? p[3] : p[1];
+                t0 += dpp_f64<0x128>(b3 ? p[0] : p[2]);          // row_ror 8: lane i takes from lane i ^ 8
+                t1 += dpp_f64<0x128>(b3 ? p[1] : p[3]);
+                t = b2 ? t1 : t0;
+                t += dpp_f64<0x141>(b2 ? t0 : t1);               // row_half_mirror: lane i ^ 7
+                t += dpp_f64<0xB1>(t);
+                t += dpp_f64<0x4E>(t);
+                row = cg >> 2;
+            } else if constexpr (NR == 2) {
+                const bool b3 = (cg & 8) != 0;
+                t = b3 ? p[3] : p[2];
+                t += dpp_f64<0x128>(b3 ? p[2] : p[3]);
+                t += dpp_f64<0x141>(t);
+                t += dpp_f64<0xB1>(t);
+                t += dpp_f64<0x4E>(t);
+                row = 2 + (cg >> 3);
+            } else {
+                t = row16_sum_f64(p[3]);
+                row = 3;
+            }
+            S.ps[eig_spread(rg + 32 * row)] = t;                 // (several lanes store the same number)
+#pragma unroll
+            for (int i = R0; i < TRI_ROWS; ++i) {
+                const double z = vb[eig_spread(rg + 32 * i)];
+                vi[i] = z;
+            }
+            tau = S.tau[k];
+            if (rg == 31) {                                      // the last group to finish keeps the record
+#pragma unroll
+                for (int q = KB >> 1; q < 4; ++q)
+                    *(f64x2*)(Vg + (size_t)k * D + (q * 16 + cg) * 2) = (f64x2){2 * q < KB ? 0.0 : v[2 * q], v[2 * q + 1]};
+            }
+        }
+        lds_barrier();
+        if (live) {
+            double w[8], wi[TRI_ROWS];
+            double d0 = 0.0, d1 = 0.0;
+#pragma unroll
+            for (int q = KB >> 1; q < 4; ++q) {
+                const f64x2 t = *(const f64x2*)(S.ps + (q * 16 + cg) * 2);
+                w[2 * q] = t.x;
+                w[2 * q + 1] = t.y;
+            }
+#pragma unroll
+            for (int i = R0; i < TRI_ROWS; ++i) wi[i] = S.ps[eig_spread(rg + 32 * i)];
+#pragma unroll
+            for (int m = KB; m < 8; ++m) {
+                if (m & 1) d1 = fma(v[m], w[m], d1);
+                else d0 = fma(v[m], w[m], d0);
+            }
+            const double nh = -0.5 * tau * row16_sum_f64(d0 + d1);
+#pragma unroll
+            for (int m = KB; m < 8; ++m) w[m] = fma(nh, v[m], w[m]);
+            auto update = [&](int i) {
+                // rows that are finished hold leftovers of v: whatever they become is never read
+                const double tw = -tau * fma(nh, vi[i], wi[i]), tv = -tau * vi[i];
+#pragma unroll
+                for (int m = KB; m < 8; ++m) a[i][m] = fma(tv, w[m], fma(tw, v[m], a[i][m]));
+            };
+            // the next row sits in place R0, or R0 + 1 behind the last step of an odd block
+            const int kn = k + 1;
+            update(R0);
+            if constexpr ((KB & 1) != 0 && R0 < TRI_ROWS - 1) update(R0 + 1);
+            if (kn < D - 2 && wave == ((kn & 31) >> 2)) {
+                __builtin_amdgcn_s_setprio(3);
+                if ((KB & 1) != 0 && R0 < TRI_ROWS - 1 && (kn >> 5) > R0) tri_publish<KB>(a[R0 < 3 ? R0 + 1 : 3], kn, S, rg, cg);
+                else tri_publish<KB>(a[R0], kn, S, rg, cg);
+                __builtin_amdgcn_s_setprio(0);
+            }
+#pragma unroll
+            for (int i = R0 + 1 + (KB & 1); i < TRI_ROWS; ++i) update(i);
+        }
+        lds_barrier();
+    }
+    if constexpr (KB < 7) tri_block<KB + 1>(a, S, Vg, rg, cg, wave);
+}
+
+__global__ __launch_bounds__(TRI_THREADS) void eig_tridiag(const float* __restrict__ cov, const float* __restrict__ sigma,
+                                                           double* __restrict__ scratch, int32_t* __restrict__ status)
+{
+    __shared__ __attribute__((aligned(16))) TriShared S;
+    const int u = blockIdx.x, tid = threadIdx.x, lane = tid & 63, rg = tid >> 4, cg = tid & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const float* C = cov + (size_t)u * D * D;
+    double* W = scratch + (size_t)u * EIGW_TOTAL;
+
+    double a[TRI_ROWS][8];
+    float cf[TRI_ROWS][8];                  // every load is out before the first is used
+#pragma unroll
+    for (int i = 0; i < TRI_ROWS; ++i)
+#pragma unroll
+        for (int m = 0; m < 8; ++m) cf[i][m] = C[(rg + 32 * i) * D + cg + 16 * m];
+    float sr[TRI_ROWS], sc[8];
+#pragma unroll
+    for (int i = 0; i < TRI_ROWS; ++i) sr[i] = sigma ? sigma[(size_t)u * D + rg + 32 * i] : 1.f;
+#pragma unroll
+    for (int m = 0; m < 8; ++m) sc[m] = sigma ? sigma[(size_t)u * D + cg + 16 * m] : 1.f;
+    double all = 0.0, off = 0.0;
+#pragma unroll
+    for (int i = 0; i < TRI_ROWS; ++i)
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+            const double x = (double)cf[i][m] * ((double)sr[i] * (double)sc[m]);
+            a[i][m] = x;
+            all = fma(x, x, all);
+            off = rg + 32 * i == cg + 16 * m ? off : fma(x, x, off);
+        }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        all += __shfl_xor(all, o);
+        off += __shfl_xor(off, o);
+    }
+    if (lane == 0) { S.red[0][wave] = all; S.red[1][wave] = off; }
+    __syncthreads();
+    all = off = 0.0;
+    for (int w = 0; w < TRI_THREADS / 64; ++w) { all += S.red[0][w]; off += S.red[1][w]; }
+    // uniform: left to Jacobi, whose threshold this is (2e-8 ||C_q||_F); NaN and infinities land here too
+    if (!(off > 4e-16 * all) || !(all < 1e300)) {
+        if (tid == 0) { status[2 * u] = 1; status[2 * u + 1] = 0; }
+        return;
+    }
+    // scaled by a power of two to a Frobenius norm in [1/2, 1)
+    const int ex = __builtin_amdgcn_frexp_exp(sqrt(all));
+#pragma unroll
+    for (int i = 0; i < TRI_ROWS; ++i)
+#pragma unroll
+        for (int m = 0; m < 8; ++m) a[i][m] = ldexp(a[i][m], -ex);
+
+    if (wave == 0) tri_publish<0>(a[0], 0, S, rg, cg);
+    __syncthreads();
+    tri_block<0>(a, S, W + EIGW_V, rg, cg, wave);
+    if (rg == 30 && cg == 14) S.d[126] = a[3][7];
+    if (rg == 30 && cg == 15) S.e[126] = a[3][7];
+    if (rg == 31 && cg == 15) S.d[127] = a[3][7];
+    __syncthreads();
+    // What the vectors are computed from: T plus a diagonal of up to 6.4e-11 (128 distinct multiples of 5e-13), which
+    // separates eigenvalues that are equal to rounding (dead channels, rank-deficient Keys) by enough for
+    // independent vectors and is a thousandth of the fp32 rounding of C; off-diagonals at least 1e-18, so T never splits.
+    if (tid < D) {
+        const double ep = tid > 0 ? S.e[tid - 1] : 0.0, en = tid < D - 1 ? S.e[tid] : 0.0;
+        const double epf = fabs(ep) < 1e-18 ? 1e-18 : ep, enf = fabs(en) < 1e-18 ? 1e-18 : en;
+        ((f64x2*)(W + EIGW_DE))[tid] = (f64x2){S.d[tid] + 5e-13 * (double)((37 * tid) & (D - 1)), tid > 0 ? epf * epf : 0.0};
+        W[EIGW_E + tid] = enf;
+        W[EIGW_TAU + tid] = tid < D - 2 ? S.tau[tid] : 0.0;
+    }
+    if (tid == 0) {
+        W[EIGW_SCALE] = ldexp(1.0, ex);
+        status[2 * u] = 0;
+        status[2 * u + 1] = 0;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Work-group -> (matrix, slice) of the two whole-chip kernels: the eight work-groups of a matrix get linear indices that
+// agree modulo 8, so that they run on one XCD and share the matrix's scratch in its L2 (work-groups are dealt round-robin
+// to the XCDs; eig_tridiag's work-group u is on the same one).
+__device__ __forceinline__ void eig_slice(int& u, int& slice)
+{
+    const int slot = (int)blockIdx.x >> 3;
+    slice = slot & 7;
+    u = 8 * (slot >> 3) + ((int)blockIdx.x & 7);
+}
+static unsigned eig_slices(int U) { return 64u * (unsigned)((U + 7) / 8); }
+
+// Eigenpairs of T, four per wave, 16 lanes each; a work-group makes 16 of a matrix's 128.
+// Eigenvalue by multisection: the 16 lanes count the eigenvalues below 16 points of the interval (sign changes of
+// the three-term recurrence p_{i+1} = (d_i - x) p_i - e_{i-1}^2 p_{i-1}, division-free, rescaled every 16 steps: a step is at
+// least a factor 5e-13 but for one, so 16 stay above 1e-250) and the
+// interval shrinks 17-fold, 12 times: 2 / 17^12 = 3e-15.  T comes through the scalar cache, 8 rows ahead: one wave
+// per SIMD has nobody else to hide a load behind.
+// Vector by twisted factorisation, again without a division in the chain: lane 0 runs (T - lambda) y = 0 from the
+// top, lane 1 from the bottom, both rescaled every 8 steps (exponents kept per block of 8); the vector is the one above
+// the row with the smallest twist gamma_i = (d_i - lambda) + e_{i-1} y_{i-1} / y_i + e_i x_{i+1} / x_i and the other below
+// it.  The second round runs at the Rayleigh-corrected eigenvalue, which leaves a residual of a few 1e-16.
+constexpr int TV_PAIRS = 16, TV_SECT = 12, TV_LD = D + 2;
+
+__global__ __launch_bounds__(256) void eig_tri_vectors(int U, const double* __restrict__ scratch,
+                                                       double* __restrict__ Zout, float* __restrict__ lam_out,
+                                                       int32_t* __restrict__ status)
+{
+    // coefficients of the two recurrences, in the order in which a lane walks them: (d, 1 / e ahead), e behind / e ahead
+    __shared__ f64x2 sco[2][D];
+    __shared__ double sw[2][D];
+    __shared__ double se[D];
+    __shared__ double yx[TV_PAIRS][2][TV_LD];        // y (from the top) and x (from the bottom)
+    __shared__ int ys[TV_PAIRS][2][D / 8];           // their exponents, per block of 8 rows
+    int u, slice;
+    eig_slice(u, slice);
+    if (u >= U || status[2 * u] != 0) return;
+    const int tid = threadIdx.x, lane = tid & 63, s = lane & 15;
+    const int pr = tid >> 4;                          // eigenpair of this work-group
+    const int col = slice * TV_PAIRS + pr;            // result column: descending eigenvalues
+    const int below = D - 1 - col;                    // eigenvalues below this one
+    const double* W = scratch + (size_t)u * EIGW_TOTAL;
+    const f64x2* __restrict__ de = (const f64x2*)(W + EIGW_DE);
+    if (tid < D) {
+        const int i = tid, r = D - 1 - i;
+        const double d = de[i].x, e = W[EIGW_E + i], ep = W[EIGW_E + max(i - 1, 0)];
+        // ahead of row i lies e_i from the top and e_{i-1} from the bottom; past the last row anything finite does
+        const double ie = rcp_f64(i < D - 1 ? e : 1.0), iep = rcp_f64(i > 0 ? ep : 1.0);
+        sco[0][i] = (f64x2){d, ie};
+        sw[0][i] = i > 0 ? ep * ie : 0.0;
+        sco[1][r] = (f64x2){d, iep};
+        sw[1][r] = i < D - 1 ? e * iep : 0.0;
+        se[i] = e;
+    }
+
+    double lo = -1.001, hi = 1.001;                   // the Frobenius norm is below 1
+#pragma unroll 1
+    for (int it = 0; it < TV_SECT; ++it) {
+        const double wid = (hi - lo) * (1.0 / 17.0), x = fma(wid, (double)(s + 1), lo);
+        double p0 = 0.0, p = 1.0;
+        int changes = 0;
+        uint32_t last = 0, sg = 0;
+        f64x2 ca[8], cb[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) ca[i] = de[i];
+        // Scalar loads complete out of order, so a wait for one batch is a wait for all that are out: the next batch is
+        // requested right behind the first use of the present one.
+        auto steps = [&](const f64x2 (&c)[8], f64x2 (&next)[8], int at) {
+            double t = c[0].x - x;
+            asm volatile("" : "+v"(t));
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) next[i] = de[at + i];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const double pn = fma(t, p, -(c[i].y * p0));
+                p0 = p;
+                p = pn;
+                if (i < 7) t = c[i + 1].x - x;
+                sg = __builtin_amdgcn_alignbit(sg, (uint32_t)__double2hiint(p), 31);     // (sg << 1) | sign
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+#pragma unroll 1
+        for (int i0 = 0; i0 < D; i0 += 16) {
+            steps(ca, cb, i0 + 8);
+            steps(cb, ca, min(i0 + 16, D - 8));
+            const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(p), fabs(p0)));
+            p = ldexp(p, -ex);
+            p0 = ldexp(p0, -ex);
+            // 16 signs of this block behind the last one of the block before it
+            changes += __popc((sg ^ ((sg >> 1) | (last << 15))) & 0xffffu);
+            last = sg & 1u;
+            sg &= 0xffffu;
+        }
+        const uint64_t le = __ballot(changes <= below);          // points with at most `below` eigenvalues under them
+        const int m = __popc((uint32_t)(le >> (lane & 48)) & 0xffffu);
+        const double nlo = fma(wid, (double)m, lo);
+        hi = m == 16 ? hi : fma(wid, (double)(m + 1), lo);
+        lo = nlo;
+    }
+    double lam = 0.5 * (lo + hi);
+    __syncthreads();
+
+    const int dir = s & 1;
+    double (*yv)[TV_LD] = yx[pr];
+    double zz[8];
+    double norm2 = 1.0, gam = 0.0;
+#pragma unroll 1
+    for (int round = 0; round < 2; ++round) {
+        {
+            // (all lanes of a pair run the chain of their parity and store the same numbers)
+            double y0 = 0.0, y = 1.0;
+            int exps = 0;
+            double* dst = yv[dir] + (dir ? D - 1 : 0);
+            const int stp = dir ? -1 : 1;
+            f64x2 ca[8], cb[8];
+            double wa[8], wb[8];
+            auto fetch = [&](f64x2 (&c)[8], double (&w)[8], int b) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) { c[i] = sco[dir][8 * b + i]; w[i] = sw[dir][8 * b + i]; }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            auto steps = [&](const f64x2 (&c)[8], const double (&w)[8], int b) {
+                ys[pr][dir][dir ? D / 8 - 1 - b : b] = exps;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    dst[stp * (8 * b + i)] = y;
+                    const double yn = fma((lam - c[i].x) * c[i].y, y, -(w[i] * y0));
+                    y0 = y;
+                    y = yn;
+                }
+                const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(y), fabs(y0)));
+                y = ldexp(y, -ex);
+                y0 = ldexp(y0, -ex);
+                exps += ex;
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            fetch(ca, wa, 0);
+#pragma unroll 1
+            for (int b = 0; b < D / 8; b += 2) {
+                fetch(cb, wb, b + 1);
+                steps(ca, wa, b);
+                fetch(ca, wa, min(b + 2, D / 8 - 1));
+                steps(cb, wb, b + 1);
+            }
+        }
+        __syncthreads();
+        // the twist: smallest |gamma|, first row of equals
+        double best = __builtin_huge_val(), bg = best;
+        int twist = 0;
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+            const int i = s + 16 * m, blk = i >> 3;
+            double g = sco[0][i].x - lam;
+            if (i > 0) {
+                const double yb = ldexp(yv[0][max(i - 1, 0)], ys[pr][0][max(i - 1, 0) >> 3] - ys[pr][0][blk]);
+                g = fma(se[max(i - 1, 0)], yb * rcp_f64(yv[0][i]), g);
+            }
+            if (i < D - 1) {
+                const double xb = ldexp(yv[1][min(i + 1, D - 1)], ys[pr][1][min(i + 1, D - 1) >> 3] - ys[pr][1][blk]);
+                g = fma(se[i], xb * rcp_f64(yv[1][i]), g);
+            }
+            if (fabs(g) < best) { best = fabs(g); bg = g; twist = i; }
+        }
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) {
+            const double ob = __shfl_xor(best, o), og = __shfl_xor(bg, o);
+            const int ot = __shfl_xor(twist, o);
+            if (ob < best || (ob == best && ot < twist)) { best = ob; bg = og; twist = ot; }
+        }
+        const double iy = rcp_f64(yv[0][twist]), ix = rcp_f64(yv[1][twist]);
+        const int ey = ys[pr][0][twist >> 3], ex = ys[pr][1][twist >> 3];
+        double n2 = 0.0;
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+            const int i = s + 16 * m;
+            const double zi = i <= twist ? ldexp(yv[0][i] * iy, ys[pr][0][i >> 3] - ey)
+                                         : ldexp(yv[1][i] * ix, ys[pr][1][i >> 3] - ex);
+            zz[m] = zi;
+            n2 = fma(zi, zi, n2);
+        }
+        norm2 = row16_sum_f64(n2);
+        gam = bg;
+        if (round == 0) lam += gam / norm2;
+        __syncthreads();
+    }
+    const double inv = 1.0 / sqrt(norm2);
+    // residual |gamma| / ||z||: a few 1e-16 when all is well; anything else (NaN included) goes to Jacobi
+    if (s == 0) {
+        lam_out[(size_t)u * D + col] = (float)((lam + gam / norm2) * W[EIGW_SCALE]);
+        if (!(fabs(gam) * inv < 1e-12)) status[2 * u + 1] = 1;
+    }
+    double* Zc = Zout + (size_t)u * EIGW_TOTAL + EIGW_Z + (size_t)col * D;
+#pragma unroll
+    for (int m = 0; m < 8; ++m) Zc[s + 16 * m] = zz[m] * inv;
+}
+
+// ---------------------------------------------------------------------------
+// R = Q Z after one Newton-Schulz step Z <- Z (3 I - Z^T Z) / 2; 16 columns per work-group of 4 waves.
+// The step is what makes independent vectors safe: neighbours a gap g apart come out orthogonal only to about
+// 1e-16 / g, the step squares that defect, and because each vector is an eigenvector to 1e-16 the correction mixes
+// close neighbours only and costs no residual.  A defect above 0.05 sends the matrix to Jacobi.
+// Both products run on the fp64 matrix cores with all of Z in LDS; then Z's space takes the reflections, which are
+// applied in descending order, 16 lanes per column, the column in registers.  Bound: the 126 dependent reflections
+// (LDS read, dot product over a lane group, update).
+constexpr int OB_LD = D + 2, OB_MLD = 17;
+constexpr size_t OB_LDS_BYTES = (size_t)(D * OB_LD + D * OB_MLD + D) * sizeof(double);
+
+template <int KB>
+__device__ __forceinline__ void ob_reflect(double (&x)[8], const double* __restrict__ Vs, const double* __restrict__ taus,
+                                           int s)
+{
+    constexpr int K1 = 16 * KB + 15 < D - 2 ? 16 * KB + 15 : D - 3;
+#pragma unroll 2
+    for (int k = K1; k >= 16 * KB; --k) {
+        double v[8];
+#pragma unroll
+        for (int p = KB >> 1; p < 4; ++p) {
+            const f64x2 t = *(const f64x2*)(Vs + (size_t)k * D + (p * 16 + s) * 2);
+            v[2 * p] = t.x;
+            v[2 * p + 1] = t.y;
+        }
+        double t0 = 0.0, t1 = 0.0;
+#pragma unroll
+        for (int m = KB; m < 8; ++m) {
+            if (m & 1) t1 = fma(v[m], x[m], t1);
+            else t0 = fma(v[m], x[m], t0);
+        }
+        const double t = row16_sum_f64(t0 + t1) * -taus[k];
+#pragma unroll
+        for (int m = KB; m < 8; ++m) x[m] = fma(t, v[m], x[m]);
+    }
+    if constexpr (KB > 0) ob_reflect<KB - 1>(x, Vs, taus, s);
+}
+
+__global__ __launch_bounds__(256) void eig_orth_back(int U, const double* __restrict__ scratch,
+                                                     float* __restrict__ R_out, int32_t* __restrict__ status)
+{
+    extern __shared__ __attribute__((aligned(16))) double ob_lds[];
+    double* Zs = ob_lds;                    // [128][130] all vectors of T; later the reflections [126][128]
+    double* Ms = Zs + D * OB_LD;            // [128][17]
+    double* taus = Ms + D * OB_MLD;         // [128]
+    int u, slice;
+    eig_slice(u, slice);
+    if (u >= U || status[2 * u] != 0) return;
+    const int c0 = slice * 16;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, n = lane & 15;
+    const double* W = scratch + (size_t)u * EIGW_TOTAL;
+    for (int i = tid; i < D * D / 2; i += 256) {
+        const f64x2 t = ((const f64x2*)(W + EIGW_Z))[i];
+        *(f64x2*)(Zs + (i >> 6) * OB_LD + 2 * (i & 63)) = t;
+    }
+    if (tid < D) taus[tid] = W[EIGW_TAU + tid];
+    __syncthreads();
+
+    // G = Z^T Z[:, c0 ..]: wave = rows 32 wave ..+31 of G.  A 16x16x4 step takes one contraction index per lane group;
+    // two steps share a 16-byte read, so group g holds indices 8 t + 2 g + b of step pair t.
+    // Result element r of lane (g, n) is row 4 r + g, column n.
+    f64x4 acc[2];
+    acc[0] = acc[1] = (f64x4){0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+    for (int t = 0; t < 16; ++t) {
+        const int kk = 8 * t + 2 * g;
+        const f64x2 bv = *(const f64x2*)(Zs + (c0 + n) * OB_LD + kk);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const f64x2 av = *(const f64x2*)(Zs + (32 * wave + 16 * q + n) * OB_LD + kk);
+            acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(av.x, bv.x, acc[q], 0, 0, 0);
+            acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(av.y, bv.y, acc[q], 0, 0, 0);
+        }
+    }
+    bool bad = false;
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = 32 * wave + 16 * q + 4 * r + g;
+            const double dev = acc[q][r] - (i == c0 + n ? 1.0 : 0.0);
+            bad = bad || !(fabs(dev) < 0.05);
+            Ms[i * OB_MLD + n] = (i == c0 + n ? 1.0 : 0.0) - 0.5 * dev;
+        }
+    if (bad) status[2 * u + 1] = 1;
+    __syncthreads();
+
+    // Z' = Z M for the 16 columns: rows 32 wave ..+31
+    acc[0] = acc[1] = (f64x4){0.0, 0.0, 0.0, 0.0};
+#pragma unroll 8
+    for (int t = 0; t < 32; ++t) {
+        const int i = 4 * t + g;
+        const double bv = Ms[i * OB_MLD + n];
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(Zs[i * OB_LD + 32 * wave + 16 * q + n], bv, acc[q], 0, 0, 0);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) Ms[(32 * wave + 16 * q + 4 * r + g) * OB_MLD + n] = acc[q][r];
+    for (int i = tid; i < (D - 2) * D / 2; i += 256) *(f64x2*)(Zs + 2 * i) = ((const f64x2*)(W + EIGW_V))[i];
+    __syncthreads();
+
+    const int cc = 4 * wave + g;            // 16 lanes per column, lane n: rows n + 16 m
+    double x[8];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) x[m] = Ms[(n + 16 * m) * OB_MLD + cc];
+    ob_reflect<7>(x, Zs, taus, n);
+#pragma unroll
+    for (int m = 0; m < 8; ++m) Ms[(n + 16 * m) * OB_MLD + cc] = x[m];
+    __syncthreads();
+    const int row = tid >> 1, h = 8 * (tid & 1);
+    float4 o[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+        o[q] = make_float4((float)Ms[row * OB_MLD + h + 4 * q], (float)Ms[row * OB_MLD + h + 4 * q + 1],
+                           (float)Ms[row * OB_MLD + h + 4 * q + 2], (float)Ms[row * OB_MLD + h + 4 * q + 3]);
+    float4* dst = (float4*)(R_out + (size_t)u * D * D + (size_t)row * D + c0 + h);
+    dst[0] = o[0];
+    dst[1] = o[1];
+}
+
+// ---------------------------------------------------------------------------
+// Parallel two-sided Jacobi for the matrices that the reduction leaves alone, run by the work-group of eig_finish: a
+// round-robin ordering (a sweep is 127 rounds of 64 disjoint pairs), A in LDS, the rows of V in registers.
+// Pairs are taken by POSITION: position 2 k and 2 k + 1 form pair k, and after every round the rows and columns move
+// to new positions (position 0 stays, 1 -> 2, even positions move up by two, 126 -> 127, odd positions move down by
+// two): the 127 moving positions form one cycle, every two indices meet exactly once in 127 rounds, and after a sweep
+// every index is back where it started, so eigenvalue c is the final A[c][c] and its vector is V[:, c].  Every thread
+// reads and writes the same LDS addresses in every round: the rotated 2x2 block is written straight to its next
+// position in a second copy of A, and only the part on or above the diagonal (by pair, then by position) is kept.
+// V: lane k of a wave holds the elements at positions 2 k ("top") and 2 k + 1 ("bottom") of its rows, lane 0 its pair
+// exchanged, so that the 127 moving positions form one ring through the registers: a round's movement is two
+// whole-wave lane shifts and a select.
+constexpr int EIG_THREADS = 1024;
+constexpr int EIG_MAX_SWEEPS = 20;
+constexpr int EIG_ROUNDS = D - 1;
+constexpr int EIG_LD = D + 2;             // row stride of the LDS copies of A (even: a 2x2 block is two 8-byte reads)
+constexpr size_t EIG_LDS_BYTES = (size_t)(2 * D * EIG_LD + 4 * 64 + 32 + D) * sizeof(float);
+
+// LDS offset of the kept copy of element (r, c) = (c, r): pairs in ascending order, then positions
+__device__ __forceinline__ constexpr int eig_upper(int r, int c)
+{
+    return ((r >> 1) < (c >> 1) || ((r >> 1) == (c >> 1) && r <= c)) ? r * (D + 2) + c : c * (D + 2) + r;
+}
+
+// position of a row / column after one round
+__host__ __device__ constexpr int eig_next_pos(int p)
+{
+    return p == 0 ? 0 : p == 1 ? 2 : p == D - 2 ? D - 1 : (p & 1) ? p - 2 : p + 2;
+}
+
+// Rotation that annihilates the (p, q) element: t = tan, s = sin, tau = s / (1 + c).  One square
+// root and hardware reciprocals with a Newton step each: the chain sits between the two barriers of
+// every round, and the IEEE division and square-root sequences are several times as long.
+// (s, tau) is applied as x' = x - s (y + tau x), y' = y + s (x - tau y), which is orthogonal to the
+// accuracy of tau = s / (1 + c) alone, so a last-place error in t only moves the angle.
+__device__ __forceinline__ float rcp_nr(float x)
+{
+    float r = __builtin_amdgcn_rcpf(x);
+    return fmaf(r, fmaf(-x, r, 1.f), r);
+}
+__device__ __forceinline__ void jacobi_params(float app, float aqq, float apq, float thr_skip, float& s, float& tau,
+                                              float& t)
+{
+    s = 0.f; tau = 0.f; t = 0.f;
+    if (fabsf(apq) > thr_skip) {
+        // t = sgn(theta) / (|theta| + sqrt(theta^2 + 1)), theta = (aqq - app) / (2 apq), without forming theta
+        const float al = aqq - app, be = 2.f * apq;
+        const float h = __builtin_amdgcn_sqrtf(fmaf(al, al, be * be));
+        t = (al >= 0.f) ? be * rcp_nr(al + h) : be * rcp_nr(al - h);
+        const float d = fmaf(t, t, 1.f);
+        float c = __builtin_amdgcn_rsqf(d);
+        c = c * fmaf(-0.5f * d * c, c, 1.5f);          // one Newton step on 1/sqrt(d)
+        s = t * c;
+        tau = s * rcp_nr(1.f + c);
+    }
+}
+
+// whole-wave lane shifts by one (data-parallel-primitive moves; the end lane has no source and keeps `keep`)
+__device__ __forceinline__ float lane_from_below(float keep, float v)      // lane i <- lane i - 1; lane 0 keeps `keep`
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, keep), __builtin_bit_cast(int, v),
+                                                                 0x138, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float lane_from_above(float keep, float v)      // lane i <- lane i + 1; lane 63 keeps `keep`
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, keep), __builtin_bit_cast(int, v),
+                                                                 0x130, 0xf, 0xf, false));
+}
+
+template <bool B>
+struct EigBool { static constexpr bool value = B; };
+
+constexpr int EIGV_ROWS = 9;                            // rows of V per wave (waves 1..15)
+// Eigenvalues to lam_out [128] and vectors to R_out [128][128] (column c = vector of lam_out[c]); returns the number of
+// sweeps, 20 = still above the threshold of 2e-8 ||C_q||_F.
+__device__ __forceinline__ int jacobi_solve(const float* __restrict__ C, const float* __restrict__ sg,
+                                            float* __restrict__ lam_out, float* __restrict__ R_out, float* sm)
+{
+    float* A2 = sm;                                   // [2][128][130]: the two copies of A
+    float2* prm = (float2*)(A2 + 2 * D * EIG_LD);     // [2][64] (sin, sin / (1 + cos)) of this round and the next
+    float* red = (float*)(prm + 128);                 // [32] reduction scratch
+    constexpr int BUF = D * EIG_LD;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);          // 16 waves
+
+    // load C_q = sigma_i sigma_j C_ij and ||C_q||_F^2
+    float nrm = 0.f;
+    for (int idx = tid; idx < D * D; idx += EIG_THREADS) {
+        int i = idx >> 7, j = idx & 127;
+        float v = C[idx];
+        if (sg) v *= sg[i] * sg[j];
+        A2[i * EIG_LD + j] = v;
+        nrm = fmaf(v, v, nrm);
+    }
+    nrm = wave_sum(nrm);
+    if (lane == 0) red[wave] = nrm;
+    __syncthreads();
+    float normF2 = 0.f;
+    for (int w = 0; w < 16; ++w) normF2 += red[w];
+    const float normF = sqrtf(normF2);
+    const float thr_skip = 1e-12f * normF;
+    const float tol2 = (2e-8f * 2e-8f) * normF2;
+    __syncthreads();
+
+    // The 2016 blocks above the diagonal as 32 wave-wide tasks, two per wave: task j covers row
+    // pair j (63 - j blocks) in its first lanes and row pair 62 - j (j + 1 blocks) in the rest;
+    // task 31 is the 32 blocks of row pair 31 alone.  A thread's two blocks never change.
+    // Stores: one instruction stores an even column from lanes with bit 4 clear and an odd column from
+    // the others (and the second instruction the other way round), so that the 32 lanes the LDS serves
+    // together spread over all 32 banks instead of the 16 of one column parity.
+    const bool hi16 = (lane & 16) != 0;
+    int rd[2], rd1[2], pk[2], pkp[2], wa[2][2], wb[2][2];
+    bool act[2];
+#pragma unroll
+    for (int ts = 0; ts < 2; ++ts) {
+        const int j = ts == 0 ? wave : 31 - wave;
+        const int split = 63 - j;
+        const int k = lane < split ? j : 62 - j;
+        const int kp = lane < split ? j + 1 + lane : 63 - j + (lane - split);
+        act[ts] = !(j == 31 && lane >= 32);
+        rd[ts] = 2 * k * EIG_LD + 2 * kp;
+        rd1[ts] = rd[ts] + EIG_LD;
+        asm volatile("" : "+v"(rd1[ts]));      // two 8-byte reads: measured at 7 cycles per wave against 10 for one two-address read
+        pk[ts] = k;
+        pkp[ts] = kp;
+        const int r0 = eig_next_pos(2 * k), r1 = eig_next_pos(2 * k + 1);
+        const int c0 = eig_next_pos(2 * kp), c1 = eig_next_pos(2 * kp + 1);
+        // pairs (x0, x1) = (e00, e01) and (e10, e11): first store takes x0 in the low lanes and x1 in the
+        // high lanes, second store the rest
+        const int w00 = eig_upper(r0, c0), w01 = eig_upper(r0, c1), w10 = eig_upper(r1, c0), w11 = eig_upper(r1, c1);
+        wa[ts][0] = hi16 ? w01 : w00; wb[ts][0] = hi16 ? w00 : w01;
+        wa[ts][1] = hi16 ? w11 : w10; wb[ts][1] = hi16 ? w10 : w11;
+    }
+    // Wave 0, lane k, owns pair k: its diagonal block and its rotation.  The rotation of round n + 1 is
+    // computed DURING round n, so that no wave ever waits for it: after round n the new diagonal
+    // block of pair k holds the old (rotated) diagonal elements of pairs k - 1 and k + 1 -- known to
+    // this wave -- and one off-diagonal element of the block (k - 1, k + 1), which the lane rotates
+    // for itself from the current copy of A (lanes 0, 1 and 63 sit at the ends of the cycle and take
+    // their three elements from the neighbouring places instead).
+    const int lk = lane;
+    const int lrow = lk <= 1 ? 0 : lk == 63 ? 62 : lk - 1;              // row pair of the look-ahead block
+    const int lcol = lk == 0 ? 1 : lk == 63 ? 63 : lk + 1;              // its column pair
+    const int lrd = 2 * lrow * EIG_LD + 2 * lcol;
+    int lrd1 = lrd + EIG_LD;
+    asm volatile("" : "+v"(lrd1));
+    const int dn0 = eig_next_pos(2 * lk), dn1 = eig_next_pos(2 * lk + 1);
+    float ps = 0.f, ptau = 0.f, dE00 = 0.f, dE11 = 0.f, dOff = 0.f;    // pair k: rotation and rotated diagonal block
+    if (wave == 0) __builtin_amdgcn_s_setprio(3);     // its dependent chain is the critical path of every round (740 -> 727 us)
+    if (wave == 0) {
+        const int dg = 2 * lk * EIG_LD + 2 * lk;
+        const float app = A2[dg], apq = A2[dg + 1], aqq = A2[dg + EIG_LD + 1];
+        float tn;
+        jacobi_params(app, aqq, apq, thr_skip, ps, ptau, tn);
+        prm[lk] = make_float2(ps, ptau);
+        dOff = (ps == 0.f) ? apq : 0.f;                    // left as it is when the rotation is skipped
+        dE00 = app - tn * apq;
+        dE11 = aqq + tn * apq;
+    }
+    __syncthreads();
+    // Wave w >= 1 holds rows 9 (w - 1) .. + 8 of V (rows >= 128 are padding), lane k the elements at
+    // positions 2 k and 2 k + 1
+    float vtop[EIGV_ROWS], vbot[EIGV_ROWS];
+    const int vrow0 = (wave - 1) * EIGV_ROWS;
+#pragma unroll
+    for (int i = 0; i < EIGV_ROWS; ++i) {
+        {
+            // lane 0 holds its pair exchanged (position 1 on top)
+            vtop[i] = (wave > 0 && vrow0 + i == (lane == 0 ? 1 : 2 * lane)) ? 1.f : 0.f;
+            vbot[i] = (wave > 0 && vrow0 + i == (lane == 0 ? 0 : 2 * lane + 1)) ? 1.f : 0.f;
+        }
+    }
+
+    // One round: from copy FROM1 of A to the other one; rotations of this round in prm[FROM1].
+    // Rotations are applied as x' = x - s (y + tau x), y' = y + s (x - tau y) with tau = s / (1 + c):
+    // 1 - c is then carried to relative precision, so small angles (c rounding to 1) do not inflate
+    // the column norms of V.
+    auto round_step = [&](auto from1) {
+        constexpr int F = decltype(from1)::value ? 1 : 0;
+        const float* cur = A2 + F * BUF;
+        float* nxt = A2 + (1 - F) * BUF;
+        const float2* pcur = prm + 64 * F;
+        float2* pnext = prm + 64 * (1 - F);
+        if (wave == 0) {
+            // this round's rotated diagonal blocks, at their next positions
+            nxt[dn0 * EIG_LD + dn0] = dE00;
+            nxt[dn1 * EIG_LD + dn1] = dE11;
+            nxt[eig_upper(dn0, dn1)] = dOff;
+            // next round's pair k
+            const float2 ltop = *(const float2*)(cur + lrd), lbot = *(const float2*)(cur + lrd1);
+            const float a00 = ltop.x, a01 = ltop.y, a10 = lbot.x, a11 = lbot.y;
+            const float s1 = lane_from_below(ps, ps), tau1 = lane_from_below(ptau, ptau);      // pair k - 1 (lane 0: its own)
+            const float s2 = lane_from_above(ps, ps), tau2 = lane_from_above(ptau, ptau);      // pair k + 1 (lane 63: its own)
+            const float b00 = a00 - s1 * (a10 + tau1 * a00), b01 = a01 - s1 * (a11 + tau1 * a01);
+            const float b10 = a10 + s1 * (a00 - tau1 * a10), b11 = a11 + s1 * (a01 - tau1 * a11);
+            const float e00 = b00 - s2 * (b01 + tau2 * b00), e01 = b01 + s2 * (b00 - tau2 * b01);
+            const float e11 = b11 + s2 * (b10 - tau2 * b11);
+            const float apq = lk == 1 ? e11 : lk == 63 ? e00 : e01;
+            const float below00 = lane_from_below(dE00, dE00), below11 = lane_from_below(dE11, dE11);
+            const float app = lk == 1 ? below11 : below00;                 // lane 0: its own dE00
+            const float aqq = lane_from_above(dE00, dE11);                 // lane 63: its own dE00
+            float tn;
+            jacobi_params(app, aqq, apq, thr_skip, ps, ptau, tn);
+            pnext[lk] = make_float2(ps, ptau);
+            dOff = (ps == 0.f) ? apq : 0.f;
+            dE00 = app - tn * apq;
+            dE11 = aqq + tn * apq;
+        }
+        float2 pv = make_float2(0.f, 0.f);
+        if (wave != 0) {
+            pv = pcur[lane];
+            if (lane == 0) pv = make_float2(-pv.x, -pv.y);
+        }
+        float a[2][4];
+        float2 p1[2], p2[2];
+#pragma unroll
+        for (int ts = 0; ts < 2; ++ts) {
+            const float2 top = *(const float2*)(cur + rd[ts]), bot = *(const float2*)(cur + rd1[ts]);
+            a[ts][0] = top.x; a[ts][1] = top.y; a[ts][2] = bot.x; a[ts][3] = bot.y;
+            p1[ts] = pcur[pk[ts]];
+            p2[ts] = pcur[pkp[ts]];
+        }
+#pragma unroll
+        for (int ts = 0; ts < 2; ++ts) {
+            const float s1 = p1[ts].x, tau1 = p1[ts].y, s2 = p2[ts].x, tau2 = p2[ts].y;
+            const float a00 = a[ts][0], a01 = a[ts][1], a10 = a[ts][2], a11 = a[ts][3];
+            // rows 2 k, 2 k + 1 : J^T from the left
+            const float b00 = a00 - s1 * (a10 + tau1 * a00), b01 = a01 - s1 * (a11 + tau1 * a01);
+            const float b10 = a10 + s1 * (a00 - tau1 * a10), b11 = a11 + s1 * (a01 - tau1 * a11);
+            // columns 2 k', 2 k' + 1 : J from the right
+            const float e00 = b00 - s2 * (b01 + tau2 * b00), e01 = b01 + s2 * (b00 - tau2 * b01);
+            const float e10 = b10 - s2 * (b11 + tau2 * b10), e11 = b11 + s2 * (b10 - tau2 * b11);
+            const float xa0 = hi16 ? e01 : e00, xb0 = hi16 ? e00 : e01;
+            const float xa1 = hi16 ? e11 : e10, xb1 = hi16 ? e10 : e11;
+            if (act[ts]) { nxt[wa[ts][0]] = xa0; nxt[wb[ts][0]] = xb0; nxt[wa[ts][1]] = xa1; nxt[wb[ts][1]] = xb1; }
+        }
+        if (wave != 0) {                      // V <- V J, then the columns move
+            const bool lane0 = lane == 0;
+#pragma unroll
+            for (int i = 0; i < EIGV_ROWS; ++i) {
+                const float x = vtop[i], y = vbot[i];
+                const float xn = x - pv.x * (y + pv.y * x), yn = y + pv.x * (x - pv.y * y);
+                const float b_dn = lane_from_above(xn, yn);
+                vtop[i] = lane_from_below(b_dn, xn);
+                vbot[i] = lane0 ? yn : b_dn;
+            }
+        }
+        __syncthreads();
+    };
+    // One sweep that starts in copy START1 (and ends in the other one: 127 is odd).
+    auto sweep_from = [&](auto start1) {
+        constexpr bool S1 = decltype(start1)::value;
+#pragma unroll 1
+        for (int round = 0; round < EIG_ROUNDS - 1; round += 2) {
+            round_step(EigBool<S1>{});
+            round_step(EigBool<!S1>{});
+        }
+        round_step(EigBool<S1>{});
+    };
+
+    int sweeps_done = 0;
+    for (int sweep = 0; sweep < EIG_MAX_SWEEPS; ++sweep) {
+        // off-diagonal norm (every index is at its own position between sweeps)
+        const float* cur = A2 + (sweeps_done & 1) * BUF;
+        float off = 0.f;
+        for (int idx = tid; idx < D * D; idx += EIG_THREADS) {
+            int i = idx >> 7, j = idx & 127;
+            float v = cur[i * EIG_LD + j];
+            if (i < j) off = fmaf(2.f * v, v, off);             // only the upper triangle is kept
+        }
+        off = wave_sum(off);
+        if (lane == 0) red[16 + wave] = off;
+        __syncthreads();
+        float off2 = 0.f;
+        for (int w = 0; w < 16; ++w) off2 += red[16 + w];
+        __syncthreads();
+        if (!(off2 > tol2)) break;      // uniform across the block
+        if (sweeps_done & 1) sweep_from(EigBool<true>{});
+        else sweep_from(EigBool<false>{});
+        ++sweeps_done;
+    }
+
+    const float* Af = A2 + (sweeps_done & 1) * BUF;
+    if (tid < D) lam_out[tid] = Af[tid * EIG_LD + tid];
+    if (wave != 0) {
+#pragma unroll
+        for (int i = 0; i < EIGV_ROWS; ++i)
+            if (vrow0 + i < D)
+                *(float2*)(R_out + (size_t)(vrow0 + i) * D + 2 * lane) =
+                    lane == 0 ? make_float2(vbot[i], vtop[i]) : make_float2(vtop[i], vbot[i]);
+    }
+    __syncthreads();
+    return sweeps_done;
+}
+
+// ---------------------------------------------------------------------------
+// Rank, keep-mask and keep_idx; R_r = R[:, keep] and delta_mu = mu - R_r R_r^T mu (Alg. 1 steps 14 to 16), one
+// work-group per matrix; R is staged in LDS (row stride 129) so that the column reads do not go to memory one by one.
+// status NULL: every matrix is solved by Jacobi here.
+constexpr int EIGF_LD = D + 1;
+constexpr int EIGF_THREADS = EIG_THREADS, EIGF_PARTS = EIGF_THREADS / D;
+constexpr size_t EIGF_LDS_BYTES = (size_t)(D * EIGF_LD + EIGF_PARTS * D + 3 * D) * sizeof(float) + D * sizeof(int);
+constexpr size_t EIGF_LDS_ALL = EIGF_LDS_BYTES > EIG_LDS_BYTES ? EIGF_LDS_BYTES : EIG_LDS_BYTES;
+__global__ __launch_bounds__(EIGF_THREADS) void eig_finish(const float* __restrict__ cov, const float* __restrict__ sigma,
+                                                           const int32_t* __restrict__ status, int r, float* R,
+                                                           float* lam, uint8_t* __restrict__ mask_out,
+                                                           int32_t* __restrict__ keep_out,
+                                                           int32_t* __restrict__ sweeps_out,
+                                                           const float* __restrict__ mu_in, float* __restrict__ Rr_out,
+                                                           float* __restrict__ dmu_out)
+{
+    extern __shared__ __attribute__((aligned(16))) float fsm[];
+    const int u = blockIdx.x, tid = threadIdx.x;
+    int sweeps = 1;                           // solved by the reduction
+    if (!status || (status[2 * u] | status[2 * u + 1]) != 0) {
+        sweeps = jacobi_solve(cov + (size_t)u * D * D, sigma ? sigma + (size_t)u * D : nullptr, lam + (size_t)u * D,
+                              R + (size_t)u * D * D, fsm);
+        __threadfence_block();
+        __syncthreads();
+    }
+    if (tid == 0 && sweeps_out) sweeps_out[u] = sweeps;
+    float* Vs = fsm;                          // [128][129]
+    float* part = Vs + D * EIGF_LD;           // [parts][128] partial sums
+    float* sw = part + EIGF_PARTS * D;        // [128] R_r^T mu
+    float* smu = sw + D;                      // [128]
+    int* skeep = (int*)(smu + D);             // [128]
+    float* slam = (float*)(skeep + D);        // [128]
+    const float* V = R + (size_t)u * D * D;
+    for (int idx = tid; idx < D * D / 4; idx += EIGF_THREADS) {
+        const float4 v = *(const float4*)(V + 4 * idx);
+        float* d = Vs + (idx >> 5) * EIGF_LD + 4 * (idx & 31);
+        d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
+    }
+    if (tid < D) smu[tid] = mu_in[(size_t)u * D + tid];
+    if (tid < D) { slam[tid] = lam[(size_t)u * D + tid]; skeep[tid] = 0; }
+    __syncthreads();
+    if (tid < D) {                             // rank by value, ties to the lower column
+        const float lc = slam[tid];
+        int rank = 0;
+        for (int i = 0; i < D; ++i) {
+            const float li = slam[i];
+            rank += (li > lc || (li == lc && i < tid)) ? 1 : 0;
+        }
+        mask_out[(size_t)u * D + tid] = (uint8_t)(rank < r);
+        if (rank < r) {
+            keep_out[(size_t)u * r + rank] = tid;
+            skeep[rank] = tid;
+        }
+    }
+    __syncthreads();
+    for (int idx = tid; idx < D * r; idx += EIGF_THREADS) {
+        int c = idx / r, j = idx - c * r;
+        Rr_out[(size_t)u * D * r + idx] = Vs[c * EIGF_LD + skeep[j]];
+    }
+    const int pt = tid >> 7, x = tid & (D - 1);
+    {                                          // w_j = sum_c V[c][keep_j] mu[c], the rows in EIGF_PARTS ranges
+        float w = 0.f;
+        if (x < r) {
+            const int col = skeep[x];
+            constexpr int RP = D / EIGF_PARTS;
+            for (int c = RP * pt; c < RP * pt + RP; ++c) w = fmaf(Vs[c * EIGF_LD + col], smu[c], w);
+        }
+        part[pt * D + x] = w;
+    }
+    __syncthreads();
+    if (tid < r) {
+        float w = 0.f;
+#pragma unroll
+        for (int k = 0; k < EIGF_PARTS; ++k) w += part[k * D + tid];
+        sw[tid] = w;
+    }
+    __syncthreads();
+    {                                          // delta_mu[c] = mu[c] - sum_j V[c][keep_j] w_j, the kept columns in ranges
+        float pr = 0.f;
+        const int per = (r + EIGF_PARTS - 1) / EIGF_PARTS, j0 = min(pt * per, r), j1 = min(j0 + per, r);
+        for (int j = j0; j < j1; ++j) pr = fmaf(Vs[x * EIGF_LD + skeep[j]], sw[j], pr);
+        part[pt * D + x] = pr;
+    }
+    __syncthreads();
+    if (tid < D) {
+        float pr = 0.f;
+#pragma unroll
+        for (int k = 0; k < EIGF_PARTS; ++k) pr += part[k * D + tid];
+        dmu_out[(size_t)u * D + tid] = smu[tid] - pr;
+    }
+}
+
+__global__ __launch_bounds__(256) void gather_rotation_kernel(int r, const float* __restrict__ R,
+                                                              const int32_t* __restrict__ keep_idx,
+                                                              float* __restrict__ Rr)
+{
+    const int u = blockIdx.x;
+    for (int idx = threadIdx.x; idx < D * r; idx += 256) {
+        int c = idx / r, j = idx - c * r;
+        int col = keep_idx[(size_t)u * r + j];
+        col = min(max(col, 0), D - 1);
+        Rr[(size_t)u * D * r + idx] = R[(size_t)u * D * D + c * D + col];
+    }
+}
+
+// ---------------------------------------------------------------------------
+hipError_t launch_eig(bool plain, int U, const float* cov, const float* sigma, const float* mu, int r, float* R,
+                      float* lam, uint8_t* mask, int32_t* keep_idx, float* Rr, float* dmu, int32_t* sweeps,
+                      void* scratch, int32_t* status, hipStream_t st)
+{
+    double* W = (double*)scratch;
+    hipError_t e;
+    if (!plain) {
+        hipLaunchKernelGGL(eig_tridiag, dim3(U), dim3(TRI_THREADS), 0, st, cov, sigma, W, status);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(eig_tri_vectors, dim3(eig_slices(U)), dim3(256), 0, st, U, W, W, lam, status);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        e = allow_dynamic_lds((const void*)eig_orth_back, OB_LDS_BYTES);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(eig_orth_back, dim3(eig_slices(U)), dim3(256), OB_LDS_BYTES, st, U, W, R, status);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    e = allow_dynamic_lds((const void*)eig_finish, EIGF_LDS_ALL);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(eig_finish, dim3(U), dim3(EIGF_THREADS), EIGF_LDS_ALL, st, cov, sigma,
+                       plain ? (const int32_t*)nullptr : status, r, R, lam, mask,
+                       keep_idx, sweeps, mu, Rr, dmu);
+    return hipGetLastError();
+}
+
+hipError_t launch_gather_rotation(int U, int r, const float* R, const int32_t* keep_idx, float* Rr,
+                                  hipStream_t st)
+{
+    hipLaunchKernelGGL(gather_rotation_kernel, dim3(U), dim3(256), 0, st, r, R, keep_idx, Rr);
+    return hipGetLastError();
+}
+
+}  // namespace rk

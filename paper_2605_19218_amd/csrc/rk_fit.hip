@@ -1,10 +1,8 @@
-// Prefill-side rotation construction (Alg. 1 of the RotateK paper, with the full
-// eigendecomposition of Sec. 3.2 "Query-Weighted PCA" as the solver):
+// Prefill-side rotation construction (Alg. 1 of the RotateK paper):
 //   cov_partial_*   : per token chunk, S = sum x x^T and column sums   (Alg. 1 steps 1-3)
 //   cov_finalize    : mu, C = S - n mu mu^T, reduced over chunks in fp64
-//   eig_jacobi      : C_q = (sigma sigma^T) .* C (step 5 / Eq. 4), all eigenpairs by
-//                     parallel two-sided Jacobi resident in LDS, then the keep-mask,
-//                     R_r and delta_mu (step 15)
+//   subspace_iter   : the Cholesky-based subspace iteration (steps 6-13)
+// The full eigendecomposition is in rk_eig.hip.
 #include <mutex>
 #include <set>
 #include <utility>
@@ -12,9 +10,7 @@
 
 namespace rk {
 
-// Kernels that use more than 64 KB of dynamic LDS need the limit raised once per (device,
-// kernel); launches may come from several host threads and contexts.
-static hipError_t allow_dynamic_lds(const void* kernel, size_t bytes)
+hipError_t allow_dynamic_lds(const void* kernel, size_t bytes)
 {
     static std::mutex mu;
     static std::set<std::pair<int, const void*>> done;
@@ -27,7 +23,6 @@ static hipError_t allow_dynamic_lds(const void* kernel, size_t bytes)
     if (e == hipSuccess) done.insert({dev, kernel});
     return e;
 }
-
 
 // ---------------------------------------------------------------------------
 // Plain covariance partial: 256 threads, thread (ty, tx) owns the 8x8 outputs
@@ -472,487 +467,6 @@ __global__ __launch_bounds__(256) void cov_finalize_tiled(RowsDev rows, int Hkv,
 }
 
 // ---------------------------------------------------------------------------
-// Batched symmetric eigensolver: parallel two-sided Jacobi with a round-robin ordering (a sweep is
-// 127 rounds of 64 disjoint pairs), in three launches.
-//   eig_jacobi_rotations  one 1024-thread work-group per 128x128 matrix iterates on A alone and
-//                         records the 64 rotations (sin, sin / (1 + cos)) of every round;
-//   eig_apply_rotations   replays the recorded rotations on V = I.  Rows of V are independent, so
-//                         this half of the arithmetic leaves the one compute unit that holds A and
-//                         spreads over the chip, four rows per wave, in registers;
-//   eig_finish            gathers R_r and forms delta_mu.
-// Pairs are taken by POSITION: position 2 k and 2 k + 1 form pair k, and after every round the rows
-// and columns move to new positions (position 0 stays, 1 -> 2, even positions move up by two,
-// 126 -> 127, odd positions move down by two): the 127 moving positions form one cycle, every two
-// indices meet exactly once in 127 rounds, and after a sweep every index is back where it started,
-// so eigenvalue c is the final A[c][c] and its vector is V[:, c].  Because the pairing is fixed in
-// position space, every thread reads and writes the same LDS addresses in every round: the rotated
-// 2x2 block is written straight to its next position in a second copy of A (two copies, row stride
-// 130 floats), there is no index arithmetic in the loop, and only the part of A on or above the
-// diagonal (by pair, then by position) is kept: a rotated element is stored once, at (r, c) or (c, r),
-// whichever lies there.  The LDS pipeline is the bound of a round (about five cycles per wave-wide
-// instruction, whatever its width up to 8 bytes per lane), so the loop is written for few LDS
-// instructions: 7 per block.
-constexpr int EIG_THREADS = 1024;
-constexpr int EIG_MAX_SWEEPS = 20;
-constexpr int EIG_ROUNDS = D - 1;
-constexpr int EIG_LD = D + 2;             // row stride of the LDS copies of A (even: a 2x2 block is two 8-byte reads)
-constexpr int EIG_ROT_ROUNDS = EIG_MAX_SWEEPS * EIG_ROUNDS;     // recorded rounds per matrix
-constexpr int EIG_FUSE_V_FROM = 192;      // matrices per call from which V is carried inside the A kernel
-                                          // (measured: 128 matrices 1.29 ms carried / 1.17 ms replayed, 256: 1.41 / 1.53, 512: 2.48 / 3.0)
-constexpr size_t EIG_LDS_BYTES = (size_t)(2 * D * EIG_LD + 4 * 64 + 32 + D) * sizeof(float);
-
-// LDS offset of the kept copy of element (r, c) = (c, r): pairs in ascending order, then positions
-__device__ __forceinline__ constexpr int eig_upper(int r, int c)
-{
-    return ((r >> 1) < (c >> 1) || ((r >> 1) == (c >> 1) && r <= c)) ? r * (D + 2) + c : c * (D + 2) + r;
-}
-
-size_t eig_rotation_bytes(size_t U) { return U * EIG_ROT_ROUNDS * 64 * sizeof(float2); }
-
-// position of a row / column after one round
-__host__ __device__ constexpr int eig_next_pos(int p)
-{
-    return p == 0 ? 0 : p == 1 ? 2 : p == D - 2 ? D - 1 : (p & 1) ? p - 2 : p + 2;
-}
-
-// Rotation that annihilates the (p, q) element: t = tan, s = sin, tau = s / (1 + c).  One square
-// root and hardware reciprocals with a Newton step each: the chain sits between the two barriers of
-// every round, and the IEEE division and square-root sequences are several times as long.
-// (s, tau) is applied as x' = x - s (y + tau x), y' = y + s (x - tau y), which is orthogonal to the
-// accuracy of tau = s / (1 + c) alone, so a last-place error in t only moves the angle.
-__device__ __forceinline__ float rcp_nr(float x)
-{
-    float r = __builtin_amdgcn_rcpf(x);
-    return fmaf(r, fmaf(-x, r, 1.f), r);
-}
-__device__ __forceinline__ void jacobi_params(float app, float aqq, float apq, float thr_skip, float& s, float& tau,
-                                              float& t)
-{
-    s = 0.f; tau = 0.f; t = 0.f;
-    if (fabsf(apq) > thr_skip) {
-        // t = sgn(theta) / (|theta| + sqrt(theta^2 + 1)), theta = (aqq - app) / (2 apq), without forming theta
-        const float al = aqq - app, be = 2.f * apq;
-        const float h = __builtin_amdgcn_sqrtf(fmaf(al, al, be * be));
-        t = (al >= 0.f) ? be * rcp_nr(al + h) : be * rcp_nr(al - h);
-        const float d = fmaf(t, t, 1.f);
-        float c = __builtin_amdgcn_rsqf(d);
-        c = c * fmaf(-0.5f * d * c, c, 1.5f);          // one Newton step on 1/sqrt(d)
-        s = t * c;
-        tau = s * rcp_nr(1.f + c);
-    }
-}
-
-// whole-wave lane shifts by one (data-parallel-primitive moves; the end lane has no source and keeps `keep`)
-__device__ __forceinline__ float lane_from_below(float keep, float v)      // lane i <- lane i - 1; lane 0 keeps `keep`
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, keep), __builtin_bit_cast(int, v),
-                                                                 0x138, 0xf, 0xf, false));
-}
-__device__ __forceinline__ float lane_from_above(float keep, float v)      // lane i <- lane i + 1; lane 63 keeps `keep`
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, keep), __builtin_bit_cast(int, v),
-                                                                 0x130, 0xf, 0xf, false));
-}
-
-template <bool B>
-struct EigBool { static constexpr bool value = B; };
-
-// WITH_V: the rows of V are updated in this kernel as well (waves 1-15, nine rows each, in registers, as
-// in eig_apply_rotations) and R is written at the end; nothing is recorded.  A round is then bound by
-// vector issue (about 2000 cycles instead of 1400), which pays once there are enough matrices to fill
-// the chip: the replay kernel is throughput-bound, this one is not.
-constexpr int EIGV_FUSED_ROWS = 9;
-template <bool WITH_V>
-__global__ __launch_bounds__(EIG_THREADS) void eig_jacobi_rotations(const float* __restrict__ cov,
-                                                                    const float* __restrict__ sigma, int r,
-                                                                    float* __restrict__ lam_out,
-                                                                    uint8_t* __restrict__ mask_out,
-                                                                    int32_t* __restrict__ keep_out,
-                                                                    float2* __restrict__ rot,
-                                                                    int32_t* __restrict__ sweeps_ws,
-                                                                    int32_t* __restrict__ sweeps_out,
-                                                                    float* __restrict__ R_out)
-{
-    extern __shared__ float sm[];
-    float* A2 = sm;                                   // [2][128][129]: the two copies of A
-    float2* prm = (float2*)(A2 + 2 * D * EIG_LD);     // [2][64] (sin, sin / (1 + cos)) of this round and the next
-    float* red = (float*)(prm + 128);                 // [32] reduction scratch
-    float* slam = red + 32;                           // [128]
-    constexpr int BUF = D * EIG_LD;
-
-    const int u = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);          // 16 waves
-    const float* C = cov + (size_t)u * D * D;
-    const float* sg = sigma ? sigma + (size_t)u * D : nullptr;
-    float2* rot_u = rot + (size_t)u * EIG_ROT_ROUNDS * 64;
-
-    // load C_q = sigma_i sigma_j C_ij and ||C_q||_F^2
-    float nrm = 0.f;
-    for (int idx = tid; idx < D * D; idx += EIG_THREADS) {
-        int i = idx >> 7, j = idx & 127;
-        float v = C[idx];
-        if (sg) v *= sg[i] * sg[j];
-        A2[i * EIG_LD + j] = v;
-        nrm = fmaf(v, v, nrm);
-    }
-    nrm = wave_sum(nrm);
-    if (lane == 0) red[wave] = nrm;
-    __syncthreads();
-    float normF2 = 0.f;
-    for (int w = 0; w < 16; ++w) normF2 += red[w];
-    const float normF = sqrtf(normF2);
-    const float thr_skip = 1e-12f * normF;
-    const float tol2 = (2e-8f * 2e-8f) * normF2;
-    __syncthreads();
-
-    // The 2016 blocks above the diagonal as 32 wave-wide tasks, two per wave: task j covers row
-    // pair j (63 - j blocks) in its first lanes and row pair 62 - j (j + 1 blocks) in the rest;
-    // task 31 is the 32 blocks of row pair 31 alone.  A thread's two blocks never change.
-    // Stores: one instruction stores an even column from lanes with bit 4 clear and an odd column from
-    // the others (and the second instruction the other way round), so that the 32 lanes the LDS serves
-    // together spread over all 32 banks instead of the 16 of one column parity.
-    const bool hi16 = (lane & 16) != 0;
-    int rd[2], rd1[2], pk[2], pkp[2], wa[2][2], wb[2][2];
-    bool act[2];
-#pragma unroll
-    for (int ts = 0; ts < 2; ++ts) {
-        const int j = ts == 0 ? wave : 31 - wave;
-        const int split = 63 - j;
-        const int k = lane < split ? j : 62 - j;
-        const int kp = lane < split ? j + 1 + lane : 63 - j + (lane - split);
-        act[ts] = !(j == 31 && lane >= 32);
-        rd[ts] = 2 * k * EIG_LD + 2 * kp;
-        rd1[ts] = rd[ts] + EIG_LD;
-        asm volatile("" : "+v"(rd1[ts]));      // two 8-byte reads: measured at 7 cycles per wave against 10 for one two-address read
-        pk[ts] = k;
-        pkp[ts] = kp;
-        const int r0 = eig_next_pos(2 * k), r1 = eig_next_pos(2 * k + 1);
-        const int c0 = eig_next_pos(2 * kp), c1 = eig_next_pos(2 * kp + 1);
-        // pairs (x0, x1) = (e00, e01) and (e10, e11): first store takes x0 in the low lanes and x1 in the
-        // high lanes, second store the rest
-        const int w00 = eig_upper(r0, c0), w01 = eig_upper(r0, c1), w10 = eig_upper(r1, c0), w11 = eig_upper(r1, c1);
-        wa[ts][0] = hi16 ? w01 : w00; wb[ts][0] = hi16 ? w00 : w01;
-        wa[ts][1] = hi16 ? w11 : w10; wb[ts][1] = hi16 ? w10 : w11;
-    }
-    // Wave 0, lane k, owns pair k: its diagonal block and its rotation.  The rotation of round n + 1 is
-    // computed DURING round n, so that no wave ever waits for it: after round n the new diagonal
-    // block of pair k holds the old (rotated) diagonal elements of pairs k - 1 and k + 1 -- known to
-    // this wave -- and one off-diagonal element of the block (k - 1, k + 1), which the lane rotates
-    // for itself from the current copy of A (lanes 0, 1 and 63 sit at the ends of the cycle and take
-    // their three elements from the neighbouring places instead).
-    const int lk = lane;
-    const int lrow = lk <= 1 ? 0 : lk == 63 ? 62 : lk - 1;              // row pair of the look-ahead block
-    const int lcol = lk == 0 ? 1 : lk == 63 ? 63 : lk + 1;              // its column pair
-    const int lrd = 2 * lrow * EIG_LD + 2 * lcol;
-    int lrd1 = lrd + EIG_LD;
-    asm volatile("" : "+v"(lrd1));
-    const int dn0 = eig_next_pos(2 * lk), dn1 = eig_next_pos(2 * lk + 1);
-    float ps = 0.f, ptau = 0.f, dE00 = 0.f, dE11 = 0.f, dOff = 0.f;    // pair k: rotation and rotated diagonal block
-    if (wave == 0) __builtin_amdgcn_s_setprio(3);     // its dependent chain is the critical path of every round (740 -> 727 us)
-    if (wave == 0) {
-        const int dg = 2 * lk * EIG_LD + 2 * lk;
-        const float app = A2[dg], apq = A2[dg + 1], aqq = A2[dg + EIG_LD + 1];
-        float tn;
-        jacobi_params(app, aqq, apq, thr_skip, ps, ptau, tn);
-        prm[lk] = make_float2(ps, ptau);
-        if (!WITH_V) rot_u[lk] = lk == 0 ? make_float2(-ps, -ptau) : make_float2(ps, ptau);   // pair 0: see eig_apply_rotations
-        dOff = (ps == 0.f) ? apq : 0.f;                    // left as it is when the rotation is skipped
-        dE00 = app - tn * apq;
-        dE11 = aqq + tn * apq;
-    }
-    __syncthreads();
-    // WITH_V: wave w >= 1 holds rows 9 (w - 1) .. + 8 of V (rows >= 128 are padding), lane k the elements at
-    // positions 2 k and 2 k + 1
-    float vtop[EIGV_FUSED_ROWS], vbot[EIGV_FUSED_ROWS];
-    const int vrow0 = (wave - 1) * EIGV_FUSED_ROWS;
-    if (WITH_V) {
-#pragma unroll
-        for (int i = 0; i < EIGV_FUSED_ROWS; ++i) {
-            // lane 0 holds its pair exchanged (position 1 on top): see eig_apply_rotations
-            vtop[i] = (wave > 0 && vrow0 + i == (lane == 0 ? 1 : 2 * lane)) ? 1.f : 0.f;
-            vbot[i] = (wave > 0 && vrow0 + i == (lane == 0 ? 0 : 2 * lane + 1)) ? 1.f : 0.f;
-        }
-    }
-
-    // One round: from copy FROM1 of A to the other one; rotations of this round in prm[FROM1].
-    // Rotations are applied as x' = x - s (y + tau x), y' = y + s (x - tau y) with tau = s / (1 + c):
-    // 1 - c is then carried to relative precision, so small angles (c rounding to 1) do not inflate
-    // the column norms of V.
-    auto round_step = [&](auto from1, int t) {
-        constexpr int F = decltype(from1)::value ? 1 : 0;
-        const float* cur = A2 + F * BUF;
-        float* nxt = A2 + (1 - F) * BUF;
-        const float2* pcur = prm + 64 * F;
-        float2* pnext = prm + 64 * (1 - F);
-        if (wave == 0) {
-            // this round's rotated diagonal blocks, at their next positions
-            nxt[dn0 * EIG_LD + dn0] = dE00;
-            nxt[dn1 * EIG_LD + dn1] = dE11;
-            nxt[eig_upper(dn0, dn1)] = dOff;
-            // next round's pair k
-            const float2 ltop = *(const float2*)(cur + lrd), lbot = *(const float2*)(cur + lrd1);
-            const float a00 = ltop.x, a01 = ltop.y, a10 = lbot.x, a11 = lbot.y;
-            const float s1 = lane_from_below(ps, ps), tau1 = lane_from_below(ptau, ptau);      // pair k - 1 (lane 0: its own)
-            const float s2 = lane_from_above(ps, ps), tau2 = lane_from_above(ptau, ptau);      // pair k + 1 (lane 63: its own)
-            const float b00 = a00 - s1 * (a10 + tau1 * a00), b01 = a01 - s1 * (a11 + tau1 * a01);
-            const float b10 = a10 + s1 * (a00 - tau1 * a10), b11 = a11 + s1 * (a01 - tau1 * a11);
-            const float e00 = b00 - s2 * (b01 + tau2 * b00), e01 = b01 + s2 * (b00 - tau2 * b01);
-            const float e11 = b11 + s2 * (b10 - tau2 * b11);
-            const float apq = lk == 1 ? e11 : lk == 63 ? e00 : e01;
-            const float below00 = lane_from_below(dE00, dE00), below11 = lane_from_below(dE11, dE11);
-            const float app = lk == 1 ? below11 : below00;                 // lane 0: its own dE00
-            const float aqq = lane_from_above(dE00, dE11);                 // lane 63: its own dE00
-            float tn;
-            jacobi_params(app, aqq, apq, thr_skip, ps, ptau, tn);
-            pnext[lk] = make_float2(ps, ptau);
-            if (!WITH_V && t + 1 < EIG_ROT_ROUNDS)
-                rot_u[(size_t)(t + 1) * 64 + lk] = lk == 0 ? make_float2(-ps, -ptau) : make_float2(ps, ptau);
-            dOff = (ps == 0.f) ? apq : 0.f;
-            dE00 = app - tn * apq;
-            dE11 = aqq + tn * apq;
-        }
-        float2 pv = make_float2(0.f, 0.f);
-        if (WITH_V && wave != 0) {
-            pv = pcur[lane];
-            if (lane == 0) pv = make_float2(-pv.x, -pv.y);
-        }
-        float a[2][4];
-        float2 p1[2], p2[2];
-#pragma unroll
-        for (int ts = 0; ts < 2; ++ts) {
-            const float2 top = *(const float2*)(cur + rd[ts]), bot = *(const float2*)(cur + rd1[ts]);
-            a[ts][0] = top.x; a[ts][1] = top.y; a[ts][2] = bot.x; a[ts][3] = bot.y;
-            p1[ts] = pcur[pk[ts]];
-            p2[ts] = pcur[pkp[ts]];
-        }
-#pragma unroll
-        for (int ts = 0; ts < 2; ++ts) {
-            const float s1 = p1[ts].x, tau1 = p1[ts].y, s2 = p2[ts].x, tau2 = p2[ts].y;
-            const float a00 = a[ts][0], a01 = a[ts][1], a10 = a[ts][2], a11 = a[ts][3];
-            // rows 2 k, 2 k + 1 : J^T from the left
-            const float b00 = a00 - s1 * (a10 + tau1 * a00), b01 = a01 - s1 * (a11 + tau1 * a01);
-            const float b10 = a10 + s1 * (a00 - tau1 * a10), b11 = a11 + s1 * (a01 - tau1 * a11);
-            // columns 2 k', 2 k' + 1 : J from the right
-            const float e00 = b00 - s2 * (b01 + tau2 * b00), e01 = b01 + s2 * (b00 - tau2 * b01);
-            const float e10 = b10 - s2 * (b11 + tau2 * b10), e11 = b11 + s2 * (b10 - tau2 * b11);
-            const float xa0 = hi16 ? e01 : e00, xb0 = hi16 ? e00 : e01;
-            const float xa1 = hi16 ? e11 : e10, xb1 = hi16 ? e10 : e11;
-            if (act[ts]) { nxt[wa[ts][0]] = xa0; nxt[wb[ts][0]] = xb0; nxt[wa[ts][1]] = xa1; nxt[wb[ts][1]] = xb1; }
-        }
-        if (WITH_V && wave != 0) {                      // V <- V J, then the columns move (see eig_apply_rotations)
-            const bool lane0 = lane == 0;
-#pragma unroll
-            for (int i = 0; i < EIGV_FUSED_ROWS; ++i) {
-                const float x = vtop[i], y = vbot[i];
-                const float xn = x - pv.x * (y + pv.y * x), yn = y + pv.x * (x - pv.y * y);
-                const float b_dn = lane_from_above(xn, yn);
-                vtop[i] = lane_from_below(b_dn, xn);
-                vbot[i] = lane0 ? yn : b_dn;
-            }
-        }
-        __syncthreads();
-    };
-    // One sweep that starts in copy START1 (and ends in the other one: 127 is odd).
-    auto sweep_from = [&](auto start1, int t0) {
-        constexpr bool S1 = decltype(start1)::value;
-#pragma unroll 1
-        for (int round = 0; round < EIG_ROUNDS - 1; round += 2) {
-            round_step(EigBool<S1>{}, t0 + round);
-            round_step(EigBool<!S1>{}, t0 + round + 1);
-        }
-        round_step(EigBool<S1>{}, t0 + EIG_ROUNDS - 1);
-    };
-
-    int sweeps_done = 0;
-    for (int sweep = 0; sweep < EIG_MAX_SWEEPS; ++sweep) {
-        // off-diagonal norm (every index is at its own position between sweeps)
-        const float* cur = A2 + (sweeps_done & 1) * BUF;
-        float off = 0.f;
-        for (int idx = tid; idx < D * D; idx += EIG_THREADS) {
-            int i = idx >> 7, j = idx & 127;
-            float v = cur[i * EIG_LD + j];
-            if (i < j) off = fmaf(2.f * v, v, off);             // only the upper triangle is kept
-        }
-        off = wave_sum(off);
-        if (lane == 0) red[16 + wave] = off;
-        __syncthreads();
-        float off2 = 0.f;
-        for (int w = 0; w < 16; ++w) off2 += red[16 + w];
-        __syncthreads();
-        if (!(off2 > tol2)) break;      // uniform across the block
-        if (sweeps_done & 1) sweep_from(EigBool<true>{}, sweeps_done * EIG_ROUNDS);
-        else sweep_from(EigBool<false>{}, sweeps_done * EIG_ROUNDS);
-        ++sweeps_done;
-    }
-
-    // ---- eigenvalues, rank, mask (integer logic) -----------------------------
-    const float* Af = A2 + (sweeps_done & 1) * BUF;
-    if (tid == 0) {
-        sweeps_ws[u] = sweeps_done;
-        if (sweeps_out) sweeps_out[u] = sweeps_done;
-    }
-    if (tid < D) slam[tid] = Af[tid * EIG_LD + tid];
-    if (WITH_V && wave != 0) {
-#pragma unroll
-        for (int i = 0; i < EIGV_FUSED_ROWS; ++i)
-            if (vrow0 + i < D)
-                *(float2*)(R_out + (size_t)u * D * D + (size_t)(vrow0 + i) * D + 2 * lane) =
-                    lane == 0 ? make_float2(vbot[i], vtop[i]) : make_float2(vtop[i], vbot[i]);
-    }
-    __syncthreads();
-    if (tid < D) {
-        float lc = slam[tid];
-        int rank = 0;
-        for (int i = 0; i < D; ++i) {
-            float li = slam[i];
-            rank += (li > lc || (li == lc && i < tid)) ? 1 : 0;
-        }
-        lam_out[(size_t)u * D + tid] = lc;
-        mask_out[(size_t)u * D + tid] = (uint8_t)(rank < r);
-        if (rank < r) keep_out[(size_t)u * r + rank] = tid;
-    }
-}
-
-// V <- V J_1 J_2 ... over the recorded rounds, V = I at the start.  Wave = four rows of V; lane k
-// holds the elements at positions 2 k ("top") and 2 k + 1 ("bottom") of each row -- except lane 0,
-// which holds its pair exchanged (position 1 on top, the position 0 that never moves at the bottom;
-// its recorded rotation is stored negated, which is the same rotation with the two roles swapped).
-// A round rotates every lane's pair and then moves the columns to their next positions.  With lane 0
-// exchanged the 127 moving positions form one ring through the registers: up the tops from lane 0 to
-// lane 63, down the bottoms from lane 63 to lane 1, and back into lane 0's top.  That is two whole-wave
-// shifts by one lane (data-parallel-primitive moves, no LDS) -- the bottoms move down, lane 63 taking
-// its own top; the tops move up, lane 0 taking what came down to it -- and one select that puts the
-// fixed element back: 7 vector instructions per row and round.  Grid (8, U), 256 threads.
-constexpr int EIGV_ROWS = 4;
-__global__ __launch_bounds__(256) void eig_apply_rotations(const float2* __restrict__ rot,
-                                                           const int32_t* __restrict__ sweeps_ws,
-                                                           float* __restrict__ R_out)
-{
-    const int u = blockIdx.y;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int row0 = (blockIdx.x * 4 + wave) * EIGV_ROWS;
-    const float2* rot_u = rot + (size_t)u * EIG_ROT_ROUNDS * 64 + lane;
-    const int n_rounds = min(max(sweeps_ws[u], 0), EIG_MAX_SWEEPS) * EIG_ROUNDS;
-    float top[EIGV_ROWS], bot[EIGV_ROWS];
-#pragma unroll
-    for (int i = 0; i < EIGV_ROWS; ++i) {
-        top[i] = (row0 + i == (lane == 0 ? 1 : 2 * lane)) ? 1.f : 0.f;
-        bot[i] = (row0 + i == (lane == 0 ? 0 : 2 * lane + 1)) ? 1.f : 0.f;
-    }
-    const bool lane0 = lane == 0;
-    auto apply = [&](float2 p) {
-#pragma unroll
-        for (int i = 0; i < EIGV_ROWS; ++i) {
-            const float x = top[i], y = bot[i];
-            const float xn = x - p.x * (y + p.y * x), yn = y + p.x * (x - p.y * y);
-            const float b_dn = lane_from_above(xn, yn);      // lane k <- bottom of lane k + 1; lane 63 <- its own top
-            top[i] = lane_from_below(b_dn, xn);              // lane k <- top of lane k - 1; lane 0 <- what came down to it
-            bot[i] = lane0 ? yn : b_dn;                      // position 0 stays
-        }
-    };
-    constexpr int PF = 8;                                  // rounds of rotations requested ahead
-    float2 nx[PF];
-    int t = 0;
-    if (n_rounds >= PF) {
-#pragma unroll
-        for (int i = 0; i < PF; ++i) nx[i] = rot_u[(size_t)i * 64];
-        for (; t + 2 * PF <= n_rounds; t += PF) {
-#pragma unroll
-            for (int i = 0; i < PF; ++i) {
-                const float2 p = nx[i];
-                nx[i] = rot_u[(size_t)(t + PF + i) * 64];
-                apply(p);
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < PF; ++i) apply(nx[i]);
-        t += PF;
-    }
-    for (; t < n_rounds; ++t) apply(rot_u[(size_t)t * 64]);
-#pragma unroll
-    for (int i = 0; i < EIGV_ROWS; ++i)
-        *(float2*)(R_out + (size_t)u * D * D + (size_t)(row0 + i) * D + 2 * lane) =
-            lane == 0 ? make_float2(bot[i], top[i]) : make_float2(top[i], bot[i]);
-}
-
-// R_r = R[:, keep] and delta_mu = mu - R_r R_r^T mu (Alg. 1 step 14 and 16), one work-group per matrix;
-// R is staged in LDS (row stride 129) so that the column reads below do not go to memory one by one.
-constexpr int EIGF_LD = D + 1;
-constexpr int EIGF_THREADS = 1024, EIGF_PARTS = EIGF_THREADS / D;
-constexpr size_t EIGF_LDS_BYTES = (size_t)(D * EIGF_LD + EIGF_PARTS * D + 2 * D) * sizeof(float) + D * sizeof(int);
-__global__ __launch_bounds__(EIGF_THREADS) void eig_finish(int r, const float* __restrict__ R,
-                                                           const int32_t* __restrict__ keep_idx,
-                                                           const float* __restrict__ mu_in, float* __restrict__ Rr_out,
-                                                           float* __restrict__ dmu_out)
-{
-    extern __shared__ float fsm[];
-    float* Vs = fsm;                          // [128][129]
-    float* part = Vs + D * EIGF_LD;           // [parts][128] partial sums
-    float* sw = part + EIGF_PARTS * D;        // [128] R_r^T mu
-    float* smu = sw + D;                      // [128]
-    int* skeep = (int*)(smu + D);             // [128]
-    const int u = blockIdx.x, tid = threadIdx.x;
-    const float* V = R + (size_t)u * D * D;
-    for (int idx = tid; idx < D * D / 4; idx += EIGF_THREADS) {
-        const float4 v = *(const float4*)(V + 4 * idx);
-        float* d = Vs + (idx >> 5) * EIGF_LD + 4 * (idx & 31);
-        d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
-    }
-    if (tid < D) smu[tid] = mu_in[(size_t)u * D + tid];
-    if (tid < r) skeep[tid] = min(max(keep_idx[(size_t)u * r + tid], 0), D - 1);
-    __syncthreads();
-    for (int idx = tid; idx < D * r; idx += EIGF_THREADS) {
-        int c = idx / r, j = idx - c * r;
-        Rr_out[(size_t)u * D * r + idx] = Vs[c * EIGF_LD + skeep[j]];
-    }
-    const int pt = tid >> 7, x = tid & (D - 1);
-    {                                          // w_j = sum_c V[c][keep_j] mu[c], the rows in EIGF_PARTS ranges
-        float w = 0.f;
-        if (x < r) {
-            const int col = skeep[x];
-            constexpr int RP = D / EIGF_PARTS;
-            for (int c = RP * pt; c < RP * pt + RP; ++c) w = fmaf(Vs[c * EIGF_LD + col], smu[c], w);
-        }
-        part[pt * D + x] = w;
-    }
-    __syncthreads();
-    if (tid < r) {
-        float w = 0.f;
-#pragma unroll
-        for (int k = 0; k < EIGF_PARTS; ++k) w += part[k * D + tid];
-        sw[tid] = w;
-    }
-    __syncthreads();
-    {                                          // delta_mu[c] = mu[c] - sum_j V[c][keep_j] w_j, the kept columns in ranges
-        float pr = 0.f;
-        const int per = (r + EIGF_PARTS - 1) / EIGF_PARTS, j0 = min(pt * per, r), j1 = min(j0 + per, r);
-        for (int j = j0; j < j1; ++j) pr = fmaf(Vs[x * EIGF_LD + skeep[j]], sw[j], pr);
-        part[pt * D + x] = pr;
-    }
-    __syncthreads();
-    if (tid < D) {
-        float pr = 0.f;
-#pragma unroll
-        for (int k = 0; k < EIGF_PARTS; ++k) pr += part[k * D + tid];
-        dmu_out[(size_t)u * D + tid] = smu[tid] - pr;
-    }
-}
-
-__global__ __launch_bounds__(256) void gather_rotation_kernel(int r, const float* __restrict__ R,
-                                                              const int32_t* __restrict__ keep_idx,
-                                                              float* __restrict__ Rr)
-{
-    const int u = blockIdx.x;
-    for (int idx = threadIdx.x; idx < D * r; idx += 256) {
-        int c = idx / r, j = idx - c * r;
-        int col = keep_idx[(size_t)u * r + j];
-        col = min(max(col, 0), D - 1);
-        Rr[(size_t)u * D * r + idx] = R[(size_t)u * D * D + c * D + col];
-    }
-}
-
-// ---------------------------------------------------------------------------
 int cov_chunk_tokens(int dtype, bool mfma) { return (mfma && dtype == 1) ? COVM_CHUNK : COV_CHUNK; }
 
 hipError_t launch_cov_partial(int dtype, bool mfma, const RowsDev& rows, int B, int Hkv, int n_chunks,
@@ -1339,38 +853,6 @@ __global__ __launch_bounds__(128) void sigma_window_kernel(const T* __restrict__
     sigma[(size_t)u * D + c] = sqrtf(a0 + a1);
 }
 
-hipError_t launch_eig(int U, const float* cov, const float* sigma, const float* mu, int r, float* R,
-                      float* lam, uint8_t* mask, int32_t* keep_idx, float* Rr, float* dmu, int32_t* sweeps,
-                      void* rotations, int32_t* sweeps_ws, hipStream_t st)
-{
-    // Few matrices: one compute unit each iterates on A and the whole chip replays the rotations on V.
-    // From three quarters of a chip of matrices on, the replay (throughput-bound) costs more than carrying V along.
-    hipError_t e;
-    if (U >= EIG_FUSE_V_FROM) {
-        e = allow_dynamic_lds((const void*)eig_jacobi_rotations<true>, EIG_LDS_BYTES);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(eig_jacobi_rotations<true>, dim3(U), dim3(EIG_THREADS), EIG_LDS_BYTES, st, cov, sigma, r, lam,
-                           mask, keep_idx, (float2*)rotations, sweeps_ws, sweeps, R);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    } else {
-        e = allow_dynamic_lds((const void*)eig_jacobi_rotations<false>, EIG_LDS_BYTES);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(eig_jacobi_rotations<false>, dim3(U), dim3(EIG_THREADS), EIG_LDS_BYTES, st, cov, sigma, r, lam,
-                           mask, keep_idx, (float2*)rotations, sweeps_ws, sweeps, R);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(eig_apply_rotations, dim3(D / (4 * EIGV_ROWS), U), dim3(256), 0, st, (const float2*)rotations,
-                           sweeps_ws, R);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    e = allow_dynamic_lds((const void*)eig_finish, EIGF_LDS_BYTES);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(eig_finish, dim3(U), dim3(EIGF_THREADS), EIGF_LDS_BYTES, st, r, R, keep_idx, mu, Rr, dmu);
-    return hipGetLastError();
-}
-
 int subspace_max_keep() { return SUB_MAX_K; }
 
 hipError_t launch_subspace(int U, const float* cov, const float* sigma, const float* mu, const float* V0, int k,
@@ -1404,13 +886,6 @@ hipError_t launch_sigma_window(int dtype, const void* qw, int64_t sb, int64_t sh
     else
         hipLaunchKernelGGL(sigma_window_kernel<bf16_t>, dim3(B * Hkv), dim3(128), 0, st, (const bf16_t*)qw, sb, sh,
                            sw, Hq, Hkv, W, sigma);
-    return hipGetLastError();
-}
-
-hipError_t launch_gather_rotation(int U, int r, const float* R, const int32_t* keep_idx, float* Rr,
-                                  hipStream_t st)
-{
-    hipLaunchKernelGGL(gather_rotation_kernel, dim3(U), dim3(256), 0, st, r, R, keep_idx, Rr);
     return hipGetLastError();
 }
 

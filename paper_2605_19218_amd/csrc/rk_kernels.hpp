@@ -6,6 +6,10 @@
 
 namespace rk {
 
+// Kernels that use more than 64 KB of dynamic LDS need the limit raised once per (device,
+// kernel); launches may come from several host threads and contexts.
+hipError_t allow_dynamic_lds(const void* kernel, size_t bytes);
+
 // ---- rk_fit.hip ------------------------------------------------------------
 // Partials are [U, n_chunks, d*d] + [U, n_chunks, d]; n_chunks = ceil(tokens / cov_chunk_tokens()).
 constexpr int COV_CHUNK = 512;             // tokens per work-group of the plain kernel (the smaller chunk)
@@ -16,12 +20,6 @@ hipError_t launch_cov_partial(int dtype, bool mfma, const RowsDev& rows, int B, 
 hipError_t launch_cov_finalize(const RowsDev& rows, int B, int Hkv, int n_chunks, bool center, bool tiled,
                                const float* part_S, const float* part_sum, float* cov, float* mu,
                                hipStream_t st);
-// rotations: eig_rotation_bytes(U) bytes of device scratch (the recorded Jacobi rotations),
-// sweeps_ws: U ints of device scratch; sweeps (optional) receives the sweep counts
-size_t eig_rotation_bytes(size_t U);
-hipError_t launch_eig(int U, const float* cov, const float* sigma, const float* mu, int r, float* R,
-                      float* lam, uint8_t* mask, int32_t* keep_idx, float* Rr, float* dmu, int32_t* sweeps,
-                      void* rotations, int32_t* sweeps_ws, hipStream_t st);
 // Cholesky-based subspace iteration (Alg. 1 steps 6-13): V0 [U,d,k] -> Rr [U,d,k], dmu [U,d];
 // status [U] (optional): 0, or t+1 if iteration t met a non-positive pivot.
 int subspace_max_keep();
@@ -30,6 +28,14 @@ hipError_t launch_subspace(int U, const float* cov, const float* sigma, const fl
 // sigma [B,Hkv,d] from a query window [B,Hq,W,d] with element strides (sb, sh, sw)
 hipError_t launch_sigma_window(int dtype, const void* qw, int64_t sb, int64_t sh, int64_t sw, int B, int Hq,
                                int Hkv, int W, float* sigma, hipStream_t st);
+// ---- rk_eig.hip ------------------------------------------------------------
+// scratch: eig_scratch_bytes(U) bytes of device memory, 16-byte aligned; status: 2 U ints of device memory.  sweeps
+// (optional) receives 1 for a matrix solved by the tridiagonal reduction, else the sweeps of the Jacobi solver;
+// plain: Jacobi for every matrix.
+size_t eig_scratch_bytes(size_t U);
+hipError_t launch_eig(bool plain, int U, const float* cov, const float* sigma, const float* mu, int r, float* R,
+                      float* lam, uint8_t* mask, int32_t* keep_idx, float* Rr, float* dmu, int32_t* sweeps,
+                      void* scratch, int32_t* status, hipStream_t st);
 hipError_t launch_gather_rotation(int U, int r, const float* R, const int32_t* keep_idx, float* Rr,
                                   hipStream_t st);
 
