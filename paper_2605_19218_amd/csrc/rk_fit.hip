@@ -827,30 +827,63 @@ __global__ __launch_bounds__(SUB_THREADS) void subspace_iter(const float* __rest
 }
 
 // ---------------------------------------------------------------------------
-// Alg. 1 step 4: sigma_j = ||(Q_W)_{:,j}||_2 over the window of recent queries, pooled
-// over the G query heads that share a KV head.  One block per (b, h_kv), thread =
-// channel; rows are coalesced 256- or 512-byte reads.
-template <typename T>
-__global__ __launch_bounds__(128) void sigma_window_kernel(const T* __restrict__ qw, int64_t sb, int64_t sh,
-                                                           int64_t sw, int Hq, int Hkv, int W,
-                                                           float* __restrict__ sigma)
+// Alg. 1 step 4: sigma_j = ||(Q_W)_{:,j}||_2 over the window of recent queries, pooled over the G query heads that
+// share a KV head.  One 1024-thread work-group per (b, h_kv): a row of 128 channels is read by 128 / VEC lanes, VEC
+// elements (16 bytes where base and strides allow it, else one) each, and the other lanes take other rows, so that a
+// window of 7 x 32 rows is four loads per thread, all out together.  (One thread per channel walking the rows two at a
+// time: 30-51 us for 32 work-groups of 224 rows, a memory round trip for every pair of rows; now 4 us.)
+constexpr int SIG_THREADS = 1024;
+template <typename T, int VEC>
+__global__ __launch_bounds__(SIG_THREADS) void sigma_window_kernel(const T* __restrict__ qw, int64_t sb, int64_t sh,
+                                                                   int64_t sw, int Hq, int Hkv, int W,
+                                                                   float* __restrict__ sigma)
 {
-    const int u = blockIdx.x, b = u / Hkv, hk = u % Hkv, G = Hq / Hkv, c = threadIdx.x;
-    float a0 = 0.f, a1 = 0.f;
-    for (int g = 0; g < G; ++g) {
-        const T* base = qw + (int64_t)b * sb + (int64_t)(hk * G + g) * sh + c;
-        int w = 0;
-        for (; w + 2 <= W; w += 2) {
-            const float x0 = ld_elem(base + (int64_t)w * sw), x1 = ld_elem(base + (int64_t)(w + 1) * sw);
-            a0 = fmaf(x0, x0, a0);
-            a1 = fmaf(x1, x1, a1);
+    constexpr int CG = D / VEC, RG = SIG_THREADS / CG, NF = 4;
+    __shared__ float part[RG][D + 4];
+    const int u = blockIdx.x, b = u / Hkv, hk = u % Hkv, G = Hq / Hkv;
+    const int cg = threadIdx.x % CG, rg = threadIdx.x / CG;
+    const int64_t rows = (int64_t)G * W;
+    const T* base = qw + (int64_t)b * sb + (int64_t)hk * G * sh + cg * VEC;
+    float a[VEC];
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) a[e] = 0.f;
+    for (int64_t n0 = rg; n0 < rows; n0 += NF * RG) {
+        alignas(16) T x[NF][VEC];
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {               // rows past the end are clamped and count for nothing
+            const int64_t n = n0 + f * RG < rows ? n0 + f * RG : rows - 1, g = n / W, w = n - g * W;
+            const T* src = base + g * sh + w * sw;
+            if constexpr (VEC == 1) x[f][0] = *src;
+            else *(uint4*)x[f] = *(const uint4*)src;
         }
-        if (w < W) {
-            const float x0 = ld_elem(base + (int64_t)w * sw);
-            a0 = fmaf(x0, x0, a0);
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            const float keep = n0 + f * RG < rows ? 1.f : 0.f;
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                const float v = keep != 0.f ? ld_elem(&x[f][e]) : 0.f;
+                a[e] = fmaf(v, v, a[e]);
+            }
         }
     }
-    sigma[(size_t)u * D + c] = sqrtf(a0 + a1);
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) part[rg][cg * VEC + e] = a[e];
+    __syncthreads();
+    // the row groups in eight ranges, then the ranges, both in ascending order
+    __shared__ float sums[8][D];
+    {
+        const int c = threadIdx.x & (D - 1), k = threadIdx.x >> 7;
+        float t = 0.f;
+        for (int i = k * RG / 8; i < (k + 1) * RG / 8; ++i) t += part[i][c];
+        sums[k][c] = t;
+    }
+    __syncthreads();
+    if (threadIdx.x < D) {
+        float t = 0.f;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) t += sums[k][threadIdx.x];
+        sigma[(size_t)u * D + threadIdx.x] = sqrtf(t);
+    }
 }
 
 int subspace_max_keep() { return SUB_MAX_K; }
@@ -880,12 +913,18 @@ hipError_t launch_subspace(int U, const float* cov, const float* sigma, const fl
 hipError_t launch_sigma_window(int dtype, const void* qw, int64_t sb, int64_t sh, int64_t sw, int B, int Hq,
                                int Hkv, int W, float* sigma, hipStream_t st)
 {
-    if (dtype == 0)
-        hipLaunchKernelGGL(sigma_window_kernel<float>, dim3(B * Hkv), dim3(128), 0, st, (const float*)qw, sb, sh, sw,
-                           Hq, Hkv, W, sigma);
+    // 16-byte reads need every row on a 16-byte boundary; the entry point takes any base and strides
+    const int64_t es = dtype == 0 ? 4 : 2;
+    const bool vec = (((int64_t)(uintptr_t)qw | sb * es | sh * es | sw * es) & 15) == 0;
+    const dim3 grid(B * Hkv), block(SIG_THREADS);
+    if (dtype == 0 && vec)
+        hipLaunchKernelGGL((sigma_window_kernel<float, 4>), grid, block, 0, st, (const float*)qw, sb, sh, sw, Hq, Hkv, W, sigma);
+    else if (dtype == 0)
+        hipLaunchKernelGGL((sigma_window_kernel<float, 1>), grid, block, 0, st, (const float*)qw, sb, sh, sw, Hq, Hkv, W, sigma);
+    else if (vec)
+        hipLaunchKernelGGL((sigma_window_kernel<bf16_t, 8>), grid, block, 0, st, (const bf16_t*)qw, sb, sh, sw, Hq, Hkv, W, sigma);
     else
-        hipLaunchKernelGGL(sigma_window_kernel<bf16_t>, dim3(B * Hkv), dim3(128), 0, st, (const bf16_t*)qw, sb, sh,
-                           sw, Hq, Hkv, W, sigma);
+        hipLaunchKernelGGL((sigma_window_kernel<bf16_t, 1>), grid, block, 0, st, (const bf16_t*)qw, sb, sh, sw, Hq, Hkv, W, sigma);
     return hipGetLastError();
 }
 
