@@ -96,14 +96,22 @@ RowsDev to_dev(const rk_rows* r)
     return d;
 }
 
-int cov_chunks(int max_tokens) { int n = (max_tokens + COV_CHUNK - 1) / COV_CHUNK; return n < 1 ? 1 : n; }
+// Chunk partials the workspace holds per (b, h_kv): what any choice of kernel needs (the size is given without a
+// context) for any number of rows up to max_tokens (a workspace may be reused for a shorter input, which may take shorter
+// chunks).
+int cov_chunks(const rk_layout* L, int max_tokens)
+{
+    const int n = (max_tokens + COV_CHUNK - 1) / COV_CHUNK, few = cov_short_chunks(L->dtype, L->batch * L->n_kv_heads);
+    const int m = (max_tokens + COV_CHUNK_MIN - 1) / COV_CHUNK_MIN, k = m < few ? m : few;
+    return n > k ? (n < 1 ? 1 : n) : (k < 1 ? 1 : k);
+}
 
 // The covariance partials are dead once the covariance is reduced: the eigensolver's
 // scratch reuses their space (the region is sized for the larger of the two).
 struct FitWs { size_t part_S, part_sum, cov, status, total; };
 FitWs fit_ws(const rk_layout* L, int max_tokens)
 {
-    size_t U = (size_t)L->batch * L->n_kv_heads, nc = (size_t)cov_chunks(max_tokens);
+    size_t U = (size_t)L->batch * L->n_kv_heads, nc = (size_t)cov_chunks(L, max_tokens);
     FitWs w;
     w.part_S = 0;
     size_t first = U * nc * D * D * sizeof(float);
@@ -117,7 +125,7 @@ FitWs fit_ws(const rk_layout* L, int max_tokens)
 
 bool use_mfma_decode(const rk_ctx* ctx, const rk_layout* L)
 {
-    return !(ctx && ctx->force_generic) && decode_mfma_supported(L->dtype, L->keep);
+    return !(ctx && ctx->force_generic) && L->keep >= 1 && L->keep <= D;
 }
 
 rk_status check_text(rk_ctx* ctx, const rk_text* t, bool need_len)
@@ -169,7 +177,8 @@ void decode_plan(const rk_ctx* ctx, const rk_layout* L, int* S_out, int* tiles_o
         // prologue and its partial: measured optimum on short caches and small batches.  Very short
         // caches (under 2K tokens) still gain from up to four splits of 256 tokens or more
         // (32 heads x 1024 tokens: 9.4 us with two splits, 8.2 us with four).
-        const int cap_long = tiles / 4, cap_short = tiles / 2 < 4 ? tiles / 2 : 4;
+        // (fp32 rows are twice as long: 256 tokens there)
+        const int cap_long = mfma && L->dtype == RK_F32 ? tiles / 2 : tiles / 4, cap_short = tiles / 2 < 4 ? tiles / 2 : 4;
         const int cap = cap_long > cap_short ? cap_long : cap_short;
         if (S > cap) S = cap;
     }
@@ -380,7 +389,8 @@ rk_status rk_fit_rotation(rk_ctx* ctx, const rk_layout* L, const rk_rows* keys, 
     hipError_t e = dev.status;
     if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
     const int B = L->batch, Hkv = L->n_kv_heads, U = B * Hkv;
-    const int ct = cov_chunk_tokens(L->dtype, !ctx->force_generic);
+    const bool mfma = !ctx->force_generic;
+    const int ct = cov_chunk_tokens(L->dtype, mfma, U, keys->n_tokens);
     int nc = (keys->n_tokens + ct - 1) / ct;        // never more than the workspace was sized for
     if (nc < 1) nc = 1;
     char* ws = (char*)workspace;
@@ -389,10 +399,9 @@ rk_status rk_fit_rotation(rk_ctx* ctx, const rk_layout* L, const rk_rows* keys, 
     float* cov = out->cov ? out->cov : (float*)(ws + w.cov);
     const RowsDev rows = to_dev(keys);
     hipStream_t st = as_stream(stream);
-    e = launch_cov_partial(L->dtype, !ctx->force_generic, rows, B, Hkv, nc, part_S, part_sum, st);
+    e = launch_cov_partial(L->dtype, mfma, rows, B, Hkv, nc, ct, part_S, part_sum, st);
     if (e != hipSuccess) return hip_fail(ctx, e, "covariance launch");
-    e = launch_cov_finalize(rows, B, Hkv, nc, (flags & RK_FIT_CENTER) != 0, ct == cov_chunk_tokens(RK_BF16, true),
-                            part_S, part_sum, cov, out->mu, st);
+    e = launch_cov_finalize(L->dtype, mfma, rows, B, Hkv, nc, (flags & RK_FIT_CENTER) != 0, part_S, part_sum, cov, out->mu, st);
     if (e != hipSuccess) return hip_fail(ctx, e, "covariance reduction launch");
     e = launch_eig(ctx->force_generic != 0, U, cov, sigma, out->mu, L->keep, out->R, out->eigvals, out->mask, out->keep_idx, out->R_r,
                    out->delta_mu, out->sweeps, ws + w.part_S, (int32_t*)(ws + w.status), st);
@@ -446,7 +455,8 @@ rk_status rk_fit_subspace(rk_ctx* ctx, const rk_layout* L, const rk_rows* keys, 
     hipError_t e = dev.status;
     if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
     const int B = L->batch, Hkv = L->n_kv_heads, U = B * Hkv;
-    const int ct = cov_chunk_tokens(L->dtype, !ctx->force_generic);
+    const bool mfma = !ctx->force_generic;
+    const int ct = cov_chunk_tokens(L->dtype, mfma, U, keys->n_tokens);
     int nc = (keys->n_tokens + ct - 1) / ct;
     if (nc < 1) nc = 1;
     char* ws = (char*)workspace;
@@ -455,10 +465,9 @@ rk_status rk_fit_subspace(rk_ctx* ctx, const rk_layout* L, const rk_rows* keys, 
     float* cov = cov_out ? cov_out : (float*)(ws + w.cov);
     const RowsDev rows = to_dev(keys);
     hipStream_t st = as_stream(stream);
-    e = launch_cov_partial(L->dtype, !ctx->force_generic, rows, B, Hkv, nc, part_S, part_sum, st);
+    e = launch_cov_partial(L->dtype, mfma, rows, B, Hkv, nc, ct, part_S, part_sum, st);
     if (e != hipSuccess) return hip_fail(ctx, e, "covariance launch");
-    e = launch_cov_finalize(rows, B, Hkv, nc, (flags & RK_FIT_CENTER) != 0, ct == cov_chunk_tokens(RK_BF16, true),
-                            part_S, part_sum, cov, mu, st);
+    e = launch_cov_finalize(L->dtype, mfma, rows, B, Hkv, nc, (flags & RK_FIT_CENTER) != 0, part_S, part_sum, cov, mu, st);
     if (e != hipSuccess) return hip_fail(ctx, e, "covariance reduction launch");
     e = launch_subspace(U, cov, sigma, mu, solver->v0, L->keep, solver->iterations, solver->ridge, R_r, delta_mu,
                         status, st);

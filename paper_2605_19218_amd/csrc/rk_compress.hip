@@ -275,6 +275,72 @@ __global__ __launch_bounds__(256, 2) void compress_mfma(RowsDev rows, int Hkv, i
 }
 
 // ---------------------------------------------------------------------------
+// MFMA kernel for fp32 caches: D^T[j, token] = R_r^T . K^T with v_mfma_f32_16x16x4_f32, all in fp32.  The contraction
+// may run over the channels in any order as long as both operands agree: step (i, e) takes channel 16 i + 4 g + e in lane
+// group g, so a lane's four steps of one i are one 16-byte piece of a Key row and one 16-byte LDS read of the
+// fragments of R_r ([jb][i][lane]).  Lane (g, n) ends up with output channels 16 jb + 4 g ..+3 of token n: one 16-byte
+// piece of the packed layout, consecutive lanes writing consecutive pieces.  128 tokens per work-group, two 16-token
+// tiles per wave.  Bound: the fp32 matrix rate (2 R MFMA of 32 cycles per tile), close to the memory time.
+// (32 heads x 2944 tokens, r = 64: 154 us through the plain kernel, whose every output is a 128-step loop over R_r
+// in memory; 25 us here.)
+template <int R>
+__global__ __launch_bounds__(256) void compress_f32(RowsDev rows, int Hkv, int cap, int r, const float* __restrict__ Rr,
+                                                    float* __restrict__ Kp, int32_t* __restrict__ seq_len_out)
+{
+    constexpr int JB = R / 16, TT = 2, TOK = 4 * TT * 16;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    f32x4* frag = (f32x4*)smem_raw;         // [JB][8][64]
+    const int h = blockIdx.y, b = blockIdx.z, u = b * Hkv + h;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, n = lane & 15;
+    const int n_b = min(rows_count(rows, b), cap);
+    if (blockIdx.x == 0 && h == 0 && tid == 0 && seq_len_out) seq_len_out[b] = n_b;
+    const int blk0 = blockIdx.x * TOK;
+    if (blk0 >= n_b) return;
+    const int w0 = blk0 + wave * (TT * 16);
+
+    f32x4 kb[TT][8];
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) {       // rows past the end are read as the last row and never stored
+        const float* row = (const float*)rows.data + rows_offset(rows, b, h, min(w0 + 16 * tt + n, n_b - 1)) + 4 * g;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) kb[tt][i] = __builtin_nontemporal_load((const f32x4*)(row + 16 * i));
+    }
+    const float* Ru = Rr + (size_t)u * D * r;
+    for (int f = tid; f < JB * 8 * 64; f += 256) {
+        const int fl = f & 63, i = (f >> 6) & 7, j = 16 * (f >> 9) + (fl & 15);
+        f32x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float x = Ru[(16 * i + 4 * (fl >> 4) + e) * r + min(j, r - 1)];
+            v[e] = j < r ? x : 0.f;         // columns r .. R - 1: the layout's zero padding
+        }
+        frag[f] = v;
+    }
+    __syncthreads();
+    float* Ku = Kp + (size_t)u * slab_tokens(cap) * R;
+#pragma unroll
+    for (int jb = 0; jb < JB; ++jb) {
+        f32x4 acc[TT];
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) acc[tt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const f32x4 a = frag[(jb * 8 + i) * 64 + lane];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int tt = 0; tt < TT; ++tt)
+                    acc[tt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], kb[tt][i][e], acc[tt], 0, 0, 0);
+        }
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt)
+            if (w0 + 16 * tt + n < n_b)
+                __builtin_nontemporal_store(acc[tt], (f32x4*)(Ku + (size_t)((w0 >> 4) + tt) * (16 * R) +
+                                                              (2 * jb + (g >> 1)) * 128 + n * 8 + 4 * (g & 1)));
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Values -> fragment-major V cache: one block per 32-token block, transposed
 // through LDS; rows past the sequence end inside the last block are zero-filled.
 template <typename T>
@@ -423,6 +489,18 @@ static hipError_t launch_compress_mfma_r(const RowsDev& rows, int B, int Hkv, in
     return launch_compress_mfma_rp<R, 4>(rows, B, Hkv, cap, r, Rr, Kp, seq_len_out, st);
 }
 
+template <int R>
+static hipError_t launch_compress_f32_r(const RowsDev& rows, int B, int Hkv, int cap, int r, const float* Rr, float* Kp,
+                                        int32_t* seq_len_out, hipStream_t st)
+{
+    constexpr size_t lds = (size_t)(R / 16) * 8 * 64 * 16;
+    const hipError_t e = allow_dynamic_lds((const void*)compress_f32<R>, lds);
+    if (e != hipSuccess) return e;
+    const int nblk = rows.n_tokens > 0 ? (rows.n_tokens + 127) / 128 : 1;
+    hipLaunchKernelGGL(compress_f32<R>, dim3(nblk, Hkv, B), dim3(256), lds, st, rows, Hkv, cap, r, Rr, Kp, seq_len_out);
+    return hipGetLastError();
+}
+
 hipError_t launch_compress(int dtype, bool mfma, const RowsDev& rows, int B, int Hkv, int cap, int r,
                            const float* Rr, void* Kp, int32_t* seq_len_out, hipStream_t st)
 {
@@ -437,6 +515,20 @@ hipError_t launch_compress(int dtype, bool mfma, const RowsDev& rows, int B, int
             case 96: return launch_compress_mfma_r<96>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, st);
             case 112: return launch_compress_mfma_r<112>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, st);
             case 128: return launch_compress_mfma_r<128>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, st);
+            default: break;
+        }
+    }
+    if (mfma && dtype == 0) {
+        float* kp = (float*)Kp;
+        switch (keep_padded(r)) {
+            case 16: return launch_compress_f32_r<16>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, st);
+            case 32: return launch_compress_f32_r<32>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, st);
+            case 48: return launch_compress_f32_r<48>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, st);
+            case 64: return launch_compress_f32_r<64>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, st);
+            case 80: return launch_compress_f32_r<80>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, st);
+            case 96: return launch_compress_f32_r<96>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, st);
+            case 112: return launch_compress_f32_r<112>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, st);
+            case 128: return launch_compress_f32_r<128>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, st);
             default: break;
         }
     }

@@ -1233,6 +1233,237 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
 }
 
 // ---------------------------------------------------------------------------
+// MFMA split-K kernel for fp32 caches: the scheme of decode_split_mfma (one work-group per (split, KV head, head group),
+// four waves, two tiles of loads in flight each, the waves' states merged through LDS) on 16-token tiles and
+// v_mfma_f32_16x16x4_f32, everything in fp32.  As in compress_f32 the contraction order follows the layouts: a score
+// step (i, e) takes channel 16 i + 4 g + e in lane group g, so a lane's 16-byte piece of the packed Keys (token n of the
+// tile, channels 16 i + 4 g ..+3) is four operands; the scores of tokens 4 g + ii come out in lane group g, and the
+// 16-byte piece of the Values that holds just those four tokens of channel 16 cb + n is the other operand of four P.V
+// steps.  Partials are folded by decode_merge (or, with a text segment, by decode_text_merge).
+// Bound: HBM; the matrix work (R / 4 + 32 MFMA of 32 cycles per tile) takes a third of that time at one query head per
+// KV head.  (32 heads x 2944 tokens, r = 64: 59 us through the plain kernel, which reads a cache line per lane and score
+// channel, 16 us here.)
+template <int R>
+struct DecTileF32 {
+    f32x4 k[R / 16], v[8];
+};
+
+template <int R>
+__device__ __forceinline__ void load_tile_f32(DecTileF32<R>& T, const float* __restrict__ Ku, const float* __restrict__ Vu,
+                                              int tok0, int lane)
+{
+    const int g = lane >> 4, n = lane & 15;
+    const float* kb = Ku + (size_t)(tok0 >> 4) * (16 * R) + (g >> 1) * 128 + n * 8 + 4 * (g & 1);
+#pragma unroll
+    for (int i = 0; i < R / 16; ++i) T.k[i] = __builtin_nontemporal_load((const f32x4*)(kb + i * 256));
+    const float* vb = Vu + (size_t)(tok0 >> 5) * 4096 + lane * 8 + 4 * ((tok0 >> 4) & 1);
+#pragma unroll
+    for (int cb = 0; cb < 8; ++cb) T.v[cb] = __builtin_nontemporal_load((const f32x4*)(vb + cb * 512));
+}
+
+template <int R>
+__device__ __forceinline__ void compute_tile_f32(DecTileF32<R>& T, float& m_run, float& l_run, f32x4 (&O)[8],
+                                                 const f32x4 (&qb)[R / 16], int tok0, int t1, int g)
+{
+    f32x4 s = (f32x4){0.f, 0.f, 0.f, 0.f}, s2 = s;
+#pragma unroll
+    for (int i = 0; i < R / 16; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; e += 2) {
+            s = __builtin_amdgcn_mfma_f32_16x16x4f32(T.k[i][e], qb[i][e], s, 0, 0, 0);
+            s2 = __builtin_amdgcn_mfma_f32_16x16x4f32(T.k[i][e + 1], qb[i][e + 1], s2, 0, 0, 0);
+        }
+    s += s2;
+    if (tok0 + 16 > t1) {           // rows past the end may hold anything: mask their scores, zero their Values
+#pragma unroll
+        for (int ii = 0; ii < 4; ++ii)
+            if (tok0 + 4 * g + ii >= t1) {
+                s[ii] = NEG_INF;
+#pragma unroll
+                for (int cb = 0; cb < 8; ++cb) T.v[cb][ii] = 0.f;
+            }
+    }
+    float mt = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+    mt = fmaxf(mt, __shfl_xor(mt, 16));
+    mt = fmaxf(mt, __shfl_xor(mt, 32));
+    const float m_new = fmaxf(m_run, mt);
+    const float alpha = exp2f(m_run - m_new);
+    f32x4 p;
+#pragma unroll
+    for (int ii = 0; ii < 4; ++ii) p[ii] = exp2f(s[ii] - m_new);
+    l_run = fmaf(l_run, alpha, (p[0] + p[1]) + (p[2] + p[3]));
+    if (__any(m_new > m_run)) {
+        f32x4 a4;
+#pragma unroll
+        for (int ii = 0; ii < 4; ++ii) a4[ii] = __shfl(alpha, 4 * g + ii);
+#pragma unroll
+        for (int cb = 0; cb < 8; ++cb) O[cb] *= a4;
+    }
+    m_run = m_new;
+#pragma unroll
+    for (int ii = 0; ii < 4; ++ii)
+#pragma unroll
+        for (int cb = 0; cb < 8; ++cb) O[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(p[ii], T.v[cb][ii], O[cb], 0, 0, 0);
+}
+
+template <int R>
+__global__ __launch_bounds__(256, 2) void decode_split_f32(
+    const float* __restrict__ q, const float* __restrict__ Kp, const float* __restrict__ Vc, const float* __restrict__ Rr,
+    const float* __restrict__ dmu, const int32_t* __restrict__ seq_len, int Hq, int Hkv, int cap, int r, int tiles_all,
+    float scale_log2, float* __restrict__ ws_m, float* __restrict__ ws_l, float* __restrict__ ws_acc, int S,
+    float* __restrict__ out, TextAppendDev ta)
+{
+    constexpr int NK = R / 16;                     // 16-channel groups, and 16-column blocks of R_r
+    constexpr int NBW = (NK + 3) / 4;              // blocks of R_r per wave
+    __shared__ f32x4 park[4 * 8 * 64];             // the four waves' O at the end
+    __shared__ __attribute__((aligned(16))) float qt[16][R + 4];
+    __shared__ float sbias[16], sm_m[4][16], sm_l[4][16];
+    const int split = blockIdx.x, b = blockIdx.z;
+    const int G = Hq / Hkv, ngrp = (G + 15) >> 4;
+    const int hk = blockIdx.y / ngrp, grp = blockIdx.y - hk * ngrp;
+    const int h0 = hk * G + grp * 16, Gc = min(16, G - grp * 16), u = b * Hkv + hk;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, n = lane & 15;
+    if (ta.k && split == 0 && blockIdx.y == 0 && wave == 1) text_append_rows<float>(ta, b, Hkv, lane);
+
+    const int seq_raw = seq_len[b];
+    const int tp = tiles_all / S, trem = tiles_all - tp * S;     // the last splits get one 128-token tile more
+    const int t0 = 128 * (split * tp + max(split - (S - trem), 0));
+    const int t1_full = 128 * ((split + 1) * tp + max(split + 1 - (S - trem), 0));
+    const float* Ku = Kp + (size_t)u * slab_tokens(cap) * R;
+    const float* Vu = Vc + (size_t)u * slab_tokens(cap) * D;
+
+    // q~ = q R_r: D[j][h] = sum_c R_r[c][j] q[h][c]; all loads unconditional with clamped indices, see decode_split_mfma
+    const float* Ru = Rr + (size_t)u * D * r;
+    const float* qrow = q + ((size_t)b * Hq + h0 + min(n, Gc - 1)) * D + 4 * g;
+    f32x4 qf[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) qf[i] = *(const f32x4*)(qrow + 16 * i);
+    f32x4 ra[NBW][8], dm[8];
+#pragma unroll
+    for (int bw = 0; bw < NBW; ++bw) {
+        const int col = min(16 * (wave + 4 * bw) + n, r - 1);
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) ra[bw][i][e] = Ru[(16 * i + 4 * g + e) * r + col];
+    }
+    const float* dp = dmu ? dmu + (size_t)u * D : q;             // any readable address when there is no bias
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dm[i][e] = dp[16 * i + 4 * g + e];
+
+    DecTileF32<R> TA, TB;
+    const int tokA = t0 + wave * 16;                             // this wave's tiles: every 64 tokens
+    const int t_spec = min(t1_full, cap);
+    load_tile_f32<R>(TA, Ku, Vu, tokA + 16 <= t_spec ? tokA : 0, lane);
+    const int t1 = min(t1_full, min(max(seq_raw, 0), cap));
+    if (t0 >= t1) {                                              // empty split
+        for (int idx = tid; idx < Gc * D; idx += 256) {
+            const size_t row = (size_t)b * Hq + h0 + (idx >> 7);
+            if (out) out[row * D + (idx & 127)] = 0.f;
+            else {
+                ws_acc[(row * S + split) * D + (idx & 127)] = 0.f;
+                if ((idx & 127) == 0) { ws_m[row * S + split] = NEG_INF; ws_l[row * S + split] = 0.f; }
+            }
+        }
+        return;
+    }
+#pragma unroll
+    for (int bw = 0; bw < NBW; ++bw) {
+        const int jb = wave + 4 * bw;
+        const bool live = 16 * jb + n < r;                       // columns r .. R - 1 read as zero
+        if (jb < NK) {
+            f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(live ? ra[bw][i][e] : 0.f, n < Gc ? qf[i][e] : 0.f, acc, 0, 0, 0);
+            *(f32x4*)&qt[n][16 * jb + 4 * g] = acc * scale_log2;
+        }
+    }
+    if (wave == 0) {                                             // bias b_n = q_n . delta_mu
+        float bp = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) bp = fmaf(qf[i][e], dm[i][e], bp);
+        bp += __shfl_xor(bp, 16);
+        bp += __shfl_xor(bp, 32);
+        if (g == 0) sbias[n] = dmu ? bp * scale_log2 : 0.f;
+    }
+    load_tile_f32<R>(TB, Ku, Vu, tokA + 64 + 16 <= t_spec ? tokA + 64 : 0, lane);
+    __syncthreads();
+    f32x4 qb[NK];
+#pragma unroll
+    for (int i = 0; i < NK; ++i) qb[i] = *(const f32x4*)&qt[n][16 * i + 4 * g];
+
+    float m_run = NEG_INF, l_run = 0.f;
+    f32x4 O[8];
+#pragma unroll
+    for (int cb = 0; cb < 8; ++cb) O[cb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    const int ntiles = (t1 - t0 + 15) >> 4, nk = (ntiles - wave + 3) >> 2;
+    int k = 0;
+    for (; k + 3 < nk; k += 2) {
+        compute_tile_f32<R>(TA, m_run, l_run, O, qb, tokA + 64 * k, t1, g);
+        load_tile_f32<R>(TA, Ku, Vu, tokA + 64 * (k + 2), lane);
+        compute_tile_f32<R>(TB, m_run, l_run, O, qb, tokA + 64 * (k + 1), t1, g);
+        load_tile_f32<R>(TB, Ku, Vu, tokA + 64 * (k + 3), lane);
+    }
+    if (k < nk) {
+        compute_tile_f32<R>(TA, m_run, l_run, O, qb, tokA + 64 * k, t1, g);
+        if (k + 2 < nk) load_tile_f32<R>(TA, Ku, Vu, tokA + 64 * (k + 2), lane);
+    }
+    if (k + 1 < nk) compute_tile_f32<R>(TB, m_run, l_run, O, qb, tokA + 64 * (k + 1), t1, g);
+    if (k + 2 < nk) compute_tile_f32<R>(TA, m_run, l_run, O, qb, tokA + 64 * (k + 2), t1, g);
+
+    // merge the four waves' states, lane to lane (all hold O in one layout: heads 4 g + ii, channel 16 cb + n)
+    l_run += __shfl_xor(l_run, 16);
+    l_run += __shfl_xor(l_run, 32);
+#pragma unroll
+    for (int cb = 0; cb < 8; ++cb) park[(wave * 8 + cb) * 64 + lane] = O[cb];
+    if (g == 0) { sm_m[wave][n] = m_run; sm_l[wave][n] = l_run; }
+    __syncthreads();
+    f32x4 wgt[4], Mh, lh = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ii = 0; ii < 4; ++ii) {
+        const int hh = 4 * g + ii;
+        const float M = fmaxf(fmaxf(sm_m[0][hh], sm_m[1][hh]), fmaxf(sm_m[2][hh], sm_m[3][hh]));
+        Mh[ii] = M;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float x = sm_m[w][hh] > NEG_INF ? exp2f(sm_m[w][hh] - M) : 0.f;
+            wgt[w][ii] = x;
+            lh[ii] = fmaf(sm_l[w][hh], x, lh[ii]);
+        }
+    }
+#pragma unroll
+    for (int c2 = 0; c2 < 2; ++c2) {
+        const int cb = 2 * wave + c2;
+        f32x4 acc = park[cb * 64 + lane] * wgt[0];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) acc += park[(w * 8 + cb) * 64 + lane] * wgt[w];
+#pragma unroll
+        for (int ii = 0; ii < 4; ++ii)
+            if (4 * g + ii < Gc) {
+                const size_t row = (size_t)b * Hq + h0 + 4 * g + ii;
+                if (out) out[row * D + 16 * cb + n] = acc[ii] / lh[ii];
+                else ws_acc[(row * S + split) * D + 16 * cb + n] = acc[ii];
+            }
+    }
+    if (!out && wave == 0 && n == 0) {
+#pragma unroll
+        for (int ii = 0; ii < 4; ++ii)
+            if (4 * g + ii < Gc) {
+                const size_t row = (size_t)b * Hq + h0 + 4 * g + ii;
+                ws_m[row * S + split] = Mh[ii] + sbias[4 * g + ii];
+                ws_l[row * S + split] = lh[ii];
+            }
+    }
+}
+
+// ---------------------------------------------------------------------------
 bool decode_mfma_supported(int dtype, int r) { return dtype == 1 && r >= 1 && r <= 128; }
 
 template <int R>
@@ -1344,6 +1575,21 @@ hipError_t launch_decode(int dtype, bool mfma, int B, int Hq, int Hkv, int cap, 
 #undef RK_CASE
         e = hipGetLastError();
         if (e != hipSuccess || direct || fused_merge) return e;
+    } else if (mfma && dtype == 0) {
+        const dim3 grid(S, Hkv * ((Hq / Hkv + 15) / 16), B);
+        float* o = direct ? (float*)out : nullptr;
+#define RK_CASE(RV)                                                                                              \
+    case RV:                                                                                                     \
+        hipLaunchKernelGGL(decode_split_f32<RV>, grid, dim3(256), 0, st, (const float*)q, (const float*)Kp,       \
+                           (const float*)Vc, Rr, dmu, seq_len, Hq, Hkv, cap, r, tiles_all, sl2, ws_m, ws_l, ws_acc, S, o, ta); \
+        break;
+        switch (keep_padded(r)) {
+            RK_CASE(16) RK_CASE(32) RK_CASE(48) RK_CASE(64) RK_CASE(80) RK_CASE(96) RK_CASE(112) RK_CASE(128)
+            default: return hipErrorInvalidValue;
+        }
+#undef RK_CASE
+        e = hipGetLastError();
+        if (e != hipSuccess || direct) return e;
     } else {
         dim3 grid(S, Hq, B);
         if (dtype == 0)

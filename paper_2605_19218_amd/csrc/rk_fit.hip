@@ -360,6 +360,91 @@ __global__ __launch_bounds__(256) void cov_partial_mfma(RowsDev rows, int Hkv, i
 }
 
 // ---------------------------------------------------------------------------
+// MFMA covariance partial for fp32 Keys: S = K^T K over a chunk with v_mfma_f32_32x32x2_f32.  A 16-byte load of lane
+// (h, m) = (lane / 32, lane % 32) takes channels 4 m ..+3 of token 2 t + h: its four elements are the operands of the four
+// channel blocks, block cbk holding channels ch(cbk, m) = 4 m + cbk, so rows go from memory to the matrix cores as
+// they are, two whole rows per load instruction.  Each wave accumulates the 10 upper-triangular tiles over a quarter of the chunk;
+// the end of the chunk and the partial's layout are those of the bf16 kernel.
+// Bound: the fp32 matrix rate (10 MFMA of 64 cycles per two tokens).  The chunk is 128 tokens while that gives at most two
+// rounds of work-groups (a wave then has 16 steps; 2 x 512 tokens 97 us through the plain kernel, 9 us here), else 512.
+constexpr int COVF_STAGES = 8;             // two-token steps of loads in flight per wave
+
+template <bool GATHER>
+__global__ __launch_bounds__(256) void cov_partial_f32(RowsDev rows, int Hkv, int n_chunks, int chunk_tokens,
+                                                       float* __restrict__ part_S, float* __restrict__ part_sum)
+{
+    const int chunk = blockIdx.x, h = blockIdx.y, b = blockIdx.z, u = b * Hkv + h;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int hh = lane >> 5, m = lane & 31;
+    const int n_b = rows_count(rows, b);
+    const int quarter = chunk_tokens / 4;
+    const int t0 = chunk * chunk_tokens + wave * quarter, t1 = min(t0 + quarter, n_b);
+    const int nst = t1 > t0 ? (t1 - t0 + 1) >> 1 : 0;
+    const float* base = (const float*)rows.data + (int64_t)b * rows.sb + (int64_t)h * rows.sh + 4 * m;
+    const int32_t* list = GATHER ? rows.tok_idx + rows.tok_off[b] : nullptr;
+
+    extern __shared__ __attribute__((aligned(16))) float cov_smem[];
+    f32x4* bufv = (f32x4*)cov_smem;             // parked accumulator groups: [wave][30][lane]
+    float (*ssum)[D] = (float (*)[D])(cov_smem + 4 * 30 * 4 * 64);
+
+    f32x16 acc[10];
+#pragma unroll
+    for (int t = 0; t < 10; ++t)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
+    f32x4 csum = (f32x4){0.f, 0.f, 0.f, 0.f};
+    if (nst > 0) {
+        f32x4 st[COVF_STAGES];
+        // rows past the end are read as the last row and count as zeros
+        auto load = [&](int step) {
+            const int tok = t0 + 2 * step + hh, tc = min(tok, t1 - 1);
+            const f32x4 v = *(const f32x4*)(base + (GATHER ? (int64_t)list[tc] : (int64_t)tc) * rows.st);
+            return tok < t1 ? v : (f32x4){0.f, 0.f, 0.f, 0.f};
+        };
+#pragma unroll
+        for (int s = 0; s < COVF_STAGES; ++s) st[s] = load(s);
+        for (int k = 0; k < nst; k += COVF_STAGES) {
+#pragma unroll
+            for (int s = 0; s < COVF_STAGES; ++s) {
+                const f32x4 x = st[s];          // (steps past the last are zeros)
+                csum += x;
+                int t = 0;
+#pragma unroll
+                for (int bi = 0; bi < 4; ++bi)
+#pragma unroll
+                    for (int bj = bi; bj < 4; ++bj) {
+                        acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[bi], x[bj], acc[t], 0, 0, 0);
+                        ++t;
+                    }
+                st[s] = load(k + s + COVF_STAGES);
+            }
+        }
+    }
+#pragma unroll
+    for (int cbk = 0; cbk < 4; ++cbk) {
+        const float s = csum[cbk] + __shfl_xor(csum[cbk], 32);
+        if (hh == 0) ssum[wave][4 * m + cbk] = s;
+    }
+    switch (wave) {
+    case 0: covm_park<0>(acc, bufv, lane); break;
+    case 1: covm_park<1>(acc, bufv, lane); break;
+    case 2: covm_park<2>(acc, bufv, lane); break;
+    default: covm_park<3>(acc, bufv, lane); break;
+    }
+    __syncthreads();
+    f32x4* S4 = (f32x4*)(part_S + ((size_t)u * n_chunks + chunk) * (D * D));
+    switch (wave) {
+    case 0: covm_fold_store<0>(acc, bufv, lane, S4); break;
+    case 1: covm_fold_store<1>(acc, bufv, lane, S4); break;
+    case 2: covm_fold_store<2>(acc, bufv, lane, S4); break;
+    default: covm_fold_store<3>(acc, bufv, lane, S4); break;
+    }
+    if (tid < D)
+        part_sum[((size_t)u * n_chunks + chunk) * D + tid] = ((ssum[0][tid] + ssum[1][tid]) + ssum[2][tid]) + ssum[3][tid];
+}
+
+// ---------------------------------------------------------------------------
 // Reduce the chunk partials in fp64 and apply the centering correction
 // C = S - n mu mu^T (equal to (K-mu)^T (K-mu)).  grid (8, U): block x covers rows
 // [16x, 16x+16).
@@ -403,11 +488,13 @@ __global__ __launch_bounds__(256) void cov_finalize(RowsDev rows, int Hkv, int n
     }
 }
 
-// Reduction of tile-format partials (written by cov_partial_mfma) in their own order: thread =
+// Reduction of tile-format partials (written by cov_partial_mfma, or by cov_partial_f32 with its own channel order) in
+// their own order: thread =
 // one (tile, i, lane) position, so every load is coalesced across the wave and all chunks of a
 // position are in flight together; the element goes to cov[r][c] and, for off-diagonal tiles
 // and off-diagonal elements of diagonal tiles, cov[c][r] is written by its own position or
 // mirrored here.  Grid (40, U): 10 tiles x 1024 positions per (b, h_kv).
+template <bool F32>
 __global__ __launch_bounds__(256) void cov_finalize_tiled(RowsDev rows, int Hkv, int n_chunks, int center,
                                                           const float* __restrict__ part_S,
                                                           const float* __restrict__ part_sum,
@@ -458,8 +545,8 @@ __global__ __launch_bounds__(256) void cov_finalize_tiled(RowsDev rows, int Hkv,
     while (rem >= 4 - br) { rem -= 4 - br; ++br; }
     const int bc = br + rem;
     const int mr = 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3), mc = lane & 31;
-    const int rch = ((mr & 15) << 3) | (br << 1) | (mr >> 4);
-    const int cch = ((mc & 15) << 3) | (bc << 1) | (mc >> 4);
+    const int rch = F32 ? 4 * mr + br : ((mr & 15) << 3) | (br << 1) | (mr >> 4);
+    const int cch = F32 ? 4 * mc + bc : ((mc & 15) << 3) | (bc << 1) | (mc >> 4);
     if (center) acc -= (double)n_b * (smu[rch] * smu[cch]);
     float* Cu = cov + (size_t)u * D * D;
     Cu[rch * D + cch] = (float)acc;
@@ -467,21 +554,35 @@ __global__ __launch_bounds__(256) void cov_finalize_tiled(RowsDev rows, int Hkv,
 }
 
 // ---------------------------------------------------------------------------
-int cov_chunk_tokens(int dtype, bool mfma) { return (mfma && dtype == 1) ? COVM_CHUNK : COV_CHUNK; }
+// fp32: short chunks while they make at most 512 work-groups (two rounds), see cov_partial_f32
+int cov_short_chunks(int dtype, int units) { return dtype == 0 ? 512 / units : 0; }
+int cov_chunk_tokens(int dtype, bool mfma, int units, int max_tokens)
+{
+    if (!mfma) return COV_CHUNK;
+    if (dtype == 1) return COVM_CHUNK;
+    return (max_tokens + COV_CHUNK_MIN - 1) / COV_CHUNK_MIN <= cov_short_chunks(dtype, units) ? COV_CHUNK_MIN : COV_CHUNK;
+}
 
-hipError_t launch_cov_partial(int dtype, bool mfma, const RowsDev& rows, int B, int Hkv, int n_chunks,
+hipError_t launch_cov_partial(int dtype, bool mfma, const RowsDev& rows, int B, int Hkv, int n_chunks, int chunk_tokens,
                               float* part_S, float* part_sum, hipStream_t st)
 {
     dim3 grid(n_chunks, Hkv, B);
-    if (mfma && dtype == 1) {
-        hipError_t e = allow_dynamic_lds(rows.tok_idx ? (const void*)cov_partial_mfma<true>
-                                                      : (const void*)cov_partial_mfma<false>, COVM_LDS_BYTES);
+    if (mfma) {
+        const void* k = dtype == 1 ? (rows.tok_idx ? (const void*)cov_partial_mfma<true> : (const void*)cov_partial_mfma<false>)
+                                   : (rows.tok_idx ? (const void*)cov_partial_f32<true> : (const void*)cov_partial_f32<false>);
+        hipError_t e = allow_dynamic_lds(k, COVM_LDS_BYTES);
         if (e != hipSuccess) return e;
-        if (rows.tok_idx)
+        if (dtype == 1 && rows.tok_idx)
             hipLaunchKernelGGL(cov_partial_mfma<true>, grid, dim3(256), COVM_LDS_BYTES, st, rows, Hkv, n_chunks, part_S,
                                part_sum);
-        else
+        else if (dtype == 1)
             hipLaunchKernelGGL(cov_partial_mfma<false>, grid, dim3(256), COVM_LDS_BYTES, st, rows, Hkv, n_chunks,
+                               part_S, part_sum);
+        else if (rows.tok_idx)
+            hipLaunchKernelGGL(cov_partial_f32<true>, grid, dim3(256), COVM_LDS_BYTES, st, rows, Hkv, n_chunks, chunk_tokens,
+                               part_S, part_sum);
+        else
+            hipLaunchKernelGGL(cov_partial_f32<false>, grid, dim3(256), COVM_LDS_BYTES, st, rows, Hkv, n_chunks, chunk_tokens,
                                part_S, part_sum);
         return hipGetLastError();
     }
@@ -492,12 +593,14 @@ hipError_t launch_cov_partial(int dtype, bool mfma, const RowsDev& rows, int B, 
     return hipGetLastError();
 }
 
-hipError_t launch_cov_finalize(const RowsDev& rows, int B, int Hkv, int n_chunks, bool center, bool tiled,
-                               const float* part_S, const float* part_sum, float* cov, float* mu,
-                               hipStream_t st)
+hipError_t launch_cov_finalize(int dtype, bool mfma, const RowsDev& rows, int B, int Hkv, int n_chunks, bool center,
+                               const float* part_S, const float* part_sum, float* cov, float* mu, hipStream_t st)
 {
-    if (tiled)
-        hipLaunchKernelGGL(cov_finalize_tiled, dim3(40, B * Hkv), dim3(256), 0, st, rows, Hkv, n_chunks,
+    if (mfma && dtype == 1)
+        hipLaunchKernelGGL(cov_finalize_tiled<false>, dim3(40, B * Hkv), dim3(256), 0, st, rows, Hkv, n_chunks,
+                           center ? 1 : 0, part_S, part_sum, cov, mu);
+    else if (mfma)
+        hipLaunchKernelGGL(cov_finalize_tiled<true>, dim3(40, B * Hkv), dim3(256), 0, st, rows, Hkv, n_chunks,
                            center ? 1 : 0, part_S, part_sum, cov, mu);
     else
         hipLaunchKernelGGL(cov_finalize, dim3(8, B * Hkv), dim3(256), 0, st, rows, Hkv, n_chunks, center ? 1 : 0,

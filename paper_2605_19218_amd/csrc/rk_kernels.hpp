@@ -11,15 +11,16 @@ namespace rk {
 hipError_t allow_dynamic_lds(const void* kernel, size_t bytes);
 
 // ---- rk_fit.hip ------------------------------------------------------------
-// Partials are [U, n_chunks, d*d] + [U, n_chunks, d]; n_chunks = ceil(tokens / cov_chunk_tokens()).
-constexpr int COV_CHUNK = 512;             // tokens per work-group of the plain kernel (the smaller chunk)
-int cov_chunk_tokens(int dtype, bool mfma);
-hipError_t launch_cov_partial(int dtype, bool mfma, const RowsDev& rows, int B, int Hkv, int n_chunks,
+// Partials are [U, n_chunks, d*d] + [U, n_chunks, d]; n_chunks = ceil(tokens / cov_chunk_tokens()).  The matrix-core
+// kernels write them as 10 upper-triangular tiles in register layout.
+constexpr int COV_CHUNK = 512;             // tokens per work-group of the plain kernel, and of the fp32 kernel on long inputs
+constexpr int COV_CHUNK_MIN = 128;         // the smallest chunk (fp32, short inputs)
+int cov_short_chunks(int dtype, int units);           // most chunks of COV_CHUNK_MIN tokens that a call makes per (b, h_kv)
+int cov_chunk_tokens(int dtype, bool mfma, int units, int max_tokens);
+hipError_t launch_cov_partial(int dtype, bool mfma, const RowsDev& rows, int B, int Hkv, int n_chunks, int chunk_tokens,
                               float* part_S, float* part_sum, hipStream_t st);
-// tiled: the partials were written by the MFMA kernel (10 upper-triangular tiles in register layout)
-hipError_t launch_cov_finalize(const RowsDev& rows, int B, int Hkv, int n_chunks, bool center, bool tiled,
-                               const float* part_S, const float* part_sum, float* cov, float* mu,
-                               hipStream_t st);
+hipError_t launch_cov_finalize(int dtype, bool mfma, const RowsDev& rows, int B, int Hkv, int n_chunks, bool center,
+                               const float* part_S, const float* part_sum, float* cov, float* mu, hipStream_t st);
 // Cholesky-based subspace iteration (Alg. 1 steps 6-13): V0 [U,d,k] -> Rr [U,d,k], dmu [U,d];
 // status [U] (optional): 0, or t+1 if iteration t met a non-positive pivot.
 int subspace_max_keep();

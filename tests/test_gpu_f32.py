@@ -1,0 +1,124 @@
+"""fp32 storage on the matrix-core kernels (covariance, compress, decode) at the edges of their tiles, against the
+oracle and against the plain kernels.  fp32 results: max|x - y| / max|y| <= 1e-4, as everywhere in this suite."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2605_19218_amd as rk
+
+from gpu_util import D, DEV, Pipeline, to_dev, to_host
+from test_gpu_parity import check_out, check_packed, layer, oracle_decode, rel_max, run_prefill
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = rk.rk_create(0)
+    yield c
+    rk.rk_destroy(c)
+
+
+# lengths around the two-token steps, the 32-token quarters and 128-token chunks, and (last) the 512-token chunks of a
+# call with more than 512 short ones
+@pytest.mark.parametrize("B,Hkv,L,lengths,center", [
+    (5, 1, 129, [129, 128, 127, 1, 0], True), (3, 2, 97, [97, 33, 2], False), (1, 1, 2000, None, True),
+    (2, 40, 1100, [1100, 513], True),
+])
+def test_covariance(ctx, B, Hkv, L, lengths, center):
+    data = layer(B, Hkv, Hkv, L, "f32", 61, lengths=lengths, mean_shift=3.0)
+    p = Pipeline(ctx, B, Hkv, Hkv, 16, "f32", L)
+    n_dev = None if lengths is None else torch.tensor(lengths, device=DEV, dtype=torch.int32)
+    p.fit(to_dev(data["K"], "f32"), L, center=center, n_dev=n_dev)
+    cov, mu = to_host(p.cov), to_host(p.mu)
+    for b in range(B):
+        n = L if lengths is None else lengths[b]
+        for h in range(0, Hkv, 13):
+            if n == 0:
+                assert not cov[b, h].any() and not mu[b, h].any()
+                continue
+            mu_o, C_o = oracle.mean_scatter(data["K"][b, h, :n], center=center)
+            # centring one row leaves the rounding of the fp32 products, against their own size
+            scale = max(np.abs(C_o).max(), 1e-6 * np.abs(data["K"][b, h, :n]).max() ** 2 * n / 1e-4)
+            assert np.abs(cov[b, h] - C_o).max() <= 1e-4 * scale
+            assert rel_max(mu[b, h], mu_o) <= 1e-4
+            assert np.array_equal(cov[b, h], cov[b, h].T)
+
+
+@pytest.mark.parametrize("r", [1, 16, 37, 64, 100, 128])
+def test_compress_and_token_list(ctx, r):
+    B, Hkv, L = 3, 2, 300
+    lengths = [300, 129, 15]
+    data = layer(B, Hkv, Hkv, L, "f32", 62, lengths=lengths)
+    p = run_prefill(ctx, data, B, Hkv, Hkv, L, r, "f32", lengths=lengths)
+    (Kt, Vc), Rr = p.unpacked(), to_host(p.Rr)
+    for b in range(B):
+        for h in range(Hkv):
+            check_packed(Kt[b, h, :lengths[b]], data["K"][b, h, :lengths[b]].astype(np.float64), Rr[b, h], "f32")
+            assert not Kt[b, h, lengths[b]:].any()
+    idx = np.concatenate([np.arange(0, n, 2) for n in lengths]).astype(np.int32)
+    off = np.concatenate([[0], np.cumsum([(n + 1) // 2 for n in lengths])]).astype(np.int64)
+    p2 = Pipeline(ctx, B, Hkv, Hkv, r, "f32", 160)
+    p2.fit(to_dev(data["K"], "f32"), 150, tok_idx=torch.from_numpy(idx).to(DEV), tok_off=torch.from_numpy(off).to(DEV))
+    p2.compress(to_dev(data["K"], "f32"), 150, V_dev=to_dev(data["V"], "f32"), tok_idx=torch.from_numpy(idx).to(DEV),
+                tok_off=torch.from_numpy(off).to(DEV))
+    Kt, Rr, cov = p2.unpacked()[0], to_host(p2.Rr), to_host(p2.cov)
+    for b in range(B):
+        rows = idx[off[b]:off[b + 1]]
+        check_packed(Kt[b, 1, :rows.size], data["K"][b, 1][rows].astype(np.float64), Rr[b, 1], "f32")
+        assert rel_max(cov[b, 1], oracle.mean_scatter(data["K"][b, 1], tok=rows)[1]) <= 1e-4
+
+
+DECODE = [
+    # B, Hq, Hkv, L, lengths, r, splits
+    (6, 4, 2, 129, [129, 65, 64, 17, 16, 1], 64, 0),
+    (3, 14, 2, 700, [700, 0, 513], 37, 0),          # G = 7, an empty sequence, padded channels
+    (2, 16, 1, 300, [300, 31], 16, 3),              # a full block of 16 heads
+    (1, 20, 1, 260, None, 100, 2),                  # two head groups
+    (1, 2, 2, 4096, None, 128, 2),                  # the steady loop: 32 tiles per wave
+    (2, 2, 1, 1500, [1500, 200], 1, 7),
+    (1, 2, 2, 90, None, 80, 1),                     # a lone split writes the output itself
+]
+
+
+@pytest.mark.parametrize("case", DECODE)
+def test_decode(ctx, case):
+    B, Hq, Hkv, L, lengths, r, splits = case
+    data = layer(B, Hq, Hkv, L, "f32", 63, lengths=lengths, mean_shift=1.5)
+    p = run_prefill(ctx, data, B, Hq, Hkv, L, r, "f32", lengths=lengths)
+    q = to_dev(data["q"], "f32")
+    # rows behind the end hold NaN patterns: they may be read, never used
+    for buf, width in ((p.Kp, (r + 15) // 16 * 16), (p.Vc, D)):
+        tail = torch.full((32, width), float("nan"), device=DEV)
+        flat = buf.view(torch.float32).view(B * Hkv, -1)
+        for b in range(B):
+            n = (lengths or [L] * B)[b]
+            if (n + 31) // 32 * 32 + 32 <= p.cap:
+                for h in range(Hkv):
+                    flat[b * Hkv + h, (n + 31) // 32 * 32 * width:((n + 31) // 32 * 32 + 32) * width] = tail.view(-1)
+    rk.rk_set_option(ctx, rk.RK_OPT_DECODE_SPLITS, splits)
+    try:
+        got, again = p.decode(q).copy(), p.decode(q).copy()
+        nobias = p.decode(q, use_bias=False).copy()
+        rk.rk_set_option(ctx, rk.RK_OPT_FORCE_GENERIC, 1)
+        plain = p.decode(q).copy()
+    finally:
+        rk.rk_set_option(ctx, rk.RK_OPT_FORCE_GENERIC, 0)
+        rk.rk_set_option(ctx, rk.RK_OPT_DECODE_SPLITS, 0)
+    lens = lengths or [L] * B
+    want = oracle_decode(p, data["q"], lens)
+    for x in (got, nobias, plain):
+        check_out(x, want, "f32")
+    assert np.array_equal(got, again)
+    for b in range(B):
+        if lens[b] == 0:
+            assert not got[b].any()
+
+
+def test_workspace_of_a_longer_input_serves_a_shorter_one():
+    """Short inputs take shorter chunks: the workspace size must not fall as the bound on the rows grows."""
+    for H in (1, 4, 32, 300, 600):
+        lay = rk.Layout(1, H, H, 32, rk.RK_F32, 64, 0)
+        sizes = [rk.rk_fit_workspace_size(lay, n) for n in (0, 1, 128, 129, 511, 513, 2048, 4097, 16384, 16385, 65537, 300000)]
+        assert sizes == sorted(sizes)
