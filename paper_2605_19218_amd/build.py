@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librotatek.so")
-SOURCES = ["rk_api.hip", "rk_fit.hip", "rk_eig.hip", "rk_compress.hip", "rk_decode.hip"]
+SOURCES = ["rk_api.hip", "rk_fit.hip", "rk_eig.hip", "rk_subspace.hip", "rk_compress.hip", "rk_decode.hip"]
 
 
 def hipcc() -> str:

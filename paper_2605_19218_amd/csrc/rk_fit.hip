@@ -1,8 +1,8 @@
 // Prefill-side rotation construction (Alg. 1 of the RotateK paper):
 //   cov_partial_*   : per token chunk, S = sum x x^T and column sums   (Alg. 1 steps 1-3)
 //   cov_finalize    : mu, C = S - n mu mu^T, reduced over chunks in fp64
-//   subspace_iter   : the Cholesky-based subspace iteration (steps 6-13)
-// The full eigendecomposition is in rk_eig.hip.
+//   sigma_window    : the query weights (step 4)
+// The full eigendecomposition is in rk_eig.hip, the subspace iteration in rk_subspace.hip.
 #include <mutex>
 #include <set>
 #include <utility>
@@ -609,327 +609,6 @@ hipError_t launch_cov_finalize(int dtype, bool mfma, const RowsDev& rows, int B,
 }
 
 // ---------------------------------------------------------------------------
-// Cholesky-based subspace iteration (Alg. 1 steps 6-13, App. E), one work-group
-// per (b, h_kv), the whole T-step loop in one launch (the paper's four kernels
-// per iteration exist to cut dispatch count; here there is nothing to dispatch).
-// All arithmetic is fp64: the Gram matrix of C_q V has the squared condition of
-// C_q's leading block, which fp32 cannot factor reliably; the fp64 vector rate of
-// this part is half its fp32 rate, which does not matter at this size.
-//
-// LDS (doubles): W [128][ks] (the basis, row stride ks = k padded so that ks % 32 == 8:
-// eight consecutive rows then start 16 banks apart), G packed lower triangle
-// [k(k+1)/2], per-column pivots, sigma, a k-vector, the published pivot row (x2).
-//
-// One iteration:
-//   W <- diag(sigma) C diag(sigma) W   register-tiled: thread = 4 rows x RJ columns
-//                                      (adjacent pairs), C read from global/L2 as
-//                                      float4 broadcasts, in place via registers;
-//   G <- W^T W (lower, 2x2 blocks), rho = eps tr(G) / k added to the diagonal;
-//   right-looking elimination of the stacked matrix [W; G], one barrier per column,
-//   with the rows held in registers (see elim_step): step j uses row j of G (final
-//   since step j-1) to update columns > j,
-//       G[a][b] -= G[a][j] G[j][b] / G[j][j],   W[i][b] -= W[i][j] G[j][b] / G[j][j];
-//   this is the Cholesky factorisation and the solve V L^{-T} at once, with the
-//   square roots deferred: V[i][j] = W[i][j] / sqrt(pivot_j) at the end.
-constexpr int SUB_THREADS = 1024;
-constexpr int SUB_MAX_K = 104;
-
-__host__ __device__ inline int sub_row_stride(int k)
-{
-    int ks = k;
-    while (ks % 32 != 8) ++ks;
-    return ks;
-}
-__host__ __device__ inline size_t sub_lds_bytes(int k)
-{
-    const size_t kpad = 16 * (size_t)((k + 15) / 16) + 8;      // one published pivot row: 4 parts x (columns / 4 + 2)
-    return sizeof(double) * ((size_t)D * sub_row_stride(k) + (size_t)k * (k + 1) / 2 + 2 * (size_t)(k + 4) + D + 2 * kpad + 2);
-}
-
-__device__ __forceinline__ double wave_sum_f64(double v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-}
-
-// 1 / g for g > 0 in double: hardware estimate + two Newton steps (the full IEEE division
-// sequence is four times as long and sits on the critical path of every elimination step)
-__device__ __forceinline__ double fast_rcp_f64(double g)
-{
-    double r = __builtin_amdgcn_rcp(g);
-    double e = fma(-g, r, 1.0);
-    r = fma(r, e, r);
-    e = fma(-g, r, 1.0);
-    return fma(r, e, r);
-}
-
-// Two doubles as one 16-byte LDS access: a true vector type keeps the access whole (the struct double2 is loaded
-// member by member, and the pair then comes back as a two-address 8-byte read, which takes almost twice as long).
-typedef double f64x2 __attribute__((ext_vector_type(2)));
-
-// value of lane (quad base + PJ) for every lane of the quad
-template <int PJ>
-__device__ __forceinline__ double quad_bcast(double v)
-{
-    constexpr int ctrl = PJ | (PJ << 2) | (PJ << 4) | (PJ << 6);       // DPP quad_perm [PJ, PJ, PJ, PJ]
-    int lo = __double2loint(v), hi = __double2hiint(v);
-    lo = __builtin_amdgcn_mov_dpp(lo, ctrl, 0xf, 0xf, true);
-    hi = __builtin_amdgcn_mov_dpp(hi, ctrl, 0xf, 0xf, true);
-    return __hiloint2double(hi, lo);
-}
-
-// Right-looking elimination of the stacked matrix [W; G] with the rows in registers: thread
-// (row, part) holds x[c] = element (row, part + 4 c); rows 0..127 are W, rows 128.. are G (k
-// padded to a multiple of 4 with an identity block, so that every step exists).  Step
-// j = 4 CJ + PJ: the four owners of stack row 128 + j (= row j of G, final since step j-1)
-// publish it scaled by 1 / G[j][j] (the raw pivot goes to slot j), one barrier, then every
-// thread subtracts (its own column-j element) x (the published row) from its columns > j.
-// The code is straight-line per block of four steps; a pivot that is not positive is only
-// recorded, the remaining steps then run on meaningless numbers and the caller discards the
-// result (early exits here made the register allocator spill the whole row).
-// The published row is laid out by part: element (part, c) = column part + 4 c at rb[part * (NCOL + 2) + c],
-// so that a thread's columns are consecutive doubles and two of them come with one 16-byte LDS read
-// (the LDS pipeline issues about one wave-wide instruction per five cycles whatever its width, and a
-// step is little else than these reads); the stride NCOL + 2 keeps the four parts of a wave in
-// different banks and every even c 16-byte aligned.
-template <int NCOL, int CJ, int PJ>
-__device__ __forceinline__ void elim_step(double (&x)[NCOL], double* __restrict__ rb, double* __restrict__ piv,
-                                          int row, int part, int tid, bool& bad)
-{
-    constexpr int j = 4 * CJ + PJ, RS = NCOL + 2;
-    double* rbp = rb + part * RS;
-    if (row == D + j) {
-        const double gjj = quad_bcast<PJ>(x[CJ]);
-        const double rinv = fast_rcp_f64(gjj);
-        if (part == PJ) rbp[CJ] = gjj;
-        else if (part > PJ) rbp[CJ] = x[CJ] * rinv;
-#pragma unroll
-        for (int c = CJ + 1; c < NCOL; ++c) rbp[c] = x[c] * rinv;
-    }
-    __syncthreads();
-    // The wave that holds stack row 128 + j + 1 publishes next: its reads, its update and the reciprocal are the
-    // dependent chain between this barrier and the next one, so it issues ahead of the others.
-    if (__builtin_amdgcn_readfirstlane(tid >> 6) == ((D + j + 1) >> 4)) __builtin_amdgcn_s_setprio(3);
-    else __builtin_amdgcn_s_setprio(0);
-    const double gjj = rb[PJ * RS + CJ];
-    bad = bad || !(gjj > 0.0);
-    if (tid == 0) piv[j] = gjj;
-    const double f = -quad_bcast<PJ>(x[CJ]);
-    if (part > PJ) x[CJ] = fma(f, rbp[CJ], x[CJ]);
-    constexpr int c0 = CJ + 1, c1 = (c0 + 1) & ~1;          // c1: first even column index from c0 on
-    if constexpr ((c0 & 1) != 0 && c0 < NCOL) x[c0] = fma(f, rbp[c0], x[c0]);
-#pragma unroll
-    for (int c = c1; c + 1 < NCOL; c += 2) {
-        const f64x2 v = *(const f64x2*)(rbp + c);
-        x[c] = fma(f, v.x, x[c]);
-        x[c + 1] = fma(f, v.y, x[c + 1]);
-    }
-}
-
-// Blocks CJ, CJ + 1, ... while they exist (4 CJ < kp4, uniform); nested so that the register
-// values only merge once, after the last block.
-template <int NCOL, int CJ>
-__device__ __forceinline__ void elim_block(double (&x)[NCOL], double* __restrict__ rowbuf2, double* __restrict__ piv,
-                                           int kp4, int kpad, int row, int part, int tid, bool& bad)
-{
-    if constexpr (CJ < NCOL) {
-        if (4 * CJ < kp4) {
-            elim_step<NCOL, CJ, 0>(x, rowbuf2, piv, row, part, tid, bad);
-            elim_step<NCOL, CJ, 1>(x, rowbuf2 + kpad, piv, row, part, tid, bad);
-            elim_step<NCOL, CJ, 2>(x, rowbuf2, piv, row, part, tid, bad);
-            elim_step<NCOL, CJ, 3>(x, rowbuf2 + kpad, piv, row, part, tid, bad);
-            elim_block<NCOL, CJ + 1>(x, rowbuf2, piv, kp4, kpad, row, part, tid, bad);
-        }
-    }
-}
-
-template <int KB>
-__global__ __launch_bounds__(SUB_THREADS) void subspace_iter(const float* __restrict__ cov,
-                                                             const float* __restrict__ sigma,
-                                                             const float* __restrict__ mu,
-                                                             const float* __restrict__ V0, int k, int T,
-                                                             double eps, float* __restrict__ Rr,
-                                                             float* __restrict__ dmu, int32_t* __restrict__ status)
-{
-    extern __shared__ __attribute__((aligned(16))) double sub_lds[];
-    const int ks = sub_row_stride(k);
-    double* W = sub_lds;                                  // [D][ks]
-    double* G = W + (size_t)D * ks;                       // packed lower triangle
-    double* piv = G + (size_t)k * (k + 1) / 2;            // [k + 4] (k padded to a multiple of 4)
-    double* tv = piv + k + 4;                             // [k + 4]
-    double* sig = tv + k + 4;                             // [D]
-    double* rowbuf2 = sig + D;                            // [2][kpad]: the published pivot row, double-buffered
-    rowbuf2 += ((uintptr_t)rowbuf2 >> 3) & 1;             // 16-byte aligned (the packed triangle has k (k + 1) / 2 doubles)
-    constexpr int RJ = (KB + 1) / 2;                      // GEMM columns per thread (32 apart)
-    constexpr int NCOL = 4 * KB;                          // elimination: columns per thread (4 apart)
-    const int kpad = 4 * (NCOL + 2);                      // one published row: [part][NCOL + 2]
-
-    const int u = blockIdx.x, tid0 = threadIdx.x, tid = tid0;
-    const float* C = cov + (size_t)u * D * D;
-    const bool weighted = sigma != nullptr;
-
-    for (int idx = tid; idx < D * k; idx += SUB_THREADS) {
-        const int i = idx / k, j = idx - i * k;
-        W[i * ks + j] = (double)V0[(size_t)u * D * k + idx];
-    }
-    for (int idx = tid; idx < D * (ks - k); idx += SUB_THREADS) {     // padding columns: keep them finite
-        const int i = idx / (ks - k), j = k + idx - i * (ks - k);
-        W[i * ks + j] = 0.0;
-    }
-    if (tid < D) sig[tid] = weighted ? (double)sigma[(size_t)u * D + tid] : 1.0;
-    __syncthreads();
-
-    int fail = 0;
-    for (int t = 0; t < T; ++t) {
-        // The thread index is made opaque once per iteration and per phase: otherwise every address and
-        // mask derived from it (a few dozen) is computed before the loop, held in registers through all
-        // phases, and spilled.
-        int tid = tid0;
-        asm volatile("" : "+v"(tid));
-        int ib = tid >> 5, jb = tid & 31;                  // GEMM tile: rows 4 ib .. +3, columns gemm_col(c)
-        // ---- W <- C_q W ----
-        if (weighted) {
-            for (int idx = tid; idx < D * k; idx += SUB_THREADS) {
-                const int i = idx / k, j = idx - i * k;
-                W[i * ks + j] *= sig[i];
-            }
-            __syncthreads();
-        }
-        double acc[4][RJ];
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int c = 0; c < RJ; ++c) acc[r][c] = 0.0;
-        // a thread's columns come in adjacent pairs, 64 c' + 2 jb and + 1 (c' = 0 .. RJ / 2 - 1), so that a pair is
-        // one 16-byte LDS read, plus the single column 64 (RJ / 2) + jb when RJ is odd; reads of surplus threads
-        // are clamped onto the end of the padded row, and they store nothing
-        auto gemm_col = [&](int c) { return c < (RJ & ~1) ? 64 * (c >> 1) + 2 * jb + (c & 1) : 64 * (RJ >> 1) + jb; };
-#pragma unroll 2
-        for (int m0 = 0; m0 < D; m0 += 4) {          // bounded unroll: a full unroll hoists 512 registers of C
-            float4 c4[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) c4[r] = *(const float4*)(C + (size_t)(4 * ib + r) * D + m0);
-#pragma unroll
-            for (int mm = 0; mm < 4; ++mm) {
-                double wv[RJ];
-                const double* wrow = W + (m0 + mm) * ks;
-#pragma unroll
-                for (int c = 0; c + 1 < RJ; c += 2) {
-                    const f64x2 w2 = *(const f64x2*)(wrow + min(gemm_col(c), (ks - 2) & ~1));
-                    wv[c] = w2.x;
-                    wv[c + 1] = w2.y;
-                }
-                if (RJ & 1) wv[RJ - 1] = wrow[min(gemm_col(RJ - 1), ks - 1)];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float cf = mm == 0 ? c4[r].x : mm == 1 ? c4[r].y : mm == 2 ? c4[r].z : c4[r].w;
-                    const double cd = (double)cf;
-#pragma unroll
-                    for (int c = 0; c < RJ; ++c) acc[r][c] = fma(cd, wv[c], acc[r][c]);
-                }
-            }
-        }
-        __syncthreads();                                   // every thread has read the old basis
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int c = 0; c < RJ; ++c)
-                if (gemm_col(c) < k) W[(4 * ib + r) * ks + gemm_col(c)] = acc[r][c] * sig[4 * ib + r];
-        __syncthreads();
-
-        // ---- G <- W^T W (lower triangle, 2 x 2 blocks) ----
-        const int K2 = (k + 1) >> 1, nblk = K2 * (K2 + 1) / 2;
-        for (int blk = tid; blk < nblk; blk += SUB_THREADS) {
-            int pa = (int)((sqrtf(8.f * (float)blk + 1.f) - 1.f) * 0.5f);
-            while (pa * (pa + 1) / 2 > blk) --pa;
-            while ((pa + 1) * (pa + 2) / 2 <= blk) ++pa;
-            const int pb = blk - pa * (pa + 1) / 2;
-            double s00 = 0.0, s01 = 0.0, s10 = 0.0, s11 = 0.0;
-            for (int i = 0; i < D; ++i) {
-                const f64x2 wa = *(const f64x2*)(W + i * ks + 2 * pa);
-                const f64x2 wb = *(const f64x2*)(W + i * ks + 2 * pb);
-                s00 = fma(wa.x, wb.x, s00);
-                s01 = fma(wa.x, wb.y, s01);
-                s10 = fma(wa.y, wb.x, s10);
-                s11 = fma(wa.y, wb.y, s11);
-            }
-            const int a0 = 2 * pa, a1 = a0 + 1, b0 = 2 * pb, b1 = b0 + 1;
-            G[a0 * (a0 + 1) / 2 + b0] = s00;
-            if (pa > pb) G[a0 * (a0 + 1) / 2 + b1] = s01;
-            if (a1 < k) {
-                G[a1 * (a1 + 1) / 2 + b0] = s10;
-                G[a1 * (a1 + 1) / 2 + b1] = s11;          // b1 <= a1 < k
-            }
-        }
-        __syncthreads();
-        if (tid < 64) {                                    // rho = eps tr(G) / k
-            double tr = 0.0;
-            for (int a = tid; a < k; a += 64) tr += G[a * (a + 1) / 2 + a];
-            tr = wave_sum_f64(tr);
-            const double rho = eps * tr / (double)k;
-            for (int a = tid; a < k; a += 64) G[a * (a + 1) / 2 + a] += rho;
-        }
-        __syncthreads();
-
-        // ---- elimination of [W; G] with the rows in registers, one barrier per column ----
-        {
-            asm volatile("" : "+v"(tid));
-            int row = tid >> 2, part = tid & 3;            // stacked row: W rows 0..127, then G rows
-            const int kp4 = (k + 3) & ~3;                  // G padded with an identity block to a multiple of 4
-            double x[NCOL];
-#pragma unroll
-            for (int c = 0; c < NCOL; ++c) {
-                const int bcol = part + 4 * c;
-                double v = 0.0;
-                if (row < D) {
-                    if (bcol < k) v = W[row * ks + bcol];
-                } else if (row < D + kp4) {
-                    const int a = row - D, hi = max(a, bcol), lo = min(a, bcol);
-                    if (hi < k) v = G[hi * (hi + 1) / 2 + lo];
-                    else if (a == bcol) v = 1.0;
-                }
-                x[c] = v;
-            }
-            bool bad = false;
-            elim_block<NCOL, 0>(x, rowbuf2, piv, kp4, kpad, row, part, tid, bad);
-            __builtin_amdgcn_s_setprio(0);
-            if (bad) { fail = t + 1; break; }              // uniform: every thread saw the same pivots
-            __syncthreads();                               // piv complete
-            if (tid < k) tv[tid] = 1.0 / sqrt(piv[tid]);
-            __syncthreads();
-            asm volatile("" : "+v"(row), "+v"(part), "+v"(tid));      // recompute the column numbers: keeping them costs NCOL registers
-            if (row < D) {
-#pragma unroll
-                for (int c = 0; c < NCOL; ++c) {
-                    const int bcol = part + 4 * c;
-                    if (bcol < k) W[row * ks + bcol] = x[c] * tv[bcol];
-                }
-            }
-            __syncthreads();
-        }
-    }
-
-    // ---- outputs: R_k = V, delta_mu = mu - V V^T mu (Alg. 1 steps 14, 16) ----
-    if (tid == 0 && status) status[u] = fail;
-    for (int idx = tid; idx < D * k; idx += SUB_THREADS) {
-        const int i = idx / k, j = idx - i * k;
-        Rr[(size_t)u * D * k + idx] = (float)W[i * ks + j];
-    }
-    if (tid < k) {
-        double a = 0.0;
-        for (int i = 0; i < D; ++i) a = fma(W[i * ks + tid], (double)mu[(size_t)u * D + i], a);
-        tv[tid] = a;
-    }
-    __syncthreads();
-    if (tid < D) {
-        double a = (double)mu[(size_t)u * D + tid];
-        for (int j = 0; j < k; ++j) a = fma(-W[tid * ks + j], tv[j], a);
-        dmu[(size_t)u * D + tid] = (float)a;
-    }
-}
-
-// ---------------------------------------------------------------------------
 // Alg. 1 step 4: sigma_j = ||(Q_W)_{:,j}||_2 over the window of recent queries, pooled over the G query heads that
 // share a KV head.  One 1024-thread work-group per (b, h_kv): a row of 128 channels is read by 128 / VEC lanes, VEC
 // elements (16 bytes where base and strides allow it, else one) each, and the other lanes take other rows, so that a
@@ -987,30 +666,6 @@ __global__ __launch_bounds__(SIG_THREADS) void sigma_window_kernel(const T* __re
         for (int k = 0; k < 8; ++k) t += sums[k][threadIdx.x];
         sigma[(size_t)u * D + threadIdx.x] = sqrtf(t);
     }
-}
-
-int subspace_max_keep() { return SUB_MAX_K; }
-
-hipError_t launch_subspace(int U, const float* cov, const float* sigma, const float* mu, const float* V0, int k,
-                           int T, double eps, float* Rr, float* dmu, int32_t* status, hipStream_t st)
-{
-    if (k < 1 || k > SUB_MAX_K) return hipErrorInvalidValue;
-    const size_t lds = sub_lds_bytes(k);
-    const int kb = (k + 15) / 16;
-#define RK_SUB(KBV)                                                                                          \
-    case KBV: {                                                                                              \
-        hipError_t e = allow_dynamic_lds((const void*)subspace_iter<KBV>, sub_lds_bytes(SUB_MAX_K));         \
-        if (e != hipSuccess) return e;                                                                       \
-        hipLaunchKernelGGL(subspace_iter<KBV>, dim3(U), dim3(SUB_THREADS), lds, st, cov, sigma, mu, V0, k, T, eps, \
-                           Rr, dmu, status);                                                                 \
-        break;                                                                                               \
-    }
-    switch (kb) {
-        RK_SUB(1) RK_SUB(2) RK_SUB(3) RK_SUB(4) RK_SUB(5) RK_SUB(6) RK_SUB(7)
-        default: return hipErrorInvalidValue;
-    }
-#undef RK_SUB
-    return hipGetLastError();
 }
 
 hipError_t launch_sigma_window(int dtype, const void* qw, int64_t sb, int64_t sh, int64_t sw, int B, int Hq,
