@@ -87,7 +87,7 @@ __global__ __launch_bounds__(256) void cov_partial_generic(RowsDev rows, int Hkv
 }
 
 // ---------------------------------------------------------------------------
-// MFMA covariance partial (bf16 Keys): S = K^T K over a 2048-token chunk with
+// MFMA covariance partial (bf16 Keys): S = K^T K over a chunk of 4 TPW tokens (2048, fewer on small inputs) with
 // v_mfma_f32_32x32x16_bf16, contraction index = tokens.  The matrix core wants, per
 // lane, 8 consecutive TOKENS of one channel, while memory holds 8 consecutive
 // CHANNELS of one token.  No LDS staging is used: lane (g2, m) loads the 8x8 block
@@ -96,10 +96,9 @@ __global__ __launch_bounds__(256) void cov_partial_generic(RowsDev rows, int Hkv
 // the even / odd channels of it.  The channel held by MFMA row m of block cbk is
 // therefore ch(cbk, m) = 8 (m % 16) + 2 cbk + m / 16 -- a permutation that is undone
 // when the 128x128 partial is written.  Each wave accumulates the 10 upper-triangular
-// 32x32 tiles for its own 512 tokens (160 accumulator registers); the four waves are
+// 32x32 tiles for its own TPW tokens (160 accumulator registers); the four waves are
 // summed through LDS in a fixed order, each wave folding and storing a quarter.
-constexpr int COVM_TOK_PER_WAVE = 512;
-constexpr int COVM_CHUNK = 4 * COVM_TOK_PER_WAVE;
+constexpr int COVM_CHUNK = 2048;           // the longest chunk
 constexpr int COVM_STAGES = 4;             // 16-token k-steps of loads in flight per wave (16 KB; 3 to 5 time alike, 6 and 8 slower)
 constexpr size_t COVM_LDS_BYTES = (size_t)(4 * 30 * 4 * 64 + 4 * D) * sizeof(float);   // 4 x 30 parked groups + column sums
 
@@ -223,7 +222,7 @@ __device__ __forceinline__ void covm_fold_store(const f32x16 (&acc)[10], const f
     }
 }
 
-template <bool GATHER>
+template <bool GATHER, int TPW>
 __global__ __launch_bounds__(256) void cov_partial_mfma(RowsDev rows, int Hkv, int n_chunks,
                                                         float* __restrict__ part_S, float* __restrict__ part_sum)
 {
@@ -238,8 +237,8 @@ __global__ __launch_bounds__(256) void cov_partial_mfma(RowsDev rows, int Hkv, i
     const int g2 = lane >> 5, m = lane & 31, o = m & 15, par = m >> 4;
     const uint32_t sel = par ? 0x07060302u : 0x05040100u;
     const int n_b = rows_count(rows, b);
-    const int t0 = chunk * COVM_CHUNK, t1 = min(t0 + COVM_CHUNK, n_b);
-    const int tw0 = t0 + wave * COVM_TOK_PER_WAVE, tw1 = min(tw0 + COVM_TOK_PER_WAVE, t1);
+    const int t0 = chunk * (4 * TPW), t1 = min(t0 + 4 * TPW, n_b);
+    const int tw0 = t0 + wave * TPW, tw1 = min(tw0 + TPW, t1);
     const int nks = tw1 > tw0 ? (tw1 - tw0 + 15) >> 4 : 0;      // 16-token k-steps, the last may be partial
     const int nfull = tw1 > tw0 ? (tw1 - tw0) >> 4 : 0;         // k-steps with all 16 tokens valid
     const bf16_t* base = (const bf16_t*)rows.data;
@@ -262,12 +261,12 @@ __global__ __launch_bounds__(256) void cov_partial_mfma(RowsDev rows, int Hkv, i
     if (nks > 0) {
         uint4 st[COVM_STAGES][8];
         int ks = 0;
-        // Every wave owns a 128 KB run of rows at a 128 KB-aligned offset; walking them all from
+        // Every wave owns a run of TPW rows (128 KB of them at a 128 KB-aligned offset); walking them all from
         // the start would keep the 1024 waves of the grid on the same few HBM channels at any
-        // instant.  A full wave (32 k-steps) therefore starts at a wave/chunk/head dependent
+        // instant.  A full wave therefore starts at a wave/chunk/head dependent
         // k-step and wraps around (the sum is order-independent up to fp32 rounding, and the
         // order is still fixed for a given launch shape).
-        constexpr int NKW = COVM_TOK_PER_WAVE / 16;
+        constexpr int NKW = TPW / 16;
         const int shift = (nfull == NKW) ? ((wave * 8 + chunk * 5 + u * 11) & (NKW - 1)) : 0;
 #define KSTEP_TOK(i) (16 * (((i) + shift) & (NKW - 1)))
         if (GATHER && nfull >= 2 * COVM_STAGES) {
@@ -559,8 +558,39 @@ int cov_short_chunks(int dtype, int units) { return dtype == 0 ? 512 / units : 0
 int cov_chunk_tokens(int dtype, bool mfma, int units, int max_tokens)
 {
     if (!mfma) return COV_CHUNK;
-    if (dtype == 1) return COVM_CHUNK;
+    if (dtype == 1) {
+        // Work-groups run one per compute unit (registers and LDS): rounds of 256.  A full chunk of 2048 tokens takes
+        // about 21 us of streaming when all units stream, and a work-group about 5 us beside it (dispatch, end of
+        // chunk); a shorter chunk is taken where it is at least 15 % cheaper so priced (a last chunk that is partly filled
+        // makes the long ones cheaper than this).  32 heads x 2944 tokens: 64 work-groups of 2048 tokens 16.6 us, 192 of
+        // 512 tokens 11.8 us; 8 heads x 1024 tokens 14.6 / 8.5 us; 128 heads x 5000 tokens 39 us (2048) / 42 us (1024).
+        int best = COVM_CHUNK;
+        double least = 1e30;
+        for (int ct = COVM_CHUNK; ct >= COV_CHUNK; ct /= 2) {
+            const double wgs = (double)units * ((max_tokens + ct - 1) / ct), rounds = (double)((int64_t)(wgs + 255) / 256);
+            const double t = rounds * (21.0 * ct / COVM_CHUNK + 5.0);
+            if (t < 0.85 * least) { least = t; best = ct; }
+        }
+        return best;
+    }
     return (max_tokens + COV_CHUNK_MIN - 1) / COV_CHUNK_MIN <= cov_short_chunks(dtype, units) ? COV_CHUNK_MIN : COV_CHUNK;
+}
+
+template <int TPW>
+static hipError_t launch_cov_mfma(const RowsDev& rows, dim3 grid, int Hkv, int n_chunks, float* part_S, float* part_sum,
+                                  hipStream_t st)
+{
+    static_assert(TPW % 16 == 0 && ((TPW / 16) & (TPW / 16 - 1)) == 0, "k-steps of a wave wrap by mask");
+    const hipError_t e = allow_dynamic_lds(rows.tok_idx ? (const void*)cov_partial_mfma<true, TPW>
+                                                        : (const void*)cov_partial_mfma<false, TPW>, COVM_LDS_BYTES);
+    if (e != hipSuccess) return e;
+    if (rows.tok_idx)
+        hipLaunchKernelGGL((cov_partial_mfma<true, TPW>), grid, dim3(256), COVM_LDS_BYTES, st, rows, Hkv, n_chunks, part_S,
+                           part_sum);
+    else
+        hipLaunchKernelGGL((cov_partial_mfma<false, TPW>), grid, dim3(256), COVM_LDS_BYTES, st, rows, Hkv, n_chunks, part_S,
+                           part_sum);
+    return hipGetLastError();
 }
 
 hipError_t launch_cov_partial(int dtype, bool mfma, const RowsDev& rows, int B, int Hkv, int n_chunks, int chunk_tokens,
@@ -568,17 +598,15 @@ hipError_t launch_cov_partial(int dtype, bool mfma, const RowsDev& rows, int B, 
 {
     dim3 grid(n_chunks, Hkv, B);
     if (mfma) {
-        const void* k = dtype == 1 ? (rows.tok_idx ? (const void*)cov_partial_mfma<true> : (const void*)cov_partial_mfma<false>)
-                                   : (rows.tok_idx ? (const void*)cov_partial_f32<true> : (const void*)cov_partial_f32<false>);
-        hipError_t e = allow_dynamic_lds(k, COVM_LDS_BYTES);
+        if (dtype == 1) {
+            if (chunk_tokens == 512) return launch_cov_mfma<128>(rows, grid, Hkv, n_chunks, part_S, part_sum, st);
+            if (chunk_tokens == 1024) return launch_cov_mfma<256>(rows, grid, Hkv, n_chunks, part_S, part_sum, st);
+            return launch_cov_mfma<512>(rows, grid, Hkv, n_chunks, part_S, part_sum, st);
+        }
+        hipError_t e = allow_dynamic_lds(rows.tok_idx ? (const void*)cov_partial_f32<true> : (const void*)cov_partial_f32<false>,
+                                         COVM_LDS_BYTES);
         if (e != hipSuccess) return e;
-        if (dtype == 1 && rows.tok_idx)
-            hipLaunchKernelGGL(cov_partial_mfma<true>, grid, dim3(256), COVM_LDS_BYTES, st, rows, Hkv, n_chunks, part_S,
-                               part_sum);
-        else if (dtype == 1)
-            hipLaunchKernelGGL(cov_partial_mfma<false>, grid, dim3(256), COVM_LDS_BYTES, st, rows, Hkv, n_chunks,
-                               part_S, part_sum);
-        else if (rows.tok_idx)
+        if (rows.tok_idx)
             hipLaunchKernelGGL(cov_partial_f32<true>, grid, dim3(256), COVM_LDS_BYTES, st, rows, Hkv, n_chunks, chunk_tokens,
                                part_S, part_sum);
         else
