@@ -101,7 +101,7 @@ RowsDev to_dev(const rk_rows* r)
 // chunks).
 int cov_chunks(const rk_layout* L, int max_tokens)
 {
-    const int n = (max_tokens + COV_CHUNK - 1) / COV_CHUNK, few = cov_short_chunks(L->dtype, L->batch * L->n_kv_heads);
+    const int n = (max_tokens + COV_CHUNK - 1) / COV_CHUNK, few = cov_short_chunks(L->dtype, (int64_t)L->batch * L->n_kv_heads);
     const int m = (max_tokens + COV_CHUNK_MIN - 1) / COV_CHUNK_MIN, k = m < few ? m : few;
     return n > k ? (n < 1 ? 1 : n) : (k < 1 ? 1 : k);
 }

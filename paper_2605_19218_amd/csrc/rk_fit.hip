@@ -554,8 +554,8 @@ __global__ __launch_bounds__(256) void cov_finalize_tiled(RowsDev rows, int Hkv,
 
 // ---------------------------------------------------------------------------
 // fp32: short chunks while they make at most 512 work-groups (two rounds), see cov_partial_f32
-int cov_short_chunks(int dtype, int units) { return dtype == 0 ? 512 / units : 0; }
-int cov_chunk_tokens(int dtype, bool mfma, int units, int max_tokens)
+int cov_short_chunks(int dtype, int64_t units) { return dtype == 0 ? (int)(512 / units) : 0; }
+int cov_chunk_tokens(int dtype, bool mfma, int64_t units, int max_tokens)
 {
     if (!mfma) return COV_CHUNK;
     if (dtype == 1) {
