@@ -335,10 +335,9 @@ rk_status rk_append_decode_attn(rk_ctx* ctx, const rk_layout* L, const void* k_n
  * P [V_vis; V_pt].  The bias therefore matters here: it shifts the visual
  * scores against the text scores.  Either segment may be empty per sequence;
  * both empty yields zeros.  On the matrix-core path the text attention runs in
- * extra work-groups of the split-K launch, in slices of about 512 rows that
- * each leave a partial of their own, and visual and text partials are folded
- * alike, inside that launch where rk_decode_attn folds its own, else by the
- * merge kernel; with fp32 storage or the plain kernels
+ * the split-K launch: in splits of its own while compute units are left over, else
+ * every split takes a share of the text rows in front of its share of the cache;
+ * the partials are folded as rk_decode_attn's.  With fp32 storage or the plain kernels
  * the second kernel runs the text attention itself and then folds the visual
  * partials (the fusion App. C describes).  Same workspace as rk_decode_attn.
  * Errors: as rk_decode_attn, plus INVALID_ARG for a malformed `text`

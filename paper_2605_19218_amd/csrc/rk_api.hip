@@ -188,6 +188,23 @@ void decode_plan(const rk_ctx* ctx, const rk_layout* L, int* S_out, int* tiles_o
     *tiles_out = tiles;
 }
 
+// Splits of a dual decode (bf16 matrix-core kernels) that take text rows alone, next to the S of the cache: while compute
+// units are left over, one per 128 rows (a 32-row tile for each wave).  With the device full there are none and every
+// split takes a share of the text in front of its share of the cache.  Measured: 32 heads, 2880 tokens (S = 5 of 8 possible)
+// and 64 text rows 14 us shared, 12 us with a split of their own; 32 units x 16384 tokens (S = 8) and 1024 rows 39 us shared,
+// 45 us in work-groups of their own.
+int text_splits(const rk_ctx* ctx, const rk_layout* L, int S, int text_rows)
+{
+    if (ctx && ctx->decode_splits > 0) return 0;
+    const int G = L->n_q_heads / L->n_kv_heads;
+    const long units = (long)L->batch * L->n_kv_heads * ((G + 15) / 16);
+    long left = (ctx ? ctx->n_cu : 256) / units - S;
+    const int rows128 = (int)(((int64_t)text_rows + 127) / 128);
+    if (left > rows128) left = rows128;
+    if (left > DECODE_TEXT_SPLITS_MAX) left = DECODE_TEXT_SPLITS_MAX;
+    return left > 0 ? (int)left : 0;
+}
+
 hipStream_t as_stream(void* s) { return (hipStream_t)s; }
 
 // Makes `device` current for the duration of a call and puts the caller's device back
@@ -310,8 +327,8 @@ size_t rk_decode_workspace_size(const rk_ctx* ctx, const rk_layout* L)
     if (check_layout(nullptr, L) != RK_OK) return 0;
     int S, tiles;
     decode_plan(ctx, L, &S, &tiles);
-    // (m, l, acc[d]) per split and per text slice of the dual path, plus one score per row for a fused append
-    return align_up((size_t)L->batch * L->n_q_heads * ((size_t)(S + DECODE_TEXT_SLICES_MAX) * (D + 2) + 1) * sizeof(float), 256);
+    // (m, l, acc[d]) per split, for the dual path's plan too, plus one score per row for a fused append
+    return align_up((size_t)L->batch * L->n_q_heads * ((size_t)(S + DECODE_TEXT_SPLITS_MAX) * (D + 2) + 1) * sizeof(float), 256);
 }
 
 rk_status rk_decode_plan(const rk_ctx* ctx, const rk_layout* L, int32_t* n_splits, int32_t* tokens_per_split)
@@ -598,9 +615,10 @@ static rk_status decode_common(rk_ctx* ctx, const rk_layout* L, const void* q, c
     if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
     int S, tiles;
     decode_plan(ctx, L, &S, &tiles);
+    const int St = text && L->dtype == RK_BF16 && use_mfma_decode(ctx, L) ? text_splits(ctx, L, S, td.max_len) : 0;
     const float sc = scale > 0.f ? scale : 1.0f / sqrtf((float)L->head_dim);
     e = launch_decode(L->dtype, use_mfma_decode(ctx, L), L->batch, L->n_q_heads, L->n_kv_heads, L->capacity,
-                      L->keep, S, tiles, q, k_packed, v_cache, R_r, delta_mu, L->seq_len, text ? &td : nullptr, nullptr,
+                      L->keep, S + St, S, tiles, q, k_packed, v_cache, R_r, delta_mu, L->seq_len, text ? &td : nullptr, nullptr,
                       tk_new ? &ta : nullptr, sc, out, (float*)workspace,
                       ctx->fuse_merge && ctx->xcd_deal_ok ? ctx->tickets + APP_TICKETS : nullptr, DEC_COUNTERS,
                       L->batch <= APP_TICKETS ? ctx->tickets : nullptr, as_stream(stream));
@@ -689,7 +707,7 @@ rk_status rk_append_decode_attn(rk_ctx* ctx, const rk_layout* L, const void* k_n
                           v_cache, seq_len, ctx->tickets, st);
         if (e != hipSuccess) return hip_fail(ctx, e, "append launch");
     }
-    e = launch_decode(L->dtype, mfma, L->batch, L->n_q_heads, L->n_kv_heads, L->capacity, L->keep, S, tiles, q,
+    e = launch_decode(L->dtype, mfma, L->batch, L->n_q_heads, L->n_kv_heads, L->capacity, L->keep, S, S, tiles, q,
                       k_packed, v_cache, R_r, delta_mu, seq_len, nullptr, fused ? &app : nullptr, nullptr, sc, out,
                       (float*)workspace, ctx->fuse_merge && ctx->xcd_deal_ok ? ctx->tickets + APP_TICKETS : nullptr,
                       DEC_COUNTERS, ctx->tickets, st);

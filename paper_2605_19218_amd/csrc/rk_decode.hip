@@ -14,10 +14,8 @@
 //     nothing passes through LDS in the streaming loop;
 //   - q~ and P are fed as bf16 head + remainder pairs so that the fp32 rotation
 //     and the softmax weights keep ~2^-17 relative accuracy;
-//   - the split-K partials are folded by a second, tiny kernel as in the paper.
-//     (Folding them in the split kernel itself -- last work-group done -- was
-//     measured and rejected: on this multi-XCD part partials must then cross L2s
-//     as device-scope write-through stores, which cost more than a launch.)
+//   - the split-K partials are folded by the unit's last work-group where all of a unit's
+//     work-groups share an L2 (fold_unit), else by a second, tiny kernel as in the paper.
 #include "rk_kernels.hpp"
 
 namespace rk {
@@ -155,8 +153,7 @@ __global__ __launch_bounds__(128) void decode_merge(const float* __restrict__ ws
         }
     }
     // online over chunks of MC partials: the 3 MC loads of a chunk are independent of each other
-    // and of the running maximum, so one memory round trip serves a whole chunk (MC = 16; 24 when
-    // text slices of the dual path sit behind the splits)
+    // and of the running maximum, so one memory round trip serves a whole chunk (MC = 16)
     float M = NEG_INF, den = 0.f, num = 0.f;
     for (int i0 = 0; i0 < S; i0 += MC) {
         float av[MC], mv[MC], lv[MC];
@@ -424,134 +421,6 @@ __global__ __launch_bounds__(128) void append_text_rows(const T* __restrict__ k_
 }
 
 // ---------------------------------------------------------------------------
-// One slice of the text attention as a split-K partial: the same thread mapping and
-// thread-private online softmax as decode_text_merge, run by a 256-thread work-group of the
-// split launch for one query head and rows [r0, r1) of the text segment; the result goes to a
-// workspace slot of its own as (m, l, acc) in the log2 domain, with no bias (Alg. 2 step 4), and
-// the plain merge kernel folds it with the visual partials.  `lds` needs 16 * 128 + 32 floats.
-// Fused text append (ta.k != NULL): row len[b] of the segment is the new token.  Every work-group
-// takes it from k_new / v_new, not from the segment, so nobody reads what this launch writes; the
-// work-group of the group's first head whose slice holds that row (`writer`) stores it, and the
-// merge kernel bumps len[b] once the whole launch is done.
-__device__ __forceinline__ void text_partial(const bf16_t* __restrict__ q, const TextDev& text,
-                                             const TextAppendDev& ta, bool writer, int b, int hk, int Hkv,
-                                             size_t row, int ts, int TS, float scale_log2,
-                                             float* __restrict__ ws_m, float* __restrict__ ws_l,
-                                             float* __restrict__ ws_acc, size_t pidx, float* lds)
-{
-    constexpr int EPV = 8, CG = 16, TG = 16, NV = 8, CHUNK = TG * NV;
-    const int tid = threadIdx.x;
-    const int cg = tid % CG, tg = tid / CG;
-    float (*part)[D] = (float (*)[D])lds;
-    float* sm_m = lds + TG * D;
-    float* sm_l = sm_m + TG;
-    // rows stored in the segment, and rows attended: one more when a token is appended and fits
-    // (with an append text.max_len already counts the new row: the caller's bound plus one)
-    const int Ms = text.len ? min(max(text.len[b], 0), text.max_len) : text.max_len;
-    const bool add = ta.k != nullptr && text.len[b] >= 0 && text.len[b] < min(ta.capacity, text.max_len);
-    const int Mt = Ms + (add ? 1 : 0);
-    // slices of whole passes, the last one takes what is left
-    const int per = ((Mt + TS - 1) / TS + CHUNK - 1) / CHUNK * CHUNK;
-    const int r0 = ts * per, r1 = min(r0 + per, Mt);
-    const bf16_t* Kt = (const bf16_t*)text.k + (int64_t)b * text.sb + (int64_t)hk * text.sh + cg * EPV;
-    const bf16_t* Vt = (const bf16_t*)text.v + (int64_t)b * text.sb + (int64_t)hk * text.sh + cg * EPV;
-    const bf16_t* kn = add ? (const bf16_t*)ta.k_new + ((size_t)b * Hkv + hk) * D + cg * EPV : nullptr;
-    const bf16_t* vn = add ? (const bf16_t*)ta.v_new + ((size_t)b * Hkv + hk) * D + cg * EPV : nullptr;
-
-    float qf[EPV];
-    {
-        const uint4 qraw = *(const uint4*)(q + row * D + cg * EPV);
-        unpack16(qraw, qf, (const bf16_t*)nullptr);
-    }
-    float mrun = NEG_INF, lrun = 0.f;
-    float acc[EPV];
-#pragma unroll
-    for (int e = 0; e < EPV; ++e) acc[e] = 0.f;
-
-    uint4 kraw[NV], vraw[NV];
-    auto load_pass = [&](int base, uint4 (&kr)[NV], uint4 (&vr)[NV]) {
-#pragma unroll
-        for (int k = 0; k < NV; ++k) {           // rows past the end are clamped; their weight is 0
-            const int ri = base + tg + TG * k;
-            const int64_t off = (int64_t)max(min(ri, Ms - 1), 0) * text.st;
-            const bool fresh = add && ri == Ms;    // the appended row comes from the inputs
-            kr[k] = *(const uint4*)(fresh ? kn : Kt + off);
-            vr[k] = *(const uint4*)(fresh ? vn : Vt + off);
-        }
-    };
-    if (r0 < r1) load_pass(r0, kraw, vraw);
-    for (int base = r0; base < r1; base += CHUNK) {
-        uint4 knext[NV], vnext[NV];
-        load_pass(base + CHUNK, knext, vnext);
-        float sc[NV];
-#pragma unroll
-        for (int k = 0; k < NV; ++k) {
-            float kf[EPV];
-            unpack16(kraw[k], kf, (const bf16_t*)nullptr);
-            float d0 = 0.f, d1 = 0.f;
-#pragma unroll
-            for (int e = 0; e < EPV; e += 2) {
-                d0 = fmaf(qf[e], kf[e], d0);
-                d1 = fmaf(qf[e + 1], kf[e + 1], d1);
-            }
-            sc[k] = row16_sum(d0 + d1);
-        }
-        float mloc = NEG_INF;
-#pragma unroll
-        for (int k = 0; k < NV; ++k) {
-            sc[k] = (base + tg + TG * k < r1) ? sc[k] * scale_log2 : NEG_INF;
-            mloc = fmaxf(mloc, sc[k]);
-        }
-        const float m_new = fmaxf(mrun, mloc);
-        const float m_ref = (m_new > NEG_INF) ? m_new : 0.f;       // a token group may still be empty
-        const float alpha = exp2f(mrun - m_ref);
-        lrun *= alpha;
-#pragma unroll
-        for (int e = 0; e < EPV; ++e) acc[e] *= alpha;
-#pragma unroll
-        for (int k = 0; k < NV; ++k) {
-            const float w = exp2f(sc[k] - m_ref);
-            lrun += w;
-            float vf[EPV];
-            unpack16(vraw[k], vf, (const bf16_t*)nullptr);
-#pragma unroll
-            for (int e = 0; e < EPV; ++e) acc[e] = fmaf(w, vf[e], acc[e]);
-        }
-        mrun = m_new;
-#pragma unroll
-        for (int k = 0; k < NV; ++k) {
-            kraw[k] = knext[k];
-            vraw[k] = vnext[k];
-        }
-    }
-#pragma unroll
-    for (int e = 0; e < EPV; ++e) part[tg][cg * EPV + e] = acc[e];
-    if (cg == 0) { sm_m[tg] = mrun; sm_l[tg] = lrun; }
-    __syncthreads();
-    if (tid < D) {
-        float Mx = NEG_INF, den = 0.f, num = 0.f;
-#pragma unroll
-        for (int k = 0; k < TG; ++k) Mx = fmaxf(Mx, sm_m[k]);
-        if (Mx > NEG_INF) {
-#pragma unroll
-            for (int k = 0; k < TG; ++k) {
-                const float w = exp2f(sm_m[k] - Mx);               // 0 for an empty token group
-                den = fmaf(sm_l[k], w, den);
-                num = fmaf(part[k][tid], w, num);
-            }
-        }
-        ws_acc[pidx * D + tid] = num;
-        if (tid == 0) { ws_m[pidx] = Mx; ws_l[pidx] = den; }
-    }
-    if (writer && add && Ms >= r0 && Ms < r0 + per && tg == 0) {   // one 16-lane group stores the new row
-        bf16_t* kd = (bf16_t*)ta.k + (int64_t)b * ta.sb + (int64_t)hk * ta.sh + (int64_t)Ms * ta.st + cg * EPV;
-        bf16_t* vd = (bf16_t*)ta.v + (int64_t)b * ta.sb + (int64_t)hk * ta.sh + (int64_t)Ms * ta.st + cg * EPV;
-        *(uint4*)kd = *(const uint4*)kn;
-        *(uint4*)vd = *(const uint4*)vn;
-    }
-}
-
-// ---------------------------------------------------------------------------
 // MFMA split-K kernel (bf16 cache; R = r padded to a multiple of 16: the cache's padding
 // channels hold zeros and columns r .. R - 1 of R_r read as zero).  256 threads = 4 waves;
 // grid (split, H_kv * head groups of 16, B).  Each wave walks its own 32-token
@@ -664,13 +533,11 @@ __device__ __forceinline__ void fold_partials(const float* pm, const float* pl, 
 // kernel), so the one that draws the last ticket finds all partials in that same L2; what its own
 // L1 may hold of them from an earlier fold on the same compute unit it reads around (load_past_l1).
 // The fold runs in slot order, whoever does it.  `bump`: this launch also appends a row (rotated cache: NEW = true, the row's own score in
-// snew and its Values in v_new enter as one more term; text segment: NEW = false, the text
-// work-groups already counted it); the length of batch item b moves once every work-group of the
+// snew and its Values in v_new enter as one more term; text segment: NEW = false, the splits already counted it); the length of batch item b moves once every work-group of the
 // item -- they sit on different XCDs, hence a second, device-wide set of tickets -- has taken one,
 // i.e. has read the old length and is done with it.
 template <bool NEW>
-__device__ __forceinline__ void fold_unit(int unit, int unit_parts, int n_slots, int SP, int b, int u, int Hq, int h0,
-                                          int Gc, const float* ws_m, const float* ws_l, const float* ws_acc,
+__device__ __forceinline__ void fold_unit(int unit, int S, int b, int u, int Hq, int h0, int Gc, const float* ws_m, const float* ws_l, const float* ws_acc,
                                           bf16_t* __restrict__ out_merged, int32_t* done, bool bump,
                                           int32_t* batch_tickets, int batch_wgs, int32_t* len_rw, int len_cap,
                                           const float* snew, const bf16_t* __restrict__ v_new, int* sm_last)
@@ -679,7 +546,7 @@ __device__ __forceinline__ void fold_unit(int unit, int unit_parts, int n_slots,
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (tid == 0) {
-        *sm_last = __hip_atomic_fetch_add(done + unit, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == unit_parts - 1;
+        *sm_last = __hip_atomic_fetch_add(done + unit, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == S - 1;
         if (bump &&
             __hip_atomic_fetch_add(batch_tickets + b, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == batch_wgs - 1) {
             batch_tickets[b] = 0;
@@ -692,9 +559,9 @@ __device__ __forceinline__ void fold_unit(int unit, int unit_parts, int n_slots,
     const int hh = tid >> 4, c0 = (tid & 15) * 8;           // thread = (head, 8 channels)
     if (hh < Gc) {
         const size_t row = (size_t)b * Hq + h0 + hh;
-        const float* pm = ws_m + row * SP;
-        const float* pl = ws_l + row * SP;
-        const float* pa = ws_acc + row * SP * D + c0;
+        const float* pm = ws_m + row * S;
+        const float* pl = ws_l + row * S;
+        const float* pa = ws_acc + row * S * D + c0;
         float M = NEG_INF, den = 0.f;
         f32x4 n0 = (f32x4){0.f, 0.f, 0.f, 0.f}, n1 = n0;
         float sx = NEG_INF;
@@ -703,8 +570,8 @@ __device__ __forceinline__ void fold_unit(int unit, int unit_parts, int n_slots,
             sx = load_past_l1(snew + row);
             vraw = *(const uint4*)(v_new + (size_t)u * D + c0);
         }
-        if (n_slots <= 8) fold_partials<8>(pm, pl, pa, n_slots, M, den, n0, n1);     // one round trip to the L2
-        else fold_partials<16>(pm, pl, pa, n_slots, M, den, n0, n1);
+        if (S <= 8) fold_partials<8>(pm, pl, pa, S, M, den, n0, n1);     // one round trip to the L2
+        else fold_partials<16>(pm, pl, pa, S, M, den, n0, n1);
         if (NEW && sx > NEG_INF) {
             const float Mc = fmaxf(M, sx);
             const float resc = exp2f(M - Mc), w = exp2f(sx - Mc);
@@ -816,35 +683,223 @@ __device__ __forceinline__ void compute_tile(DecTile<R>& T, DecState<R>& st, con
     }
 }
 
+// ---------------------------------------------------------------------------
+// The dual path's text attention (Alg. 2 step 4: unrotated query, full-width rows, no bias) inside the split kernel: a
+// split takes its share of the text rows in front of its share of the cache, in tiles of 32 rows per wave, with a softmax
+// state of its own per wave that joins the visual states in the work-group's merge.  Rows are row-major, so a Key fragment is a
+// 16-byte piece of row n, and the Value operand is made in registers: lane (g, n) loads channels 8 n ..+7 of the eight
+// rows that its lane group's k-slots hold, and an 8 x 8 transpose of 16-bit values within the lane gives, for block cb,
+// the eight rows of channel 8 n + cb.  The accumulators therefore hold channel 8 n + cb where the visual ones hold
+// 16 cb + n; the merge sorts that out.  (With the text in work-groups of their own, one per head and 512 rows on vector
+// code, 1024 rows added 11 us to the benchmark's 35 us step; as part of the splits they add 4 us.)
+struct TextTile {
+    bf16x8 k[2][4];
+    uint4 v[8];
+};
+struct TextRows {
+    const bf16_t *k, *v;         // row 0 of this (b, h_kv)
+    const bf16_t *kn, *vn;       // the appended row (row `stored`), valid when there is one
+    int64_t st;
+    int stored;                  // rows in the segment
+    bool add;                    // an appended row follows them: it is taken from the inputs, never from the segment
+};
+
+// element `off` of a row; rows behind the last are clamped to it (or to row 0 of an empty segment) and masked later
+__device__ __forceinline__ const bf16_t* text_at(const TextRows& x, const bf16_t* base, const bf16_t* fresh, int row, int off)
+{
+    const bf16_t* p = base + (int64_t)max(min(row, x.stored - 1), 0) * x.st;
+    return (x.add && row == x.stored ? fresh : p) + off;
+}
+__device__ __forceinline__ void load_text_k(TextTile& T, const TextRows& x, int row0, int lane)
+{
+    const int g = lane >> 4, n = lane & 15;
+#pragma unroll
+    for (int tb = 0; tb < 2; ++tb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) T.k[tb][i] = *(const bf16x8*)text_at(x, x.k, x.kn, row0 + 16 * tb + n, 32 * i + 8 * g);
+}
+__device__ __forceinline__ void load_text_v(TextTile& T, const TextRows& x, int row0, int lane)
+{
+    const int g = lane >> 4, n = lane & 15;
+#pragma unroll
+    for (int jj = 0; jj < 8; ++jj)
+        T.v[jj] = *(const uint4*)text_at(x, x.v, x.vn, row0 + (jj < 4 ? 4 * g + jj : 12 + 4 * g + jj), 8 * n);
+}
+
+__device__ __forceinline__ uint32_t text_dw(const uint4& v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
+
+// One tile; with MORE the Keys of the tile at row `next` are requested as soon as this tile's are used up, its Values at
+// the end.
+template <bool MORE>
+__device__ __forceinline__ void compute_text_tile(TextTile& T, const TextRows& x, float& m_run, float& l_run, f32x4 (&O)[8],
+                                                  const bf16x8 (&qf)[4], int row0, int r1, int next, float scale_log2, int lane)
+{
+    const int g = lane >> 4;
+    f32x4 s[2];
+#pragma unroll
+    for (int tb = 0; tb < 2; ++tb) {
+        s[tb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(T.k[tb][i], qf[i], s[tb], 0, 0, 0);
+        s[tb] *= scale_log2;
+    }
+    if (MORE) load_text_k(T, x, next, lane);
+    if (row0 + 32 > r1) {            // rows past the end: no weight, and no Values (they may hold anything)
+#pragma unroll
+        for (int tb = 0; tb < 2; ++tb)
+#pragma unroll
+            for (int ii = 0; ii < 4; ++ii)
+                if (row0 + 16 * tb + 4 * g + ii >= r1) {
+                    s[tb][ii] = NEG_INF;
+                    T.v[4 * tb + ii] = make_uint4(0, 0, 0, 0);
+                }
+    }
+    float mt = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])),
+                     fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3])));
+    mt = fmaxf(mt, __shfl_xor(mt, 16));
+    mt = fmaxf(mt, __shfl_xor(mt, 32));
+    const float m_new = fmaxf(m_run, mt);
+    const float alpha = fast_exp2(m_run - m_new);
+    float psum = 0.f;
+    bf16x8 ph, pl;
+#pragma unroll
+    for (int tb = 0; tb < 2; ++tb)
+#pragma unroll
+        for (int ii = 0; ii < 4; ++ii) {
+            const float p = fast_exp2(s[tb][ii] - m_new);
+            psum += p;
+            __bf16 hi, lo;
+            split_bf16(p, hi, lo);
+            ph[4 * tb + ii] = hi;
+            pl[4 * tb + ii] = lo;
+        }
+    l_run = fmaf(l_run, alpha, psum);
+    if (__any(m_new > m_run)) {
+        f32x4 a4;
+#pragma unroll
+        for (int ii = 0; ii < 4; ++ii) a4[ii] = __shfl(alpha, 4 * g + ii);
+#pragma unroll
+        for (int cb = 0; cb < 8; ++cb) O[cb] *= a4;
+    }
+    m_run = m_new;
+#pragma unroll
+    for (int cb = 0; cb < 8; ++cb) {
+        const uint32_t sel = (cb & 1) ? 0x07060302u : 0x05040100u;       // the high or the low halves of two dwords
+        uint4 d;
+        d.x = __builtin_amdgcn_perm(text_dw(T.v[1], cb >> 1), text_dw(T.v[0], cb >> 1), sel);
+        d.y = __builtin_amdgcn_perm(text_dw(T.v[3], cb >> 1), text_dw(T.v[2], cb >> 1), sel);
+        d.z = __builtin_amdgcn_perm(text_dw(T.v[5], cb >> 1), text_dw(T.v[4], cb >> 1), sel);
+        d.w = __builtin_amdgcn_perm(text_dw(T.v[7], cb >> 1), text_dw(T.v[6], cb >> 1), sel);
+        const bf16x8 vf = __builtin_bit_cast(bf16x8, d);
+        O[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ph, vf, O[cb], 0, 0, 0);
+        O[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pl, vf, O[cb], 0, 0, 0);
+    }
+    if (MORE) load_text_v(T, x, next, lane);
+}
+
+// This wave's share of text rows [r0, r1) as a softmax state: accumulators to `park` ([8 cb][64 lanes] in the layout of the
+// visual states), maximum and sum (log2 domain) to sm_m, sm_l [16].  The last wave takes the first tile: it has the fewest
+// tiles of the cache.
+__device__ __forceinline__ void text_state(const TextRows& tr, int r0, int r1, const bf16x8 (&qf)[4], float scale_log2,
+                                           f32x4* __restrict__ park, float* __restrict__ sm_m, float* __restrict__ sm_l,
+                                           int wave, int lane)
+{
+    const int g = lane >> 4, n = lane & 15;
+    const int tw0 = r0 + 32 * (3 - wave);
+    float m_run = NEG_INF, l_run = 0.f;
+    if (tw0 < r1) {
+        TextTile X;
+        load_text_k(X, tr, tw0, lane);
+        load_text_v(X, tr, tw0, lane);
+        f32x4 O[8];
+#pragma unroll
+        for (int cb = 0; cb < 8; ++cb) O[cb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        int row = tw0;
+#pragma unroll 1
+        for (; row + 128 < r1; row += 128)
+            compute_text_tile<true>(X, tr, m_run, l_run, O, qf, row, r1, row + 128, scale_log2, lane);
+        compute_text_tile<false>(X, tr, m_run, l_run, O, qf, row, r1, 0, scale_log2, lane);
+        l_run += __shfl_xor(l_run, 16);
+        l_run += __shfl_xor(l_run, 32);
+        // channel 8 n + cb goes to where channel 16 cb' + n' of the visual layout lies
+#pragma unroll
+        for (int cb = 0; cb < 8; ++cb) park[(n >> 1) * 64 + 16 * g + 8 * (n & 1) + cb] = O[cb];
+    }
+    if (g == 0) { sm_m[n] = m_run; sm_l[n] = l_run; }
+}
+// whether wave w has left a text state behind
+__device__ __forceinline__ bool text_parked(int r0, int r1, int w) { return r0 + 32 * (3 - w) < r1; }
+
+// The appended row goes into the segment: 16 lanes, 16 bytes of Key and Value each.  No work-group of the launch reads it
+// from there.
+__device__ __forceinline__ void text_store_row(const TextRows& tr, const TextAppendDev& ta, int b, int hk, int lane16)
+{
+    const int64_t dst = (int64_t)b * ta.sb + (int64_t)hk * ta.sh + (int64_t)tr.stored * ta.st + 8 * lane16;
+    *(uint4*)((bf16_t*)ta.k + dst) = *(const uint4*)(tr.kn + 8 * lane16);
+    *(uint4*)((bf16_t*)ta.v + dst) = *(const uint4*)(tr.vn + 8 * lane16);
+}
+
+// A split that has text rows only: its partial (m, l, acc) for the Gc heads from query row `row0` on.
+__device__ __forceinline__ void text_split(const bf16_t* __restrict__ q, const TextRows& tr, int r0, int r1, size_t row0,
+                                           int Gc, int split, int S, float scale_log2, f32x4* __restrict__ park,
+                                           float (*sm_m)[16], float (*sm_l)[16], float* __restrict__ ws_m,
+                                           float* __restrict__ ws_l, float* __restrict__ ws_acc, int tid)
+{
+    const int lane = tid & 63, wave = tid >> 6, g = lane >> 4, n = lane & 15;
+    const bf16_t* qr = q + (row0 + min(n, Gc - 1)) * D + 8 * g;          // columns of heads that do not exist are never read
+    bf16x8 qf[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) qf[i] = *(const bf16x8*)(qr + 32 * i);
+    text_state(tr, r0, r1, qf, scale_log2, park + wave * 512, sm_m[wave], sm_l[wave], wave, lane);
+    __syncthreads();
+#pragma unroll
+    for (int ii = 0; ii < 4; ++ii) {
+        const int hh = 4 * g + ii;
+        if (hh >= Gc) continue;
+        const float M = fmaxf(fmaxf(sm_m[0][hh], sm_m[1][hh]), fmaxf(sm_m[2][hh], sm_m[3][hh]));
+        float l = 0.f, acc[2] = {0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+            if (text_parked(r0, r1, w)) {
+                const float x = fast_exp2(sm_m[w][hh] - M);
+                l = fmaf(sm_l[w][hh], x, l);
+#pragma unroll
+                for (int c2 = 0; c2 < 2; ++c2) acc[c2] = fmaf(park[w * 512 + (2 * wave + c2) * 64 + lane][ii], x, acc[c2]);
+            }
+        const size_t pidx = (row0 + hh) * S + split;
+#pragma unroll
+        for (int c2 = 0; c2 < 2; ++c2) ws_acc[pidx * D + 16 * (2 * wave + c2) + n] = acc[c2];
+        if (wave == 0 && n == 0) { ws_m[pidx] = M; ws_l[pidx] = l; }      // (no rows: -inf and zeros)
+    }
+}
+
 // STEP = false is the plain decode; STEP = true adds the fused appends of a whole decode step;
-// TEXT = true adds work-groups that compute slices of the text attention (dual path) next to the
-// visual splits.  Each form is compiled separately, so the plain call carries none of the others'
-// arguments or branches.
-// Grid: (split, (h_kv, head group), b).  With TEXT the grid has one dimension: indices [0, n_vis)
-// are the visual splits in the same order (split fastest), and from n_vis rounded up to 8 on come
-// the text work-groups, in blocks of 8 (unit, slice) groups x Gm heads numbered 8 * head + group % 8:
-// the heads of a group, which read the same text rows, then have indices that agree modulo 8, i.e.
-// run on one XCD (work-groups are dealt round-robin to the 8 XCDs) at about the same time, and share
-// its L2.
-template <int R, bool STEP, bool TEXT, bool FUSED>
+// TEXT adds the text attention of the dual path, to every split (TEXT_SHARED) or in splits of its own behind those of the
+// cache (TEXT_APART).  Each form is compiled separately, so the plain call, and the splits of the cache beside splits of
+// text, carry none of the others' branches.
+// Grid: (split, (h_kv, head group), b); one-dimensional with FUSED, see below.
+enum { TEXT_NONE = 0, TEXT_APART = 1, TEXT_SHARED = 2 };
+template <int R, bool STEP, int TEXT, bool FUSED>
 __global__ __launch_bounds__(256, 2) void decode_split_mfma(
     const bf16_t* __restrict__ q, bf16_t* Kp, bf16_t* Vc, const float* __restrict__ Rr,
     const float* __restrict__ dmu, const int32_t* seq_len, int Hq, int Hkv, int cap, int r, int tiles_all,
     float scale_log2, float* ws_m, float* ws_l, float* ws_acc, int S,
     bf16_t* __restrict__ out, const bf16_t* __restrict__ k_new, const bf16_t* __restrict__ v_new,
-    float* ws_snew, TextAppendDev ta, TextDev text, int TS, int SP, int n_vis,
+    float* ws_snew, TextAppendDev ta, TextDev text, int Sv, int n_units,
     bf16_t* __restrict__ out_merged, int32_t* done, int32_t* batch_tickets, int32_t* seq_len_rw)
 {
     typedef DecTile<R> Tile;
     constexpr int NF = Tile::NF, NFA = Tile::NFA;
     constexpr bool TAIL = Tile::TAIL;
 
-    // big: the four waves' O [4][16][128] at the end
-    __shared__ __attribute__((aligned(16))) float big[4 * 16 * D];
+    // the four waves' O [4][16][128] at the end, and with SHARED the four text states behind them
+    constexpr bool SHARED = TEXT == TEXT_SHARED;
+    constexpr int NST = SHARED ? 8 : 4;
+    __shared__ __attribute__((aligned(16))) float big[NST * 16 * D];
     __shared__ __attribute__((aligned(16))) float qt[16][R + 4];     // rows 16 bytes apart in the banks: lanes of a wave index the row
     __shared__ float sbias[16];
     __shared__ __attribute__((aligned(16))) float sdm[D];
-    __shared__ float sm_m[4][16], sm_l[4][16];
+    __shared__ float sm_m[NST][16], sm_l[NST][16];
     __shared__ int sm_last;
     const bool direct = out != nullptr;     // the only split of a single-path call writes the result itself
     // Fused frozen-R append (k_new != NULL; the host guarantees G < 16 and never combines it
@@ -856,55 +911,21 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
     const bool app = STEP && k_new != nullptr;
     const int G = Hq / Hkv;
     const int ngrp = (G + 15) >> 4;
-    int split, by, b, tgin = -1, tslice = 0, unit = 0;
+    int split, by, b, unit = 0;
     if constexpr (FUSED) {
         // One-dimensional grid.  Work-groups are dealt to the XCDs round-robin by their linear index, so
         // index & 7 is this work-group's XCD: all S work-groups of a unit get the same XCD (unit = 8 ul + xcd)
         // and therefore share an L2, which is what lets the unit's last work-group read the others'
-        // partials without any device-wide cache write-back (n_vis = number of units here; the host
-        // checks the deal once per context, see rk_create).  Units go fastest inside an XCD's slots, so
-        // every unit has work-groups among the first dispatched and among the last.
-        const int id = blockIdx.x, upx = (n_vis + 7) >> 3;
-        int slot = id >> 3, ul;
-        if (!TEXT || slot < upx * S) {
-            ul = slot % upx;
-            split = slot / upx;
-        } else {
-            // text work-groups of the dual path, behind the visual ones: (unit, slice, head) with the head
-            // fastest, on the unit's XCD like its splits; the heads of a group read the same rows at about
-            // the same time and share the XCD's L2
-            slot -= upx * S;
-            const int Gm = min(G, 16), item = slot / upx;
-            ul = slot % upx;
-            tgin = item % Gm;
-            tslice = item / Gm;
-            split = 0;
-        }
-        unit = 8 * ul + (id & 7);
-        if (unit >= n_vis) return;
+        // partials without any device-wide cache write-back (the host checks the deal once per context, see
+        // rk_create).  Units go fastest inside an XCD's slots, so every unit has work-groups among the first
+        // dispatched and among the last.
+        const int id = blockIdx.x, upx = (n_units + 7) >> 3, slot = id >> 3;
+        split = slot / upx;
+        unit = 8 * (slot % upx) + (id & 7);
+        if (unit >= n_units) return;
         const int gy = Hkv * ngrp;
         by = unit % gy;
         b = unit / gy;
-    } else if constexpr (TEXT) {
-        const int gy = Hkv * ngrp;             // (KV head, head group) pairs per batch item
-        int id = blockIdx.x;
-        if (id >= n_vis) {
-            // text work-groups come in blocks of 8 (unit, slice) groups x Gm heads, numbered
-            // 8 * head + (group % 8) inside a block
-            const int Gm = min(G, 16), ngroup = (n_vis / S) * TS;
-            const int t = id - ((n_vis + 7) & ~7);
-            if (t < 0) return;                 // padding between the two index ranges
-            const int blk = t / (8 * Gm), w = t - blk * 8 * Gm;
-            const int grp_id = 8 * blk + (w & 7);
-            tgin = w >> 3;
-            if (grp_id >= ngroup) return;      // padding of the group count
-            tslice = grp_id % TS;
-            id = (grp_id / TS) * S;            // the unit's first visual index: same (b, h_kv, head group)
-        }
-        split = id % S;
-        const int yz = id / S;
-        by = yz % gy;
-        b = yz / gy;
     } else {
         split = blockIdx.x;
         by = blockIdx.y;
@@ -916,20 +937,39 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
     const int u = b * Hkv + hk;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int g = lane >> 4, n = lane & 15;
-    // FUSED: partials a unit collects (its splits, and with TEXT one per head and text slice) and the
-    // work-groups of a batch item (all of them take a ticket before the item's lengths may move)
-    const int unit_parts = S + (TEXT ? TS * Gc : 0);
-    const int batch_wgs = Hkv * (ngrp * S + (TEXT ? TS * G : 0));
-    if (TEXT && tgin >= 0) {                   // a text work-group: one query head, one slice of the rows
-        if (tgin >= Gc) return;
-        const size_t row = (size_t)b * Hq + h0 + tgin;
-        text_partial(q, text, ta, tgin == 0 && grp == 0, b, hk, Hkv, row, tslice, TS, scale_log2, ws_m, ws_l,
-                     ws_acc, row * SP + S + tslice, big);
-        if constexpr (FUSED)
-            fold_unit<false>(unit, unit_parts, S + TS, SP, b, u, Hq, h0, Gc, ws_m, ws_l, ws_acc, out_merged, done,
-                             ta.k != nullptr, batch_tickets, batch_wgs, ta.len, min(ta.capacity, text.max_len),
-                             nullptr, nullptr, &sm_last);
-        return;
+    // The split's text rows [r0, r1): whole 32-row tiles, shared by the splits behind the first Sv, which have no part of the
+    // cache (TEXT_APART), or by all of them (TEXT_SHARED).  With an append text.max_len already counts the new row: the
+    // caller's bound plus one.
+    TextRows tr{};
+    int r0 = 0, r1 = 0;
+    auto text_share = [&](int text_raw, int idx, int cnt) {
+        tr.stored = min(max(text_raw, 0), text.max_len);
+        tr.add = ta.k != nullptr && text_raw >= 0 && text_raw < min(ta.capacity, text.max_len);
+        tr.st = text.st;
+        tr.k = (const bf16_t*)text.k + (int64_t)b * text.sb + (int64_t)hk * text.sh;
+        tr.v = (const bf16_t*)text.v + (int64_t)b * text.sb + (int64_t)hk * text.sh;
+        tr.kn = tr.add ? (const bf16_t*)ta.k_new + (size_t)u * D : tr.k;
+        tr.vn = tr.add ? (const bf16_t*)ta.v_new + (size_t)u * D : tr.v;
+        const int rows = tr.stored + (tr.add ? 1 : 0), per = ((rows + 31) / 32 + cnt - 1) / cnt * 32;
+        r0 = min(idx * per, rows);
+        r1 = min(r0 + per, rows);
+    };
+    // the first work-group with text rows stores the appended one
+    auto store_row = [&]() {
+        if (tr.add && r0 == 0 && r1 > 0 && grp == 0 && tid < 16) text_store_row(tr, ta, b, hk, tid);
+    };
+    if constexpr (TEXT == TEXT_APART) {
+        if (split >= Sv) {                 // no part of the cache: nothing of what follows is needed
+            text_share(text.len ? text.len[b] : text.max_len, split - Sv, S - Sv);
+            text_split(q, tr, r0, r1, (size_t)b * Hq + h0, Gc, split, S, scale_log2, (f32x4*)big, sm_m, sm_l, ws_m, ws_l,
+                       ws_acc, tid);
+            store_row();
+            if constexpr (FUSED)
+                fold_unit<false>(unit, S, b, u, Hq, h0, Gc, ws_m, ws_l, ws_acc, out_merged, done, ta.k != nullptr,
+                                 batch_tickets, Hkv * ngrp * S, ta.len, min(ta.capacity, text.max_len), nullptr, nullptr,
+                                 &sm_last);
+            return;
+        }
     }
 
     // ---- everything that does not need seq_len goes out first -----------------------------
@@ -940,11 +980,14 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
     // skipped later (the prologue is on the kernel's critical path: while it runs only the
     // prefetched tiles keep the memory system busy).
     const int seq_raw = seq_len[b];
+    const int text_raw = SHARED ? (text.len ? text.len[b] : text.max_len) : 0;
     // balanced partition of the 128-token tiles: the LAST (tiles % S) splits get one tile more (the
     // final tile of a cache is usually only partly filled, so the longer shares belong at the end)
-    const int tp = tiles_all / S, trem = tiles_all - tp * S;
-    const int t0 = 128 * (split * tp + max(split - (S - trem), 0));
-    const int t1_full = 128 * ((split + 1) * tp + max(split + 1 - (S - trem), 0));
+    // (with TEXT_APART the cache is left to the first Sv splits)
+    const int nv = TEXT == TEXT_APART ? Sv : S;
+    const int tp = tiles_all / nv, trem = tiles_all - tp * nv;
+    const int t0 = 128 * (split * tp + max(split - (nv - trem), 0));
+    const int t1_full = 128 * ((split + 1) * tp + max(split + 1 - (nv - trem), 0));
     const bf16_t* Ku = Kp + (size_t)u * slab_tokens(cap) * R;
     const bf16_t* Vu = Vc + (size_t)u * slab_tokens(cap) * D;
 
@@ -1012,8 +1055,9 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
     const bool empty = t0 >= t1;
     const bool app_here = app && split == 0;       // this work-group stores and scores the new row
     const bool app_ok = seq_raw >= 0 && seq_raw < cap;
+    if constexpr (SHARED) text_share(text_raw, split, S);
 
-    if (!empty || app_here) {
+    if (!empty || app_here || (SHARED && r0 < r1)) {
         const int ntiles = (t1 - t0 + 31) >> 5;
         const int nk = (ntiles - wave + 3) >> 2;
 
@@ -1098,7 +1142,15 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
             }
         }
 
-        load_tile<R>(TB, Ku, Vu, okB ? tokB : 0, okB ? lane : 0);
+        f32x4* park = (f32x4*)big;                 // [4 waves][8 cb][64 lanes], then the text states alike
+        if constexpr (!SHARED || R < 64) load_tile<R>(TB, Ku, Vu, okB ? tokB : 0, okB ? lane : 0);
+        if constexpr (SHARED) {
+            // The text comes first: it needs the plain query only, its loads join those of the first cache tiles, and its state
+            // is parked before the streaming loop needs the registers.
+            text_state(tr, r0, r1, qfrag, scale_log2, park + (4 + wave) * 512, sm_m[4 + wave], sm_l[4 + wave], wave, lane);
+            store_row();
+            if constexpr (R >= 64) load_tile<R>(TB, Ku, Vu, okB ? tokB : 0, okB ? lane : 0);
+        }
 
         // B operands of the score MFMAs: q~ of head n, split into bf16 head + remainder
         bf16x8 qh[NFA], ql[NFA];
@@ -1160,22 +1212,25 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
         float l_run = st.l_run;
         l_run += __shfl_xor(l_run, 16);
         l_run += __shfl_xor(l_run, 32);
-        f32x4* park = (f32x4*)big;                 // [4 waves][8 cb][64 lanes]
 #pragma unroll
         for (int cb = 0; cb < 8; ++cb) park[(wave * 8 + cb) * 64 + lane] = st.O[cb];
         if (g == 0) { sm_m[wave][n] = st.m_run; sm_l[wave][n] = l_run; }
         __syncthreads();
 
-        f32x4 wgt[4];                              // weight of wave w for heads 4g + ii
+        f32x4 wgt[NST];                            // weight of state w for heads 4g + ii
         f32x4 Mh, lh = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ii = 0; ii < 4; ++ii) {
             const int hh = 4 * g + ii;
-            float M = fmaxf(fmaxf(sm_m[0][hh], sm_m[1][hh]), fmaxf(sm_m[2][hh], sm_m[3][hh]));
-            Mh[ii] = M;
+            // (next to text scores the visual ones need their bias here; alone it is added to the stored maximum)
+            const float bias = SHARED ? sbias[hh] : 0.f;
+            float M = fmaxf(fmaxf(sm_m[0][hh], sm_m[1][hh]), fmaxf(sm_m[2][hh], sm_m[3][hh])) + bias;
+            if constexpr (SHARED)
+                M = fmaxf(M, fmaxf(fmaxf(sm_m[4][hh], sm_m[5][hh]), fmaxf(sm_m[6][hh], sm_m[7][hh])));
+            Mh[ii] = SHARED ? M : M + sbias[hh];
 #pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                float mw = sm_m[w][hh];
+            for (int w = 0; w < NST; ++w) {
+                float mw = sm_m[w][hh] + (w < 4 ? bias : 0.f);
                 float x = (mw > NEG_INF) ? fast_exp2(mw - M) : 0.f;
                 wgt[w][ii] = x;
                 lh[ii] = fmaf(sm_l[w][hh], x, lh[ii]);
@@ -1187,6 +1242,12 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
             f32x4 acc = park[(0 * 8 + cb) * 64 + lane] * wgt[0];
 #pragma unroll
             for (int w = 1; w < 4; ++w) acc += park[(w * 8 + cb) * 64 + lane] * wgt[w];
+            if constexpr (SHARED) {
+                // (waves without a text tile have left nothing behind)
+#pragma unroll
+                for (int w = 4; w < NST; ++w)
+                    if (text_parked(r0, r1, w - 4)) acc += park[(w * 8 + cb) * 64 + lane] * wgt[w];
+            }
 #pragma unroll
             for (int ii = 0; ii < 4; ++ii) {
                 const int hh = 4 * g + ii;
@@ -1194,7 +1255,7 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
                     const size_t row = (size_t)b * Hq + h0 + hh;
                     const int c = 16 * cb + n;
                     if (direct) out[row * D + c] = f32_to_bf16(acc[ii] / lh[ii]);
-                    else ws_acc[(row * SP + split) * D + c] = acc[ii];
+                    else ws_acc[(row * S + split) * D + c] = acc[ii];
                 }
             }
         }
@@ -1203,8 +1264,8 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
             for (int ii = 0; ii < 4; ++ii) {
                 const int hh = 4 * g + ii;
                 if (hh < Gc) {
-                    const size_t pidx = ((size_t)b * Hq + h0 + hh) * SP + split;
-                    ws_m[pidx] = Mh[ii] + sbias[hh];
+                    const size_t pidx = ((size_t)b * Hq + h0 + hh) * S + split;
+                    ws_m[pidx] = Mh[ii];
                     ws_l[pidx] = lh[ii];
                 }
             }
@@ -1217,7 +1278,7 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
             if (out != nullptr) {
                 out[row * D + c] = f32_to_bf16(0.f);
             } else {
-                const size_t pidx = row * SP + split;
+                const size_t pidx = row * S + split;
                 ws_acc[pidx * D + c] = 0.f;
                 if (c == 0) { ws_m[pidx] = NEG_INF; ws_l[pidx] = 0.f; }
             }
@@ -1226,9 +1287,9 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
 
     if constexpr (FUSED) {
         const bool bump = STEP ? app : (TEXT && ta.k != nullptr);
-        fold_unit<STEP>(unit, unit_parts, S + (TEXT ? TS : 0), SP, b, u, Hq, h0, Gc, ws_m, ws_l, ws_acc, out_merged, done,
-                        bump, batch_tickets, batch_wgs, STEP ? seq_len_rw : ta.len,
-                        STEP ? cap : min(ta.capacity, text.max_len), STEP && app ? ws_snew : nullptr, v_new, &sm_last);
+        fold_unit<STEP>(unit, S, b, u, Hq, h0, Gc, ws_m, ws_l, ws_acc, out_merged, done, bump, batch_tickets,
+                        Hkv * ngrp * S, STEP ? seq_len_rw : ta.len, STEP ? cap : min(ta.capacity, text.max_len),
+                        STEP && app ? ws_snew : nullptr, v_new, &sm_last);
     }
 }
 
@@ -1471,33 +1532,22 @@ static void launch_decode_mfma_r(dim3 grid, hipStream_t st, const bf16_t* q, bf1
                                  const float* Rr, const float* dmu, const int32_t* seq_len, int Hq, int Hkv, int cap,
                                  int r, int tiles_all, float sl2, float* m, float* l, float* acc, int S, bf16_t* out,
                                  const bf16_t* k_new, const bf16_t* v_new, float* snew, const TextAppendDev& ta,
-                                 const TextDev& text, int TS, int SP, int n_vis, bf16_t* out_merged, int32_t* done,
+                                 const TextDev& text, int Sv, int n_units, bf16_t* out_merged, int32_t* done,
                                  int32_t* batch_tickets, int32_t* seq_len_rw)
 {
-    if (out_merged && TS > 0)
-        hipLaunchKernelGGL((decode_split_mfma<R, false, true, true>), grid, dim3(256), 0, st, q, Kp, Vc, Rr, dmu,
-                           seq_len, Hq, Hkv, cap, r, tiles_all, sl2, m, l, acc, S, out, k_new, v_new, snew, ta, text, TS,
-                           SP, n_vis, out_merged, done, batch_tickets, seq_len_rw);
-    else if (out_merged && k_new)
-        hipLaunchKernelGGL((decode_split_mfma<R, true, false, true>), grid, dim3(256), 0, st, q, Kp, Vc, Rr, dmu,
-                           seq_len, Hq, Hkv, cap, r, tiles_all, sl2, m, l, acc, S, out, k_new, v_new, snew, ta, text, TS,
-                           SP, n_vis, out_merged, done, batch_tickets, seq_len_rw);
-    else if (out_merged)
-        hipLaunchKernelGGL((decode_split_mfma<R, false, false, true>), grid, dim3(256), 0, st, q, Kp, Vc, Rr, dmu,
-                           seq_len, Hq, Hkv, cap, r, tiles_all, sl2, m, l, acc, S, out, k_new, v_new, snew, ta, text, TS,
-                           SP, n_vis, out_merged, done, batch_tickets, seq_len_rw);
-    else if (TS > 0)
-        hipLaunchKernelGGL((decode_split_mfma<R, false, true, false>), grid, dim3(256), 0, st, q, Kp, Vc, Rr, dmu,
-                           seq_len, Hq, Hkv, cap, r, tiles_all, sl2, m, l, acc, S, out, k_new, v_new, snew, ta, text, TS,
-                           SP, n_vis, out_merged, done, batch_tickets, seq_len_rw);
-    else if (k_new || ta.k)
-        hipLaunchKernelGGL((decode_split_mfma<R, true, false, false>), grid, dim3(256), 0, st, q, Kp, Vc, Rr, dmu,
-                           seq_len, Hq, Hkv, cap, r, tiles_all, sl2, m, l, acc, S, out, k_new, v_new, snew, ta, text, TS,
-                           SP, n_vis, out_merged, done, batch_tickets, seq_len_rw);
-    else
-        hipLaunchKernelGGL((decode_split_mfma<R, false, false, false>), grid, dim3(256), 0, st, q, Kp, Vc, Rr, dmu,
-                           seq_len, Hq, Hkv, cap, r, tiles_all, sl2, m, l, acc, S, out, k_new, v_new, snew, ta, text, TS,
-                           SP, n_vis, out_merged, done, batch_tickets, seq_len_rw);
+#define RK_FORM(STEP, TEXT, FUSED)                                                                                     \
+    hipLaunchKernelGGL((decode_split_mfma<R, STEP, TEXT, FUSED>), grid, dim3(256), 0, st, q, Kp, Vc, Rr, dmu, seq_len, Hq, \
+                       Hkv, cap, r, tiles_all, sl2, m, l, acc, S, out, k_new, v_new, snew, ta, text, Sv, n_units,       \
+                       out_merged, done, batch_tickets, seq_len_rw)
+    if (out_merged && text.k && Sv < S) RK_FORM(false, TEXT_APART, true);
+    else if (out_merged && text.k) RK_FORM(false, TEXT_SHARED, true);
+    else if (out_merged && k_new) RK_FORM(true, TEXT_NONE, true);
+    else if (out_merged) RK_FORM(false, TEXT_NONE, true);
+    else if (text.k && Sv < S) RK_FORM(false, TEXT_APART, false);
+    else if (text.k) RK_FORM(false, TEXT_SHARED, false);
+    else if (k_new) RK_FORM(true, TEXT_NONE, false);
+    else RK_FORM(false, TEXT_NONE, false);
+#undef RK_FORM
 }
 
 // The fused append needs a free MFMA column next to the query heads: one group of fewer than 16.
@@ -1506,30 +1556,21 @@ bool decode_append_fusable(int dtype, bool mfma, int Hq, int Hkv, int r)
     return mfma && decode_mfma_supported(dtype, r) && (Hq / Hkv) < 16;
 }
 
-// Text slices computed by work-groups of the split launch (dual path on the matrix-core kernels):
-// how many slices for a segment of max_len rows (0 = not this way).
-int decode_text_slices(int dtype, bool mfma, int r, const TextDev* text)
-{
-    if (!text || !mfma || !decode_mfma_supported(dtype, r)) return 0;
-    int ts = (text->max_len + 511) / 512;              // about 512 rows per slice
-    return ts < 1 ? 1 : (ts > DECODE_TEXT_SLICES_MAX ? DECODE_TEXT_SLICES_MAX : ts);
-}
-
-hipError_t launch_decode(int dtype, bool mfma, int B, int Hq, int Hkv, int cap, int r, int S, int tiles_all,
+hipError_t launch_decode(int dtype, bool mfma, int B, int Hq, int Hkv, int cap, int r, int S, int Sv, int tiles_all,
                          const void* q, const void* Kp, const void* Vc, const float* Rr, const float* dmu,
                          const int32_t* seq_len, const TextDev* text, const AppendDev* app, const TextAppendDev* tapp,
                          float scale, void* out, float* ws, int32_t* counters, int n_counters, int32_t* batch_tickets,
                          hipStream_t st)
 {
     const size_t rows = (size_t)B * Hq;
-    const int TS = decode_text_slices(dtype, mfma, r, text);
-    const int SP = S + TS;                              // partials per (b, h_q)
+    const bool text_in_split = text && mfma && decode_mfma_supported(dtype, r);    // else the second kernel runs the text
     float* ws_m = ws;
-    float* ws_l = ws_m + rows * SP;
-    float* ws_acc = ws_l + rows * SP;
-    float* ws_snew = ws_acc + rows * SP * D;           // [rows], fused append only
+    float* ws_l = ws_m + rows * S;
+    float* ws_acc = ws_l + rows * S;
+    float* ws_snew = ws_acc + rows * S * D;           // [rows], fused append only
     const float sl2 = scale * 1.4426950408889634f;    // scores in the log2 domain
-    const bool direct = S == 1 && text == nullptr && app == nullptr;   // a lone split of a plain call writes `out` itself
+    // a lone split writes `out` itself, unless somebody has to move a length behind it
+    const bool direct = S == 1 && (text == nullptr || text_in_split) && app == nullptr && tapp == nullptr;
     hipError_t e;
     if (app && (text || !decode_append_fusable(dtype, mfma, Hq, Hkv, r))) return hipErrorInvalidValue;
     if (tapp && !text) return hipErrorInvalidValue;
@@ -1537,10 +1578,7 @@ hipError_t launch_decode(int dtype, bool mfma, int B, int Hq, int Hkv, int cap, 
     if (mfma && decode_mfma_supported(dtype, r)) {
         const int G = Hq / Hkv, ngrp = (G + 15) / 16;
         const int nunit = B * Hkv * ngrp;
-        int n_vis = nunit * S;
-        dim3 grid(S, Hkv * ngrp, B);                    // visual splits only: (split, (h_kv, head group), b)
-        if (TS > 0)                                     // one dimension: the splits, then the text work-groups
-            grid = dim3((unsigned)(((n_vis + 7) & ~7) + (G < 16 ? G : 16) * ((nunit * TS + 7) & ~7)));
+        dim3 grid(S, Hkv * ngrp, B);                    // (split, (h_kv, head group), b)
         // Merge folded into the split launch: the splits of a unit share an XCD there, so a unit count
         // that is not a multiple of 8 loads the XCDs unevenly (4 units: half of them idle).  The busiest
         // XCD then streams ceil(nunit / 8) * 8 / nunit times its fair share; folded is chosen while that
@@ -1548,24 +1586,20 @@ hipError_t launch_decode(int dtype, bool mfma, int B, int Hq, int Hkv, int cap, 
         // (measured: 4 units x 4K tokens 9.8 us folded against 11.6 us, 4 units x 16K tokens 14.6 against 13.5 us).
         const double cache_bytes = (double)nunit * tiles_all * 128.0 * (keep_padded(r) + D) * 2.0;
         const double excess_us = ((double)((nunit + 7) / 8 * 8) / nunit - 1.0) * cache_bytes / 6.5e6;
-        // (with a text segment the partials of the text work-groups join the same fold, so there S = 1 folds too)
-        const bool fused_merge = (!text || TS > 0) && ((!app && !tapp) || batch_tickets) && (S >= 2 || TS > 0) && counters &&
-                                 nunit <= n_counters && excess_us < 3.0;
-        if (fused_merge) {
-            grid = dim3((unsigned)(8 * ((nunit + 7) / 8) * (S + TS * (G < 16 ? G : 16))));
-            n_vis = nunit;
-        }
+        const bool fused_merge = ((!app && !tapp) || batch_tickets) && (S >= 2 || tapp) && counters && nunit <= n_counters &&
+                                 excess_us < 3.0;
+        if (fused_merge) grid = dim3((unsigned)(8 * ((nunit + 7) / 8) * S));
         const bf16_t* q_ = (const bf16_t*)q;
         // the caches are written only by a fused append, whose caller handed them over writable
         bf16_t *k_ = const_cast<bf16_t*>((const bf16_t*)Kp), *v_ = const_cast<bf16_t*>((const bf16_t*)Vc);
         const bf16_t* kn = app ? (const bf16_t*)app->k_new : nullptr;
         const bf16_t* vn = app ? (const bf16_t*)app->v_new : nullptr;
-        const TextDev tx = TS > 0 ? *text : TextDev{};
+        const TextDev tx = text ? *text : TextDev{};
 #define RK_CASE(RV)                                                                                        \
     case RV:                                                                                               \
         launch_decode_mfma_r<RV>(grid, st, q_, k_, v_, Rr, dmu, seq_len, Hq, Hkv, cap, r, tiles_all, sl2, ws_m,   \
-                                 ws_l, ws_acc, S, direct ? (bf16_t*)out : nullptr, kn, vn, ws_snew, ta, tx, TS, SP, \
-                                 n_vis, fused_merge ? (bf16_t*)out : nullptr, counters, batch_tickets,     \
+                                 ws_l, ws_acc, S, direct ? (bf16_t*)out : nullptr, kn, vn, ws_snew, ta, tx, Sv, nunit, \
+                                 fused_merge ? (bf16_t*)out : nullptr, counters, batch_tickets,     \
                                  app ? app->seq_len : nullptr);                                            \
         break;
         switch (keep_padded(r)) {
@@ -1603,7 +1637,7 @@ hipError_t launch_decode(int dtype, bool mfma, int B, int Hq, int Hkv, int cap, 
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (text && TS == 0) {
+    if (text && !text_in_split) {
         const int U = B * Hkv, upad = (U + 7) & ~7, n_pad = upad - U;
         const unsigned tblocks = (unsigned)(upad * (Hq / Hkv));
         const bool wide = text->max_len > 128;       // bf16 only: the fp32 form would not fit its registers
@@ -1617,20 +1651,16 @@ hipError_t launch_decode(int dtype, bool mfma, int B, int Hq, int Hkv, int cap, 
             hipLaunchKernelGGL((decode_text_merge<bf16_t, 128>), dim3(tblocks), dim3(128), 0, st,
                                (const bf16_t*)q, *text, Hq, Hkv, sl2, ws_m, ws_l, ws_acc, S, (bf16_t*)out, n_pad);
     } else if (dtype == 0) {
-        hipLaunchKernelGGL((decode_merge<float, 16>), dim3((unsigned)rows), dim3(128), 0, st, ws_m, ws_l, ws_acc, SP,
+        hipLaunchKernelGGL((decode_merge<float, 16>), dim3((unsigned)rows), dim3(128), 0, st, ws_m, ws_l, ws_acc, S,
                            (float*)out, (const float*)nullptr, (const float*)nullptr, Hq, Hkv, cap,
                            (int32_t*)nullptr, (int32_t*)nullptr, 0);
-    } else if (TS > 0) {
-        // with a fused text append the split launch has stored the new rows: the lengths move here
-        hipLaunchKernelGGL((decode_merge<bf16_t, 24>), dim3((unsigned)rows), dim3(128), 0, st, ws_m, ws_l, ws_acc, SP,
-                           (bf16_t*)out, (const float*)nullptr, (const bf16_t*)nullptr, Hq, Hkv, cap,
-                           (int32_t*)nullptr, tapp ? tapp->len : (int32_t*)nullptr,
-                           tapp ? (tapp->capacity < text->max_len ? tapp->capacity : text->max_len) : 0);
     } else {
-        hipLaunchKernelGGL((decode_merge<bf16_t, 16>), dim3((unsigned)rows), dim3(128), 0, st, ws_m, ws_l, ws_acc, SP,
+        // with a fused append the split launch has stored the new rows: the lengths move here
+        hipLaunchKernelGGL((decode_merge<bf16_t, 16>), dim3((unsigned)rows), dim3(128), 0, st, ws_m, ws_l, ws_acc, S,
                            (bf16_t*)out, app ? (const float*)ws_snew : (const float*)nullptr,
                            app ? (const bf16_t*)app->v_new : (const bf16_t*)nullptr, Hq, Hkv, cap,
-                           app ? app->seq_len : (int32_t*)nullptr, (int32_t*)nullptr, 0);
+                           app ? app->seq_len : (int32_t*)nullptr, tapp ? tapp->len : (int32_t*)nullptr,
+                           tapp ? (tapp->capacity < text->max_len ? tapp->capacity : text->max_len) : 0);
     }
     return hipGetLastError();
 }

@@ -78,26 +78,26 @@ struct TextAppendDev {
     int32_t* len;            // device [B], bumped by the one wave that copies the rows
     int capacity;
 };
-// Dual path on the matrix-core kernels: the text attention runs as up to this
-// many slices in work-groups of the split launch, each writing a partial of its own (the workspace holds
-// S + DECODE_TEXT_SLICES_MAX partials per row); otherwise the text rows are handled by the merge kernel.
-constexpr int DECODE_TEXT_SLICES_MAX = 8;
+// A dual decode may take up to this many splits more than its cache alone would; the workspace is sized for them.
+constexpr int DECODE_TEXT_SPLITS_MAX = 8;
 // whether launch_decode can take `app` for this shape (MFMA kernel with a free column: G < 16)
 bool decode_append_fusable(int dtype, bool mfma, int Hq, int Hkv, int r);
-// text == nullptr: visual segment only; otherwise the text segment joins the softmax in the merge kernel
+// text == nullptr: visual segment only; otherwise the text segment joins the softmax, in the splits themselves (bf16
+//                 matrix-core kernels) or in the second kernel
 // app != nullptr: the new token is written to row seq_len[b] of both caches (which must then be writable),
 //                 joins the softmax, and seq_len[b] += 1; needs decode_append_fusable and text == nullptr
 // tapp != nullptr (needs text): row text.len[b] of the text segment receives k_new / v_new and the length is
 //                 bumped before the merge kernel reads it; text->max_len must already count the new row
-// tiles_all: 128-token tiles of the longest sequence; split s takes a balanced share of them
-// ws: partials, ((S + DECODE_TEXT_SLICES_MAX) (d + 2) + 1) floats per (b, h_q)
+// tiles_all: 128-token tiles of the longest sequence, shared by the first Sv of the S splits; Sv < S (bf16 dual path only):
+//            the splits behind them take the text rows, which otherwise all splits share
+// ws: partials, (S (d + 2) + 1) floats per (b, h_q)
 // counters: n_counters ints that are zero between launches (or null): lets a plain matrix-core decode
 //           fold its partials inside the split launch (one counter per (b, h_kv, head group)).  Only
 //           valid on a device that deals work-groups to its XCDs round-robin by linear index
 //           (probe_xcd_deal)
 // batch_tickets: B ints that are zero between launches (or null): with them a fused append is folded
 //           the same way and the launch bumps seq_len itself
-hipError_t launch_decode(int dtype, bool mfma, int B, int Hq, int Hkv, int cap, int r, int S, int tiles_all,
+hipError_t launch_decode(int dtype, bool mfma, int B, int Hq, int Hkv, int cap, int r, int S, int Sv, int tiles_all,
                          const void* q, const void* Kp, const void* Vc, const float* Rr, const float* dmu,
                          const int32_t* seq_len, const TextDev* text, const AppendDev* app, const TextAppendDev* tapp,
                          float scale, void* out, float* ws, int32_t* counters, int n_counters, int32_t* batch_tickets,

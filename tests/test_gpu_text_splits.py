@@ -1,0 +1,100 @@
+"""The text attention inside the splits of the bf16 dual decode: text lengths around the 32-row tiles and the shares of
+the splits, long text beside a short or an empty cache (more splits than the cache alone would take), one split that
+writes the output itself, several head groups, and the appended row taken from the inputs.  Against the oracle, bf16
+outputs within 2e-2 as everywhere in this suite; rows behind the end hold NaN patterns."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2605_19218_amd as rk
+
+from gpu_util import D, DEV, Pipeline, to_dev, to_host
+from test_gpu_parity import check_out, layer, run_prefill
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = rk.rk_create(0)
+    yield c
+    rk.rk_destroy(c)
+
+
+CASES = [
+    # B, Hq, Hkv, L, lengths, r, text capacity, text lengths, splits
+    (5, 14, 2, 700, [700, 300, 128, 1, 0], 64, 200, [33, 32, 31, 1, 0], 0),
+    (2, 8, 2, 300, [300, 0], 32, 1500, [1500, 1029], 0),            # long text, short and empty cache
+    (1, 4, 4, 4096, None, 128, 300, [257], 2),                      # the widest kernel, steady loop
+    (2, 20, 1, 500, [500, 129], 96, 140, [129, 65], 3),             # two head groups
+    (2, 2, 1, 200, [200, 64], 16, 700, [700, 97], 1),               # a lone split
+    (9, 16, 2, 900, [900] * 8 + [5], 48, 64, [64, 63, 0, 1, 2, 40, 50, 60, 33], 0),
+]
+
+
+def with_text(p, data, cid, cap, lens, extra=0):
+    B, Hkv = p.B, p.Hkv
+    t = layer(B, p.Hq, Hkv, max(cap, 1), "bf16", cid)
+    kt, vt = to_dev(t["K"], "bf16"), to_dev(t["V"], "bf16")
+    dk = torch.full((B, Hkv, cap + extra, D), float("nan"), device=DEV, dtype=torch.bfloat16)
+    dv = dk.clone()
+    for b in range(B):
+        dk[b, :, :lens[b]], dv[b, :, :lens[b]] = kt[b, :, :lens[b]], vt[b, :, :lens[b]]
+    return t, dk, dv, torch.tensor(lens, device=DEV, dtype=torch.int32)
+
+
+def want_dual(p, q, lens, t, tlens, extra=None):
+    Kt, V = p.unpacked()
+    pad = np.zeros((p.B, p.Hkv, 1, D))
+    kt, vt = np.concatenate([t["K"], pad], 2), np.concatenate([t["V"], pad], 2)
+    n = np.asarray(tlens, np.int32)
+    if extra is not None:
+        for b in range(p.B):
+            kt[b, :, n[b]], vt[b, :, n[b]] = extra[0][b], extra[1][b]
+        n = n + 1
+    return oracle.decode_dual_batch(q.astype(np.float64), Kt, V, kt, vt, to_host(p.Rr), to_host(p.dmu),
+                                    lens=np.asarray(lens, np.int32), lens_t=n.astype(np.int32))
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_text_in_splits(ctx, case):
+    B, Hq, Hkv, L, lengths, r, cap, tlens, splits = case
+    data = layer(B, Hq, Hkv, L, "bf16", 81, lengths=lengths, mean_shift=1.5)
+    p = run_prefill(ctx, data, B, Hq, Hkv, L, r, "bf16", lengths=lengths)
+    lens = lengths or [L] * B
+    t, dk, dv, dlen = with_text(p, data, 82, cap, tlens, extra=1)
+    q = to_dev(data["q"], "bf16")
+    new = layer(B, Hq, Hkv, 1, "bf16", 83)
+    kn, vn = to_dev(new["k_new"], "bf16"), to_dev(new["v_new"], "bf16")
+    results = []
+    rk.rk_set_option(ctx, rk.RK_OPT_DECODE_SPLITS, splits)
+    try:
+        for fuse in (1, 1, 0):
+            rk.rk_set_option(ctx, rk.RK_OPT_FUSE_MERGE, fuse)
+            ws = torch.empty(rk.rk_decode_workspace_size(ctx, p.layout()), device=DEV, dtype=torch.uint8)
+            rk.rk_decode_attn_dual(ctx, p.layout(), q, p.Kp, p.Vc, p.Rr, p.dmu, rk.Text(dk, dv, cap, len=dlen), 0.0, p.out, ws)
+            torch.cuda.synchronize()
+            results.append(to_host(p.out))
+        want = want_dual(p, data["q"], lens, t, tlens)
+        for got in results:
+            check_out(got, want, "bf16")
+        assert np.array_equal(results[0], results[1])
+        for b in range(B):
+            if lens[b] == 0 and tlens[b] == 0:
+                assert not results[0][b].any()
+        for fuse in (1, 0):                                   # the appended row joins this step's softmax
+            rk.rk_set_option(ctx, rk.RK_OPT_FUSE_MERGE, fuse)
+            k2, v2, l2 = dk.clone(), dv.clone(), dlen.clone()
+            ws = torch.empty(rk.rk_decode_workspace_size(ctx, p.layout()), device=DEV, dtype=torch.uint8)
+            rk.rk_append_text_decode_attn_dual(ctx, p.layout(), kn, vn, q, p.Kp, p.Vc, p.Rr, p.dmu,
+                                               rk.Text(k2, v2, cap, len=l2), 0.0, p.out, ws)
+            torch.cuda.synchronize()
+            check_out(to_host(p.out), want_dual(p, data["q"], lens, t, tlens, (new["k_new"], new["v_new"])), "bf16")
+            assert l2.cpu().tolist() == [n + 1 for n in tlens]
+            for b in range(B):
+                assert torch.equal(k2[b, :, tlens[b]], kn[b]) and torch.equal(v2[b, :, tlens[b]], vn[b])
+                assert torch.equal(k2[b, :, :tlens[b]], dk[b, :, :tlens[b]])
+    finally:
+        rk.rk_set_option(ctx, rk.RK_OPT_FUSE_MERGE, 1)
+        rk.rk_set_option(ctx, rk.RK_OPT_DECODE_SPLITS, 0)
