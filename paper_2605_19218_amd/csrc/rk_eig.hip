@@ -10,9 +10,11 @@
 // The fp64 vector rate of this part equals its unpacked fp32 rate, so double costs registers and LDS width only; it
 // buys vectors that need no iteration over the whole matrix.  A sweep of Jacobi is 127 dependent rounds on one compute
 // unit and 8-10 sweeps are needed; the reduction is 126 dependent steps in all, and everything behind it is independent
-// per eigenpair.  Measured (32 / 512 matrices): 102 + 36 + 28 + 10 us / 214 + 334 + 546 us against 756 us / 2.3 ms of the
+// per eigenpair.  Measured (32 / 512 matrices): 106 + 34 + 23 + 10 us / 222 + 307 + 322 us against 756 us / 2.3 ms of the
 // parallel Jacobi that solved every matrix before, with eigenvalues to their fp32 rounding (1e-7 of the spectrum
 // against 8e-7).
+#include <type_traits>
+
 #include "rk_kernels.hpp"
 
 namespace rk {
@@ -342,6 +344,7 @@ static unsigned eig_slices(int U) { return 64u * (unsigned)((U + 7) / 8); }
 // top, lane 1 from the bottom, both rescaled every 8 steps (exponents kept per block of 8); the vector is the one above
 // the row with the smallest twist gamma_i = (d_i - lambda) + e_{i-1} y_{i-1} / y_i + e_i x_{i+1} / x_i and the other below
 // it.  The second round runs at the Rayleigh-corrected eigenvalue, which leaves a residual of a few 1e-16.
+// 39000 cycles for the eigenvalues, about 8000 + 5000 for each round of chains and twist.
 constexpr int TV_PAIRS = 16, TV_SECT = 12, TV_LD = D + 2;
 
 __global__ __launch_bounds__(256) void eig_tri_vectors(int U, const double* __restrict__ scratch,
@@ -354,6 +357,7 @@ __global__ __launch_bounds__(256) void eig_tri_vectors(int U, const double* __re
     __shared__ double se[D];
     __shared__ double yx[TV_PAIRS][2][TV_LD];        // y (from the top) and x (from the bottom)
     __shared__ int ys[TV_PAIRS][2][D / 8];           // their exponents, per block of 8 rows
+    __shared__ double slam[TV_PAIRS];
     int u, slice;
     eig_slice(u, slice);
     if (u >= U || status[2 * u] != 0) return;
@@ -423,20 +427,24 @@ __global__ __launch_bounds__(256) void eig_tri_vectors(int U, const double* __re
         lo = nlo;
     }
     double lam = 0.5 * (lo + hi);
+    if (s == 0) slam[pr] = lam;
     __syncthreads();
 
-    const int dir = s & 1;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     double (*yv)[TV_LD] = yx[pr];
     double zz[8];
     double norm2 = 1.0, gam = 0.0;
 #pragma unroll 1
     for (int round = 0; round < 2; ++round) {
-        {
-            // (all lanes of a pair run the chain of their parity and store the same numbers)
+        // Wave 0 runs the 16 chains from the top, wave 1 those from the bottom: with each wave running its own pairs' every
+        // coefficient was read four times from LDS (11400 cycles a round).
+        auto chain = [&](auto direction) {
+            constexpr int dir = decltype(direction)::value;
+            const double lam = slam[lane];
             double y0 = 0.0, y = 1.0;
             int exps = 0;
-            double* dst = yv[dir] + (dir ? D - 1 : 0);
-            const int stp = dir ? -1 : 1;
+            double* dst = yx[lane][dir] + (dir ? D - 1 : 0);
+            constexpr int stp = dir ? -1 : 1;
             f64x2 ca[8], cb[8];
             double wa[8], wb[8];
             auto fetch = [&](f64x2 (&c)[8], double (&w)[8], int b) {
@@ -445,14 +453,15 @@ __global__ __launch_bounds__(256) void eig_tri_vectors(int U, const double* __re
                 __builtin_amdgcn_sched_barrier(0);
             };
             auto steps = [&](const f64x2 (&c)[8], const double (&w)[8], int b) {
-                ys[pr][dir][dir ? D / 8 - 1 - b : b] = exps;
+                ys[lane][dir][dir ? D / 8 - 1 - b : b] = exps;
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    dst[stp * (8 * b + i)] = y;
+                    dst[stp * i] = y;
                     const double yn = fma((lam - c[i].x) * c[i].y, y, -(w[i] * y0));
                     y0 = y;
                     y = yn;
                 }
+                dst += 8 * stp;
                 const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(y), fabs(y0)));
                 y = ldexp(y, -ex);
                 y0 = ldexp(y0, -ex);
@@ -467,10 +476,12 @@ __global__ __launch_bounds__(256) void eig_tri_vectors(int U, const double* __re
                 fetch(ca, wa, min(b + 2, D / 8 - 1));
                 steps(cb, wb, b + 1);
             }
-        }
+        };
+        if (wave == 0 && lane < TV_PAIRS) chain(std::integral_constant<int, 0>());
+        if (wave == 1 && lane < TV_PAIRS) chain(std::integral_constant<int, 1>());
         __syncthreads();
         // the twist: smallest |gamma|, first row of equals
-        double best = __builtin_huge_val(), bg = best;
+        double bg = __builtin_huge_val();
         int twist = 0;
 #pragma unroll
         for (int m = 0; m < 8; ++m) {
@@ -484,13 +495,16 @@ __global__ __launch_bounds__(256) void eig_tri_vectors(int U, const double* __re
                 const double xb = ldexp(yv[1][min(i + 1, D - 1)], ys[pr][1][min(i + 1, D - 1) >> 3] - ys[pr][1][blk]);
                 g = fma(se[i], xb * rcp_f64(yv[1][i]), g);
             }
-            if (fabs(g) < best) { best = fabs(g); bg = g; twist = i; }
+            if (fabs(g) < fabs(bg)) { bg = g; twist = i; }
         }
 #pragma unroll
-        for (int o = 1; o < 16; o <<= 1) {
-            const double ob = __shfl_xor(best, o), og = __shfl_xor(bg, o);
-            const int ot = __shfl_xor(twist, o);
-            if (ob < best || (ob == best && ot < twist)) { best = ob; bg = og; twist = ot; }
+        for (int o = 0; o < 4; ++o) {                            // the lane permutations of row16_sum_f64
+            const double og = o == 0 ? dpp_f64<0xB1>(bg) : o == 1 ? dpp_f64<0x4E>(bg) : o == 2 ? dpp_f64<0x141>(bg) : dpp_f64<0x140>(bg);
+            const int ot = o == 0   ? __builtin_amdgcn_mov_dpp(twist, 0xB1, 0xf, 0xf, true)
+                           : o == 1 ? __builtin_amdgcn_mov_dpp(twist, 0x4E, 0xf, 0xf, true)
+                           : o == 2 ? __builtin_amdgcn_mov_dpp(twist, 0x141, 0xf, 0xf, true)
+                                    : __builtin_amdgcn_mov_dpp(twist, 0x140, 0xf, 0xf, true);
+            if (fabs(og) < fabs(bg) || (fabs(og) == fabs(bg) && ot < twist)) { bg = og; twist = ot; }
         }
         const double iy = rcp_f64(yv[0][twist]), ix = rcp_f64(yv[1][twist]);
         const int ey = ys[pr][0][twist >> 3], ex = ys[pr][1][twist >> 3];
@@ -505,8 +519,11 @@ __global__ __launch_bounds__(256) void eig_tri_vectors(int U, const double* __re
         }
         norm2 = row16_sum_f64(n2);
         gam = bg;
-        if (round == 0) lam += gam / norm2;
-        __syncthreads();
+        if (round == 0) {
+            lam += gam / norm2;
+            if (s == 0) slam[pr] = lam;
+            __syncthreads();
+        }
     }
     const double inv = 1.0 / sqrt(norm2);
     // residual |gamma| / ||z||: a few 1e-16 when all is well; anything else (NaN included) goes to Jacobi
@@ -524,58 +541,114 @@ __global__ __launch_bounds__(256) void eig_tri_vectors(int U, const double* __re
 // The step is what makes independent vectors safe: neighbours a gap g apart come out orthogonal only to about
 // 1e-16 / g, the step squares that defect, and because each vector is an eigenvector to 1e-16 the correction mixes
 // close neighbours only and costs no residual.  A defect above 0.05 sends the matrix to Jacobi.
-// Both products run on the fp64 matrix cores with all of Z in LDS; then Z's space takes the reflections, which are
-// applied in descending order, 16 lanes per column, the column in registers.  Bound: the 126 dependent reflections
-// (LDS read, dot product over a lane group, update).
-constexpr int OB_LD = D + 2, OB_MLD = 17;
-constexpr size_t OB_LDS_BYTES = (size_t)(D * OB_LD + D * OB_MLD + D) * sizeof(double);
+// Both products run on the fp64 matrix cores with all of Z in LDS; then Z's space takes the reflections, which were on
+// their way in registers meanwhile and are applied in descending order, four at a time, 16 lanes per column, the column in
+// registers: four inner products with the same x, the 4 x 4 triangle of the reflections' own inner products, one update.
+// Bound, of 44000 cycles: loading Z 5700, the products 6000 + 6700 (matrix pipe 4100 each), reflections 20000 (every
+// lane group reads all of them from LDS).  One reflection at a time and loads where they are used: 56000 cycles (9200,
+// 5800, 8100, 8900 for the record, 23500), 27.7 us instead of 23 for 32 matrices, 547 instead of 322 for 512.
+constexpr int OB_LD = D + 2, OB_MLD = 17, OB_CF = 10;
+constexpr size_t OB_LDS_BYTES = (size_t)(D * OB_LD + D * OB_MLD + D / 4 * OB_CF) * sizeof(double);
 
+// Four reflections, rows 4 Q + 3 down to 4 Q of the record, as far as block KB and the one behind it need them.
 template <int KB>
-__device__ __forceinline__ void ob_reflect(double (&x)[8], const double* __restrict__ Vs, const double* __restrict__ taus,
-                                           int s)
+__device__ __forceinline__ void ob_load(f64x2 (&v)[4][4], f64x2 (&cf)[5], const double* __restrict__ Vs,
+                                        const double* __restrict__ coef, int Q, int s)
 {
-    constexpr int K1 = 16 * KB + 15 < D - 2 ? 16 * KB + 15 : D - 3;
-#pragma unroll 2
-    for (int k = K1; k >= 16 * KB; --k) {
-        double v[8];
+    constexpr int P0 = (KB > 0 ? KB - 1 : 0) >> 1;
 #pragma unroll
-        for (int p = KB >> 1; p < 4; ++p) {
-            const f64x2 t = *(const f64x2*)(Vs + (size_t)k * D + (p * 16 + s) * 2);
-            v[2 * p] = t.x;
-            v[2 * p + 1] = t.y;
-        }
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int p = P0; p < 4; ++p) v[i][p] = *(const f64x2*)(Vs + (size_t)(4 * Q + 3 - i) * D + (p * 16 + s) * 2);
+#pragma unroll
+    for (int i = 0; i < 5; ++i) cf[i] = *(const f64x2*)(coef + Q * OB_CF + 2 * i);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// x <- H_3 H_2 H_1 H_0 x in one go: H_i = I - tau_i w_i w_i^T, so x <- x + sum_i a_i w_i with
+// a_i = -tau_i (w_i^T x) + sum_{j < i} (-tau_i w_i^T w_j) a_j; cf holds the four -tau_i and the six bracketed numbers.
+template <int KB>
+__device__ __forceinline__ void ob_reflect4(double (&x)[8], const f64x2 (&v)[4][4], const f64x2 (&cf)[5])
+{
+    double a[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
         double t0 = 0.0, t1 = 0.0;
 #pragma unroll
         for (int m = KB; m < 8; ++m) {
-            if (m & 1) t1 = fma(v[m], x[m], t1);
-            else t0 = fma(v[m], x[m], t0);
+            if (m & 1) t1 = fma(v[i][m >> 1].y, x[m], t1);
+            else t0 = fma(v[i][m >> 1].x, x[m], t0);
         }
-        const double t = row16_sum_f64(t0 + t1) * -taus[k];
-#pragma unroll
-        for (int m = KB; m < 8; ++m) x[m] = fma(t, v[m], x[m]);
+        a[i] = t0 + t1;
     }
-    if constexpr (KB > 0) ob_reflect<KB - 1>(x, Vs, taus, s);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[i] += dpp_f64<0xB1>(a[i]);     // the steps of row16_sum_f64, four sums abreast
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[i] += dpp_f64<0x4E>(a[i]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[i] += dpp_f64<0x141>(a[i]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[i] += dpp_f64<0x140>(a[i]);
+    a[0] *= cf[0].x;
+    a[1] = fma(cf[2].x, a[0], cf[0].y * a[1]);
+    a[2] = fma(cf[3].x, a[1], fma(cf[2].y, a[0], cf[1].x * a[2]));
+    a[3] = fma(cf[4].y, a[2], fma(cf[4].x, a[1], fma(cf[3].y, a[0], cf[1].y * a[3])));
+#pragma unroll
+    for (int m = KB; m < 8; ++m)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[m] = fma(a[i], m & 1 ? v[i][m >> 1].y : v[i][m >> 1].x, x[m]);
+}
+
+// Reflections 16 KB + 15 down to 0; va, ca: the first four of them.
+template <int KB>
+__device__ __forceinline__ void ob_reflect(double (&x)[8], f64x2 (&va)[4][4], f64x2 (&ca)[5], const double* __restrict__ Vs,
+                                           const double* __restrict__ coef, int s)
+{
+    f64x2 vb[4][4], cb[5];
+#pragma unroll 1
+    for (int Q = 4 * KB + 3; Q > 4 * KB; Q -= 2) {
+        ob_load<KB>(vb, cb, Vs, coef, Q - 1, s);
+        ob_reflect4<KB>(x, va, ca);
+        ob_load<KB>(va, ca, Vs, coef, max(Q - 2, 0), s);
+        ob_reflect4<KB>(x, vb, cb);
+    }
+    if constexpr (KB > 0) ob_reflect<KB - 1>(x, va, ca, Vs, coef, s);
 }
 
 __global__ __launch_bounds__(256) void eig_orth_back(int U, const double* __restrict__ scratch,
                                                      float* __restrict__ R_out, int32_t* __restrict__ status)
 {
     extern __shared__ __attribute__((aligned(16))) double ob_lds[];
-    double* Zs = ob_lds;                    // [128][130] all vectors of T; later the reflections [126][128]
+    double* Zs = ob_lds;                    // [128][130] all vectors of T; later the reflections [128][128]
     double* Ms = Zs + D * OB_LD;            // [128][17]
-    double* taus = Ms + D * OB_MLD;         // [128]
+    double* coef = Ms + D * OB_MLD;         // [32][10] coefficients of four reflections each
     int u, slice;
     eig_slice(u, slice);
     if (u >= U || status[2 * u] != 0) return;
     const int c0 = slice * 16;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, n = lane & 15;
     const double* W = scratch + (size_t)u * EIGW_TOTAL;
-    for (int i = tid; i < D * D / 2; i += 256) {
-        const f64x2 t = ((const f64x2*)(W + EIGW_Z))[i];
-        *(f64x2*)(Zs + (i >> 6) * OB_LD + 2 * (i & 63)) = t;
+    // every load of Z is out before the first is waited for; the reflections follow into registers and arrive under the
+    // two products
+    f64x2 stage[D * D / 512];
+#pragma unroll
+    for (int i = 0; i < D * D / 512; ++i) stage[i] = ((const f64x2*)(W + EIGW_Z))[tid + 256 * i];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < D * D / 512; ++i) *(f64x2*)(Zs + ((tid >> 6) + 4 * i) * OB_LD + 2 * (tid & 63)) = stage[i];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < D * D / 512; ++i) {
+        const int k = (tid >> 6) + 4 * i;   // (rows 126 and 127 do not exist)
+        stage[i] = ((const f64x2*)(W + EIGW_V))[min(k, D - 3) * (D / 2) + (tid & 63)];
     }
-    if (tid < D) taus[tid] = W[EIGW_TAU + tid];
-    __syncthreads();
+    double nt[2][4];                        // -tau of the two quads whose coefficients this lane group makes
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) nt[h][i] = -W[EIGW_TAU + 4 * ((tid >> 4) + 16 * h) + 3 - i];
+    __builtin_amdgcn_sched_barrier(0);
+    lds_barrier();
 
     // G = Z^T Z[:, c0 ..]: wave = rows 32 wave ..+31 of G.  A 16x16x4 step takes one contraction index per lane group;
     // two steps share a 16-byte read, so group g holds indices 8 t + 2 g + b of step pair t.
@@ -604,7 +677,7 @@ __global__ __launch_bounds__(256) void eig_orth_back(int U, const double* __rest
             Ms[i * OB_MLD + n] = (i == c0 + n ? 1.0 : 0.0) - 0.5 * dev;
         }
     if (bad) status[2 * u + 1] = 1;
-    __syncthreads();
+    lds_barrier();
 
     // Z' = Z M for the 16 columns: rows 32 wave ..+31
     acc[0] = acc[1] = (f64x4){0.0, 0.0, 0.0, 0.0};
@@ -616,19 +689,59 @@ __global__ __launch_bounds__(256) void eig_orth_back(int U, const double* __rest
         for (int q = 0; q < 2; ++q)
             acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(Zs[i * OB_LD + 32 * wave + 16 * q + n], bv, acc[q], 0, 0, 0);
     }
-    __syncthreads();
+    lds_barrier();
 #pragma unroll
     for (int q = 0; q < 2; ++q)
 #pragma unroll
         for (int r = 0; r < 4; ++r) Ms[(32 * wave + 16 * q + 4 * r + g) * OB_MLD + n] = acc[q][r];
-    for (int i = tid; i < (D - 2) * D / 2; i += 256) *(f64x2*)(Zs + 2 * i) = ((const f64x2*)(W + EIGW_V))[i];
+    // pairs left of block k / 32 of row k were not recorded
+#pragma unroll
+    for (int i = 0; i < D * D / 512; ++i) {
+        const int k = (tid >> 6) + 4 * i, p = (tid & 63) >> 4;
+        *(f64x2*)(Zs + 2 * (tid + 256 * i)) = k < D - 2 && p >= (k >> 5) ? stage[i] : (f64x2){0.0, 0.0};
+    }
+    lds_barrier();
+    // two quads of reflections per lane group: their inner products and coefficients
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int Q = (tid >> 4) + 16 * h;
+        f64x2 w[4][4];
+        double c[6];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int p = 0; p < 4; ++p) w[i][p] = *(const f64x2*)(Zs + (4 * Q + 3 - i) * D + (p * 16 + n) * 2);
+#pragma unroll
+        for (int i = 1; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < i; ++j) {
+                double t0 = 0.0, t1 = 0.0;
+#pragma unroll
+                for (int p = 0; p < 4; ++p) {
+                    t0 = fma(w[i][p].x, w[j][p].x, t0);
+                    t1 = fma(w[i][p].y, w[j][p].y, t1);
+                }
+                c[i * (i - 1) / 2 + j] = row16_sum_f64(t0 + t1);
+            }
+        if (n == 0) {
+            double* d = coef + Q * OB_CF;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) d[i] = nt[h][i];
+#pragma unroll
+            for (int i = 1; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < i; ++j) d[4 + i * (i - 1) / 2 + j] = nt[h][i] * c[i * (i - 1) / 2 + j];
+        }
+    }
     __syncthreads();
 
     const int cc = 4 * wave + g;            // 16 lanes per column, lane n: rows n + 16 m
     double x[8];
 #pragma unroll
     for (int m = 0; m < 8; ++m) x[m] = Ms[(n + 16 * m) * OB_MLD + cc];
-    ob_reflect<7>(x, Zs, taus, n);
+    f64x2 va[4][4], ca[5];
+    ob_load<7>(va, ca, Zs, coef, D / 4 - 1, n);
+    ob_reflect<7>(x, va, ca, Zs, coef, n);
 #pragma unroll
     for (int m = 0; m < 8; ++m) Ms[(n + 16 * m) * OB_MLD + cc] = x[m];
     __syncthreads();
