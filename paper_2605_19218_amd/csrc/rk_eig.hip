@@ -10,7 +10,7 @@
 // The fp64 vector rate of this part equals its unpacked fp32 rate, so double costs registers and LDS width only; it
 // buys vectors that need no iteration over the whole matrix.  A sweep of Jacobi is 127 dependent rounds on one compute
 // unit and 8-10 sweeps are needed; the reduction is 126 dependent steps in all, and everything behind it is independent
-// per eigenpair.  Measured (32 / 512 matrices): 106 + 34 + 23 + 10 us / 222 + 307 + 322 us against 756 us / 2.3 ms of the
+// per eigenpair.  Measured (32 / 512 matrices): 106 + 34 + 18 + 10 us / 222 + 302 + 257 us against 756 us / 2.3 ms of the
 // parallel Jacobi that solved every matrix before, with eigenvalues to their fp32 rounding (1e-7 of the spectrum
 // against 8e-7).
 #include <type_traits>
@@ -32,7 +32,8 @@ constexpr int EIGW_DE = EIGW_Z + D * D;            // [128] pairs (d_i, e_{i-1}^
 constexpr int EIGW_E = EIGW_DE + 2 * D;            // [128] e_i (e_127 unused)
 constexpr int EIGW_TAU = EIGW_E + D;               // [128] H_k = I - tau_k v_k v_k^T
 constexpr int EIGW_SCALE = EIGW_TAU + D;           // C_q = scale * (Q T Q^T)
-constexpr int EIGW_TOTAL = EIGW_SCALE + 2;
+constexpr int EIGW_T = EIGW_SCALE + 2;             // [8][16][16] -T_b of H_{16 b} ... H_{16 b + 15} = I - V_b T_b V_b^T
+constexpr int EIGW_TOTAL = EIGW_T + 8 * 256;
 
 size_t eig_scratch_bytes(size_t U) { return U * EIGW_TOTAL * sizeof(double); }
 
@@ -347,7 +348,50 @@ static unsigned eig_slices(int U) { return 64u * (unsigned)((U + 7) / 8); }
 // 39000 cycles for the eigenvalues, about 8000 + 5000 for each round of chains and twist.
 constexpr int TV_PAIRS = 16, TV_SECT = 12, TV_LD = D + 2;
 
-__global__ __launch_bounds__(256) void eig_tri_vectors(int U, const double* __restrict__ scratch,
+// -T of reflections 16 b .. 16 b + 15 by one wave: their inner products G on the matrix cores (the order of the contraction
+// is that of the record, from its first written pair on; a lane's row of V serves as both operands), then
+// T_ij = -tau_j sum_{i <= l < j} T_il G_lj, a row of T per lane, lane groups alike.  G: 256 doubles of LDS.
+__device__ __forceinline__ void tri_block_t(const double* __restrict__ W, double* __restrict__ Tout, double* __restrict__ G,
+                                            int b, int lane)
+{
+    const int g = lane >> 4, n = lane & 15;
+    const double* row = W + EIGW_V + (size_t)min(16 * b + n, D - 3) * D;      // (rows 126 and 127: tau is 0)
+    f64x2 v[16];
+#pragma unroll
+    for (int t = 0; t < 16; ++t) v[t] = *(const f64x2*)(row + max(8 * t, 32 * (b >> 1)) + 2 * g);
+    const double tau = W[EIGW_TAU + 16 * b + n];
+    f64x4 acc[2];
+    acc[0] = acc[1] = (f64x4){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int t = 0; t < 16; ++t)
+        if (8 * t >= 32 * (b >> 1)) {
+            acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(v[t].x, v[t].x, acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(v[t].y, v[t].y, acc[1], 0, 0, 0);
+        }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) G[(4 * r + g) * 16 + n] = acc[0][r] + acc[1][r];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    double T[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+        for (int l = 0; l < j; ++l) {
+            if (l & 1) s1 = fma(T[l], G[l * 16 + j], s1);
+            else s0 = fma(T[l], G[l * 16 + j], s0);
+        }
+        const double tj = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(tau), j),
+                                           __builtin_amdgcn_readlane(__double2loint(tau), j));
+        T[j] = j < n ? 0.0 : j == n ? tj : -tj * (s0 + s1);
+    }
+    if (g == 0)
+#pragma unroll
+        for (int j = 0; j < 16; j += 2) *(f64x2*)(Tout + n * 16 + j) = (f64x2){-T[j], -T[j + 1]};
+}
+
+__global__ __launch_bounds__(256, 2) void eig_tri_vectors(int U, const double* __restrict__ scratch,
                                                        double* __restrict__ Zout, float* __restrict__ lam_out,
                                                        int32_t* __restrict__ status)
 {
@@ -358,6 +402,7 @@ __global__ __launch_bounds__(256) void eig_tri_vectors(int U, const double* __re
     __shared__ double yx[TV_PAIRS][2][TV_LD];        // y (from the top) and x (from the bottom)
     __shared__ int ys[TV_PAIRS][2][D / 8];           // their exponents, per block of 8 rows
     __shared__ double slam[TV_PAIRS];
+    __shared__ double sg16[256];
     int u, slice;
     eig_slice(u, slice);
     if (u >= U || status[2 * u] != 0) return;
@@ -479,6 +524,8 @@ __global__ __launch_bounds__(256) void eig_tri_vectors(int U, const double* __re
         };
         if (wave == 0 && lane < TV_PAIRS) chain(std::integral_constant<int, 0>());
         if (wave == 1 && lane < TV_PAIRS) chain(std::integral_constant<int, 1>());
+        // meanwhile the block reflector that eig_orth_back wants of reflections 16 slice .. + 15
+        if (wave == 2 && round == 0) tri_block_t(W, Zout + (size_t)u * EIGW_TOTAL + EIGW_T + 256 * slice, sg16, slice, lane);
         __syncthreads();
         // the twist: smallest |gamma|, first row of equals
         double bg = __builtin_huge_val();
@@ -542,86 +589,70 @@ __global__ __launch_bounds__(256) void eig_tri_vectors(int U, const double* __re
 // 1e-16 / g, the step squares that defect, and because each vector is an eigenvector to 1e-16 the correction mixes
 // close neighbours only and costs no residual.  A defect above 0.05 sends the matrix to Jacobi.
 // Both products run on the fp64 matrix cores with all of Z in LDS; then Z's space takes the reflections, which were on
-// their way in registers meanwhile and are applied in descending order, four at a time, 16 lanes per column, the column in
-// registers: four inner products with the same x, the 4 x 4 triangle of the reflections' own inner products, one update.
-// Bound, of 44000 cycles: loading Z 5700, the products 6000 + 6700 (matrix pipe 4100 each), reflections 20000 (every
-// lane group reads all of them from LDS).  One reflection at a time and loads where they are used: 56000 cycles (9200,
-// 5800, 8100, 8900 for the record, 23500), 27.7 us instead of 23 for 32 matrices, 547 instead of 322 for 512.
-constexpr int OB_LD = D + 2, OB_MLD = 17, OB_CF = 10;
-constexpr size_t OB_LDS_BYTES = (size_t)(D * OB_LD + D * OB_MLD + D / 4 * OB_CF) * sizeof(double);
+// their way in registers meanwhile.  They are applied 16 at a time as I - V T V^T, again on the matrix cores, with the 16
+// columns of Z staying in result registers; T comes from eig_tri_vectors, where two waves have nothing else to do.
+// Bound, of 36000 cycles: loading Z 6500, the products 6000 + 6600 (matrix pipe 4100 each), storing V 2800, reflections 13700
+// (eight rounds of four dependent matrix steps, one exchange between the waves, eight more).  Four reflections at a time
+// on the vector unit: 20000 + 2500 for their inner products (LDS-bound, every lane group reads all of V), 23 us; one at a time
+// with loads where they are used: 56000 cycles in all, 27.7 us.  Now 18 us for 32 matrices, 257 for 512 (547 at first).
+constexpr int OB_LD = D + 2, OB_MLD = 17;
+constexpr size_t OB_LDS_BYTES = (size_t)(D * OB_LD + D * OB_MLD) * sizeof(double);
 
-// Four reflections, rows 4 Q + 3 down to 4 Q of the record, as far as block KB and the one behind it need them.
-template <int KB>
-__device__ __forceinline__ void ob_load(f64x2 (&v)[4][4], f64x2 (&cf)[5], const double* __restrict__ Vs,
-                                        const double* __restrict__ coef, int Q, int s)
+// Z <- H_{16 KB} ... H_{16 KB + 15} Z and on to block 0.  Wave w holds row tiles w and w + 4 of the 16 columns in result
+// layout, whose register r is the right operand of contraction step r.  X = -T (V^T Z), Z += V X: V^T Z is summed over
+// the waves in LDS (Wx: two buffers, so one barrier per block), the rest stays within the wave.
+// T: -T of this block as left operand; that of the next block is on its way meanwhile.
+__device__ __forceinline__ void ob_load_t(double (&T)[4], const double* __restrict__ Tg, int b, int g, int n)
 {
-    constexpr int P0 = (KB > 0 ? KB - 1 : 0) >> 1;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int p = P0; p < 4; ++p) v[i][p] = *(const f64x2*)(Vs + (size_t)(4 * Q + 3 - i) * D + (p * 16 + s) * 2);
-#pragma unroll
-    for (int i = 0; i < 5; ++i) cf[i] = *(const f64x2*)(coef + Q * OB_CF + 2 * i);
-    __builtin_amdgcn_sched_barrier(0);
+    for (int r = 0; r < 4; ++r) T[r] = Tg[256 * b + 16 * n + 4 * r + g];
 }
 
-// x <- H_3 H_2 H_1 H_0 x in one go: H_i = I - tau_i w_i w_i^T, so x <- x + sum_i a_i w_i with
-// a_i = -tau_i (w_i^T x) + sum_{j < i} (-tau_i w_i^T w_j) a_j; cf holds the four -tau_i and the six bracketed numbers.
 template <int KB>
-__device__ __forceinline__ void ob_reflect4(double (&x)[8], const f64x2 (&v)[4][4], const f64x2 (&cf)[5])
+__device__ __forceinline__ void ob_block(f64x4 (&z)[2], const double (&T)[4], const double* __restrict__ Tg,
+                                         const double* __restrict__ Vs, double* Wx, int wave, int g, int n)
 {
-    double a[4];
+    double T_next[4];
+    ob_load_t(T_next, Tg, KB > 0 ? KB - 1 : 0, g, n);
+    constexpr int Q0 = KB >= 4 ? 1 : 0;                   // block KB leaves the rows above 16 KB alone
+    const double* V = Vs + 16 * KB * OB_LD + 16 * wave;
+    double left[2][4], up[2][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        double t0 = 0.0, t1 = 0.0;
+    for (int q = Q0; q < 2; ++q)
 #pragma unroll
-        for (int m = KB; m < 8; ++m) {
-            if (m & 1) t1 = fma(v[i][m >> 1].y, x[m], t1);
-            else t0 = fma(v[i][m >> 1].x, x[m], t0);
-        }
-        a[i] = t0 + t1;
-    }
+        for (int r = 0; r < 4; ++r) left[q][r] = V[n * OB_LD + 64 * q + 4 * r + g];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) a[i] += dpp_f64<0xB1>(a[i]);     // the steps of row16_sum_f64, four sums abreast
+    for (int q = Q0; q < 2; ++q)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) a[i] += dpp_f64<0x4E>(a[i]);
+        for (int r = 0; r < 4; ++r) up[q][r] = V[(4 * r + g) * OB_LD + 64 * q + n];
+    f64x4 w[2];
+    w[0] = w[1] = (f64x4){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) a[i] += dpp_f64<0x141>(a[i]);
+    for (int r = 0; r < 4; ++r)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) a[i] += dpp_f64<0x140>(a[i]);
-    a[0] *= cf[0].x;
-    a[1] = fma(cf[2].x, a[0], cf[0].y * a[1]);
-    a[2] = fma(cf[3].x, a[1], fma(cf[2].y, a[0], cf[1].x * a[2]));
-    a[3] = fma(cf[4].y, a[2], fma(cf[4].x, a[1], fma(cf[3].y, a[0], cf[1].y * a[3])));
+        for (int q = Q0; q < 2; ++q) w[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(left[q][r], z[q][r], w[q], 0, 0, 0);
+    f64x2* x = (f64x2*)Wx + (KB & 1) * 512 + 16 * g + n;
+    x[128 * wave] = (f64x2){w[0][0] + w[1][0], w[0][1] + w[1][1]};
+    x[128 * wave + 64] = (f64x2){w[0][2] + w[1][2], w[0][3] + w[1][3]};
+    lds_barrier();
+    const f64x2 lo = (x[0] + x[128]) + (x[256] + x[384]), hi = (x[64] + x[192]) + (x[320] + x[448]);
+    const double s[4] = {lo.x, lo.y, hi.x, hi.y};
+    f64x4 y = (f64x4){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int m = KB; m < 8; ++m)
+    for (int r = 0; r < 4; ++r) y = __builtin_amdgcn_mfma_f64_16x16x4f64(T[r], s[r], y, 0, 0, 0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) x[m] = fma(a[i], m & 1 ? v[i][m >> 1].y : v[i][m >> 1].x, x[m]);
-}
-
-// Reflections 16 KB + 15 down to 0; va, ca: the first four of them.
-template <int KB>
-__device__ __forceinline__ void ob_reflect(double (&x)[8], f64x2 (&va)[4][4], f64x2 (&ca)[5], const double* __restrict__ Vs,
-                                           const double* __restrict__ coef, int s)
-{
-    f64x2 vb[4][4], cb[5];
-#pragma unroll 1
-    for (int Q = 4 * KB + 3; Q > 4 * KB; Q -= 2) {
-        ob_load<KB>(vb, cb, Vs, coef, Q - 1, s);
-        ob_reflect4<KB>(x, va, ca);
-        ob_load<KB>(va, ca, Vs, coef, max(Q - 2, 0), s);
-        ob_reflect4<KB>(x, vb, cb);
-    }
-    if constexpr (KB > 0) ob_reflect<KB - 1>(x, va, ca, Vs, coef, s);
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int q = Q0; q < 2; ++q) z[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(up[q][r], y[r], z[q], 0, 0, 0);
+    if constexpr (KB > 0) ob_block<KB - 1>(z, T_next, Tg, Vs, Wx, wave, g, n);
 }
 
 __global__ __launch_bounds__(256) void eig_orth_back(int U, const double* __restrict__ scratch,
                                                      float* __restrict__ R_out, int32_t* __restrict__ status)
 {
     extern __shared__ __attribute__((aligned(16))) double ob_lds[];
-    double* Zs = ob_lds;                    // [128][130] all vectors of T; later the reflections [128][128]
-    double* Ms = Zs + D * OB_LD;            // [128][17]
-    double* coef = Ms + D * OB_MLD;         // [32][10] coefficients of four reflections each
+    double* Zs = ob_lds;                    // [128][130] all vectors of T; later the reflections, in natural order
+    double* Ms = Zs + D * OB_LD;            // [128][17]; later the sums of ob_block (2048)
     int u, slice;
     eig_slice(u, slice);
     if (u >= U || status[2 * u] != 0) return;
@@ -642,11 +673,8 @@ __global__ __launch_bounds__(256) void eig_orth_back(int U, const double* __rest
         const int k = (tid >> 6) + 4 * i;   // (rows 126 and 127 do not exist)
         stage[i] = ((const f64x2*)(W + EIGW_V))[min(k, D - 3) * (D / 2) + (tid & 63)];
     }
-    double nt[2][4];                        // -tau of the two quads whose coefficients this lane group makes
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) nt[h][i] = -W[EIGW_TAU + 4 * ((tid >> 4) + 16 * h) + 3 - i];
+    double T[4];
+    ob_load_t(T, W + EIGW_T, 7, g, n);
     __builtin_amdgcn_sched_barrier(0);
     lds_barrier();
 
@@ -679,81 +707,34 @@ __global__ __launch_bounds__(256) void eig_orth_back(int U, const double* __rest
     if (bad) status[2 * u + 1] = 1;
     lds_barrier();
 
-    // Z' = Z M for the 16 columns: rows 32 wave ..+31
-    acc[0] = acc[1] = (f64x4){0.0, 0.0, 0.0, 0.0};
+    // Z' = Z M for the 16 columns: row tiles wave and wave + 4
+    f64x4 z[2];
+    z[0] = z[1] = (f64x4){0.0, 0.0, 0.0, 0.0};
 #pragma unroll 8
     for (int t = 0; t < 32; ++t) {
         const int i = 4 * t + g;
         const double bv = Ms[i * OB_MLD + n];
 #pragma unroll
         for (int q = 0; q < 2; ++q)
-            acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(Zs[i * OB_LD + 32 * wave + 16 * q + n], bv, acc[q], 0, 0, 0);
+            z[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(Zs[i * OB_LD + 16 * wave + 64 * q + n], bv, z[q], 0, 0, 0);
     }
     lds_barrier();
-#pragma unroll
-    for (int q = 0; q < 2; ++q)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) Ms[(32 * wave + 16 * q + 4 * r + g) * OB_MLD + n] = acc[q][r];
     // pairs left of block k / 32 of row k were not recorded
 #pragma unroll
     for (int i = 0; i < D * D / 512; ++i) {
         const int k = (tid >> 6) + 4 * i, p = (tid & 63) >> 4;
-        *(f64x2*)(Zs + 2 * (tid + 256 * i)) = k < D - 2 && p >= (k >> 5) ? stage[i] : (f64x2){0.0, 0.0};
+        const bool there = k < D - 2 && p >= (k >> 5);
+        double* d = Zs + k * OB_LD + 32 * p + (tid & 15);
+        d[0] = there ? stage[i].x : 0.0;
+        d[16] = there ? stage[i].y : 0.0;
     }
     lds_barrier();
-    // two quads of reflections per lane group: their inner products and coefficients
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int Q = (tid >> 4) + 16 * h;
-        f64x2 w[4][4];
-        double c[6];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int p = 0; p < 4; ++p) w[i][p] = *(const f64x2*)(Zs + (4 * Q + 3 - i) * D + (p * 16 + n) * 2);
-#pragma unroll
-        for (int i = 1; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < i; ++j) {
-                double t0 = 0.0, t1 = 0.0;
-#pragma unroll
-                for (int p = 0; p < 4; ++p) {
-                    t0 = fma(w[i][p].x, w[j][p].x, t0);
-                    t1 = fma(w[i][p].y, w[j][p].y, t1);
-                }
-                c[i * (i - 1) / 2 + j] = row16_sum_f64(t0 + t1);
-            }
-        if (n == 0) {
-            double* d = coef + Q * OB_CF;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) d[i] = nt[h][i];
-#pragma unroll
-            for (int i = 1; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < i; ++j) d[4 + i * (i - 1) / 2 + j] = nt[h][i] * c[i * (i - 1) / 2 + j];
-        }
-    }
-    __syncthreads();
-
-    const int cc = 4 * wave + g;            // 16 lanes per column, lane n: rows n + 16 m
-    double x[8];
-#pragma unroll
-    for (int m = 0; m < 8; ++m) x[m] = Ms[(n + 16 * m) * OB_MLD + cc];
-    f64x2 va[4][4], ca[5];
-    ob_load<7>(va, ca, Zs, coef, D / 4 - 1, n);
-    ob_reflect<7>(x, va, ca, Zs, coef, n);
-#pragma unroll
-    for (int m = 0; m < 8; ++m) Ms[(n + 16 * m) * OB_MLD + cc] = x[m];
-    __syncthreads();
-    const int row = tid >> 1, h = 8 * (tid & 1);
-    float4 o[2];
+    ob_block<7>(z, T, W + EIGW_T, Zs, Ms, wave, g, n);
+    float* R = R_out + (size_t)u * D * D + c0 + n;
 #pragma unroll
     for (int q = 0; q < 2; ++q)
-        o[q] = make_float4((float)Ms[row * OB_MLD + h + 4 * q], (float)Ms[row * OB_MLD + h + 4 * q + 1],
-                           (float)Ms[row * OB_MLD + h + 4 * q + 2], (float)Ms[row * OB_MLD + h + 4 * q + 3]);
-    float4* dst = (float4*)(R_out + (size_t)u * D * D + (size_t)row * D + c0 + h);
-    dst[0] = o[0];
-    dst[1] = o[1];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) R[(16 * wave + 64 * q + 4 * r + g) * D] = (float)z[q][r];
 }
 
 // ---------------------------------------------------------------------------
