@@ -189,10 +189,12 @@ void decode_plan(const rk_ctx* ctx, const rk_layout* L, int* S_out, int* tiles_o
 }
 
 // Splits of a dual decode (bf16 matrix-core kernels) that take text rows alone, next to the S of the cache: while compute
-// units are left over, one per 128 rows (a 32-row tile for each wave).  With the device full there are none and every
-// split takes a share of the text in front of its share of the cache.  Measured: 32 heads, 2880 tokens (S = 5 of 8 possible)
-// and 64 text rows 14 us shared, 12 us with a split of their own; 32 units x 16384 tokens (S = 8) and 1024 rows 39 us shared,
-// 45 us in work-groups of their own.
+// units are left over, one per 128 rows (a 32-row tile for each wave).  With the device full, a text of at most 128 rows
+// still gets one, which runs beside the cache's (but not where a unit has one split only: a second would be another round);
+// a longer one is shared, every split taking its part of it in front of its part of the cache.  Measured, shared against
+// apart: 32 heads x 2880 tokens (S = 5 of 8 possible) and 64 rows 14 / 12 us a token; 32 units x 16384 tokens (S = 8) and 64
+// rows 36.1 / 35.9 us, 37.2 / 36.6 us a token with the append, 200 rows 36.2 / 36.8, 1024 rows 39 / 45; 256 units x 4096 (S = 1) and
+// 64 rows 65.3 / 66.5.
 int text_splits(const rk_ctx* ctx, const rk_layout* L, int S, int text_rows)
 {
     if (ctx && ctx->decode_splits > 0) return 0;
@@ -202,7 +204,8 @@ int text_splits(const rk_ctx* ctx, const rk_layout* L, int S, int text_rows)
     const int rows128 = (int)(((int64_t)text_rows + 127) / 128);
     if (left > rows128) left = rows128;
     if (left > DECODE_TEXT_SPLITS_MAX) left = DECODE_TEXT_SPLITS_MAX;
-    return left > 0 ? (int)left : 0;
+    if (left <= 0) return S >= 2 && rows128 == 1 ? 1 : 0;
+    return (int)left;
 }
 
 hipStream_t as_stream(void* s) { return (hipStream_t)s; }

@@ -30,6 +30,7 @@ CASES = [
     (2, 20, 1, 500, [500, 129], 96, 140, [129, 65], 3),             # two head groups
     (2, 2, 1, 200, [200, 64], 16, 700, [700, 97], 1),               # a lone split
     (9, 16, 2, 900, [900] * 8 + [5], 48, 64, [64, 63, 0, 1, 2, 40, 50, 60, 33], 0),
+    (32, 8, 2, 2048, None, 32, 127, [(37 * i) % 128 for i in range(32)], 0),      # a full device, one split more
 ]
 
 
