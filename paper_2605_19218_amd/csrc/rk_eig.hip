@@ -341,8 +341,8 @@ static unsigned eig_slices(int U) { return 64u * (unsigned)((U + 7) / 8); }
 // least a factor 5e-13 but for one, so 16 stay above 1e-250) and the
 // interval shrinks 17-fold, 12 times: 2 / 17^12 = 3e-15.  T comes through the scalar cache, 8 rows ahead: one wave
 // per SIMD has nobody else to hide a load behind.
-// Vector by twisted factorisation, again without a division in the chain: lane 0 runs (T - lambda) y = 0 from the
-// top, lane 1 from the bottom, both rescaled every 8 steps (exponents kept per block of 8); the vector is the one above
+// Vector by twisted factorisation, again without a division in the chain: a lane of wave 0 runs (T - lambda) y = 0 from the
+// top, one of wave 1 from the bottom, both rescaled every 8 steps (exponents kept per block of 8); the vector is the one above
 // the row with the smallest twist gamma_i = (d_i - lambda) + e_{i-1} y_{i-1} / y_i + e_i x_{i+1} / x_i and the other below
 // it.  The second round runs at the Rayleigh-corrected eigenvalue, which leaves a residual of a few 1e-16.
 // 39000 cycles for the eigenvalues, about 8000 + 5000 for each round of chains and twist.
