@@ -759,14 +759,15 @@ __device__ __forceinline__ void compute_text_tile(TextTile& T, const TextRows& x
     mt = fmaxf(mt, __shfl_xor(mt, 16));
     mt = fmaxf(mt, __shfl_xor(mt, 32));
     const float m_new = fmaxf(m_run, mt);
-    const float alpha = fast_exp2(m_run - m_new);
+    const float m_ref = m_new > NEG_INF ? m_new : 0.f;       // every row so far may score -inf: no weight, not NaN
+    const float alpha = fast_exp2(m_run - m_ref);
     float psum = 0.f;
     bf16x8 ph, pl;
 #pragma unroll
     for (int tb = 0; tb < 2; ++tb)
 #pragma unroll
         for (int ii = 0; ii < 4; ++ii) {
-            const float p = fast_exp2(s[tb][ii] - m_new);
+            const float p = fast_exp2(s[tb][ii] - m_ref);
             psum += p;
             __bf16 hi, lo;
             split_bf16(p, hi, lo);
@@ -861,7 +862,7 @@ __device__ __forceinline__ void text_split(const bf16_t* __restrict__ q, const T
 #pragma unroll
         for (int w = 0; w < 4; ++w)
             if (text_parked(r0, r1, w)) {
-                const float x = fast_exp2(sm_m[w][hh] - M);
+                const float x = sm_m[w][hh] > NEG_INF ? fast_exp2(sm_m[w][hh] - M) : 0.f;
                 l = fmaf(sm_l[w][hh], x, l);
 #pragma unroll
                 for (int c2 = 0; c2 < 2; ++c2) acc[c2] = fmaf(park[w * 512 + (2 * wave + c2) * 64 + lane][ii], x, acc[c2]);
@@ -1254,7 +1255,8 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
                 if (hh < Gc) {
                     const size_t row = (size_t)b * Hq + h0 + hh;
                     const int c = 16 * cb + n;
-                    if (direct) out[row * D + c] = f32_to_bf16(acc[ii] / lh[ii]);
+                    // (an empty cache may stand beside text rows that all score -inf)
+                    if (direct) out[row * D + c] = f32_to_bf16(SHARED && !(Mh[ii] > NEG_INF) ? 0.f : acc[ii] / lh[ii]);
                     else ws_acc[(row * S + split) * D + c] = acc[ii];
                 }
             }

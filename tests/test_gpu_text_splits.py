@@ -99,3 +99,37 @@ def test_text_in_splits(ctx, case):
     finally:
         rk.rk_set_option(ctx, rk.RK_OPT_FUSE_MERGE, 1)
         rk.rk_set_option(ctx, rk.RK_OPT_DECODE_SPLITS, 0)
+
+
+# Rows whose score is minus infinity weigh nothing, also where they fill a whole tile, a wave's first one, or the text.
+@pytest.mark.parametrize("L,n,masked,splits", [
+    (700, 33, [32], 0), (700, 33, [32], 3), (200, 200, range(32), 1), (300, 200, range(32), 2), (300, 200, range(150), 0),
+    (300, 5, range(5), 0), (300, 5, range(5), 1), (0, 5, range(5), 1), (0, 40, range(40), 0),
+])
+def test_infinite_text_scores(ctx, L, n, masked, splits):
+    B, Hq, Hkv, r, cap = 1, 4, 2, 32, 256
+    data = layer(B, Hq, Hkv, max(L, 32), "bf16", 84, mean_shift=1.5)
+    p = run_prefill(ctx, data, B, Hq, Hkv, max(L, 32), r, "bf16", lengths=[L])
+    t, dk, dv, dlen = with_text(p, data, 85, cap, [n])
+    data["q"][..., 0] = 1.0
+    q = to_dev(data["q"], "bf16")
+    dk[:, :, list(masked), 0] = float("-inf")
+    left = [i for i in range(n) if i not in masked]
+    kept = {k: np.concatenate([t[k][:, :, left], t[k]], 2)[:, :, :max(len(left), 1)] for k in ("K", "V")}
+    want = want_dual(p, data["q"], [L], kept, [len(left)])
+    rk.rk_set_option(ctx, rk.RK_OPT_DECODE_SPLITS, splits)
+    try:
+        for fuse in (1, 0):
+            rk.rk_set_option(ctx, rk.RK_OPT_FUSE_MERGE, fuse)
+            ws = torch.empty(rk.rk_decode_workspace_size(ctx, p.layout()), device=DEV, dtype=torch.uint8)
+            rk.rk_decode_attn_dual(ctx, p.layout(), q, p.Kp, p.Vc, p.Rr, p.dmu, rk.Text(dk, dv, cap, len=dlen), 0.0, p.out, ws)
+            torch.cuda.synchronize()
+            got = to_host(p.out)
+            assert np.isfinite(got).all()
+            if L == 0 and not left:
+                assert not got.any()
+            else:
+                check_out(got, want, "bf16")
+    finally:
+        rk.rk_set_option(ctx, rk.RK_OPT_FUSE_MERGE, 1)
+        rk.rk_set_option(ctx, rk.RK_OPT_DECODE_SPLITS, 0)
