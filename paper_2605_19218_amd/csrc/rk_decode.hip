@@ -728,8 +728,9 @@ __device__ __forceinline__ void load_text_v(TextTile& T, const TextRows& x, int 
 
 __device__ __forceinline__ uint32_t text_dw(const uint4& v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
 
-// One tile; with MORE the Keys of the tile at row `next` are requested as soon as this tile's are used up, its Values at
-// the end.
+// One tile; with MORE the Keys of the tile at row `next` are requested once this tile's weights are made (any earlier they
+// would cost the widest kernel its last registers), its Values at the end.  The weights stay fp32: exp2f, and all 24 bits of
+// P through the matrix cores.
 template <bool MORE>
 __device__ __forceinline__ void compute_text_tile(TextTile& T, const TextRows& x, float& m_run, float& l_run, f32x4 (&O)[8],
                                                   const bf16x8 (&qf)[4], int row0, int r1, int next, float scale_log2, int lane)
@@ -743,7 +744,6 @@ __device__ __forceinline__ void compute_text_tile(TextTile& T, const TextRows& x
         for (int i = 0; i < 4; ++i) s[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(T.k[tb][i], qf[i], s[tb], 0, 0, 0);
         s[tb] *= scale_log2;
     }
-    if (MORE) load_text_k(T, x, next, lane);
     if (row0 + 32 > r1) {            // rows past the end: no weight, and no Values (they may hold anything)
 #pragma unroll
         for (int tb = 0; tb < 2; ++tb)
@@ -760,20 +760,23 @@ __device__ __forceinline__ void compute_text_tile(TextTile& T, const TextRows& x
     mt = fmaxf(mt, __shfl_xor(mt, 32));
     const float m_new = fmaxf(m_run, mt);
     const float m_ref = m_new > NEG_INF ? m_new : 0.f;       // every row so far may score -inf: no weight, not NaN
-    const float alpha = fast_exp2(m_run - m_ref);
+    const float alpha = exp2f(m_run - m_ref);
     float psum = 0.f;
-    bf16x8 ph, pl;
+    bf16x8 ph, pm, pl;               // P in three bf16 parts: all 24 bits of it
 #pragma unroll
     for (int tb = 0; tb < 2; ++tb)
 #pragma unroll
         for (int ii = 0; ii < 4; ++ii) {
-            const float p = fast_exp2(s[tb][ii] - m_ref);
+            const float p = exp2f(s[tb][ii] - m_ref);
             psum += p;
-            __bf16 hi, lo;
-            split_bf16(p, hi, lo);
+            __bf16 hi, mid, lo;
+            split3_bf16(p, hi, mid, lo);
             ph[4 * tb + ii] = hi;
+            pm[4 * tb + ii] = mid;
             pl[4 * tb + ii] = lo;
         }
+    __builtin_amdgcn_sched_barrier(0);
+    if (MORE) load_text_k(T, x, next, lane);
     l_run = fmaf(l_run, alpha, psum);
     if (__any(m_new > m_run)) {
         f32x4 a4;
@@ -792,8 +795,9 @@ __device__ __forceinline__ void compute_text_tile(TextTile& T, const TextRows& x
         d.z = __builtin_amdgcn_perm(text_dw(T.v[5], cb >> 1), text_dw(T.v[4], cb >> 1), sel);
         d.w = __builtin_amdgcn_perm(text_dw(T.v[7], cb >> 1), text_dw(T.v[6], cb >> 1), sel);
         const bf16x8 vf = __builtin_bit_cast(bf16x8, d);
-        O[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ph, vf, O[cb], 0, 0, 0);
         O[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pl, vf, O[cb], 0, 0, 0);
+        O[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pm, vf, O[cb], 0, 0, 0);
+        O[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ph, vf, O[cb], 0, 0, 0);
     }
     if (MORE) load_text_v(T, x, next, lane);
 }
@@ -862,7 +866,7 @@ __device__ __forceinline__ void text_split(const bf16_t* __restrict__ q, const T
 #pragma unroll
         for (int w = 0; w < 4; ++w)
             if (text_parked(r0, r1, w)) {
-                const float x = sm_m[w][hh] > NEG_INF ? fast_exp2(sm_m[w][hh] - M) : 0.f;
+                const float x = sm_m[w][hh] > NEG_INF ? exp2f(sm_m[w][hh] - M) : 0.f;
                 l = fmaf(sm_l[w][hh], x, l);
 #pragma unroll
                 for (int c2 = 0; c2 < 2; ++c2) acc[c2] = fmaf(park[w * 512 + (2 * wave + c2) * 64 + lane][ii], x, acc[c2]);
@@ -1144,14 +1148,13 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
         }
 
         f32x4* park = (f32x4*)big;                 // [4 waves][8 cb][64 lanes], then the text states alike
-        if constexpr (!SHARED || R < 64) load_tile<R>(TB, Ku, Vu, okB ? tokB : 0, okB ? lane : 0);
         if constexpr (SHARED) {
             // The text comes first: it needs the plain query only, its loads join those of the first cache tiles, and its state
-            // is parked before the streaming loop needs the registers.
+            // is parked before the streaming loop, and the second tile of the cache, need the registers.
             text_state(tr, r0, r1, qfrag, scale_log2, park + (4 + wave) * 512, sm_m[4 + wave], sm_l[4 + wave], wave, lane);
             store_row();
-            if constexpr (R >= 64) load_tile<R>(TB, Ku, Vu, okB ? tokB : 0, okB ? lane : 0);
         }
+        load_tile<R>(TB, Ku, Vu, okB ? tokB : 0, okB ? lane : 0);
 
         // B operands of the score MFMAs: q~ of head n, split into bf16 head + remainder
         bf16x8 qh[NFA], ql[NFA];
@@ -1232,7 +1235,7 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
 #pragma unroll
             for (int w = 0; w < NST; ++w) {
                 float mw = sm_m[w][hh] + (w < 4 ? bias : 0.f);
-                float x = (mw > NEG_INF) ? fast_exp2(mw - M) : 0.f;
+                float x = (mw > NEG_INF) ? (w < 4 ? fast_exp2(mw - M) : exp2f(mw - M)) : 0.f;
                 wgt[w][ii] = x;
                 lh[ii] = fmaf(sm_l[w][hh], x, lh[ii]);
             }

@@ -32,6 +32,14 @@ __device__ __forceinline__ void split_bf16(float x, __bf16& hi, __bf16& lo) {
     lo = (__bf16)(x - (float)hi);
 }
 
+// split an fp32 value into three bf16 parts that hold all of its 24 bits: x = hi + mid + lo (both remainders are exact)
+__device__ __forceinline__ void split3_bf16(float x, __bf16& hi, __bf16& mid, __bf16& lo) {
+    hi = (__bf16)x;
+    const float r = x - (float)hi;
+    mid = (__bf16)r;
+    lo = (__bf16)(r - (float)mid);
+}
+
 // Orders this wave's LDS writes before its later LDS reads by other lanes.  DS
 // operations of one wave execute in issue order, so only the compiler has to be
 // kept from moving them.

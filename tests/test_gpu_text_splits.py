@@ -2,6 +2,8 @@
 the splits, long text beside a short or an empty cache (more splits than the cache alone would take), one split that
 writes the output itself, several head groups, and the appended row taken from the inputs.  Against the oracle, bf16
 outputs within 2e-2 as everywhere in this suite; rows behind the end hold NaN patterns."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -133,3 +135,49 @@ def test_infinite_text_scores(ctx, L, n, masked, splits):
     finally:
         rk.rk_set_option(ctx, rk.RK_OPT_FUSE_MERGE, 1)
         rk.rk_set_option(ctx, rk.RK_OPT_DECODE_SPLITS, 0)
+
+
+def cancelling_rows():
+    """Scores and Values of a text whose output all but cancels, so that an error of the softmax weights shows: rows with the
+    largest remainders of a weight against a sum of two bf16 numbers, signs along them, and two rows that balance the sum."""
+    def bf16(x):
+        return float(torch.tensor(x, dtype=torch.float32).to(torch.bfloat16))
+
+    rows = []
+    for j in range(1, 256):                               # scores -j / 256
+        p = float(np.float32(np.exp(np.float64(-j / 256))))
+        rest = p - bf16(p)
+        rows.append(((rest - bf16(rest)) / p, -j / 256))
+    rows.sort()
+    pick = [(-1.0, s) for _, s in rows[:3]] + [(1.0, s) for _, s in rows[-3:]]
+    total = sum(v * math.exp(s) for v, s in pick)
+    for s in (0.0, -0.5):                                 # exp(0) has no remainder; the last Value is 2^-9 of the others
+        v = bf16(-total / math.exp(s))
+        pick.append((v, s))
+        total += v * math.exp(s)
+    v, s = np.array([x[0] for x in pick]), np.array([x[1] for x in pick])
+    p = np.exp(s)
+    return s, v, (p * v).sum() / p.sum(), (p * np.abs(v)).sum() / p.sum()
+
+
+@pytest.mark.parametrize("splits", [0, 1])
+def test_text_weights_keep_fp32(ctx, splits):
+    """Eight rows: a weight in fp32 is off by 2^-22 of itself at most (exp2 one place, the scaled score half a place of 1),
+    the sum by 8 2^-24, so 2^-20.4 of sum(p |v|) in all; 17-bit weights would be off by 2^-17.3 of it here."""
+    s, v, want, size = cancelling_rows()
+    p = Pipeline(ctx, 1, 1, 1, 16, "bf16", 32)
+    k, val = torch.zeros(1, 1, 8, D), torch.zeros(1, 1, 8, D)
+    k[0, 0, :, 0], val[0, 0] = torch.from_numpy(s), torch.from_numpy(v)[:, None].expand(8, D)
+    q = torch.zeros(1, 1, D)
+    q[..., 0] = 1.0
+    bf = dict(device=DEV, dtype=torch.bfloat16)
+    rk.rk_set_option(ctx, rk.RK_OPT_DECODE_SPLITS, splits)
+    try:
+        ws = torch.empty(rk.rk_decode_workspace_size(ctx, p.layout()), device=DEV, dtype=torch.uint8)
+        rk.rk_decode_attn_dual(ctx, p.layout(), q.to(**bf), p.Kp, p.Vc, p.Rr, None, rk.Text(k.to(**bf), val.to(**bf), 8), 1.0,
+                               p.out, ws)
+        torch.cuda.synchronize()
+    finally:
+        rk.rk_set_option(ctx, rk.RK_OPT_DECODE_SPLITS, 0)
+    err = np.abs(to_host(p.out) - want).max()
+    assert err <= 2.0 ** -20.4 * size + 2.0 ** -9 * abs(want), (err / size, want / size)
