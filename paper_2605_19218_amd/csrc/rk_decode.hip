@@ -1226,16 +1226,21 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
 #pragma unroll
         for (int ii = 0; ii < 4; ++ii) {
             const int hh = 4 * g + ii;
-            // (next to text scores the visual ones need their bias here; alone it is added to the stored maximum)
-            const float bias = SHARED ? sbias[hh] : 0.f;
-            float M = fmaxf(fmaxf(sm_m[0][hh], sm_m[1][hh]), fmaxf(sm_m[2][hh], sm_m[3][hh])) + bias;
-            if constexpr (SHARED)
+            // Next to text scores the visual ones need their bias here; alone it is added to the stored maximum.  The waves are
+            // weighed against each other without it: a large bias would round their differences away.
+            const float Mv = fmaxf(fmaxf(sm_m[0][hh], sm_m[1][hh]), fmaxf(sm_m[2][hh], sm_m[3][hh])), Mb = Mv + sbias[hh];
+            float M = Mb, f = 1.f;
+            if constexpr (SHARED) {
                 M = fmaxf(M, fmaxf(fmaxf(sm_m[4][hh], sm_m[5][hh]), fmaxf(sm_m[6][hh], sm_m[7][hh])));
-            Mh[ii] = SHARED ? M : M + sbias[hh];
+                f = Mv > NEG_INF ? exp2f(Mb - M) : 0.f;
+            }
+            Mh[ii] = M;
 #pragma unroll
             for (int w = 0; w < NST; ++w) {
-                float mw = sm_m[w][hh] + (w < 4 ? bias : 0.f);
-                float x = (mw > NEG_INF) ? (w < 4 ? fast_exp2(mw - M) : exp2f(mw - M)) : 0.f;
+                const float mw = sm_m[w][hh];
+                float x = 0.f;
+                if (mw > NEG_INF) x = w < 4 ? fast_exp2(mw - Mv) : exp2f(mw - M);
+                if (SHARED && w < 4) x *= f;
                 wgt[w][ii] = x;
                 lh[ii] = fmaf(sm_l[w][hh], x, lh[ii]);
             }

@@ -181,3 +181,26 @@ def test_text_weights_keep_fp32(ctx, splits):
         rk.rk_set_option(ctx, rk.RK_OPT_DECODE_SPLITS, 0)
     err = np.abs(to_host(p.out) - want).max()
     assert err <= 2.0 ** -20.4 * size + 2.0 ** -9 * abs(want), (err / size, want / size)
+
+
+@pytest.mark.parametrize("splits", [1, 2])
+def test_large_bias_beside_text(ctx, splits):
+    """A bias of 2^20 (log2 domain) leaves the cache's own softmax alone: with a text that weighs nothing the result is the
+    plain decode's, bit for bit."""
+    B, Hq, Hkv, L, r = 1, 4, 2, 600, 32
+    data = layer(B, Hq, Hkv, L, "bf16", 86)
+    p = run_prefill(ctx, data, B, Hq, Hkv, L, r, "bf16")
+    data["q"][..., 0] = 1.0
+    q = to_dev(data["q"], "bf16")
+    p.dmu.zero_()
+    p.dmu[..., 0] = 2.0 ** 20 / math.log2(math.e) * math.sqrt(D)
+    t, dk, dv, dlen = with_text(p, data, 87, 40, [40])
+    rk.rk_set_option(ctx, rk.RK_OPT_DECODE_SPLITS, splits)
+    try:
+        plain = p.decode(q).copy()
+        ws = torch.empty(rk.rk_decode_workspace_size(ctx, p.layout()), device=DEV, dtype=torch.uint8)
+        rk.rk_decode_attn_dual(ctx, p.layout(), q, p.Kp, p.Vc, p.Rr, p.dmu, rk.Text(dk, dv, 40, len=dlen), 0.0, p.out, ws)
+        torch.cuda.synchronize()
+    finally:
+        rk.rk_set_option(ctx, rk.RK_OPT_DECODE_SPLITS, 0)
+    assert np.array_equal(to_host(p.out), plain)
