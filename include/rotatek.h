@@ -231,9 +231,9 @@ typedef struct {
  * of the leading subspace, orthonormal up to the ridge, NOT eigenvectors one by
  * one: there are no eigenvalues, mask or keep_idx on this route); mu, delta_mu
  * [B,H_kv,d]; optionally cov [B,H_kv,d,d] and status [B,H_kv] (int32: 0, or t+1 if
- * iteration t met a non-positive Cholesky pivot, in which case that head's R_r and
- * delta_mu are undefined).  keep <= 104 (the basis and the Gram matrix stay in LDS
- * as doubles); larger keep: RK_ERR_UNSUPPORTED, use rk_fit_rotation.  Workspace as
+ * iteration t met a non-positive Cholesky pivot, as an empty sequence's does: that
+ * head's R_r is then zero and its delta_mu is mu).  keep <= 104 (the basis and the
+ * Gram matrix stay in LDS as doubles); larger keep: RK_ERR_UNSUPPORTED, use rk_fit_rotation.  Workspace as
  * rk_fit_rotation.  Errors: INVALID_ARG, UNSUPPORTED, WORKSPACE, HIP.          */
 rk_status rk_fit_subspace(rk_ctx* ctx, const rk_layout* L, const rk_rows* keys, const float* sigma,
                           uint32_t flags, const rk_subspace* solver, float* R_r, float* mu,

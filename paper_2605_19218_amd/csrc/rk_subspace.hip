@@ -285,6 +285,13 @@ __global__ __launch_bounds__(SUB_THREADS) void subspace_iter(const float* __rest
         lds_barrier();
     }
 
+    // a head that failed has no basis (its place holds Gram tiles): R_k = 0 and delta_mu = mu, so that an empty sequence of a
+    // ragged batch, whose Gram matrix is zero, stays finite when tokens are appended to it
+    if (fail) {
+        for (int idx = tid; idx < D * LDW; idx += SUB_THREADS) W[idx] = 0.0;
+        lds_barrier();
+    }
+
     // ---- outputs: R_k = V, delta_mu = mu - V V^T mu (Alg. 1 steps 14, 16) ----
     if (tid == 0 && status) status[u] = fail;
     for (int idx = tid; idx < D * k; idx += SUB_THREADS) {

@@ -133,3 +133,24 @@ def test_subspace_route_end_to_end(ctx):
             err_sub = max(err_sub, np.abs(out_sub[b, h] - full).max())
             err_eig = max(err_eig, np.abs(out_eig[b, h] - full).max())
     assert err_sub <= 1.5 * err_eig + 2e-2, (err_sub, err_eig)
+
+
+@pytest.mark.parametrize("k", [8, 40, 104])
+def test_empty_sequence_takes_appended_tokens(ctx, k):
+    """An empty sequence in a ragged batch has a zero Gram matrix and fails at its first pivot, ridge or not.  Its rotation is
+    zero, not leftovers of the factorisation, so the tokens that are appended to it later score 0 and are averaged."""
+    B, Hkv, L, dtype = 2, 2, 200, "bf16"
+    data = layer(B, Hkv, Hkv, L, dtype, 47)
+    Kd, Vd = to_dev(data["K"], dtype), to_dev(data["V"], dtype)
+    n_dev = torch.tensor([0, L], device=DEV, dtype=torch.int32)
+    V0 = start_basis(B, Hkv, k, 48)
+    p = Pipeline(ctx, B, Hkv, Hkv, k, dtype, L + 8)
+    p.Rr.fill_(float("nan"))
+    st = fit_subspace(ctx, p, Kd, L, V0, n_dev=n_dev)
+    assert st[0].tolist() == [1] * Hkv and not st[1].any()
+    assert not p.Rr[0].any() and torch.equal(p.dmu[0], p.mu[0])
+    p.compress(Kd, L, V_dev=Vd, n_dev=n_dev)
+    new = layer(B, Hkv, Hkv, 2, dtype, 49)
+    for t in range(2):
+        got = p.append_decode(to_dev(new["K"][:, :, t], dtype), to_dev(new["V"][:, :, t], dtype), to_dev(data["q"], dtype))
+    check_out(got[0], new["V"][0].mean(1), dtype)
