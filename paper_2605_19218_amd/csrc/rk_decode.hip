@@ -1358,10 +1358,11 @@ __device__ __forceinline__ void compute_tile_f32(DecTileF32<R>& T, float& m_run,
     mt = fmaxf(mt, __shfl_xor(mt, 16));
     mt = fmaxf(mt, __shfl_xor(mt, 32));
     const float m_new = fmaxf(m_run, mt);
-    const float alpha = exp2f(m_run - m_new);
+    const float m_ref = m_new > NEG_INF ? m_new : 0.f;       // every row so far may score -inf: no weight, not NaN
+    const float alpha = exp2f(m_run - m_ref);
     f32x4 p;
 #pragma unroll
-    for (int ii = 0; ii < 4; ++ii) p[ii] = exp2f(s[ii] - m_new);
+    for (int ii = 0; ii < 4; ++ii) p[ii] = exp2f(s[ii] - m_ref);
     l_run = fmaf(l_run, alpha, (p[0] + p[1]) + (p[2] + p[3]));
     if (__any(m_new > m_run)) {
         f32x4 a4;
@@ -1519,7 +1520,7 @@ __global__ __launch_bounds__(256, 2) void decode_split_f32(
         for (int ii = 0; ii < 4; ++ii)
             if (4 * g + ii < Gc) {
                 const size_t row = (size_t)b * Hq + h0 + 4 * g + ii;
-                if (out) out[row * D + 16 * cb + n] = acc[ii] / lh[ii];
+                if (out) out[row * D + 16 * cb + n] = Mh[ii] > NEG_INF ? acc[ii] / lh[ii] : 0.f;
                 else ws_acc[(row * S + split) * D + 16 * cb + n] = acc[ii];
             }
     }

@@ -116,6 +116,36 @@ def test_decode(ctx, case):
             assert not got[b].any()
 
 
+# Tokens whose score overflows to minus infinity weigh nothing, also where they fill a 16-token tile, a wave's first one,
+# or the cache (its output is then zero).
+@pytest.mark.parametrize("L,masked,splits", [(200, range(16), 1), (200, [199], 1), (97, [96], 2), (400, range(64), 3),
+                                             (400, range(256, 272), 1), (129, [128], 0), (40, range(40), 1), (300, range(300), 2)])
+def test_infinite_scores(ctx, L, masked, splits):
+    B, Hq, Hkv, r = 1, 4, 2, 16
+    data = layer(B, Hq, Hkv, L, "f32", 64)
+    data["K"][:, :, list(masked), :] = 0.0
+    data["K"][:, :, list(masked), 0] = -3e38
+    data["q"][..., 0] = 64.0
+    p = Pipeline(ctx, B, Hq, Hkv, r, "f32", L)
+    p.Rr.copy_(torch.eye(D, r, device=DEV).expand_as(p.Rr))
+    p.compress(to_dev(data["K"], "f32"), L, V_dev=to_dev(data["V"], "f32"))
+    q = to_dev(data["q"], "f32")
+    rk.rk_set_option(ctx, rk.RK_OPT_DECODE_SPLITS, splits)
+    try:
+        got = p.decode(q, use_bias=False).copy()
+    finally:
+        rk.rk_set_option(ctx, rk.RK_OPT_DECODE_SPLITS, 0)
+    left = [i for i in range(L) if i not in masked]
+    if not left:
+        assert not got.any()
+        return
+    Kt, V = p.unpacked()
+    want = oracle.decode_batch(data["q"].astype(np.float64), np.ascontiguousarray(Kt[:, :, left]),
+                               np.ascontiguousarray(V[:, :, left]), to_host(p.Rr), None,
+                               lens=np.asarray([len(left)], np.int32), scale=0.0)
+    check_out(got, want, "f32")
+
+
 def test_workspace_of_a_longer_input_serves_a_shorter_one():
     """Short inputs take shorter chunks: the workspace size must not fall as the bound on the rows grows."""
     for H in (1, 4, 32, 300, 600):
