@@ -332,6 +332,12 @@ __global__ __launch_bounds__(256) void compress_f32(RowsDev rows, int Hkv, int c
                 for (int tt = 0; tt < TT; ++tt)
                     acc[tt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], kb[tt][i][e], acc[tt], 0, 0, 0);
         }
+        if (16 * jb + 16 > r) {             // an infinity or NaN in a Key times the zeros there is NaN: the padding stays zero
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[tt][e] = 16 * jb + 4 * g + e < r ? acc[tt][e] : 0.f;
+        }
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt)
             if (w0 + 16 * tt + n < n_b)

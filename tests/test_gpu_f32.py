@@ -70,6 +70,22 @@ def test_compress_and_token_list(ctx, r):
         assert rel_max(cov[b, 1], oracle.mean_scatter(data["K"][b, 1], tok=rows)[1]) <= 1e-4
 
 
+@pytest.mark.parametrize("r", [1, 18, 37])
+def test_padding_of_non_finite_keys(ctx, r):
+    """The padding channels of a row are zero whatever its Key holds: as NaN they would reach every score of the row."""
+    L, rp = 40, (r + 15) // 16 * 16
+    p = Pipeline(ctx, 1, 1, 1, r, "f32", L)
+    p.Rr.copy_(torch.eye(D, r, device=DEV).expand_as(p.Rr))
+    p.Kp.fill_(0xff)
+    K = np.ones((1, 1, L, D), np.float32)
+    K[0, 0, 3, 0], K[0, 0, 21, 1], K[0, 0, 39, 127] = np.inf, np.nan, -np.inf
+    p.compress(to_dev(K, "f32"), L, V_dev=to_dev(np.ones_like(K), "f32"))
+    rows = p.Kp.view(torch.float32)[:48 * rp].view(3, rp // 8, 16, 8).permute(0, 2, 1, 3).reshape(48, rp)[:L]
+    assert not rows[:, r:].any()
+    rest = torch.ones(L, r, device=DEV)
+    assert torch.equal(rows[[0, 20, 38], :r], rest[:3])
+
+
 DECODE = [
     # B, Hq, Hkv, L, lengths, r, splits
     (6, 4, 2, 129, [129, 65, 64, 17, 16, 1], 64, 0),
