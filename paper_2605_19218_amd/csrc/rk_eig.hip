@@ -587,7 +587,9 @@ __global__ __launch_bounds__(256, 2) void eig_tri_vectors(int U, const double* _
 // R = Q Z after one Newton-Schulz step Z <- Z (3 I - Z^T Z) / 2; 16 columns per work-group of 4 waves.
 // The step is what makes independent vectors safe: neighbours a gap g apart come out orthogonal only to about
 // 1e-16 / g, the step squares that defect, and because each vector is an eigenvector to 1e-16 the correction mixes
-// close neighbours only and costs no residual.  A defect above 0.05 sends the matrix to Jacobi.
+// close neighbours only and costs no residual.  A defect E leaves (3/4) E^2 behind, so what the step may be given is bounded
+// by what the result is held to: an element above EIG_ORTH_MAX sends the matrix to Jacobi.  (Eigenvalues of T that stay
+// apart by the shift of 5e-13 give 6e-5 at most; above that two vectors have become one.)
 // Both products run on the fp64 matrix cores with all of Z in LDS; then Z's space takes the reflections, which were on
 // their way in registers meanwhile.  They are applied 16 at a time as I - V T V^T, again on the matrix cores, with the 16
 // columns of Z staying in result registers; T comes from eig_tri_vectors, where two waves have nothing else to do.
@@ -595,6 +597,8 @@ __global__ __launch_bounds__(256, 2) void eig_tri_vectors(int U, const double* _
 // (eight rounds of four dependent matrix steps, one exchange between the waves, eight more).  Four reflections at a time
 // on the vector unit: 20000 + 2500 for their inner products (LDS-bound, every lane group reads all of V), 23 us; one at a time
 // with loads where they are used: 56000 cycles in all, 27.7 us.  Now 18 us for 32 matrices, 257 for 512 (547 at first).
+constexpr double EIG_ORTH_MAX = 3e-4;
+static_assert(0.75 * D * EIG_ORTH_MAX * EIG_ORTH_MAX <= 1e-5, "|R^T R - I| <= 1e-5, every column of E at its limit");
 constexpr int OB_LD = D + 2, OB_MLD = 17;
 constexpr size_t OB_LDS_BYTES = (size_t)(D * OB_LD + D * OB_MLD) * sizeof(double);
 
@@ -701,7 +705,7 @@ __global__ __launch_bounds__(256) void eig_orth_back(int U, const double* __rest
         for (int r = 0; r < 4; ++r) {
             const int i = 32 * wave + 16 * q + 4 * r + g;
             const double dev = acc[q][r] - (i == c0 + n ? 1.0 : 0.0);
-            bad = bad || !(fabs(dev) < 0.05);
+            bad = bad || !(fabs(dev) < EIG_ORTH_MAX);
             Ms[i * OB_MLD + n] = (i == c0 + n ? 1.0 : 0.0) - 0.5 * dev;
         }
     if (bad) status[2 * u + 1] = 1;

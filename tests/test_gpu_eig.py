@@ -119,6 +119,27 @@ def test_jacobi(ctx, name):
     assert np.linalg.norm(R.T @ C @ R - np.diag(lam)) <= 1e-5 * np.linalg.norm(C)
 
 
+# A matrix whose tridiagonal form takes the solver's own shift of its diagonal back: a dense 4 x 4 block, and diagonal entries
+# that the shift brings to within `gap` of each other.  Vectors of equal eigenvalues become one, which only the check behind
+# the reduction can see; the matrix then goes to Jacobi.
+@pytest.mark.parametrize("gap", [0.0, 1e-15, 4e-15, 1e-14, 1e-13, 1e-12])
+def test_coinciding_eigenvalues(ctx, gap):
+    block = np.random.default_rng(5).standard_normal((6, D))
+    block[:, 4:] = 0.0
+    block *= np.sqrt(0.7 / np.linalg.norm(block.T @ block))           # Frobenius norm in [1/2, 1): the solver's scale is 1
+    i = np.arange(4, D)
+    single = np.zeros((D - 4, D))
+    single[i - 4, i] = np.sqrt(7e-11 - 5e-13 * (37 * i % D) + gap * (i - 4))
+    R, lam, C, sweeps, p = solve(ctx, np.vstack([block, single]))
+    if gap == 0.0:
+        assert 1 < sweeps < 20
+    assert np.abs(R.T @ R - np.eye(D)).max() <= 1e-5
+    assert np.linalg.norm(R.T @ C @ R - np.diag(lam)) <= 1e-5 * np.linalg.norm(C)
+    keep = p.keep_idx.cpu().numpy()[0, 0]
+    assert np.array_equal(keep, np.lexsort((np.arange(D), -lam))[:24])
+    assert np.array_equal(to_host(p.Rr)[0, 0], R[:, keep])
+
+
 def test_non_finite_keys(ctx):
     """A head with an infinity or a NaN in its Keys: no eigenproblem to solve; the call ends, the other heads are as ever."""
     K = np.stack([recipe(100), recipe(100), recipe(100)]).astype(np.float32)[None]
