@@ -143,16 +143,9 @@ rk_status check_text(rk_ctx* ctx, const rk_text* t, bool need_len)
     return RK_OK;
 }
 
-// N_s and the number of 128-token tiles they share (split s gets floor(tiles / N_s) tiles, the
-// last tiles % N_s splits one more)
-void decode_plan(const rk_ctx* ctx, const rk_layout* L, int* S_out, int* tiles_out)
+// N_s for `units` work-groups a split; splits of at least `tiles_min` 128-token tiles on long caches
+int plan_splits(const rk_ctx* ctx, long units, int tiles, int tiles_min)
 {
-    const int G = L->n_q_heads / L->n_kv_heads;
-    const bool mfma = use_mfma_decode(ctx, L);
-    const long units = mfma ? (long)L->batch * L->n_kv_heads * ((G + 15) / 16) : (long)L->batch * L->n_q_heads;
-    const int maxL = L->max_seq_len > 0 ? L->max_seq_len : 1;
-    const int tiles = (maxL + 127) / 128;
-    const int n_cu = ctx ? ctx->n_cu : 256;
     int S;
     if (ctx && ctx->decode_splits > 0) S = ctx->decode_splits;
     else {
@@ -160,7 +153,7 @@ void decode_plan(const rk_ctx* ctx, const rk_layout* L, int* S_out, int* tiles_o
         // after the first one's (measured: its prologue then ends 10 us later), and every work-group
         // pays its own prologue and partial
         // (rounded down: a few work-groups more than compute units would run as a second round)
-        long target = n_cu;
+        const long target = ctx ? ctx->n_cu : 256;
         S = (int)(target / units);
         if (S < 1) {
             // more units than compute units: a partly filled last round costs a whole round (320 units:
@@ -177,15 +170,42 @@ void decode_plan(const rk_ctx* ctx, const rk_layout* L, int* S_out, int* tiles_o
         // prologue and its partial: measured optimum on short caches and small batches.  Very short
         // caches (under 2K tokens) still gain from up to four splits of 256 tokens or more
         // (32 heads x 1024 tokens: 9.4 us with two splits, 8.2 us with four).
-        // (fp32 rows are twice as long: 256 tokens there)
-        const int cap_long = mfma && L->dtype == RK_F32 ? tiles / 2 : tiles / 4, cap_short = tiles / 2 < 4 ? tiles / 2 : 4;
+        const int cap_long = tiles / tiles_min, cap_short = tiles / 2 < 4 ? tiles / 2 : 4;
         const int cap = cap_long > cap_short ? cap_long : cap_short;
         if (S > cap) S = cap;
     }
     if (S > tiles) S = tiles;
-    if (S < 1) S = 1;
-    *S_out = S;
-    *tiles_out = tiles;
+    return S < 1 ? 1 : S;
+}
+
+// partials: the slots per (b, h_q) whose (m, l, acc[d]) the workspace holds, plus one score per row for a fused append
+size_t partial_bytes(const rk_layout* L, int slots)
+{
+    return align_up((size_t)L->batch * L->n_q_heads * ((size_t)slots * (D + 2) + 1) * sizeof(float), 256);
+}
+
+// N_s, the number of 128-token tiles they share (split s gets floor(tiles / N_s) tiles, the last tiles % N_s splits one
+// more) and the partials the workspace holds per (b, h_q)
+struct DecodePlan { int S, tiles, slots; };
+DecodePlan decode_plan(const rk_ctx* ctx, const rk_layout* L)
+{
+    const int G = L->n_q_heads / L->n_kv_heads;
+    const bool mfma = use_mfma_decode(ctx, L), f32 = mfma && L->dtype == RK_F32;
+    const long rows = (long)L->batch * L->n_q_heads, groups = (long)L->batch * L->n_kv_heads * ((G + 15) / 16);
+    DecodePlan p;
+    p.tiles = ((L->max_seq_len > 0 ? L->max_seq_len : 1) + 127) / 128;
+    // (fp32 rows are twice as long: splits of 256 tokens there)
+    p.S = plan_splits(ctx, mfma ? groups : rows, p.tiles, f32 ? 2 : 4);
+    p.slots = p.S + DECODE_TEXT_SPLITS_MAX;
+    if (f32) {
+        // The size of an fp32 workspace is that of the plain kernel's plan (a split count per query head), by which
+        // rk_decode_attn_static takes or refuses a shape: splits per KV head, up to 16 times as many, may not take it over
+        // the built-in scratch.  The text takes no splits here, so all slots are the cache's.
+        p.slots = plan_splits(ctx, rows, p.tiles, 4) + DECODE_TEXT_SPLITS_MAX;
+        while (p.S > p.slots && partial_bytes(L, p.S) > RK_STATIC_SCRATCH_BYTES) --p.S;
+        if (p.slots < p.S) p.slots = p.S;
+    }
+    return p;
 }
 
 // Splits of a dual decode (bf16 matrix-core kernels) that take text rows alone, next to the S of the cache: while compute
@@ -328,10 +348,7 @@ size_t rk_fit_workspace_size(const rk_layout* L, int32_t max_tokens)
 size_t rk_decode_workspace_size(const rk_ctx* ctx, const rk_layout* L)
 {
     if (check_layout(nullptr, L) != RK_OK) return 0;
-    int S, tiles;
-    decode_plan(ctx, L, &S, &tiles);
-    // (m, l, acc[d]) per split, for the dual path's plan too, plus one score per row for a fused append
-    return align_up((size_t)L->batch * L->n_q_heads * ((size_t)(S + DECODE_TEXT_SPLITS_MAX) * (D + 2) + 1) * sizeof(float), 256);
+    return partial_bytes(L, decode_plan(ctx, L).slots);
 }
 
 rk_status rk_decode_plan(const rk_ctx* ctx, const rk_layout* L, int32_t* n_splits, int32_t* tokens_per_split)
@@ -339,10 +356,9 @@ rk_status rk_decode_plan(const rk_ctx* ctx, const rk_layout* L, int32_t* n_split
     rk_status s = check_layout(nullptr, L);
     if (s != RK_OK) return s;
     if (!n_splits || !tokens_per_split) return RK_ERR_INVALID_ARG;
-    int S, tiles;
-    decode_plan(ctx, L, &S, &tiles);
-    *n_splits = S;
-    *tokens_per_split = 128 * ((tiles + S - 1) / S);      // the largest split
+    const DecodePlan p = decode_plan(ctx, L);
+    *n_splits = p.S;
+    *tokens_per_split = 128 * ((p.tiles + p.S - 1) / p.S);      // the largest split
     return RK_OK;
 }
 
@@ -616,12 +632,12 @@ static rk_status decode_common(rk_ctx* ctx, const rk_layout* L, const void* q, c
     DeviceGuard dev(ctx->device);
     hipError_t e = dev.status;
     if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
-    int S, tiles;
-    decode_plan(ctx, L, &S, &tiles);
+    const DecodePlan p = decode_plan(ctx, L);
+    const int S = p.S;
     const int St = text && L->dtype == RK_BF16 && use_mfma_decode(ctx, L) ? text_splits(ctx, L, S, td.max_len) : 0;
     const float sc = scale > 0.f ? scale : 1.0f / sqrtf((float)L->head_dim);
     e = launch_decode(L->dtype, use_mfma_decode(ctx, L), L->batch, L->n_q_heads, L->n_kv_heads, L->capacity,
-                      L->keep, S + St, S, tiles, q, k_packed, v_cache, R_r, delta_mu, L->seq_len, text ? &td : nullptr, nullptr,
+                      L->keep, S + St, S, p.tiles, q, k_packed, v_cache, R_r, delta_mu, L->seq_len, text ? &td : nullptr, nullptr,
                       tk_new ? &ta : nullptr, sc, out, (float*)workspace,
                       ctx->fuse_merge && ctx->xcd_deal_ok ? ctx->tickets + APP_TICKETS : nullptr, DEC_COUNTERS,
                       L->batch <= APP_TICKETS ? ctx->tickets : nullptr, as_stream(stream));
@@ -697,8 +713,7 @@ rk_status rk_append_decode_attn(rk_ctx* ctx, const rk_layout* L, const void* k_n
     hipError_t e = dev.status;
     if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
     hipStream_t st = as_stream(stream);
-    int S, tiles;
-    decode_plan(ctx, &La, &S, &tiles);
+    const DecodePlan p = decode_plan(ctx, &La);
     const float sc = scale > 0.f ? scale : 1.0f / sqrtf((float)L->head_dim);
     const bool mfma = use_mfma_decode(ctx, L);
     const AppendDev app{k_new, v_new, seq_len};
@@ -710,7 +725,7 @@ rk_status rk_append_decode_attn(rk_ctx* ctx, const rk_layout* L, const void* k_n
                           v_cache, seq_len, ctx->tickets, st);
         if (e != hipSuccess) return hip_fail(ctx, e, "append launch");
     }
-    e = launch_decode(L->dtype, mfma, L->batch, L->n_q_heads, L->n_kv_heads, L->capacity, L->keep, S, S, tiles, q,
+    e = launch_decode(L->dtype, mfma, L->batch, L->n_q_heads, L->n_kv_heads, L->capacity, L->keep, p.S, p.S, p.tiles, q,
                       k_packed, v_cache, R_r, delta_mu, seq_len, nullptr, fused ? &app : nullptr, nullptr, sc, out,
                       (float*)workspace, ctx->fuse_merge && ctx->xcd_deal_ok ? ctx->tickets + APP_TICKETS : nullptr,
                       DEC_COUNTERS, ctx->tickets, st);

@@ -282,3 +282,28 @@ def test_static_scratch_entry_validates_on_the_host(ctx):
     text = open(os.path.join(ROOT, "include", "rotatek.h")).read()
     m = re.search(r"#define RK_STATIC_SCRATCH_BYTES \((\d+)u << (\d+)\)", text)
     assert m and int(m.group(1)) << int(m.group(2)) == rk.RK_STATIC_SCRATCH_BYTES
+
+
+def test_fp32_shapes_keep_to_the_static_scratch(ctx):
+    """fp32 caches are split per KV head on the matrix cores and per query head by the plain kernels.  Which shapes
+    rk_decode_attn_static takes follows the latter on both, and a larger split count stays within what they hold."""
+    plain = rk.rk_create(rk.RK_DEVICE_NONE)
+    rk.rk_set_option(plain, rk.RK_OPT_FORCE_GENERIC, 1)
+    call = lambda c, lay: status_of(rk.rk_decode_attn_static, c, lay, PTR, PTR, PTR, PTR, None, 0.0, PTR)
+    limit, taken = rk.RK_STATIC_SCRATCH_BYTES, {rk.RK_ERR_NO_DEVICE: 0, rk.RK_ERR_WORKSPACE: 0}
+    try:
+        for B in (1, 2, 3, 8, 20, 40, 55, 56, 57, 64, 100, 200):
+            for Hq, Hkv in ((1, 1), (8, 8), (32, 8), (28, 4), (32, 2), (40, 1), (64, 4)):
+                for L in (0, 100, 300, 1000, 3000, 5000, 33000, 100000):
+                    lay = layout(dtype=rk.RK_F32, batch=B, n_q_heads=Hq, n_kv_heads=Hkv, capacity=(L + 63) // 32 * 32, max_seq_len=L)
+                    size, was = rk.rk_decode_workspace_size(ctx, lay), rk.rk_decode_workspace_size(plain, lay)
+                    st = call(ctx, lay)
+                    assert st == call(plain, lay) == (rk.RK_ERR_NO_DEVICE if size <= limit else rk.RK_ERR_WORKSPACE)
+                    assert was <= size <= max(was, limit)
+                    assert rk.rk_decode_plan(ctx, lay)[0] * 130 * 4 * B * Hq <= size
+                    taken[st] += 1
+        assert min(taken.values()) > 50
+        lay = layout(dtype=rk.RK_F32, batch=55, n_q_heads=32, n_kv_heads=8, capacity=3008, max_seq_len=3000)
+        assert call(ctx, lay) == rk.RK_ERR_NO_DEVICE
+    finally:
+        rk.rk_destroy(plain)
