@@ -744,15 +744,17 @@ __device__ __forceinline__ void compute_text_tile(TextTile& T, const TextRows& x
         for (int i = 0; i < 4; ++i) s[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(T.k[tb][i], qf[i], s[tb], 0, 0, 0);
         s[tb] *= scale_log2;
     }
-    if (row0 + 32 > r1) {            // rows past the end: no weight, and no Values (they may hold anything)
+    if (!MORE && row0 + 32 > r1) {   // rows past the end: no weight, and no Values (they may hold anything)
 #pragma unroll
         for (int tb = 0; tb < 2; ++tb)
 #pragma unroll
-            for (int ii = 0; ii < 4; ++ii)
-                if (row0 + 16 * tb + 4 * g + ii >= r1) {
-                    s[tb][ii] = NEG_INF;
-                    T.v[4 * tb + ii] = make_uint4(0, 0, 0, 0);
-                }
+            for (int ii = 0; ii < 4; ++ii) {
+                const bool in = row0 + 16 * tb + 4 * g + ii < r1;
+                const uint32_t keep = in ? ~0u : 0u;             // (masked bits: a condition per row became a branch per row)
+                uint4& v = T.v[4 * tb + ii];
+                v = make_uint4(v.x & keep, v.y & keep, v.z & keep, v.w & keep);
+                s[tb][ii] = in ? s[tb][ii] : NEG_INF;
+            }
     }
     float mt = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])),
                      fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3])));
@@ -803,8 +805,8 @@ __device__ __forceinline__ void compute_text_tile(TextTile& T, const TextRows& x
 }
 
 // This wave's share of text rows [r0, r1) as a softmax state: accumulators to `park` ([8 cb][64 lanes] in the layout of the
-// visual states), maximum and sum (log2 domain) to sm_m, sm_l [16].  The last wave takes the first tile: it has the fewest
-// tiles of the cache.
+// visual states), maximum and sum (log2 domain) to sm_m, sm_l [16]; -inf and zeros without a row.  The last wave takes the
+// first tile: it has the fewest tiles of the cache.
 __device__ __forceinline__ void text_state(const TextRows& tr, int r0, int r1, const bf16x8 (&qf)[4], float scale_log2,
                                            f32x4* __restrict__ park, float* __restrict__ sm_m, float* __restrict__ sm_l,
                                            int wave, int lane)
@@ -829,11 +831,12 @@ __device__ __forceinline__ void text_state(const TextRows& tr, int r0, int r1, c
         // channel 8 n + cb goes to where channel 16 cb' + n' of the visual layout lies
 #pragma unroll
         for (int cb = 0; cb < 8; ++cb) park[(n >> 1) * 64 + 16 * g + 8 * (n & 1) + cb] = O[cb];
+    } else {
+#pragma unroll
+        for (int cb = 0; cb < 8; ++cb) park[cb * 64 + lane] = (f32x4){0.f, 0.f, 0.f, 0.f};
     }
     if (g == 0) { sm_m[n] = m_run; sm_l[n] = l_run; }
 }
-// whether wave w has left a text state behind
-__device__ __forceinline__ bool text_parked(int r0, int r1, int w) { return r0 + 32 * (3 - w) < r1; }
 
 // The appended row goes into the segment: 16 lanes, 16 bytes of Key and Value each.  No work-group of the launch reads it
 // from there.
@@ -856,25 +859,32 @@ __device__ __forceinline__ void text_split(const bf16_t* __restrict__ q, const T
 #pragma unroll
     for (int i = 0; i < 4; ++i) qf[i] = *(const bf16x8*)(qr + 32 * i);
     text_state(tr, r0, r1, qf, scale_log2, park + wave * 512, sm_m[wave], sm_l[wave], wave, lane);
-    __syncthreads();
+    lds_barrier();
+    f32x4 w[4], l = (f32x4){0.f, 0.f, 0.f, 0.f}, M = l;                  // lane (g, n): heads 4 g ..+3
+#pragma unroll
+    for (int k = 0; k < 4; ++k) w[k] = *(const f32x4*)&sm_m[k][4 * g];
 #pragma unroll
     for (int ii = 0; ii < 4; ++ii) {
-        const int hh = 4 * g + ii;
-        if (hh >= Gc) continue;
-        const float M = fmaxf(fmaxf(sm_m[0][hh], sm_m[1][hh]), fmaxf(sm_m[2][hh], sm_m[3][hh]));
-        float l = 0.f, acc[2] = {0.f, 0.f};
+        M[ii] = fmaxf(fmaxf(w[0][ii], w[1][ii]), fmaxf(w[2][ii], w[3][ii]));
 #pragma unroll
-        for (int w = 0; w < 4; ++w)
-            if (text_parked(r0, r1, w)) {
-                const float x = sm_m[w][hh] > NEG_INF ? exp2f(sm_m[w][hh] - M) : 0.f;
-                l = fmaf(sm_l[w][hh], x, l);
+        for (int k = 0; k < 4; ++k) w[k][ii] = w[k][ii] > NEG_INF ? exp2f(w[k][ii] - M[ii]) : 0.f;
+    }
 #pragma unroll
-                for (int c2 = 0; c2 < 2; ++c2) acc[c2] = fmaf(park[w * 512 + (2 * wave + c2) * 64 + lane][ii], x, acc[c2]);
-            }
-        const size_t pidx = (row0 + hh) * S + split;
+    for (int k = 0; k < 4; ++k) l += *(const f32x4*)&sm_l[k][4 * g] * w[k];
+    f32x4 acc[2];
 #pragma unroll
-        for (int c2 = 0; c2 < 2; ++c2) ws_acc[pidx * D + 16 * (2 * wave + c2) + n] = acc[c2];
-        if (wave == 0 && n == 0) { ws_m[pidx] = M; ws_l[pidx] = l; }      // (no rows: -inf and zeros)
+    for (int c2 = 0; c2 < 2; ++c2) {
+        acc[c2] = park[(2 * wave + c2) * 64 + lane] * w[0];
+#pragma unroll
+        for (int k = 1; k < 4; ++k) acc[c2] += park[k * 512 + (2 * wave + c2) * 64 + lane] * w[k];
+    }
+#pragma unroll
+    for (int ii = 0; ii < 4; ++ii) {
+        if (4 * g + ii >= Gc) continue;
+        const size_t pidx = (row0 + 4 * g + ii) * S + split;
+#pragma unroll
+        for (int c2 = 0; c2 < 2; ++c2) ws_acc[pidx * D + 16 * (2 * wave + c2) + n] = acc[c2][ii];
+        if (wave == 0 && n == 0) { ws_m[pidx] = M[ii]; ws_l[pidx] = l[ii]; }      // (no rows: -inf and zeros)
     }
 }
 
@@ -904,7 +914,7 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
     __shared__ __attribute__((aligned(16))) float qt[16][R + 4];     // rows 16 bytes apart in the banks: lanes of a wave index the row
     __shared__ float sbias[16];
     __shared__ __attribute__((aligned(16))) float sdm[D];
-    __shared__ float sm_m[NST][16], sm_l[NST][16];
+    __shared__ __attribute__((aligned(16))) float sm_m[NST][16], sm_l[NST][16];
     __shared__ int sm_last;
     const bool direct = out != nullptr;     // the only split of a single-path call writes the result itself
     // Fused frozen-R append (k_new != NULL; the host guarantees G < 16 and never combines it
@@ -964,333 +974,327 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
         if (tr.add && r0 == 0 && r1 > 0 && grp == 0 && tid < 16) text_store_row(tr, ta, b, hk, tid);
     };
     if constexpr (TEXT == TEXT_APART) {
-        if (split >= Sv) {                 // no part of the cache: nothing of what follows is needed
+        // no part of the cache: nothing of what follows is needed (marked unlikely, so that the cache's code stays in line)
+        if (__builtin_expect(split >= Sv, 0)) {
             text_share(text.len ? text.len[b] : text.max_len, split - Sv, S - Sv);
             text_split(q, tr, r0, r1, (size_t)b * Hq + h0, Gc, split, S, scale_log2, (f32x4*)big, sm_m, sm_l, ws_m, ws_l,
                        ws_acc, tid);
             store_row();
-            if constexpr (FUSED)
-                fold_unit<false>(unit, S, b, u, Hq, h0, Gc, ws_m, ws_l, ws_acc, out_merged, done, ta.k != nullptr,
-                                 batch_tickets, Hkv * ngrp * S, ta.len, min(ta.capacity, text.max_len), nullptr, nullptr,
-                                 &sm_last);
-            return;
         }
     }
+    if (TEXT != TEXT_APART || __builtin_expect(split < Sv, 1)) {
+        // ---- everything that does not need seq_len goes out first -----------------------------
+        // The sequence length costs a cold round trip to memory; the prologue operands (q, this
+        // thread's R_r pieces, delta_mu) and the first tile of every wave are requested before
+        // it is used.  The tile prefetch is speculative: it assumes the split is full and only
+        // checks that the tile lies inside the cache slab; rows past the real end are masked or
+        // skipped later (the prologue is on the kernel's critical path: while it runs only the
+        // prefetched tiles keep the memory system busy).
+        const int seq_raw = seq_len[b];
+        const int text_raw = SHARED ? (text.len ? text.len[b] : text.max_len) : 0;
+        // balanced partition of the 128-token tiles: the LAST (tiles % S) splits get one tile more (the
+        // final tile of a cache is usually only partly filled, so the longer shares belong at the end)
+        // (with TEXT_APART the cache is left to the first Sv splits)
+        const int nv = TEXT == TEXT_APART ? Sv : S;
+        const int tp = tiles_all / nv, trem = tiles_all - tp * nv;
+        const int t0 = 128 * (split * tp + max(split - (nv - trem), 0));
+        const int t1_full = 128 * ((split + 1) * tp + max(split + 1 - (nv - trem), 0));
+        const bf16_t* Ku = Kp + (size_t)u * slab_tokens(cap) * R;
+        const bf16_t* Vu = Vc + (size_t)u * slab_tokens(cap) * D;
 
-    // ---- everything that does not need seq_len goes out first -----------------------------
-    // The sequence length costs a cold round trip to memory; the prologue operands (q, this
-    // thread's R_r pieces, delta_mu) and the first tile of every wave are requested before
-    // it is used.  The tile prefetch is speculative: it assumes the split is full and only
-    // checks that the tile lies inside the cache slab; rows past the real end are masked or
-    // skipped later (the prologue is on the kernel's critical path: while it runs only the
-    // prefetched tiles keep the memory system busy).
-    const int seq_raw = seq_len[b];
-    const int text_raw = SHARED ? (text.len ? text.len[b] : text.max_len) : 0;
-    // balanced partition of the 128-token tiles: the LAST (tiles % S) splits get one tile more (the
-    // final tile of a cache is usually only partly filled, so the longer shares belong at the end)
-    // (with TEXT_APART the cache is left to the first Sv splits)
-    const int nv = TEXT == TEXT_APART ? Sv : S;
-    const int tp = tiles_all / nv, trem = tiles_all - tp * nv;
-    const int t0 = 128 * (split * tp + max(split - (nv - trem), 0));
-    const int t1_full = 128 * ((split + 1) * tp + max(split + 1 - (nv - trem), 0));
-    const bf16_t* Ku = Kp + (size_t)u * slab_tokens(cap) * R;
-    const bf16_t* Vu = Vc + (size_t)u * slab_tokens(cap) * D;
-
-    // prologue operands, in matrix-core layout (lane (g, n)):
-    //   qfrag[i]     B operand: q of head n, channels 32 i + 8 g ..+7 (q is bf16: exact);
-    //   ra[bw][i][.] A operand: R_r^T block jb = wave + 4 bw: column 16 jb + n of R_r, the same
-    //                channels (fp32, split into a bf16 head + remainder pair before use);
-    constexpr int NJB = R / 16;                    // 16-column blocks of R_r
-    constexpr int NBW = (NJB + 3) / 4;             // blocks per wave
-    const float* Ru = Rr + (size_t)u * D * r;
-    bf16x8 qfrag[4];
-    float ra[NBW][4][8];
-    float dmv;                                     // delta_mu goes through LDS (one value per thread)
-    {
-        // Every load below is unconditional (indices clamped, the value discarded afterwards): a load
-        // under a per-lane condition compiles to a branch, and past a branch the compiler no longer knows
-        // how many loads are outstanding, so the first use of R_r would wait for the tile prefetch too
-        // (a round trip to HBM under full load instead of an L2 hit).
-        const bool newcol = app && n == 15;
-        const bf16_t* qrow = newcol ? k_new + (size_t)u * D + 8 * g
-                                    : q + ((size_t)b * Hq + h0 + min(n, Gc - 1)) * D + 8 * g;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) qfrag[i] = *(const bf16x8*)(qrow + 32 * i);
-#pragma unroll
-        for (int bw = 0; bw < NBW; ++bw) {
-            const int col = min(16 * (wave + 4 * bw) + n, r - 1);
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int jj = 0; jj < 8; ++jj) ra[bw][i][jj] = Ru[(32 * i + 8 * g + jj) * r + col];
-        }
-        const float* dp = dmu ? dmu + (size_t)u * D : Ru;     // any readable address when there is no bias
-        dmv = dp[tid & (D - 1)];
-    }
-
-    Tile TA, TB;
-#pragma unroll
-    for (int tb = 0; tb < 2; ++tb) {
-        TA.kt[tb] = (s16x4){0, 0, 0, 0};
-        TB.kt[tb] = (s16x4){0, 0, 0, 0};
-#pragma unroll
-        for (int i = 0; i < NFA; ++i) {
-            TA.kf[tb][i] = (bf16x8){0, 0, 0, 0, 0, 0, 0, 0};
-            TB.kf[tb][i] = (bf16x8){0, 0, 0, 0, 0, 0, 0, 0};
-        }
-    }
-#pragma unroll
-    for (int cb = 0; cb < 8; ++cb) {
-        TA.vf[cb] = (bf16x8){0, 0, 0, 0, 0, 0, 0, 0};
-        TB.vf[cb] = (bf16x8){0, 0, 0, 0, 0, 0, 0, 0};
-    }
-    // This wave's tiles are wave, wave + 4, ...; tile k starts at tokA + 128 k.  Only the first is
-    // requested here: the compute unit's queue of memory requests is full within a microsecond of
-    // the launch, so a second tile ahead of the prologue would only delay the wave on its way to
-    // the q~ arithmetic (the instructions issue in order); it follows right behind that arithmetic.
-    // Unconditional like the prologue loads: a tile outside the split is "loaded" with every lane on
-    // one 16-byte piece of the slab's first tile and never computed.
-    const int tokA = t0 + wave * 32, tokB = tokA + 128;
-    const int t_spec = min(t1_full, cap);          // the slab ends at cap (a multiple of 32)
-    const bool okA = tokA + 32 <= t_spec, okB = tokB + 32 <= t_spec;
-    load_tile<R>(TA, Ku, Vu, okA ? tokA : 0, okA ? lane : 0);
-
-    const int L = min(max(seq_raw, 0), cap);
-    const int t1 = min(t1_full, L);
-    const bool empty = t0 >= t1;
-    const bool app_here = app && split == 0;       // this work-group stores and scores the new row
-    const bool app_ok = seq_raw >= 0 && seq_raw < cap;
-    if constexpr (SHARED) text_share(text_raw, split, S);
-
-    if (!empty || app_here || (SHARED && r0 < r1)) {
-        const int ntiles = (t1 - t0 + 31) >> 5;
-        const int nk = (ntiles - wave + 3) >> 2;
-
-        // ---- q~ = q R_r scaled into the log2 domain, and the bias ----------------------
-        // On the matrix cores: D[j][h] = sum_c R_r[c][j] q[h][c], one 16-column block of R_r per
-        // wave and pass, R_r as bf16 head + remainder (two MFMAs per 32 channels).  Lane (g, n)
-        // ends up with q~[head n][16 jb + 4 g + 0..3]: one 16-byte store to LDS, one barrier.
+        // prologue operands, in matrix-core layout (lane (g, n)):
+        //   qfrag[i]     B operand: q of head n, channels 32 i + 8 g ..+7 (q is bf16: exact);
+        //   ra[bw][i][.] A operand: R_r^T block jb = wave + 4 bw: column 16 jb + n of R_r, the same
+        //                channels (fp32, split into a bf16 head + remainder pair before use);
+        constexpr int NJB = R / 16;                    // 16-column blocks of R_r
+        constexpr int NBW = (NJB + 3) / 4;             // blocks per wave
+        const float* Ru = Rr + (size_t)u * D * r;
+        bf16x8 qfrag[4];
+        float ra[NBW][4][8];
+        float dmv;                                     // delta_mu goes through LDS (one value per thread)
         {
-            // discard what the clamped prologue loads fetched for heads and columns that do not exist
-            if (!(n < Gc || (app && n == 15))) {
+            // Every load below is unconditional (indices clamped, the value discarded afterwards): a load
+            // under a per-lane condition compiles to a branch, and past a branch the compiler no longer knows
+            // how many loads are outstanding, so the first use of R_r would wait for the tile prefetch too
+            // (a round trip to HBM under full load instead of an L2 hit).
+            const bool newcol = app && n == 15;
+            const bf16_t* qrow = newcol ? k_new + (size_t)u * D + 8 * g
+                                        : q + ((size_t)b * Hq + h0 + min(n, Gc - 1)) * D + 8 * g;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) qfrag[i] = (bf16x8){0, 0, 0, 0, 0, 0, 0, 0};
-            }
-#pragma unroll
-            for (int bw = 0; bw < NBW; ++bw)
-                if (16 * (wave + 4 * bw) + n >= r) {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-#pragma unroll
-                        for (int jj = 0; jj < 8; ++jj) ra[bw][i][jj] = 0.f;
-                }
-            if (tid < D) sdm[tid] = dmu ? dmv : 0.f;
+            for (int i = 0; i < 4; ++i) qfrag[i] = *(const bf16x8*)(qrow + 32 * i);
 #pragma unroll
             for (int bw = 0; bw < NBW; ++bw) {
-                const int jb = wave + 4 * bw;
-                if (jb < NJB) {
-                    f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f};
+                const int col = min(16 * (wave + 4 * bw) + n, r - 1);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        bf16x8 ah, al;
+                for (int i = 0; i < 4; ++i)
 #pragma unroll
-                        for (int jj = 0; jj < 8; ++jj) {
-                            __bf16 hi, lo;
-                            split_bf16(ra[bw][i][jj], hi, lo);
-                            ah[jj] = hi;
-                            al[jj] = lo;
-                        }
-                        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, qfrag[i], acc, 0, 0, 0);
-                        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, qfrag[i], acc, 0, 0, 0);
-                    }
-                    *(f32x4*)&qt[n][16 * jb + 4 * g] = acc * ((app && n == 15) ? 1.f : scale_log2);
-                }
+                    for (int jj = 0; jj < 8; ++jj) ra[bw][i][jj] = Ru[(32 * i + 8 * g + jj) * r + col];
+            }
+            const float* dp = dmu ? dmu + (size_t)u * D : Ru;     // any readable address when there is no bias
+            dmv = dp[tid & (D - 1)];
+        }
+
+        Tile TA, TB;
+#pragma unroll
+        for (int tb = 0; tb < 2; ++tb) {
+            TA.kt[tb] = (s16x4){0, 0, 0, 0};
+            TB.kt[tb] = (s16x4){0, 0, 0, 0};
+#pragma unroll
+            for (int i = 0; i < NFA; ++i) {
+                TA.kf[tb][i] = (bf16x8){0, 0, 0, 0, 0, 0, 0, 0};
+                TB.kf[tb][i] = (bf16x8){0, 0, 0, 0, 0, 0, 0, 0};
             }
         }
-        __syncthreads();
-        if (wave == 0) {                           // bias b_n = q_n . delta_mu, needed only at the end
-            float bpart = 0.f;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const f32x4 d0 = *(const f32x4*)&sdm[32 * i + 8 * g], d1 = *(const f32x4*)&sdm[32 * i + 8 * g + 4];
+        for (int cb = 0; cb < 8; ++cb) {
+            TA.vf[cb] = (bf16x8){0, 0, 0, 0, 0, 0, 0, 0};
+            TB.vf[cb] = (bf16x8){0, 0, 0, 0, 0, 0, 0, 0};
+        }
+        // This wave's tiles are wave, wave + 4, ...; tile k starts at tokA + 128 k.  Only the first is
+        // requested here: the compute unit's queue of memory requests is full within a microsecond of
+        // the launch, so a second tile ahead of the prologue would only delay the wave on its way to
+        // the q~ arithmetic (the instructions issue in order); it follows right behind that arithmetic.
+        // Unconditional like the prologue loads: a tile outside the split is "loaded" with every lane on
+        // one 16-byte piece of the slab's first tile and never computed.
+        const int tokA = t0 + wave * 32, tokB = tokA + 128;
+        const int t_spec = min(t1_full, cap);          // the slab ends at cap (a multiple of 32)
+        const bool okA = tokA + 32 <= t_spec, okB = tokB + 32 <= t_spec;
+        constexpr bool V_LATE = SHARED && R > 96;      // (the widest kernels have no registers for them beside a text tile)
+        if constexpr (V_LATE) load_tile_k<R>(TA, Ku, okA ? tokA : 0, okA ? lane : 0);
+        else load_tile<R>(TA, Ku, Vu, okA ? tokA : 0, okA ? lane : 0);
+
+        const int L = min(max(seq_raw, 0), cap);
+        const int t1 = min(t1_full, L);
+        const bool empty = t0 >= t1;
+        const bool app_here = app && split == 0;       // this work-group stores and scores the new row
+        const bool app_ok = seq_raw >= 0 && seq_raw < cap;
+        if constexpr (SHARED) text_share(text_raw, split, S);
+
+        if (!empty || app_here || (SHARED && r0 < r1)) {
+            const int ntiles = (t1 - t0 + 31) >> 5;
+            const int nk = (ntiles - wave + 3) >> 2;
+
+            // ---- q~ = q R_r scaled into the log2 domain, and the bias ----------------------
+            // On the matrix cores: D[j][h] = sum_c R_r[c][j] q[h][c], one 16-column block of R_r per
+            // wave and pass, R_r as bf16 head + remainder (two MFMAs per 32 channels).  Lane (g, n)
+            // ends up with q~[head n][16 jb + 4 g + 0..3]: one 16-byte store to LDS, one barrier.
+            {
+                // discard what the clamped prologue loads fetched for heads and columns that do not exist
+                if (!(n < Gc || (app && n == 15))) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) qfrag[i] = (bf16x8){0, 0, 0, 0, 0, 0, 0, 0};
+                }
+#pragma unroll
+                for (int bw = 0; bw < NBW; ++bw)
+                    if (16 * (wave + 4 * bw) + n >= r) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+#pragma unroll
+                            for (int jj = 0; jj < 8; ++jj) ra[bw][i][jj] = 0.f;
+                    }
+                if (tid < D) sdm[tid] = dmu ? dmv : 0.f;
+#pragma unroll
+                for (int bw = 0; bw < NBW; ++bw) {
+                    const int jb = wave + 4 * bw;
+                    if (jb < NJB) {
+                        f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            bf16x8 ah, al;
+#pragma unroll
+                            for (int jj = 0; jj < 8; ++jj) {
+                                __bf16 hi, lo;
+                                split_bf16(ra[bw][i][jj], hi, lo);
+                                ah[jj] = hi;
+                                al[jj] = lo;
+                            }
+                            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, qfrag[i], acc, 0, 0, 0);
+                            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, qfrag[i], acc, 0, 0, 0);
+                        }
+                        *(f32x4*)&qt[n][16 * jb + 4 * g] = acc * ((app && n == 15) ? 1.f : scale_log2);
+                    }
+                }
+            }
+            __syncthreads();
+            if (wave == 0) {                           // bias b_n = q_n . delta_mu, needed only at the end
+                float bpart = 0.f;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const f32x4 d0 = *(const f32x4*)&sdm[32 * i + 8 * g], d1 = *(const f32x4*)&sdm[32 * i + 8 * g + 4];
+#pragma unroll
+                    for (int jj = 0; jj < 4; ++jj) {
+                        bpart = fmaf((float)qfrag[i][jj], d0[jj], bpart);
+                        bpart = fmaf((float)qfrag[i][jj + 4], d1[jj], bpart);
+                    }
+                }
+                bpart += __shfl_xor(bpart, 16);
+                bpart += __shfl_xor(bpart, 32);
+                if (g == 0) sbias[n] = bpart * scale_log2;
+                if (app_here) {
+                    // score of the new row against every head, with the row rounded to storage
+                    // precision exactly as later steps will read it
+                    float sp = 0.f;
+#pragma unroll
+                    for (int jq = 0; jq < R / 16; ++jq) {
+                        const f32x4 a = *(const f32x4*)&qt[n][16 * jq + 4 * g], kx = *(const f32x4*)&qt[15][16 * jq + 4 * g];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) sp = fmaf(a[e], bf16_to_f32(f32_to_bf16(kx[e])), sp);
+                    }
+                    sp += __shfl_xor(sp, 16);
+                    sp += __shfl_xor(sp, 32);
+                    if (g == 0 && n < Gc)
+                        ws_snew[(size_t)b * Hq + h0 + n] = app_ok ? fmaf(bpart, scale_log2, sp) : NEG_INF;
+                }
+            } else if (app_here && app_ok && grp == 0) {
+                if (wave == 1) {
+                    for (int j = lane; j < R; j += 64)
+                        Kp[(size_t)u * slab_tokens(cap) * R + kidx(seq_raw, j, R)] = f32_to_bf16(qt[15][j]);
+                } else {
+                    const int c = tid - 128;
+                    Vc[(size_t)u * slab_tokens(cap) * D + vidx(seq_raw, c)] = v_new[(size_t)u * D + c];
+                }
+            }
+
+            f32x4* park = (f32x4*)big;                 // [4 waves][8 cb][64 lanes], then the text states alike
+            if constexpr (SHARED) {
+                // The text comes first: it needs the plain query only, its loads join those of the first cache tiles, and its state
+                // is parked before the streaming loop, and the second tile of the cache, need the registers.
+                text_state(tr, r0, r1, qfrag, scale_log2, park + (4 + wave) * 512, sm_m[4 + wave], sm_l[4 + wave], wave, lane);
+                store_row();
+            }
+            if constexpr (V_LATE) load_tile_v<R>(TA, Vu, okA ? tokA : 0, okA ? lane : 0);
+            load_tile<R>(TB, Ku, Vu, okB ? tokB : 0, okB ? lane : 0);
+
+            // B operands of the score MFMAs: q~ of head n, split into bf16 head + remainder
+            bf16x8 qh[NFA], ql[NFA];
+            s16x4 qth = (s16x4){0, 0, 0, 0}, qtl = (s16x4){0, 0, 0, 0};
+#pragma unroll
+            for (int i = 0; i < NFA; ++i) {
+                qh[i] = (bf16x8){0, 0, 0, 0, 0, 0, 0, 0};
+                ql[i] = qh[i];
+            }
+#pragma unroll
+            for (int i = 0; i < NF; ++i) {
+#pragma unroll
+                for (int jj = 0; jj < 8; ++jj) {
+                    __bf16 hi, lo;
+                    split_bf16(qt[n][32 * i + 8 * g + jj], hi, lo);
+                    qh[i][jj] = hi;
+                    ql[i][jj] = lo;
+                }
+            }
+            if (TAIL) {
 #pragma unroll
                 for (int jj = 0; jj < 4; ++jj) {
-                    bpart = fmaf((float)qfrag[i][jj], d0[jj], bpart);
-                    bpart = fmaf((float)qfrag[i][jj + 4], d1[jj], bpart);
+                    __bf16 hi, lo;
+                    split_bf16(qt[n][32 * NF + 4 * g + jj], hi, lo);
+                    qth[jj] = __builtin_bit_cast(short, hi);
+                    qtl[jj] = __builtin_bit_cast(short, lo);
                 }
             }
-            bpart += __shfl_xor(bpart, 16);
-            bpart += __shfl_xor(bpart, 32);
-            if (g == 0) sbias[n] = bpart * scale_log2;
-            if (app_here) {
-                // score of the new row against every head, with the row rounded to storage
-                // precision exactly as later steps will read it
-                float sp = 0.f;
-#pragma unroll
-                for (int jq = 0; jq < R / 16; ++jq) {
-                    const f32x4 a = *(const f32x4*)&qt[n][16 * jq + 4 * g], kx = *(const f32x4*)&qt[15][16 * jq + 4 * g];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) sp = fmaf(a[e], bf16_to_f32(f32_to_bf16(kx[e])), sp);
-                }
-                sp += __shfl_xor(sp, 16);
-                sp += __shfl_xor(sp, 32);
-                if (g == 0 && n < Gc)
-                    ws_snew[(size_t)b * Hq + h0 + n] = app_ok ? fmaf(bpart, scale_log2, sp) : NEG_INF;
-            }
-        } else if (app_here && app_ok && grp == 0) {
-            if (wave == 1) {
-                for (int j = lane; j < R; j += 64)
-                    Kp[(size_t)u * slab_tokens(cap) * R + kidx(seq_raw, j, R)] = f32_to_bf16(qt[15][j]);
-            } else {
-                const int c = tid - 128;
-                Vc[(size_t)u * slab_tokens(cap) * D + vidx(seq_raw, c)] = v_new[(size_t)u * D + c];
-            }
-        }
 
-        f32x4* park = (f32x4*)big;                 // [4 waves][8 cb][64 lanes], then the text states alike
-        if constexpr (SHARED) {
-            // The text comes first: it needs the plain query only, its loads join those of the first cache tiles, and its state
-            // is parked before the streaming loop, and the second tile of the cache, need the registers.
-            text_state(tr, r0, r1, qfrag, scale_log2, park + (4 + wave) * 512, sm_m[4 + wave], sm_l[4 + wave], wave, lane);
-            store_row();
-        }
-        load_tile<R>(TB, Ku, Vu, okB ? tokB : 0, okB ? lane : 0);
+            DecState<R> st;
+            st.m_run = NEG_INF;
+            st.l_run = 0.f;
+#pragma unroll
+            for (int cb = 0; cb < 8; ++cb) st.O[cb] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
-        // B operands of the score MFMAs: q~ of head n, split into bf16 head + remainder
-        bf16x8 qh[NFA], ql[NFA];
-        s16x4 qth = (s16x4){0, 0, 0, 0}, qtl = (s16x4){0, 0, 0, 0};
-#pragma unroll
-        for (int i = 0; i < NFA; ++i) {
-            qh[i] = (bf16x8){0, 0, 0, 0, 0, 0, 0, 0};
-            ql[i] = qh[i];
-        }
-#pragma unroll
-        for (int i = 0; i < NF; ++i) {
-#pragma unroll
-            for (int jj = 0; jj < 8; ++jj) {
-                __bf16 hi, lo;
-                split_bf16(qt[n][32 * i + 8 * g + jj], hi, lo);
-                qh[i][jj] = hi;
-                ql[i][jj] = lo;
+            // Steady state: two tiles of loads always in flight behind the tile being computed.
+            // No branch around the loads here, so the compiler's outstanding-load counts
+            // (s_waitcnt vmcnt) are exact and a wave never waits for its newest prefetch.
+            int k = 0;
+            for (; k + 3 < nk; k += 2) {
+                compute_tile<R>(TA, st, qh, ql, qth, qtl, tokA + 128 * k, t1, g);
+                load_tile<R>(TA, Ku, Vu, tokA + 128 * (k + 2), lane);
+                compute_tile<R>(TB, st, qh, ql, qth, qtl, tokA + 128 * (k + 1), t1, g);
+                load_tile<R>(TB, Ku, Vu, tokA + 128 * (k + 3), lane);
             }
-        }
-        if (TAIL) {
-#pragma unroll
-            for (int jj = 0; jj < 4; ++jj) {
-                __bf16 hi, lo;
-                split_bf16(qt[n][32 * NF + 4 * g + jj], hi, lo);
-                qth[jj] = __builtin_bit_cast(short, hi);
-                qtl[jj] = __builtin_bit_cast(short, lo);
+            // tail: up to three tiles left (A, B, A)
+            if (k < nk) {
+                compute_tile<R>(TA, st, qh, ql, qth, qtl, tokA + 128 * k, t1, g);
+                if (k + 2 < nk) load_tile<R>(TA, Ku, Vu, tokA + 128 * (k + 2), lane);
             }
-        }
+            if (k + 1 < nk) compute_tile<R>(TB, st, qh, ql, qth, qtl, tokA + 128 * (k + 1), t1, g);
+            if (k + 2 < nk) compute_tile<R>(TA, st, qh, ql, qth, qtl, tokA + 128 * (k + 2), t1, g);
 
-        DecState<R> st;
-        st.m_run = NEG_INF;
-        st.l_run = 0.f;
+            // ---- merge the four waves' states ----------------------------------------------
+            // Every wave holds O in the same lane layout, so the exchange is lane-to-lane: each
+            // lane parks its 8 accumulator quads in LDS ([wave][cb][lane], 128-bit, conflict
+            // free); wave w then folds channel blocks 2w, 2w+1 of all four waves and stores the
+            // result straight from the MFMA layout (lane (g, n): heads 4g..4g+3, channel 16cb+n).
+            float l_run = st.l_run;
+            l_run += __shfl_xor(l_run, 16);
+            l_run += __shfl_xor(l_run, 32);
 #pragma unroll
-        for (int cb = 0; cb < 8; ++cb) st.O[cb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            for (int cb = 0; cb < 8; ++cb) park[(wave * 8 + cb) * 64 + lane] = st.O[cb];
+            if (g == 0) { sm_m[wave][n] = st.m_run; sm_l[wave][n] = l_run; }
+            __syncthreads();
 
-        // Steady state: two tiles of loads always in flight behind the tile being computed.
-        // No branch around the loads here, so the compiler's outstanding-load counts
-        // (s_waitcnt vmcnt) are exact and a wave never waits for its newest prefetch.
-        int k = 0;
-        for (; k + 3 < nk; k += 2) {
-            compute_tile<R>(TA, st, qh, ql, qth, qtl, tokA + 128 * k, t1, g);
-            load_tile<R>(TA, Ku, Vu, tokA + 128 * (k + 2), lane);
-            compute_tile<R>(TB, st, qh, ql, qth, qtl, tokA + 128 * (k + 1), t1, g);
-            load_tile<R>(TB, Ku, Vu, tokA + 128 * (k + 3), lane);
-        }
-        // tail: up to three tiles left (A, B, A)
-        if (k < nk) {
-            compute_tile<R>(TA, st, qh, ql, qth, qtl, tokA + 128 * k, t1, g);
-            if (k + 2 < nk) load_tile<R>(TA, Ku, Vu, tokA + 128 * (k + 2), lane);
-        }
-        if (k + 1 < nk) compute_tile<R>(TB, st, qh, ql, qth, qtl, tokA + 128 * (k + 1), t1, g);
-        if (k + 2 < nk) compute_tile<R>(TA, st, qh, ql, qth, qtl, tokA + 128 * (k + 2), t1, g);
-
-        // ---- merge the four waves' states ----------------------------------------------
-        // Every wave holds O in the same lane layout, so the exchange is lane-to-lane: each
-        // lane parks its 8 accumulator quads in LDS ([wave][cb][lane], 128-bit, conflict
-        // free); wave w then folds channel blocks 2w, 2w+1 of all four waves and stores the
-        // result straight from the MFMA layout (lane (g, n): heads 4g..4g+3, channel 16cb+n).
-        float l_run = st.l_run;
-        l_run += __shfl_xor(l_run, 16);
-        l_run += __shfl_xor(l_run, 32);
-#pragma unroll
-        for (int cb = 0; cb < 8; ++cb) park[(wave * 8 + cb) * 64 + lane] = st.O[cb];
-        if (g == 0) { sm_m[wave][n] = st.m_run; sm_l[wave][n] = l_run; }
-        __syncthreads();
-
-        f32x4 wgt[NST];                            // weight of state w for heads 4g + ii
-        f32x4 Mh, lh = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ii = 0; ii < 4; ++ii) {
-            const int hh = 4 * g + ii;
-            // Next to text scores the visual ones need their bias here; alone it is added to the stored maximum.  The waves are
-            // weighed against each other without it: a large bias would round their differences away.
-            const float Mv = fmaxf(fmaxf(sm_m[0][hh], sm_m[1][hh]), fmaxf(sm_m[2][hh], sm_m[3][hh])), Mb = Mv + sbias[hh];
-            float M = Mb, f = 1.f;
-            if constexpr (SHARED) {
-                M = fmaxf(M, fmaxf(fmaxf(sm_m[4][hh], sm_m[5][hh]), fmaxf(sm_m[6][hh], sm_m[7][hh])));
-                f = Mv > NEG_INF ? exp2f(Mb - M) : 0.f;
-            }
-            Mh[ii] = M;
-#pragma unroll
-            for (int w = 0; w < NST; ++w) {
-                const float mw = sm_m[w][hh];
-                float x = 0.f;
-                if (mw > NEG_INF) x = w < 4 ? fast_exp2(mw - Mv) : exp2f(mw - M);
-                if (SHARED && w < 4) x *= f;
-                wgt[w][ii] = x;
-                lh[ii] = fmaf(sm_l[w][hh], x, lh[ii]);
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int cb = 2 * wave + k;
-            f32x4 acc = park[(0 * 8 + cb) * 64 + lane] * wgt[0];
-#pragma unroll
-            for (int w = 1; w < 4; ++w) acc += park[(w * 8 + cb) * 64 + lane] * wgt[w];
-            if constexpr (SHARED) {
-                // (waves without a text tile have left nothing behind)
-#pragma unroll
-                for (int w = 4; w < NST; ++w)
-                    if (text_parked(r0, r1, w - 4)) acc += park[(w * 8 + cb) * 64 + lane] * wgt[w];
-            }
+            f32x4 wgt[NST];                            // weight of state w for heads 4g + ii
+            f32x4 Mh, lh = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int ii = 0; ii < 4; ++ii) {
                 const int hh = 4 * g + ii;
-                if (hh < Gc) {
-                    const size_t row = (size_t)b * Hq + h0 + hh;
-                    const int c = 16 * cb + n;
-                    // (an empty cache may stand beside text rows that all score -inf)
-                    if (direct) out[row * D + c] = f32_to_bf16(SHARED && !(Mh[ii] > NEG_INF) ? 0.f : acc[ii] / lh[ii]);
-                    else ws_acc[(row * S + split) * D + c] = acc[ii];
+                // Next to text scores the visual ones need their bias here; alone it is added to the stored maximum.  The waves are
+                // weighed against each other without it: a large bias would round their differences away.
+                const float Mv = fmaxf(fmaxf(sm_m[0][hh], sm_m[1][hh]), fmaxf(sm_m[2][hh], sm_m[3][hh])), Mb = Mv + sbias[hh];
+                float M = Mb, f = 1.f;
+                if constexpr (SHARED) {
+                    M = fmaxf(M, fmaxf(fmaxf(sm_m[4][hh], sm_m[5][hh]), fmaxf(sm_m[6][hh], sm_m[7][hh])));
+                    f = Mv > NEG_INF ? exp2f(Mb - M) : 0.f;
                 }
-            }
-        }
-        if (!direct && wave == 0 && n == 0) {        // lanes (g, 0): m and l of heads 4g..4g+3
+                Mh[ii] = M;
 #pragma unroll
-            for (int ii = 0; ii < 4; ++ii) {
-                const int hh = 4 * g + ii;
-                if (hh < Gc) {
-                    const size_t pidx = ((size_t)b * Hq + h0 + hh) * S + split;
-                    ws_m[pidx] = Mh[ii];
-                    ws_l[pidx] = lh[ii];
+                for (int w = 0; w < NST; ++w) {
+                    const float mw = sm_m[w][hh];
+                    float x = 0.f;
+                    if (mw > NEG_INF) x = w < 4 ? fast_exp2(mw - Mv) : exp2f(mw - M);
+                    if (SHARED && w < 4) x *= f;
+                    wgt[w][ii] = x;
+                    lh[ii] = fmaf(sm_l[w][hh], x, lh[ii]);
                 }
             }
-        }
-    } else {
-        // ---- empty split: zeros with m = -inf (or zeros to `out` if it is the only split) ----
-        for (int idx = tid; idx < Gc * D; idx += 256) {
-            int hh = idx >> 7, c = idx & 127;
-            const size_t row = (size_t)b * Hq + h0 + hh;
-            if (out != nullptr) {
-                out[row * D + c] = f32_to_bf16(0.f);
-            } else {
-                const size_t pidx = row * S + split;
-                ws_acc[pidx * D + c] = 0.f;
-                if (c == 0) { ws_m[pidx] = NEG_INF; ws_l[pidx] = 0.f; }
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int cb = 2 * wave + k;
+                f32x4 acc = park[(0 * 8 + cb) * 64 + lane] * wgt[0];
+#pragma unroll
+                for (int w = 1; w < NST; ++w) acc += park[(w * 8 + cb) * 64 + lane] * wgt[w];
+#pragma unroll
+                for (int ii = 0; ii < 4; ++ii) {
+                    const int hh = 4 * g + ii;
+                    if (hh < Gc) {
+                        const size_t row = (size_t)b * Hq + h0 + hh;
+                        const int c = 16 * cb + n;
+                        // (an empty cache may stand beside text rows that all score -inf)
+                        if (direct) out[row * D + c] = f32_to_bf16(SHARED && !(Mh[ii] > NEG_INF) ? 0.f : acc[ii] / lh[ii]);
+                        else ws_acc[(row * S + split) * D + c] = acc[ii];
+                    }
+                }
+            }
+            if (!direct && wave == 0 && n == 0) {        // lanes (g, 0): m and l of heads 4g..4g+3
+#pragma unroll
+                for (int ii = 0; ii < 4; ++ii) {
+                    const int hh = 4 * g + ii;
+                    if (hh < Gc) {
+                        const size_t pidx = ((size_t)b * Hq + h0 + hh) * S + split;
+                        ws_m[pidx] = Mh[ii];
+                        ws_l[pidx] = lh[ii];
+                    }
+                }
+            }
+        } else {
+            // ---- empty split: zeros with m = -inf (or zeros to `out` if it is the only split) ----
+            for (int idx = tid; idx < Gc * D; idx += 256) {
+                int hh = idx >> 7, c = idx & 127;
+                const size_t row = (size_t)b * Hq + h0 + hh;
+                if (out != nullptr) {
+                    out[row * D + c] = f32_to_bf16(0.f);
+                } else {
+                    const size_t pidx = row * S + split;
+                    ws_acc[pidx * D + c] = 0.f;
+                    if (c == 0) { ws_m[pidx] = NEG_INF; ws_l[pidx] = 0.f; }
+                }
             }
         }
     }
@@ -1666,12 +1670,15 @@ hipError_t launch_decode(int dtype, bool mfma, int B, int Hq, int Hkv, int cap, 
                            (float*)out, (const float*)nullptr, (const float*)nullptr, Hq, Hkv, cap,
                            (int32_t*)nullptr, (int32_t*)nullptr, 0);
     } else {
-        // with a fused append the split launch has stored the new rows: the lengths move here
-        hipLaunchKernelGGL((decode_merge<bf16_t, 16>), dim3((unsigned)rows), dim3(128), 0, st, ws_m, ws_l, ws_acc, S,
-                           (bf16_t*)out, app ? (const float*)ws_snew : (const float*)nullptr,
-                           app ? (const bf16_t*)app->v_new : (const bf16_t*)nullptr, Hq, Hkv, cap,
-                           app ? app->seq_len : (int32_t*)nullptr, tapp ? tapp->len : (int32_t*)nullptr,
-                           tapp ? (tapp->capacity < text->max_len ? tapp->capacity : text->max_len) : 0);
+        // With a fused append the split launch has stored the new rows: the lengths move here.  Beside text 24 partials a
+        // round (64 splits of the cache and the text's are three rounds to the L2, not five).
+        const float* sn = app ? (const float*)ws_snew : nullptr;
+        const bf16_t* vn = app ? (const bf16_t*)app->v_new : nullptr;
+        int32_t *len = app ? app->seq_len : nullptr, *tlen = tapp ? tapp->len : nullptr;
+        const int tcap = tapp ? (tapp->capacity < text->max_len ? tapp->capacity : text->max_len) : 0;
+        const auto merge = text ? decode_merge<bf16_t, 24> : decode_merge<bf16_t, 16>;
+        hipLaunchKernelGGL(merge, dim3((unsigned)rows), dim3(128), 0, st, ws_m, ws_l, ws_acc, S, (bf16_t*)out, sn, vn, Hq, Hkv,
+                           cap, len, tlen, tcap);
     }
     return hipGetLastError();
 }
