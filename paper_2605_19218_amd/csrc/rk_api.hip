@@ -208,24 +208,37 @@ DecodePlan decode_plan(const rk_ctx* ctx, const rk_layout* L)
     return p;
 }
 
-// Splits of a dual decode (bf16 matrix-core kernels) that take text rows alone, next to the S of the cache: while compute
-// units are left over, one per 128 rows (a 32-row tile for each wave).  With the device full, a text of at most 128 rows
-// still gets one, which runs beside the cache's (but not where a unit has one split only: a second would be another round);
-// a longer one is shared, every split taking its part of it in front of its part of the cache.  Measured, shared against
-// apart: 32 heads x 2880 tokens (S = 5 of 8 possible) and 64 rows 14 / 12 us a token; 32 units x 16384 tokens (S = 8) and 64
-// rows 36.1 / 35.9 us, 37.2 / 36.6 us a token with the append, 200 rows 36.2 / 36.8, 1024 rows 39 / 45; 256 units x 4096 (S = 1) and
-// 64 rows 65.3 / 66.5.
+// Splits of a dual decode (bf16 matrix-core kernels) that take text rows alone, next to the S of the cache; 0: every split
+// takes its part of the text in front of its part of the cache.
 int text_splits(const rk_ctx* ctx, const rk_layout* L, int S, int text_rows)
 {
-    if (ctx && ctx->decode_splits > 0) return 0;
+    if ((ctx && ctx->decode_splits > 0) || text_rows <= 0) return 0;
     const int G = L->n_q_heads / L->n_kv_heads;
-    const long units = (long)L->batch * L->n_kv_heads * ((G + 15) / 16);
-    long left = (ctx ? ctx->n_cu : 256) / units - S;
-    const int rows128 = (int)(((int64_t)text_rows + 127) / 128);
-    if (left > rows128) left = rows128;
-    if (left > DECODE_TEXT_SPLITS_MAX) left = DECODE_TEXT_SPLITS_MAX;
-    if (left <= 0) return S >= 2 && rows128 == 1 ? 1 : 0;
-    return (int)left;
+    const long units = (long)L->batch * L->n_kv_heads * ((G + 15) / 16), n_cu = ctx ? ctx->n_cu : 256;
+    const long left = n_cu / units - S, room = 2 * n_cu / units - S;      // to one and to two work-groups a compute unit
+    auto pieces = [&](int rows) { return (long)(((int64_t)text_rows + rows - 1) / rows); };
+    auto least = [](long a, long b) { return (int)(a < b ? a : b); };
+    if (left >= 1) {
+        // compute units are left over: a split per 128 rows (a 32-row tile for each wave), but no more than are left ...
+        if (pieces(128) <= left) return least(pieces(128), DECODE_TEXT_SPLITS_MAX);
+        // ... unless each would then read more than twice what a split of the cache does: the launch waits for them
+        // (32 units x 3700 tokens, S = 7, 1500 rows: 22.2 us with one, 17.3 with eight; 500 rows: 13.8 / 15.0).  Next to one split
+        // a unit the text is most of the launch, and second work-groups pay later (128 x 256 tokens, 1024 rows: 16.7 us with
+        // one, 17.9 with three; 1500 rows: 25.8 / 23.1).
+        const double text = 512.0 * text_rows / (double)left;
+        const double cache = (double)L->max_seq_len / S * 2.0 * (keep_padded(L->keep) + D);
+        if (text <= (S == 1 ? 6.0 : 2.0) * cache) return least(left, DECODE_TEXT_SPLITS_MAX);
+        return least(least(pieces(128), room), DECODE_TEXT_SPLITS_MAX);
+    }
+    // The device is full.  One split a unit: its text in a second one would be another round (256 x 4096 tokens, 64 rows: 64.8 us
+    // shared, 66.9 apart).
+    if (S == 1) return 0;
+    // A split per 64 rows, run beside the cache's as a second work-group a compute unit (32 x 8192 tokens: 200 rows 20.4 us in four
+    // splits, 21.0 shared, 21.6 in vector code as before; 1500 rows 23.2 / 23.6 / 24.6).
+    if (room >= 1) return least(least(pieces(64), room), DECODE_TEXT_SPLITS_MAX);
+    // several rounds: more work-groups pay while the text is short (320 x 1024 tokens, S = 4: 200 rows 33.6 us with one split, 37.1
+    // shared; 1024 rows 59 / 57)
+    return pieces(256) <= 2 ? (int)pieces(256) : 0;
 }
 
 hipStream_t as_stream(void* s) { return (hipStream_t)s; }

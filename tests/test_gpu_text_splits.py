@@ -33,6 +33,10 @@ CASES = [
     (2, 2, 1, 200, [200, 64], 16, 700, [700, 97], 1),               # a lone split
     (9, 16, 2, 900, [900] * 8 + [5], 48, 64, [64, 63, 0, 1, 2, 40, 50, 60, 33], 0),
     (32, 8, 2, 2048, None, 32, 127, [(37 * i) % 128 for i in range(32)], 0),      # a full device, one split more
+    (16, 8, 8, 1024, None, 16, 300, [300 - 17 * i for i in range(16)], 0),        # a full device, two splits more
+    (8, 4, 4, 3700, None, 32, 1500, [1500, 1499, 0, 1, 1400, 33, 700, 65], 0),     # one unit in seven left, eight splits
+    (40, 8, 8, 600, [600 - 13 * i for i in range(40)], 16, 300, [7 * i for i in range(40)], 0),    # several rounds, two splits
+    (40, 8, 8, 600, None, 16, 600, [600 - 15 * i for i in range(40)], 0),         # several rounds, shared
 ]
 
 
