@@ -638,62 +638,84 @@ hipError_t launch_cov_finalize(int dtype, bool mfma, const RowsDev& rows, int B,
 
 // ---------------------------------------------------------------------------
 // Alg. 1 step 4: sigma_j = ||(Q_W)_{:,j}||_2 over the window of recent queries, pooled over the G query heads that
-// share a KV head.  One 1024-thread work-group per (b, h_kv): a row of 128 channels is read by 128 / VEC lanes, VEC
+// share a KV head.  One work-group per (b, h_kv), of 1024 threads unless there are many: a row of 128 channels is read by 128 / VEC lanes, VEC
 // elements (16 bytes where base and strides allow it, else one) each, and the other lanes take other rows, so that a
 // window of 7 x 32 rows is four loads per thread, all out together.  (One thread per channel walking the rows two at a
 // time: 30-51 us for 32 work-groups of 224 rows, a memory round trip for every pair of rows; now 4 us.)
-constexpr int SIG_THREADS = 1024;
-template <typename T, int VEC>
-__global__ __launch_bounds__(SIG_THREADS) void sigma_window_kernel(const T* __restrict__ qw, int64_t sb, int64_t sh,
+template <typename T, int VEC, int THREADS>
+__global__ __launch_bounds__(THREADS) void sigma_window_kernel(const T* __restrict__ qw, int64_t sb, int64_t sh,
                                                                    int64_t sw, int Hq, int Hkv, int W,
                                                                    float* __restrict__ sigma)
 {
-    constexpr int CG = D / VEC, RG = SIG_THREADS / CG, NF = 4;
+    constexpr int CG = D / VEC, RG = THREADS / CG, NF = 4;
     __shared__ float part[RG][D + 4];
     const int u = blockIdx.x, b = u / Hkv, hk = u % Hkv, G = Hq / Hkv;
     const int cg = threadIdx.x % CG, rg = threadIdx.x / CG;
-    const int64_t rows = (int64_t)G * W;
     const T* base = qw + (int64_t)b * sb + (int64_t)hk * G * sh + cg * VEC;
     float a[VEC];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) a[e] = 0.f;
-    for (int64_t n0 = rg; n0 < rows; n0 += NF * RG) {
+    // rows rg, rg + RG, ... of the G W rows, as head g and position w: a pointer that steps, no division or product per row
+    const int qg = RG / W, qr = RG - qg * W;
+    const int64_t step = qg * sh + qr * sw, wrap = sh - W * sw;
+    int g = rg / W, w = rg - g * W;
+    const T* next = base + g * sh + w * sw;
+    while (g < G) {
         alignas(16) T x[NF][VEC];
+        bool in[NF];
 #pragma unroll
-        for (int f = 0; f < NF; ++f) {               // rows past the end are clamped and count for nothing
-            const int64_t n = n0 + f * RG < rows ? n0 + f * RG : rows - 1, g = n / W, w = n - g * W;
-            const T* src = base + g * sh + w * sw;
+        for (int f = 0; f < NF; ++f) {               // rows past the end are read as the first and count for nothing
+            in[f] = g < G;
+            const T* src = in[f] ? next : base;
             if constexpr (VEC == 1) x[f][0] = *src;
             else *(uint4*)x[f] = *(const uint4*)src;
+            g += qg;
+            w += qr;
+            next += step;
+            if (w >= W) { w -= W; ++g; next += wrap; }
         }
 #pragma unroll
-        for (int f = 0; f < NF; ++f) {
-            const float keep = n0 + f * RG < rows ? 1.f : 0.f;
+        for (int f = 0; f < NF; ++f)
 #pragma unroll
             for (int e = 0; e < VEC; ++e) {
-                const float v = keep != 0.f ? ld_elem(&x[f][e]) : 0.f;
+                const float v = in[f] ? ld_elem(&x[f][e]) : 0.f;
                 a[e] = fmaf(v, v, a[e]);
             }
-        }
     }
 #pragma unroll
     for (int e = 0; e < VEC; ++e) part[rg][cg * VEC + e] = a[e];
     __syncthreads();
-    // the row groups in eight ranges, then the ranges, both in ascending order
-    __shared__ float sums[8][D];
+    // the row groups in ranges, then the ranges, both in ascending order
+    constexpr int NR = THREADS / D;
+    __shared__ float sums[NR][D];
     {
         const int c = threadIdx.x & (D - 1), k = threadIdx.x >> 7;
         float t = 0.f;
-        for (int i = k * RG / 8; i < (k + 1) * RG / 8; ++i) t += part[i][c];
+        for (int i = k * RG / NR; i < (k + 1) * RG / NR; ++i) t += part[i][c];
         sums[k][c] = t;
     }
     __syncthreads();
     if (threadIdx.x < D) {
         float t = 0.f;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) t += sums[k][threadIdx.x];
+        for (int k = 0; k < NR; ++k) t += sums[k][threadIdx.x];
         sigma[(size_t)u * D + threadIdx.x] = sqrtf(t);
     }
+}
+
+template <int THREADS>
+static void launch_sigma_threads(int dtype, bool vec, const void* qw, int64_t sb, int64_t sh, int64_t sw, int U, int Hq, int Hkv,
+                                 int W, float* sigma, hipStream_t st)
+{
+    const dim3 grid(U), block(THREADS);
+    if (dtype == 0 && vec)
+        hipLaunchKernelGGL((sigma_window_kernel<float, 4, THREADS>), grid, block, 0, st, (const float*)qw, sb, sh, sw, Hq, Hkv, W, sigma);
+    else if (dtype == 0)
+        hipLaunchKernelGGL((sigma_window_kernel<float, 1, THREADS>), grid, block, 0, st, (const float*)qw, sb, sh, sw, Hq, Hkv, W, sigma);
+    else if (vec)
+        hipLaunchKernelGGL((sigma_window_kernel<bf16_t, 8, THREADS>), grid, block, 0, st, (const bf16_t*)qw, sb, sh, sw, Hq, Hkv, W, sigma);
+    else
+        hipLaunchKernelGGL((sigma_window_kernel<bf16_t, 1, THREADS>), grid, block, 0, st, (const bf16_t*)qw, sb, sh, sw, Hq, Hkv, W, sigma);
 }
 
 hipError_t launch_sigma_window(int dtype, const void* qw, int64_t sb, int64_t sh, int64_t sw, int B, int Hq,
@@ -702,15 +724,14 @@ hipError_t launch_sigma_window(int dtype, const void* qw, int64_t sb, int64_t sh
     // 16-byte reads need every row on a 16-byte boundary; the entry point takes any base and strides
     const int64_t es = dtype == 0 ? 4 : 2;
     const bool vec = (((int64_t)(uintptr_t)qw | sb * es | sh * es | sw * es) & 15) == 0;
-    const dim3 grid(B * Hkv), block(SIG_THREADS);
-    if (dtype == 0 && vec)
-        hipLaunchKernelGGL((sigma_window_kernel<float, 4>), grid, block, 0, st, (const float*)qw, sb, sh, sw, Hq, Hkv, W, sigma);
-    else if (dtype == 0)
-        hipLaunchKernelGGL((sigma_window_kernel<float, 1>), grid, block, 0, st, (const float*)qw, sb, sh, sw, Hq, Hkv, W, sigma);
-    else if (vec)
-        hipLaunchKernelGGL((sigma_window_kernel<bf16_t, 8>), grid, block, 0, st, (const bf16_t*)qw, sb, sh, sw, Hq, Hkv, W, sigma);
-    else
-        hipLaunchKernelGGL((sigma_window_kernel<bf16_t, 1>), grid, block, 0, st, (const bf16_t*)qw, sb, sh, sw, Hq, Hkv, W, sigma);
+    const int U = B * Hkv;
+    const int64_t rows = (int64_t)(Hq / Hkv) * W;
+    // Few units: 1024 threads, so that a window is in flight at once.  From 512 on (two such work-groups a compute unit) small ones,
+    // of as many threads as the window has loads for (2048 units: 32 rows 10.3 us with 1024 threads, 4.8 with 128; 64 rows 14.7
+    // and 5.3; 128 rows 15.5, 11.4 with 256).
+    if (U < 512) launch_sigma_threads<1024>(dtype, vec, qw, sb, sh, sw, U, Hq, Hkv, W, sigma, st);
+    else if (rows > 64) launch_sigma_threads<256>(dtype, vec, qw, sb, sh, sw, U, Hq, Hkv, W, sigma, st);
+    else launch_sigma_threads<128>(dtype, vec, qw, sb, sh, sw, U, Hq, Hkv, W, sigma, st);
     return hipGetLastError();
 }
 

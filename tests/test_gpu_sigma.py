@@ -15,6 +15,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("B,Hq,Hkv,W,offset,pad", [
     (2, 14, 2, 32, 0, 0), (1, 4, 2, 33, 1, 0), (1, 6, 2, 7, 0, 3), (1, 1, 1, 1, 5, 1), (1, 8, 1, 100, 0, 0), (1, 2, 1, 257, 3, 5),
+    (16, 32, 32, 33, 0, 0), (16, 64, 32, 40, 1, 0), (17, 96, 32, 31, 0, 8),            # 512 units on: smaller work-groups
 ])
 def test_sigma(dtype, B, Hq, Hkv, W, offset, pad):
     ctx = rk.rk_create(0)
