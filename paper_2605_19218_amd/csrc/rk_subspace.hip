@@ -285,15 +285,15 @@ __global__ __launch_bounds__(SUB_THREADS) void subspace_iter(const float* __rest
         lds_barrier();
     }
 
-    // a head that failed has no basis (its place holds Gram tiles): R_k = 0 and delta_mu = mu, so that an empty sequence of a
-    // ragged batch, whose Gram matrix is zero, stays finite when tokens are appended to it
-    if (fail) {
-        for (int idx = tid; idx < D * LDW; idx += SUB_THREADS) W[idx] = 0.0;
-        lds_barrier();
-    }
-
     // ---- outputs: R_k = V, delta_mu = mu - V V^T mu (Alg. 1 steps 14, 16) ----
     if (tid == 0 && status) status[u] = fail;
+    if (fail) {
+        // No basis (its place holds Gram tiles): R_k = 0 and delta_mu = mu, so that an empty sequence of a ragged batch, whose
+        // Gram matrix is zero, stays finite when tokens are appended to it.
+        for (int idx = tid; idx < D * k; idx += SUB_THREADS) Rr[(size_t)u * D * k + idx] = 0.f;
+        if (tid < D) dmu[(size_t)u * D + tid] = mu[(size_t)u * D + tid];
+        return;
+    }
     for (int idx = tid; idx < D * k; idx += SUB_THREADS) {
         const int i = idx / k, j = idx - i * k;
         Rr[(size_t)u * D * k + idx] = (float)W[i * LDW + j];
