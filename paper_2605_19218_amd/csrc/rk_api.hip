@@ -233,9 +233,17 @@ int text_splits(const rk_ctx* ctx, const rk_layout* L, int S, int text_rows)
     // The device is full.  One split a unit: its text in a second one would be another round (256 x 4096 tokens, 64 rows: 64.8 us
     // shared, 66.9 apart).
     if (S == 1) return 0;
-    // A split per 64 rows, run beside the cache's as a second work-group a compute unit (32 x 8192 tokens: 200 rows 20.4 us in four
-    // splits, 21.0 shared, 21.6 in vector code as before; 1500 rows 23.2 / 23.6 / 24.6).
-    if (room >= 1) return least(least(pieces(64), room), DECODE_TEXT_SPLITS_MAX);
+    const double text = 512.0 * text_rows, cache = (double)L->max_seq_len / S * 2.0 * (keep_padded(L->keep) + D);
+    if (room >= 1) {
+        // Long splits of the cache cover a tile of text for each wave (32 x 22417 tokens, 742 rows: 188 us for four tokens, 199 with
+        // eight splits of text; 32 x 16384, 1024 rows 38.5 us a step, 45.3 in vector code as before).
+        if (S >= 4 && text_rows > 128 && text_rows <= 128 * S && cache >= 400e3) return 0;
+        // Else a split per 64 rows runs beside the cache's as a second work-group (32 x 8192 tokens, 200 rows: 20.5 us, shared 21.2,
+        // vector code 21.6), on no more than half the compute units while both are short (128 x 864 tokens, 227 rows, four
+        // tokens: 57 us with one split a unit, 65 with two, 64 shared).
+        const long most = text_rows <= 128 || (cache < 400e3 && text < 2.5 * cache) ? (room + 1) / 2 : room;
+        return least(least(pieces(64), most), DECODE_TEXT_SPLITS_MAX);
+    }
     // several rounds: more work-groups pay while the text is short (320 x 1024 tokens, S = 4: 200 rows 33.6 us with one split, 37.1
     // shared; 1024 rows 59 / 57)
     return pieces(256) <= 2 ? (int)pieces(256) : 0;
