@@ -447,7 +447,7 @@ rk_status rk_fit_rotation(rk_ctx* ctx, const rk_layout* L, const rk_rows* keys, 
     if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
     const int B = L->batch, Hkv = L->n_kv_heads, U = B * Hkv;
     const bool mfma = !ctx->force_generic;
-    const int ct = cov_chunk_tokens(L->dtype, mfma, U, keys->n_tokens);
+    const int ct = cov_chunk_tokens(L->dtype, mfma, U, keys->n_tokens, ctx->n_cu);
     int nc = (keys->n_tokens + ct - 1) / ct;        // never more than the workspace was sized for
     if (nc < 1) nc = 1;
     char* ws = (char*)workspace;
@@ -513,7 +513,7 @@ rk_status rk_fit_subspace(rk_ctx* ctx, const rk_layout* L, const rk_rows* keys, 
     if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
     const int B = L->batch, Hkv = L->n_kv_heads, U = B * Hkv;
     const bool mfma = !ctx->force_generic;
-    const int ct = cov_chunk_tokens(L->dtype, mfma, U, keys->n_tokens);
+    const int ct = cov_chunk_tokens(L->dtype, mfma, U, keys->n_tokens, ctx->n_cu);
     int nc = (keys->n_tokens + ct - 1) / ct;
     if (nc < 1) nc = 1;
     char* ws = (char*)workspace;

@@ -261,7 +261,7 @@ __global__ __launch_bounds__(256) void cov_partial_mfma(RowsDev rows, int Hkv, i
     if (nks > 0) {
         uint4 st[COVM_STAGES][8];
         int ks = 0;
-        // Every wave owns a run of TPW rows (128 KB of them at a 128 KB-aligned offset); walking them all from
+        // Every wave owns a run of TPW rows (256 TPW bytes at a multiple of that); walking them all from
         // the start would keep the 1024 waves of the grid on the same few HBM channels at any
         // instant.  A full wave therefore starts at a wave/chunk/head dependent
         // k-step and wraps around (the sum is order-independent up to fp32 rounding, and the
@@ -364,8 +364,8 @@ __global__ __launch_bounds__(256) void cov_partial_mfma(RowsDev rows, int Hkv, i
 // channel blocks, block cbk holding channels ch(cbk, m) = 4 m + cbk, so rows go from memory to the matrix cores as
 // they are, two whole rows per load instruction.  Each wave accumulates the 10 upper-triangular tiles over a quarter of the chunk;
 // the end of the chunk and the partial's layout are those of the bf16 kernel.
-// Bound: the fp32 matrix rate (10 MFMA of 64 cycles per two tokens).  The chunk is 128 tokens while that gives at most two
-// rounds of work-groups (a wave then has 16 steps; 2 x 512 tokens 97 us through the plain kernel, 9 us here), else 512.
+// Bound: the fp32 matrix rate (10 MFMA of 64 cycles per two tokens).  Chunks of 128 to 512 tokens, see cov_chunk_tokens
+// (2 x 512 tokens: 97 us through the plain kernel, 9 us here).
 constexpr int COVF_STAGES = 8;             // two-token steps of loads in flight per wave
 
 template <bool GATHER>
@@ -553,27 +553,39 @@ __global__ __launch_bounds__(256) void cov_finalize_tiled(RowsDev rows, int Hkv,
 }
 
 // ---------------------------------------------------------------------------
-// fp32: short chunks while they make at most 512 work-groups (two rounds), see cov_partial_f32
+// Most chunks under COV_CHUNK tokens that a call makes per (b, h_kv): fp32 only, 512 work-groups in all (the workspace is sized
+// by it, without a device to ask).
 int cov_short_chunks(int dtype, int64_t units) { return dtype == 0 ? (int)(512 / units) : 0; }
-int cov_chunk_tokens(int dtype, bool mfma, int64_t units, int max_tokens)
+// Work-groups run one per compute unit (registers and LDS): rounds of n_cu.  The chunk length that comes out cheapest:
+int cov_chunk_tokens(int dtype, bool mfma, int64_t units, int max_tokens, int n_cu)
 {
     if (!mfma) return COV_CHUNK;
+    int best = COV_CHUNK;
+    double least = 1e30;
     if (dtype == 1) {
-        // Work-groups run one per compute unit (registers and LDS): rounds of 256.  A full chunk of 2048 tokens takes
-        // about 21 us of streaming when all units stream, and a work-group about 5 us beside it (dispatch, end of
-        // chunk); a shorter chunk is taken where it is at least 15 % cheaper so priced (a last chunk that is partly filled
-        // makes the long ones cheaper than this).  32 heads x 2944 tokens: 64 work-groups of 2048 tokens 16.6 us, 192 of
-        // 512 tokens 11.8 us; 8 heads x 1024 tokens 14.6 / 8.5 us; 128 heads x 5000 tokens 39 us (2048) / 42 us (1024).
-        int best = COVM_CHUNK;
-        double least = 1e30;
+        // A full chunk of 2048 tokens takes about 21 us of streaming when all units stream, and a work-group about 5 us beside it
+        // (dispatch, end of chunk); a shorter chunk is taken where it is at least 15 % cheaper so priced (a last chunk that is
+        // partly filled makes the long ones cheaper than this).  32 heads x 2944 tokens: 64 work-groups of 2048 tokens 16.6 us,
+        // 192 of 512 tokens 11.8 us; 8 heads x 1024 tokens 14.6 / 8.5 us; 128 heads x 5000 tokens 39 us (2048) / 42 us (1024).
         for (int ct = COVM_CHUNK; ct >= COV_CHUNK; ct /= 2) {
-            const double wgs = (double)units * ((max_tokens + ct - 1) / ct), rounds = (double)((int64_t)(wgs + 255) / 256);
+            const double wgs = (double)units * ((max_tokens + ct - 1) / ct), rounds = (double)((int64_t)(wgs + n_cu - 1) / n_cu);
             const double t = rounds * (21.0 * ct / COVM_CHUNK + 5.0);
             if (t < 0.85 * least) { least = t; best = ct; }
         }
         return best;
     }
-    return (max_tokens + COV_CHUNK_MIN - 1) / COV_CHUNK_MIN <= cov_short_chunks(dtype, units) ? COV_CHUNK_MIN : COV_CHUNK;
+    // fp32: 5 us of matrix work per 128 tokens and 3 us beside it, then the reduction, which reads eight chunks at a time (1 us of
+    // latency each, and their bytes).  Whole fit, 1 x 65536 tokens: 94 us with 512 chunks of 128 tokens, 60 with 128 of 512; 8 x
+    // 8192: 50 (128), 42 (256), 48 (512); 8 x 4000: 38, 38, 46; 32 x 3000: 50 with 512.
+    const int few = cov_short_chunks(dtype, units);
+    for (int ct = COV_CHUNK; ct >= COV_CHUNK_MIN; ct /= 2) {
+        const int nc = (max_tokens + ct - 1) / ct;
+        if (ct < COV_CHUNK && nc > few) break;
+        const double rounds = (double)(((int64_t)units * nc + n_cu - 1) / n_cu);
+        const double t = rounds * (5.1 * ct / 128 + 3.0) + ((nc + 7) / 8) * (1.0 + 0.1 * (double)units);
+        if (t < least) { least = t; best = ct; }
+    }
+    return best;
 }
 
 template <int TPW>

@@ -15,8 +15,8 @@ hipError_t allow_dynamic_lds(const void* kernel, size_t bytes);
 // kernels write them as 10 upper-triangular tiles in register layout.
 constexpr int COV_CHUNK = 512;             // tokens per work-group of the plain kernel, and of the fp32 kernel on long inputs
 constexpr int COV_CHUNK_MIN = 128;         // the smallest chunk (fp32, short inputs)
-int cov_short_chunks(int dtype, int64_t units);       // most chunks of COV_CHUNK_MIN tokens that a call makes per (b, h_kv)
-int cov_chunk_tokens(int dtype, bool mfma, int64_t units, int max_tokens);
+int cov_short_chunks(int dtype, int64_t units);       // most chunks under COV_CHUNK tokens that a call makes per (b, h_kv)
+int cov_chunk_tokens(int dtype, bool mfma, int64_t units, int max_tokens, int n_cu);
 hipError_t launch_cov_partial(int dtype, bool mfma, const RowsDev& rows, int B, int Hkv, int n_chunks, int chunk_tokens,
                               float* part_S, float* part_sum, hipStream_t st);
 hipError_t launch_cov_finalize(int dtype, bool mfma, const RowsDev& rows, int B, int Hkv, int n_chunks, bool center,

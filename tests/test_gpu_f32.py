@@ -20,11 +20,11 @@ def ctx():
     rk.rk_destroy(c)
 
 
-# lengths around the two-token steps, the 32-token quarters and 128-token chunks, and (last) the 512-token chunks of a
-# call with more than 512 short ones
+# lengths around the two-token steps, the 32-token quarters and 128-token chunks, the 512-token chunks of a call with
+# more than 512 short ones, and chunks of 256 (two matrices) and 512 (one) where the reduction of short ones costs more
 @pytest.mark.parametrize("B,Hkv,L,lengths,center", [
     (5, 1, 129, [129, 128, 127, 1, 0], True), (3, 2, 97, [97, 33, 2], False), (1, 1, 2000, None, True),
-    (2, 40, 1100, [1100, 513], True),
+    (2, 40, 1100, [1100, 513], True), (2, 1, 16001, [16001, 257], True), (1, 1, 66000, None, True),
 ])
 def test_covariance(ctx, B, Hkv, L, lengths, center):
     data = layer(B, Hkv, Hkv, L, "f32", 61, lengths=lengths, mean_shift=3.0)
