@@ -250,11 +250,8 @@ __device__ __forceinline__ float row16_sum(float v)
 // needs for P.V are the ones it has just computed), so a pass needs no LDS and no barrier.  The
 // TG thread-private states are folded through LDS once, after the last pass.  The loads of pass
 // i + 1 are issued before pass i is computed (row indices clamped to the last row).
-// THREADS = 128 serves the usual short segment; 512 (four times the tokens per pass at the same
-// work per thread) is launched for bf16 segments longer than 128 rows.  The fold of the visual
-// partials and the output use threads 0..127.
-template <typename T, int THREADS>
-__global__ __launch_bounds__(THREADS) void decode_text_merge(const T* __restrict__ q, TextDev text, int Hq, int Hkv,
+template <typename T>
+__global__ __launch_bounds__(128) void decode_text_merge(const T* __restrict__ q, TextDev text, int Hq, int Hkv,
                                                              float scale_log2, const float* __restrict__ ws_m,
                                                              const float* __restrict__ ws_l,
                                                              const float* __restrict__ ws_acc, int S,
@@ -262,7 +259,7 @@ __global__ __launch_bounds__(THREADS) void decode_text_merge(const T* __restrict
 {
     constexpr int EPV = 16 / (int)sizeof(T);
     constexpr int CG = D / EPV;                 // pieces per row = lanes per token: 16 or 32
-    constexpr int TG = THREADS / CG;            // token groups
+    constexpr int TG = 128 / CG;                // token groups
     constexpr int NV = 8;                       // rows per thread and pass
     constexpr int CHUNK = TG * NV;              // text tokens per pass
 
@@ -281,7 +278,7 @@ __global__ __launch_bounds__(THREADS) void decode_text_merge(const T* __restrict
 
     const float* m = ws_m + row * S;
     const float* l = ws_l + row * S;
-    const float* a = ws_acc + row * S * D + min(tid, D - 1);
+    const float* a = ws_acc + row * S * D + tid;
     const int Mt = text.len ? min(max(text.len[b], 0), text.max_len) : text.max_len;
     const T* Kt = (const T*)text.k + (int64_t)b * text.sb + (int64_t)hk * text.sh + cg * EPV;
     const T* Vt = (const T*)text.v + (int64_t)b * text.sb + (int64_t)hk * text.sh + cg * EPV;
@@ -372,7 +369,7 @@ __global__ __launch_bounds__(THREADS) void decode_text_merge(const T* __restrict
         for (int k = 0; k < TG; ++k) {
             const float w = exp2f(sm_m[k] - Mx);                   // 0 for an empty token group
             den = fmaf(sm_l[k], w, den);
-            num = fmaf(part[k][tid & (D - 1)], w, num);
+            num = fmaf(part[k][tid], w, num);
         }
     }
 
@@ -396,7 +393,7 @@ __global__ __launch_bounds__(THREADS) void decode_text_merge(const T* __restrict
         }
     }
     const float o = (Mx > NEG_INF) ? num / den : 0.f;
-    if (tid < D) st_elem(out + row * D + tid, o);
+    st_elem(out + row * D + tid, o);
 }
 
 // One token per sequence appended to the full-width text segment (the paper keeps
@@ -1655,15 +1652,11 @@ hipError_t launch_decode(int dtype, bool mfma, int B, int Hq, int Hkv, int cap, 
     if (text && !text_in_split) {
         const int U = B * Hkv, upad = (U + 7) & ~7, n_pad = upad - U;
         const unsigned tblocks = (unsigned)(upad * (Hq / Hkv));
-        const bool wide = text->max_len > 128;       // bf16 only: the fp32 form would not fit its registers
         if (dtype == 0)
-            hipLaunchKernelGGL((decode_text_merge<float, 128>), dim3(tblocks), dim3(128), 0, st, (const float*)q,
+            hipLaunchKernelGGL(decode_text_merge<float>, dim3(tblocks), dim3(128), 0, st, (const float*)q,
                                *text, Hq, Hkv, sl2, ws_m, ws_l, ws_acc, S, (float*)out, n_pad);
-        else if (wide)
-            hipLaunchKernelGGL((decode_text_merge<bf16_t, 512>), dim3(tblocks), dim3(512), 0, st,
-                               (const bf16_t*)q, *text, Hq, Hkv, sl2, ws_m, ws_l, ws_acc, S, (bf16_t*)out, n_pad);
         else
-            hipLaunchKernelGGL((decode_text_merge<bf16_t, 128>), dim3(tblocks), dim3(128), 0, st,
+            hipLaunchKernelGGL(decode_text_merge<bf16_t>, dim3(tblocks), dim3(128), 0, st,
                                (const bf16_t*)q, *text, Hq, Hkv, sl2, ws_m, ws_l, ws_acc, S, (bf16_t*)out, n_pad);
     } else if (dtype == 0) {
         hipLaunchKernelGGL((decode_merge<float, 16>), dim3((unsigned)rows), dim3(128), 0, st, ws_m, ws_l, ws_acc, S,
