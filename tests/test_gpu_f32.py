@@ -104,15 +104,15 @@ def test_decode(ctx, case):
     data = layer(B, Hq, Hkv, L, "f32", 63, lengths=lengths, mean_shift=1.5)
     p = run_prefill(ctx, data, B, Hq, Hkv, L, r, "f32", lengths=lengths)
     q = to_dev(data["q"], "f32")
-    # rows behind the end hold NaN patterns: they may be read, never used
-    for buf, width in ((p.Kp, (r + 15) // 16 * 16), (p.Vc, D)):
-        tail = torch.full((32, width), float("nan"), device=DEV)
-        flat = buf.view(torch.float32).view(B * Hkv, -1)
-        for b in range(B):
-            n = (lengths or [L] * B)[b]
-            if (n + 31) // 32 * 32 + 32 <= p.cap:
-                for h in range(Hkv):
-                    flat[b * Hkv + h, (n + 31) // 32 * 32 * width:((n + 31) // 32 * 32 + 32) * width] = tail.view(-1)
+    # rows behind the end hold NaN patterns, in the last token's own block and in the one behind it: they may be read, never used
+    rp = (r + 15) // 16 * 16
+    K = p.Kp.view(torch.float32).view(B * Hkv, -1)[:, :p.cap * rp].view(B, Hkv, p.cap // 16, rp // 8, 16, 8)
+    V = p.Vc.view(torch.float32).view(B * Hkv, -1)[:, :p.cap * D].view(B, Hkv, p.cap // 32, D // 16, 4, 16, 2, 4)
+    for b in range(B):
+        n = (lengths or [L] * B)[b]
+        for t in range(n, min(p.cap, (n // 32 + 2) * 32)):
+            K[b, :, t // 16, :, t % 16] = float("nan")
+            V[b, :, t // 32, :, t % 16 // 4, :, t % 32 // 16, t % 4] = float("nan")
     rk.rk_set_option(ctx, rk.RK_OPT_DECODE_SPLITS, splits)
     try:
         got, again = p.decode(q).copy(), p.decode(q).copy()
