@@ -168,8 +168,9 @@ rk_status rk_cache_bytes(const rk_layout* L, size_t* k_packed_bytes, size_t* v_c
 
 /* Bytes of workspace rk_fit_rotation / rk_fit_subspace need for at most max_tokens rows per sequence
  * (0 for an invalid layout or max_tokens outside 0..RK_MAX_TOKENS).  At least 0.3 MB per (b, h_kv):
- * the eigensolver keeps its reflections and vectors there after the covariance partials, 64 KB per
- * 512 rows, are no longer needed. */
+ * the eigensolver keeps its reflections and vectors there after the covariance partials are no
+ * longer needed: 64 KB for every 512 rows, or with fp32 storage for every 128 rows where those are at
+ * most 512 / (B H_kv). */
 size_t rk_fit_workspace_size(const rk_layout* L, int32_t max_tokens);
 /* Bytes of workspace rk_decode_attn needs (depends on batch, heads, max_seq_len). */
 size_t rk_decode_workspace_size(const rk_ctx* ctx, const rk_layout* L);
