@@ -282,7 +282,7 @@ __global__ __launch_bounds__(256, 2) void compress_mfma(RowsDev rows, int Hkv, i
 // piece of the packed layout, consecutive lanes writing consecutive pieces.  128 tokens per work-group, two 16-token
 // tiles per wave.  Bound: the fp32 matrix rate (2 R MFMA of 32 cycles per tile), close to the memory time.
 // (32 heads x 2944 tokens, r = 64: 154 us through the plain kernel, whose every output is a 128-step loop over R_r
-// in memory; 25 us here.)
+// in memory; 24 us here, 27 on cold Keys.)
 template <int R>
 __global__ __launch_bounds__(256) void compress_f32(RowsDev rows, int Hkv, int cap, int r, const float* __restrict__ Rr,
                                                     float* __restrict__ Kp, int32_t* __restrict__ seq_len_out)

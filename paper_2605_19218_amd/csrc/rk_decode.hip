@@ -688,7 +688,7 @@ __device__ __forceinline__ void compute_tile(DecTile<R>& T, DecState<R>& st, con
 // rows that its lane group's k-slots hold, and an 8 x 8 transpose of 16-bit values within the lane gives, for block cb,
 // the eight rows of channel 8 n + cb.  The accumulators therefore hold channel 8 n + cb where the visual ones hold
 // 16 cb + n; the merge sorts that out.  (With the text in work-groups of their own, one per head and 512 rows on vector
-// code, 1024 rows added 11 us to the benchmark's 35 us step; as part of the splits they add 4 us.)
+// code, 1024 rows added 11 us to the benchmark's 35 us step; as part of the splits they add 4-5 us.)
 struct TextTile {
     bf16x8 k[2][4];
     uint4 v[8];
@@ -1314,7 +1314,7 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
 // steps.  Partials are folded by decode_merge (or, with a text segment, by decode_text_merge).
 // Bound: HBM; the matrix work (R / 4 + 32 MFMA of 32 cycles per tile) takes a third of that time at one query head per
 // KV head.  (32 heads x 2944 tokens, r = 64: 59 us through the plain kernel, which reads a cache line per lane and score
-// channel, 16 us here.)
+// channel, 19 us here (17 at best), and the merge behind it 4.)
 template <int R>
 struct DecTileF32 {
     f32x4 k[R / 16], v[8];

@@ -10,7 +10,7 @@
 // The fp64 vector rate of this part equals its unpacked fp32 rate, so double costs registers and LDS width only; it
 // buys vectors that need no iteration over the whole matrix.  A sweep of Jacobi is 127 dependent rounds on one compute
 // unit and 8-10 sweeps are needed; the reduction is 126 dependent steps in all, and everything behind it is independent
-// per eigenpair.  Measured (32 / 512 matrices): 106 + 34 + 18 + 10 us / 222 + 302 + 257 us against 756 us / 2.3 ms of the
+// per eigenpair.  Measured (32 / 512 matrices): 106 + 34 + 18 + 10 us / 225 + 327 + 266 us against 756 us / 2.3 ms of the
 // parallel Jacobi that solved every matrix before, with eigenvalues to their fp32 rounding (1e-7 of the spectrum
 // against 8e-7).
 #include <type_traits>
@@ -596,7 +596,7 @@ __global__ __launch_bounds__(256, 2) void eig_tri_vectors(int U, const double* _
 // Bound, of 36000 cycles: loading Z 6500, the products 6000 + 6600 (matrix pipe 4100 each), storing V 2800, reflections 13700
 // (eight rounds of four dependent matrix steps, one exchange between the waves, eight more).  Four reflections at a time
 // on the vector unit: 20000 + 2500 for their inner products (LDS-bound, every lane group reads all of V), 23 us; one at a time
-// with loads where they are used: 56000 cycles in all, 27.7 us.  Now 18 us for 32 matrices, 257 for 512 (547 at first).
+// with loads where they are used: 56000 cycles in all, 27.7 us.  Now 18 us for 32 matrices, 266 for 512 (547 at first).
 constexpr double EIG_ORTH_MAX = 3e-4;
 static_assert(0.75 * D * EIG_ORTH_MAX * EIG_ORTH_MAX <= 1e-5, "|R^T R - I| <= 1e-5, every column of E at its limit");
 constexpr int OB_LD = D + 2, OB_MLD = 17;

@@ -365,7 +365,7 @@ __global__ __launch_bounds__(256) void cov_partial_mfma(RowsDev rows, int Hkv, i
 // they are, two whole rows per load instruction.  Each wave accumulates the 10 upper-triangular tiles over a quarter of the chunk;
 // the end of the chunk and the partial's layout are those of the bf16 kernel.
 // Bound: the fp32 matrix rate (10 MFMA of 64 cycles per two tokens).  Chunks of 128 to 512 tokens, see cov_chunk_tokens
-// (2 x 512 tokens: 97 us through the plain kernel, 9 us here).
+// (2 x 512 tokens: 97 us through the plain kernel, 10 us here).
 constexpr int COVF_STAGES = 8;             // two-token steps of loads in flight per wave
 
 template <bool GATHER>
@@ -653,7 +653,7 @@ hipError_t launch_cov_finalize(int dtype, bool mfma, const RowsDev& rows, int B,
 // share a KV head.  One work-group per (b, h_kv), of 1024 threads unless there are many: a row of 128 channels is read by 128 / VEC lanes, VEC
 // elements (16 bytes where base and strides allow it, else one) each, and the other lanes take other rows, so that a
 // window of 7 x 32 rows is four loads per thread, all out together.  (One thread per channel walking the rows two at a
-// time: 30-51 us for 32 work-groups of 224 rows, a memory round trip for every pair of rows; now 4 us.)
+// time: 30-51 us for 32 work-groups of 224 rows, a memory round trip for every pair of rows; now 4.6 us.)
 template <typename T, int VEC, int THREADS>
 __global__ __launch_bounds__(THREADS) void sigma_window_kernel(const T* __restrict__ qw, int64_t sb, int64_t sh,
                                                                    int64_t sw, int Hq, int Hkv, int W,
