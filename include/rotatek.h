@@ -336,9 +336,11 @@ rk_status rk_append_decode_attn(rk_ctx* ctx, const rk_layout* L, const void* k_n
  * P [V_vis; V_pt].  The bias therefore matters here: it shifts the visual
  * scores against the text scores.  Either segment may be empty per sequence;
  * both empty yields zeros.  On the matrix-core path the text attention runs in
- * the split-K launch: in splits of its own while compute units are left over, else
- * every split takes a share of the text rows in front of its share of the cache;
- * the partials are folded as rk_decode_attn's.  With fp32 storage or the plain kernels
+ * the split-K launch: in up to 8 splits of its own, or every split takes a share of
+ * the text rows in front of its share of the cache, whichever leaves the splits'
+ * bytes closer to each other; the partials are folded as rk_decode_attn's.  The text's softmax weights
+ * are held in fp32 and multiplied with all their 24 bits; a row that scores minus
+ * infinity weighs nothing.  With fp32 storage or the plain kernels
  * the second kernel runs the text attention itself and then folds the visual
  * partials (the fusion App. C describes).  Same workspace as rk_decode_attn.
  * Errors: as rk_decode_attn, plus INVALID_ARG for a malformed `text`
