@@ -65,187 +65,239 @@ __device__ __forceinline__ double rcp_f64(double x)
 }
 
 // ---------------------------------------------------------------------------
-// Householder reduction, one 512-thread work-group per matrix.  Thread (rg, cg) = (tid / 16, tid % 16) holds rows
-// rg + 32 i and columns cg + 16 m: the active part shrinks evenly over the threads, and a row lies in the 16
-// consecutive lanes of a group, where sums are lane permutations.  A step has two barriers:
-//   v_k is in LDS; every group forms p = A v on its rows                 -> LDS, barrier
-//   w = p - (tau v^T p / 2) v, A -= tau (v w^T + w v^T); the wave that owns row k + 1 updates that row first, makes the
-//   next reflection from it and publishes it before it goes on          -> LDS, barrier
-// What bounds a step is its dependent chain (two LDS round trips, three lane-group sums, a square root, two barriers).
-// Tried: 1024 threads of 2 x 8 elements (119 us for 32 matrices: twice the sums and LDS reads per element); A v from A x
-// and the column k + 1, every wave taking the square root for itself off the chain (138 us: the second vector and the
-// redundant sums cost more LDS and issue than the chain saves).
+// Householder reduction, one work-group of five waves per matrix.  Threads 0 .. 255 hold the matrix: thread (rg, cg) =
+// (tid / 16, tid % 16) has rows rg + 16 i and columns cg + 16 m, so the active part shrinks evenly over the threads in both
+// directions, a row lies in the 16 consecutive lanes of a group, where sums are lane permutations, and a vector is
+// read from LDS by rows exactly as by columns.  The fifth wave makes the reflections.  With x the part of row k behind the
+// diagonal, the reflection's vector is v = x + s e with s = +-|x| and e its first place, so that A v = A x + s a, a = row
+// k + 1.  A step has two barriers:
+//   x is in LDS; every group forms A x on its rows -> LDS, and the group that owns row k + 1 hands it over as it stands;
+//   meanwhile the fifth wave finds s and tau and keeps the record                                    -> barrier
+//   p = A x + s a, A -= tau (v p^T + p v^T - tau (v^T p) v v^T), the first two products while v^T p is being summed; meanwhile
+//   the fifth wave applies the same to row k + 1 alone and publishes the next x                      -> barrier
+// What bounds a step is its dependent chain (two LDS round trips, two lane-group sums one behind the other, two barriers) and
+// the instructions of one wave: a wave alone on its SIMD issues one about every seven cycles.  32 matrices: 93 us; 106 with 512
+// threads of 4 x 8 elements (which read every vector twice as often) whose waves made the reflections between their own
+// updates.  Tried: 1024 threads of 2 x 8 elements (119 us: twice the sums and LDS reads per element); the reflection found
+// between the barriers of the update, behind the sum v^T p (94 us); every lane group finding it for itself, with one barrier a step
+// (114 us: the instructions of all that redundancy cost more than the barrier).
 // status[2 u]: 1 for a matrix left to Jacobi (already diagonal to its threshold, zero, or not finite), else 0; status
 // [2 u + 1] is cleared for the two kernels behind, which set it when a vector fails its check (they read the first flag
 // only: the second may change while they run).
-constexpr int TRI_THREADS = 512, TRI_ROWS = 4;
+constexpr int TRI_HOLD = 256, TRI_THREADS = TRI_HOLD + 64;
 
 struct TriShared {
-    double vs[2][D];                    // spread: v of this step and of the next
-    double ps[D];                       // spread: A v
-    double d[D], e[D], tau[D];
-    double red[2][TRI_THREADS / 64];
+    double xs[2][D];                    // spread: x of this step and of the next, zeros in front of its first place
+    double ps[D];                       // spread: A x
+    double row[D];                      // spread: row k + 1 before this step
+    f64x2 ts[D];                        // (tau, s)
+    double d[D], e[D];
+    double red[2][TRI_HOLD / 64];
 };
 
-// The reflection that clears row kn right of its first off-diagonal element, made by the wave that owns the row:
-// H = I - tau v v^T, v = x + sign(x_first) |x| e_first, tau = 1 / (|x|^2 + |x_first| |x|).
+// 8 - KB places of a spread vector
 template <int KB>
-__device__ __forceinline__ void tri_publish(const double (&row)[8], int kn, TriShared& S, int rg, int cg)
+__device__ __forceinline__ void tri_read(double (&x)[8], const double* s, int g)
 {
-    double x[8];
-    double s0 = 0.0, s1 = 0.0;
-    const bool own = rg == (kn & 31);
-    const int lead = kn + 1;
-    const double xl = KB < 7 && (lead >> 4) > KB ? row[KB < 7 ? KB + 1 : KB] : row[KB];
-    const int src = 16 * (kn & 3) + (lead & 15);
-    const double first = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(xl), src),
-                                          __builtin_amdgcn_readlane(__double2loint(xl), src));
 #pragma unroll
-    for (int m = KB; m < 8; ++m) {
-        x[m] = m > KB + 1 || cg + 16 * m > lead ? row[m] : 0.0;
-        if (m & 1) s1 = fma(x[m], x[m], s1);
-        else s0 = fma(x[m], x[m], s0);
-    }
-    const double sig = row16_sum_f64(s0 + s1);
-    const double h = fma(first, first, sig);
-    // |x| = h / sqrt(h): hardware estimate and one third-order step
-    const double y = __builtin_amdgcn_rsq(h), t = h * y, r = fma(-t, y, 1.0);
-    const double nrm = fma(t * r, fma(r, 0.375, 0.5), t);
-    const bool act = sig > 1e-36;                                // else nothing to clear at double precision: H = I
-    const double vl = !act ? 0.0 : first >= 0.0 ? first + nrm : first - nrm;      // (|x| is NaN for x = 0)
-    if (own) {
-        double* vb = S.vs[kn & 1];
-#pragma unroll
-        for (int q = KB >> 1; q < 4; ++q) {
-            f64x2 v2;
-#pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                const int m = 2 * q + b;
-                v2[b] = m < KB ? 0.0 : (m <= KB + 1 && cg + 16 * m == lead ? vl : x[m < KB ? KB : m]);
-            }
-            *(f64x2*)(vb + (q * 16 + cg) * 2) = v2;
-        }
-        if (cg == (kn & 15)) {                                   // (this lane also holds the diagonal element)
-            S.tau[kn] = act ? rcp_f64(fma(fabs(first), nrm, h)) : 0.0;
-            S.e[kn] = act ? (first >= 0.0 ? -nrm : nrm) : first;
-            S.d[kn] = KB < 7 && (kn >> 4) > KB ? row[KB < 7 ? KB + 1 : KB] : row[KB];
-        }
+    for (int q = KB >> 1; q < 4; ++q) {
+        const f64x2 t = *(const f64x2*)(s + (q * 16 + g) * 2);
+        x[2 * q] = t.x;
+        x[2 * q + 1] = t.y;
     }
 }
 
-// Steps 16 KB .. 16 KB + 15: column blocks m < KB are finished, and so are row places i < KB / 2.
+// x + s e: place `lead`, the first of x, is in place KB or KB + 1 of a lane
 template <int KB>
-__device__ __forceinline__ void tri_block(double (&a)[TRI_ROWS][8], TriShared& S, double* __restrict__ Vg, int rg, int cg,
-                                          int wave)
+__device__ __forceinline__ void tri_add_first(double (&x)[8], double s, int lead, int g)
 {
-    constexpr int R0 = KB >> 1, NR = TRI_ROWS - R0;
-    const int k1 = min(16 * KB + 16, D - 2);
+#pragma unroll
+    for (int m = KB; m < 8 && m < KB + 2; ++m) x[m] += g + 16 * m == lead ? s : 0.0;
+}
+
+// The x of step kn out of row kn, into LDS and x; the diagonal element beside it.
+template <int KB>
+__device__ __forceinline__ void tri_publish(const double (&row)[8], int kn, double (&x)[8], TriShared& S, int lane)
+{
+    const int cg = lane & 15;
+#pragma unroll
+    for (int m = 0; m < 8; ++m) x[m] = m < KB ? 0.0 : m > KB + 1 || cg + 16 * m > kn ? row[m] : 0.0;
+    if (lane < 16) {
+        double* xb = S.xs[kn & 1];
+#pragma unroll
+        for (int q = KB >> 1; q < 4; ++q) *(f64x2*)(xb + (q * 16 + cg) * 2) = (f64x2){x[2 * q], x[2 * q + 1]};
+        if (cg == (kn & 15)) S.d[kn] = KB < 7 && (kn >> 4) > KB ? row[KB < 7 ? KB + 1 : KB] : row[KB];
+    }
+}
+
+// Steps 16 KB .. 16 KB + 15 of the fifth wave, whose lane groups all hold the same: x of the step in v.
+template <int KB>
+__device__ __forceinline__ void tri_reflect(double (&v)[8], TriShared& S, double* __restrict__ Vg, int lane)
+{
+    const int cg = lane & 15, k1 = min(16 * KB + 16, D - 2);
 #pragma unroll 1
     for (int k = 16 * KB; k < k1; ++k) {
-        const bool live = 96 + 4 * wave + 3 > k;                // wave-uniform: some row of this wave is still active
-        double v[8], vi[TRI_ROWS], tau = 0.0;
-        if (live) {
-            const double* vb = S.vs[k & 1];
+        const int kn = k + 1;                                    // the first place of x, and the next row
+        const double xl = KB < 7 && (kn >> 4) > KB ? v[KB < 7 ? KB + 1 : KB] : v[KB];
+        const double first = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(xl), kn & 15),
+                                              __builtin_amdgcn_readlane(__double2loint(xl), kn & 15));
+        double s0 = 0.0, s1 = 0.0;
 #pragma unroll
-            for (int q = KB >> 1; q < 4; ++q) {
-                const f64x2 t = *(const f64x2*)(vb + (q * 16 + cg) * 2);
-                v[2 * q] = t.x;
-                v[2 * q + 1] = t.y;
-            }
-            double p[TRI_ROWS];
+        for (int m = KB; m < 8; ++m) {
+            const double y = m <= KB + 1 && cg + 16 * m == kn ? 0.0 : v[m];
+            if (m & 1) s1 = fma(y, y, s1);
+            else s0 = fma(y, y, s0);
+        }
+        const double sig = row16_sum_f64(s0 + s1);
+        const double h = fma(first, first, sig);
+        // |x| = h / sqrt(h): hardware estimate and one third-order step
+        const double y = __builtin_amdgcn_rsq(h), t = h * y, r = fma(-t, y, 1.0);
+        const double nrm = fma(t * r, fma(r, 0.375, 0.5), t);
+        const bool act = sig > 1e-36;                            // else nothing to clear at double precision: H = I
+        const double s = !act ? 0.0 : first >= 0.0 ? nrm : -nrm;                      // (|x| is NaN for x = 0)
+        const double tau = act ? rcp_f64(fma(fabs(first), nrm, h)) : 0.0;             // H = I - tau v v^T
+        tri_add_first<KB>(v, s, kn, cg);
+        if (lane == 0) {
+            S.ts[k] = (f64x2){tau, s};
+            S.e[k] = act ? -s : first;
+        }
+        if (lane < 16) {
 #pragma unroll
-            for (int i = 0; i < TRI_ROWS; ++i) {
-                double s0 = 0.0, s1 = 0.0;
-                if (i >= R0) {
-#pragma unroll
-                    for (int m = KB; m < 8; ++m) {
-                        if (m & 1) s1 = fma(a[i][m], v[m], s1);
-                        else s0 = fma(a[i][m], v[m], s0);
-                    }
-                }
-                p[i] = s0 + s1;
-            }
-            // sums over the 16 lanes; with several rows the first steps halve the rows a lane carries
-            // instead of adding all of them everywhere
-            double t;
-            int row;
-            if constexpr (NR >= 3) {
-                const bool b3 = (cg & 8) != 0, b2 = (cg & 4) != 0;
-                double t0 = b3 ? p[2] : p[0], t1 = b3 ? p[3] : p[1];
-                t0 += dpp_f64<0x128>(b3 ? p[0] : p[2]);          // row_ror 8: lane i takes from lane i ^ 8
-                t1 += dpp_f64<0x128>(b3 ? p[1] : p[3]);
-                t = b2 ? t1 : t0;
-                t += dpp_f64<0x141>(b2 ? t0 : t1);               // row_half_mirror: lane i ^ 7
-                t += dpp_f64<0xB1>(t);
-                t += dpp_f64<0x4E>(t);
-                row = cg >> 2;
-            } else if constexpr (NR == 2) {
-                const bool b3 = (cg & 8) != 0;
-                t = b3 ? p[3] : p[2];
-                t += dpp_f64<0x128>(b3 ? p[2] : p[3]);
-                t += dpp_f64<0x141>(t);
-                t += dpp_f64<0xB1>(t);
-                t += dpp_f64<0x4E>(t);
-                row = 2 + (cg >> 3);
-            } else {
-                t = row16_sum_f64(p[3]);
-                row = 3;
-            }
-            S.ps[eig_spread(rg + 32 * row)] = t;                 // (several lanes store the same number)
-#pragma unroll
-            for (int i = R0; i < TRI_ROWS; ++i) {
-                const double z = vb[eig_spread(rg + 32 * i)];
-                vi[i] = z;
-            }
-            tau = S.tau[k];
-            if (rg == 31) {                                      // the last group to finish keeps the record
-#pragma unroll
-                for (int q = KB >> 1; q < 4; ++q)
-                    *(f64x2*)(Vg + (size_t)k * D + (q * 16 + cg) * 2) = (f64x2){2 * q < KB ? 0.0 : v[2 * q], v[2 * q + 1]};
-            }
+            for (int q = KB >> 1; q < 4; ++q)
+                *(f64x2*)(Vg + (size_t)k * D + (q * 16 + cg) * 2) = (f64x2){2 * q < KB ? 0.0 : v[2 * q], v[2 * q + 1]};
         }
         lds_barrier();
-        if (live) {
-            double w[8], wi[TRI_ROWS];
+        if (kn < D - 2) {
+            double p[8], row[8];
+            tri_read<KB>(p, S.ps, cg);
+            tri_read<KB>(row, S.row, cg);
+            const double pk = fma(s, S.row[eig_spread(kn)], S.ps[eig_spread(kn)]);
+#pragma unroll
+            for (int m = KB; m < 8; ++m) p[m] = fma(s, row[m], p[m]);
             double d0 = 0.0, d1 = 0.0;
 #pragma unroll
-            for (int q = KB >> 1; q < 4; ++q) {
-                const f64x2 t = *(const f64x2*)(S.ps + (q * 16 + cg) * 2);
-                w[2 * q] = t.x;
-                w[2 * q + 1] = t.y;
-            }
-#pragma unroll
-            for (int i = R0; i < TRI_ROWS; ++i) wi[i] = S.ps[eig_spread(rg + 32 * i)];
-#pragma unroll
             for (int m = KB; m < 8; ++m) {
-                if (m & 1) d1 = fma(v[m], w[m], d1);
-                else d0 = fma(v[m], w[m], d0);
+                if (m & 1) d1 = fma(v[m], p[m], d1);
+                else d0 = fma(v[m], p[m], d0);
             }
-            const double nh = -0.5 * tau * row16_sum_f64(d0 + d1);
+            const double tl = -tau * (first + s), tp = -tau * pk;
 #pragma unroll
-            for (int m = KB; m < 8; ++m) w[m] = fma(nh, v[m], w[m]);
-            auto update = [&](int i) {
-                // rows that are finished hold leftovers of v: whatever they become is never read
-                const double tw = -tau * fma(nh, vi[i], wi[i]), tv = -tau * vi[i];
+            for (int m = KB; m < 8; ++m) row[m] = fma(tl, p[m], fma(tp, v[m], row[m]));
+            const double c = -tau * tl * row16_sum_f64(d0 + d1);
 #pragma unroll
-                for (int m = KB; m < 8; ++m) a[i][m] = fma(tv, w[m], fma(tw, v[m], a[i][m]));
-            };
-            // the next row sits in place R0, or R0 + 1 behind the last step of an odd block
-            const int kn = k + 1;
-            update(R0);
-            if constexpr ((KB & 1) != 0 && R0 < TRI_ROWS - 1) update(R0 + 1);
-            if (kn < D - 2 && wave == ((kn & 31) >> 2)) {
-                __builtin_amdgcn_s_setprio(3);
-                if ((KB & 1) != 0 && R0 < TRI_ROWS - 1 && (kn >> 5) > R0) tri_publish<KB>(a[R0 < 3 ? R0 + 1 : 3], kn, S, rg, cg);
-                else tri_publish<KB>(a[R0], kn, S, rg, cg);
-                __builtin_amdgcn_s_setprio(0);
-            }
-#pragma unroll
-            for (int i = R0 + 1 + (KB & 1); i < TRI_ROWS; ++i) update(i);
+            for (int m = KB; m < 8; ++m) row[m] = fma(c, v[m], row[m]);
+            tri_publish<KB>(row, kn, v, S, lane);
         }
         lds_barrier();
     }
-    if constexpr (KB < 7) tri_block<KB + 1>(a, S, Vg, rg, cg, wave);
+    if constexpr (KB < 7) tri_reflect<KB + 1>(v, S, Vg, lane);
+}
+
+// Sums of p[KB ..] over the 16 lanes of a group.  With several rows the first steps halve the rows that a lane carries instead
+// of adding all of them everywhere: H of N rows stay, lanes with the step's bit set taking row j + H where there is one.
+// row: which of them this lane ends up with.
+template <int N, int STEP>
+__device__ __forceinline__ double tri_fold(const double (&t)[8], int cg)
+{
+    auto other = [](double x) {
+        return STEP == 0 ? dpp_f64<0x128>(x)                     // row_ror 8: lane i takes from lane i ^ 8
+             : STEP == 1 ? dpp_f64<0x141>(x)                     // row_half_mirror: lane i ^ 7
+             : STEP == 2 ? dpp_f64<0x4E>(x) : dpp_f64<0xB1>(x);  // lane i ^ 2, lane i ^ 1
+    };
+    if constexpr (STEP == 4) {
+        return t[0];
+    } else {
+        constexpr int H = N > 4 ? 4 : N > 2 ? 2 : 1;
+        const bool up = (cg & (8 >> STEP)) != 0;
+        double s[8];
+#pragma unroll
+        for (int j = 0; j < H; ++j) {
+            const double a = t[j], b = j + H < N ? t[j + H] : 0.0;      // (by value: a choice between places becomes an index)
+            if (j + H < N) s[j] = (up ? b : a) + other(up ? a : b);
+            else s[j] = a + other(a);
+        }
+        return tri_fold<H, STEP + 1>(s, cg);
+    }
+}
+template <int N>
+__device__ __forceinline__ int tri_fold_row(int cg)
+{
+    const int b3 = (cg >> 3) & 1, b2 = (cg >> 2) & 1, b1 = (cg >> 1) & 1;
+    if (N > 4) { const int j = 2 * b2 + b1; return j + (b3 && j + 4 < N ? 4 : 0); }
+    if (N > 2) return b2 + (b3 && b2 + 2 < N ? 2 : 0);
+    return N > 1 ? b3 : 0;
+}
+
+// Steps 16 KB .. 16 KB + 15 of the waves that hold the matrix: row and column places below KB are finished.
+template <int KB>
+__device__ __forceinline__ void tri_block(double (&a)[8][8], TriShared& S, int rg, int cg, int wave)
+{
+    constexpr int N = 8 - KB;
+    const int k1 = min(16 * KB + 16, D - 2);
+    const int mine = eig_spread(rg + 16 * (KB + tri_fold_row<N>(cg)));
+#pragma unroll 1
+    for (int k = 16 * KB; k < k1; ++k) {
+        const int kn = k + 1;
+        const bool live = 112 + 4 * wave + 3 > k;               // wave-uniform: some row of this wave is still active
+        double v[8], vi[8];
+        if (live) {
+            tri_read<KB>(v, S.xs[k & 1], cg);
+            tri_read<KB>(vi, S.xs[k & 1], rg);
+            if (rg == (kn & 15)) {
+                const bool far = KB < 7 && (kn >> 4) > KB;
+                constexpr int FAR = KB < 7 ? KB + 1 : KB;
+#pragma unroll
+                for (int q = KB >> 1; q < 4; ++q)
+                    *(f64x2*)(S.row + (q * 16 + cg) * 2) = far ? (f64x2){a[FAR][2 * q], a[FAR][2 * q + 1]}
+                                                               : (f64x2){a[KB][2 * q], a[KB][2 * q + 1]};
+            }
+            double p[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) p[j] = 0.0;
+#pragma unroll
+            for (int m = KB; m < 8; ++m)
+#pragma unroll
+                for (int j = 0; j < N; ++j) p[j] = fma(a[KB + j][m], v[m], p[j]);
+            S.ps[mine] = tri_fold<N, 0>(p, cg);                  // (several lanes store the same number)
+        }
+        lds_barrier();
+        if (live) {
+            double w[8], wi[8], r[8], ri[8];
+            const f64x2 ts = S.ts[k];
+            tri_read<KB>(w, S.ps, cg);
+            tri_read<KB>(r, S.row, cg);
+            tri_read<KB>(wi, S.ps, rg);
+            tri_read<KB>(ri, S.row, rg);
+            const double tau = ts.x;
+            tri_add_first<KB>(v, ts.y, kn, cg);
+            tri_add_first<KB>(vi, ts.y, kn, rg);
+            double d0 = 0.0, d1 = 0.0;
+#pragma unroll
+            for (int m = KB; m < 8; ++m) {
+                w[m] = fma(ts.y, r[m], w[m]);
+                if (m & 1) d1 = fma(v[m], w[m], d1);
+                else d0 = fma(v[m], w[m], d0);
+            }
+#pragma unroll
+            for (int i = KB; i < 8; ++i) wi[i] = fma(ts.y, ri[i], wi[i]);
+            // rows that are finished hold leftovers of v: whatever they become is never read
+#pragma unroll
+            for (int i = KB; i < 8; ++i) {
+                const double tv = -tau * vi[i];
+#pragma unroll
+                for (int m = KB; m < 8; ++m) a[i][m] = fma(tv, w[m], a[i][m]);
+            }
+            const double nd = -tau * row16_sum_f64(d0 + d1);
+#pragma unroll
+            for (int i = KB; i < 8; ++i) {
+                const double tw = -tau * fma(nd, vi[i], wi[i]);
+#pragma unroll
+                for (int m = KB; m < 8; ++m) a[i][m] = fma(tw, v[m], a[i][m]);
+            }
+        }
+        lds_barrier();
+    }
+    if constexpr (KB < 7) tri_block<KB + 1>(a, S, rg, cg, wave);
 }
 
 __global__ __launch_bounds__(TRI_THREADS) void eig_tridiag(const float* __restrict__ cov, const float* __restrict__ sigma,
@@ -257,36 +309,38 @@ __global__ __launch_bounds__(TRI_THREADS) void eig_tridiag(const float* __restri
     const float* C = cov + (size_t)u * D * D;
     double* W = scratch + (size_t)u * EIGW_TOTAL;
 
-    double a[TRI_ROWS][8];
-    float cf[TRI_ROWS][8];                  // every load is out before the first is used
+    double a[8][8];
+    if (wave < TRI_HOLD / 64) {
+        float cf[8][8];                     // every load is out before the first is used
 #pragma unroll
-    for (int i = 0; i < TRI_ROWS; ++i)
+        for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int m = 0; m < 8; ++m) cf[i][m] = C[(rg + 32 * i) * D + cg + 16 * m];
-    float sr[TRI_ROWS], sc[8];
+            for (int m = 0; m < 8; ++m) cf[i][m] = C[(rg + 16 * i) * D + cg + 16 * m];
+        float sr[8], sc[8];
 #pragma unroll
-    for (int i = 0; i < TRI_ROWS; ++i) sr[i] = sigma ? sigma[(size_t)u * D + rg + 32 * i] : 1.f;
+        for (int i = 0; i < 8; ++i) sr[i] = sigma ? sigma[(size_t)u * D + rg + 16 * i] : 1.f;
 #pragma unroll
-    for (int m = 0; m < 8; ++m) sc[m] = sigma ? sigma[(size_t)u * D + cg + 16 * m] : 1.f;
-    double all = 0.0, off = 0.0;
+        for (int m = 0; m < 8; ++m) sc[m] = sigma ? sigma[(size_t)u * D + cg + 16 * m] : 1.f;
+        double all = 0.0, off = 0.0;
 #pragma unroll
-    for (int i = 0; i < TRI_ROWS; ++i)
+        for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int m = 0; m < 8; ++m) {
-            const double x = (double)cf[i][m] * ((double)sr[i] * (double)sc[m]);
-            a[i][m] = x;
-            all = fma(x, x, all);
-            off = rg + 32 * i == cg + 16 * m ? off : fma(x, x, off);
+            for (int m = 0; m < 8; ++m) {
+                const double x = (double)cf[i][m] * ((double)sr[i] * (double)sc[m]);
+                a[i][m] = x;
+                all = fma(x, x, all);
+                off = rg + 16 * i == cg + 16 * m ? off : fma(x, x, off);
+            }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            all += __shfl_xor(all, o);
+            off += __shfl_xor(off, o);
         }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        all += __shfl_xor(all, o);
-        off += __shfl_xor(off, o);
+        if (lane == 0) { S.red[0][wave] = all; S.red[1][wave] = off; }
     }
-    if (lane == 0) { S.red[0][wave] = all; S.red[1][wave] = off; }
     __syncthreads();
-    all = off = 0.0;
-    for (int w = 0; w < TRI_THREADS / 64; ++w) { all += S.red[0][w]; off += S.red[1][w]; }
+    double all = 0.0, off = 0.0;
+    for (int w = 0; w < TRI_HOLD / 64; ++w) { all += S.red[0][w]; off += S.red[1][w]; }
     // uniform: left to Jacobi, whose threshold this is (2e-8 ||C_q||_F); NaN and infinities land here too
     if (!(off > 4e-16 * all) || !(all < 1e300)) {
         if (tid == 0) { status[2 * u] = 1; status[2 * u + 1] = 0; }
@@ -294,17 +348,30 @@ __global__ __launch_bounds__(TRI_THREADS) void eig_tridiag(const float* __restri
     }
     // scaled by a power of two to a Frobenius norm in [1/2, 1)
     const int ex = __builtin_amdgcn_frexp_exp(sqrt(all));
+    if (wave < TRI_HOLD / 64) {
 #pragma unroll
-    for (int i = 0; i < TRI_ROWS; ++i)
+        for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int m = 0; m < 8; ++m) a[i][m] = ldexp(a[i][m], -ex);
-
-    if (wave == 0) tri_publish<0>(a[0], 0, S, rg, cg);
-    __syncthreads();
-    tri_block<0>(a, S, W + EIGW_V, rg, cg, wave);
-    if (rg == 30 && cg == 14) S.d[126] = a[3][7];
-    if (rg == 30 && cg == 15) S.e[126] = a[3][7];
-    if (rg == 31 && cg == 15) S.d[127] = a[3][7];
+            for (int m = 0; m < 8; ++m) a[i][m] = ldexp(a[i][m], -ex);
+        if (rg == 0)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) *(f64x2*)(S.row + (q * 16 + cg) * 2) = (f64x2){a[0][2 * q], a[0][2 * q + 1]};
+        __syncthreads();
+        __syncthreads();
+        tri_block<0>(a, S, rg, cg, wave);
+        if (rg == 14 && cg == 14) S.d[126] = a[7][7];
+        if (rg == 14 && cg == 15) S.e[126] = a[7][7];
+        if (rg == 15 && cg == 15) S.d[127] = a[7][7];
+    } else {
+        __builtin_amdgcn_s_setprio(3);      // its chain is the longer one, and it shares its SIMD with a wave of the others
+        __syncthreads();
+        double row[8], v[8];
+        tri_read<0>(row, S.row, cg);
+        tri_publish<0>(row, 0, v, S, lane);
+        __syncthreads();
+        tri_reflect<0>(v, S, W + EIGW_V, lane);
+        __builtin_amdgcn_s_setprio(0);
+    }
     __syncthreads();
     // What the vectors are computed from: T plus a diagonal of up to 6.4e-11 (128 distinct multiples of 5e-13), which
     // separates eigenvalues that are equal to rounding (dead channels, rank-deficient Keys) by enough for
@@ -314,7 +381,7 @@ __global__ __launch_bounds__(TRI_THREADS) void eig_tridiag(const float* __restri
         const double epf = fabs(ep) < 1e-18 ? 1e-18 : ep, enf = fabs(en) < 1e-18 ? 1e-18 : en;
         ((f64x2*)(W + EIGW_DE))[tid] = (f64x2){S.d[tid] + 5e-13 * (double)((37 * tid) & (D - 1)), tid > 0 ? epf * epf : 0.0};
         W[EIGW_E + tid] = enf;
-        W[EIGW_TAU + tid] = tid < D - 2 ? S.tau[tid] : 0.0;
+        W[EIGW_TAU + tid] = tid < D - 2 ? S.ts[tid].x : 0.0;
     }
     if (tid == 0) {
         W[EIGW_SCALE] = ldexp(1.0, ex);
