@@ -56,6 +56,9 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// 16 bytes of fp32 in a caller's array of which no more than the element's alignment is asked
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
 // Device view of rk_rows (see rotatek.h).
 struct RowsDev {
     const void* data;

@@ -4,9 +4,9 @@
 // Four launches, all arithmetic in double:
 //   eig_tridiag      C_q = Q T Q^T by Householder reflections, one work-group per matrix, C_q in registers
 //   eig_tri_vectors  eigenvalues of T by multisection, vectors of T by twisted factorisation, whole chip
-//   eig_orth_back    one Newton-Schulz step on the vectors of T, then R = Q Z, whole chip
-//   eig_finish       rank, mask, keep_idx, R_r, delta_mu; solves the (rare) matrices that the first three
-//                    leave alone by parallel Jacobi
+//   eig_orth_back    one Newton-Schulz step on the vectors of T, then R = Q Z, rank, mask, keep_idx, R_r, whole chip
+//   eig_finish       sums delta_mu; solves the (rare) matrices that the first three leave alone by parallel
+//                    Jacobi, with their rank, mask, keep_idx, R_r and delta_mu
 // The fp64 vector rate of this part equals its unpacked fp32 rate, so double costs registers and LDS width only; it
 // buys vectors that need no iteration over the whole matrix.  A sweep of Jacobi is 127 dependent rounds on one compute
 // unit and 8-10 sweeps are needed; the reduction is 126 dependent steps in all, and everything behind it is independent
@@ -33,6 +33,8 @@ constexpr int EIGW_E = EIGW_DE + 2 * D;            // [128] e_i (e_127 unused)
 constexpr int EIGW_TAU = EIGW_E + D;               // [128] H_k = I - tau_k v_k v_k^T
 constexpr int EIGW_SCALE = EIGW_TAU + D;           // C_q = scale * (Q T Q^T)
 constexpr int EIGW_T = EIGW_SCALE + 2;             // [8][16][16] -T_b of H_{16 b} ... H_{16 b + 15} = I - V_b T_b V_b^T
+constexpr int EIGW_PART = EIGW_DE;                 // [8][128] fp32, in the place of T and tau: shares of R_r R_r^T mu
+static_assert(2 * (EIGW_SCALE - EIGW_PART) >= 8 * D, "eight rows of 128 fp32 numbers");
 constexpr int EIGW_TOTAL = EIGW_T + 8 * 256;
 
 size_t eig_scratch_bytes(size_t U) { return U * EIGW_TOTAL * sizeof(double); }
@@ -718,8 +720,12 @@ __device__ __forceinline__ void ob_block(f64x4 (&z)[2], const double (&T)[4], co
     if constexpr (KB > 0) ob_block<KB - 1>(z, T_next, Tg, Vs, Wx, wave, g, n);
 }
 
-__global__ __launch_bounds__(256) void eig_orth_back(int U, const double* __restrict__ scratch,
-                                                     float* __restrict__ R_out, int32_t* __restrict__ status)
+// Rank, mask, keep_idx, R_r and this slice's share of R_r R_r^T mu are made here as well, where the columns are in registers:
+// the ranks while Z is on its way, and of R_r R_r^T mu 128 sums per slice, for eig_finish.
+__global__ __launch_bounds__(256) void eig_orth_back(int U, double* __restrict__ scratch, float* __restrict__ R_out,
+                                                     int32_t* __restrict__ status, int r, const float* __restrict__ lam,
+                                                     const float* __restrict__ mu, uint8_t* __restrict__ mask_out,
+                                                     int32_t* __restrict__ keep_out, float* __restrict__ Rr_out)
 {
     extern __shared__ __attribute__((aligned(16))) double ob_lds[];
     double* Zs = ob_lds;                    // [128][130] all vectors of T; later the reflections, in natural order
@@ -729,12 +735,34 @@ __global__ __launch_bounds__(256) void eig_orth_back(int U, const double* __rest
     if (u >= U || status[2 * u] != 0) return;
     const int c0 = slice * 16;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, n = lane & 15;
-    const double* W = scratch + (size_t)u * EIGW_TOTAL;
+    double* W = scratch + (size_t)u * EIGW_TOTAL;
+    float mu_row[8], lam_at[32];
+    const float lam_own = lam[(size_t)u * D + c0 + n];
+#pragma unroll
+    for (int i = 0; i < 32; i += 4) {
+        const f32x4_any l = *(const f32x4_any*)(lam + (size_t)u * D + 32 * g + i);
+        lam_at[i] = l.x; lam_at[i + 1] = l.y; lam_at[i + 2] = l.z; lam_at[i + 3] = l.w;
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) mu_row[i] = mu[(size_t)u * D + 16 * wave + 64 * (i >> 2) + 4 * (i & 3) + g];
     // every load of Z is out before the first is waited for; the reflections follow into registers and arrive under the
     // two products
     f64x2 stage[D * D / 512];
 #pragma unroll
     for (int i = 0; i < D * D / 512; ++i) stage[i] = ((const f64x2*)(W + EIGW_Z))[tid + 256 * i];
+    __builtin_amdgcn_sched_barrier(0);
+    // rank of column c0 + n by value, ties to the lower column: a lane group counts over 32 of the others
+    int rank = 0;
+#pragma unroll
+    for (int i = 0; i < 32; ++i)
+        rank += (lam_at[i] > lam_own || (lam_at[i] == lam_own && 32 * g + i < c0 + n)) ? 1 : 0;
+    rank += __shfl_xor(rank, 16);
+    rank += __shfl_xor(rank, 32);
+    const bool kept = rank < r;
+    if (tid < 16) {
+        mask_out[(size_t)u * D + c0 + n] = (uint8_t)kept;
+        if (kept) keep_out[(size_t)u * r + rank] = c0 + n;
+    }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < D * D / 512; ++i) *(f64x2*)(Zs + ((tid >> 6) + 4 * i) * OB_LD + 2 * (tid & 63)) = stage[i];
@@ -802,10 +830,29 @@ __global__ __launch_bounds__(256) void eig_orth_back(int U, const double* __rest
     lds_barrier();
     ob_block<7>(z, T, W + EIGW_T, Zs, Ms, wave, g, n);
     float* R = R_out + (size_t)u * D * D + c0 + n;
+    float* Rk = Rr_out + (size_t)u * D * r + (kept ? rank : 0);
+    double x[8], w = 0.0;                   // the columns as they are stored, and R^T mu
 #pragma unroll
-    for (int q = 0; q < 2; ++q)
+    for (int i = 0; i < 8; ++i) {
+        const int row = 16 * wave + 64 * (i >> 2) + 4 * (i & 3) + g;
+        const float f = (float)z[i >> 2][i & 3];
+        R[row * D] = f;
+        if (kept) Rk[row * r] = f;
+        x[i] = (double)f;
+        w = fma(x[i], (double)mu_row[i], w);
+    }
+    double* ws = Ms + 1024;                 // (ob_block<1>'s sums: everyone has read them before ob_block<0>'s barrier)
+    ws[tid] = w;
+    lds_barrier();
+    w = 0.0;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) R[(16 * wave + 64 * q + 4 * r + g) * D] = (float)z[q][r];
+    for (int i = 0; i < 16; ++i) w += ws[16 * i + n];
+    w = kept ? w : 0.0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] *= w;
+    const double part = tri_fold<8, 0>(x, n);
+    const int i = tri_fold_row<8>(n);
+    if (!(n & 1)) ((float*)(W + EIGW_PART))[slice * D + 16 * wave + 64 * (i >> 2) + 4 * (i & 3) + g] = (float)part;
 }
 
 // ---------------------------------------------------------------------------
@@ -1104,15 +1151,20 @@ __device__ __forceinline__ int jacobi_solve(const float* __restrict__ C, const f
 }
 
 // ---------------------------------------------------------------------------
-// Rank, keep-mask and keep_idx; R_r = R[:, keep] and delta_mu = mu - R_r R_r^T mu (Alg. 1 steps 14 to 16), one
-// work-group per matrix; R is staged in LDS (row stride 129) so that the column reads do not go to memory one by one.
+// delta_mu = mu - R_r R_r^T mu (Alg. 1 steps 14 to 16), one work-group per matrix: for a solved matrix the sum of what
+// eig_orth_back left (the work-groups of the other slices may still be running there, so the sum takes a launch).  A matrix
+// that the reduction left alone is solved by Jacobi, and its rank, mask, keep_idx and R_r = R[:, keep] are made here too; R is
+// staged in LDS (row stride 129) so that the column reads do not go to memory one by one.
 // status NULL: every matrix is solved by Jacobi here.
+// Bound: the launch and one memory round trip.  With the ranks, R_r and both products with mu made here, from R in memory, this
+// kernel took 9.3 us for 32 matrices; the call is 6 us shorter so.
 constexpr int EIGF_LD = D + 1;
 constexpr int EIGF_THREADS = EIG_THREADS, EIGF_PARTS = EIGF_THREADS / D;
 constexpr size_t EIGF_LDS_BYTES = (size_t)(D * EIGF_LD + EIGF_PARTS * D + 3 * D) * sizeof(float) + D * sizeof(int);
 constexpr size_t EIGF_LDS_ALL = EIGF_LDS_BYTES > EIG_LDS_BYTES ? EIGF_LDS_BYTES : EIG_LDS_BYTES;
 __global__ __launch_bounds__(EIGF_THREADS) void eig_finish(const float* __restrict__ cov, const float* __restrict__ sigma,
-                                                           const int32_t* __restrict__ status, int r, float* R,
+                                                           const int32_t* __restrict__ status,
+                                                           const double* __restrict__ scratch, int r, float* R,
                                                            float* lam, uint8_t* __restrict__ mask_out,
                                                            int32_t* __restrict__ keep_out,
                                                            int32_t* __restrict__ sweeps_out,
@@ -1121,13 +1173,27 @@ __global__ __launch_bounds__(EIGF_THREADS) void eig_finish(const float* __restri
 {
     extern __shared__ __attribute__((aligned(16))) float fsm[];
     const int u = blockIdx.x, tid = threadIdx.x;
-    int sweeps = 1;                           // solved by the reduction
-    if (!status || (status[2 * u] | status[2 * u + 1]) != 0) {
-        sweeps = jacobi_solve(cov + (size_t)u * D * D, sigma ? sigma + (size_t)u * D : nullptr, lam + (size_t)u * D,
-                              R + (size_t)u * D * D, fsm);
-        __threadfence_block();
-        __syncthreads();
+    if (status) {                             // (everything is requested before the flags are looked at)
+        const float* part = (const float*)(scratch + (size_t)u * EIGW_TOTAL + EIGW_PART) + (tid & (D - 1));
+        float p[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) p[i] = part[i * D];
+        const float m = mu_in[(size_t)u * D + (tid & (D - 1))];
+        if ((status[2 * u] | status[2 * u + 1]) == 0) {
+            if (tid < D) {
+                double sum = 0.0;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) sum += (double)p[i];
+                dmu_out[(size_t)u * D + tid] = (float)((double)m - sum);
+            }
+            if (tid == 0 && sweeps_out) sweeps_out[u] = 1;       // solved by the reduction
+            return;
+        }
     }
+    const int sweeps = jacobi_solve(cov + (size_t)u * D * D, sigma ? sigma + (size_t)u * D : nullptr, lam + (size_t)u * D,
+                                    R + (size_t)u * D * D, fsm);
+    __threadfence_block();
+    __syncthreads();
     if (tid == 0 && sweeps_out) sweeps_out[u] = sweeps;
     float* Vs = fsm;                          // [128][129]
     float* part = Vs + D * EIGF_LD;           // [parts][128] partial sums
@@ -1224,14 +1290,15 @@ hipError_t launch_eig(bool plain, int U, const float* cov, const float* sigma, c
         if (e != hipSuccess) return e;
         e = allow_dynamic_lds((const void*)eig_orth_back, OB_LDS_BYTES);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(eig_orth_back, dim3(eig_slices(U)), dim3(256), OB_LDS_BYTES, st, U, W, R, status);
+        hipLaunchKernelGGL(eig_orth_back, dim3(eig_slices(U)), dim3(256), OB_LDS_BYTES, st, U, W, R, status,
+                           r, (const float*)lam, mu, mask, keep_idx, Rr);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     e = allow_dynamic_lds((const void*)eig_finish, EIGF_LDS_ALL);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(eig_finish, dim3(U), dim3(EIGF_THREADS), EIGF_LDS_ALL, st, cov, sigma,
-                       plain ? (const int32_t*)nullptr : status, r, R, lam, mask,
+                       plain ? (const int32_t*)nullptr : status, (const double*)W, r, R, lam, mask,
                        keep_idx, sweeps, mu, Rr, dmu);
     return hipGetLastError();
 }
