@@ -17,6 +17,7 @@
 //   - the split-K partials are folded by the unit's last work-group where all of a unit's
 //     work-groups share an L2 (fold_unit), else by a second, tiny kernel as in the paper.
 #include "rk_kernels.hpp"
+#include <type_traits>
 
 namespace rk {
 
@@ -533,9 +534,10 @@ __device__ __forceinline__ void fold_partials(const float* pm, const float* pl, 
 // snew and its Values in v_new enter as one more term; text segment: NEW = false, the splits already counted it); the length of batch item b moves once every work-group of the
 // item -- they sit on different XCDs, hence a second, device-wide set of tickets -- has taken one,
 // i.e. has read the old length and is done with it.
-template <bool NEW>
+// T: storage type of the result (the appended token's Values are read as bf16: NEW comes with bf16 only).
+template <bool NEW, typename T>
 __device__ __forceinline__ void fold_unit(int unit, int S, int b, int u, int Hq, int h0, int Gc, const float* ws_m, const float* ws_l, const float* ws_acc,
-                                          bf16_t* __restrict__ out_merged, int32_t* done, bool bump,
+                                          T* __restrict__ out_merged, int32_t* done, bool bump,
                                           int32_t* batch_tickets, int batch_wgs, int32_t* len_rw, int len_cap,
                                           const float* snew, const bf16_t* __restrict__ v_new, int* sm_last)
 {
@@ -583,13 +585,21 @@ __device__ __forceinline__ void fold_unit(int unit, int S, int b, int u, int Hq,
             }
             M = Mc;
         }
-        const float inv = (M > NEG_INF) ? 1.f / den : 0.f;
-        uint4 pk;
-        pk.x = (uint32_t)f32_to_bf16(n0[0] * inv) | ((uint32_t)f32_to_bf16(n0[1] * inv) << 16);
-        pk.y = (uint32_t)f32_to_bf16(n0[2] * inv) | ((uint32_t)f32_to_bf16(n0[3] * inv) << 16);
-        pk.z = (uint32_t)f32_to_bf16(n1[0] * inv) | ((uint32_t)f32_to_bf16(n1[1] * inv) << 16);
-        pk.w = (uint32_t)f32_to_bf16(n1[2] * inv) | ((uint32_t)f32_to_bf16(n1[3] * inv) << 16);
-        *(uint4*)(out_merged + row * D + c0) = pk;
+        if constexpr (std::is_same<T, float>::value) {
+            f32x4_any* o = (f32x4_any*)(out_merged + row * D + c0);
+            if (M > NEG_INF) { n0 /= den; n1 /= den; }
+            else n0 = n1 = (f32x4){0.f, 0.f, 0.f, 0.f};
+            o[0] = n0;
+            o[1] = n1;
+        } else {
+            const float inv = (M > NEG_INF) ? 1.f / den : 0.f;
+            uint4 pk;
+            pk.x = (uint32_t)f32_to_bf16(n0[0] * inv) | ((uint32_t)f32_to_bf16(n0[1] * inv) << 16);
+            pk.y = (uint32_t)f32_to_bf16(n0[2] * inv) | ((uint32_t)f32_to_bf16(n0[3] * inv) << 16);
+            pk.z = (uint32_t)f32_to_bf16(n1[0] * inv) | ((uint32_t)f32_to_bf16(n1[1] * inv) << 16);
+            pk.w = (uint32_t)f32_to_bf16(n1[2] * inv) | ((uint32_t)f32_to_bf16(n1[3] * inv) << 16);
+            *(uint4*)(out_merged + row * D + c0) = pk;
+        }
     }
     __syncthreads();
     if (tid == 0) done[unit] = 0;                           // ready for the next launch on this context
@@ -1311,10 +1321,11 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
 // step (i, e) takes channel 16 i + 4 g + e in lane group g, so a lane's 16-byte piece of the packed Keys (token n of the
 // tile, channels 16 i + 4 g ..+3) is four operands; the scores of tokens 4 g + ii come out in lane group g, and the
 // 16-byte piece of the Values that holds just those four tokens of channel 16 cb + n is the other operand of four P.V
-// steps.  Partials are folded by decode_merge (or, with a text segment, by decode_text_merge).
+// steps.  Partials are folded inside the launch where decode_split_mfma's are (fold_unit), else by decode_merge, or, with a text
+// segment, by decode_text_merge.
 // Bound: HBM; the matrix work (R / 4 + 32 MFMA of 32 cycles per tile) takes a third of that time at one query head per
 // KV head.  (32 heads x 2944 tokens, r = 64: 59 us through the plain kernel, which reads a cache line per lane and score
-// channel, 19 us here (17 at best), and the merge behind it 4.)
+// channel; 22.3 here with a merge launch behind it, 19.9 with the merge folded in.)
 template <int R>
 struct DecTileF32 {
     f32x4 k[R / 16], v[8];
@@ -1379,24 +1390,37 @@ __device__ __forceinline__ void compute_tile_f32(DecTileF32<R>& T, float& m_run,
         for (int cb = 0; cb < 8; ++cb) O[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(p[ii], T.v[cb][ii], O[cb], 0, 0, 0);
 }
 
-template <int R>
+template <int R, bool FUSED>
 __global__ __launch_bounds__(256, 2) void decode_split_f32(
     const float* __restrict__ q, const float* __restrict__ Kp, const float* __restrict__ Vc, const float* __restrict__ Rr,
     const float* __restrict__ dmu, const int32_t* __restrict__ seq_len, int Hq, int Hkv, int cap, int r, int tiles_all,
-    float scale_log2, float* __restrict__ ws_m, float* __restrict__ ws_l, float* __restrict__ ws_acc, int S,
-    float* __restrict__ out, TextAppendDev ta)
+    float scale_log2, float* ws_m, float* ws_l, float* ws_acc, int S, float* __restrict__ out, TextAppendDev ta,
+    int n_units, float* __restrict__ out_merged, int32_t* done)
 {
     constexpr int NK = R / 16;                     // 16-channel groups, and 16-column blocks of R_r
     constexpr int NBW = (NK + 3) / 4;              // blocks of R_r per wave
     __shared__ f32x4 park[4 * 8 * 64];             // the four waves' O at the end
     __shared__ __attribute__((aligned(16))) float qt[16][R + 4];
     __shared__ float sbias[16], sm_m[4][16], sm_l[4][16];
-    const int split = blockIdx.x, b = blockIdx.z;
+    __shared__ int sm_last;
     const int G = Hq / Hkv, ngrp = (G + 15) >> 4;
-    const int hk = blockIdx.y / ngrp, grp = blockIdx.y - hk * ngrp;
+    int split, by, b, unit = 0;
+    if constexpr (FUSED) {                         // all splits of a unit on one XCD, as in decode_split_mfma
+        const int id = blockIdx.x, upx = (n_units + 7) >> 3, slot = id >> 3, gy = Hkv * ngrp;
+        split = __builtin_amdgcn_readfirstlane(slot / upx);      // (a division by a variable leaves its result in vector registers)
+        unit = 8 * (slot - split * upx) + (id & 7);
+        if (unit >= n_units) return;
+        b = __builtin_amdgcn_readfirstlane(unit / gy);
+        by = unit - b * gy;
+    } else {
+        split = blockIdx.x;
+        by = blockIdx.y;
+        b = blockIdx.z;
+    }
+    const int hk = FUSED ? __builtin_amdgcn_readfirstlane(by / ngrp) : by / ngrp, grp = by - hk * ngrp;
     const int h0 = hk * G + grp * 16, Gc = min(16, G - grp * 16), u = b * Hkv + hk;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, n = lane & 15;
-    if (ta.k && split == 0 && blockIdx.y == 0 && wave == 1) text_append_rows<float>(ta, b, Hkv, lane);
+    if (!FUSED && ta.k && split == 0 && by == 0 && wave == 1) text_append_rows<float>(ta, b, Hkv, lane);
 
     const int seq_raw = seq_len[b];
     const int tp = tiles_all / S, trem = tiles_all - tp * S;     // the last splits get one 128-token tile more
@@ -1440,103 +1464,116 @@ __global__ __launch_bounds__(256, 2) void decode_split_f32(
                 if ((idx & 127) == 0) { ws_m[row * S + split] = NEG_INF; ws_l[row * S + split] = 0.f; }
             }
         }
-        return;
-    }
+    } else {
 #pragma unroll
-    for (int bw = 0; bw < NBW; ++bw) {
-        const int jb = wave + 4 * bw;
-        const bool live = 16 * jb + n < r;                       // columns r .. R - 1 read as zero
-        if (jb < NK) {
-            f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int bw = 0; bw < NBW; ++bw) {
+            const int jb = wave + 4 * bw;
+            const bool live = 16 * jb + n < r;                       // columns r .. R - 1 read as zero
+            if (jb < NK) {
+                f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(live ? ra[bw][i][e] : 0.f, n < Gc ? qf[i][e] : 0.f, acc, 0, 0, 0);
+                *(f32x4*)&qt[n][16 * jb + 4 * g] = acc * scale_log2;
+            }
+        }
+        if (wave == 0) {                                             // bias b_n = q_n . delta_mu
+            float bp = 0.f;
 #pragma unroll
             for (int i = 0; i < 8; ++i)
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(live ? ra[bw][i][e] : 0.f, n < Gc ? qf[i][e] : 0.f, acc, 0, 0, 0);
-            *(f32x4*)&qt[n][16 * jb + 4 * g] = acc * scale_log2;
+                for (int e = 0; e < 4; ++e) bp = fmaf(qf[i][e], dm[i][e], bp);
+            bp += __shfl_xor(bp, 16);
+            bp += __shfl_xor(bp, 32);
+            if (g == 0) sbias[n] = dmu ? bp * scale_log2 : 0.f;
+        }
+        load_tile_f32<R>(TB, Ku, Vu, tokA + 64 + 16 <= t_spec ? tokA + 64 : 0, lane);
+        __syncthreads();
+        f32x4 qb[NK];
+#pragma unroll
+        for (int i = 0; i < NK; ++i) qb[i] = *(const f32x4*)&qt[n][16 * i + 4 * g];
+
+        float m_run = NEG_INF, l_run = 0.f;
+        f32x4 O[8];
+#pragma unroll
+        for (int cb = 0; cb < 8; ++cb) O[cb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        const int ntiles = (t1 - t0 + 15) >> 4, nk = (ntiles - wave + 3) >> 2;
+        int k = 0;
+        for (; k + 3 < nk; k += 2) {
+            compute_tile_f32<R>(TA, m_run, l_run, O, qb, tokA + 64 * k, t1, g);
+            load_tile_f32<R>(TA, Ku, Vu, tokA + 64 * (k + 2), lane);
+            compute_tile_f32<R>(TB, m_run, l_run, O, qb, tokA + 64 * (k + 1), t1, g);
+            load_tile_f32<R>(TB, Ku, Vu, tokA + 64 * (k + 3), lane);
+        }
+        if (k < nk) {
+            compute_tile_f32<R>(TA, m_run, l_run, O, qb, tokA + 64 * k, t1, g);
+            if (k + 2 < nk) load_tile_f32<R>(TA, Ku, Vu, tokA + 64 * (k + 2), lane);
+        }
+        if (k + 1 < nk) compute_tile_f32<R>(TB, m_run, l_run, O, qb, tokA + 64 * (k + 1), t1, g);
+        if (k + 2 < nk) compute_tile_f32<R>(TA, m_run, l_run, O, qb, tokA + 64 * (k + 2), t1, g);
+
+        // merge the four waves' states, lane to lane (all hold O in one layout: heads 4 g + ii, channel 16 cb + n)
+        l_run += __shfl_xor(l_run, 16);
+        l_run += __shfl_xor(l_run, 32);
+#pragma unroll
+        for (int cb = 0; cb < 8; ++cb) park[(wave * 8 + cb) * 64 + lane] = O[cb];
+        if (g == 0) { sm_m[wave][n] = m_run; sm_l[wave][n] = l_run; }
+        __syncthreads();
+        f32x4 wgt[4], Mh, lh = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ii = 0; ii < 4; ++ii) {
+            const int hh = 4 * g + ii;
+            const float M = fmaxf(fmaxf(sm_m[0][hh], sm_m[1][hh]), fmaxf(sm_m[2][hh], sm_m[3][hh]));
+            Mh[ii] = M;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const float x = sm_m[w][hh] > NEG_INF ? exp2f(sm_m[w][hh] - M) : 0.f;
+                wgt[w][ii] = x;
+                lh[ii] = fmaf(sm_l[w][hh], x, lh[ii]);
+            }
+        }
+#pragma unroll
+        for (int c2 = 0; c2 < 2; ++c2) {
+            const int cb = 2 * wave + c2;
+            f32x4 acc = park[cb * 64 + lane] * wgt[0];
+#pragma unroll
+            for (int w = 1; w < 4; ++w) acc += park[(w * 8 + cb) * 64 + lane] * wgt[w];
+#pragma unroll
+            for (int ii = 0; ii < 4; ++ii)
+                if (4 * g + ii < Gc) {
+                    const size_t row = (size_t)b * Hq + h0 + 4 * g + ii;
+                    if (out) out[row * D + 16 * cb + n] = Mh[ii] > NEG_INF ? acc[ii] / lh[ii] : 0.f;
+                    else ws_acc[(row * S + split) * D + 16 * cb + n] = acc[ii];
+                }
+        }
+        if (!out && wave == 0 && n == 0) {
+#pragma unroll
+            for (int ii = 0; ii < 4; ++ii)
+                if (4 * g + ii < Gc) {
+                    const size_t row = (size_t)b * Hq + h0 + 4 * g + ii;
+                    ws_m[row * S + split] = Mh[ii] + sbias[4 * g + ii];
+                    ws_l[row * S + split] = lh[ii];
+                }
         }
     }
-    if (wave == 0) {                                             // bias b_n = q_n . delta_mu
-        float bp = 0.f;
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) bp = fmaf(qf[i][e], dm[i][e], bp);
-        bp += __shfl_xor(bp, 16);
-        bp += __shfl_xor(bp, 32);
-        if (g == 0) sbias[n] = dmu ? bp * scale_log2 : 0.f;
-    }
-    load_tile_f32<R>(TB, Ku, Vu, tokA + 64 + 16 <= t_spec ? tokA + 64 : 0, lane);
-    __syncthreads();
-    f32x4 qb[NK];
-#pragma unroll
-    for (int i = 0; i < NK; ++i) qb[i] = *(const f32x4*)&qt[n][16 * i + 4 * g];
-
-    float m_run = NEG_INF, l_run = 0.f;
-    f32x4 O[8];
-#pragma unroll
-    for (int cb = 0; cb < 8; ++cb) O[cb] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    const int ntiles = (t1 - t0 + 15) >> 4, nk = (ntiles - wave + 3) >> 2;
-    int k = 0;
-    for (; k + 3 < nk; k += 2) {
-        compute_tile_f32<R>(TA, m_run, l_run, O, qb, tokA + 64 * k, t1, g);
-        load_tile_f32<R>(TA, Ku, Vu, tokA + 64 * (k + 2), lane);
-        compute_tile_f32<R>(TB, m_run, l_run, O, qb, tokA + 64 * (k + 1), t1, g);
-        load_tile_f32<R>(TB, Ku, Vu, tokA + 64 * (k + 3), lane);
-    }
-    if (k < nk) {
-        compute_tile_f32<R>(TA, m_run, l_run, O, qb, tokA + 64 * k, t1, g);
-        if (k + 2 < nk) load_tile_f32<R>(TA, Ku, Vu, tokA + 64 * (k + 2), lane);
-    }
-    if (k + 1 < nk) compute_tile_f32<R>(TB, m_run, l_run, O, qb, tokA + 64 * (k + 1), t1, g);
-    if (k + 2 < nk) compute_tile_f32<R>(TA, m_run, l_run, O, qb, tokA + 64 * (k + 2), t1, g);
-
-    // merge the four waves' states, lane to lane (all hold O in one layout: heads 4 g + ii, channel 16 cb + n)
-    l_run += __shfl_xor(l_run, 16);
-    l_run += __shfl_xor(l_run, 32);
-#pragma unroll
-    for (int cb = 0; cb < 8; ++cb) park[(wave * 8 + cb) * 64 + lane] = O[cb];
-    if (g == 0) { sm_m[wave][n] = m_run; sm_l[wave][n] = l_run; }
-    __syncthreads();
-    f32x4 wgt[4], Mh, lh = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ii = 0; ii < 4; ++ii) {
-        const int hh = 4 * g + ii;
-        const float M = fmaxf(fmaxf(sm_m[0][hh], sm_m[1][hh]), fmaxf(sm_m[2][hh], sm_m[3][hh]));
-        Mh[ii] = M;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const float x = sm_m[w][hh] > NEG_INF ? exp2f(sm_m[w][hh] - M) : 0.f;
-            wgt[w][ii] = x;
-            lh[ii] = fmaf(sm_l[w][hh], x, lh[ii]);
-        }
-    }
-#pragma unroll
-    for (int c2 = 0; c2 < 2; ++c2) {
-        const int cb = 2 * wave + c2;
-        f32x4 acc = park[cb * 64 + lane] * wgt[0];
-#pragma unroll
-        for (int w = 1; w < 4; ++w) acc += park[(w * 8 + cb) * 64 + lane] * wgt[w];
-#pragma unroll
-        for (int ii = 0; ii < 4; ++ii)
-            if (4 * g + ii < Gc) {
-                const size_t row = (size_t)b * Hq + h0 + 4 * g + ii;
-                if (out) out[row * D + 16 * cb + n] = Mh[ii] > NEG_INF ? acc[ii] / lh[ii] : 0.f;
-                else ws_acc[(row * S + split) * D + 16 * cb + n] = acc[ii];
-            }
-    }
-    if (!out && wave == 0 && n == 0) {
-#pragma unroll
-        for (int ii = 0; ii < 4; ++ii)
-            if (4 * g + ii < Gc) {
-                const size_t row = (size_t)b * Hq + h0 + 4 * g + ii;
-                ws_m[row * S + split] = Mh[ii] + sbias[4 * g + ii];
-                ws_l[row * S + split] = lh[ii];
-            }
-    }
+    if constexpr (FUSED)
+        fold_unit<false>(unit, S, b, u, Hq, h0, Gc, ws_m, ws_l, ws_acc, out_merged, done, false, nullptr, 0, nullptr, 0, nullptr,
+                         nullptr, &sm_last);
 }
 
 // ---------------------------------------------------------------------------
+// Merge folded into the split launch: the splits of a unit share an XCD there, so a unit count that is not a multiple of 8
+// loads the XCDs unevenly (4 units: half of them idle).  The busiest XCD then streams ceil(nunit / 8) * 8 / nunit times
+// its fair share; folded is chosen while that excess, priced at the chip's streaming rate, stays below what the second
+// launch costs (bf16: 4 units x 4K tokens 9.8 us folded against 11.6 us, 4 units x 16K tokens 14.6 against 13.5 us).
+static bool fold_pays(int nunit, int tiles_all, int r, int elem)
+{
+    const double cache_bytes = (double)nunit * tiles_all * 128.0 * (keep_padded(r) + D) * elem;
+    return ((double)((nunit + 7) / 8 * 8) / nunit - 1.0) * cache_bytes / 6.5e6 < 3.0;
+}
+
 bool decode_mfma_supported(int dtype, int r) { return dtype == 1 && r >= 1 && r <= 128; }
 
 template <int R>
@@ -1591,15 +1628,8 @@ hipError_t launch_decode(int dtype, bool mfma, int B, int Hq, int Hkv, int cap, 
         const int G = Hq / Hkv, ngrp = (G + 15) / 16;
         const int nunit = B * Hkv * ngrp;
         dim3 grid(S, Hkv * ngrp, B);                    // (split, (h_kv, head group), b)
-        // Merge folded into the split launch: the splits of a unit share an XCD there, so a unit count
-        // that is not a multiple of 8 loads the XCDs unevenly (4 units: half of them idle).  The busiest
-        // XCD then streams ceil(nunit / 8) * 8 / nunit times its fair share; folded is chosen while that
-        // excess, priced at the chip's streaming rate, stays below what the second launch costs
-        // (measured: 4 units x 4K tokens 9.8 us folded against 11.6 us, 4 units x 16K tokens 14.6 against 13.5 us).
-        const double cache_bytes = (double)nunit * tiles_all * 128.0 * (keep_padded(r) + D) * 2.0;
-        const double excess_us = ((double)((nunit + 7) / 8 * 8) / nunit - 1.0) * cache_bytes / 6.5e6;
         const bool fused_merge = ((!app && !tapp) || batch_tickets) && (S >= 2 || tapp) && counters && nunit <= n_counters &&
-                                 excess_us < 3.0;
+                                 fold_pays(nunit, tiles_all, r, 2);
         if (fused_merge) grid = dim3((unsigned)(8 * ((nunit + 7) / 8) * S));
         const bf16_t* q_ = (const bf16_t*)q;
         // the caches are written only by a fused append, whose caller handed them over writable
@@ -1622,20 +1652,27 @@ hipError_t launch_decode(int dtype, bool mfma, int B, int Hq, int Hkv, int cap, 
         e = hipGetLastError();
         if (e != hipSuccess || direct || fused_merge) return e;
     } else if (mfma && dtype == 0) {
-        const dim3 grid(S, Hkv * ((Hq / Hkv + 15) / 16), B);
+        const int gy = Hkv * ((Hq / Hkv + 15) / 16), nunit = B * gy;
+        const bool fused_merge = !text && S >= 2 && counters && nunit <= n_counters && fold_pays(nunit, tiles_all, r, 4);
+        const dim3 grid = fused_merge ? dim3((unsigned)(8 * ((nunit + 7) / 8) * S)) : dim3(S, gy, B);
         float* o = direct ? (float*)out : nullptr;
+#define RK_FORM(RV, FUSED)                                                                                       \
+    hipLaunchKernelGGL((decode_split_f32<RV, FUSED>), grid, dim3(256), 0, st, (const float*)q, (const float*)Kp,  \
+                       (const float*)Vc, Rr, dmu, seq_len, Hq, Hkv, cap, r, tiles_all, sl2, ws_m, ws_l, ws_acc, S, o, ta, \
+                       nunit, (float*)out, counters)
 #define RK_CASE(RV)                                                                                              \
     case RV:                                                                                                     \
-        hipLaunchKernelGGL(decode_split_f32<RV>, grid, dim3(256), 0, st, (const float*)q, (const float*)Kp,       \
-                           (const float*)Vc, Rr, dmu, seq_len, Hq, Hkv, cap, r, tiles_all, sl2, ws_m, ws_l, ws_acc, S, o, ta); \
+        if (fused_merge) RK_FORM(RV, true);                                                                      \
+        else RK_FORM(RV, false);                                                                                 \
         break;
         switch (keep_padded(r)) {
             RK_CASE(16) RK_CASE(32) RK_CASE(48) RK_CASE(64) RK_CASE(80) RK_CASE(96) RK_CASE(112) RK_CASE(128)
             default: return hipErrorInvalidValue;
         }
 #undef RK_CASE
+#undef RK_FORM
         e = hipGetLastError();
-        if (e != hipSuccess || direct) return e;
+        if (e != hipSuccess || direct || fused_merge) return e;
     } else {
         dim3 grid(S, Hq, B);
         if (dtype == 0)

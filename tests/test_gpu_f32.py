@@ -132,6 +132,34 @@ def test_decode(ctx, case):
             assert not got[b].any()
 
 
+# The merge inside the split launch against the merge launch: the same partials folded in the same order, so the same bits.  Unit
+# counts around the eight XCDs, up to 40 splits (three rounds of loads), empty splits and sequences, two head groups, and a result
+# that is only 4-byte aligned.
+@pytest.mark.parametrize("B,Hq,Hkv,L,lengths,r,splits", [
+    (2, 14, 7, 700, [700, 0], 37, 0), (1, 8, 8, 513, None, 64, 2), (3, 9, 3, 1300, [1300, 129, 1], 128, 9), (1, 40, 2, 300, None, 100, 3),
+    (1, 17, 17, 5200, None, 16, 40), (5, 32, 8, 260, [260, 0, 128, 129, 31], 112, 0),
+])
+def test_merge_in_the_split_launch(ctx, B, Hq, Hkv, L, lengths, r, splits):
+    data = layer(B, Hq, Hkv, L, "f32", 65, lengths=lengths, mean_shift=1.0)
+    p = run_prefill(ctx, data, B, Hq, Hkv, L, r, "f32", lengths=lengths)
+    q = to_dev(data["q"], "f32")
+    rk.rk_set_option(ctx, rk.RK_OPT_DECODE_SPLITS, splits)
+    got = []
+    try:
+        for fuse in (1, 0, 1):
+            rk.rk_set_option(ctx, rk.RK_OPT_FUSE_MERGE, fuse)
+            lay = p.layout()
+            ws = torch.full((rk.rk_decode_workspace_size(ctx, lay),), 0xff, device=DEV, dtype=torch.uint8)
+            out = torch.full((B * Hq * D + 1,), float("nan"), device=DEV)[1:].view(B, Hq, D)
+            rk.rk_decode_attn(ctx, lay, q, p.Kp, p.Vc, p.Rr, p.dmu, 0.0, out, ws)
+            got.append(out.cpu().numpy())
+    finally:
+        rk.rk_set_option(ctx, rk.RK_OPT_FUSE_MERGE, 1)
+        rk.rk_set_option(ctx, rk.RK_OPT_DECODE_SPLITS, 0)
+    check_out(got[0], oracle_decode(p, data["q"], lengths or [L] * B), "f32")
+    assert np.array_equal(got[0], got[1]) and np.array_equal(got[0], got[2])
+
+
 # Tokens whose score overflows to minus infinity weigh nothing, also where they fill a 16-token tile, a wave's first one,
 # or the cache (its output is then zero).
 @pytest.mark.parametrize("L,masked,splits", [(200, range(16), 1), (200, [199], 1), (97, [96], 2), (400, range(64), 3),
