@@ -59,6 +59,24 @@ __device__ __forceinline__ void lds_barrier() {
 // 16 bytes of fp32 in a caller's array of which no more than the element's alignment is asked
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 
+// a double through a data-parallel-primitive lane permutation
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v)
+{
+    int lo = __double2loint(v), hi = __double2hiint(v);
+    lo = __builtin_amdgcn_mov_dpp(lo, CTRL, 0xf, 0xf, true);
+    hi = __builtin_amdgcn_mov_dpp(hi, CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+// sum over each aligned group of 16 lanes, the same bits in all of them
+__device__ __forceinline__ double row16_sum_f64(double v)
+{
+    v += dpp_f64<0xB1>(v);       // quad_perm [1, 0, 3, 2]
+    v += dpp_f64<0x4E>(v);       // quad_perm [2, 3, 0, 1]
+    v += dpp_f64<0x141>(v);      // row_half_mirror
+    v += dpp_f64<0x140>(v);      // row_mirror
+    return v;
+}
 // Device view of rk_rows (see rotatek.h).
 struct RowsDev {
     const void* data;

@@ -41,23 +41,6 @@ size_t eig_scratch_bytes(size_t U) { return U * EIGW_TOTAL * sizeof(double); }
 
 __host__ __device__ constexpr int eig_spread(int j) { return (((j >> 5) * 16 + (j & 15)) << 1) | ((j >> 4) & 1); }
 
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v)
-{
-    int lo = __double2loint(v), hi = __double2hiint(v);
-    lo = __builtin_amdgcn_mov_dpp(lo, CTRL, 0xf, 0xf, true);
-    hi = __builtin_amdgcn_mov_dpp(hi, CTRL, 0xf, 0xf, true);
-    return __hiloint2double(hi, lo);
-}
-// sum over each aligned group of 16 lanes, the same bits in all of them
-__device__ __forceinline__ double row16_sum_f64(double v)
-{
-    v += dpp_f64<0xB1>(v);       // quad_perm [1, 0, 3, 2]
-    v += dpp_f64<0x4E>(v);       // quad_perm [2, 3, 0, 1]
-    v += dpp_f64<0x141>(v);      // row_half_mirror
-    v += dpp_f64<0x140>(v);      // row_mirror
-    return v;
-}
 // 1 / x: hardware estimate and two Newton steps
 __device__ __forceinline__ double rcp_f64(double x)
 {

@@ -5,7 +5,7 @@
 //
 // Everything but the 16 x 16 factorisations runs on the fp64 matrix cores (v_mfma_f64_16x16x4), whose rate equals the
 // vector rate here, but whose operands come 256 FMA to a lane's double: the vector form of this kernel was bound by LDS
-// reads and by one barrier per column (163 / 235 / 377 us at k = 32 / 64 / 96, T = 5, 32 heads; now 65 / 128 / 207 us).
+// reads and by one barrier per column (163 / 235 / 377 us at k = 32 / 64 / 96, T = 5, 32 heads; now 61 / 120 / 195 us).
 // Lane (g, n) = (lane / 16, lane % 16).  A 16x16x4 step takes A[n][g], B[g][n]; result register r is D[4 r + g][n].
 // A tile held in that result layout is therefore, register by register, the B operand of a product that contracts over
 // its rows, and, read as its transpose, the A operand.  The whole round is arranged around that:
@@ -46,9 +46,7 @@ __device__ __forceinline__ double sub_make(uint32_t lo, uint32_t hi) { return __
 template <int J>
 __device__ __forceinline__ double sub_row_bcast(double v)
 {
-    constexpr int ctrl = 0x150 + J;                       // DPP row_newbcast
-    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), ctrl, 0xf, 0xf, true),
-                            __builtin_amdgcn_mov_dpp(__double2loint(v), ctrl, 0xf, 0xf, true));
+    return __builtin_amdgcn_mov_dpp(v, 0x150 + J, 0xf, 0xf, true);      // DPP row_newbcast, which takes 64 bits at a time
 }
 // value of lane (G0, n) for every lane (., n): odd and even rows of 16 lanes exchanged, then the halves of the wave
 template <int G0>
@@ -64,18 +62,20 @@ __device__ __forceinline__ double sub_group_bcast(double v)
 {
     return sub_make(sub_group_bcast32<G0>((uint32_t)__double2loint(v)), sub_group_bcast32<G0>((uint32_t)__double2hiint(v)));
 }
-// 1 / g for g > 0: hardware estimate and two Newton steps
-__device__ __forceinline__ double sub_rcp(double g)
+// 1 / sqrt(a) for a > 0: hardware estimate and one third-order step
+__device__ __forceinline__ double sub_rsqrt(double a)
 {
-    double r = __builtin_amdgcn_rcp(g);
-    r = fma(r, fma(-g, r, 1.0), r);
-    return fma(r, fma(-g, r, 1.0), r);
+    const double y = __builtin_amdgcn_rsq(a), r = fma(-(a * y), y, 1.0);
+    return fma(y * r, fma(r, 0.375, 0.5), y);
 }
 
 // Steps J .. 15 of the elimination of [x | m] = [G_JJ | I] in one wave: lane (g, n) holds elements (n, 4 q + g) of both.
-// Row n loses (G[n][J] / pivot) times row J; what is left of m is L^{-1} with a unit diagonal, and the pivots are D.
+// Row n becomes (pivot times itself - G[n][J] times row J) / 2^e, 2^e the pivot's power of two, so that no reciprocal stands
+// between one pivot and the next; the pivot's mantissa, in [1/2, 1), scales all the rows below alike, and `scale` keeps
+// their product: what is left of m is scale times L^{-1}, and the pivots are scale times D.  (With the reciprocal, 1 / pivot, in
+// the chain the kernel took 62 / 124 / 201 us at k = 32 / 64 / 96; with lanes' values moved by halves besides, 65 / 129 / 207.)
 template <int J>
-__device__ __forceinline__ void sub_eliminate(double (&x)[4], double (&m)[4], double& own, bool& bad, int n)
+__device__ __forceinline__ void sub_eliminate(double (&x)[4], double (&m)[4], double& own, double& scale, bool& bad, int n)
 {
     if constexpr (J < 16) {
         constexpr int QJ = J >> 2, GJ = J & 3;
@@ -84,12 +84,15 @@ __device__ __forceinline__ void sub_eliminate(double (&x)[4], double (&m)[4], do
                                           __builtin_amdgcn_readlane(__double2loint(x[QJ]), src));
         bad = bad || !(p > 0.0);
         own = n == J ? p : own;
-        const double f = n > J ? -sub_group_bcast<GJ>(x[QJ]) * sub_rcp(p) : 0.0;
+        const double col = sub_group_bcast<GJ>(x[QJ]);
+        const double keep = n > J ? __builtin_amdgcn_frexp_mant(p) : 1.0;
+        const double f = n > J ? -ldexp(col, -__builtin_amdgcn_frexp_exp(p)) : 0.0;
+        scale *= keep;
 #pragma unroll
-        for (int q = QJ; q < 4; ++q) x[q] = fma(f, sub_row_bcast<J>(x[q]), x[q]);
+        for (int q = QJ; q < 4; ++q) x[q] = fma(f, sub_row_bcast<J>(x[q]), keep * x[q]);
 #pragma unroll
-        for (int q = 0; q <= QJ; ++q) m[q] = fma(f, sub_row_bcast<J>(m[q]), m[q]);
-        sub_eliminate<J + 1>(x, m, own, bad, n);
+        for (int q = 0; q < 4; ++q) m[q] = q <= QJ ? fma(f, sub_row_bcast<J>(m[q]), keep * m[q]) : keep * m[q];
+        sub_eliminate<J + 1>(x, m, own, scale, bad, n);
     }
 }
 
@@ -97,15 +100,15 @@ __device__ __forceinline__ void sub_eliminate(double (&x)[4], double (&m)[4], do
 __device__ __forceinline__ void sub_factor(f64x4 x4, double* __restrict__ tile, int* __restrict__ flag, int lane)
 {
     const int g = lane >> 4, n = lane & 15;
-    double x[4], m[4], own = 1.0;
+    double x[4], m[4], own = 1.0, scale = 1.0;
     bool bad = false;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         x[q] = x4[q];
         m[q] = n == 4 * q + g ? 1.0 : 0.0;
     }
-    sub_eliminate<0>(x, m, own, bad, n);
-    const double sc = 1.0 / sqrt(own);
+    sub_eliminate<0>(x, m, own, scale, bad, n);
+    const double sc = sub_rsqrt(own * scale);
     ((f64x2*)tile)[2 * lane] = (f64x2){m[0] * sc, m[1] * sc};
     ((f64x2*)tile)[2 * lane + 1] = (f64x2){m[2] * sc, m[3] * sc};
     if (lane == 0 && bad) *flag = 1;
@@ -230,8 +233,8 @@ __global__ __launch_bounds__(SUB_THREADS) void subspace_iter(const float* __rest
                 d[h] = a < k ? G[at[h]] : 0.0;
                 tr += d[h];
             }
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) tr += __shfl_xor(tr, o);
+            tr = row16_sum_f64(tr);
+            tr = (sub_group_bcast<0>(tr) + sub_group_bcast<1>(tr)) + (sub_group_bcast<2>(tr) + sub_group_bcast<3>(tr));
             const double rho = eps * tr / (double)k;
 #pragma unroll
             for (int h = 0; h < 2; ++h)

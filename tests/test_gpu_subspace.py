@@ -83,6 +83,20 @@ def test_subspace_parity(ctx, case):
             assert np.abs(dmu[b, h] - want_dmu).max() <= TOL_F32 * max(np.abs(mu[b, h]).max(), 1e-30)
 
 
+@pytest.mark.parametrize("scale,k", [(1e12, 40), (1e-12, 40), (1e-12, 16)])
+def test_scales(ctx, scale, k):
+    """The elimination scales its rows by powers of two of its pivots, which lie far from 1 here."""
+    B, Hkv, L = 1, 2, 400
+    data = layer(B, Hkv, Hkv, L, "f32", 50)
+    p = Pipeline(ctx, B, Hkv, Hkv, k, "f32", L)
+    V0 = start_basis(B, Hkv, k, 51)
+    assert not fit_subspace(ctx, p, to_dev(data["K"] * np.float32(scale), "f32"), L, V0).any()
+    cov, Rr = to_host(p.cov), to_host(p.Rr)
+    for h in range(Hkv):
+        want = oracle.subspace_iter(oracle.weight(cov[0, h], None), V0[0, h].astype(np.float64), 5, 1e-6)
+        assert rel_max(Rr[0, h], want) <= TOL_F32
+
+
 def test_zero_keys_report_the_failed_pivot(ctx):
     """All-zero Keys: C_q = 0, the Gram matrix is 0 and, without a ridge, the first pivot is
     not positive.  The oracle reports iteration 0; the kernel must report the same code."""
