@@ -563,6 +563,81 @@ __global__ __launch_bounds__(256) void cov_finalize_tiled(RowsDev rows, int Hkv,
     if (br != bc) Cu[cch * D + rch] = (float)acc;       // diagonal tiles hold both (r, c) and (c, r)
 }
 
+// The same sums in the same order for many units, one work-group per (b, h_kv) and class of rows: the 32 channels of one
+// channel block, whose four tiles (those of the blocks before it transposed) come out through LDS as whole rows of cov.  In
+// cov_finalize_tiled every position stores four bytes here and four there, a line's pieces from work-groups on different XCDs, and
+// 40 work-groups per unit form the mean.  128 units of 3 chunks 12.8 -> 9.8 us, 512 of one 35.7 -> 17.2.
+template <bool F32>
+__global__ __launch_bounds__(256) void cov_finalize_rows(RowsDev rows, int Hkv, int n_chunks, int center,
+                                                         const float* __restrict__ part_S, const float* __restrict__ part_sum,
+                                                         float* __restrict__ cov, float* __restrict__ mu_out)
+{
+    constexpr int LD = D + 4, NC = 4;
+    __shared__ double smu[D];
+    __shared__ __attribute__((aligned(16))) float out[32 * LD];
+    const int u = blockIdx.y, q = blockIdx.x, b = u / Hkv, tid = threadIdx.x, lane = tid & 63;
+    const int n_b = rows_count(rows, b);
+    // four positions of each tile: groups [tile][i / 4][lane][i % 4] of cov_partial_mfma
+    const f32x4* pS = (const f32x4*)(part_S + (size_t)u * n_chunks * (D * D)) + tid;
+    auto tile = [&](int c) { const int lo = min(q, c), hi = max(q, c); return 4 * lo - lo * (lo - 1) / 2 + hi - lo; };
+    f32x4 v[NC][4];
+    auto load = [&](int ch) {
+#pragma unroll
+        for (int k = 0; k < NC; ++k)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[k][c] = pS[(size_t)min(ch + k, n_chunks - 1) * (D * D / 4) + 256 * tile(c)];
+    };
+    load(0);                                            // requested before the mean is formed
+    if (tid < D) {
+        const float* ps = part_sum + (size_t)u * n_chunks * D + tid;
+        double s = 0.0;
+        for (int ch = 0; ch < n_chunks; ch += 8) {
+            float w[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) w[k] = ps[(size_t)min(ch + k, n_chunks - 1) * D];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) s += ch + k < n_chunks ? (double)w[k] : 0.0;
+        }
+        const double m = n_b > 0 ? s / (double)n_b : 0.0;
+        smu[tid] = m;
+        if (q == 0) mu_out[(size_t)u * D + tid] = (float)m;
+    }
+    __syncthreads();
+    double acc[4][4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[c][e] = 0.0;
+    for (int ch = 0; ch < n_chunks; ch += NC) {
+        if (ch) load(ch);
+#pragma unroll
+        for (int k = 0; k < NC; ++k)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[c][e] += ch + k < n_chunks ? (double)v[k][c][e] : 0.0;
+    }
+    auto channel = [](int block, int m) { return F32 ? 4 * m + block : ((m & 15) << 3) | (block << 1) | (m >> 4); };
+    const int mc = lane & 31;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int mr = 8 * (tid >> 6) + 4 * (lane >> 5) + e;
+            const int row = q <= c ? mr : mc, col = channel(c, q <= c ? mc : mr);
+            double x = acc[c][e];
+            if (center) x -= (double)n_b * (smu[channel(q, row)] * smu[col]);
+            out[row * LD + col] = (float)x;
+        }
+    __syncthreads();
+    float* Cu = cov + (size_t)u * D * D;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int row = (tid >> 5) + 8 * k;
+        *(f32x4_any*)(Cu + channel(q, row) * D + 4 * (tid & 31)) = *(const f32x4*)(out + row * LD + 4 * (tid & 31));
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Most chunks under COV_CHUNK tokens that a call makes per (b, h_kv): fp32 only, 512 work-groups in all (the workspace is sized
 // by it, without a device to ask).
@@ -647,7 +722,11 @@ hipError_t launch_cov_partial(int dtype, bool mfma, const RowsDev& rows, int B, 
 hipError_t launch_cov_finalize(int dtype, bool mfma, const RowsDev& rows, int B, int Hkv, int n_chunks, bool center,
                                const float* part_S, const float* part_sum, float* cov, float* mu, hipStream_t st)
 {
-    if (mfma && dtype == 1)
+    // from two work-groups a compute unit on: on 32 units the positions' 1280 small ones take 6.2 us, the rows' 128 8.5
+    if (mfma && B * Hkv >= 128) {
+        const auto kernel = dtype == 1 ? cov_finalize_rows<false> : cov_finalize_rows<true>;
+        hipLaunchKernelGGL(kernel, dim3(4, B * Hkv), dim3(256), 0, st, rows, Hkv, n_chunks, center ? 1 : 0, part_S, part_sum, cov, mu);
+    } else if (mfma && dtype == 1)
         hipLaunchKernelGGL(cov_finalize_tiled<false>, dim3(40, B * Hkv), dim3(256), 0, st, rows, Hkv, n_chunks,
                            center ? 1 : 0, part_S, part_sum, cov, mu);
     else if (mfma)

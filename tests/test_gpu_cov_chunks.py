@@ -42,3 +42,27 @@ def test_chunk_lengths(B, Hkv, L, lengths, lists):
             scale = max(np.abs(C_o).max(), 1e-2 * np.abs(data["K"][b, h, :n]).max() ** 2 * n)
             assert np.abs(cov[b, h] - C_o).max() <= 1e-4 * scale
             assert rel_max(mu[b, h], mu_o) <= 1e-4
+
+
+def test_many_units_fp32():
+    """From 128 heads on the reduction goes by rows, four chunks at a time: five of 512 tokens here, in the fp32 kernel's channel order
+    (the bf16 one above has two)."""
+    B, Hkv, L, lengths = 4, 32, 2100, [2100, 2048, 513, 0]
+    ctx = rk.rk_create(0)
+    data = layer(B, Hkv, Hkv, L, "f32", 73, lengths=lengths, mean_shift=2.0)
+    p = Pipeline(ctx, B, Hkv, Hkv, 16, "f32", L)
+    p.cov.fill_(float("nan"))
+    for center in (True, False):
+        p.fit(to_dev(data["K"], "f32"), L, center=center, n_dev=torch.tensor(lengths, device=DEV, dtype=torch.int32))
+        cov, mu = to_host(p.cov), to_host(p.mu)
+        for b in range(B):
+            n = lengths[b]
+            for h in (0, 9, 31):
+                assert np.array_equal(cov[b, h], cov[b, h].T)
+                if n == 0:
+                    assert not cov[b, h].any() and not mu[b, h].any()
+                    continue
+                mu_o, C_o = oracle.mean_scatter(data["K"][b, h, :n], center=center)
+                assert np.abs(cov[b, h] - C_o).max() <= 1e-4 * np.abs(C_o).max()
+                assert rel_max(mu[b, h], mu_o) <= 1e-4
+    rk.rk_destroy(ctx)
