@@ -387,18 +387,29 @@ __device__ __forceinline__ void eig_slice(int& u, int& slice)
 }
 static unsigned eig_slices(int U) { return 64u * (unsigned)((U + 7) / 8); }
 
+__device__ __forceinline__ int row16_sum_i32(int v)
+{
+    v += __builtin_amdgcn_mov_dpp(v, 0xB1, 0xf, 0xf, true);      // the lane permutations of row16_sum_f64
+    v += __builtin_amdgcn_mov_dpp(v, 0x4E, 0xf, 0xf, true);
+    v += __builtin_amdgcn_mov_dpp(v, 0x141, 0xf, 0xf, true);
+    return v + __builtin_amdgcn_mov_dpp(v, 0x140, 0xf, 0xf, true);
+}
+
 // Eigenpairs of T, four per wave, 16 lanes each; a work-group makes 16 of a matrix's 128.
 // Eigenvalue by multisection: the 16 lanes count the eigenvalues below 16 points of the interval (sign changes of
 // the three-term recurrence p_{i+1} = (d_i - x) p_i - e_{i-1}^2 p_{i-1}, division-free, rescaled every 16 steps: a step is at
-// least a factor 5e-13 but for one, so 16 stay above 1e-250) and the
-// interval shrinks 17-fold, 12 times: 2 / 17^12 = 3e-15.  T comes through the scalar cache, 8 rows ahead: one wave
-// per SIMD has nobody else to hide a load behind.
+// least a factor 5e-13 but for one, so 16 stay above 1e-250) and the interval shrinks 17-fold, eleven times, behind a first
+// round in which the whole work-group counts below 256 points for all of its pairs: 2 / (257 17^11) = 2e-16.  T comes through
+// the scalar cache, 8 rows ahead: one wave per SIMD has nobody else to hide a load behind.  (The recurrence from both ends at
+// once, joined in the middle, took as long: a wave alone on its SIMD issues an instruction about every seven cycles, whatever
+// it waits for.)
 // Vector by twisted factorisation, again without a division in the chain: a lane of wave 0 runs (T - lambda) y = 0 from the
 // top, one of wave 1 from the bottom, both rescaled every 8 steps (exponents kept per block of 8); the vector is the one above
 // the row with the smallest twist gamma_i = (d_i - lambda) + e_{i-1} y_{i-1} / y_i + e_i x_{i+1} / x_i and the other below
-// it.  The second round runs at the Rayleigh-corrected eigenvalue, which leaves a residual of a few 1e-16.
-// 39000 cycles for the eigenvalues, about 8000 + 5000 for each round of chains and twist.
+// it.  A second round, at the Rayleigh-corrected eigenvalue, leaves a residual of a few 1e-16; only close neighbours need it.
+// 32 matrices 30 us, 34 with twelve rounds of 17, both rounds of vectors always and chains that make their coefficients on the way.
 constexpr int TV_PAIRS = 16, TV_SECT = 12, TV_LD = D + 2;
+constexpr double TV_GAP = 5e-12;
 
 // -T of reflections 16 b .. 16 b + 15 by one wave: their inner products G on the matrix cores (the order of the contraction
 // is that of the record, from its first written pair on; a lane's row of V serves as both operands), then
@@ -449,12 +460,14 @@ __global__ __launch_bounds__(256, 2) void eig_tri_vectors(int U, const double* _
 {
     // coefficients of the two recurrences, in the order in which a lane walks them: (d, 1 / e ahead), e behind / e ahead
     __shared__ f64x2 sco[2][D];
-    __shared__ double sw[2][D];
+    __shared__ __attribute__((aligned(16))) double sw[2][D];
     __shared__ double se[D];
-    __shared__ double yx[TV_PAIRS][2][TV_LD];        // y (from the top) and x (from the bottom)
+    // y (from the top) and x (from the bottom); before a chain comes by, its coefficients (lambda - d) / e ahead
+    __shared__ __attribute__((aligned(16))) double yx[TV_PAIRS][2][TV_LD];
     __shared__ int ys[TV_PAIRS][2][D / 8];           // their exponents, per block of 8 rows
     __shared__ double slam[TV_PAIRS];
     __shared__ double sg16[256];
+    __shared__ __attribute__((aligned(16))) unsigned char first_counts[256];
     int u, slice;
     eig_slice(u, slice);
     if (u >= U || status[2 * u] != 0) return;
@@ -476,10 +489,8 @@ __global__ __launch_bounds__(256, 2) void eig_tri_vectors(int U, const double* _
         se[i] = e;
     }
 
-    double lo = -1.001, hi = 1.001;                   // the Frobenius norm is below 1
-#pragma unroll 1
-    for (int it = 0; it < TV_SECT; ++it) {
-        const double wid = (hi - lo) * (1.0 / 17.0), x = fma(wid, (double)(s + 1), lo);
+    // eigenvalues below x
+    auto count = [&](double x) {
         double p0 = 0.0, p = 1.0;
         int changes = 0;
         uint32_t last = 0, sg = 0;
@@ -517,61 +528,105 @@ __global__ __launch_bounds__(256, 2) void eig_tri_vectors(int U, const double* _
             last = sg & 1u;
             sg &= 0xffffu;
         }
-        const uint64_t le = __ballot(changes <= below);          // points with at most `below` eigenvalues under them
-        const int m = __popc((uint32_t)(le >> (lane & 48)) & 0xffffu);
+        return changes;
+    };
+    double lo = -1.001, hi = 1.001;                   // the Frobenius norm is below 1
+    double under = 2.0, over = -2.0;                  // of the points between this eigenvalue and its neighbours, the outermost
+    int points = 256;                                 // of the first round: all of the work-group's, for all of its pairs
+#pragma unroll 1
+    for (int it = 0; it < TV_SECT; ++it) {
+        const double wid = (hi - lo) * (1.0 / (points + 1)), x = fma(wid, (double)((it == 0 ? tid : s) + 1), lo);
+        const int changes = count(x);
+        int m;                                        // points with at most `below` eigenvalues under them
+        if (it == 0) {
+            first_counts[tid] = (unsigned char)changes;
+            __syncthreads();
+            const uint4 c = *(const uint4*)(first_counts + 16 * s);
+            const uint32_t w[4] = {c.x, c.y, c.z, c.w};
+            m = 0;
+#pragma unroll
+            for (int k = 0; k < 16; ++k) m += (int)((w[k >> 2] >> (8 * (k & 3))) & 0xffu) <= below;
+            m = row16_sum_i32(m);
+        } else {
+            under = changes == below ? fmin(under, x) : under;
+            over = changes == below + 1 ? fmax(over, x) : over;
+            m = __popc((uint32_t)(__ballot(changes <= below) >> (lane & 48)) & 0xffffu);
+        }
         const double nlo = fma(wid, (double)m, lo);
-        hi = m == 16 ? hi : fma(wid, (double)(m + 1), lo);
+        hi = m == points ? hi : fma(wid, (double)(m + 1), lo);
         lo = nlo;
+        points = 16;
     }
     double lam = 0.5 * (lo + hi);
+#pragma unroll
+    for (int o = 0; o < 4; ++o) {                                // the lane permutations of row16_sum_f64
+        under = fmin(under, o == 0 ? dpp_f64<0xB1>(under) : o == 1 ? dpp_f64<0x4E>(under) : o == 2 ? dpp_f64<0x141>(under) : dpp_f64<0x140>(under));
+        over = fmax(over, o == 0 ? dpp_f64<0xB1>(over) : o == 1 ? dpp_f64<0x4E>(over) : o == 2 ? dpp_f64<0x141>(over) : dpp_f64<0x140>(over));
+    }
     if (s == 0) slam[pr] = lam;
     __syncthreads();
+    // One round leaves a vector with a residual of some 5e-16, and that over the gap to the next eigenvalue in its direction:
+    // 1e-4 at TV_GAP, of which the step in eig_orth_back leaves 1e-8, a sixth of the fp32 rounding of R.  A nearer neighbour (of any pair of this work-group; the
+    // neighbours of its first and last pair are only known to lie beyond a point) asks for the second round.
+    const double above = (pr > 0 ? slam[max(pr - 1, 0)] : over) - lam, under_by = lam - (pr < TV_PAIRS - 1 ? slam[min(pr + 1, TV_PAIRS - 1)] : under);
+    const int rounds = __syncthreads_or(!(above > TV_GAP) || !(under_by > TV_GAP)) ? 2 : 1;
 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     double (*yv)[TV_LD] = yx[pr];
     double zz[8];
     double norm2 = 1.0, gam = 0.0;
 #pragma unroll 1
-    for (int round = 0; round < 2; ++round) {
-        // Wave 0 runs the 16 chains from the top, wave 1 those from the bottom: with each wave running its own pairs' every
-        // coefficient was read four times from LDS (11400 cycles a round).
+    for (int round = 0; round < rounds; ++round) {
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+            const int i = s + 16 * m;
+            const f64x2 c = sco[0][i];
+            const double t = lam - c.x;
+            yv[0][i] = t * c.y;
+            yv[1][i] = t * sco[1][D - 1 - i].y;
+        }
+        __syncthreads();
+        // Wave 0 runs the 16 chains from the top, wave 1 those from the bottom, each a wave alone on its SIMD, which issues an
+        // instruction about every seven cycles: the coefficients come ready (by all waves, above) and two rows to an access,
+        // and the vector takes their place.  With the coefficients made on the way a step took 62 cycles.
         auto chain = [&](auto direction) {
-            constexpr int dir = decltype(direction)::value;
-            const double lam = slam[lane];
+            constexpr int dir = decltype(direction)::value, stp = dir ? -2 : 2;
             double y0 = 0.0, y = 1.0;
             int exps = 0;
-            double* dst = yx[lane][dir] + (dir ? D - 1 : 0);
-            constexpr int stp = dir ? -1 : 1;
-            f64x2 ca[8], cb[8];
-            double wa[8], wb[8];
-            auto fetch = [&](f64x2 (&c)[8], double (&w)[8], int b) {
+            double* at = yx[lane][dir] + (dir ? D - 2 : 0);
+            f64x2 ca[2], cb[2], wa[2], wb[2];
+            auto fetch = [&](f64x2 (&c)[2], f64x2 (&w)[2], int row) {     // rows row .. row + 3 of the walk
 #pragma unroll
-                for (int i = 0; i < 8; ++i) { c[i] = sco[dir][8 * b + i]; w[i] = sw[dir][8 * b + i]; }
+                for (int i = 0; i < 2; ++i) {
+                    c[i] = *(const f64x2*)(yx[lane][dir] + (dir ? D - 2 - row - 2 * i : row + 2 * i));
+                    w[i] = *(const f64x2*)(sw[dir] + row + 2 * i);
+                }
                 __builtin_amdgcn_sched_barrier(0);
             };
-            auto steps = [&](const f64x2 (&c)[8], const double (&w)[8], int b) {
-                ys[lane][dir][dir ? D / 8 - 1 - b : b] = exps;
+            auto steps = [&](const f64x2 (&c)[2], const f64x2 (&w)[2]) {
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    dst[stp * i] = y;
-                    const double yn = fma((lam - c[i].x) * c[i].y, y, -(w[i] * y0));
-                    y0 = y;
-                    y = yn;
+                for (int i = 0; i < 2; ++i) {
+                    const double y1 = fma(dir ? c[i].y : c[i].x, y, -(w[i].x * y0));
+                    const double y2 = fma(dir ? c[i].x : c[i].y, y1, -(w[i].y * y));
+                    *(f64x2*)at = dir ? (f64x2){y1, y} : (f64x2){y, y1};
+                    at += stp;
+                    y0 = y1;
+                    y = y2;
                 }
-                dst += 8 * stp;
-                const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(y), fabs(y0)));
-                y = ldexp(y, -ex);
-                y0 = ldexp(y0, -ex);
-                exps += ex;
                 __builtin_amdgcn_sched_barrier(0);
             };
             fetch(ca, wa, 0);
 #pragma unroll 1
-            for (int b = 0; b < D / 8; b += 2) {
-                fetch(cb, wb, b + 1);
-                steps(ca, wa, b);
-                fetch(ca, wa, min(b + 2, D / 8 - 1));
-                steps(cb, wb, b + 1);
+            for (int b = 0; b < D / 8; ++b) {
+                ys[lane][dir][dir ? D / 8 - 1 - b : b] = exps;
+                fetch(cb, wb, 8 * b + 4);
+                steps(ca, wa);
+                fetch(ca, wa, min(8 * b + 8, D - 4));
+                steps(cb, wb);
+                const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(y), fabs(y0)));
+                y = ldexp(y, -ex);
+                y0 = ldexp(y0, -ex);
+                exps += ex;
             }
         };
         if (wave == 0 && lane < TV_PAIRS) chain(std::integral_constant<int, 0>());
@@ -618,9 +673,8 @@ __global__ __launch_bounds__(256, 2) void eig_tri_vectors(int U, const double* _
         }
         norm2 = row16_sum_f64(n2);
         gam = bg;
-        if (round == 0) {
+        if (round + 1 < rounds) {
             lam += gam / norm2;
-            if (s == 0) slam[pr] = lam;
             __syncthreads();
         }
     }

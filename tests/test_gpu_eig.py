@@ -140,6 +140,23 @@ def test_coinciding_eigenvalues(ctx, gap):
     assert np.array_equal(to_host(p.Rr)[0, 0], R[:, keep])
 
 
+# Neighbours on both sides of the distance below which a vector takes a second round, in a chain beside a dense block.  The chain's
+# entries are squares of fp32 numbers, 2e-6 and up: rounded by 2e-13 of the norm, a twentieth of the smallest gap.
+@pytest.mark.parametrize("gap", [3e-9, 1e-10, 2e-11, 7e-12, 4e-12])
+def test_close_eigenvalues(ctx, gap):
+    block = np.random.default_rng(6).standard_normal((6, D))
+    block[:, 4:] = 0.0
+    block *= np.sqrt(0.7 / np.linalg.norm(block.T @ block))
+    i = np.arange(4, D)
+    single = np.zeros((D - 4, D))
+    single[i - 4, i] = np.sqrt(2e-6 - 5e-13 * (37 * i % D) + gap * (i - 4))
+    R, lam, C, sweeps, p = solve(ctx, np.vstack([block, single]))
+    eps = 2.0 ** -24
+    assert sweeps == 1
+    assert np.abs(R.T @ R - np.eye(D)).max() <= 2 * eps * np.sqrt(D)
+    assert np.linalg.norm(R.T @ C @ R - np.diag(lam)) <= 4 * eps * np.sqrt(D) * np.linalg.norm(C)
+
+
 def test_non_finite_keys(ctx):
     """A head with an infinity or a NaN in its Keys: no eigenproblem to solve; the call ends, the other heads are as ever."""
     K = np.stack([recipe(100), recipe(100), recipe(100)]).astype(np.float32)[None]
