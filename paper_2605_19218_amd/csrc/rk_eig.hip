@@ -10,7 +10,7 @@
 // The fp64 vector rate of this part equals its unpacked fp32 rate, so double costs registers and LDS width only; it
 // buys vectors that need no iteration over the whole matrix.  A sweep of Jacobi is 127 dependent rounds on one compute
 // unit and 8-10 sweeps are needed; the reduction is 126 dependent steps in all, and everything behind it is independent
-// per eigenpair.  Measured (32 / 512 matrices): 106 + 34 + 18 + 10 us / 225 + 327 + 266 us against 756 us / 2.3 ms of the
+// per eigenpair.  Measured (32 / 512 matrices): 86 + 31 + 20 + 5 us / 187 + 304 + 287 + 5 us against 756 us / 2.3 ms of the
 // parallel Jacobi that solved every matrix before, with eigenvalues to their fp32 rounding (1e-7 of the spectrum
 // against 8e-7).
 #include <type_traits>
@@ -56,14 +56,18 @@ __device__ __forceinline__ double rcp_f64(double x)
 // read from LDS by rows exactly as by columns.  The fifth wave makes the reflections.  With x the part of row k behind the
 // diagonal, the reflection's vector is v = x + s e with s = +-|x| and e its first place, so that A v = A x + s a, a = row
 // k + 1.  A step has two barriers:
-//   x is in LDS; every group forms A x on its rows -> LDS, and the group that owns row k + 1 hands it over as it stands;
-//   meanwhile the fifth wave finds s and tau and keeps the record                                    -> barrier
-//   p = A x + s a, A -= tau (v p^T + p v^T - tau (v^T p) v v^T), the first two products while v^T p is being summed; meanwhile
-//   the fifth wave applies the same to row k + 1 alone and publishes the next x                      -> barrier
+//   x is in LDS; every group forms A x on its rows -> LDS; meanwhile the fifth wave finds s and tau and keeps the
+//   record                                                                                           -> barrier
+//   p = A x + s a, A -= tau (v p^T + p v^T - tau (v^T p) v v^T), the first two products while v^T p is being summed, and the
+//   group that owns row k + 2 hands it over; meanwhile the fifth wave applies the same to row k + 1 alone and publishes the
+//   next x                                                                                           -> barrier
 // What bounds a step is its dependent chain (two LDS round trips, two lane-group sums one behind the other, two barriers) and
-// the instructions of one wave: a wave alone on its SIMD issues one about every seven cycles.  32 matrices: 93 us; 106 with 512
-// threads of 4 x 8 elements (which read every vector twice as often) whose waves made the reflections between their own
-// updates.  Tried: 1024 threads of 2 x 8 elements (119 us: twice the sums and LDS reads per element); the reflection found
+// the instructions of one wave: a wave alone on its SIMD issues one about every seven cycles, and a taken branch costs some 36.
+// So the steps come two to a loop iteration, and the last step of a block, whose row lies in the next place of a lane, is one of
+// its own: no choice between places is left in the others.  32 matrices: 86 us, 512: 187; 93 with those choices, one step an iteration and
+// the row handed over in front of A x; 106 with 512 threads of 4 x 8 elements (which read every vector twice as often) whose
+// waves made the reflections between their own updates.  Tried: four steps an iteration (the same); 512 threads and the ninth
+// wave (103 us: twice the LDS reads); 1024 threads of 2 x 8 elements (119 us: twice the sums and LDS reads per element); the reflection found
 // between the barriers of the update, behind the sum v^T p (94 us); every lane group finding it for itself, with one barrier a step
 // (114 us: the instructions of all that redundancy cost more than the barrier).
 // status[2 u]: 1 for a matrix left to Jacobi (already diagonal to its threshold, zero, or not finite), else 0; status
@@ -74,7 +78,7 @@ constexpr int TRI_HOLD = 256, TRI_THREADS = TRI_HOLD + 64;
 struct TriShared {
     double xs[2][D];                    // spread: x of this step and of the next, zeros in front of its first place
     double ps[D];                       // spread: A x
-    double row[D];                      // spread: row k + 1 before this step
+    double row[2][D];                   // spread: row k + 1 before this step, and the next one
     f64x2 ts[D];                        // (tau, s)
     double d[D], e[D];
     double red[2][TRI_HOLD / 64];
@@ -92,90 +96,98 @@ __device__ __forceinline__ void tri_read(double (&x)[8], const double* s, int g)
     }
 }
 
-// x + s e: place `lead`, the first of x, is in place KB or KB + 1 of a lane
-template <int KB>
+// The steps of a block all have row k + 1, and the first place of x, in place AT = KB of a lane, but for the last one: AT = KB + 1.
+// x + s e
+template <int AT>
 __device__ __forceinline__ void tri_add_first(double (&x)[8], double s, int lead, int g)
 {
-#pragma unroll
-    for (int m = KB; m < 8 && m < KB + 2; ++m) x[m] += g + 16 * m == lead ? s : 0.0;
+    x[AT] += g + 16 * AT == lead ? s : 0.0;
 }
 
 // The x of step kn out of row kn, into LDS and x; the diagonal element beside it.
-template <int KB>
+template <int KB, int AT>
 __device__ __forceinline__ void tri_publish(const double (&row)[8], int kn, double (&x)[8], TriShared& S, int lane)
 {
     const int cg = lane & 15;
 #pragma unroll
-    for (int m = 0; m < 8; ++m) x[m] = m < KB ? 0.0 : m > KB + 1 || cg + 16 * m > kn ? row[m] : 0.0;
+    for (int m = 0; m < 8; ++m) x[m] = m < AT ? 0.0 : m > AT || cg + 16 * m > kn ? row[m] : 0.0;
     if (lane < 16) {
         double* xb = S.xs[kn & 1];
 #pragma unroll
         for (int q = KB >> 1; q < 4; ++q) *(f64x2*)(xb + (q * 16 + cg) * 2) = (f64x2){x[2 * q], x[2 * q + 1]};
-        if (cg == (kn & 15)) S.d[kn] = KB < 7 && (kn >> 4) > KB ? row[KB < 7 ? KB + 1 : KB] : row[KB];
+        if (cg == (kn & 15)) S.d[kn] = row[AT];
     }
 }
 
-// Steps 16 KB .. 16 KB + 15 of the fifth wave, whose lane groups all hold the same: x of the step in v.
+// Step k of the fifth wave, whose lane groups all hold the same: x of the step in v.
+template <int KB, int AT>
+__device__ __forceinline__ void tri_reflect_step(int k, double (&v)[8], TriShared& S, double* __restrict__ Vg, int lane)
+{
+    const int cg = lane & 15, kn = k + 1;                        // the first place of x, and the next row
+    const double first = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v[AT]), kn & 15),
+                                          __builtin_amdgcn_readlane(__double2loint(v[AT]), kn & 15));
+    double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+    for (int m = AT; m < 8; ++m) {
+        const double y = m == AT && cg + 16 * m == kn ? 0.0 : v[m];
+        if (m & 1) s1 = fma(y, y, s1);
+        else s0 = fma(y, y, s0);
+    }
+    const double sig = row16_sum_f64(s0 + s1);
+    const double h = fma(first, first, sig);
+    // |x| = h / sqrt(h): hardware estimate and one third-order step
+    const double y = __builtin_amdgcn_rsq(h), t = h * y, r = fma(-t, y, 1.0);
+    const double nrm = fma(t * r, fma(r, 0.375, 0.5), t);
+    const bool act = sig > 1e-36;                                // else nothing to clear at double precision: H = I
+    const double s = !act ? 0.0 : first >= 0.0 ? nrm : -nrm;                          // (|x| is NaN for x = 0)
+    const double tau = act ? rcp_f64(fma(fabs(first), nrm, h)) : 0.0;                 // H = I - tau v v^T
+    tri_add_first<AT>(v, s, kn, cg);
+    if (lane == 0) {
+        S.ts[k] = (f64x2){tau, s};
+        S.e[k] = act ? -s : first;
+    }
+    if (lane < 16) {
+#pragma unroll
+        for (int q = KB >> 1; q < 4; ++q)
+            *(f64x2*)(Vg + (size_t)k * D + (q * 16 + cg) * 2) = (f64x2){2 * q < KB ? 0.0 : v[2 * q], v[2 * q + 1]};
+    }
+    lds_barrier();
+    // (the last step's row 126 and its diagonal element, which the matrix has as well, go unused)
+    double p[8], row[8];
+    tri_read<KB>(p, S.ps, cg);
+    tri_read<KB>(row, S.row[kn & 1], cg);
+    const double pk = fma(s, S.row[kn & 1][eig_spread(kn)], S.ps[eig_spread(kn)]);
+#pragma unroll
+    for (int m = AT; m < 8; ++m) p[m] = fma(s, row[m], p[m]);
+    double d0 = 0.0, d1 = 0.0;
+#pragma unroll
+    for (int m = AT; m < 8; ++m) {
+        if (m & 1) d1 = fma(v[m], p[m], d1);
+        else d0 = fma(v[m], p[m], d0);
+    }
+    const double tl = -tau * (first + s), tp = -tau * pk;
+#pragma unroll
+    for (int m = AT; m < 8; ++m) row[m] = fma(tl, p[m], fma(tp, v[m], row[m]));
+    const double c = -tau * tl * row16_sum_f64(d0 + d1);
+#pragma unroll
+    for (int m = AT; m < 8; ++m) row[m] = fma(c, v[m], row[m]);
+    tri_publish<KB, AT>(row, kn, v, S, lane);
+    lds_barrier();
+}
+// Steps 16 KB .. 16 KB + 15
 template <int KB>
 __device__ __forceinline__ void tri_reflect(double (&v)[8], TriShared& S, double* __restrict__ Vg, int lane)
 {
-    const int cg = lane & 15, k1 = min(16 * KB + 16, D - 2);
 #pragma unroll 1
-    for (int k = 16 * KB; k < k1; ++k) {
-        const int kn = k + 1;                                    // the first place of x, and the next row
-        const double xl = KB < 7 && (kn >> 4) > KB ? v[KB < 7 ? KB + 1 : KB] : v[KB];
-        const double first = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(xl), kn & 15),
-                                              __builtin_amdgcn_readlane(__double2loint(xl), kn & 15));
-        double s0 = 0.0, s1 = 0.0;
-#pragma unroll
-        for (int m = KB; m < 8; ++m) {
-            const double y = m <= KB + 1 && cg + 16 * m == kn ? 0.0 : v[m];
-            if (m & 1) s1 = fma(y, y, s1);
-            else s0 = fma(y, y, s0);
-        }
-        const double sig = row16_sum_f64(s0 + s1);
-        const double h = fma(first, first, sig);
-        // |x| = h / sqrt(h): hardware estimate and one third-order step
-        const double y = __builtin_amdgcn_rsq(h), t = h * y, r = fma(-t, y, 1.0);
-        const double nrm = fma(t * r, fma(r, 0.375, 0.5), t);
-        const bool act = sig > 1e-36;                            // else nothing to clear at double precision: H = I
-        const double s = !act ? 0.0 : first >= 0.0 ? nrm : -nrm;                      // (|x| is NaN for x = 0)
-        const double tau = act ? rcp_f64(fma(fabs(first), nrm, h)) : 0.0;             // H = I - tau v v^T
-        tri_add_first<KB>(v, s, kn, cg);
-        if (lane == 0) {
-            S.ts[k] = (f64x2){tau, s};
-            S.e[k] = act ? -s : first;
-        }
-        if (lane < 16) {
-#pragma unroll
-            for (int q = KB >> 1; q < 4; ++q)
-                *(f64x2*)(Vg + (size_t)k * D + (q * 16 + cg) * 2) = (f64x2){2 * q < KB ? 0.0 : v[2 * q], v[2 * q + 1]};
-        }
-        lds_barrier();
-        if (kn < D - 2) {
-            double p[8], row[8];
-            tri_read<KB>(p, S.ps, cg);
-            tri_read<KB>(row, S.row, cg);
-            const double pk = fma(s, S.row[eig_spread(kn)], S.ps[eig_spread(kn)]);
-#pragma unroll
-            for (int m = KB; m < 8; ++m) p[m] = fma(s, row[m], p[m]);
-            double d0 = 0.0, d1 = 0.0;
-#pragma unroll
-            for (int m = KB; m < 8; ++m) {
-                if (m & 1) d1 = fma(v[m], p[m], d1);
-                else d0 = fma(v[m], p[m], d0);
-            }
-            const double tl = -tau * (first + s), tp = -tau * pk;
-#pragma unroll
-            for (int m = KB; m < 8; ++m) row[m] = fma(tl, p[m], fma(tp, v[m], row[m]));
-            const double c = -tau * tl * row16_sum_f64(d0 + d1);
-#pragma unroll
-            for (int m = KB; m < 8; ++m) row[m] = fma(c, v[m], row[m]);
-            tri_publish<KB>(row, kn, v, S, lane);
-        }
-        lds_barrier();
+    for (int k = 16 * KB; k < 16 * KB + 14; k += 2) {            // (a taken branch costs as much as eight instructions)
+        tri_reflect_step<KB, KB>(k, v, S, Vg, lane);
+        tri_reflect_step<KB, KB>(k + 1, v, S, Vg, lane);
     }
-    if constexpr (KB < 7) tri_reflect<KB + 1>(v, S, Vg, lane);
+    if constexpr (KB < 7) {
+        tri_reflect_step<KB, KB>(16 * KB + 14, v, S, Vg, lane);
+        tri_reflect_step<KB, KB + 1>(16 * KB + 15, v, S, Vg, lane);
+        tri_reflect<KB + 1>(v, S, Vg, lane);
+    }
 }
 
 // Sums of p[KB ..] over the 16 lanes of a group.  With several rows the first steps halve the rows that a lane carries instead
@@ -213,76 +225,88 @@ __device__ __forceinline__ int tri_fold_row(int cg)
     return N > 1 ? b3 : 0;
 }
 
-// Steps 16 KB .. 16 KB + 15 of the waves that hold the matrix: row and column places below KB are finished.
+// Step k of the waves that hold the matrix: row and column places below KB are finished.
+template <int KB, int AT>
+__device__ __forceinline__ void tri_step(int k, double (&a)[8][8], TriShared& S, int rg, int cg, int wave, int mine)
+{
+    constexpr int N = 8 - KB;
+    const int kn = k + 1;
+    const bool live = KB < 7 || 112 + 4 * wave + 3 > k;                   // wave-uniform: some row of this wave is still active
+    double v[8], vi[8];
+    if (live) {
+        tri_read<KB>(v, S.xs[k & 1], cg);
+        tri_read<KB>(vi, S.xs[k & 1], rg);
+        double p[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) p[j] = 0.0;
+#pragma unroll
+        for (int m = KB; m < 8; ++m)
+#pragma unroll
+            for (int j = 0; j < N; ++j) p[j] = fma(a[KB + j][m], v[m], p[j]);
+        S.ps[mine] = tri_fold<N, 0>(p, cg);                      // (several lanes store the same number)
+    }
+    lds_barrier();
+    if (live) {
+        double w[8], wi[8], r[8], ri[8];
+        const f64x2 ts = S.ts[k];
+        tri_read<KB>(w, S.ps, cg);
+        tri_read<KB>(r, S.row[kn & 1], cg);
+        tri_read<KB>(wi, S.ps, rg);
+        tri_read<KB>(ri, S.row[kn & 1], rg);
+        const double tau = ts.x;
+        tri_add_first<AT>(v, ts.y, kn, cg);
+        tri_add_first<AT>(vi, ts.y, kn, rg);
+        double d0 = 0.0, d1 = 0.0;
+#pragma unroll
+        for (int m = KB; m < 8; ++m) {
+            w[m] = fma(ts.y, r[m], w[m]);
+            if (m & 1) d1 = fma(v[m], w[m], d1);
+            else d0 = fma(v[m], w[m], d0);
+        }
+#pragma unroll
+        for (int i = KB; i < 8; ++i) wi[i] = fma(ts.y, ri[i], wi[i]);
+        // rows that are finished hold leftovers of v: whatever they become is never read
+#pragma unroll
+        for (int i = KB; i < 8; ++i) {
+            const double tv = -tau * vi[i];
+#pragma unroll
+            for (int m = KB; m < 8; ++m) a[i][m] = fma(tv, w[m], a[i][m]);
+        }
+        const double nd = -tau * row16_sum_f64(d0 + d1);
+#pragma unroll
+        for (int i = KB; i < 8; ++i) {
+            const double tw = -tau * fma(nd, vi[i], wi[i]);
+#pragma unroll
+            for (int m = KB; m < 8; ++m) a[i][m] = fma(tw, v[m], a[i][m]);
+        }
+        // row k + 2 for the next step, here where the fifth wave is the one to wait for
+        if (rg == ((kn + 1) & 15)) {
+            const bool far = KB < 7 && ((kn + 1) >> 4) > KB;
+            constexpr int FAR = KB < 7 ? KB + 1 : KB;
+            double* hand = S.row[(kn + 1) & 1];
+#pragma unroll
+            for (int q = KB >> 1; q < 4; ++q)
+                *(f64x2*)(hand + (q * 16 + cg) * 2) = far ? (f64x2){a[FAR][2 * q], a[FAR][2 * q + 1]}
+                                                          : (f64x2){a[KB][2 * q], a[KB][2 * q + 1]};
+        }
+    }
+    lds_barrier();
+}
+// Steps 16 KB .. 16 KB + 15
 template <int KB>
 __device__ __forceinline__ void tri_block(double (&a)[8][8], TriShared& S, int rg, int cg, int wave)
 {
-    constexpr int N = 8 - KB;
-    const int k1 = min(16 * KB + 16, D - 2);
-    const int mine = eig_spread(rg + 16 * (KB + tri_fold_row<N>(cg)));
+    const int mine = eig_spread(rg + 16 * (KB + tri_fold_row<8 - KB>(cg)));
 #pragma unroll 1
-    for (int k = 16 * KB; k < k1; ++k) {
-        const int kn = k + 1;
-        const bool live = 112 + 4 * wave + 3 > k;               // wave-uniform: some row of this wave is still active
-        double v[8], vi[8];
-        if (live) {
-            tri_read<KB>(v, S.xs[k & 1], cg);
-            tri_read<KB>(vi, S.xs[k & 1], rg);
-            if (rg == (kn & 15)) {
-                const bool far = KB < 7 && (kn >> 4) > KB;
-                constexpr int FAR = KB < 7 ? KB + 1 : KB;
-#pragma unroll
-                for (int q = KB >> 1; q < 4; ++q)
-                    *(f64x2*)(S.row + (q * 16 + cg) * 2) = far ? (f64x2){a[FAR][2 * q], a[FAR][2 * q + 1]}
-                                                               : (f64x2){a[KB][2 * q], a[KB][2 * q + 1]};
-            }
-            double p[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) p[j] = 0.0;
-#pragma unroll
-            for (int m = KB; m < 8; ++m)
-#pragma unroll
-                for (int j = 0; j < N; ++j) p[j] = fma(a[KB + j][m], v[m], p[j]);
-            S.ps[mine] = tri_fold<N, 0>(p, cg);                  // (several lanes store the same number)
-        }
-        lds_barrier();
-        if (live) {
-            double w[8], wi[8], r[8], ri[8];
-            const f64x2 ts = S.ts[k];
-            tri_read<KB>(w, S.ps, cg);
-            tri_read<KB>(r, S.row, cg);
-            tri_read<KB>(wi, S.ps, rg);
-            tri_read<KB>(ri, S.row, rg);
-            const double tau = ts.x;
-            tri_add_first<KB>(v, ts.y, kn, cg);
-            tri_add_first<KB>(vi, ts.y, kn, rg);
-            double d0 = 0.0, d1 = 0.0;
-#pragma unroll
-            for (int m = KB; m < 8; ++m) {
-                w[m] = fma(ts.y, r[m], w[m]);
-                if (m & 1) d1 = fma(v[m], w[m], d1);
-                else d0 = fma(v[m], w[m], d0);
-            }
-#pragma unroll
-            for (int i = KB; i < 8; ++i) wi[i] = fma(ts.y, ri[i], wi[i]);
-            // rows that are finished hold leftovers of v: whatever they become is never read
-#pragma unroll
-            for (int i = KB; i < 8; ++i) {
-                const double tv = -tau * vi[i];
-#pragma unroll
-                for (int m = KB; m < 8; ++m) a[i][m] = fma(tv, w[m], a[i][m]);
-            }
-            const double nd = -tau * row16_sum_f64(d0 + d1);
-#pragma unroll
-            for (int i = KB; i < 8; ++i) {
-                const double tw = -tau * fma(nd, vi[i], wi[i]);
-#pragma unroll
-                for (int m = KB; m < 8; ++m) a[i][m] = fma(tw, v[m], a[i][m]);
-            }
-        }
-        lds_barrier();
+    for (int k = 16 * KB; k < 16 * KB + 14; k += 2) {
+        tri_step<KB, KB>(k, a, S, rg, cg, wave, mine);
+        tri_step<KB, KB>(k + 1, a, S, rg, cg, wave, mine);
     }
-    if constexpr (KB < 7) tri_block<KB + 1>(a, S, rg, cg, wave);
+    if constexpr (KB < 7) {
+        tri_step<KB, KB>(16 * KB + 14, a, S, rg, cg, wave, mine);
+        tri_step<KB, KB + 1>(16 * KB + 15, a, S, rg, cg, wave, mine);
+        tri_block<KB + 1>(a, S, rg, cg, wave);
+    }
 }
 
 __global__ __launch_bounds__(TRI_THREADS) void eig_tridiag(const float* __restrict__ cov, const float* __restrict__ sigma,
@@ -338,9 +362,9 @@ __global__ __launch_bounds__(TRI_THREADS) void eig_tridiag(const float* __restri
         for (int i = 0; i < 8; ++i)
 #pragma unroll
             for (int m = 0; m < 8; ++m) a[i][m] = ldexp(a[i][m], -ex);
-        if (rg == 0)
+        if (rg < 2)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) *(f64x2*)(S.row + (q * 16 + cg) * 2) = (f64x2){a[0][2 * q], a[0][2 * q + 1]};
+            for (int q = 0; q < 4; ++q) *(f64x2*)(S.row[rg] + (q * 16 + cg) * 2) = (f64x2){a[0][2 * q], a[0][2 * q + 1]};
         __syncthreads();
         __syncthreads();
         tri_block<0>(a, S, rg, cg, wave);
@@ -351,8 +375,8 @@ __global__ __launch_bounds__(TRI_THREADS) void eig_tridiag(const float* __restri
         __builtin_amdgcn_s_setprio(3);      // its chain is the longer one, and it shares its SIMD with a wave of the others
         __syncthreads();
         double row[8], v[8];
-        tri_read<0>(row, S.row, cg);
-        tri_publish<0>(row, 0, v, S, lane);
+        tri_read<0>(row, S.row[0], cg);
+        tri_publish<0, 0>(row, 0, v, S, lane);
         __syncthreads();
         tri_reflect<0>(v, S, W + EIGW_V, lane);
         __builtin_amdgcn_s_setprio(0);
@@ -702,7 +726,8 @@ __global__ __launch_bounds__(256, 2) void eig_tri_vectors(int U, const double* _
 // Bound, of 36000 cycles: loading Z 6500, the products 6000 + 6600 (matrix pipe 4100 each), storing V 2800, reflections 13700
 // (eight rounds of four dependent matrix steps, one exchange between the waves, eight more).  Four reflections at a time
 // on the vector unit: 20000 + 2500 for their inner products (LDS-bound, every lane group reads all of V), 23 us; one at a time
-// with loads where they are used: 56000 cycles in all, 27.7 us.  Now 18 us for 32 matrices, 266 for 512 (547 at first).
+// with loads where they are used: 56000 cycles in all, 27.7 us.  18 us for 32 matrices, 266 for 512 (547 at first);
+// with the ranks, R_r and the products with mu 20 and 287, for 5 less in eig_finish.
 constexpr double EIG_ORTH_MAX = 3e-4;
 static_assert(0.75 * D * EIG_ORTH_MAX * EIG_ORTH_MAX <= 1e-5, "|R^T R - I| <= 1e-5, every column of E at its limit");
 constexpr int OB_LD = D + 2, OB_MLD = 17;
