@@ -52,14 +52,14 @@ __global__ __launch_bounds__(256) void compress_generic(RowsDev rows, int Hkv, i
 // operand are permuted so that after output blocks 2i and 2i+1 lane (g, n) holds
 // the 8 output channels 32 i + 8 g ..+7 of token n -- one 16-byte piece of the
 // packed layout, and consecutive lanes write consecutive pieces.
-template <int R>
+template <int R, int NP>
 struct CompressCfg {
     static constexpr int JB = R / 16;                 // 16-wide output-channel blocks
     static constexpr int NF = R / 32;                 // full 32-channel groups
     static constexpr bool TAIL = (R % 32) != 0;       // one trailing 16-channel block
     static constexpr int TT = 2;                      // 16-token tiles per wave and pass (two passes in flight)
     static constexpr int TOK_PER_PASS = 4 * TT * 16;  // tokens one pass of the 4 waves covers
-    static constexpr int PASSES = 4;                  // passes per work-group (amortise the R_r fragment build)
+    static constexpr int PASSES = NP;                 // passes per work-group (amortise the R_r fragment build)
     static constexpr int TOK_PER_BLOCK = PASSES * TOK_PER_PASS;
     static constexpr size_t LDS_BYTES = (size_t)JB * 4 * 2 * 64 * 16;   // A fragments, hi+lo
     // output channel held by A row a of block jb
@@ -72,12 +72,12 @@ __device__ __forceinline__ uint32_t pack2_bf16(float a, float b) {
     return (uint32_t)f32_to_bf16(a) | ((uint32_t)f32_to_bf16(b) << 16);
 }
 
-template <int R, bool GATHER>
+template <int R, bool GATHER, int NP>
 __global__ __launch_bounds__(256, 2) void compress_mfma(RowsDev rows, int Hkv, int cap, int r,
                                                      const float* __restrict__ Rr, bf16_t* __restrict__ Kp,
                                                      int32_t* __restrict__ seq_len_out)
 {
-    typedef CompressCfg<R> Cfg;
+    typedef CompressCfg<R, NP> Cfg;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     bf16x8* frag = (bf16x8*)smem_raw;       // [JB][4][2][64]
 
@@ -467,24 +467,35 @@ __global__ __launch_bounds__(256) void unpack_cache(int cap, int r, const T* __r
 }
 
 // ---------------------------------------------------------------------------
+template <int R, bool GATHER, int NP>
+static hipError_t launch_compress_mfma_rp(const RowsDev& rows, int B, int Hkv, int cap, int r, const float* Rr,
+                                          bf16_t* Kp, int32_t* seq_len_out, hipStream_t st)
+{
+    typedef CompressCfg<R, NP> Cfg;
+    int nblk = (rows.n_tokens + Cfg::TOK_PER_BLOCK - 1) / Cfg::TOK_PER_BLOCK;
+    if (nblk < 1) nblk = 1;
+    hipLaunchKernelGGL((compress_mfma<R, GATHER, NP>), dim3(nblk, Hkv, B), dim3(256), Cfg::LDS_BYTES, st, rows, Hkv, cap, r, Rr, Kp,
+                       seq_len_out);
+    return hipGetLastError();
+}
+
 // 512 tokens per work-group.  With 2048 (one R_r fragment build per 2048 rows, one work-group per compute unit) the last ones
 // decide the time of the launch, and where the lengths are on the device (token lists, n_tokens_dev) the host's bound does not
 // even say how many blocks have rows.  Call with Values, 32 heads, r = 48, 2048 / 512 tokens: 1 x 32768 162.1 / 160.7 us; 4 x 8192
 // ragged with lists 86 / 64; 16 x 14000 so 354 / 334; 8 x 14000 ragged without 287 / 275; r = 64, 8 x 16384 659 / 652.
+// At r = 128 the fragments are 64 KB and their build shows where long blocks come out at exactly one work-group per compute unit: 8 x 4
+// heads x 16384 101.3 / 104.2 us (r = 112: 100.7 both ways; two rounds of long blocks, 1 x 32 heads x 32768: 201.4 / 197.9).
 template <int R>
 static hipError_t launch_compress_mfma_r(const RowsDev& rows, int B, int Hkv, int cap, int r, const float* Rr,
                                          bf16_t* Kp, int32_t* seq_len_out, hipStream_t st)
 {
-    typedef CompressCfg<R> Cfg;
-    int nblk = (rows.n_tokens + Cfg::TOK_PER_BLOCK - 1) / Cfg::TOK_PER_BLOCK;
-    if (nblk < 1) nblk = 1;
-    if (rows.tok_idx)
-        hipLaunchKernelGGL((compress_mfma<R, true>), dim3(nblk, Hkv, B), dim3(256), Cfg::LDS_BYTES, st, rows, Hkv, cap, r, Rr, Kp,
-                           seq_len_out);
-    else
-        hipLaunchKernelGGL((compress_mfma<R, false>), dim3(nblk, Hkv, B), dim3(256), Cfg::LDS_BYTES, st, rows, Hkv, cap, r, Rr, Kp,
-                           seq_len_out);
-    return hipGetLastError();
+    if (rows.tok_idx) return launch_compress_mfma_rp<R, true, 4>(rows, B, Hkv, cap, r, Rr, Kp, seq_len_out, st);
+    if constexpr (R > 112) {
+        constexpr int LONG = CompressCfg<R, 16>::TOK_PER_BLOCK;
+        if (!rows.n_dev && (int64_t)((rows.n_tokens + LONG - 1) / LONG) * Hkv * B == 256)
+            return launch_compress_mfma_rp<R, false, 16>(rows, B, Hkv, cap, r, Rr, Kp, seq_len_out, st);
+    }
+    return launch_compress_mfma_rp<R, false, 4>(rows, B, Hkv, cap, r, Rr, Kp, seq_len_out, st);
 }
 
 template <int R>
