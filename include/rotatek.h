@@ -278,7 +278,8 @@ rk_status rk_append(rk_ctx* ctx, const rk_layout* L, const void* k_new, const vo
  * the seq_len[b] cached tokens, out = P V.  q, out: [B,H_q,d] in L->dtype; q and
  * both caches 16-byte aligned (the kernels read them in 16-byte pieces).
  * A sequence with seq_len[b] = 0 yields zeros.  Two launches (split-K, merge) as
- * in App. C, one when the plan has a single split.
+ * in App. C; one when the plan has a single split or the merge rides in the split
+ * launch (either dtype, by the number of units).
  * Errors: INVALID_ARG, UNSUPPORTED, CAPACITY (max_seq_len > capacity),
  * WORKSPACE, HIP.                                                             */
 rk_status rk_decode_attn(rk_ctx* ctx, const rk_layout* L, const void* q, const void* k_packed,
