@@ -487,7 +487,10 @@ __device__ __forceinline__ float load_past_l1(const float* p)
 
 // Fold of S partials (m, l, acc) for one (row, 8 channels) in ascending order, MC at a time: every
 // load of a chunk is issued before the first use, so a chunk costs one round trip to the L2.
-template <int MC>
+// T: storage type of the result.  An fp32 result has the bits that decode_merge gives it, whose products and sums are fused as written
+// here; where the choice is the compiler's it fuses the first term behind a rescale with the rescale, which moves last bits
+// from 17 partials on (bf16 results, 256 times as coarse, stay with that).
+template <int MC, typename T>
 __device__ __forceinline__ void fold_partials(const float* pm, const float* pl, const float* pa, int S, float& M,
                                               float& den, f32x4& n0, f32x4& n1)
 {
@@ -515,8 +518,16 @@ __device__ __forceinline__ void fold_partials(const float* pm, const float* pl, 
             for (int k = 0; k < MC; ++k) {
                 const float w = exp2f(mv[k] - Mc);              // 2^(-inf) = 0 for empty and absent partials
                 den = fmaf(lv[k], w, den);
-                n0 += a0[k] * w;
-                n1 += a1[k] * w;
+                if constexpr (std::is_same<T, float>::value) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        n0[e] = fmaf(a0[k][e], w, n0[e]);
+                        n1[e] = fmaf(a1[k][e], w, n1[e]);
+                    }
+                } else {
+                    n0 += a0[k] * w;
+                    n1 += a1[k] * w;
+                }
             }
             M = Mc;
         }
@@ -569,8 +580,8 @@ __device__ __forceinline__ void fold_unit(int unit, int S, int b, int u, int Hq,
             sx = load_past_l1(snew + row);
             vraw = *(const uint4*)(v_new + (size_t)u * D + c0);
         }
-        if (S <= 8) fold_partials<8>(pm, pl, pa, S, M, den, n0, n1);     // one round trip to the L2
-        else fold_partials<16>(pm, pl, pa, S, M, den, n0, n1);
+        if (S <= 8) fold_partials<8, T>(pm, pl, pa, S, M, den, n0, n1);     // one round trip to the L2
+        else fold_partials<16, T>(pm, pl, pa, S, M, den, n0, n1);
         if (NEW && sx > NEG_INF) {
             const float Mc = fmaxf(M, sx);
             const float resc = exp2f(M - Mc), w = exp2f(sx - Mc);

@@ -132,12 +132,18 @@ def test_decode(ctx, case):
             assert not got[b].any()
 
 
+def folds(units, S, tiles, r):
+    """Whether the split launch of an fp32 decode merges as well: its unit count must load the eight XCDs evenly enough."""
+    excess = -(-units // 8) * 8 / units - 1
+    return S > 1 and excess * units * tiles * 128 * ((r + 15) // 16 * 16 + D) * 4 / 6.5e6 < 3
+
+
 # The merge inside the split launch against the merge launch: the same partials folded in the same order, so the same bits.  Unit
-# counts around the eight XCDs, up to 40 splits (three rounds of loads), empty splits and sequences, two head groups, and a result
-# that is only 4-byte aligned.
+# counts around the eight XCDs, 17 and 40 splits (two and three rounds of loads), empty splits and sequences, two head groups, and a
+# result that is only 4-byte aligned.
 @pytest.mark.parametrize("B,Hq,Hkv,L,lengths,r,splits", [
     (2, 14, 7, 700, [700, 0], 37, 0), (1, 8, 8, 513, None, 64, 2), (3, 9, 3, 1300, [1300, 129, 1], 128, 9), (1, 40, 2, 300, None, 100, 3),
-    (1, 17, 17, 5200, None, 16, 40), (5, 32, 8, 260, [260, 0, 128, 129, 31], 112, 0),
+    (1, 24, 24, 2300, None, 32, 17), (1, 16, 16, 5200, None, 16, 40), (5, 32, 8, 260, [260, 0, 128, 129, 31], 112, 2),
 ])
 def test_merge_in_the_split_launch(ctx, B, Hq, Hkv, L, lengths, r, splits):
     data = layer(B, Hq, Hkv, L, "f32", 65, lengths=lengths, mean_shift=1.0)
@@ -146,6 +152,7 @@ def test_merge_in_the_split_launch(ctx, B, Hq, Hkv, L, lengths, r, splits):
     rk.rk_set_option(ctx, rk.RK_OPT_DECODE_SPLITS, splits)
     got = []
     try:
+        assert folds(B * Hkv * -(-(Hq // Hkv) // 16), rk.rk_decode_plan(ctx, p.layout())[0], -(-L // 128), r)
         for fuse in (1, 0, 1):
             rk.rk_set_option(ctx, rk.RK_OPT_FUSE_MERGE, fuse)
             lay = p.layout()
