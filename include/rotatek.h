@@ -279,7 +279,9 @@ rk_status rk_append(rk_ctx* ctx, const rk_layout* L, const void* k_new, const vo
  * both caches 16-byte aligned (the kernels read them in 16-byte pieces).
  * A sequence with seq_len[b] = 0 yields zeros.  Two launches (split-K, merge) as
  * in App. C; one when the plan has a single split or the merge rides in the split
- * launch (either dtype, by the number of units).
+ * launch (either dtype): all splits of a unit (b, h_kv, 16 query heads) then share an
+ * XCD, and max_seq_len, keep, the dtype and the split count decide whether the units
+ * load the XCDs evenly enough for that.
  * Errors: INVALID_ARG, UNSUPPORTED, CAPACITY (max_seq_len > capacity),
  * WORKSPACE, HIP.                                                             */
 rk_status rk_decode_attn(rk_ctx* ctx, const rk_layout* L, const void* q, const void* k_packed,

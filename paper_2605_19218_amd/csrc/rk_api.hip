@@ -661,7 +661,7 @@ static rk_status decode_common(rk_ctx* ctx, const rk_layout* L, const void* q, c
                       L->keep, S + St, S, p.tiles, q, k_packed, v_cache, R_r, delta_mu, L->seq_len, text ? &td : nullptr, nullptr,
                       tk_new ? &ta : nullptr, sc, out, (float*)workspace,
                       ctx->fuse_merge && ctx->xcd_deal_ok ? ctx->tickets + APP_TICKETS : nullptr, DEC_COUNTERS,
-                      L->batch <= APP_TICKETS ? ctx->tickets : nullptr, as_stream(stream));
+                      L->batch <= APP_TICKETS ? ctx->tickets : nullptr, ctx->n_cu, as_stream(stream));
     if (e != hipSuccess) return hip_fail(ctx, e, "decode launch");
     return RK_OK;
 }
@@ -749,7 +749,7 @@ rk_status rk_append_decode_attn(rk_ctx* ctx, const rk_layout* L, const void* k_n
     e = launch_decode(L->dtype, mfma, L->batch, L->n_q_heads, L->n_kv_heads, L->capacity, L->keep, p.S, p.S, p.tiles, q,
                       k_packed, v_cache, R_r, delta_mu, seq_len, nullptr, fused ? &app : nullptr, nullptr, sc, out,
                       (float*)workspace, ctx->fuse_merge && ctx->xcd_deal_ok ? ctx->tickets + APP_TICKETS : nullptr,
-                      DEC_COUNTERS, ctx->tickets, st);
+                      DEC_COUNTERS, ctx->tickets, ctx->n_cu, st);
     if (e != hipSuccess) return hip_fail(ctx, e, "decode launch");
     return RK_OK;
 }

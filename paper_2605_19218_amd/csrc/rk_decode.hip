@@ -1584,6 +1584,17 @@ static bool fold_pays(int nunit, int tiles_all, int r, int elem)
     const double cache_bytes = (double)nunit * tiles_all * 128.0 * (keep_padded(r) + D) * elem;
     return ((double)((nunit + 7) / 8 * 8) / nunit - 1.0) * cache_bytes / 6.5e6 < 3.0;
 }
+// fp32: besides, the busiest XCD's ceil(nunit / 8) S work-groups may not take more rounds of its compute units than all of them
+// spread over the device would: its second round then starts when the other XCDs are done.  r = 64, folded / two launches: 7 units
+// x 24000 tokens, S = 36, 48.0 / 36.2 us (12000 28.9 / 23.7); 20 x 3000, S = 12, 23.2 / 17.8; 28 x 6000, S = 9, 45.5 / 33.6; with as
+// many rounds 12 x 3000, S = 12, 15.8 / 16.1 and 7 x 6000, S = 23, 19.0 / 19.7; 258 x 2000, S = 4, five rounds either way, 87.9 /
+// 91.5.  Where the rounds are equal the bytes above still tell the sides apart: 68 units x 8000 tokens, 3.8 us of excess, 89.8 / 89.7;
+// x 4000, 1.9 us, 48.7 / 49.5.
+static bool fold_pays_f32(int nunit, int S, int tiles_all, int r, int n_cu)
+{
+    const int64_t per_xcd = n_cu >= 8 ? n_cu / 8 : 1, busiest = (int64_t)((nunit + 7) / 8) * S, all = (int64_t)nunit * S;
+    return (busiest + per_xcd - 1) / per_xcd <= (all + n_cu - 1) / n_cu && fold_pays(nunit, tiles_all, r, 4);
+}
 
 bool decode_mfma_supported(int dtype, int r) { return dtype == 1 && r >= 1 && r <= 128; }
 
@@ -1620,7 +1631,7 @@ hipError_t launch_decode(int dtype, bool mfma, int B, int Hq, int Hkv, int cap, 
                          const void* q, const void* Kp, const void* Vc, const float* Rr, const float* dmu,
                          const int32_t* seq_len, const TextDev* text, const AppendDev* app, const TextAppendDev* tapp,
                          float scale, void* out, float* ws, int32_t* counters, int n_counters, int32_t* batch_tickets,
-                         hipStream_t st)
+                         int n_cu, hipStream_t st)
 {
     const size_t rows = (size_t)B * Hq;
     const bool text_in_split = text && mfma && decode_mfma_supported(dtype, r);    // else the second kernel runs the text
@@ -1664,7 +1675,8 @@ hipError_t launch_decode(int dtype, bool mfma, int B, int Hq, int Hkv, int cap, 
         if (e != hipSuccess || direct || fused_merge) return e;
     } else if (mfma && dtype == 0) {
         const int gy = Hkv * ((Hq / Hkv + 15) / 16), nunit = B * gy;
-        const bool fused_merge = !text && S >= 2 && counters && nunit <= n_counters && fold_pays(nunit, tiles_all, r, 4);
+        const bool fused_merge = !text && S >= 2 && counters && nunit <= n_counters &&
+                                 fold_pays_f32(nunit, S, tiles_all, r, n_cu);
         const dim3 grid = fused_merge ? dim3((unsigned)(8 * ((nunit + 7) / 8) * S)) : dim3(S, gy, B);
         float* o = direct ? (float*)out : nullptr;
 #define RK_FORM(RV, FUSED)                                                                                       \

@@ -101,7 +101,7 @@ hipError_t launch_decode(int dtype, bool mfma, int B, int Hq, int Hkv, int cap, 
                          const void* q, const void* Kp, const void* Vc, const float* Rr, const float* dmu,
                          const int32_t* seq_len, const TextDev* text, const AppendDev* app, const TextAppendDev* tapp,
                          float scale, void* out, float* ws, int32_t* counters, int n_counters, int32_t* batch_tickets,
-                         hipStream_t st);
+                         int n_cu, hipStream_t st);
 // Whether work-groups whose linear indices agree modulo 8 run on the same XCD (true on MI355X in every
 // partition mode).  Launches a tiny kernel that records each work-group's XCD and synchronises;
 // scratch: 64 ints of device memory, left zeroed.

@@ -1,5 +1,7 @@
 """fp32 storage on the matrix-core kernels (covariance, compress, decode) at the edges of their tiles, against the
 oracle and against the plain kernels.  fp32 results: max|x - y| / max|y| <= 1e-4, as everywhere in this suite."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -132,10 +134,17 @@ def test_decode(ctx, case):
             assert not got[b].any()
 
 
-def folds(units, S, tiles, r):
-    """Whether the split launch of an fp32 decode merges as well: its unit count must load the eight XCDs evenly enough."""
-    excess = -(-units // 8) * 8 / units - 1
-    return S > 1 and excess * units * tiles * 128 * ((r + 15) // 16 * 16 + D) * 4 / 6.5e6 < 3
+def launches(call):
+    """Kernels that call(stream) enqueues, counted in a graph that is captured and never run."""
+    hip = C.CDLL(next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line))
+    stream, graph, n = torch.cuda.Stream(), C.c_void_p(), C.c_size_t()
+    assert hip.hipStreamBeginCapture(C.c_void_p(stream.cuda_stream), 2) == 0
+    try:
+        call(stream)
+    finally:
+        assert hip.hipStreamEndCapture(C.c_void_p(stream.cuda_stream), C.byref(graph)) == 0
+    assert hip.hipGraphGetNodes(graph, None, C.byref(n)) == 0 and hip.hipGraphDestroy(graph) == 0
+    return n.value
 
 
 # The merge inside the split launch against the merge launch: the same partials folded in the same order, so the same bits.  Unit
@@ -144,6 +153,7 @@ def folds(units, S, tiles, r):
 @pytest.mark.parametrize("B,Hq,Hkv,L,lengths,r,splits", [
     (2, 14, 7, 700, [700, 0], 37, 0), (1, 8, 8, 513, None, 64, 2), (3, 9, 3, 1300, [1300, 129, 1], 128, 9), (1, 40, 2, 300, None, 100, 3),
     (1, 24, 24, 2300, None, 32, 17), (1, 16, 16, 5200, None, 16, 40), (5, 32, 8, 260, [260, 0, 128, 129, 31], 112, 2),
+    (1, 9, 9, 2100, None, 48, 16),
 ])
 def test_merge_in_the_split_launch(ctx, B, Hq, Hkv, L, lengths, r, splits):
     data = layer(B, Hq, Hkv, L, "f32", 65, lengths=lengths, mean_shift=1.0)
@@ -152,19 +162,43 @@ def test_merge_in_the_split_launch(ctx, B, Hq, Hkv, L, lengths, r, splits):
     rk.rk_set_option(ctx, rk.RK_OPT_DECODE_SPLITS, splits)
     got = []
     try:
-        assert folds(B * Hkv * -(-(Hq // Hkv) // 16), rk.rk_decode_plan(ctx, p.layout())[0], -(-L // 128), r)
         for fuse in (1, 0, 1):
             rk.rk_set_option(ctx, rk.RK_OPT_FUSE_MERGE, fuse)
             lay = p.layout()
             ws = torch.full((rk.rk_decode_workspace_size(ctx, lay),), 0xff, device=DEV, dtype=torch.uint8)
             out = torch.full((B * Hq * D + 1,), float("nan"), device=DEV)[1:].view(B, Hq, D)
-            rk.rk_decode_attn(ctx, lay, q, p.Kp, p.Vc, p.Rr, p.dmu, 0.0, out, ws)
+
+            def call(stream=None):
+                rk.rk_decode_attn(ctx, lay, q, p.Kp, p.Vc, p.Rr, p.dmu, 0.0, out, ws, stream=stream)
+
+            assert launches(call) == 2 - fuse
+            call()
             got.append(out.cpu().numpy())
     finally:
         rk.rk_set_option(ctx, rk.RK_OPT_FUSE_MERGE, 1)
         rk.rk_set_option(ctx, rk.RK_OPT_DECODE_SPLITS, 0)
     check_out(got[0], oracle_decode(p, data["q"], lengths or [L] * B), "f32")
     assert np.array_equal(got[0], got[1]) and np.array_equal(got[0], got[2])
+
+
+# Whether the merge rides in the split launch: unit counts that load the XCDs evenly; unevenly but within one round of their compute
+# units; unevenly with a second round on some (7 units of 36 splits, 9 of 17); and by more bytes than the second launch is worth.
+@pytest.mark.parametrize("units,L,splits,kernels", [
+    (8, 24000, 0, 1), (64, 3000, 0, 1), (12, 3000, 0, 1), (7, 6000, 0, 1), (36, 1000, 0, 1), (258, 600, 0, 1), (9, 2100, 16, 1),
+    (9, 2200, 17, 2), (7, 12000, 0, 2), (7, 24000, 0, 2), (20, 3000, 0, 2), (28, 6000, 0, 2), (36, 3000, 0, 2), (60, 8000, 0, 2),
+])
+def test_where_the_merge_rides_along(ctx, units, L, splits, kernels):
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the table is for 256 compute units")
+    lay = rk.Layout(1, units, units, 64, rk.RK_F32, (L + 31) // 32 * 32, L, seq_len=torch.full((1,), L, device=DEV, dtype=torch.int32))
+    kb, vb = rk.rk_cache_bytes(lay)
+    K, V, q, Rr, out = (torch.zeros(n, device=DEV) for n in (kb // 4, vb // 4, units * D, units * D * 64, units * D))
+    rk.rk_set_option(ctx, rk.RK_OPT_DECODE_SPLITS, splits)
+    try:
+        ws = torch.empty(rk.rk_decode_workspace_size(ctx, lay), device=DEV, dtype=torch.uint8)
+        assert launches(lambda s: rk.rk_decode_attn(ctx, lay, q, K, V, Rr, None, 0.0, out, ws, stream=s)) == kernels
+    finally:
+        rk.rk_set_option(ctx, rk.RK_OPT_DECODE_SPLITS, 0)
 
 
 # Tokens whose score overflows to minus infinity weigh nothing, also where they fill a 16-token tile, a wave's first one,
