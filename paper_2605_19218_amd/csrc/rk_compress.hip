@@ -52,14 +52,14 @@ __global__ __launch_bounds__(256) void compress_generic(RowsDev rows, int Hkv, i
 // operand are permuted so that after output blocks 2i and 2i+1 lane (g, n) holds
 // the 8 output channels 32 i + 8 g ..+7 of token n -- one 16-byte piece of the
 // packed layout, and consecutive lanes write consecutive pieces.
-template <int R, int NP>
+template <int R>
 struct CompressCfg {
     static constexpr int JB = R / 16;                 // 16-wide output-channel blocks
     static constexpr int NF = R / 32;                 // full 32-channel groups
     static constexpr bool TAIL = (R % 32) != 0;       // one trailing 16-channel block
     static constexpr int TT = 2;                      // 16-token tiles per wave and pass (two passes in flight)
     static constexpr int TOK_PER_PASS = 4 * TT * 16;  // tokens one pass of the 4 waves covers
-    static constexpr int PASSES = NP;                 // passes per work-group (amortise the R_r fragment build)
+    static constexpr int PASSES = 4;                  // passes per work-group (amortise the R_r fragment build)
     static constexpr int TOK_PER_BLOCK = PASSES * TOK_PER_PASS;
     static constexpr size_t LDS_BYTES = (size_t)JB * 4 * 2 * 64 * 16;   // A fragments, hi+lo
     // output channel held by A row a of block jb
@@ -72,23 +72,36 @@ __device__ __forceinline__ uint32_t pack2_bf16(float a, float b) {
     return (uint32_t)f32_to_bf16(a) | ((uint32_t)f32_to_bf16(b) << 16);
 }
 
-template <int R, bool GATHER, int NP>
-__global__ __launch_bounds__(256, 2) void compress_mfma(RowsDev rows, int Hkv, int cap, int r,
+template <int R, bool GATHER>
+__global__ __launch_bounds__(256, 2) void compress_mfma(RowsDev rows, int Hkv, int cap, int r, int part_last,
                                                      const float* __restrict__ Rr, bf16_t* __restrict__ Kp,
                                                      int32_t* __restrict__ seq_len_out)
 {
-    typedef CompressCfg<R, NP> Cfg;
+    typedef CompressCfg<R> Cfg;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     bf16x8* frag = (bf16x8*)smem_raw;       // [JB][4][2][64]
 
-    const int h = blockIdx.y, b = blockIdx.z, u = b * Hkv + h;
+    // part_last: the last block number is a partly filled one.  Its work-groups then start behind all others, where they fill up
+    // the compute units that the full ones leave; among them, a compute unit gets two full ones while the next gets two short ones
+    // (16 x 16 heads x 600 rows, r = 32: 15.4 -> 11.8 us; 4 x 32 x 2100, r = 128: 43 -> 34.6; 1 x 32 x 16500, r = 64: 45.7 -> 41.6).
+    int h = blockIdx.y, b = blockIdx.z, nx = gridDim.x, bx = blockIdx.x;
+    bool rotate = true;
+    if (part_last) {
+        const int id = bx + nx * (h + Hkv * b), full = --nx * (int)(gridDim.y * gridDim.z);
+        rotate = id < full;
+        const int w = rotate ? id / nx : id - full;
+        bx = __builtin_amdgcn_readfirstlane(rotate ? id - w * nx : nx);
+        b = __builtin_amdgcn_readfirstlane(w / Hkv);
+        h = __builtin_amdgcn_readfirstlane(w - b * Hkv);
+    }
+    // Work-groups go to the 8 XCDs round-robin by linear index.  An even count of blocks is rotated by head and batch item, so that
+    // an XCD does not end up with "block 7 of every sequence" (which only the longest sequences have); an odd one walks over the
+    // XCDs by itself, and rotated like that 9, 17, .. blocks would stand still.
+    if (rotate && !(nx & 1)) bx = (int)((unsigned)(bx + h + b) % (unsigned)nx);
+    const int u = b * Hkv + h;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int g = lane >> 4, n = lane & 15;
     const int n_b = min(rows_count(rows, b), cap);
-    // Work-groups go to the 8 XCDs round-robin by linear index, i.e. by blockIdx.x when the grid's first
-    // extent is a multiple of 8: the block number is rotated by head and batch item, so that an XCD
-    // does not end up with "block 7 of every sequence" (which only the longest sequences have)
-    const int bx = (int)((blockIdx.x + blockIdx.y + blockIdx.z) % gridDim.x);
     if (bx == 0 && h == 0 && tid == 0 && seq_len_out) seq_len_out[b] = n_b;
     const int blk0 = bx * Cfg::TOK_PER_BLOCK;
     if (blk0 >= n_b) return;
@@ -467,35 +480,23 @@ __global__ __launch_bounds__(256) void unpack_cache(int cap, int r, const T* __r
 }
 
 // ---------------------------------------------------------------------------
-template <int R, bool GATHER, int NP>
-static hipError_t launch_compress_mfma_rp(const RowsDev& rows, int B, int Hkv, int cap, int r, const float* Rr,
-                                          bf16_t* Kp, int32_t* seq_len_out, hipStream_t st)
-{
-    typedef CompressCfg<R, NP> Cfg;
-    int nblk = (rows.n_tokens + Cfg::TOK_PER_BLOCK - 1) / Cfg::TOK_PER_BLOCK;
-    if (nblk < 1) nblk = 1;
-    hipLaunchKernelGGL((compress_mfma<R, GATHER, NP>), dim3(nblk, Hkv, B), dim3(256), Cfg::LDS_BYTES, st, rows, Hkv, cap, r, Rr, Kp,
-                       seq_len_out);
-    return hipGetLastError();
-}
-
-// 512 tokens per work-group.  With 2048 (one R_r fragment build per 2048 rows, one work-group per compute unit) the last ones
-// decide the time of the launch, and where the lengths are on the device (token lists, n_tokens_dev) the host's bound does not
-// even say how many blocks have rows.  Call with Values, 32 heads, r = 48, 2048 / 512 tokens: 1 x 32768 162.1 / 160.7 us; 4 x 8192
-// ragged with lists 86 / 64; 16 x 14000 so 354 / 334; 8 x 14000 ragged without 287 / 275; r = 64, 8 x 16384 659 / 652.
-// At r = 128 the fragments are 64 KB and their build shows where long blocks come out at exactly one work-group per compute unit: 8 x 4
-// heads x 16384 101.3 / 104.2 us (r = 112: 100.7 both ways; two rounds of long blocks, 1 x 32 heads x 32768: 201.4 / 197.9).
+// 512 tokens per work-group.  With 2048 (one R_r fragment build per 2048 rows) the last work-groups decide the time of the launch,
+// most where the lengths are on the device (token lists, n_tokens_dev) and the host's bound does not say how many blocks have
+// rows, and at some distances of the caches' slabs their concurrent streams meet in the same memory channels.  Call without Values,
+// r = 64, 2048 / 512 tokens: 1 x 32 heads x 32768 79 / 75 us; 4 x 32 x 5000 66 / 50; 17 x 16 x 1100 38 / 29; 2 x 32 x 9000 ragged 49 / 29;
+// 16 x 16 x 2048 38 / 41.  r = 128, where the fragments are 64 KB: 1 x 32 x 16384 54 / 56; 16 x 16 x 2048 55 / 60; 1 x 64 x 8192 (slabs 8256
+// tokens apart) 76 / 59; 1 x 16 x 32768 (33088 apart) 64 / 59.  With 1024: 56, 58, 62, 61, but 16 x 16 x 1536 ragged 41 / 30.
 template <int R>
 static hipError_t launch_compress_mfma_r(const RowsDev& rows, int B, int Hkv, int cap, int r, const float* Rr,
                                          bf16_t* Kp, int32_t* seq_len_out, hipStream_t st)
 {
-    if (rows.tok_idx) return launch_compress_mfma_rp<R, true, 4>(rows, B, Hkv, cap, r, Rr, Kp, seq_len_out, st);
-    if constexpr (R > 112) {
-        constexpr int LONG = CompressCfg<R, 16>::TOK_PER_BLOCK;
-        if (!rows.n_dev && (int64_t)((rows.n_tokens + LONG - 1) / LONG) * Hkv * B == 256)
-            return launch_compress_mfma_rp<R, false, 16>(rows, B, Hkv, cap, r, Rr, Kp, seq_len_out, st);
-    }
-    return launch_compress_mfma_rp<R, false, 4>(rows, B, Hkv, cap, r, Rr, Kp, seq_len_out, st);
+    typedef CompressCfg<R> Cfg;
+    int nblk = (rows.n_tokens + Cfg::TOK_PER_BLOCK - 1) / Cfg::TOK_PER_BLOCK;
+    if (nblk < 1) nblk = 1;
+    const int part_last = nblk > 1 && rows.n_tokens % Cfg::TOK_PER_BLOCK != 0 && (int64_t)Hkv * B <= INT32_MAX / nblk;
+    const auto kernel = rows.tok_idx ? compress_mfma<R, true> : compress_mfma<R, false>;
+    hipLaunchKernelGGL(kernel, dim3(nblk, Hkv, B), dim3(256), Cfg::LDS_BYTES, st, rows, Hkv, cap, r, part_last, Rr, Kp, seq_len_out);
+    return hipGetLastError();
 }
 
 template <int R>

@@ -1,6 +1,6 @@
-"""bf16 compress in blocks of 512 tokens, with lengths on the device and enough heads to fill it; lengths around the passes (128
-tokens) and blocks; and with equal lengths, where r = 128 takes one 2048-token block a head.  Against the oracle: one bf16 unit
-plus the accumulation bound, as everywhere in this suite."""
+"""bf16 compress in blocks of 512 tokens: lengths around the passes (128 tokens) and blocks, equal, on the device or by token lists;
+block counts of either parity, with the last one full or partly filled (its work-groups then start behind the others), and heads
+that fill the device or not.  Against the oracle: one bf16 unit plus the accumulation bound, as everywhere in this suite."""
 import numpy as np
 import pytest
 import torch
@@ -14,10 +14,11 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("form", ["lengths", "lists", "equal"])
-@pytest.mark.parametrize("r", [37, 128])
-def test_blocks(r, form):
-    lengths = [1100, 1025, 1024, 513, 512, 511, 129, 1, 0] + [640] * 7 if form != "equal" else [1100] * 16
-    B, Hkv, L = len(lengths), 16, max(lengths)               # 256 heads
+@pytest.mark.parametrize("r,Hkv,L", [(37, 16, 1100), (128, 16, 1100), (64, 3, 520), (64, 3, 1024), (128, 3, 1536), (16, 3, 1600), (64, 3, 2100)])
+def test_blocks(r, Hkv, L, form):
+    lengths = [L, 1025, 1024, 513, 512, 511, 129, 1, 0] + [640] * 7 if form != "equal" else [L] * 16
+    lengths = [min(n, L) for n in lengths]
+    B = len(lengths)
     ctx = rk.rk_create(0)
     data = layer(B, Hkv, Hkv, L, "bf16", 72, lengths=lengths)
     p = Pipeline(ctx, B, Hkv, Hkv, r, "bf16", L)
@@ -36,7 +37,7 @@ def test_blocks(r, form):
     rk.rk_destroy(ctx)
     assert seq == lengths
     for b in range(B):
-        for h in (0, 15):
+        for h in (0, Hkv - 1):
             check_packed(Kt[b, h, :lengths[b]], data["K"][b, h][rows[b]].astype(np.float64), Rr[b, h], "bf16")
             assert np.array_equal(Vc[b, h, :lengths[b]], data["V"][b, h][rows[b]])
             assert not Kt[b, h, lengths[b]:].any()
