@@ -720,20 +720,24 @@ hipError_t launch_cov_partial(int dtype, bool mfma, const RowsDev& rows, int B, 
 }
 
 hipError_t launch_cov_finalize(int dtype, bool mfma, const RowsDev& rows, int B, int Hkv, int n_chunks, bool center,
-                               const float* part_S, const float* part_sum, float* cov, float* mu, hipStream_t st)
+                               const float* part_S, const float* part_sum, float* cov, float* mu, int n_cu, hipStream_t st)
 {
-    // from two work-groups a compute unit on: on 32 units the positions' 1280 small ones take 6.2 us, the rows' 128 8.5
-    if (mfma && B * Hkv >= 128) {
+    // By rows from two work-groups a compute unit on, and not for long sequences of few units: four chunks are in flight in place of
+    // eight, and off-diagonal tiles are read twice.  By rows / by positions: 32 units x 2 chunks 7.4 / 6.2 us; 128 x 2 10.2 / 11.7, x 12 18.7 /
+    // 20.2, x 14 21.1 / 20.8, x 16 25.4 / 22.0; 256 x 12 33.5 / 37.2, x 16 45.4 / 42.3; 384 x 14 57 / 61, x 16 65 / 66; 512 x 14 72 / 81; fp32 128 x 6
+    // 12.1 / 12.3, x 16 25.6 / 21.5.
+    const int U = B * Hkv;
+    if (mfma && 2 * U >= n_cu && (n_chunks <= 12 || 2 * U >= 3 * n_cu)) {
         const auto kernel = dtype == 1 ? cov_finalize_rows<false> : cov_finalize_rows<true>;
-        hipLaunchKernelGGL(kernel, dim3(4, B * Hkv), dim3(256), 0, st, rows, Hkv, n_chunks, center ? 1 : 0, part_S, part_sum, cov, mu);
+        hipLaunchKernelGGL(kernel, dim3(4, U), dim3(256), 0, st, rows, Hkv, n_chunks, center ? 1 : 0, part_S, part_sum, cov, mu);
     } else if (mfma && dtype == 1)
-        hipLaunchKernelGGL(cov_finalize_tiled<false>, dim3(40, B * Hkv), dim3(256), 0, st, rows, Hkv, n_chunks,
+        hipLaunchKernelGGL(cov_finalize_tiled<false>, dim3(40, U), dim3(256), 0, st, rows, Hkv, n_chunks,
                            center ? 1 : 0, part_S, part_sum, cov, mu);
     else if (mfma)
-        hipLaunchKernelGGL(cov_finalize_tiled<true>, dim3(40, B * Hkv), dim3(256), 0, st, rows, Hkv, n_chunks,
+        hipLaunchKernelGGL(cov_finalize_tiled<true>, dim3(40, U), dim3(256), 0, st, rows, Hkv, n_chunks,
                            center ? 1 : 0, part_S, part_sum, cov, mu);
     else
-        hipLaunchKernelGGL(cov_finalize, dim3(8, B * Hkv), dim3(256), 0, st, rows, Hkv, n_chunks, center ? 1 : 0,
+        hipLaunchKernelGGL(cov_finalize, dim3(8, U), dim3(256), 0, st, rows, Hkv, n_chunks, center ? 1 : 0,
                            part_S, part_sum, cov, mu);
     return hipGetLastError();
 }

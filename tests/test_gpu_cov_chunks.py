@@ -45,8 +45,8 @@ def test_chunk_lengths(B, Hkv, L, lengths, lists):
 
 
 def test_many_units_fp32():
-    """From 128 heads on the reduction goes by rows, four chunks at a time: five of 512 tokens here, in the fp32 kernel's channel order
-    (the bf16 one above has two)."""
+    """With 128 heads the reduction goes by rows, four chunks at a time: five of 512 tokens here, in the fp32 kernel's channel order
+    (the bf16 one above has two).  Against the oracle; the bits are held below."""
     B, Hkv, L, lengths = 4, 32, 2100, [2100, 2048, 513, 0]
     ctx = rk.rk_create(0)
     data = layer(B, Hkv, Hkv, L, "f32", 73, lengths=lengths, mean_shift=2.0)
@@ -65,4 +65,26 @@ def test_many_units_fp32():
                 mu_o, C_o = oracle.mean_scatter(data["K"][b, h, :n], center=center)
                 assert np.abs(cov[b, h] - C_o).max() <= 1e-4 * np.abs(C_o).max()
                 assert rel_max(mu[b, h], mu_o) <= 1e-4
+    rk.rk_destroy(ctx)
+
+
+@pytest.mark.parametrize("dtype,B,L", [("f32", 4, 2100), ("bf16", 4, 24576), ("bf16", 4, 26000), ("bf16", 12, 26000)])
+def test_reduction_by_rows_keeps_the_bits(dtype, B, L):
+    """128 heads with 5 (fp32) and 12 chunks, and 384 with 13, are reduced by rows, 128 with 13 by positions, as are the calls of 64
+    heads that they are compared with: the same partials added in the same order, so the same bits."""
+    Hkv, ctx = 32, rk.rk_create(0)
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    base = torch.randn(L + 8 * B * Hkv, D, device=DEV, generator=torch.Generator(DEV).manual_seed(4)).add_(1.0).to(td)
+    K = base.as_strided((B, Hkv, L, D), (8 * Hkv * D, 8 * D, D, 1))                  # unit u: the L rows from 8 u on
+    lens = torch.tensor([L, L - 511, 2049, 0] * (B // 4), device=DEV, dtype=torch.int32)
+    for center in (True, False):
+        got = []
+        for n in (B, 2):
+            for b in range(0, B, n):
+                p = Pipeline(ctx, n, Hkv, Hkv, 16, dtype, 32)
+                p.cov.fill_(float("nan"))
+                p.fit(K[b:b + n], L, center=center, n_dev=lens[b:b + n].clone())
+                got.append((p.cov, p.mu))
+        assert torch.equal(got[0][0], torch.cat([c for c, _ in got[1:]]))
+        assert torch.equal(got[0][1], torch.cat([m for _, m in got[1:]]))
     rk.rk_destroy(ctx)
