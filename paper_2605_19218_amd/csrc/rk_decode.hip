@@ -490,6 +490,7 @@ __device__ __forceinline__ float load_past_l1(const float* p)
 // T: storage type of the result.  An fp32 result has the bits that decode_merge gives it, whose products and sums are fused as written
 // here; where the choice is the compiler's it fuses the first term behind a rescale with the rescale, which moves last bits
 // from 17 partials on (bf16 results, 256 times as coarse, stay with that).
+// (The accumulators lie behind 2 S scalars a row: 8 bytes past a 16-byte boundary where the rows and S are odd.)
 template <int MC, typename T>
 __device__ __forceinline__ void fold_partials(const float* pm, const float* pl, const float* pa, int S, float& M,
                                               float& den, f32x4& n0, f32x4& n1)
@@ -500,8 +501,8 @@ __device__ __forceinline__ void fold_partials(const float* pm, const float* pl, 
 #pragma unroll
         for (int k = 0; k < MC; ++k) {
             const int i = min(i0 + k, S - 1);
-            a0[k] = *(const f32x4*)(pa + (size_t)i * D);
-            a1[k] = *(const f32x4*)(pa + (size_t)i * D + 4);
+            a0[k] = *(const f32x4_any*)(pa + (size_t)i * D);
+            a1[k] = *(const f32x4_any*)(pa + (size_t)i * D + 4);
             const float mi = load_past_l1(pm + i);
             mv[k] = i0 + k < S ? mi : NEG_INF;
             lv[k] = load_past_l1(pl + i);
