@@ -590,8 +590,11 @@ __global__ __launch_bounds__(256, 2) void eig_tri_vectors(int U, const double* _
     if (s == 0) slam[pr] = lam;
     __syncthreads();
     // One round leaves a vector with a residual of some 5e-16, and that over the gap to the next eigenvalue in its direction:
-    // 1e-4 at TV_GAP, of which the step in eig_orth_back leaves 1e-8, a sixth of the fp32 rounding of R.  A nearer neighbour (of any pair of this work-group; the
-    // neighbours of its first and last pair are only known to lie beyond a point) asks for the second round.
+    // 1e-4 at TV_GAP.  What of it keeps two vectors from being orthogonal the step in eig_orth_back squares (3.2e-5 was the most in 1008
+    // glued tridiagonal matrices, 3.7e-6 with two rounds).  What turns two neighbours into each other stays, and stays below what the
+    // shift of T's diagonal, up to 6.4e-11, does to such neighbours: over 32 matrices of 16384 rows the largest element of R is 4.0461e-2 from
+    // the vectors of C_q itself with one round, 4.0460e-2 with two, and 1e-6 between them.  A nearer neighbour (of any pair
+    // of this work-group; the neighbours of its first and last pair are only known to lie beyond a point) asks for the second round.
     const double above = (pr > 0 ? slam[max(pr - 1, 0)] : over) - lam, under_by = lam - (pr < TV_PAIRS - 1 ? slam[min(pr + 1, TV_PAIRS - 1)] : under);
     const int rounds = __syncthreads_or(!(above > TV_GAP) || !(under_by > TV_GAP)) ? 2 : 1;
 
@@ -716,10 +719,12 @@ __global__ __launch_bounds__(256, 2) void eig_tri_vectors(int U, const double* _
 // ---------------------------------------------------------------------------
 // R = Q Z after one Newton-Schulz step Z <- Z (3 I - Z^T Z) / 2; 16 columns per work-group of 4 waves.
 // The step is what makes independent vectors safe: neighbours a gap g apart come out orthogonal only to about
-// 1e-16 / g, the step squares that defect, and because each vector is an eigenvector to 1e-16 the correction mixes
-// close neighbours only and costs no residual.  A defect E leaves (3/4) E^2 behind, so what the step may be given is bounded
-// by what the result is held to: an element above EIG_ORTH_MAX sends the matrix to Jacobi.  (Eigenvalues of T that stay
-// apart by the shift of 5e-13 give 6e-5 at most; above that two vectors have become one.)
+// 5e-16 / g (g above TV_GAP, one round of vectors) or 2e-17 / g (below it, two rounds), the step squares that defect, and because
+// each vector is an eigenvector to 5e-16 the correction mixes close neighbours only and costs no residual.  A defect E leaves
+// (3/4) E^2 behind, so what the step may be given is bounded by what the result is held to: an element above EIG_ORTH_MAX sends
+// the matrix to Jacobi.  (1008 glued tridiagonal matrices, with up to 91 gaps between TV_GAP and 2e-11 each: 3.2e-5 at most above TV_GAP;
+// 2.4e-4 below it, at gaps under 1e-13, the shift of 5e-13 undone; five, with gaps of 1e-14 and less, left to Jacobi, 21 when every
+// vector took two rounds behind a coarser multisection.)
 // Both products run on the fp64 matrix cores with all of Z in LDS; then Z's space takes the reflections, which were on
 // their way in registers meanwhile.  They are applied 16 at a time as I - V T V^T, again on the matrix cores, with the 16
 // columns of Z staying in result registers; T comes from eig_tri_vectors, where two waves have nothing else to do.

@@ -157,6 +157,22 @@ def test_close_eigenvalues(ctx, gap):
     assert np.linalg.norm(R.T @ C @ R - np.diag(lam)) <= 4 * eps * np.sqrt(D) * np.linalg.norm(C)
 
 
+# Blocks of equal tridiagonal matrices joined by weak links: neighbours whose vectors spread over all blocks.  Entries are dyadic, so the
+# reduction is handed the matrix as it is, and the solver's shift of its diagonal leaves many gaps just above the distance of the test before
+# (second case: on both sides of it).
+@pytest.mark.parametrize("block,link,slope,off", [(16, 18, 32, 0.125), (43, 26, 0, 0.5), (16, 28, 0, 0.5), (12, 14, 8, 0.25), (3, 28, 32, 0.125)])
+def test_glued_blocks(ctx, block, link, slope, off):
+    i = np.arange(D)
+    K = np.diag(1.0 + (np.abs(i % block - (block - 1) // 2) / slope if slope else 0.0 * i))
+    K[i[:-1], i[1:]] = np.where(i[:-1] % block == block - 1, 2.0 ** -link, off)
+    R, lam, C, sweeps, p = solve(ctx, K)
+    eps = 2.0 ** -24
+    assert np.array_equal(C, np.triu(np.tril(C, 1), -1))
+    assert sweeps == 1
+    assert np.abs(R.T @ R - np.eye(D)).max() <= 2 * eps * np.sqrt(D)
+    assert np.linalg.norm(R.T @ C @ R - np.diag(lam)) <= 4 * eps * np.sqrt(D) * np.linalg.norm(C)
+
+
 def test_non_finite_keys(ctx):
     """A head with an infinity or a NaN in its Keys: no eigenproblem to solve; the call ends, the other heads are as ever."""
     K = np.stack([recipe(100), recipe(100), recipe(100)]).astype(np.float32)[None]
