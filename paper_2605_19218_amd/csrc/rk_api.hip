@@ -576,7 +576,7 @@ rk_status rk_compress(rk_ctx* ctx, const rk_layout* L, const rk_rows* keys, cons
     if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
     hipStream_t st = as_stream(stream);
     e = launch_compress(L->dtype, !ctx->force_generic, to_dev(keys), L->batch, L->n_kv_heads, L->capacity, L->keep,
-                        R_r, k_packed, seq_len_out, st);
+                        R_r, k_packed, seq_len_out, ctx->n_cu, st);
     if (e != hipSuccess) return hip_fail(ctx, e, "compress launch");
     if (values) {
         e = launch_v_retile(L->dtype, to_dev(values), L->batch, L->n_kv_heads, L->capacity, v_cache, st);

@@ -72,8 +72,10 @@ __device__ __forceinline__ uint32_t pack2_bf16(float a, float b) {
     return (uint32_t)f32_to_bf16(a) | ((uint32_t)f32_to_bf16(b) << 16);
 }
 
+enum { ORDER_FEW, ORDER_MANY, ORDER_PART_LAST };
+
 template <int R, bool GATHER>
-__global__ __launch_bounds__(256, 2) void compress_mfma(RowsDev rows, int Hkv, int cap, int r, int part_last,
+__global__ __launch_bounds__(256, 2) void compress_mfma(RowsDev rows, int Hkv, int cap, int r, int order,
                                                      const float* __restrict__ Rr, bf16_t* __restrict__ Kp,
                                                      int32_t* __restrict__ seq_len_out)
 {
@@ -81,12 +83,12 @@ __global__ __launch_bounds__(256, 2) void compress_mfma(RowsDev rows, int Hkv, i
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     bf16x8* frag = (bf16x8*)smem_raw;       // [JB][4][2][64]
 
-    // part_last: the last block number is a partly filled one.  Its work-groups then start behind all others, where they fill up
-    // the compute units that the full ones leave; among them, a compute unit gets two full ones while the next gets two short ones
+    // ORDER_PART_LAST: the last block number is a partly filled one.  Its work-groups then start behind all others, where they fill
+    // up the compute units that the full ones leave; among them, a compute unit gets two full ones while the next gets two short ones
     // (16 x 16 heads x 600 rows, r = 32: 15.4 -> 11.8 us; 4 x 32 x 2100, r = 128: 43 -> 34.6; 1 x 32 x 16500, r = 64: 45.7 -> 41.6).
     int h = blockIdx.y, b = blockIdx.z, nx = gridDim.x, bx = blockIdx.x;
     bool rotate = true;
-    if (part_last) {
+    if (order == ORDER_PART_LAST) {
         const int id = bx + nx * (h + Hkv * b), full = --nx * (int)(gridDim.y * gridDim.z);
         rotate = id < full;
         const int w = rotate ? id / nx : id - full;
@@ -94,10 +96,12 @@ __global__ __launch_bounds__(256, 2) void compress_mfma(RowsDev rows, int Hkv, i
         b = __builtin_amdgcn_readfirstlane(w / Hkv);
         h = __builtin_amdgcn_readfirstlane(w - b * Hkv);
     }
-    // Work-groups go to the 8 XCDs round-robin by linear index.  An even count of blocks is rotated by head and batch item, so that
-    // an XCD does not end up with "block 7 of every sequence" (which only the longest sequences have); an odd one walks over the
-    // XCDs by itself, and rotated like that 9, 17, .. blocks would stand still.
-    if (rotate && !(nx & 1)) bx = (int)((unsigned)(bx + h + b) % (unsigned)nx);
+    // Work-groups go to the 8 XCDs round-robin by linear index.  The block number is rotated by head and batch item, so that
+    // an XCD does not end up with "block 7 of every sequence" (which only the longest sequences have); an odd count of blocks walks
+    // over the XCDs by itself, and rotated like that 9, 17, .. blocks would stand still.  ORDER_FEW: a compute unit for
+    // every work-group; rotated as the covariance kernel rotates its chunks, of 512 tokens as well for so few, the rows are
+    // in the L2 of the XCD that read them there (1 x 8 heads, 2410 kept of 4756 rows, fit and rotation 160.9 us, 169.9 otherwise).
+    if (rotate && (order == ORDER_FEW || !(nx & 1))) bx = (int)((unsigned)(bx + h + b) % (unsigned)nx);
     const int u = b * Hkv + h;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int g = lane >> 4, n = lane & 15;
@@ -488,14 +492,15 @@ __global__ __launch_bounds__(256) void unpack_cache(int cap, int r, const T* __r
 // tokens apart) 76 / 59; 1 x 16 x 32768 (33088 apart) 64 / 59.  With 1024: 56, 58, 62, 61, but 16 x 16 x 1536 ragged 41 / 30.
 template <int R>
 static hipError_t launch_compress_mfma_r(const RowsDev& rows, int B, int Hkv, int cap, int r, const float* Rr,
-                                         bf16_t* Kp, int32_t* seq_len_out, hipStream_t st)
+                                         bf16_t* Kp, int32_t* seq_len_out, int n_cu, hipStream_t st)
 {
     typedef CompressCfg<R> Cfg;
     int nblk = (rows.n_tokens + Cfg::TOK_PER_BLOCK - 1) / Cfg::TOK_PER_BLOCK;
     if (nblk < 1) nblk = 1;
-    const int part_last = nblk > 1 && rows.n_tokens % Cfg::TOK_PER_BLOCK != 0 && (int64_t)Hkv * B <= INT32_MAX / nblk;
+    const bool part = nblk > 1 && rows.n_tokens % Cfg::TOK_PER_BLOCK != 0 && (int64_t)Hkv * B <= INT32_MAX / nblk;
+    const int order = (int64_t)Hkv * B * nblk <= n_cu ? ORDER_FEW : part ? ORDER_PART_LAST : ORDER_MANY;
     const auto kernel = rows.tok_idx ? compress_mfma<R, true> : compress_mfma<R, false>;
-    hipLaunchKernelGGL(kernel, dim3(nblk, Hkv, B), dim3(256), Cfg::LDS_BYTES, st, rows, Hkv, cap, r, part_last, Rr, Kp, seq_len_out);
+    hipLaunchKernelGGL(kernel, dim3(nblk, Hkv, B), dim3(256), Cfg::LDS_BYTES, st, rows, Hkv, cap, r, order, Rr, Kp, seq_len_out);
     return hipGetLastError();
 }
 
@@ -512,19 +517,19 @@ static hipError_t launch_compress_f32_r(const RowsDev& rows, int B, int Hkv, int
 }
 
 hipError_t launch_compress(int dtype, bool mfma, const RowsDev& rows, int B, int Hkv, int cap, int r,
-                           const float* Rr, void* Kp, int32_t* seq_len_out, hipStream_t st)
+                           const float* Rr, void* Kp, int32_t* seq_len_out, int n_cu, hipStream_t st)
 {
     if (mfma && dtype == 1) {
         bf16_t* kp = (bf16_t*)Kp;
         switch (keep_padded(r)) {
-            case 16: return launch_compress_mfma_r<16>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, st);
-            case 32: return launch_compress_mfma_r<32>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, st);
-            case 48: return launch_compress_mfma_r<48>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, st);
-            case 64: return launch_compress_mfma_r<64>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, st);
-            case 80: return launch_compress_mfma_r<80>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, st);
-            case 96: return launch_compress_mfma_r<96>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, st);
-            case 112: return launch_compress_mfma_r<112>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, st);
-            case 128: return launch_compress_mfma_r<128>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, st);
+            case 16: return launch_compress_mfma_r<16>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, n_cu, st);
+            case 32: return launch_compress_mfma_r<32>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, n_cu, st);
+            case 48: return launch_compress_mfma_r<48>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, n_cu, st);
+            case 64: return launch_compress_mfma_r<64>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, n_cu, st);
+            case 80: return launch_compress_mfma_r<80>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, n_cu, st);
+            case 96: return launch_compress_mfma_r<96>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, n_cu, st);
+            case 112: return launch_compress_mfma_r<112>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, n_cu, st);
+            case 128: return launch_compress_mfma_r<128>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, n_cu, st);
             default: break;
         }
     }

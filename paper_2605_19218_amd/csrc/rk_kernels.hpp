@@ -42,7 +42,7 @@ hipError_t launch_gather_rotation(int U, int r, const float* R, const int32_t* k
 
 // ---- rk_compress.hip -------------------------------------------------------
 hipError_t launch_compress(int dtype, bool mfma, const RowsDev& rows, int B, int Hkv, int cap, int r,
-                           const float* Rr, void* Kp, int32_t* seq_len_out, hipStream_t st);
+                           const float* Rr, void* Kp, int32_t* seq_len_out, int n_cu, hipStream_t st);
 hipError_t launch_v_retile(int dtype, const RowsDev& rows, int B, int Hkv, int cap, void* dst, hipStream_t st);
 // tickets: B zero-initialised ints, left at zero on completion
 hipError_t launch_append(int dtype, int B, int Hkv, int cap, int r, const void* k_new, const void* v_new,

@@ -1,6 +1,6 @@
 """bf16 compress in blocks of 512 tokens: lengths around the passes (128 tokens) and blocks, equal, on the device or by token lists;
-block counts of either parity, with the last one full or partly filled (its work-groups then start behind the others), and heads
-that fill the device or not.  Against the oracle: one bf16 unit plus the accumulation bound, as everywhere in this suite."""
+block counts of either parity, with the last one full or partly filled, and more work-groups than compute units (a partly filled last
+block's then start behind the others) or fewer.  Against the oracle: one bf16 unit plus the accumulation bound, as everywhere in this suite."""
 import numpy as np
 import pytest
 import torch
@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("form", ["lengths", "lists", "equal"])
-@pytest.mark.parametrize("r,Hkv,L", [(37, 16, 1100), (128, 16, 1100), (64, 3, 520), (64, 3, 1024), (128, 3, 1536), (16, 3, 1600), (64, 3, 2100)])
+@pytest.mark.parametrize("r,Hkv,L", [
+    (37, 16, 1100), (128, 16, 1100), (64, 12, 520), (64, 12, 1024), (128, 6, 1536), (16, 6, 1600), (64, 6, 2100), (96, 3, 520), (48, 3, 1100)])
 def test_blocks(r, Hkv, L, form):
     lengths = [L, 1025, 1024, 513, 512, 511, 129, 1, 0] + [640] * 7 if form != "equal" else [L] * 16
     lengths = [min(n, L) for n in lengths]
