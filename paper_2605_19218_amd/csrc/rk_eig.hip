@@ -732,7 +732,7 @@ __global__ __launch_bounds__(256, 2) void eig_tri_vectors(int U, const double* _
 // (eight rounds of four dependent matrix steps, one exchange between the waves, eight more).  Four reflections at a time
 // on the vector unit: 20000 + 2500 for their inner products (LDS-bound, every lane group reads all of V), 23 us; one at a time
 // with loads where they are used: 56000 cycles in all, 27.7 us.  18 us for 32 matrices, 266 for 512 (547 at first);
-// with the ranks, R_r and the products with mu 20 and 287, for 5 less in eig_finish.
+// with the ranks, R_r and the products with mu 20 and 287, for 5 and 17 less in eig_finish (32 matrices gain, 512 lose 4 us by it).
 constexpr double EIG_ORTH_MAX = 3e-4;
 static_assert(0.75 * D * EIG_ORTH_MAX * EIG_ORTH_MAX <= 1e-5, "|R^T R - I| <= 1e-5, every column of E at its limit");
 constexpr int OB_LD = D + 2, OB_MLD = 17;

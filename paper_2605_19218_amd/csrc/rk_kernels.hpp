@@ -90,7 +90,7 @@ bool decode_append_fusable(int dtype, bool mfma, int Hq, int Hkv, int r);
 //                 bumped before the merge kernel reads it; text->max_len must already count the new row
 // tiles_all: 128-token tiles of the longest sequence, shared by the first Sv of the S splits; Sv < S (bf16 dual path only):
 //            the splits behind them take the text rows, which otherwise all splits share
-// ws: partials, (S (d + 2) + 1) floats per (b, h_q)
+// ws: partials, (S (d + 2) + 1) floats per (b, h_q); n_cu: compute units of the device
 // counters: n_counters ints that are zero between launches (or null): lets a plain matrix-core decode
 //           fold its partials inside the split launch (one counter per (b, h_kv, head group)).  Only
 //           valid on a device that deals work-groups to its XCDs round-robin by linear index
