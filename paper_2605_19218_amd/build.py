@@ -56,6 +56,8 @@ def build(verbose: bool = False) -> str:
     os.makedirs(objdir, exist_ok=True)
     common = [hipcc(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
               "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+              # the first 14 dwords of a kernel's arguments arrive in scalar registers with the wave, without a load
+              "-mllvm", "-amdgpu-kernarg-preload-count=16",
               "-Wno-unused-command-line-argument", "-Rpass-analysis=kernel-resource-usage",
               "-I", os.path.join(ROOT, "include"), "-I", CSRC]
     objs = [os.path.join(objdir, s.replace(".hip", ".o")) for s in SOURCES]

@@ -443,33 +443,35 @@ struct DecTile {
     bf16x8 vf[8];
 };
 
+// Addresses as a wave-uniform base and a 32-bit offset of the lane: the base stays in scalar registers, the loads take both, and
+// a tile costs no vector arithmetic.
 template <int R>
-__device__ __forceinline__ void load_tile_k(DecTile<R>& T, const bf16_t* __restrict__ Ku, int tok0, int lane)
+__device__ __forceinline__ void load_tile_k(DecTile<R>& T, const bf16_t* __restrict__ Ku, int tok0, uint32_t lane)
 {
-    const bf16_t* kb = Ku + (size_t)(tok0 >> 4) * (16 * R) + lane * 8;
+    const char* kb = (const char*)(Ku + (size_t)(tok0 >> 4) * (16 * R));
 #pragma unroll
     for (int tb = 0; tb < 2; ++tb) {
 #pragma unroll
-        for (int i = 0; i < DecTile<R>::NF; ++i) T.kf[tb][i] = __builtin_nontemporal_load((const bf16x8*)(kb + tb * 16 * R + i * 512));
+        for (int i = 0; i < DecTile<R>::NF; ++i)
+            T.kf[tb][i] = __builtin_nontemporal_load((const bf16x8*)(kb + 16 * lane + (tb * 32 * R + i * 1024)));
         if (DecTile<R>::TAIL) {
-            const int g = lane >> 4, n = lane & 15;
-            T.kt[tb] = *(const s16x4*)(Ku + (size_t)((tok0 >> 4) + tb) * (16 * R) +
-                                       (4 * DecTile<R>::NF + (g >> 1)) * 128 + n * 8 + 4 * (g & 1));
+            const uint32_t g = lane >> 4, n = lane & 15;
+            T.kt[tb] = *(const s16x4*)(kb + ((g >> 1) * 256 + n * 16 + 8 * (g & 1)) + (tb * 32 * R + DecTile<R>::NF * 1024));
         }
     }
 }
 
 template <int R>
-__device__ __forceinline__ void load_tile_v(DecTile<R>& T, const bf16_t* __restrict__ Vu, int tok0, int lane)
+__device__ __forceinline__ void load_tile_v(DecTile<R>& T, const bf16_t* __restrict__ Vu, int tok0, uint32_t lane)
 {
-    const bf16_t* vb = Vu + (size_t)(tok0 >> 5) * 4096 + lane * 8;
+    const char* vb = (const char*)(Vu + (size_t)(tok0 >> 5) * 4096);
 #pragma unroll
-    for (int cb = 0; cb < 8; ++cb) T.vf[cb] = __builtin_nontemporal_load((const bf16x8*)(vb + cb * 512));
+    for (int cb = 0; cb < 8; ++cb) T.vf[cb] = __builtin_nontemporal_load((const bf16x8*)(vb + 16 * lane + cb * 1024));
 }
 
 template <int R>
 __device__ __forceinline__ void load_tile(DecTile<R>& T, const bf16_t* __restrict__ Ku,
-                                          const bf16_t* __restrict__ Vu, int tok0, int lane)
+                                          const bf16_t* __restrict__ Vu, int tok0, uint32_t lane)
 {
     load_tile_k<R>(T, Ku, tok0, lane);
     load_tile_v<R>(T, Vu, tok0, lane);
@@ -485,51 +487,59 @@ __device__ __forceinline__ float load_past_l1(const float* p)
     return __hip_atomic_load(const_cast<float*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Fold of S partials (m, l, acc) for one (row, 8 channels) in ascending order, MC at a time: every
-// load of a chunk is issued before the first use, so a chunk costs one round trip to the L2.
-// T: storage type of the result.  An fp32 result has the bits that decode_merge gives it, whose products and sums are fused as written
-// here; where the choice is the compiler's it fuses the first term behind a rescale with the rescale, which moves last bits
-// from 17 partials on (bf16 results, 256 times as coarse, stay with that).
-// (The accumulators lie behind 2 S scalars a row: 8 bytes past a 16-byte boundary where the rows and S are odd.)
-template <int MC, typename T>
-__device__ __forceinline__ void fold_partials(const float* pm, const float* pl, const float* pa, int S, float& M,
-                                              float& den, f32x4& n0, f32x4& n1)
+// A value of lane K of each aligned group of 16, in all of them.
+template <int K>
+__device__ __forceinline__ float row16_bcast(float v)
+{
+    return dpp_mov_f32<0x150 + K>(v);
+}
+template <int K, int MC>
+__device__ __forceinline__ void fold_terms(const f32x4 (&a0)[MC], const f32x4 (&a1)[MC], float w, float l, float& den, f32x4& n0, f32x4& n1)
+{
+    if constexpr (K < MC) {
+        const float wk = row16_bcast<K>(w);
+        den = fmaf(row16_bcast<K>(l), wk, den);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            n0[e] = fmaf(a0[K][e], wk, n0[e]);
+            n1[e] = fmaf(a1[K][e], wk, n1[e]);
+        }
+        fold_terms<K + 1>(a0, a1, w, l, den, n0, n1);
+    }
+}
+// Fold of S partials (m, l, acc) of a row in ascending order, MC at a time, by 16 lanes: every load of a chunk is issued before the
+// first use, so a chunk costs one round trip to the L2.  A lane holds 8 channels, and m, l and the weight of one partial, which
+// the others take from it (each lane finding all weights for itself: twice the instructions, and they are what a short call waits for).
+// The products and sums are those of decode_merge, fused as written: an fp32 result has the bits that it gives.
+// pm, pl, pa: uniform; row, at: this lane's row and first channel behind them.  (The accumulators lie behind 2 S scalars a row: 8 bytes
+// past a 16-byte boundary where the rows and S are odd.)
+template <int MC>
+__device__ __forceinline__ void fold_partials(const float* pm, const float* pl, const float* pa, uint32_t row, uint32_t at, int S,
+                                              int lane16, float& M, float& den, f32x4& n0, f32x4& n1)
 {
     for (int i0 = 0; i0 < S; i0 += MC) {
         f32x4 a0[MC], a1[MC];
-        float mv[MC], lv[MC];
+        const int mine = min(i0 + min(lane16, MC - 1), S - 1);
+        float mv = load_past_l1(pm + (row + mine));
+        const float lv = load_past_l1(pl + (row + mine));
 #pragma unroll
         for (int k = 0; k < MC; ++k) {
-            const int i = min(i0 + k, S - 1);
-            a0[k] = *(const f32x4_any*)(pa + (size_t)i * D);
-            a1[k] = *(const f32x4_any*)(pa + (size_t)i * D + 4);
-            const float mi = load_past_l1(pm + i);
-            mv[k] = i0 + k < S ? mi : NEG_INF;
-            lv[k] = load_past_l1(pl + i);
+            const char* p = (const char*)pa + 4u * (at + (uint32_t)(min(i0 + k, S - 1) * D));
+            a0[k] = *(const f32x4_any*)p;
+            a1[k] = *(const f32x4_any*)(p + 16);
         }
-        float Mc = M;
-#pragma unroll
-        for (int k = 0; k < MC; ++k) Mc = fmaxf(Mc, mv[k]);
+        mv = lane16 < MC && i0 + lane16 < S ? mv : NEG_INF;
+        float Mc = mv;
+        Mc = fmaxf(Mc, dpp_mov_f32<0xB1>(Mc));               // (the lane permutations of row16_sum)
+        Mc = fmaxf(Mc, dpp_mov_f32<0x4E>(Mc));
+        Mc = fmaxf(Mc, dpp_mov_f32<0x141>(Mc));
+        Mc = fmaxf(fmaxf(Mc, dpp_mov_f32<0x140>(Mc)), M);
         if (Mc > NEG_INF) {
             const float resc = exp2f(M - Mc);                   // 0 on the first non-empty chunk
             den *= resc;
             n0 *= resc;
             n1 *= resc;
-#pragma unroll
-            for (int k = 0; k < MC; ++k) {
-                const float w = exp2f(mv[k] - Mc);              // 2^(-inf) = 0 for empty and absent partials
-                den = fmaf(lv[k], w, den);
-                if constexpr (std::is_same<T, float>::value) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        n0[e] = fmaf(a0[k][e], w, n0[e]);
-                        n1[e] = fmaf(a1[k][e], w, n1[e]);
-                    }
-                } else {
-                    n0 += a0[k] * w;
-                    n1 += a1[k] * w;
-                }
-            }
+            fold_terms<0>(a0, a1, exp2f(mv - Mc), lv, den, n0, n1);      // 2^(-inf) = 0 for empty and absent partials
             M = Mc;
         }
     }
@@ -548,8 +558,8 @@ __device__ __forceinline__ void fold_partials(const float* pm, const float* pl, 
 // i.e. has read the old length and is done with it.
 // T: storage type of the result (the appended token's Values are read as bf16: NEW comes with bf16 only).
 template <bool NEW, typename T>
-__device__ __forceinline__ void fold_unit(int unit, int S, int b, int u, int Hq, int h0, int Gc, const float* ws_m, const float* ws_l, const float* ws_acc,
-                                          T* __restrict__ out_merged, int32_t* done, bool bump,
+__device__ __forceinline__ void fold_unit(int unit, int S, int b, int u, size_t row0, int Gc, const float* ws_m, const float* ws_l, const float* ws_acc,
+                                          T* __restrict__ out, int32_t* done, bool bump,
                                           int32_t* batch_tickets, int batch_wgs, int32_t* len_rw, int len_cap,
                                           const float* snew, const bf16_t* __restrict__ v_new, int* sm_last)
 {
@@ -567,22 +577,23 @@ __device__ __forceinline__ void fold_unit(int unit, int S, int b, int u, int Hq,
     }
     __syncthreads();
     if (!*sm_last) return;
-    const int hh = tid >> 4, c0 = (tid & 15) * 8;           // thread = (head, 8 channels)
-    if (hh < Gc) {
-        const size_t row = (size_t)b * Hq + h0 + hh;
-        const float* pm = ws_m + row * S;
-        const float* pl = ws_l + row * S;
-        const float* pa = ws_acc + row * S * D + c0;
+    if (tid == 0) done[unit] = 0;                           // ready for the next launch on this context
+    const uint32_t hh = (uint32_t)tid >> 4, c0 = (tid & 15) * 8;         // thread = (head, 8 channels)
+    if (hh < (uint32_t)Gc) {
+        // (row0: the unit's first query head; addresses are a uniform base and a 32-bit offset of the thread)
+        const float *pm = ws_m + row0 * S, *pl = ws_l + row0 * S, *pa = ws_acc + row0 * S * D;
+        const uint32_t row = hh * S, at = row * D + c0;
         float M = NEG_INF, den = 0.f;
         f32x4 n0 = (f32x4){0.f, 0.f, 0.f, 0.f}, n1 = n0;
         float sx = NEG_INF;
         uint4 vraw = make_uint4(0, 0, 0, 0);
         if (NEW && snew) {                                   // the appended token: one more term of the softmax
-            sx = load_past_l1(snew + row);
+            sx = load_past_l1(snew + row0 + hh);
             vraw = *(const uint4*)(v_new + (size_t)u * D + c0);
         }
-        if (S <= 8) fold_partials<8, T>(pm, pl, pa, S, M, den, n0, n1);     // one round trip to the L2
-        else fold_partials<16, T>(pm, pl, pa, S, M, den, n0, n1);
+        if (S <= 4) fold_partials<4>(pm, pl, pa, row, at, S, tid & 15, M, den, n0, n1);
+        else if (S <= 8) fold_partials<8>(pm, pl, pa, row, at, S, tid & 15, M, den, n0, n1);
+        else fold_partials<16>(pm, pl, pa, row, at, S, tid & 15, M, den, n0, n1);
         if (NEW && sx > NEG_INF) {
             const float Mc = fmaxf(M, sx);
             const float resc = exp2f(M - Mc), w = exp2f(sx - Mc);
@@ -597,12 +608,12 @@ __device__ __forceinline__ void fold_unit(int unit, int S, int b, int u, int Hq,
             }
             M = Mc;
         }
+        T* o = out + row0 * D + (hh * D + c0);
         if constexpr (std::is_same<T, float>::value) {
-            f32x4_any* o = (f32x4_any*)(out_merged + row * D + c0);
             if (M > NEG_INF) { n0 /= den; n1 /= den; }
             else n0 = n1 = (f32x4){0.f, 0.f, 0.f, 0.f};
-            o[0] = n0;
-            o[1] = n1;
+            ((f32x4_any*)o)[0] = n0;
+            ((f32x4_any*)o)[1] = n1;
         } else {
             const float inv = (M > NEG_INF) ? 1.f / den : 0.f;
             uint4 pk;
@@ -610,12 +621,22 @@ __device__ __forceinline__ void fold_unit(int unit, int S, int b, int u, int Hq,
             pk.y = (uint32_t)f32_to_bf16(n0[2] * inv) | ((uint32_t)f32_to_bf16(n0[3] * inv) << 16);
             pk.z = (uint32_t)f32_to_bf16(n1[0] * inv) | ((uint32_t)f32_to_bf16(n1[1] * inv) << 16);
             pk.w = (uint32_t)f32_to_bf16(n1[2] * inv) | ((uint32_t)f32_to_bf16(n1[3] * inv) << 16);
-            *(uint4*)(out_merged + row * D + c0) = pk;
+            *(uint4*)o = pk;
         }
     }
-    __syncthreads();
-    if (tid == 0) done[unit] = 0;                           // ready for the next launch on this context
 }
+
+// The sizes of a matrix-core decode launch.
+struct DecodeShape {
+    int Hkv, cap, S;
+    int Sv;                       // splits of the cache: S, or fewer beside splits of text
+    int tiles_each, first_long;   // 128-token tiles of a split; the splits from first_long on have one more
+    int slab;                     // tokens from one (b, h_kv) to the next in the caches
+    float scale_log2;
+};
+// x / d for x, d < 2^16: x ceil(2^32 / d) / 2^32 exceeds x / d by less than x / 2^32 < 1 / d.  (d = 1 has no such product: rcp is 0.)
+static uint32_t rcp_of(int d) { return d == 1 ? 0u : (uint32_t)((0x100000000ull + d - 1) / d); }
+__device__ __forceinline__ int div_by(uint32_t x, uint32_t rcp) { return (int)(__umulhi(x, rcp) + (rcp ? 0u : x)); }
 
 template <int R>
 struct DecState {
@@ -668,25 +689,21 @@ __device__ __forceinline__ void compute_tile(DecTile<R>& T, DecState<R>& st, con
     }
     float mt = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])),
                      fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3])));
-    mt = fmaxf(mt, __shfl_xor(mt, 16));
-    mt = fmaxf(mt, __shfl_xor(mt, 32));
+    mt = groups_max(mt);
     const float m_new = fmaxf(st.m_run, mt);
     const float alpha = fast_exp2(st.m_run - m_new);
-    float psum = 0.f;
-    bf16x8 ph, pl;
+    float psum = 0.f, p[8];
 #pragma unroll
     for (int tb = 0; tb < 2; ++tb)
 #pragma unroll
         for (int ii = 0; ii < 4; ++ii) {
-            float p = fast_exp2(s[tb][ii] - m_new);
-            psum += p;
-            __bf16 hi, lo;
-            split_bf16(p, hi, lo);
-            ph[4 * tb + ii] = hi;
-            pl[4 * tb + ii] = lo;
+            p[4 * tb + ii] = fast_exp2(s[tb][ii] - m_new);
+            psum += p[4 * tb + ii];
         }
+    bf16x8 ph, pl;
+    split_bf16x8(p, ph, pl);
     st.l_run = fmaf(st.l_run, alpha, psum);
-    if (__any(m_new > st.m_run)) {
+    if (__any(m_new > st.m_run && st.m_run > NEG_INF)) {     // (nothing to rescale before a head's first score)
         // alpha lives in lanes (., n = head); the accumulators need alpha of heads 4 g + ii
         f32x4 a4;
 #pragma unroll
@@ -777,8 +794,7 @@ __device__ __forceinline__ void compute_text_tile(TextTile& T, const TextRows& x
     }
     float mt = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])),
                      fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3])));
-    mt = fmaxf(mt, __shfl_xor(mt, 16));
-    mt = fmaxf(mt, __shfl_xor(mt, 32));
+    mt = groups_max(mt);
     const float m_new = fmaxf(m_run, mt);
     const float m_ref = m_new > NEG_INF ? m_new : 0.f;       // every row so far may score -inf: no weight, not NaN
     const float alpha = exp2f(m_run - m_ref);
@@ -845,8 +861,7 @@ __device__ __forceinline__ void text_state(const TextRows& tr, int r0, int r1, c
         for (; row + 128 < r1; row += 128)
             compute_text_tile<true>(X, tr, m_run, l_run, O, qf, row, r1, row + 128, scale_log2, lane);
         compute_text_tile<false>(X, tr, m_run, l_run, O, qf, row, r1, 0, scale_log2, lane);
-        l_run += __shfl_xor(l_run, 16);
-        l_run += __shfl_xor(l_run, 32);
+        l_run = groups_sum(l_run);
         // channel 8 n + cb goes to where channel 16 cb' + n' of the visual layout lies
 #pragma unroll
         for (int cb = 0; cb < 8; ++cb) park[(n >> 1) * 64 + 16 * g + 8 * (n & 1) + cb] = O[cb];
@@ -907,20 +922,106 @@ __device__ __forceinline__ void text_split(const bf16_t* __restrict__ q, const T
     }
 }
 
+// The end of a work-group's part: the four waves' softmax states (with SHARED the four text states behind them), parked in LDS
+// as [state][channel block][lane (g, n)][head 4 g ..+3 of channel 16 cb + n], become one partial, or the result itself (`direct`).
+// GN: lane groups that hold heads, (Gc + 3) / 4 rounded to a power of two.  A thread takes two heads of a channel (GN = 1), four
+// (GN = 2) or four of two channels: every thread has outputs then, and the weights that it needs are fewer.  (One form for all, two
+// channels of four heads each: 1.0 us against 0.6, all of it instructions.)
+template <int GN, bool SHARED>
+__device__ __forceinline__ void merge_states(const float* big, const float (*sm_m)[16], const float (*sm_l)[16],
+                                             const float (*sbias)[16], int Gc, bool direct, bool empty, bf16_t* out, float* ws_m,
+                                             float* ws_l, float* ws_acc, size_t row0, int S, int split, int tid)
+{
+    constexpr int NST = SHARED ? 8 : 4, NH = GN == 1 ? 2 : 4, NC = GN == 4 ? 2 : 1;
+    typedef float vec __attribute__((ext_vector_type(NH)));
+    const int hb = GN == 1 ? 2 * (tid & 1) : GN == 2 ? 4 * (tid >> 7) : 4 * ((tid >> 4) & 3);
+    const uint32_t c = GN == 1 ? tid >> 1 : GN == 2 ? tid & 127 : 32 * (tid >> 6) + (tid & 15);
+    const float* from = big + (c >> 4) * 256 + (hb >> 2) * 64 + (c & 15) * 4 + (hb & 3);
+    vec pk[NC][NST], sw[NST], sl[NST], wgt[NST], Mh, lh;
+#pragma unroll
+    for (int w = 0; w < NST; ++w) {
+        sw[w] = *(const vec*)&sm_m[w][hb];
+        sl[w] = *(const vec*)&sm_l[w][hb];
+#pragma unroll
+        for (int k = 0; k < NC; ++k) pk[k][w] = *(const vec*)(from + w * 2048 + k * 256);
+    }
+    const vec sb = (*(const vec*)&sbias[0][hb] + *(const vec*)&sbias[1][hb]) + (*(const vec*)&sbias[2][hb] + *(const vec*)&sbias[3][hb]);
+#pragma unroll
+    for (int j = 0; j < NH; ++j) {
+        // Next to text scores the visual ones need their bias here; alone it is added to the stored maximum.  The waves are
+        // weighed against each other without it: a large bias would round their differences away.
+        const float Mv = fmaxf(fmaxf(sw[0][j], sw[1][j]), fmaxf(sw[2][j], sw[3][j]));
+        const float Mb = Mv > NEG_INF ? Mv + sb[j] : NEG_INF;
+        float M = Mb, f = 1.f;
+        if constexpr (SHARED) {
+            M = fmaxf(M, fmaxf(fmaxf(sw[4][j], sw[5][j]), fmaxf(sw[6][j], sw[7][j])));
+            f = Mv > NEG_INF ? exp2f(Mb - M) : 0.f;
+        }
+        Mh[j] = M;
+#pragma unroll
+        for (int w = 0; w < NST; ++w) {
+            const float x = w < 4 ? fast_exp2(sw[w][j] - Mv) : exp2f(sw[w][j] - M);
+            wgt[w][j] = sw[w][j] > NEG_INF ? (SHARED && w < 4 ? x * f : x) : 0.f;
+        }
+    }
+    lh = sl[0] * wgt[0];
+#pragma unroll
+    for (int w = 1; w < NST; ++w) lh += sl[w] * wgt[w];
+    vec acc[NC];
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+        acc[k] = pk[k][0] * wgt[0];
+#pragma unroll
+        for (int w = 1; w < NST; ++w) acc[k] += pk[k][w] * wgt[w];
+    }
+    if (direct) {
+        bf16_t* o = out + row0 * D;
+#pragma unroll
+        for (int j = 0; j < NH; ++j)
+            if (hb + j < Gc) {
+                // (an empty cache may stand beside text rows that all score -inf)
+                const bool none = SHARED ? !(Mh[j] > NEG_INF) : empty;
+#pragma unroll
+                for (int k = 0; k < NC; ++k) o[(uint32_t)((hb + j) * D) + c + 16 * k] = f32_to_bf16(none ? 0.f : acc[k][j] / lh[j]);
+            }
+    } else {
+        float* o = ws_acc + (row0 * S + split) * D;
+#pragma unroll
+        for (int j = 0; j < NH; ++j)
+            if (hb + j < Gc) {
+#pragma unroll
+                for (int k = 0; k < NC; ++k) o[(uint32_t)((hb + j) * S * D) + c + 16 * k] = acc[k][j];
+            }
+        if (c == 0) {
+#pragma unroll
+            for (int j = 0; j < NH; ++j)
+                if (hb + j < Gc) {
+                    (ws_m + row0 * S + split)[(uint32_t)((hb + j) * S)] = Mh[j];
+                    (ws_l + row0 * S + split)[(uint32_t)((hb + j) * S)] = lh[j];
+                }
+        }
+    }
+}
+
 // STEP = false is the plain decode; STEP = true adds the fused appends of a whole decode step;
 // TEXT adds the text attention of the dual path, to every split (TEXT_SHARED) or in splits of its own behind those of the
 // cache (TEXT_APART).  Each form is compiled separately, so the plain call, and the splits of the cache beside splits of
 // text, carry none of the others' branches.
-// Grid: (split, (h_kv, head group), b); one-dimensional with FUSED, see below.
+// Grid: (split, (h_kv, head group), b); (unit, split) with FUSED, see below.
+// What a short call spends is not memory but the instructions of one wave a SIMD (four to seven cycles each, 36 for a taken branch) and
+// round trips one behind the other.  So nothing here divides (the host passes reciprocals), addresses are uniform bases with
+// 32-bit lane offsets, the arguments that the first loads need come first (they are preloaded into scalar registers) and the others are
+// requested together behind those loads instead of one by one where they are used, seq_len is a vector load that is waited for behind the
+// q~ arithmetic (as a scalar one it held up every wait for an argument, and a branch on it every load above), and the states are
+// merged and folded in as few instructions as the number of heads allows.  Microseconds a launch, back to back, before and now:
+// 8 KV heads x 1024 tokens, r = 32 7.7 / 5.8; 32 x 2944, r = 64 12.4 / 10.9; 32 x 16384 (seven query heads each) 34.9 / 33.2.
 enum { TEXT_NONE = 0, TEXT_APART = 1, TEXT_SHARED = 2 };
 template <int R, bool STEP, int TEXT, bool FUSED>
 __global__ __launch_bounds__(256, 2) void decode_split_mfma(
-    const bf16_t* __restrict__ q, bf16_t* Kp, bf16_t* Vc, const float* __restrict__ Rr,
-    const float* __restrict__ dmu, const int32_t* seq_len, int Hq, int Hkv, int cap, int r, int tiles_all,
-    float scale_log2, float* ws_m, float* ws_l, float* ws_acc, int S,
-    bf16_t* __restrict__ out, const bf16_t* __restrict__ k_new, const bf16_t* __restrict__ v_new,
-    float* ws_snew, TextAppendDev ta, TextDev text, int Sv, int n_units,
-    bf16_t* __restrict__ out_merged, int32_t* done, int32_t* batch_tickets, int32_t* seq_len_rw)
+    const bf16_t* __restrict__ q, const float* __restrict__ Rr, const float* __restrict__ dmu, const int32_t* seq_len,
+    uint32_t r_ngrp, uint32_t g_units, uint32_t ngrp_rcp, uint32_t hkv_rcp, bf16_t* Kp, bf16_t* Vc, DecodeShape sh, float* ws_m, float* ws_l, float* ws_acc,
+    bf16_t* __restrict__ out, int32_t* done, const bf16_t* __restrict__ k_new, const bf16_t* __restrict__ v_new, float* ws_snew,
+    int32_t* batch_tickets, int32_t* seq_len_rw, TextAppendDev ta, TextDev text)
 {
     typedef DecTile<R> Tile;
     constexpr int NF = Tile::NF, NFA = Tile::NFA;
@@ -931,11 +1032,10 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
     constexpr int NST = SHARED ? 8 : 4;
     __shared__ __attribute__((aligned(16))) float big[NST * 16 * D];
     __shared__ __attribute__((aligned(16))) float qt[16][R + 4];     // rows 16 bytes apart in the banks: lanes of a wave index the row
-    __shared__ float sbias[16];
-    __shared__ __attribute__((aligned(16))) float sdm[D];
+    __shared__ __attribute__((aligned(16))) float sbias[4][16];      // a quarter of the channels each
     __shared__ __attribute__((aligned(16))) float sm_m[NST][16], sm_l[NST][16];
     __shared__ int sm_last;
-    const bool direct = out != nullptr;     // the only split of a single-path call writes the result itself
+    const bool direct = !FUSED && out != nullptr;     // the only split of a single-path call writes the result itself
     // Fused frozen-R append (k_new != NULL; the host guarantees G < 16 and never combines it
     // with `direct`): k_new rides through the q~ MFMAs as column 15, which the query heads
     // leave free, so k~_new = k_new R_r costs nothing.  Split 0 stores the new row (position
@@ -943,34 +1043,35 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
     // folds the partials: the merge kernel, which then also bumps the length, or with FUSED the
     // unit's last work-group (the length is bumped by the batch item's last work-group, see below).
     const bool app = STEP && k_new != nullptr;
-    const int G = Hq / Hkv;
-    const int ngrp = (G + 15) >> 4;
-    int split, by, b, unit = 0;
+    const int r = r_ngrp & 255, ngrp = r_ngrp >> 8, S = sh.S, cap = sh.cap, Hkv = sh.Hkv;
+    const float scale_log2 = sh.scale_log2;
+    int split, u, grp, b, unit = 0, G;
     if constexpr (FUSED) {
-        // One-dimensional grid.  Work-groups are dealt to the XCDs round-robin by their linear index, so
-        // index & 7 is this work-group's XCD: all S work-groups of a unit get the same XCD (unit = 8 ul + xcd)
+        // Work-groups are dealt to the XCDs round-robin by their linear index, and a row of the grid holds a multiple
+        // of 8 units, so unit mod 8 is this work-group's XCD: all S work-groups of a unit get the same XCD
         // and therefore share an L2, which is what lets the unit's last work-group read the others'
         // partials without any device-wide cache write-back (the host checks the deal once per context, see
-        // rk_create).  Units go fastest inside an XCD's slots, so every unit has work-groups among the first
-        // dispatched and among the last.
-        const int id = blockIdx.x, upx = (n_units + 7) >> 3, slot = id >> 3;
-        split = slot / upx;
-        unit = 8 * (slot % upx) + (id & 7);
-        if (unit >= n_units) return;
-        const int gy = Hkv * ngrp;
-        by = unit % gy;
-        b = unit / gy;
+        // rk_create).  Units go fastest, so every unit has work-groups among the first dispatched and among the last.
+        unit = blockIdx.x;
+        split = blockIdx.y;
+        G = g_units & 0xffff;
+        if (unit > (int)(g_units >> 16)) return;             // (the field holds the last unit)
+        u = div_by(unit, ngrp_rcp);
+        grp = unit - u * ngrp;
+        b = div_by(u, hkv_rcp);
     } else {
         split = blockIdx.x;
-        by = blockIdx.y;
         b = blockIdx.z;
+        G = g_units;
+        const int hk = div_by(blockIdx.y, ngrp_rcp);
+        grp = blockIdx.y - hk * ngrp;
+        u = b * Hkv + hk;
     }
-    const int hk = by / ngrp, grp = by - hk * ngrp;
-    const int h0 = hk * G + grp * 16;          // first query head of this group
     const int Gc = min(16, G - grp * 16);
-    const int u = b * Hkv + hk;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const size_t row0 = (size_t)u * G + grp * 16;            // first query row of this group
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, n = lane & 15;
+    __builtin_assume(wave >= 0 && wave < 4);
     // The split's text rows [r0, r1): whole 32-row tiles, shared by the splits behind the first Sv, which have no part of the
     // cache (TEXT_APART), or by all of them (TEXT_SHARED).  With an append text.max_len already counts the new row: the
     // caller's bound plus one.
@@ -980,8 +1081,9 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
         tr.stored = min(max(text_raw, 0), text.max_len);
         tr.add = ta.k != nullptr && text_raw >= 0 && text_raw < min(ta.capacity, text.max_len);
         tr.st = text.st;
-        tr.k = (const bf16_t*)text.k + (int64_t)b * text.sb + (int64_t)hk * text.sh;
-        tr.v = (const bf16_t*)text.v + (int64_t)b * text.sb + (int64_t)hk * text.sh;
+        const int64_t head = (int64_t)b * text.sb + (int64_t)(u - b * Hkv) * text.sh;
+        tr.k = (const bf16_t*)text.k + head;
+        tr.v = (const bf16_t*)text.v + head;
         tr.kn = tr.add ? (const bf16_t*)ta.k_new + (size_t)u * D : tr.k;
         tr.vn = tr.add ? (const bf16_t*)ta.v_new + (size_t)u * D : tr.v;
         const int rows = tr.stored + (tr.add ? 1 : 0), per = ((rows + 31) / 32 + cnt - 1) / cnt * 32;
@@ -990,18 +1092,18 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
     };
     // the first work-group with text rows stores the appended one
     auto store_row = [&]() {
-        if (tr.add && r0 == 0 && r1 > 0 && grp == 0 && tid < 16) text_store_row(tr, ta, b, hk, tid);
+        if (tr.add && r0 == 0 && r1 > 0 && grp == 0 && tid < 16) text_store_row(tr, ta, b, u - b * Hkv, tid);
     };
     if constexpr (TEXT == TEXT_APART) {
         // no part of the cache: nothing of what follows is needed (marked unlikely, so that the cache's code stays in line)
-        if (__builtin_expect(split >= Sv, 0)) {
-            text_share(text.len ? text.len[b] : text.max_len, split - Sv, S - Sv);
-            text_split(q, tr, r0, r1, (size_t)b * Hq + h0, Gc, split, S, scale_log2, (f32x4*)big, sm_m, sm_l, ws_m, ws_l,
+        if (__builtin_expect(split >= sh.Sv, 0)) {
+            text_share(text.len ? text.len[b] : text.max_len, split - sh.Sv, S - sh.Sv);
+            text_split(q, tr, r0, r1, row0, Gc, split, S, scale_log2, (f32x4*)big, sm_m, sm_l, ws_m, ws_l,
                        ws_acc, tid);
             store_row();
         }
     }
-    if (TEXT != TEXT_APART || __builtin_expect(split < Sv, 1)) {
+    if (TEXT != TEXT_APART || __builtin_expect(split < sh.Sv, 1)) {
         // ---- everything that does not need seq_len goes out first -----------------------------
         // The sequence length costs a cold round trip to memory; the prologue operands (q, this
         // thread's R_r pieces, delta_mu) and the first tile of every wave are requested before
@@ -1009,49 +1111,60 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
         // checks that the tile lies inside the cache slab; rows past the real end are masked or
         // skipped later (the prologue is on the kernel's critical path: while it runs only the
         // prefetched tiles keep the memory system busy).
-        const int seq_raw = seq_len[b];
-        const int text_raw = SHARED ? (text.len ? text.len[b] : text.max_len) : 0;
-        // balanced partition of the 128-token tiles: the LAST (tiles % S) splits get one tile more (the
-        // final tile of a cache is usually only partly filled, so the longer shares belong at the end)
-        // (with TEXT_APART the cache is left to the first Sv splits)
-        const int nv = TEXT == TEXT_APART ? Sv : S;
-        const int tp = tiles_all / nv, trem = tiles_all - tp * nv;
-        const int t0 = 128 * (split * tp + max(split - (nv - trem), 0));
-        const int t1_full = 128 * ((split + 1) * tp + max(split + 1 - (nv - trem), 0));
-        const bf16_t* Ku = Kp + (size_t)u * slab_tokens(cap) * R;
-        const bf16_t* Vu = Vc + (size_t)u * slab_tokens(cap) * D;
-
         // prologue operands, in matrix-core layout (lane (g, n)):
         //   qfrag[i]     B operand: q of head n, channels 32 i + 8 g ..+7 (q is bf16: exact);
         //   ra[bw][i][.] A operand: R_r^T block jb = wave + 4 bw: column 16 jb + n of R_r, the same
         //                channels (fp32, split into a bf16 head + remainder pair before use);
+        //   qb, dm0, dm1 this wave's quarter of the bias: q and delta_mu, channels 32 wave + 8 g ..+7.
         constexpr int NJB = R / 16;                    // 16-column blocks of R_r
         constexpr int NBW = (NJB + 3) / 4;             // blocks per wave
         const float* Ru = Rr + (size_t)u * D * r;
-        bf16x8 qfrag[4];
+        bf16x8 qfrag[4], qb;
         float ra[NBW][4][8];
-        float dmv;                                     // delta_mu goes through LDS (one value per thread)
+        f32x4 dm0, dm1;
+        int seq_raw, text_raw = 0;
         {
             // Every load below is unconditional (indices clamped, the value discarded afterwards): a load
             // under a per-lane condition compiles to a branch, and past a branch the compiler no longer knows
             // how many loads are outstanding, so the first use of R_r would wait for the tile prefetch too
             // (a round trip to HBM under full load instead of an L2 hit).
-            const bool newcol = app && n == 15;
-            const bf16_t* qrow = newcol ? k_new + (size_t)u * D + 8 * g
-                                        : q + ((size_t)b * Hq + h0 + min(n, Gc - 1)) * D + 8 * g;
+            uint32_t zero = 0;
+            asm volatile("" : "+v"(zero));             // (keeps the length a vector load)
+            seq_raw = *(const int32_t*)((const char*)(seq_len + b) + zero);
+            // Columns of heads that do not exist repeat the last head's: nothing reads their results.
+            const char* qrow = (const char*)(q + row0 * D) + (uint32_t)(256 * min(n, Gc - 1) + 16 * g);
+            if (STEP && app && n == 15) qrow = (const char*)(k_new + (size_t)u * D) + 16 * g;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) qfrag[i] = *(const bf16x8*)(qrow + 32 * i);
+            for (int i = 0; i < 4; ++i) qfrag[i] = *(const bf16x8*)(qrow + 64 * i);
+            qb = *(const bf16x8*)(qrow + 64 * wave);
 #pragma unroll
             for (int bw = 0; bw < NBW; ++bw) {
-                const int col = min(16 * (wave + 4 * bw) + n, r - 1);
+                uint32_t at = 4u * (8 * g * r + min(16 * (wave + 4 * bw) + n, r - 1));
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < 4; ++i) {
 #pragma unroll
-                    for (int jj = 0; jj < 8; ++jj) ra[bw][i][jj] = Ru[(32 * i + 8 * g + jj) * r + col];
+                    for (int jj = 0; jj < 8; ++jj) {
+                        ra[bw][i][jj] = *(const float*)((const char*)Ru + at);
+                        at += 4u * (jj < 7 ? r : 25 * r);
+                    }
+                }
             }
-            const float* dp = dmu ? dmu + (size_t)u * D : Ru;     // any readable address when there is no bias
-            dmv = dp[tid & (D - 1)];
+            const float* dp = (dmu ? dmu + (size_t)u * D : Ru) + 32 * wave;     // any readable address when there is no bias
+            dm0 = *(const f32x4_any*)(dp + 8 * g);
+            dm1 = *(const f32x4_any*)(dp + 8 * g + 4);
+            // from here on the other arguments are wanted: requested together, they are one round trip
+            asm volatile("" :: "s"(ws_m), "s"(ws_l), "s"(ws_acc), "s"(out), "s"(S), "s"(Vc), "s"(cap));
+            if constexpr (FUSED) asm volatile("" :: "s"(done));
+            __builtin_amdgcn_sched_barrier(0);
+            if (SHARED) text_raw = *(const int32_t*)((const char*)(text.len ? text.len + b : seq_len + b) + zero);
         }
+        // balanced partition of the 128-token tiles: the LAST (tiles % splits) splits get one tile more (the
+        // final tile of a cache is usually only partly filled, so the longer shares belong at the end)
+        // (with TEXT_APART the cache is left to the first Sv splits)
+        const int t0 = 128 * (split * sh.tiles_each + max(split - sh.first_long, 0));
+        const int t1_full = 128 * ((split + 1) * sh.tiles_each + max(split + 1 - sh.first_long, 0));
+        const bf16_t* Ku = Kp + (size_t)u * sh.slab * R;
+        const bf16_t* Vu = Vc + (size_t)u * sh.slab * D;
 
         Tile TA, TB;
 #pragma unroll
@@ -1082,74 +1195,66 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
         if constexpr (V_LATE) load_tile_k<R>(TA, Ku, okA ? tokA : 0, okA ? lane : 0);
         else load_tile<R>(TA, Ku, Vu, okA ? tokA : 0, okA ? lane : 0);
 
-        const int L = min(max(seq_raw, 0), cap);
-        const int t1 = min(t1_full, L);
-        const bool empty = t0 >= t1;
-        const bool app_here = app && split == 0;       // this work-group stores and scores the new row
-        const bool app_ok = seq_raw >= 0 && seq_raw < cap;
-        if constexpr (SHARED) text_share(text_raw, split, S);
-
-        if (!empty || app_here || (SHARED && r0 < r1)) {
-            const int ntiles = (t1 - t0 + 31) >> 5;
-            const int nk = (ntiles - wave + 3) >> 2;
-
+        {
             // ---- q~ = q R_r scaled into the log2 domain, and the bias ----------------------
             // On the matrix cores: D[j][h] = sum_c R_r[c][j] q[h][c], one 16-column block of R_r per
             // wave and pass, R_r as bf16 head + remainder (two MFMAs per 32 channels).  Lane (g, n)
             // ends up with q~[head n][16 jb + 4 g + 0..3]: one 16-byte store to LDS, one barrier.
             {
-                // discard what the clamped prologue loads fetched for heads and columns that do not exist
-                if (!(n < Gc || (app && n == 15))) {
+                // discard what the clamped prologue loads fetched for columns that do not exist
+                if (r < R) {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) qfrag[i] = (bf16x8){0, 0, 0, 0, 0, 0, 0, 0};
+                    for (int bw = 0; bw < NBW; ++bw)
+                        if (16 * (wave + 4 * bw) + n >= r) {
+#pragma unroll
+                            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                                for (int jj = 0; jj < 8; ++jj) ra[bw][i][jj] = 0.f;
+                        }
                 }
-#pragma unroll
-                for (int bw = 0; bw < NBW; ++bw)
-                    if (16 * (wave + 4 * bw) + n >= r) {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i)
-#pragma unroll
-                            for (int jj = 0; jj < 8; ++jj) ra[bw][i][jj] = 0.f;
-                    }
-                if (tid < D) sdm[tid] = dmu ? dmv : 0.f;
 #pragma unroll
                 for (int bw = 0; bw < NBW; ++bw) {
                     const int jb = wave + 4 * bw;
                     if (jb < NJB) {
-                        f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f};
+                        f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f}, acl = acc;
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
                             bf16x8 ah, al;
-#pragma unroll
-                            for (int jj = 0; jj < 8; ++jj) {
-                                __bf16 hi, lo;
-                                split_bf16(ra[bw][i][jj], hi, lo);
-                                ah[jj] = hi;
-                                al[jj] = lo;
-                            }
+                            split_bf16x8(ra[bw][i], ah, al);
                             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, qfrag[i], acc, 0, 0, 0);
-                            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, qfrag[i], acc, 0, 0, 0);
+                            acl = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, qfrag[i], acl, 0, 0, 0);
                         }
-                        *(f32x4*)&qt[n][16 * jb + 4 * g] = acc * ((app && n == 15) ? 1.f : scale_log2);
+                        *(f32x4*)&qt[n][16 * jb + 4 * g] = (acc + acl) * ((app && n == 15) ? 1.f : scale_log2);
                     }
                 }
             }
-            __syncthreads();
-            if (wave == 0) {                           // bias b_n = q_n . delta_mu, needed only at the end
-                float bpart = 0.f;
+            // bias b_n = q_n . delta_mu, a quarter of the channels per wave, needed only at the end
+            float bpart;
+            {
+                float b0 = 0.f, b1 = 0.f;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const f32x4 d0 = *(const f32x4*)&sdm[32 * i + 8 * g], d1 = *(const f32x4*)&sdm[32 * i + 8 * g + 4];
-#pragma unroll
-                    for (int jj = 0; jj < 4; ++jj) {
-                        bpart = fmaf((float)qfrag[i][jj], d0[jj], bpart);
-                        bpart = fmaf((float)qfrag[i][jj + 4], d1[jj], bpart);
-                    }
+                for (int jj = 0; jj < 4; ++jj) {
+                    b0 = fmaf((float)qb[jj], dm0[jj], b0);
+                    b1 = fmaf((float)qb[jj + 4], dm1[jj], b1);
                 }
-                bpart += __shfl_xor(bpart, 16);
-                bpart += __shfl_xor(bpart, 32);
-                if (g == 0) sbias[n] = bpart * scale_log2;
-                if (app_here) {
+                bpart = dmu ? groups_sum(b0 + b1) * scale_log2 : 0.f;
+                if (g == 0) sbias[wave][n] = bpart;
+            }
+            lds_barrier();
+            // the length: a round trip that everything above has hidden
+            seq_raw = __builtin_amdgcn_readfirstlane(seq_raw);
+            if constexpr (SHARED) {
+                text_raw = text.len ? __builtin_amdgcn_readfirstlane(text_raw) : text.max_len;
+                text_share(text_raw, split, S);
+            }
+            const int t1 = min(t1_full, min(max(seq_raw, 0), cap));
+            const bool empty = t0 >= t1;                   // (it goes the same way, without a tile)
+            const int ntiles = (t1 - t0 + 31) >> 5;
+            const int nk = (ntiles - wave + 3) >> 2;
+            const bool app_here = app && split == 0;       // this work-group stores and scores the new row
+            const bool app_ok = seq_raw >= 0 && seq_raw < cap;
+            if (app_here) {
+                if (wave == 0) {
                     // score of the new row against every head, with the row rounded to storage
                     // precision exactly as later steps will read it
                     float sp = 0.f;
@@ -1159,18 +1264,17 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
 #pragma unroll
                         for (int e = 0; e < 4; ++e) sp = fmaf(a[e], bf16_to_f32(f32_to_bf16(kx[e])), sp);
                     }
-                    sp += __shfl_xor(sp, 16);
-                    sp += __shfl_xor(sp, 32);
-                    if (g == 0 && n < Gc)
-                        ws_snew[(size_t)b * Hq + h0 + n] = app_ok ? fmaf(bpart, scale_log2, sp) : NEG_INF;
-                }
-            } else if (app_here && app_ok && grp == 0) {
-                if (wave == 1) {
-                    for (int j = lane; j < R; j += 64)
-                        Kp[(size_t)u * slab_tokens(cap) * R + kidx(seq_raw, j, R)] = f32_to_bf16(qt[15][j]);
-                } else {
-                    const int c = tid - 128;
-                    Vc[(size_t)u * slab_tokens(cap) * D + vidx(seq_raw, c)] = v_new[(size_t)u * D + c];
+                    sp = groups_sum(sp);
+                    const float bias = (sbias[0][n] + sbias[1][n]) + (sbias[2][n] + sbias[3][n]);
+                    if (g == 0 && n < Gc) ws_snew[row0 + n] = app_ok ? bias + sp : NEG_INF;
+                } else if (app_ok && grp == 0) {
+                    if (wave == 1) {
+                        for (int j = lane; j < R; j += 64)
+                            Kp[(size_t)u * sh.slab * R + kidx(seq_raw, j, R)] = f32_to_bf16(qt[15][j]);
+                    } else {
+                        const int c = tid - 128;
+                        Vc[(size_t)u * sh.slab * D + vidx(seq_raw, c)] = v_new[(size_t)u * D + c];
+                    }
                 }
             }
 
@@ -1194,13 +1298,10 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
             }
 #pragma unroll
             for (int i = 0; i < NF; ++i) {
-#pragma unroll
-                for (int jj = 0; jj < 8; ++jj) {
-                    __bf16 hi, lo;
-                    split_bf16(qt[n][32 * i + 8 * g + jj], hi, lo);
-                    qh[i][jj] = hi;
-                    ql[i][jj] = lo;
-                }
+                float x[8];
+                *(f32x4*)x = *(const f32x4*)&qt[n][32 * i + 8 * g];
+                *(f32x4*)(x + 4) = *(const f32x4*)&qt[n][32 * i + 8 * g + 4];
+                split_bf16x8(x, qh[i], ql[i]);
             }
             if (TAIL) {
 #pragma unroll
@@ -1241,86 +1342,22 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
             // lane parks its 8 accumulator quads in LDS ([wave][cb][lane], 128-bit, conflict
             // free); wave w then folds channel blocks 2w, 2w+1 of all four waves and stores the
             // result straight from the MFMA layout (lane (g, n): heads 4g..4g+3, channel 16cb+n).
-            float l_run = st.l_run;
-            l_run += __shfl_xor(l_run, 16);
-            l_run += __shfl_xor(l_run, 32);
+            const float l_run = groups_sum(st.l_run);
+            if (4 * g < Gc) {
 #pragma unroll
-            for (int cb = 0; cb < 8; ++cb) park[(wave * 8 + cb) * 64 + lane] = st.O[cb];
+                for (int cb = 0; cb < 8; ++cb) park[(wave * 8 + cb) * 64 + lane] = st.O[cb];
+            }
             if (g == 0) { sm_m[wave][n] = st.m_run; sm_l[wave][n] = l_run; }
-            __syncthreads();
-
-            f32x4 wgt[NST];                            // weight of state w for heads 4g + ii
-            f32x4 Mh, lh = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ii = 0; ii < 4; ++ii) {
-                const int hh = 4 * g + ii;
-                // Next to text scores the visual ones need their bias here; alone it is added to the stored maximum.  The waves are
-                // weighed against each other without it: a large bias would round their differences away.
-                const float Mv = fmaxf(fmaxf(sm_m[0][hh], sm_m[1][hh]), fmaxf(sm_m[2][hh], sm_m[3][hh])), Mb = Mv + sbias[hh];
-                float M = Mb, f = 1.f;
-                if constexpr (SHARED) {
-                    M = fmaxf(M, fmaxf(fmaxf(sm_m[4][hh], sm_m[5][hh]), fmaxf(sm_m[6][hh], sm_m[7][hh])));
-                    f = Mv > NEG_INF ? exp2f(Mb - M) : 0.f;
-                }
-                Mh[ii] = M;
-#pragma unroll
-                for (int w = 0; w < NST; ++w) {
-                    const float mw = sm_m[w][hh];
-                    float x = 0.f;
-                    if (mw > NEG_INF) x = w < 4 ? fast_exp2(mw - Mv) : exp2f(mw - M);
-                    if (SHARED && w < 4) x *= f;
-                    wgt[w][ii] = x;
-                    lh[ii] = fmaf(sm_l[w][hh], x, lh[ii]);
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const int cb = 2 * wave + k;
-                f32x4 acc = park[(0 * 8 + cb) * 64 + lane] * wgt[0];
-#pragma unroll
-                for (int w = 1; w < NST; ++w) acc += park[(w * 8 + cb) * 64 + lane] * wgt[w];
-#pragma unroll
-                for (int ii = 0; ii < 4; ++ii) {
-                    const int hh = 4 * g + ii;
-                    if (hh < Gc) {
-                        const size_t row = (size_t)b * Hq + h0 + hh;
-                        const int c = 16 * cb + n;
-                        // (an empty cache may stand beside text rows that all score -inf)
-                        if (direct) out[row * D + c] = f32_to_bf16(SHARED && !(Mh[ii] > NEG_INF) ? 0.f : acc[ii] / lh[ii]);
-                        else ws_acc[(row * S + split) * D + c] = acc[ii];
-                    }
-                }
-            }
-            if (!direct && wave == 0 && n == 0) {        // lanes (g, 0): m and l of heads 4g..4g+3
-#pragma unroll
-                for (int ii = 0; ii < 4; ++ii) {
-                    const int hh = 4 * g + ii;
-                    if (hh < Gc) {
-                        const size_t pidx = ((size_t)b * Hq + h0 + hh) * S + split;
-                        ws_m[pidx] = Mh[ii];
-                        ws_l[pidx] = lh[ii];
-                    }
-                }
-            }
-        } else {
-            // ---- empty split: zeros with m = -inf (or zeros to `out` if it is the only split) ----
-            for (int idx = tid; idx < Gc * D; idx += 256) {
-                int hh = idx >> 7, c = idx & 127;
-                const size_t row = (size_t)b * Hq + h0 + hh;
-                if (out != nullptr) {
-                    out[row * D + c] = f32_to_bf16(0.f);
-                } else {
-                    const size_t pidx = row * S + split;
-                    ws_acc[pidx * D + c] = 0.f;
-                    if (c == 0) { ws_m[pidx] = NEG_INF; ws_l[pidx] = 0.f; }
-                }
-            }
+            lds_barrier();
+            if (Gc <= 4) merge_states<1, SHARED>((const float*)big, sm_m, sm_l, sbias, Gc, direct, empty, out, ws_m, ws_l, ws_acc, row0, S, split, tid);
+            else if (Gc <= 8) merge_states<2, SHARED>((const float*)big, sm_m, sm_l, sbias, Gc, direct, empty, out, ws_m, ws_l, ws_acc, row0, S, split, tid);
+            else merge_states<4, SHARED>((const float*)big, sm_m, sm_l, sbias, Gc, direct, empty, out, ws_m, ws_l, ws_acc, row0, S, split, tid);
         }
     }
 
     if constexpr (FUSED) {
         const bool bump = STEP ? app : (TEXT && ta.k != nullptr);
-        fold_unit<STEP>(unit, S, b, u, Hq, h0, Gc, ws_m, ws_l, ws_acc, out_merged, done, bump, batch_tickets,
+        fold_unit<STEP>(unit, S, b, u, row0, Gc, ws_m, ws_l, ws_acc, out, done, bump, batch_tickets,
                         Hkv * ngrp * S, STEP ? seq_len_rw : ta.len, STEP ? cap : min(ta.capacity, text.max_len),
                         STEP && app ? ws_snew : nullptr, v_new, &sm_last);
     }
@@ -1379,8 +1416,7 @@ __device__ __forceinline__ void compute_tile_f32(DecTileF32<R>& T, float& m_run,
             }
     }
     float mt = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
-    mt = fmaxf(mt, __shfl_xor(mt, 16));
-    mt = fmaxf(mt, __shfl_xor(mt, 32));
+    mt = groups_max(mt);
     const float m_new = fmaxf(m_run, mt);
     const float m_ref = m_new > NEG_INF ? m_new : 0.f;       // every row so far may score -inf: no weight, not NaN
     const float alpha = exp2f(m_run - m_ref);
@@ -1527,8 +1563,7 @@ __global__ __launch_bounds__(256, 2) void decode_split_f32(
         if (k + 2 < nk) compute_tile_f32<R>(TA, m_run, l_run, O, qb, tokA + 64 * (k + 2), t1, g);
 
         // merge the four waves' states, lane to lane (all hold O in one layout: heads 4 g + ii, channel 16 cb + n)
-        l_run += __shfl_xor(l_run, 16);
-        l_run += __shfl_xor(l_run, 32);
+        l_run = groups_sum(l_run);
 #pragma unroll
         for (int cb = 0; cb < 8; ++cb) park[(wave * 8 + cb) * 64 + lane] = O[cb];
         if (g == 0) { sm_m[wave][n] = m_run; sm_l[wave][n] = l_run; }
@@ -1571,7 +1606,7 @@ __global__ __launch_bounds__(256, 2) void decode_split_f32(
         }
     }
     if constexpr (FUSED)
-        fold_unit<false>(unit, S, b, u, Hq, h0, Gc, ws_m, ws_l, ws_acc, out_merged, done, false, nullptr, 0, nullptr, 0, nullptr,
+        fold_unit<false>(unit, S, b, u, (size_t)b * Hq + h0, Gc, ws_m, ws_l, ws_acc, out_merged, done, false, nullptr, 0, nullptr, 0, nullptr,
                          nullptr, &sm_last);
 }
 
@@ -1600,22 +1635,21 @@ static bool fold_pays_f32(int nunit, int S, int tiles_all, int r, int n_cu)
 bool decode_mfma_supported(int dtype, int r) { return dtype == 1 && r >= 1 && r <= 128; }
 
 template <int R>
-static void launch_decode_mfma_r(dim3 grid, hipStream_t st, const bf16_t* q, bf16_t* Kp, bf16_t* Vc,
-                                 const float* Rr, const float* dmu, const int32_t* seq_len, int Hq, int Hkv, int cap,
-                                 int r, int tiles_all, float sl2, float* m, float* l, float* acc, int S, bf16_t* out,
+static void launch_decode_mfma_r(bool fused, dim3 grid, hipStream_t st, const bf16_t* q, bf16_t* Kp, bf16_t* Vc,
+                                 const float* Rr, const float* dmu, const int32_t* seq_len, uint32_t r_ngrp, uint32_t g_units,
+                                 uint32_t ngrp_rcp, uint32_t hkv_rcp, const DecodeShape& sh, float* m, float* l, float* acc, bf16_t* out,
                                  const bf16_t* k_new, const bf16_t* v_new, float* snew, const TextAppendDev& ta,
-                                 const TextDev& text, int Sv, int n_units, bf16_t* out_merged, int32_t* done,
-                                 int32_t* batch_tickets, int32_t* seq_len_rw)
+                                 const TextDev& text, int32_t* done, int32_t* batch_tickets, int32_t* seq_len_rw)
 {
 #define RK_FORM(STEP, TEXT, FUSED)                                                                                     \
-    hipLaunchKernelGGL((decode_split_mfma<R, STEP, TEXT, FUSED>), grid, dim3(256), 0, st, q, Kp, Vc, Rr, dmu, seq_len, Hq, \
-                       Hkv, cap, r, tiles_all, sl2, m, l, acc, S, out, k_new, v_new, snew, ta, text, Sv, n_units,       \
-                       out_merged, done, batch_tickets, seq_len_rw)
-    if (out_merged && text.k && Sv < S) RK_FORM(false, TEXT_APART, true);
-    else if (out_merged && text.k) RK_FORM(false, TEXT_SHARED, true);
-    else if (out_merged && k_new) RK_FORM(true, TEXT_NONE, true);
-    else if (out_merged) RK_FORM(false, TEXT_NONE, true);
-    else if (text.k && Sv < S) RK_FORM(false, TEXT_APART, false);
+    hipLaunchKernelGGL((decode_split_mfma<R, STEP, TEXT, FUSED>), grid, dim3(256), 0, st, q, Rr, dmu, seq_len, r_ngrp, g_units, \
+                       ngrp_rcp, hkv_rcp, Kp, Vc, sh, m, l, acc, out, done, k_new, v_new, snew, batch_tickets, seq_len_rw, ta, text)
+    const bool apart = text.k && sh.Sv < sh.S;
+    if (fused && apart) RK_FORM(false, TEXT_APART, true);
+    else if (fused && text.k) RK_FORM(false, TEXT_SHARED, true);
+    else if (fused && k_new) RK_FORM(true, TEXT_NONE, true);
+    else if (fused) RK_FORM(false, TEXT_NONE, true);
+    else if (apart) RK_FORM(false, TEXT_APART, false);
     else if (text.k) RK_FORM(false, TEXT_SHARED, false);
     else if (k_new) RK_FORM(true, TEXT_NONE, false);
     else RK_FORM(false, TEXT_NONE, false);
@@ -1653,7 +1687,10 @@ hipError_t launch_decode(int dtype, bool mfma, int B, int Hq, int Hkv, int cap, 
         dim3 grid(S, Hkv * ngrp, B);                    // (split, (h_kv, head group), b)
         const bool fused_merge = ((!app && !tapp) || batch_tickets) && (S >= 2 || tapp) && counters && nunit <= n_counters &&
                                  fold_pays(nunit, tiles_all, r, 2);
-        if (fused_merge) grid = dim3((unsigned)(8 * ((nunit + 7) / 8) * S));
+        if (fused_merge) grid = dim3((unsigned)(8 * ((nunit + 7) / 8)), (unsigned)S);
+        const int nv = text && Sv < S ? Sv : S;
+        const DecodeShape sh{Hkv, cap, S, Sv, tiles_all / nv, nv - tiles_all % nv, (int)slab_tokens(cap), sl2};
+        const uint32_t r_ngrp = (uint32_t)r | (uint32_t)ngrp << 8, g_units = (uint32_t)G | (fused_merge ? (uint32_t)(nunit - 1) << 16 : 0u);
         const bf16_t* q_ = (const bf16_t*)q;
         // the caches are written only by a fused append, whose caller handed them over writable
         bf16_t *k_ = const_cast<bf16_t*>((const bf16_t*)Kp), *v_ = const_cast<bf16_t*>((const bf16_t*)Vc);
@@ -1662,10 +1699,10 @@ hipError_t launch_decode(int dtype, bool mfma, int B, int Hq, int Hkv, int cap, 
         const TextDev tx = text ? *text : TextDev{};
 #define RK_CASE(RV)                                                                                        \
     case RV:                                                                                               \
-        launch_decode_mfma_r<RV>(grid, st, q_, k_, v_, Rr, dmu, seq_len, Hq, Hkv, cap, r, tiles_all, sl2, ws_m,   \
-                                 ws_l, ws_acc, S, direct ? (bf16_t*)out : nullptr, kn, vn, ws_snew, ta, tx, Sv, nunit, \
-                                 fused_merge ? (bf16_t*)out : nullptr, counters, batch_tickets,     \
-                                 app ? app->seq_len : nullptr);                                            \
+        launch_decode_mfma_r<RV>(fused_merge, grid, st, q_, k_, v_, Rr, dmu, seq_len, r_ngrp, g_units, rcp_of(ngrp), \
+                                 rcp_of(Hkv), sh, ws_m, ws_l, ws_acc, \
+                                 fused_merge || direct ? (bf16_t*)out : nullptr, kn, vn, ws_snew, ta, tx, counters,       \
+                                 batch_tickets, app ? app->seq_len : nullptr);                              \
         break;
         switch (keep_padded(r)) {
             RK_CASE(16) RK_CASE(32) RK_CASE(48) RK_CASE(64) RK_CASE(80) RK_CASE(96) RK_CASE(112) RK_CASE(128)
@@ -1773,14 +1810,14 @@ __global__ void xcd_of_workgroup(int32_t* out)
 {
     uint32_t x;
     asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(x));
-    if (threadIdx.x == 0) out[blockIdx.x] = (int32_t)(x & 15u) + 1;
+    if (threadIdx.x == 0) out[blockIdx.y * gridDim.x + blockIdx.x] = (int32_t)(x & 15u) + 1;
 }
 
 hipError_t probe_xcd_deal(int32_t* scratch, bool* same_xcd)
 {
     *same_xcd = false;
     int32_t h[64];
-    hipLaunchKernelGGL(xcd_of_workgroup, dim3(64), dim3(64), 0, 0, scratch);
+    hipLaunchKernelGGL(xcd_of_workgroup, dim3(16, 4), dim3(64), 0, 0, scratch);      // two-dimensional, as the decode grids
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     e = hipMemcpy(h, scratch, sizeof(h), hipMemcpyDeviceToHost);
