@@ -927,11 +927,12 @@ __device__ __forceinline__ void text_split(const bf16_t* __restrict__ q, const T
 // GN: lane groups that hold heads, (Gc + 3) / 4 rounded to a power of two.  A thread takes two heads of a channel (GN = 1), four
 // (GN = 2) or four of two channels: every thread has outputs then, and the weights that it needs are fewer.  (One form for all, two
 // channels of four heads each: 1.0 us against 0.6, all of it instructions.)
-template <int GN, bool SHARED>
+template <int GN, bool SHARED, typename T>
 __device__ __forceinline__ void merge_states(const float* big, const float (*sm_m)[16], const float (*sm_l)[16],
-                                             const float (*sbias)[16], int Gc, bool direct, bool empty, bf16_t* out, float* ws_m,
+                                             const float (*sbias)[16], int Gc, bool direct, bool empty, T* out, float* ws_m,
                                              float* ws_l, float* ws_acc, size_t row0, int S, int split, int tid)
 {
+    constexpr bool F32 = std::is_same<T, float>::value;
     constexpr int NST = SHARED ? 8 : 4, NH = GN == 1 ? 2 : 4, NC = GN == 4 ? 2 : 1;
     typedef float vec __attribute__((ext_vector_type(NH)));
     const int hb = GN == 1 ? 2 * (tid & 1) : GN == 2 ? 4 * (tid >> 7) : 4 * ((tid >> 4) & 3);
@@ -960,7 +961,7 @@ __device__ __forceinline__ void merge_states(const float* big, const float (*sm_
         Mh[j] = M;
 #pragma unroll
         for (int w = 0; w < NST; ++w) {
-            const float x = w < 4 ? fast_exp2(sw[w][j] - Mv) : exp2f(sw[w][j] - M);
+            const float x = w < 4 ? (F32 ? exp2f(sw[w][j] - Mv) : fast_exp2(sw[w][j] - Mv)) : exp2f(sw[w][j] - M);
             wgt[w][j] = sw[w][j] > NEG_INF ? (SHARED && w < 4 ? x * f : x) : 0.f;
         }
     }
@@ -975,14 +976,14 @@ __device__ __forceinline__ void merge_states(const float* big, const float (*sm_
         for (int w = 1; w < NST; ++w) acc[k] += pk[k][w] * wgt[w];
     }
     if (direct) {
-        bf16_t* o = out + row0 * D;
+        T* o = out + row0 * D;
 #pragma unroll
         for (int j = 0; j < NH; ++j)
             if (hb + j < Gc) {
-                // (an empty cache may stand beside text rows that all score -inf)
-                const bool none = SHARED ? !(Mh[j] > NEG_INF) : empty;
+                // (an empty cache may stand beside text rows that all score -inf; in fp32 rows that do weigh nothing)
+                const bool none = SHARED || F32 ? !(Mh[j] > NEG_INF) : empty;
 #pragma unroll
-                for (int k = 0; k < NC; ++k) o[(uint32_t)((hb + j) * D) + c + 16 * k] = f32_to_bf16(none ? 0.f : acc[k][j] / lh[j]);
+                for (int k = 0; k < NC; ++k) st_elem(o + (uint32_t)((hb + j) * D) + c + 16 * k, none ? 0.f : acc[k][j] / lh[j]);
             }
     } else {
         float* o = ws_acc + (row0 * S + split) * D;
@@ -1001,6 +1002,25 @@ __device__ __forceinline__ void merge_states(const float* big, const float (*sm_
                 }
         }
     }
+}
+
+// The four waves park their states, and merge_states does the rest.
+template <bool SHARED, typename T>
+__device__ __forceinline__ void park_and_merge(float* big, float (*sm_m)[16], float (*sm_l)[16], const float (*sbias)[16],
+                                               const f32x4 (&O)[8], float m_run, float l_run, int Gc, bool direct, bool empty, T* out,
+                                               float* ws_m, float* ws_l, float* ws_acc, size_t row0, int S, int split, int tid)
+{
+    const int lane = tid & 63, wave = tid >> 6, g = lane >> 4, n = lane & 15;
+    l_run = groups_sum(l_run);
+    if (4 * g < Gc) {
+#pragma unroll
+        for (int cb = 0; cb < 8; ++cb) ((f32x4*)big)[(wave * 8 + cb) * 64 + lane] = O[cb];
+    }
+    if (g == 0) { sm_m[wave][n] = m_run; sm_l[wave][n] = l_run; }
+    lds_barrier();
+    if (Gc <= 4) merge_states<1, SHARED>(big, sm_m, sm_l, sbias, Gc, direct, empty, out, ws_m, ws_l, ws_acc, row0, S, split, tid);
+    else if (Gc <= 8) merge_states<2, SHARED>(big, sm_m, sm_l, sbias, Gc, direct, empty, out, ws_m, ws_l, ws_acc, row0, S, split, tid);
+    else merge_states<4, SHARED>(big, sm_m, sm_l, sbias, Gc, direct, empty, out, ws_m, ws_l, ws_acc, row0, S, split, tid);
 }
 
 // STEP = false is the plain decode; STEP = true adds the fused appends of a whole decode step;
@@ -1337,21 +1357,8 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
             if (k + 1 < nk) compute_tile<R>(TB, st, qh, ql, qth, qtl, tokA + 128 * (k + 1), t1, g);
             if (k + 2 < nk) compute_tile<R>(TA, st, qh, ql, qth, qtl, tokA + 128 * (k + 2), t1, g);
 
-            // ---- merge the four waves' states ----------------------------------------------
-            // Every wave holds O in the same lane layout, so the exchange is lane-to-lane: each
-            // lane parks its 8 accumulator quads in LDS ([wave][cb][lane], 128-bit, conflict
-            // free); wave w then folds channel blocks 2w, 2w+1 of all four waves and stores the
-            // result straight from the MFMA layout (lane (g, n): heads 4g..4g+3, channel 16cb+n).
-            const float l_run = groups_sum(st.l_run);
-            if (4 * g < Gc) {
-#pragma unroll
-                for (int cb = 0; cb < 8; ++cb) park[(wave * 8 + cb) * 64 + lane] = st.O[cb];
-            }
-            if (g == 0) { sm_m[wave][n] = st.m_run; sm_l[wave][n] = l_run; }
-            lds_barrier();
-            if (Gc <= 4) merge_states<1, SHARED>((const float*)big, sm_m, sm_l, sbias, Gc, direct, empty, out, ws_m, ws_l, ws_acc, row0, S, split, tid);
-            else if (Gc <= 8) merge_states<2, SHARED>((const float*)big, sm_m, sm_l, sbias, Gc, direct, empty, out, ws_m, ws_l, ws_acc, row0, S, split, tid);
-            else merge_states<4, SHARED>((const float*)big, sm_m, sm_l, sbias, Gc, direct, empty, out, ws_m, ws_l, ws_acc, row0, S, split, tid);
+            park_and_merge<SHARED>(big, sm_m, sm_l, sbias, st.O, st.m_run, st.l_run, Gc, direct, empty, out, ws_m, ws_l, ws_acc,
+                                   row0, S, split, tid);
         }
     }
 
@@ -1382,15 +1389,16 @@ struct DecTileF32 {
 
 template <int R>
 __device__ __forceinline__ void load_tile_f32(DecTileF32<R>& T, const float* __restrict__ Ku, const float* __restrict__ Vu,
-                                              int tok0, int lane)
+                                              int tok0, uint32_t lane)
 {
-    const int g = lane >> 4, n = lane & 15;
-    const float* kb = Ku + (size_t)(tok0 >> 4) * (16 * R) + (g >> 1) * 128 + n * 8 + 4 * (g & 1);
+    const uint32_t g = lane >> 4, n = lane & 15;
+    const char* kb = (const char*)(Ku + (size_t)(tok0 >> 4) * (16 * R));           // (uniform bases, 32-bit lane offsets)
 #pragma unroll
-    for (int i = 0; i < R / 16; ++i) T.k[i] = __builtin_nontemporal_load((const f32x4*)(kb + i * 256));
-    const float* vb = Vu + (size_t)(tok0 >> 5) * 4096 + lane * 8 + 4 * ((tok0 >> 4) & 1);
+    for (int i = 0; i < R / 16; ++i)
+        T.k[i] = __builtin_nontemporal_load((const f32x4*)(kb + 4 * ((g >> 1) * 128 + n * 8 + 4 * (g & 1)) + i * 1024));
+    const char* vb = (const char*)(Vu + ((size_t)(tok0 >> 5) * 4096 + 4 * ((tok0 >> 4) & 1)));
 #pragma unroll
-    for (int cb = 0; cb < 8; ++cb) T.v[cb] = __builtin_nontemporal_load((const f32x4*)(vb + cb * 512));
+    for (int cb = 0; cb < 8; ++cb) T.v[cb] = __builtin_nontemporal_load((const f32x4*)(vb + 32 * lane + cb * 2048));
 }
 
 template <int R>
@@ -1424,7 +1432,7 @@ __device__ __forceinline__ void compute_tile_f32(DecTileF32<R>& T, float& m_run,
 #pragma unroll
     for (int ii = 0; ii < 4; ++ii) p[ii] = exp2f(s[ii] - m_ref);
     l_run = fmaf(l_run, alpha, (p[0] + p[1]) + (p[2] + p[3]));
-    if (__any(m_new > m_run)) {
+    if (__any(m_new > m_run && m_run > NEG_INF)) {           // (nothing to rescale before a head's first score)
         f32x4 a4;
 #pragma unroll
         for (int ii = 0; ii < 4; ++ii) a4[ii] = __shfl(alpha, 4 * g + ii);
@@ -1440,173 +1448,139 @@ __device__ __forceinline__ void compute_tile_f32(DecTileF32<R>& T, float& m_run,
 
 template <int R, bool FUSED>
 __global__ __launch_bounds__(256, 2) void decode_split_f32(
-    const float* __restrict__ q, const float* __restrict__ Kp, const float* __restrict__ Vc, const float* __restrict__ Rr,
-    const float* __restrict__ dmu, const int32_t* __restrict__ seq_len, int Hq, int Hkv, int cap, int r, int tiles_all,
-    float scale_log2, float* ws_m, float* ws_l, float* ws_acc, int S, float* __restrict__ out, TextAppendDev ta,
-    int n_units, float* __restrict__ out_merged, int32_t* done)
+    const float* __restrict__ q, const float* __restrict__ Rr, const float* __restrict__ dmu, const int32_t* __restrict__ seq_len,
+    uint32_t r_ngrp, uint32_t g_units, uint32_t ngrp_rcp, uint32_t hkv_rcp, const float* __restrict__ Kp, const float* __restrict__ Vc,
+    DecodeShape sh, float* ws_m, float* ws_l, float* ws_acc, float* __restrict__ out, int32_t* done, TextAppendDev ta)
 {
     constexpr int NK = R / 16;                     // 16-channel groups, and 16-column blocks of R_r
     constexpr int NBW = (NK + 3) / 4;              // blocks of R_r per wave
-    __shared__ f32x4 park[4 * 8 * 64];             // the four waves' O at the end
+    __shared__ __attribute__((aligned(16))) float big[4 * 16 * D];     // the four waves' O at the end
     __shared__ __attribute__((aligned(16))) float qt[16][R + 4];
-    __shared__ float sbias[16], sm_m[4][16], sm_l[4][16];
+    __shared__ __attribute__((aligned(16))) float sbias[4][16], sm_m[4][16], sm_l[4][16];
     __shared__ int sm_last;
-    const int G = Hq / Hkv, ngrp = (G + 15) >> 4;
-    int split, by, b, unit = 0;
+    const int r = r_ngrp & 255, ngrp = r_ngrp >> 8, S = sh.S, cap = sh.cap;
+    const float scale_log2 = sh.scale_log2;
+    int split, u, grp, b, unit = 0, G;
     if constexpr (FUSED) {                         // all splits of a unit on one XCD, as in decode_split_mfma
-        const int id = blockIdx.x, upx = (n_units + 7) >> 3, slot = id >> 3, gy = Hkv * ngrp;
-        split = __builtin_amdgcn_readfirstlane(slot / upx);      // (a division by a variable leaves its result in vector registers)
-        unit = 8 * (slot - split * upx) + (id & 7);
-        if (unit >= n_units) return;
-        b = __builtin_amdgcn_readfirstlane(unit / gy);
-        by = unit - b * gy;
+        unit = blockIdx.x;
+        split = blockIdx.y;
+        G = g_units & 0xffff;
+        if (unit > (int)(g_units >> 16)) return;
+        u = div_by(unit, ngrp_rcp);
+        grp = unit - u * ngrp;
+        b = div_by(u, hkv_rcp);
     } else {
         split = blockIdx.x;
-        by = blockIdx.y;
         b = blockIdx.z;
+        G = g_units;
+        const int hk = div_by(blockIdx.y, ngrp_rcp);
+        grp = blockIdx.y - hk * ngrp;
+        u = b * sh.Hkv + hk;
     }
-    const int hk = FUSED ? __builtin_amdgcn_readfirstlane(by / ngrp) : by / ngrp, grp = by - hk * ngrp;
-    const int h0 = hk * G + grp * 16, Gc = min(16, G - grp * 16), u = b * Hkv + hk;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, n = lane & 15;
-    if (!FUSED && ta.k && split == 0 && by == 0 && wave == 1) text_append_rows<float>(ta, b, Hkv, lane);
+    const int Gc = min(16, G - grp * 16);
+    const size_t row0 = (size_t)u * G + grp * 16;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, n = lane & 15;
+    __builtin_assume(wave >= 0 && wave < 4);
+    if (!FUSED && ta.k && split == 0 && blockIdx.y == 0 && wave == 1) text_append_rows<float>(ta, b, sh.Hkv, lane);
 
-    const int seq_raw = seq_len[b];
-    const int tp = tiles_all / S, trem = tiles_all - tp * S;     // the last splits get one 128-token tile more
-    const int t0 = 128 * (split * tp + max(split - (S - trem), 0));
-    const int t1_full = 128 * ((split + 1) * tp + max(split + 1 - (S - trem), 0));
-    const float* Ku = Kp + (size_t)u * slab_tokens(cap) * R;
-    const float* Vu = Vc + (size_t)u * slab_tokens(cap) * D;
-
-    // q~ = q R_r: D[j][h] = sum_c R_r[c][j] q[h][c]; all loads unconditional with clamped indices, see decode_split_mfma
+    // q~ = q R_r: D[j][h] = sum_c R_r[c][j] q[h][c]; all loads unconditional with clamped indices, see decode_split_mfma (heads that
+    // do not exist repeat the last one)
+    uint32_t zero = 0;
+    asm volatile("" : "+v"(zero));
+    int seq_raw = *(const int32_t*)((const char*)(seq_len + b) + zero);
     const float* Ru = Rr + (size_t)u * D * r;
-    const float* qrow = q + ((size_t)b * Hq + h0 + min(n, Gc - 1)) * D + 4 * g;
-    f32x4 qf[8];
+    const char* qrow = (const char*)(q + row0 * D) + (uint32_t)(512 * min(n, Gc - 1) + 16 * g);
+    f32x4 qf[8], qb[2], ra[NBW][8], dm[2];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) qf[i] = *(const f32x4*)(qrow + 16 * i);
-    f32x4 ra[NBW][8], dm[8];
+    for (int i = 0; i < 8; ++i) qf[i] = *(const f32x4*)(qrow + 64 * i);
 #pragma unroll
     for (int bw = 0; bw < NBW; ++bw) {
-        const int col = min(16 * (wave + 4 * bw) + n, r - 1);
+        uint32_t at = 4u * (4 * g * r + min(16 * (wave + 4 * bw) + n, r - 1));
 #pragma unroll
         for (int i = 0; i < 8; ++i)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) ra[bw][i][e] = Ru[(16 * i + 4 * g + e) * r + col];
+            for (int e = 0; e < 4; ++e) {
+                ra[bw][i][e] = *(const float*)((const char*)Ru + at);
+                at += 4u * (e < 3 ? r : 13 * r);
+            }
     }
-    const float* dp = dmu ? dmu + (size_t)u * D : q;             // any readable address when there is no bias
+    // this wave's quarter of the bias: channels 32 wave + 16 i + 4 g ..+3
+    const float* dp = (dmu ? dmu + (size_t)u * D : Ru) + 32 * wave;     // any readable address when there is no bias
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) dm[i][e] = dp[16 * i + 4 * g + e];
-
+    for (int i = 0; i < 2; ++i) {
+        qb[i] = *(const f32x4*)(qrow + 128 * wave + 64 * i);
+        dm[i] = *(const f32x4_any*)(dp + 16 * i + 4 * g);
+    }
+    // from here on the other arguments are wanted
+    asm volatile("" :: "s"(ws_m), "s"(ws_l), "s"(ws_acc), "s"(out), "s"(S), "s"(Vc), "s"(cap));
+    if constexpr (FUSED) asm volatile("" :: "s"(done));
+    __builtin_amdgcn_sched_barrier(0);
+    // the last splits get one 128-token tile more
+    const int t0 = 128 * (split * sh.tiles_each + max(split - sh.first_long, 0));
+    const int t1_full = 128 * ((split + 1) * sh.tiles_each + max(split + 1 - sh.first_long, 0));
+    const float* Ku = Kp + (size_t)u * sh.slab * R;
+    const float* Vu = Vc + (size_t)u * sh.slab * D;
     DecTileF32<R> TA, TB;
     const int tokA = t0 + wave * 16;                             // this wave's tiles: every 64 tokens
     const int t_spec = min(t1_full, cap);
     load_tile_f32<R>(TA, Ku, Vu, tokA + 16 <= t_spec ? tokA : 0, lane);
-    const int t1 = min(t1_full, min(max(seq_raw, 0), cap));
-    if (t0 >= t1) {                                              // empty split
-        for (int idx = tid; idx < Gc * D; idx += 256) {
-            const size_t row = (size_t)b * Hq + h0 + (idx >> 7);
-            if (out) out[row * D + (idx & 127)] = 0.f;
-            else {
-                ws_acc[(row * S + split) * D + (idx & 127)] = 0.f;
-                if ((idx & 127) == 0) { ws_m[row * S + split] = NEG_INF; ws_l[row * S + split] = 0.f; }
-            }
-        }
-    } else {
+
 #pragma unroll
-        for (int bw = 0; bw < NBW; ++bw) {
-            const int jb = wave + 4 * bw;
+    for (int bw = 0; bw < NBW; ++bw) {
+        const int jb = wave + 4 * bw;
+        if (jb < NK) {
+            f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f}, acc2 = acc;
             const bool live = 16 * jb + n < r;                       // columns r .. R - 1 read as zero
-            if (jb < NK) {
-                f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int i = 0; i < 8; ++i)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(live ? ra[bw][i][e] : 0.f, n < Gc ? qf[i][e] : 0.f, acc, 0, 0, 0);
-                *(f32x4*)&qt[n][16 * jb + 4 * g] = acc * scale_log2;
-            }
-        }
-        if (wave == 0) {                                             // bias b_n = q_n . delta_mu
-            float bp = 0.f;
 #pragma unroll
             for (int i = 0; i < 8; ++i)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) bp = fmaf(qf[i][e], dm[i][e], bp);
-            bp += __shfl_xor(bp, 16);
-            bp += __shfl_xor(bp, 32);
-            if (g == 0) sbias[n] = dmu ? bp * scale_log2 : 0.f;
-        }
-        load_tile_f32<R>(TB, Ku, Vu, tokA + 64 + 16 <= t_spec ? tokA + 64 : 0, lane);
-        __syncthreads();
-        f32x4 qb[NK];
-#pragma unroll
-        for (int i = 0; i < NK; ++i) qb[i] = *(const f32x4*)&qt[n][16 * i + 4 * g];
-
-        float m_run = NEG_INF, l_run = 0.f;
-        f32x4 O[8];
-#pragma unroll
-        for (int cb = 0; cb < 8; ++cb) O[cb] = (f32x4){0.f, 0.f, 0.f, 0.f};
-        const int ntiles = (t1 - t0 + 15) >> 4, nk = (ntiles - wave + 3) >> 2;
-        int k = 0;
-        for (; k + 3 < nk; k += 2) {
-            compute_tile_f32<R>(TA, m_run, l_run, O, qb, tokA + 64 * k, t1, g);
-            load_tile_f32<R>(TA, Ku, Vu, tokA + 64 * (k + 2), lane);
-            compute_tile_f32<R>(TB, m_run, l_run, O, qb, tokA + 64 * (k + 1), t1, g);
-            load_tile_f32<R>(TB, Ku, Vu, tokA + 64 * (k + 3), lane);
-        }
-        if (k < nk) {
-            compute_tile_f32<R>(TA, m_run, l_run, O, qb, tokA + 64 * k, t1, g);
-            if (k + 2 < nk) load_tile_f32<R>(TA, Ku, Vu, tokA + 64 * (k + 2), lane);
-        }
-        if (k + 1 < nk) compute_tile_f32<R>(TB, m_run, l_run, O, qb, tokA + 64 * (k + 1), t1, g);
-        if (k + 2 < nk) compute_tile_f32<R>(TA, m_run, l_run, O, qb, tokA + 64 * (k + 2), t1, g);
-
-        // merge the four waves' states, lane to lane (all hold O in one layout: heads 4 g + ii, channel 16 cb + n)
-        l_run = groups_sum(l_run);
-#pragma unroll
-        for (int cb = 0; cb < 8; ++cb) park[(wave * 8 + cb) * 64 + lane] = O[cb];
-        if (g == 0) { sm_m[wave][n] = m_run; sm_l[wave][n] = l_run; }
-        __syncthreads();
-        f32x4 wgt[4], Mh, lh = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ii = 0; ii < 4; ++ii) {
-            const int hh = 4 * g + ii;
-            const float M = fmaxf(fmaxf(sm_m[0][hh], sm_m[1][hh]), fmaxf(sm_m[2][hh], sm_m[3][hh]));
-            Mh[ii] = M;
-#pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                const float x = sm_m[w][hh] > NEG_INF ? exp2f(sm_m[w][hh] - M) : 0.f;
-                wgt[w][ii] = x;
-                lh[ii] = fmaf(sm_l[w][hh], x, lh[ii]);
-            }
-        }
-#pragma unroll
-        for (int c2 = 0; c2 < 2; ++c2) {
-            const int cb = 2 * wave + c2;
-            f32x4 acc = park[cb * 64 + lane] * wgt[0];
-#pragma unroll
-            for (int w = 1; w < 4; ++w) acc += park[(w * 8 + cb) * 64 + lane] * wgt[w];
-#pragma unroll
-            for (int ii = 0; ii < 4; ++ii)
-                if (4 * g + ii < Gc) {
-                    const size_t row = (size_t)b * Hq + h0 + 4 * g + ii;
-                    if (out) out[row * D + 16 * cb + n] = Mh[ii] > NEG_INF ? acc[ii] / lh[ii] : 0.f;
-                    else ws_acc[(row * S + split) * D + 16 * cb + n] = acc[ii];
+                for (int e = 0; e < 4; e += 2) {
+                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(live ? ra[bw][i][e] : 0.f, qf[i][e], acc, 0, 0, 0);
+                    acc2 = __builtin_amdgcn_mfma_f32_16x16x4f32(live ? ra[bw][i][e + 1] : 0.f, qf[i][e + 1], acc2, 0, 0, 0);
                 }
-        }
-        if (!out && wave == 0 && n == 0) {
-#pragma unroll
-            for (int ii = 0; ii < 4; ++ii)
-                if (4 * g + ii < Gc) {
-                    const size_t row = (size_t)b * Hq + h0 + 4 * g + ii;
-                    ws_m[row * S + split] = Mh[ii] + sbias[4 * g + ii];
-                    ws_l[row * S + split] = lh[ii];
-                }
+            *(f32x4*)&qt[n][16 * jb + 4 * g] = (acc + acc2) * scale_log2;
         }
     }
+    {
+        float b0 = 0.f, b1 = 0.f;                                    // bias b_n = q_n . delta_mu
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            b0 = fmaf(qb[0][e], dm[0][e], b0);
+            b1 = fmaf(qb[1][e], dm[1][e], b1);
+        }
+        const float bp = groups_sum(b0 + b1);
+        if (g == 0) sbias[wave][n] = dmu ? bp * scale_log2 : 0.f;
+    }
+    load_tile_f32<R>(TB, Ku, Vu, tokA + 64 + 16 <= t_spec ? tokA + 64 : 0, lane);
+    lds_barrier();
+    f32x4 qs[NK];
+#pragma unroll
+    for (int i = 0; i < NK; ++i) qs[i] = *(const f32x4*)&qt[n][16 * i + 4 * g];
+    seq_raw = __builtin_amdgcn_readfirstlane(seq_raw);
+    const int t1 = min(t1_full, min(max(seq_raw, 0), cap));          // (an empty split goes the same way, without a tile)
+
+    float m_run = NEG_INF, l_run = 0.f;
+    f32x4 O[8];
+#pragma unroll
+    for (int cb = 0; cb < 8; ++cb) O[cb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    const int ntiles = (t1 - t0 + 15) >> 4, nk = (ntiles - wave + 3) >> 2;
+    int k = 0;
+    for (; k + 3 < nk; k += 2) {
+        compute_tile_f32<R>(TA, m_run, l_run, O, qs, tokA + 64 * k, t1, g);
+        load_tile_f32<R>(TA, Ku, Vu, tokA + 64 * (k + 2), lane);
+        compute_tile_f32<R>(TB, m_run, l_run, O, qs, tokA + 64 * (k + 1), t1, g);
+        load_tile_f32<R>(TB, Ku, Vu, tokA + 64 * (k + 3), lane);
+    }
+    if (k < nk) {
+        compute_tile_f32<R>(TA, m_run, l_run, O, qs, tokA + 64 * k, t1, g);
+        if (k + 2 < nk) load_tile_f32<R>(TA, Ku, Vu, tokA + 64 * (k + 2), lane);
+    }
+    if (k + 1 < nk) compute_tile_f32<R>(TB, m_run, l_run, O, qs, tokA + 64 * (k + 1), t1, g);
+    if (k + 2 < nk) compute_tile_f32<R>(TA, m_run, l_run, O, qs, tokA + 64 * (k + 2), t1, g);
+    park_and_merge<false>(big, sm_m, sm_l, sbias, O, m_run, l_run, Gc, !FUSED && out, t0 >= t1, out, ws_m, ws_l, ws_acc, row0, S,
+                          split, tid);
     if constexpr (FUSED)
-        fold_unit<false>(unit, S, b, u, (size_t)b * Hq + h0, Gc, ws_m, ws_l, ws_acc, out_merged, done, false, nullptr, 0, nullptr, 0, nullptr,
+        fold_unit<false>(unit, S, b, u, row0, Gc, ws_m, ws_l, ws_acc, out, done, false, nullptr, 0, nullptr, 0, nullptr,
                          nullptr, &sm_last);
 }
 
@@ -1715,12 +1689,14 @@ hipError_t launch_decode(int dtype, bool mfma, int B, int Hq, int Hkv, int cap, 
         const int gy = Hkv * ((Hq / Hkv + 15) / 16), nunit = B * gy;
         const bool fused_merge = !text && S >= 2 && counters && nunit <= n_counters &&
                                  fold_pays_f32(nunit, S, tiles_all, r, n_cu);
-        const dim3 grid = fused_merge ? dim3((unsigned)(8 * ((nunit + 7) / 8) * S)) : dim3(S, gy, B);
-        float* o = direct ? (float*)out : nullptr;
+        const dim3 grid = fused_merge ? dim3((unsigned)(8 * ((nunit + 7) / 8)), (unsigned)S) : dim3(S, gy, B);
+        const int G = Hq / Hkv, ngrp = (G + 15) / 16;
+        const DecodeShape sh{Hkv, cap, S, S, tiles_all / S, S - tiles_all % S, (int)slab_tokens(cap), sl2};
+        const uint32_t r_ngrp = (uint32_t)r | (uint32_t)ngrp << 8, g_units = (uint32_t)G | (fused_merge ? (uint32_t)(nunit - 1) << 16 : 0u);
+        float* o = fused_merge || direct ? (float*)out : nullptr;
 #define RK_FORM(RV, FUSED)                                                                                       \
-    hipLaunchKernelGGL((decode_split_f32<RV, FUSED>), grid, dim3(256), 0, st, (const float*)q, (const float*)Kp,  \
-                       (const float*)Vc, Rr, dmu, seq_len, Hq, Hkv, cap, r, tiles_all, sl2, ws_m, ws_l, ws_acc, S, o, ta, \
-                       nunit, (float*)out, counters)
+    hipLaunchKernelGGL((decode_split_f32<RV, FUSED>), grid, dim3(256), 0, st, (const float*)q, Rr, dmu, seq_len, r_ngrp, g_units, \
+                       rcp_of(ngrp), rcp_of(Hkv), (const float*)Kp, (const float*)Vc, sh, ws_m, ws_l, ws_acc, o, counters, ta)
 #define RK_CASE(RV)                                                                                              \
     case RV:                                                                                                     \
         if (fused_merge) RK_FORM(RV, true);                                                                      \
