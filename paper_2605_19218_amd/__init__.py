@@ -67,11 +67,12 @@ class RotateKError(RuntimeError):
 
 
 _lib = None
+_bind = None         # marshals the per-token calls in C (csrc/rk_bind.cpp); set with _lib
 
 
 def lib():
     """Load librotatek.so (built by paper_2605_19218_amd/build.py); loud failure if absent."""
-    global _lib
+    global _lib, _bind
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise ImportError(f"{LIB_PATH} is missing: run `python -c 'import __graft_entry__ as g; g.build()'` "
@@ -111,6 +112,15 @@ def lib():
         for name in EXPORTS:
             if name not in ("rk_status_str", "rk_last_error", "rk_fit_workspace_size", "rk_decode_workspace_size"):
                 getattr(L, name).restype = C.c_int
+        try:
+            from . import _rkbind
+        except ImportError:          # not built, or for another interpreter: every call marshals its arguments through ctypes
+            pass
+        else:
+            _rkbind.bind(Layout, Text, *[C.cast(f, C.c_void_p).value for f in
+                                         (L.rk_decode_attn, L.rk_append_decode_attn, L.rk_decode_attn_dual,
+                                          L.rk_append_text_decode_attn_dual)])
+            _bind = _rkbind
         _lib = L
     return _lib
 
@@ -134,6 +144,13 @@ def _stream(stream: Any) -> Optional[int]:
     if isinstance(stream, int):
         return stream
     return int(stream.cuda_stream)        # torch.cuda.Stream
+
+
+def _done(ctx, status) -> bool:
+    """Whether _bind made the call (it answers None for arguments that it leaves to ctypes)."""
+    if status:
+        _check(ctx, status)
+    return status is not None
 
 
 def _check(ctx, status: int):
@@ -284,6 +301,9 @@ def rk_append(ctx, layout: Layout, k_new, v_new, R_r, k_packed, v_cache, seq_len
 
 def rk_append_decode_attn(ctx, layout: Layout, k_new, v_new, q, R_r, delta_mu, k_packed, v_cache, seq_len,
                           scale: float, out, workspace, stream=None, workspace_bytes: Optional[int] = None) -> None:
+    if _bind is not None and _done(ctx, _bind.append_decode(ctx, layout, k_new, v_new, q, R_r, delta_mu, k_packed, v_cache,
+                                                            seq_len, scale, out, workspace, stream, workspace_bytes)):
+        return
     wb = workspace_bytes if workspace_bytes is not None else (_nbytes(workspace) if workspace is not None else 0)
     _check(ctx, lib().rk_append_decode_attn(ctx, C.byref(layout.c()), _ptr(k_new), _ptr(v_new), _ptr(q), _ptr(R_r),
                                             _ptr(delta_mu), _ptr(k_packed), _ptr(v_cache), _ptr(seq_len),
@@ -292,6 +312,9 @@ def rk_append_decode_attn(ctx, layout: Layout, k_new, v_new, q, R_r, delta_mu, k
 
 def rk_decode_attn(ctx, layout: Layout, q, k_packed, v_cache, R_r, delta_mu, scale: float, out, workspace,
                    stream=None, workspace_bytes: Optional[int] = None) -> None:
+    if _bind is not None and _done(ctx, _bind.decode(ctx, layout, q, k_packed, v_cache, R_r, delta_mu, scale, out, workspace,
+                                                     stream, workspace_bytes)):
+        return
     wb = workspace_bytes if workspace_bytes is not None else (_nbytes(workspace) if workspace is not None else 0)
     _check(ctx, lib().rk_decode_attn(ctx, C.byref(layout.c()), _ptr(q), _ptr(k_packed), _ptr(v_cache), _ptr(R_r),
                                      _ptr(delta_mu), float(scale), _ptr(out), _ptr(workspace), wb,
@@ -313,6 +336,9 @@ def rk_decode_attn_static(ctx, layout: Layout, q, k_packed, v_cache, R_r, delta_
 
 def rk_decode_attn_dual(ctx, layout: Layout, q, k_packed, v_cache, R_r, delta_mu, text: Text, scale: float, out,
                         workspace, stream=None, workspace_bytes: Optional[int] = None) -> None:
+    if _bind is not None and _done(ctx, _bind.dual(ctx, layout, q, k_packed, v_cache, R_r, delta_mu, text, scale, out,
+                                                   workspace, stream, workspace_bytes)):
+        return
     wb = workspace_bytes if workspace_bytes is not None else (_nbytes(workspace) if workspace is not None else 0)
     tref = C.byref(text.c()) if text is not None else None
     _check(ctx, lib().rk_decode_attn_dual(ctx, C.byref(layout.c()), _ptr(q), _ptr(k_packed), _ptr(v_cache),
@@ -323,6 +349,9 @@ def rk_decode_attn_dual(ctx, layout: Layout, q, k_packed, v_cache, R_r, delta_mu
 def rk_append_text_decode_attn_dual(ctx, layout: Layout, k_new, v_new, q, k_packed, v_cache, R_r, delta_mu,
                                     text: Text, scale: float, out, workspace, stream=None,
                                     workspace_bytes: Optional[int] = None) -> None:
+    if _bind is not None and _done(ctx, _bind.append_dual(ctx, layout, k_new, v_new, q, k_packed, v_cache, R_r, delta_mu, text,
+                                                          scale, out, workspace, stream, workspace_bytes)):
+        return
     wb = workspace_bytes if workspace_bytes is not None else (_nbytes(workspace) if workspace is not None else 0)
     tref = C.byref(text.c()) if text is not None else None
     _check(ctx, lib().rk_append_text_decode_attn_dual(ctx, C.byref(layout.c()), _ptr(k_new), _ptr(v_new), _ptr(q),

@@ -4,12 +4,14 @@ from __future__ import annotations
 import os
 import re
 import subprocess
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librotatek.so")
+BIND = os.path.join(HERE, "_rkbind.so")
 SOURCES = ["rk_api.hip", "rk_fit.hip", "rk_eig.hip", "rk_subspace.hip", "rk_compress.hip", "rk_decode.hip"]
 
 
@@ -44,14 +46,22 @@ def _run(cmd, verbose):
     err = "\n".join(l for l in lines if "-Rpass-analysis=kernel-resource-usage" not in l and not ctx.match(l)
                     and "remarks generated" not in l and "warning generated" not in l)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + err)
+        raise RuntimeError(f"{os.path.basename(cmd[0])} failed:\n" + err)
     if verbose and err.strip():
         print(err)
     return remarks
 
 
+def build_bind(verbose: bool = False) -> str:
+    """The C marshalling of the per-token calls, a plain CPython extension (host code only)."""
+    _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-Wall", "-shared", "-fPIC", "-fvisibility=hidden",
+          "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "rk_bind.cpp"), "-o", BIND], verbose)
+    return BIND
+
+
 def build(verbose: bool = False) -> str:
     """Compile every source to an object (in parallel) and link librotatek.so."""
+    build_bind(verbose)
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
     common = [hipcc(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -1,0 +1,173 @@
+"""The per-token calls marshalled in C (csrc/rk_bind.cpp) hand the library the arguments that the ctypes path hands it, or leave the call to
+that path: both are pointed at entry points that write down what arrives."""
+import ctypes as C
+import types
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2605_19218_amd as rk
+
+B, HQ, HKV, CAP = 2, 8, 2, 64
+vp, f32, sz, i32 = C.c_void_p, C.c_float, C.c_size_t, C.c_int
+PL, PT = C.POINTER(rk.rk_layout), C.POINTER(rk.rk_text)
+SIGNATURES = {
+    "rk_decode_attn": [vp, PL, vp, vp, vp, vp, vp, f32, vp, vp, sz, vp],
+    "rk_append_decode_attn": [vp, PL, vp, vp, vp, vp, vp, vp, vp, vp, f32, vp, vp, sz, vp],
+    "rk_decode_attn_dual": [vp, PL, vp, vp, vp, vp, vp, PT, f32, vp, vp, sz, vp],
+    "rk_append_text_decode_attn_dual": [vp, PL, vp, vp, vp, vp, vp, vp, vp, PT, f32, vp, vp, sz, vp],
+}
+
+
+class Duck:
+    """anything with data_ptr()"""
+
+    def data_ptr(self):
+        return 4096
+
+    def numel(self):
+        return 10
+
+    def element_size(self):
+        return 3
+
+
+class OtherLayout(rk.Layout):
+    def c(self):
+        x = super().c()
+        x.keep = 5
+        return x
+
+
+def tensor(*shape):
+    return torch.zeros(*shape, dtype=torch.bfloat16)
+
+
+def layout(cls=rk.Layout, **more):
+    return cls(B, HQ, HKV, 16, rk.RK_BF16, CAP, 40, **{"seq_len": torch.zeros(B, dtype=torch.int32), **more})
+
+
+def text(**more):
+    k = tensor(B, HKV, 48, 128)
+    return rk.Text(k, tensor(B, HKV, 48, 128), 33, **{"len": torch.zeros(B, dtype=torch.int32), **more})
+
+
+@pytest.fixture
+def paths(monkeypatch):
+    """record(name, positional, keywords, fast): the arguments that reached the entry point"""
+    rk.lib()
+    if rk._bind is None:
+        pytest.fail("_rkbind.so is not built")
+    seen, keep = [], []
+
+    def entry(kinds):
+        def f(*a):
+            row = []
+            for x, kind in zip(a, kinds):
+                if kind in (PL, PT):
+                    row.append([getattr(x.contents, n) for n, _ in x.contents._fields_] if x else None)
+                else:
+                    row.append(x)
+            seen.append(row)
+            return 0
+        return C.CFUNCTYPE(i32, *kinds)(f)
+
+    stub = types.SimpleNamespace()
+    for name, kinds in SIGNATURES.items():
+        keep.append(entry(kinds))
+        f = keep[-1]
+        f.argtypes, f.restype = kinds, i32
+        setattr(stub, name, f)
+    real, bind = rk.lib(), rk._bind
+    bind.bind(rk.Layout, rk.Text, *[C.cast(getattr(stub, n), vp).value for n in SIGNATURES])
+
+    def record(name, args, kw, fast):
+        seen.clear()
+        monkeypatch.setattr(rk, "_bind", bind if fast else None)
+        monkeypatch.setattr(rk, "_lib", None if fast else stub)
+        if fast:                                    # the ctypes path must not be needed
+            monkeypatch.setattr(rk, "lib", lambda: pytest.fail("the ctypes path was taken"))
+        getattr(rk, name)(*args, **kw)
+        monkeypatch.undo()
+        assert len(seen) == 1
+        return list(seen[0])
+
+    yield record, bind
+    bind.bind(rk.Layout, rk.Text, *[C.cast(getattr(real, n), vp).value for n in SIGNATURES])
+
+
+def call(name, lay, txt, ws, scale=0.0, kv=None, ctx=77):
+    """positional arguments of an entry point; kv: in the place of a tensor"""
+    t = [tensor(4, 16) for _ in range(8)]
+    if kv is not None:
+        t[1] = kv
+    out = tensor(4, 16)
+    if name == "rk_decode_attn":
+        return [ctx, lay, *t[:5], scale, out, ws]
+    if name == "rk_append_decode_attn":
+        return [ctx, lay, *t[:8], scale, out, ws]
+    if name == "rk_decode_attn_dual":
+        return [ctx, lay, *t[:5], txt, scale, out, ws]
+    return [ctx, lay, *t[:7], txt, scale, out, ws]
+
+
+@pytest.mark.parametrize("name", list(SIGNATURES))
+def test_same_arguments(paths, name):
+    record, _ = paths
+    ws = torch.empty(1000, dtype=torch.float32)
+    forms = [
+        (call(name, layout(), text(), ws), {}),
+        (call(name, layout(seq_len=None, head_dim=64), text(len=None), ws, scale=0.25), {"stream": 12345}),
+        (call(name, layout(seq_len=1 << 47), text(strides=(9, 8, 7), capacity=40), None, scale=1), {"stream": None}),
+        (call(name, layout(), text(capacity=7), 1 << 40, kv=Duck()), {"workspace_bytes": 99}),
+        (call(name, layout(), text(), Duck(), kv=None, ctx=None), {"stream": types.SimpleNamespace(cuda_stream=321)}),
+        (call(name, layout(), text(), ws, kv=(1 << 64) - 16), {"workspace_bytes": 0}),
+    ]
+    for args, kw in forms:
+        assert record(name, args, kw, True) == record(name, args, kw, False)
+    args = call(name, layout(), text(), ws)
+    args[5] = None                                      # a missing tensor
+    assert record(name, args, {}, True) == record(name, args, {}, False)
+
+
+@pytest.mark.parametrize("name", list(SIGNATURES))
+def test_other_forms_go_to_ctypes(paths, name):
+    _, bind = paths
+    fast = {"rk_decode_attn": bind.decode, "rk_append_decode_attn": bind.append_decode, "rk_decode_attn_dual": bind.dual,
+            "rk_append_text_decode_attn_dual": bind.append_dual}[name]
+    ws = torch.empty(10)
+    odd = [call(name, layout(OtherLayout), text(), ws), call(name, layout(), text(), ws, scale="0.5"),
+           call(name, layout(), text(), ws, kv=np.int64(4096)), call(name, layout(), text(), ws, kv=-16), call(name, layout(), text(), ws, kv="x"),
+           call(name, layout(), text(), 4096), call(name, None, text(), ws), call(name, layout(), text(), ws, kv=True)]
+    big = layout()
+    big.capacity = 1 << 33
+    odd.append(call(name, big, text(), ws))
+    if "dual" in name:
+        odd += [call(name, layout(), None, ws), call(name, layout(), text(strides=[1, 2, 3]), ws), call(name, layout(), text(strides=(1, 2)), ws)]
+    for args in odd:
+        assert fast(*args, None, None) is None
+
+
+def test_statuses():
+    """Errors come out as from the ctypes path, with the library's text."""
+    ctx = rk.rk_create(rk.RK_DEVICE_NONE)
+    try:
+        lay = layout()
+        ws = torch.empty(rk.rk_decode_workspace_size(ctx, lay), dtype=torch.uint8)
+        for change, status in (({}, rk.RK_ERR_NO_DEVICE), ({"keep": 0}, rk.RK_ERR_INVALID_ARG), ({"head_dim": 64}, rk.RK_ERR_UNSUPPORTED)):
+            for k, v in change.items():
+                setattr(lay, k, v)
+            texts = []
+            for bind in (rk._bind, None):
+                old, rk._bind = rk._bind, bind
+                try:
+                    with pytest.raises(rk.RotateKError) as e:
+                        rk.rk_decode_attn(*call("rk_decode_attn", lay, None, ws, ctx=ctx))
+                finally:
+                    rk._bind = old
+                assert e.value.status == status
+                texts.append(str(e.value))
+            assert texts[0] == texts[1]
+    finally:
+        rk.rk_destroy(ctx)
