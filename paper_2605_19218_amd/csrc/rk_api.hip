@@ -458,7 +458,7 @@ rk_status rk_fit_rotation(rk_ctx* ctx, const rk_layout* L, const rk_rows* keys, 
     hipStream_t st = as_stream(stream);
     e = launch_cov_partial(L->dtype, mfma, rows, B, Hkv, nc, ct, part_S, part_sum, st);
     if (e != hipSuccess) return hip_fail(ctx, e, "covariance launch");
-    e = launch_cov_finalize(L->dtype, mfma, rows, B, Hkv, nc, (flags & RK_FIT_CENTER) != 0, part_S, part_sum, cov, out->mu, ctx->n_cu, st);
+    e = launch_cov_finalize(L->dtype, mfma, rows, B, Hkv, nc, ct, (flags & RK_FIT_CENTER) != 0, part_S, part_sum, cov, out->mu, ctx->n_cu, st);
     if (e != hipSuccess) return hip_fail(ctx, e, "covariance reduction launch");
     e = launch_eig(ctx->force_generic != 0, U, cov, sigma, out->mu, L->keep, out->R, out->eigvals, out->mask, out->keep_idx, out->R_r,
                    out->delta_mu, out->sweeps, ws + w.part_S, (int32_t*)(ws + w.status), st);
@@ -524,7 +524,7 @@ rk_status rk_fit_subspace(rk_ctx* ctx, const rk_layout* L, const rk_rows* keys, 
     hipStream_t st = as_stream(stream);
     e = launch_cov_partial(L->dtype, mfma, rows, B, Hkv, nc, ct, part_S, part_sum, st);
     if (e != hipSuccess) return hip_fail(ctx, e, "covariance launch");
-    e = launch_cov_finalize(L->dtype, mfma, rows, B, Hkv, nc, (flags & RK_FIT_CENTER) != 0, part_S, part_sum, cov, mu, ctx->n_cu, st);
+    e = launch_cov_finalize(L->dtype, mfma, rows, B, Hkv, nc, ct, (flags & RK_FIT_CENTER) != 0, part_S, part_sum, cov, mu, ctx->n_cu, st);
     if (e != hipSuccess) return hip_fail(ctx, e, "covariance reduction launch");
     e = launch_subspace(U, cov, sigma, mu, solver->v0, L->keep, solver->iterations, solver->ridge, R_r, delta_mu,
                         status, st);

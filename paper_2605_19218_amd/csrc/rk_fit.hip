@@ -87,7 +87,7 @@ __global__ __launch_bounds__(256) void cov_partial_generic(RowsDev rows, int Hkv
 }
 
 // ---------------------------------------------------------------------------
-// MFMA covariance partial (bf16 Keys): S = K^T K over a chunk of 4 TPW tokens (2048, fewer on small inputs) with
+// MFMA covariance partial (bf16 Keys): S = K^T K over a chunk (up to 2048 tokens, fewer on small inputs) with
 // v_mfma_f32_32x32x16_bf16, contraction index = tokens.  The matrix core wants, per
 // lane, 8 consecutive TOKENS of one channel, while memory holds 8 consecutive
 // CHANNELS of one token.  No LDS staging is used: lane (g2, m) loads the 8x8 block
@@ -96,29 +96,22 @@ __global__ __launch_bounds__(256) void cov_partial_generic(RowsDev rows, int Hkv
 // the even / odd channels of it.  The channel held by MFMA row m of block cbk is
 // therefore ch(cbk, m) = 8 (m % 16) + 2 cbk + m / 16 -- a permutation that is undone
 // when the 128x128 partial is written.  Each wave accumulates the 10 upper-triangular
-// 32x32 tiles for its own TPW tokens (160 accumulator registers); the four waves are
+// 32x32 tiles for a quarter of the tokens (160 accumulator registers); the four waves are
 // summed through LDS in a fixed order, each wave folding and storing a quarter.
 constexpr int COVM_CHUNK = 2048;           // the longest chunk
 constexpr int COVM_STAGES = 4;             // 16-token k-steps of loads in flight per wave (16 KB; 3 to 5 time alike, 6 and 8 slower)
 constexpr size_t COVM_LDS_BYTES = (size_t)(4 * 30 * 4 * 64 + 4 * D) * sizeof(float);   // 4 x 30 parked groups + column sums
 
-// rows >= t_end contribute zeros; the address is clamped to row t_last (always a valid row)
-// all 8 rows known to be valid: plain loads, nothing for the compiler to predicate.  Without
-// a token list the row address is lane_ptr + (tok0 + jj) * st with st wave-uniform, so the
-// only per-lane work is one 64-bit add per row (no per-lane 64-bit multiplies).
-template <bool GATHER>
-__device__ __forceinline__ void covm_load_full(uint4 (&r)[8], const bf16_t* __restrict__ base, int64_t head_base,
-                                               int64_t st, const int32_t* __restrict__ list, int tok0, int o,
-                                               const bf16_t* __restrict__ lane_ptr, int tok_rel)
+// Eight rows that all exist, without a token list: plain loads, nothing for the compiler to predicate, one 64-bit add a row.
+// covm_load clamps to row t_last (always a valid one); covm_zero_past clears what lies behind the end.
+__device__ __forceinline__ void covm_load_full(uint4 (&r)[8], const bf16_t* __restrict__ row, int64_t st)
 {
 #pragma unroll
     for (int jj = 0; jj < 8; ++jj) {
-        if (GATHER) r[jj] = *(const uint4*)(base + row_off<true>(head_base, st, list, tok0 + jj) + 8 * o);
-        else {
-            // read-once stream: non-temporal, so the rows do not displace each other in the L2
-            const u32x4 v = __builtin_nontemporal_load((const u32x4*)(lane_ptr + (int64_t)(tok_rel + jj) * st));
-            r[jj] = make_uint4(v.x, v.y, v.z, v.w);
-        }
+        // read-once stream: non-temporal, so the rows do not displace each other in the L2
+        const u32x4 v = __builtin_nontemporal_load((const u32x4*)row);
+        r[jj] = make_uint4(v.x, v.y, v.z, v.w);
+        row += st;
     }
 }
 
@@ -149,15 +142,15 @@ __device__ __forceinline__ void covm_load_rows(uint4 (&r)[8], const bf16_t* __re
 
 template <bool GATHER>
 __device__ __forceinline__ void covm_load(uint4 (&r)[8], const bf16_t* __restrict__ base, int64_t head_base,
-                                          int64_t st, const int32_t* __restrict__ list, int tok0, int t_end,
-                                          int t_last, int o)
+                                          int64_t st, const int32_t* __restrict__ list, int tok0, int t_last, int o)
 {
 #pragma unroll
-    for (int jj = 0; jj < 8; ++jj) {
-        const int tok = tok0 + jj;
-        const uint4 v = *(const uint4*)(base + row_off<GATHER>(head_base, st, list, min(tok, t_last)) + 8 * o);
-        r[jj] = tok < t_end ? v : make_uint4(0, 0, 0, 0);
-    }
+    for (int jj = 0; jj < 8; ++jj) r[jj] = *(const uint4*)(base + row_off<GATHER>(head_base, st, list, min(tok0 + jj, t_last)) + 8 * o);
+}
+__device__ __forceinline__ void covm_zero_past(uint4 (&r)[8], int tok0, int t_end)
+{
+#pragma unroll
+    for (int jj = 0; jj < 8; ++jj) r[jj] = tok0 + jj < t_end ? r[jj] : make_uint4(0, 0, 0, 0);
 }
 
 __device__ __forceinline__ uint32_t dw(const uint4& v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
@@ -232,8 +225,20 @@ __device__ __forceinline__ void covm_fold_store(const f32x16 (&acc)[10], const f
     }
 }
 
-template <bool GATHER, int TPW>
-__global__ __launch_bounds__(256) void cov_partial_mfma(RowsDev rows, int Hkv, int n_chunks,
+// A sequence of n rows is summed in as few chunks of at most `chunk_tokens` as hold it, dealt evenly to the 4 x `live` waves in blocks of
+// `unit` rows; the other work-groups of a unit end at once and leave no partial, and cov_finalize_* counts the same way.  (With full
+// chunks from the front and full shares to the waves of each, a last chunk took as long as a full one however short, and an
+// empty one 11 us to sum, store and read zeros.)
+__device__ __forceinline__ int live_chunks(int n, int chunk_tokens) { return (n + chunk_tokens - 1) / chunk_tokens; }
+__device__ __forceinline__ void wave_rows(int n, int live, int unit, int w, int& first, int& last)
+{
+    const int blocks = (n + unit - 1) / unit, each = blocks / (4 * live), more = blocks - each * 4 * live;
+    first = min((w * each + min(w, more)) * unit, n);
+    last = min(first + (each + (w < more ? 1 : 0)) * unit, n);
+}
+
+template <bool GATHER>
+__global__ __launch_bounds__(256) void cov_partial_mfma(RowsDev rows, int Hkv, int n_chunks, int chunk_tokens,
                                                         float* __restrict__ part_S, float* __restrict__ part_sum)
 {
     // the chunk number is rotated by head and batch item: with a chunk count that is a multiple of 8 an
@@ -247,8 +252,12 @@ __global__ __launch_bounds__(256) void cov_partial_mfma(RowsDev rows, int Hkv, i
     const int g2 = lane >> 5, m = lane & 31, o = m & 15, par = m >> 4;
     const uint32_t sel = par ? 0x07060302u : 0x05040100u;
     const int n_b = rows_count(rows, b);
-    const int t0 = chunk * (4 * TPW), t1 = min(t0 + 4 * TPW, n_b);
-    const int tw0 = t0 + wave * TPW, tw1 = min(tw0 + TPW, t1);
+    const int live = live_chunks(n_b, chunk_tokens);
+    if (chunk >= live) return;
+    int tw0, tw1;                                               // this wave's rows: whole turns of the stage ring but for the last wave's
+    wave_rows(n_b, live, 16 * COVM_STAGES, 4 * chunk + wave, tw0, tw1);
+    tw0 = __builtin_amdgcn_readfirstlane(tw0);
+    tw1 = __builtin_amdgcn_readfirstlane(tw1);
     const int nks = tw1 > tw0 ? (tw1 - tw0 + 15) >> 4 : 0;      // 16-token k-steps, the last may be partial
     const int nfull = tw1 > tw0 ? (tw1 - tw0) >> 4 : 0;         // k-steps with all 16 tokens valid
     const bf16_t* base = (const bf16_t*)rows.data;
@@ -271,24 +280,34 @@ __global__ __launch_bounds__(256) void cov_partial_mfma(RowsDev rows, int Hkv, i
     if (nks > 0) {
         uint4 st[COVM_STAGES][8];
         int ks = 0;
-        // Every wave owns a run of TPW rows (256 TPW bytes at a multiple of that); walking them all from
+        // Every wave owns a run of rows (often 256 x a power of two bytes at a multiple of that); walking them all from
         // the start would keep the 1024 waves of the grid on the same few HBM channels at any
         // instant.  A full wave therefore starts at a wave/chunk/head dependent
         // k-step and wraps around (the sum is order-independent up to fp32 rounding, and the
         // order is still fixed for a given launch shape).
-        constexpr int NKW = TPW / 16;
-        const int shift = (nfull == NKW) ? ((wave * 8 + chunk * 5 + u * 11) & (NKW - 1)) : 0;
-#define KSTEP_TOK(i) (16 * (((i) + shift) & (NKW - 1)))
+        const bool wraps = nfull == nks && nks >= 2 * COVM_STAGES && nks % COVM_STAGES == 0;
+        const int shift = wraps ? ((wave * 8 + chunk * 5 + u * 11) & ((1 << (31 - __clz(nks))) - 1)) : 0;
+        int at = shift;                                             // the k-step that is requested next
+        auto next_tok = [&]() {
+            const int tok = 16 * at;
+            ++at;
+            at = wraps && at == nks ? 0 : at;
+            return tok;
+        };
         if (GATHER && nfull >= 2 * COVM_STAGES) {
             int ix[COVM_STAGES][8];
-            const int last = nfull == NKW ? 2 * NKW : nfull - 1;      // (a full wave wraps; the rows behind another's last full step are read, not used)
+            const int last = nfull - 1;             // (behind the last full step of a wave that does not wrap it is read again, not used)
+            auto next_full = [&]() {
+                const int tok = next_tok();
+                return wraps ? tok : min(tok, 16 * last);
+            };
 #pragma unroll
-            for (int s = 0; s < COVM_STAGES; ++s) covm_load_idx_full(ix[s], list, tw0 + KSTEP_TOK(s) + 8 * g2);
+            for (int s = 0; s < COVM_STAGES; ++s) covm_load_idx_full(ix[s], list, tw0 + next_full() + 8 * g2);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int s = 0; s < COVM_STAGES; ++s) {
                 covm_load_rows(st[s], base, hb, rst, ix[s], o);
-                covm_load_idx_full(ix[s], list, tw0 + KSTEP_TOK(s + COVM_STAGES) + 8 * g2);
+                covm_load_idx_full(ix[s], list, tw0 + next_full() + 8 * g2);
                 __builtin_amdgcn_sched_barrier(0);
             }
             for (; ks + 2 * COVM_STAGES <= nfull; ks += COVM_STAGES) {
@@ -296,7 +315,7 @@ __global__ __launch_bounds__(256) void cov_partial_mfma(RowsDev rows, int Hkv, i
                 for (int s = 0; s < COVM_STAGES; ++s) {
                     covm_step(st[s], sel, acc, csum);
                     covm_load_rows(st[s], base, hb, rst, ix[s], o);           // k-step ks + s + STAGES
-                    covm_load_idx_full(ix[s], list, tw0 + KSTEP_TOK(min(ks + s + 2 * COVM_STAGES, last)) + 8 * g2);
+                    covm_load_idx_full(ix[s], list, tw0 + next_full() + 8 * g2);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -306,15 +325,14 @@ __global__ __launch_bounds__(256) void cov_partial_mfma(RowsDev rows, int Hkv, i
             // (a conservative wait-count state entering the loop would be paid every iteration).
 #pragma unroll
             for (int s = 0; s < COVM_STAGES; ++s) {
-                covm_load_full<GATHER>(st[s], base, hb, rst, list, tw0 + KSTEP_TOK(s) + 8 * g2, o, lane_ptr, KSTEP_TOK(s));
+                covm_load_full(st[s], lane_ptr + (int64_t)next_tok() * rst, rst);
                 __builtin_amdgcn_sched_barrier(0);      // stage 0 must be the OLDEST load on loop entry
             }
             for (; ks + 2 * COVM_STAGES <= nfull; ks += COVM_STAGES) {
 #pragma unroll
                 for (int s = 0; s < COVM_STAGES; ++s) {
                     covm_step(st[s], sel, acc, csum);
-                    covm_load_full<GATHER>(st[s], base, hb, rst, list, tw0 + KSTEP_TOK(ks + s + COVM_STAGES) + 8 * g2, o,
-                                           lane_ptr, KSTEP_TOK(ks + s + COVM_STAGES));
+                    covm_load_full(st[s], lane_ptr + (int64_t)next_tok() * rst, rst);
                     // keep "consume stage s, refill stage s" together: without this the scheduler
                     // hoists all four stages' math above all 32 loads and the pipeline collapses
                     __builtin_amdgcn_sched_barrier(0);
@@ -322,25 +340,35 @@ __global__ __launch_bounds__(256) void cov_partial_mfma(RowsDev rows, int Hkv, i
             }
         } else {
 #pragma unroll
-            for (int s = 0; s < COVM_STAGES; ++s)
-                covm_load<GATHER>(st[s], base, hb, rst, list, tw0 + 16 * s + 8 * g2, s < nks ? tw1 : 0, tw1 - 1, o);
+            for (int s = 0; s < COVM_STAGES; ++s) covm_load<GATHER>(st[s], base, hb, rst, list, tw0 + 16 * s + 8 * g2, tw1 - 1, o);
         }
-        // remaining k-steps (at most 2 STAGES - 1 after a steady loop), the last possibly partial
-        for (; ks < nks; ks += COVM_STAGES) {
+        // The stages in flight, and in the last wave of a sequence (or a short one) up to as many k-steps again, the last of them
+        // possibly partial: all requested before the first is waited for.
+        const int left = nks - ks;
+        int ix[COVM_STAGES][8];
+        if (GATHER && left > COVM_STAGES) {
 #pragma unroll
-            for (int s = 0; s < COVM_STAGES; ++s) {
-                if (ks + s < nks) {
-                    covm_step(st[s], sel, acc, csum);
-                    if (ks + s + COVM_STAGES < nks)
-                        covm_load<GATHER>(st[s], base, hb, rst, list,
-                                          tw0 + (shift ? KSTEP_TOK(ks + s + COVM_STAGES) : 16 * (ks + s + COVM_STAGES)) + 8 * g2,
-                                          tw1, tw1 - 1, o);
-                }
+            for (int s = 0; s < COVM_STAGES; ++s) covm_load_idx(ix[s], list, tw0 + 16 * (ks + s + COVM_STAGES) + 8 * g2, tw1 - 1);
+        }
+        auto step = [&](int s, int k) {
+            if (k >= nks) return;
+            if (k == nfull) covm_zero_past(st[s], tw0 + 16 * k + 8 * g2, tw1);
+            covm_step(st[s], sel, acc, csum);
+        };
+#pragma unroll
+        for (int s = 0; s < COVM_STAGES; ++s) {
+            step(s, ks + s);
+            if (s + COVM_STAGES < left) {
+                if (GATHER) covm_load_rows(st[s], base, hb, rst, ix[s], o);
+                else covm_load<false>(st[s], base, hb, rst, list, tw0 + 16 * (ks + s + COVM_STAGES) + 8 * g2, tw1 - 1, o);
             }
+        }
+        if (left > COVM_STAGES) {
+#pragma unroll
+            for (int s = 0; s < COVM_STAGES; ++s) step(s, ks + s + COVM_STAGES);
         }
     }
 
-#undef KSTEP_TOK
     // ---- sum the four waves, every element as ((w0 + w1) + w2) + w3 ----------------------
     // The 160 accumulators of a lane form 40 groups of four, g = 4 tile + i / 4.  Wave w owns
     // groups [10 w, 10 w + 10): it parks the 30 groups it does not own, and after ONE barrier
@@ -388,8 +416,10 @@ __global__ __launch_bounds__(256) void cov_partial_f32(RowsDev rows, int Hkv, in
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int hh = lane >> 5, m = lane & 31;
     const int n_b = rows_count(rows, b);
-    const int quarter = chunk_tokens / 4;
-    const int t0 = chunk * chunk_tokens + wave * quarter, t1 = min(t0 + quarter, n_b);
+    const int live = live_chunks(n_b, chunk_tokens);
+    if (chunk >= live) return;
+    int t0, t1;
+    wave_rows(n_b, live, 2 * COVF_STAGES, 4 * chunk + wave, t0, t1);
     const int nst = t1 > t0 ? (t1 - t0 + 1) >> 1 : 0;
     const float* base = (const float*)rows.data + (int64_t)b * rows.sb + (int64_t)h * rows.sh + 4 * m;
     const int32_t* list = GATHER ? rows.tok_idx + rows.tok_off[b] : nullptr;
@@ -505,7 +535,7 @@ __global__ __launch_bounds__(256) void cov_finalize(RowsDev rows, int Hkv, int n
 // and off-diagonal elements of diagonal tiles, cov[c][r] is written by its own position or
 // mirrored here.  Grid (40, U): 10 tiles x 1024 positions per (b, h_kv).
 template <bool F32>
-__global__ __launch_bounds__(256) void cov_finalize_tiled(RowsDev rows, int Hkv, int n_chunks, int center,
+__global__ __launch_bounds__(256) void cov_finalize_tiled(RowsDev rows, int Hkv, int slots, int chunk_tokens, int center,
                                                           const float* __restrict__ part_S,
                                                           const float* __restrict__ part_sum,
                                                           float* __restrict__ cov, float* __restrict__ mu_out)
@@ -513,23 +543,23 @@ __global__ __launch_bounds__(256) void cov_finalize_tiled(RowsDev rows, int Hkv,
     const int u = blockIdx.y, b = u / Hkv;
     const int tid = threadIdx.x;
     const int n_b = rows_count(rows, b);
+    const int n_chunks = min(live_chunks(n_b, chunk_tokens), slots), last = max(n_chunks - 1, 0);
     __shared__ double smu[D];
     const int posn = blockIdx.x * 256 + tid;            // [tile][i / 4][lane][i % 4], 0 .. 10239
-    const float* pS = part_S + (size_t)u * n_chunks * (D * D) + posn;
+    const float* pS = part_S + (size_t)u * slots * (D * D) + posn;
     // the first 8 chunks of this position: requested before the mean is formed
     float v0[8];
-    const int first = min(n_chunks, 8);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) v0[k] = pS[(size_t)min(k, first - 1) * (D * D)];
+    for (int k = 0; k < 8; ++k) v0[k] = pS[(size_t)min(k, last) * (D * D)];
     if (tid < D) {
         // column sums of the chunks, eight loads in flight at a time (one at a time this loop was most of
         // the kernel: eight dependent round trips), added in ascending chunk order
-        const float* ps = part_sum + (size_t)u * n_chunks * D + tid;
+        const float* ps = part_sum + (size_t)u * slots * D + tid;
         double s = 0.0;
         for (int ch = 0; ch < n_chunks; ch += 8) {
             float v[8];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] = ps[(size_t)min(ch + k, n_chunks - 1) * D];
+            for (int k = 0; k < 8; ++k) v[k] = ps[(size_t)min(ch + k, last) * D];
 #pragma unroll
             for (int k = 0; k < 8; ++k) s += ch + k < n_chunks ? (double)v[k] : 0.0;
         }
@@ -540,10 +570,9 @@ __global__ __launch_bounds__(256) void cov_finalize_tiled(RowsDev rows, int Hkv,
     __syncthreads();
     double acc = 0.0;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) acc += k < first ? (double)v0[k] : 0.0;          // ascending chunk order
+    for (int k = 0; k < 8; ++k) acc += k < n_chunks ? (double)v0[k] : 0.0;          // ascending chunk order
     for (int ch = 8; ch < n_chunks; ch += 8) {
         float v[8];
-        const int last = n_chunks - 1;
 #pragma unroll
         for (int k = 0; k < 8; ++k) v[k] = pS[(size_t)min(ch + k, last) * (D * D)];
 #pragma unroll
@@ -568,7 +597,7 @@ __global__ __launch_bounds__(256) void cov_finalize_tiled(RowsDev rows, int Hkv,
 // cov_finalize_tiled every position stores four bytes here and four there, a line's pieces from work-groups on different XCDs, and
 // 40 work-groups per unit form the mean.  128 units of 3 chunks 12.8 -> 9.8 us, 512 of one 35.7 -> 17.2.
 template <bool F32>
-__global__ __launch_bounds__(256) void cov_finalize_rows(RowsDev rows, int Hkv, int n_chunks, int center,
+__global__ __launch_bounds__(256) void cov_finalize_rows(RowsDev rows, int Hkv, int slots, int chunk_tokens, int center,
                                                          const float* __restrict__ part_S, const float* __restrict__ part_sum,
                                                          float* __restrict__ cov, float* __restrict__ mu_out)
 {
@@ -577,24 +606,25 @@ __global__ __launch_bounds__(256) void cov_finalize_rows(RowsDev rows, int Hkv, 
     __shared__ __attribute__((aligned(16))) float out[32 * LD];
     const int u = blockIdx.y, q = blockIdx.x, b = u / Hkv, tid = threadIdx.x, lane = tid & 63;
     const int n_b = rows_count(rows, b);
+    const int n_chunks = min(live_chunks(n_b, chunk_tokens), slots), last = max(n_chunks - 1, 0);
     // four positions of each tile: groups [tile][i / 4][lane][i % 4] of cov_partial_mfma
-    const f32x4* pS = (const f32x4*)(part_S + (size_t)u * n_chunks * (D * D)) + tid;
+    const f32x4* pS = (const f32x4*)(part_S + (size_t)u * slots * (D * D)) + tid;
     auto tile = [&](int c) { const int lo = min(q, c), hi = max(q, c); return 4 * lo - lo * (lo - 1) / 2 + hi - lo; };
     f32x4 v[NC][4];
     auto load = [&](int ch) {
 #pragma unroll
         for (int k = 0; k < NC; ++k)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) v[k][c] = pS[(size_t)min(ch + k, n_chunks - 1) * (D * D / 4) + 256 * tile(c)];
+            for (int c = 0; c < 4; ++c) v[k][c] = pS[(size_t)min(ch + k, last) * (D * D / 4) + 256 * tile(c)];
     };
     load(0);                                            // requested before the mean is formed
     if (tid < D) {
-        const float* ps = part_sum + (size_t)u * n_chunks * D + tid;
+        const float* ps = part_sum + (size_t)u * slots * D + tid;
         double s = 0.0;
         for (int ch = 0; ch < n_chunks; ch += 8) {
             float w[8];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) w[k] = ps[(size_t)min(ch + k, n_chunks - 1) * D];
+            for (int k = 0; k < 8; ++k) w[k] = ps[(size_t)min(ch + k, last) * D];
 #pragma unroll
             for (int k = 0; k < 8; ++k) s += ch + k < n_chunks ? (double)w[k] : 0.0;
         }
@@ -674,42 +704,16 @@ int cov_chunk_tokens(int dtype, bool mfma, int64_t units, int max_tokens, int n_
     return best;
 }
 
-template <int TPW>
-static hipError_t launch_cov_mfma(const RowsDev& rows, dim3 grid, int Hkv, int n_chunks, float* part_S, float* part_sum,
-                                  hipStream_t st)
-{
-    static_assert(TPW % 16 == 0 && ((TPW / 16) & (TPW / 16 - 1)) == 0, "k-steps of a wave wrap by mask");
-    const hipError_t e = allow_dynamic_lds(rows.tok_idx ? (const void*)cov_partial_mfma<true, TPW>
-                                                        : (const void*)cov_partial_mfma<false, TPW>, COVM_LDS_BYTES);
-    if (e != hipSuccess) return e;
-    if (rows.tok_idx)
-        hipLaunchKernelGGL((cov_partial_mfma<true, TPW>), grid, dim3(256), COVM_LDS_BYTES, st, rows, Hkv, n_chunks, part_S,
-                           part_sum);
-    else
-        hipLaunchKernelGGL((cov_partial_mfma<false, TPW>), grid, dim3(256), COVM_LDS_BYTES, st, rows, Hkv, n_chunks, part_S,
-                           part_sum);
-    return hipGetLastError();
-}
-
 hipError_t launch_cov_partial(int dtype, bool mfma, const RowsDev& rows, int B, int Hkv, int n_chunks, int chunk_tokens,
                               float* part_S, float* part_sum, hipStream_t st)
 {
     dim3 grid(n_chunks, Hkv, B);
     if (mfma) {
-        if (dtype == 1) {
-            if (chunk_tokens == 512) return launch_cov_mfma<128>(rows, grid, Hkv, n_chunks, part_S, part_sum, st);
-            if (chunk_tokens == 1024) return launch_cov_mfma<256>(rows, grid, Hkv, n_chunks, part_S, part_sum, st);
-            return launch_cov_mfma<512>(rows, grid, Hkv, n_chunks, part_S, part_sum, st);
-        }
-        hipError_t e = allow_dynamic_lds(rows.tok_idx ? (const void*)cov_partial_f32<true> : (const void*)cov_partial_f32<false>,
-                                         COVM_LDS_BYTES);
+        const auto kernel = dtype == 1 ? (rows.tok_idx ? cov_partial_mfma<true> : cov_partial_mfma<false>)
+                                       : (rows.tok_idx ? cov_partial_f32<true> : cov_partial_f32<false>);
+        const hipError_t e = allow_dynamic_lds((const void*)kernel, COVM_LDS_BYTES);
         if (e != hipSuccess) return e;
-        if (rows.tok_idx)
-            hipLaunchKernelGGL(cov_partial_f32<true>, grid, dim3(256), COVM_LDS_BYTES, st, rows, Hkv, n_chunks, chunk_tokens,
-                               part_S, part_sum);
-        else
-            hipLaunchKernelGGL(cov_partial_f32<false>, grid, dim3(256), COVM_LDS_BYTES, st, rows, Hkv, n_chunks, chunk_tokens,
-                               part_S, part_sum);
+        hipLaunchKernelGGL(kernel, grid, dim3(256), COVM_LDS_BYTES, st, rows, Hkv, n_chunks, chunk_tokens, part_S, part_sum);
         return hipGetLastError();
     }
     if (dtype == 0)
@@ -719,7 +723,7 @@ hipError_t launch_cov_partial(int dtype, bool mfma, const RowsDev& rows, int B, 
     return hipGetLastError();
 }
 
-hipError_t launch_cov_finalize(int dtype, bool mfma, const RowsDev& rows, int B, int Hkv, int n_chunks, bool center,
+hipError_t launch_cov_finalize(int dtype, bool mfma, const RowsDev& rows, int B, int Hkv, int n_chunks, int chunk_tokens, bool center,
                                const float* part_S, const float* part_sum, float* cov, float* mu, int n_cu, hipStream_t st)
 {
     // By rows from two work-groups a compute unit on, and not for long sequences of few units: four chunks are in flight in place of
@@ -729,12 +733,12 @@ hipError_t launch_cov_finalize(int dtype, bool mfma, const RowsDev& rows, int B,
     const int U = B * Hkv;
     if (mfma && 2 * U >= n_cu && (n_chunks <= 12 || 2 * U >= 3 * n_cu)) {
         const auto kernel = dtype == 1 ? cov_finalize_rows<false> : cov_finalize_rows<true>;
-        hipLaunchKernelGGL(kernel, dim3(4, U), dim3(256), 0, st, rows, Hkv, n_chunks, center ? 1 : 0, part_S, part_sum, cov, mu);
+        hipLaunchKernelGGL(kernel, dim3(4, U), dim3(256), 0, st, rows, Hkv, n_chunks, chunk_tokens, center ? 1 : 0, part_S, part_sum, cov, mu);
     } else if (mfma && dtype == 1)
-        hipLaunchKernelGGL(cov_finalize_tiled<false>, dim3(40, U), dim3(256), 0, st, rows, Hkv, n_chunks,
+        hipLaunchKernelGGL(cov_finalize_tiled<false>, dim3(40, U), dim3(256), 0, st, rows, Hkv, n_chunks, chunk_tokens,
                            center ? 1 : 0, part_S, part_sum, cov, mu);
     else if (mfma)
-        hipLaunchKernelGGL(cov_finalize_tiled<true>, dim3(40, U), dim3(256), 0, st, rows, Hkv, n_chunks,
+        hipLaunchKernelGGL(cov_finalize_tiled<true>, dim3(40, U), dim3(256), 0, st, rows, Hkv, n_chunks, chunk_tokens,
                            center ? 1 : 0, part_S, part_sum, cov, mu);
     else
         hipLaunchKernelGGL(cov_finalize, dim3(8, U), dim3(256), 0, st, rows, Hkv, n_chunks, center ? 1 : 0,

@@ -19,7 +19,7 @@ int cov_short_chunks(int dtype, int64_t units);       // most chunks under COV_C
 int cov_chunk_tokens(int dtype, bool mfma, int64_t units, int max_tokens, int n_cu);
 hipError_t launch_cov_partial(int dtype, bool mfma, const RowsDev& rows, int B, int Hkv, int n_chunks, int chunk_tokens,
                               float* part_S, float* part_sum, hipStream_t st);
-hipError_t launch_cov_finalize(int dtype, bool mfma, const RowsDev& rows, int B, int Hkv, int n_chunks, bool center,
+hipError_t launch_cov_finalize(int dtype, bool mfma, const RowsDev& rows, int B, int Hkv, int n_chunks, int chunk_tokens, bool center,
                                const float* part_S, const float* part_sum, float* cov, float* mu, int n_cu, hipStream_t st);
 // Cholesky-based subspace iteration (Alg. 1 steps 6-13): V0 [U,d,k] -> Rr [U,d,k], dmu [U,d];
 // status [U] (optional): 0, or t+1 if iteration t met a non-positive pivot.

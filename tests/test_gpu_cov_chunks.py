@@ -88,3 +88,29 @@ def test_reduction_by_rows_keeps_the_bits(dtype, B, L):
         assert torch.equal(got[0][0], torch.cat([c for c, _ in got[1:]]))
         assert torch.equal(got[0][1], torch.cat([m for _, m in got[1:]]))
     rk.rk_destroy(ctx)
+
+
+@pytest.mark.parametrize("dtype,Hkv", [("bf16", 1), ("bf16", 8), ("f32", 1)])      # chunks of 512 and of 2048 tokens; fp32: of 128
+@pytest.mark.parametrize("lists", [False, True])
+def test_shares_of_the_waves(dtype, Hkv, lists):
+    """Lengths that leave the last wave of a sequence whole turns of its ring, one to three k-steps more, a part of one, or nothing."""
+    lengths = [2064, 2080, 2096, 2095, 1553, 1568, 1040, 1056, 528, 544, 560, 576, 144, 160, 192, 255, 257, 64, 63, 65, 16, 15, 17, 1]
+    B, L, ctx = len(lengths), max(lengths), rk.rk_create(0)
+    data = layer(B, Hkv, Hkv, L, dtype, 75, lengths=lengths, mean_shift=2.0)
+    p = Pipeline(ctx, B, Hkv, Hkv, 16, dtype, L)
+    p.cov.fill_(float("nan"))
+    if lists:
+        idx = np.concatenate([np.arange(n - 1, -1, -1) for n in lengths]).astype(np.int32)          # every row, last first
+        off = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+        p.fit(to_dev(data["K"], dtype), L, tok_idx=torch.from_numpy(idx).to(DEV), tok_off=torch.from_numpy(off).to(DEV))
+    else:
+        p.fit(to_dev(data["K"], dtype), L, n_dev=torch.tensor(lengths, device=DEV, dtype=torch.int32))
+    cov, mu = to_host(p.cov), to_host(p.mu)
+    rk.rk_destroy(ctx)
+    for b, n in enumerate(lengths):
+        for h in range(0, Hkv, 5):
+            mu_o, C_o = oracle.mean_scatter(data["K"][b, h, :n])
+            # (what few rows leave behind their mean is the rounding of the products, against their own size)
+            scale = max(np.abs(C_o).max(), 1e-2 * np.abs(data["K"][b, h, :n]).max() ** 2 * n)
+            assert np.abs(cov[b, h] - C_o).max() <= 1e-4 * scale
+            assert rel_max(mu[b, h], mu_o) <= 1e-4
