@@ -1586,24 +1586,29 @@ __global__ __launch_bounds__(256, 2) void decode_split_f32(
 
 // ---------------------------------------------------------------------------
 // Merge folded into the split launch: the splits of a unit share an XCD there, so a unit count that is not a multiple of 8
-// loads the XCDs unevenly (4 units: half of them idle).  The busiest XCD then streams ceil(nunit / 8) * 8 / nunit times
-// its fair share; folded is chosen while that excess, priced at the chip's streaming rate, stays below what the second
-// launch costs (bf16: 4 units x 4K tokens 9.8 us folded against 11.6 us, 4 units x 16K tokens 14.6 against 13.5 us).
-static bool fold_pays(int nunit, int tiles_all, int r, int elem)
-{
-    const double cache_bytes = (double)nunit * tiles_all * 128.0 * (keep_padded(r) + D) * elem;
-    return ((double)((nunit + 7) / 8 * 8) / nunit - 1.0) * cache_bytes / 6.5e6 < 3.0;
-}
-// fp32: besides, the busiest XCD's ceil(nunit / 8) S work-groups may not take more rounds of its compute units than all of them
-// spread over the device would: its second round then starts when the other XCDs are done.  r = 64, folded / two launches: 7 units
-// x 24000 tokens, S = 36, 48.0 / 36.2 us (12000 28.9 / 23.7); 20 x 3000, S = 12, 23.2 / 17.8; 28 x 6000, S = 9, 45.5 / 33.6; with as
-// many rounds 12 x 3000, S = 12, 15.8 / 16.1 and 7 x 6000, S = 23, 19.0 / 19.7; 258 x 2000, S = 4, five rounds either way, 87.9 /
-// 91.5.  Where the rounds are equal the bytes above still tell the sides apart: 68 units x 8000 tokens, 3.8 us of excess, 89.8 / 89.7;
-// x 4000, 1.9 us, 48.7 / 49.5.
-static bool fold_pays_f32(int nunit, int S, int tiles_all, int r, int n_cu)
+// loads the XCDs unevenly, and the busiest one's ceil(nunit / 8) S work-groups may take more rounds of its compute units than all of
+// them spread over the device would; its last round then starts when the other XCDs are done.
+static int64_t fold_rounds(int nunit, int S, int n_cu)
 {
     const int64_t per_xcd = n_cu >= 8 ? n_cu / 8 : 1, busiest = (int64_t)((nunit + 7) / 8) * S, all = (int64_t)nunit * S;
-    return (busiest + per_xcd - 1) / per_xcd <= (all + n_cu - 1) / n_cu && fold_pays(nunit, tiles_all, r, 4);
+    return (busiest + per_xcd - 1) / per_xcd - (all + n_cu - 1) / n_cu;
+}
+// bf16: folded unless there are such rounds (folded / two launches in us: 12 units x 12000 tokens, S = 21, 16.0 / 14.3; 28 x 6000, S = 9, 22.5 / 18.5;
+// 36 x 24000, S = 7, 72 / 56; with as many rounds 4 x 12000, S = 23, 10.3 / 11.6; 44 x 24000, S = 5, 64.8 / 65.6; 258 x 2000, S = 4, 32.1 / 34.7; none of 70
+// such shapes lost more than 2 % by it), or where they are so short that one more costs less than the second launch (84 x 700, S = 3, 75 KB a
+// split: 9.0 / 9.4; x 2000, 213 KB: 16.4 / 14.1).
+static bool fold_pays(int nunit, int S, int tiles_all, int r, int n_cu)
+{
+    const int64_t more = fold_rounds(nunit, S, n_cu);
+    return more <= 0 || (double)more * 128.0 * tiles_all / S * (keep_padded(r) + D) * 2 < 90e3;
+}
+// fp32: not where there are such rounds (r = 64, folded / two launches: 7 units x 24000 tokens, S = 36, 48.0 / 36.2 us; 20 x 3000, S = 12, 23.2 / 17.8;
+// with as many rounds 12 x 3000, S = 12, 15.8 / 16.1; 7 x 6000, S = 23, 19.0 / 19.7), nor where the busiest XCD's share of the bytes, ceil(nunit / 8) * 8 /
+// nunit times the fair one, is 3 us more at the chip's streaming rate (68 x 8000, 3.8 us, 89.8 / 89.7; x 4000, 1.9 us, 48.7 / 49.5).
+static bool fold_pays_f32(int nunit, int S, int tiles_all, int r, int n_cu)
+{
+    const double cache_bytes = (double)nunit * tiles_all * 128.0 * (keep_padded(r) + D) * 4;
+    return fold_rounds(nunit, S, n_cu) <= 0 && ((double)((nunit + 7) / 8 * 8) / nunit - 1.0) * cache_bytes / 6.5e6 < 3.0;
 }
 
 bool decode_mfma_supported(int dtype, int r) { return dtype == 1 && r >= 1 && r <= 128; }
@@ -1660,7 +1665,7 @@ hipError_t launch_decode(int dtype, bool mfma, int B, int Hq, int Hkv, int cap, 
         const int nunit = B * Hkv * ngrp;
         dim3 grid(S, Hkv * ngrp, B);                    // (split, (h_kv, head group), b)
         const bool fused_merge = ((!app && !tapp) || batch_tickets) && (S >= 2 || tapp) && counters && nunit <= n_counters &&
-                                 fold_pays(nunit, tiles_all, r, 2);
+                                 fold_pays(nunit, S, tiles_all, r, n_cu);
         if (fused_merge) grid = dim3((unsigned)(8 * ((nunit + 7) / 8)), (unsigned)S);
         const int nv = text && Sv < S ? Sv : S;
         const DecodeShape sh{Hkv, cap, S, Sv, tiles_all / nv, nv - tiles_all % nv, (int)slab_tokens(cap), sl2};
