@@ -172,12 +172,14 @@ rk_status rk_cache_bytes(const rk_layout* L, size_t* k_packed_bytes, size_t* v_c
  * longer needed: 64 KB for every 512 rows, or with fp32 storage for every 128 rows where those are at
  * most 512 / (B H_kv). */
 size_t rk_fit_workspace_size(const rk_layout* L, int32_t max_tokens);
-/* Bytes of workspace rk_decode_attn needs (depends on batch, heads, max_seq_len). */
+/* Bytes of workspace rk_decode_attn needs (depends on batch, heads, max_seq_len);
+ * what serves one max_seq_len serves every shorter one.                       */
 size_t rk_decode_workspace_size(const rk_ctx* ctx, const rk_layout* L);
 /* The split-K plan rk_decode_attn will use: N_s and the tokens of the largest split
  * (the 128-token tiles are shared out evenly, split sizes differ by at most one
  * tile).  App. C: N_s = max(1, min(ceil(S_v / BLOCK_N), 64)) on the A100; here it
- * is sized to fill 256 compute units.                                         */
+ * is sized to fill 256 compute units, and on short caches by what comes out fastest
+ * (a dual decode, whose text takes splits too, may take fewer).               */
 rk_status rk_decode_plan(const rk_ctx* ctx, const rk_layout* L, int32_t* n_splits, int32_t* tokens_per_split);
 
 /* ---- measurement helper: streaming-read ceiling --------------------------------

@@ -184,30 +184,6 @@ size_t partial_bytes(const rk_layout* L, int slots)
     return align_up((size_t)L->batch * L->n_q_heads * ((size_t)slots * (D + 2) + 1) * sizeof(float), 256);
 }
 
-// N_s, the number of 128-token tiles they share (split s gets floor(tiles / N_s) tiles, the last tiles % N_s splits one
-// more) and the partials the workspace holds per (b, h_q)
-struct DecodePlan { int S, tiles, slots; };
-DecodePlan decode_plan(const rk_ctx* ctx, const rk_layout* L)
-{
-    const int G = L->n_q_heads / L->n_kv_heads;
-    const bool mfma = use_mfma_decode(ctx, L), f32 = mfma && L->dtype == RK_F32;
-    const long rows = (long)L->batch * L->n_q_heads, groups = (long)L->batch * L->n_kv_heads * ((G + 15) / 16);
-    DecodePlan p;
-    p.tiles = ((L->max_seq_len > 0 ? L->max_seq_len : 1) + 127) / 128;
-    // (fp32 rows are twice as long: splits of 256 tokens there)
-    p.S = plan_splits(ctx, mfma ? groups : rows, p.tiles, f32 ? 2 : 4);
-    p.slots = p.S + DECODE_TEXT_SPLITS_MAX;
-    if (f32) {
-        // The size of an fp32 workspace is that of the plain kernel's plan (a split count per query head), by which
-        // rk_decode_attn_static takes or refuses a shape: splits per KV head, up to 16 times as many, may not take it over
-        // the built-in scratch.  The text takes no splits here, so all slots are the cache's.
-        p.slots = plan_splits(ctx, rows, p.tiles, 4) + DECODE_TEXT_SPLITS_MAX;
-        while (p.S > p.slots && partial_bytes(L, p.S) > RK_STATIC_SCRATCH_BYTES) --p.S;
-        if (p.slots < p.S) p.slots = p.S;
-    }
-    return p;
-}
-
 // Splits of a dual decode (bf16 matrix-core kernels) that take text rows alone, next to the S of the cache; 0: every split
 // takes its part of the text in front of its part of the cache.
 int text_splits(const rk_ctx* ctx, const rk_layout* L, int S, int text_rows)
@@ -247,6 +223,64 @@ int text_splits(const rk_ctx* ctx, const rk_layout* L, int S, int text_rows)
     // several rounds: more work-groups pay while the text is short (320 x 1024 tokens, S = 4: 200 rows 33.6 us with one split, 37.1
     // shared; 1024 rows 59 / 57)
     return pieces(256) <= 2 ? (int)pieces(256) : 0;
+}
+
+// More splits than `least` (plan_splits) where units of work-groups leave compute units idle, up to `most`: the count that comes out cheapest.
+//   A split's own time goes by round trips, not by tokens: with 4 waves and two tiles a wave in flight, 256 tokens of bf16 take one (1.5 us at
+//   r = 64, 0.8 for 128), 128 of fp32 2.3 us; a split of text rows beside them some 2.2.  All splits together cannot be faster than the device
+//   streams.  A split more is another prologue and a partial more, folded 4, 8 or 16 a round trip; none with one split.
+// Measured with each count (us): bf16 8 units x 2000 tokens, r = 64: 4 splits 8.0, 6 7.8, 8 6.5, 16 7.0; 2 x 6000: 11 9.6, 16 7.7, 24 7.5, 32 7.6; 32 x
+// 2944: 5 10.3, 6 9.6, 8 10.2; 32 x 1500: 4 8.0, 6 7.6, 8 7.5; 16 x 900, r = 128: 4 7.8, 8 8.0; 8 x 300, r = 32: 1 5.1, 3 5.7; with 64 text rows
+// 8 x 1000, four tokens: 4 29.8, 8 31.1; fp32 8 x 1024, r = 32: 4 10.9, 8 8.6; 32 x 500, r = 64: 2 11.3, 4 9.2.
+int more_splits(const rk_ctx* ctx, const rk_layout* L, long units, int tiles, int least, int most, bool f32, int text_rows)
+{
+    const int token_bytes = (keep_padded(L->keep) + D) * (int)elem_size(L->dtype);
+    const double unit = f32 ? 2.3 * token_bytes / 768 : 1.5 * token_bytes / 384, stream = 128e-6 * units * tiles * token_bytes / 6.5;
+    double best = 1e30;
+    int S = least;
+    for (int c = least, each; c <= most; c = each > 1 ? (tiles + each - 2) / (each - 1) : most + 1) {     // (the fewest splits of a length)
+        each = (tiles + c - 1) / c;
+        const int parts = c + (f32 ? 0 : text_splits(ctx, L, c, text_rows));
+        double own = unit * (f32 ? each : each == 1 ? 0.55 : (each + 1) / 2);
+        if (parts > c && own < 2.2) own = 2.2;
+        const double fold = parts == 1 ? 0.0 : parts <= 4 ? 1.9 : parts <= 8 ? 2.1 : 1.9 + (parts + 15) / 16;
+        const double cost = (own > stream ? own + 0.35 * stream : stream + 0.35 * own) + fold + 0.005 * L->keep / 64 * units * c;
+        if (cost < best - 0.1) { best = cost; S = c; }
+    }
+    return S;
+}
+
+// N_s, the number of 128-token tiles they share (split s gets floor(tiles / N_s) tiles, the last tiles % N_s splits one
+// more) and the partials the workspace holds per (b, h_q): never fewer than a shorter max_seq_len needs
+struct DecodePlan { int S, tiles, slots; };
+DecodePlan decode_plan(const rk_ctx* ctx, const rk_layout* L, int text_rows = 0)
+{
+    const int G = L->n_q_heads / L->n_kv_heads;
+    const bool mfma = use_mfma_decode(ctx, L), f32 = mfma && L->dtype == RK_F32;
+    const long rows = (long)L->batch * L->n_q_heads, groups = (long)L->batch * L->n_kv_heads * ((G + 15) / 16);
+    DecodePlan p;
+    p.tiles = ((L->max_seq_len > 0 ? L->max_seq_len : 1) + 127) / 128;
+    // (fp32 rows are twice as long: splits of 256 tokens there)
+    p.S = plan_splits(ctx, mfma ? groups : rows, p.tiles, f32 ? 2 : 4);
+    int bound = p.S;                                            // of the splits for this max_seq_len and any shorter one
+    const int n_cu = ctx ? ctx->n_cu : 256;
+    if (mfma && !(ctx && ctx->decode_splits > 0) && groups <= n_cu) {
+        const int most = n_cu / groups < 64 ? (int)(n_cu / groups) : 64, here = most < p.tiles ? most : p.tiles;
+        // (no shape may leave the built-in scratch by it: such a one keeps to the fewer splits at every length)
+        if (here > bound && (f32 || partial_bytes(L, most + DECODE_TEXT_SPLITS_MAX) <= RK_STATIC_SCRATCH_BYTES)) bound = here;
+    }
+    p.slots = bound + DECODE_TEXT_SPLITS_MAX;
+    if (f32) {
+        // The size of an fp32 workspace is that of the plain kernel's plan (a split count per query head), by which
+        // rk_decode_attn_static takes or refuses a shape: splits per KV head, up to 16 times as many, may not take it over
+        // the built-in scratch.  The text takes no splits here, so all slots are the cache's.
+        p.slots = plan_splits(ctx, rows, p.tiles, 4) + DECODE_TEXT_SPLITS_MAX;
+        while (bound > p.slots && partial_bytes(L, bound) > RK_STATIC_SCRATCH_BYTES) --bound;
+        if (p.S > bound) p.S = bound;
+        if (p.slots < bound) p.slots = bound;
+    }
+    if (bound > p.S) p.S = more_splits(ctx, L, groups, p.tiles, p.S, bound, f32, text_rows);
+    return p;
 }
 
 hipStream_t as_stream(void* s) { return (hipStream_t)s; }
@@ -638,7 +672,8 @@ static rk_status decode_common(rk_ctx* ctx, const rk_layout* L, const void* q, c
                                text->len, text->capacity};
         }
     }
-    const size_t need = rk_decode_workspace_size(ctx, L);
+    const DecodePlan p = decode_plan(ctx, L, text ? td.max_len : 0);
+    const size_t need = partial_bytes(L, p.slots);
     if (use_static) {
         if (need > (size_t)RK_STATIC_SCRATCH_BYTES)
             return fail(ctx, RK_ERR_WORKSPACE, "decode (static scratch): this shape needs %zu bytes of partials, the "
@@ -653,7 +688,6 @@ static rk_status decode_common(rk_ctx* ctx, const rk_layout* L, const void* q, c
     DeviceGuard dev(ctx->device);
     hipError_t e = dev.status;
     if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
-    const DecodePlan p = decode_plan(ctx, L);
     const int S = p.S;
     const int St = text && L->dtype == RK_BF16 && use_mfma_decode(ctx, L) ? text_splits(ctx, L, S, td.max_len) : 0;
     const float sc = scale > 0.f ? scale : 1.0f / sqrtf((float)L->head_dim);
@@ -725,7 +759,8 @@ rk_status rk_append_decode_attn(rk_ctx* ctx, const rk_layout* L, const void* k_n
     rk_layout La = *L;
     La.max_seq_len = L->max_seq_len + 1;
     La.seq_len = seq_len;
-    const size_t need = rk_decode_workspace_size(ctx, &La);
+    const DecodePlan p = decode_plan(ctx, &La);
+    const size_t need = partial_bytes(&La, p.slots);
     if (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 15))
         return fail(ctx, RK_ERR_WORKSPACE, "append_decode workspace: need %zu bytes, 16-byte aligned", need);
     if (ctx->device == RK_DEVICE_NONE) return fail(ctx, RK_ERR_NO_DEVICE, "valid arguments, but the context has no device");
@@ -734,7 +769,6 @@ rk_status rk_append_decode_attn(rk_ctx* ctx, const rk_layout* L, const void* k_n
     hipError_t e = dev.status;
     if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
     hipStream_t st = as_stream(stream);
-    const DecodePlan p = decode_plan(ctx, &La);
     const float sc = scale > 0.f ? scale : 1.0f / sqrtf((float)L->head_dim);
     const bool mfma = use_mfma_decode(ctx, L);
     const AppendDev app{k_new, v_new, seq_len};
