@@ -88,6 +88,12 @@ rk_status check_rows(rk_ctx* ctx, const rk_layout* L, const rk_rows* r, const ch
     return RK_OK;
 }
 
+bool ranges_meet(const void* a, size_t a_bytes, const void* b, size_t b_bytes)
+{
+    const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+    return x < y + b_bytes && y < x + a_bytes;
+}
+
 RowsDev to_dev(const rk_rows* r)
 {
     RowsDev d;
@@ -609,14 +615,22 @@ rk_status rk_compress(rk_ctx* ctx, const rk_layout* L, const rk_rows* keys, cons
     hipError_t e = dev.status;
     if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
     hipStream_t st = as_stream(stream);
-    e = launch_compress(L->dtype, !ctx->force_generic, to_dev(keys), L->batch, L->n_kv_heads, L->capacity, L->keep,
-                        R_r, k_packed, seq_len_out, ctx->n_cu, st);
-    if (e != hipSuccess) return hip_fail(ctx, e, "compress launch");
+    RowsDev vals;
+    bool join = false;
     if (values) {
-        e = launch_v_retile(L->dtype, to_dev(values), L->batch, L->n_kv_heads, L->capacity, v_cache, st);
-        if (e != hipSuccess) return hip_fail(ctx, e, "value re-tiling launch");
+        vals = to_dev(values);
+        // One launch for Keys and Values, except through token lists (every row's address then comes from a load, and the few work-groups that
+        // fit beside the rotation's registers do not hide two round trips: a prefill of 4 x 32 heads, 8192 rows, half of them listed, r = 32,
+        // took 187 us instead of 178) and where the Value cache lies over the Keys or R_r, which must have been read by then.
+        const size_t es = elem_size(L->dtype), units = (size_t)L->batch * L->n_kv_heads;
+        const size_t kb = (size_t)((L->batch - 1) * keys->stride_b + (L->n_kv_heads - 1) * keys->stride_h +
+                                   (int64_t)(keys->n_tokens > 0 ? keys->n_tokens - 1 : 0) * keys->stride_t + D) * es;
+        const size_t vb = units * slab_tokens(L->capacity) * D * es;
+        join = !keys->tok_idx && !ranges_meet(v_cache, vb, keys->data, kb) && !ranges_meet(v_cache, vb, R_r, units * D * L->keep * sizeof(float));
     }
-    return RK_OK;
+    e = launch_compress(L->dtype, !ctx->force_generic, to_dev(keys), L->batch, L->n_kv_heads, L->capacity, L->keep,
+                        R_r, k_packed, seq_len_out, values ? &vals : nullptr, v_cache, join, ctx->n_cu, st);
+    return e == hipSuccess ? RK_OK : hip_fail(ctx, e, "compress launch");
 }
 
 rk_status rk_append(rk_ctx* ctx, const rk_layout* L, const void* k_new, const void* v_new, const float* R_r,

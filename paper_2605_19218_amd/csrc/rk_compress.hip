@@ -43,6 +43,90 @@ __global__ __launch_bounds__(256) void compress_generic(RowsDev rows, int Hkv, i
 }
 
 // ---------------------------------------------------------------------------
+// Values -> fragment-major V cache: NB blocks of 32 tokens from token t0 on, transposed through LDS; rows past the sequence end
+// inside the last block are zero-filled.  All rows are requested before the first is parked (bf16: 32 KB a work-group with NB = 4).
+template <typename T>
+struct alignas(16) Oct { T v[8]; };
+constexpr int RETILE_LD = 17;                    // 16 octets per row + 1 pad
+
+template <typename T, int NB>
+__device__ __forceinline__ void retile_blocks(const RowsDev& rows, int b, int h, int n_b, int t0, T* __restrict__ Vu,
+                                              Oct<T>* __restrict__ tile)
+{
+    const int tid = threadIdx.x;
+    const T* base = (const T*)rows.data;
+    Oct<T> x[2 * NB];
+    auto fetch = [&](int t) { return *(const Oct<T>*)(base + rows_offset(rows, b, h, t) + (tid & 15) * 8); };
+#pragma unroll
+    for (int k = 0; k < 2 * NB; ++k) {           // several blocks: nothing conditional between the loads, the last row in place of those past it
+        const int t = t0 + 16 * k + (tid >> 4);
+        if (NB > 1 || t < n_b) x[k] = fetch(NB > 1 ? min(t, n_b - 1) : t);
+    }
+#pragma unroll
+    for (int k = 0; k < 2 * NB; ++k) {
+        const int row = 16 * k + (tid >> 4);
+        if (t0 + row >= n_b) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[k].v[e] = (T)0;
+        }
+        tile[row * RETILE_LD + (tid & 15)] = x[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 2 * NB; ++k) {
+        const int tb = t0 + 32 * (k >> 1);
+        if (tb >= n_b) break;
+        const int o = tid + 256 * (k & 1);       // piece index: [cb][g][n]
+        const int cb = o >> 6, g = (o >> 4) & 3, n = o & 15;
+        const int c = 16 * cb + n;
+        Oct<T> y;
+#pragma unroll
+        for (int jj = 0; jj < 8; ++jj) {
+            const int tl = 32 * (k >> 1) + (jj < 4 ? 4 * g + jj : 16 + 4 * g + (jj - 4));
+            y.v[jj] = tile[tl * RETILE_LD + (c >> 3)].v[c & 7];
+        }
+        T* to = Vu + (size_t)(tb >> 5) * 4096 + (size_t)o * 8;
+        if constexpr (sizeof(Oct<T>) == 16) nt_store16(to, __builtin_bit_cast(uint4, y));
+        else *(Oct<T>*)to = y;
+    }
+}
+
+// The Values of the call, by work-groups behind those of the Keys in the same launch (grid.z from `batch` on, `per_head` work-groups a
+// head).  They need nothing of the Keys' result, so the launch's ramp and tail are paid once, and the short work-groups
+// here fill up the compute units that the rotation leaves early.
+template <typename T>
+struct ValuesJob {
+    static constexpr int NB = sizeof(T) == 2 ? 4 : 1;
+    static constexpr size_t LDS_BYTES = (size_t)NB * 32 * RETILE_LD * sizeof(Oct<T>);
+    RowsDev rows;
+    T* dst;
+    int batch, heads, per_head;
+};
+struct NoValues {};
+template <typename T, bool VALUES>
+using ValuesArg = std::conditional_t<VALUES, ValuesJob<T>, NoValues>;
+
+template <typename T>
+__device__ __forceinline__ void retile_job(const ValuesJob<T>& v, int Hkv, int cap, Oct<T>* tile)
+{
+    const int id = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * (blockIdx.z - v.batch)), u = id / v.per_head;
+    if (u >= v.heads) return;
+    const int b = u / Hkv, t0 = (id - u * v.per_head) * 32 * ValuesJob<T>::NB;
+    const int n_b = min(rows_count(v.rows, b), cap);
+    if (t0 < n_b) retile_blocks<T, ValuesJob<T>::NB>(v.rows, b, u - b * Hkv, n_b, t0, v.dst + (size_t)u * slab_tokens(cap) * D, tile);
+}
+
+// a launch of its own
+template <typename T>
+__global__ __launch_bounds__(256) void v_retile(RowsDev rows, int Hkv, int cap, T* __restrict__ dst)
+{
+    __shared__ Oct<T> tile[32 * RETILE_LD];
+    const int h = blockIdx.y, b = blockIdx.z;
+    const int n_b = min(rows_count(rows, b), cap), t0 = blockIdx.x * 32;
+    if (t0 < n_b) retile_blocks<T, 1>(rows, b, h, n_b, t0, dst + (size_t)(b * Hkv + h) * slab_tokens(cap) * D, tile);
+}
+
+// ---------------------------------------------------------------------------
 // MFMA kernel (bf16; R = r padded to a multiple of 16, columns r .. R - 1 of R_r read as
 // zero, which writes the layout's zero padding).  Per wave: D^T[j, token] = R_r^T . K^T
 // with v_mfma_f32_16x16x32_bf16; the B operand (lane (g, n): token n, channels
@@ -74,13 +158,21 @@ __device__ __forceinline__ uint32_t pack2_bf16(float a, float b) {
 
 enum { ORDER_FEW, ORDER_MANY, ORDER_PART_LAST };
 
-template <int R, bool GATHER>
+// VALUES: the launch also lays out the Values (a kernel of its own: with the branch in every launch, 4 x 32 heads through token lists took 23.2
+// us instead of 20.9).
+template <int R, bool GATHER, bool VALUES>
 __global__ __launch_bounds__(256, 2) void compress_mfma(RowsDev rows, int Hkv, int cap, int r, int order,
                                                      const float* __restrict__ Rr, bf16_t* __restrict__ Kp,
-                                                     int32_t* __restrict__ seq_len_out)
+                                                     int32_t* __restrict__ seq_len_out, ValuesArg<bf16_t, VALUES> vals)
 {
     typedef CompressCfg<R> Cfg;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    if constexpr (VALUES) {
+        if ((int)blockIdx.z >= vals.batch) {
+            retile_job(vals, Hkv, cap, (Oct<bf16_t>*)smem_raw);
+            return;
+        }
+    }
     bf16x8* frag = (bf16x8*)smem_raw;       // [JB][4][2][64]
 
     // ORDER_PART_LAST: the last block number is a partly filled one.  Its work-groups then start behind all others, where they fill
@@ -88,8 +180,10 @@ __global__ __launch_bounds__(256, 2) void compress_mfma(RowsDev rows, int Hkv, i
     // (16 x 16 heads x 600 rows, r = 32: 15.4 -> 11.8 us; 4 x 32 x 2100, r = 128: 43 -> 34.6; 1 x 32 x 16500, r = 64: 45.7 -> 41.6).
     int h = blockIdx.y, b = blockIdx.z, nx = gridDim.x, bx = blockIdx.x;
     bool rotate = true;
+    int vals_batch = gridDim.z;
+    if constexpr (VALUES) vals_batch = vals.batch;
     if (order == ORDER_PART_LAST) {
-        const int id = bx + nx * (h + Hkv * b), full = --nx * (int)(gridDim.y * gridDim.z);
+        const int id = bx + nx * (h + Hkv * b), full = --nx * (int)gridDim.y * vals_batch;
         rotate = id < full;
         const int w = rotate ? id / nx : id - full;
         bx = __builtin_amdgcn_readfirstlane(rotate ? id - w * nx : nx);
@@ -300,12 +394,19 @@ __global__ __launch_bounds__(256, 2) void compress_mfma(RowsDev rows, int Hkv, i
 // tiles per wave.  Bound: the fp32 matrix rate (2 R MFMA of 32 cycles per tile), close to the memory time.
 // (32 heads x 2944 tokens, r = 64: 154 us through the plain kernel, whose every output is a 128-step loop over R_r
 // in memory; 24 us here, 27 on cold Keys.)
-template <int R>
+template <int R, bool VALUES>
 __global__ __launch_bounds__(256) void compress_f32(RowsDev rows, int Hkv, int cap, int r, const float* __restrict__ Rr,
-                                                    float* __restrict__ Kp, int32_t* __restrict__ seq_len_out)
+                                                    float* __restrict__ Kp, int32_t* __restrict__ seq_len_out,
+                                                    ValuesArg<float, VALUES> vals)
 {
     constexpr int JB = R / 16, TT = 2, TOK = 4 * TT * 16;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    if constexpr (VALUES) {
+        if ((int)blockIdx.z >= vals.batch) {
+            retile_job(vals, Hkv, cap, (Oct<float>*)smem_raw);
+            return;
+        }
+    }
     f32x4* frag = (f32x4*)smem_raw;         // [JB][8][64]
     const int h = blockIdx.y, b = blockIdx.z, u = b * Hkv + h;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, n = lane & 15;
@@ -360,51 +461,6 @@ __global__ __launch_bounds__(256) void compress_f32(RowsDev rows, int Hkv, int c
             if (w0 + 16 * tt + n < n_b)
                 __builtin_nontemporal_store(acc[tt], (f32x4*)(Ku + (size_t)((w0 >> 4) + tt) * (16 * R) +
                                                               (2 * jb + (g >> 1)) * 128 + n * 8 + 4 * (g & 1)));
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Values -> fragment-major V cache: one block per 32-token block, transposed
-// through LDS; rows past the sequence end inside the last block are zero-filled.
-template <typename T>
-struct alignas(16) Oct { T v[8]; };
-
-template <typename T>
-__global__ __launch_bounds__(256) void v_retile(RowsDev rows, int Hkv, int cap, T* __restrict__ dst)
-{
-    const int h = blockIdx.y, b = blockIdx.z, u = b * Hkv + h;
-    const int tid = threadIdx.x;
-    const int n_b = min(rows_count(rows, b), cap);
-    const int t0 = blockIdx.x * 32;
-    if (t0 >= n_b) return;
-    __shared__ Oct<T> tile[32][17];              // 16 octets per row + 1 pad
-    const T* base = (const T*)rows.data;
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        int p = tid + 256 * k, row = p >> 4, oc = p & 15;
-        Oct<T> x;
-        if (t0 + row < n_b) x = *(const Oct<T>*)(base + rows_offset(rows, b, h, t0 + row) + oc * 8);
-        else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) x.v[e] = (T)0;
-        }
-        tile[row][oc] = x;
-    }
-    __syncthreads();
-    T* Vu = dst + (size_t)u * slab_tokens(cap) * D + (size_t)blockIdx.x * 4096;
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        int o = tid + 256 * k;                   // piece index: [cb][g][n]
-        int cb = o >> 6, g = (o >> 4) & 3, n = o & 15;
-        int c = 16 * cb + n;
-        Oct<T> x;
-#pragma unroll
-        for (int jj = 0; jj < 8; ++jj) {
-            int tl = jj < 4 ? 4 * g + jj : 16 + 4 * g + (jj - 4);
-            x.v[jj] = tile[tl][c >> 3].v[c & 7];
-        }
-        if constexpr (sizeof(Oct<T>) == 16) nt_store16(Vu + (size_t)o * 8, __builtin_bit_cast(uint4, x));
-        else *(Oct<T>*)(Vu + (size_t)o * 8) = x;
     }
 }
 
@@ -484,6 +540,31 @@ __global__ __launch_bounds__(256) void unpack_cache(int cap, int r, const T* __r
 }
 
 // ---------------------------------------------------------------------------
+template <typename T>
+static hipError_t launch_v_retile(const RowsDev& rows, int B, int Hkv, int cap, T* dst, hipStream_t st)
+{
+    const int nblk = rows.n_tokens > 0 ? (rows.n_tokens + 31) / 32 : 1;
+    hipLaunchKernelGGL(v_retile<T>, dim3(nblk, Hkv, B), dim3(256), 0, st, rows, Hkv, cap, dst);
+    return hipGetLastError();
+}
+
+// The Values' work-groups behind the Keys' (`grid`, one entry of z per batch item), as many more entries of z as hold them.  False: no
+// Values (or no rows), or more of their work-groups than `most`, than a grid's third dimension or than an int32 index takes; they then get a launch
+// of their own.
+template <typename T>
+static bool add_values(const RowsDev* values, T* Vc, int B, int Hkv, int64_t most, dim3& grid, ValuesJob<T>& vals)
+{
+    vals = ValuesJob<T>{RowsDev{}, Vc, B, 0, 1};
+    if (!values) return false;
+    constexpr int TOK = 32 * ValuesJob<T>::NB;
+    const int64_t per_head = ((int64_t)values->n_tokens + TOK - 1) / TOK, heads = (int64_t)B * Hkv;
+    const int64_t per_z = (int64_t)grid.x * grid.y, more = (per_head * heads + per_z - 1) / per_z;
+    if (per_head == 0 || per_head * heads > most || B + more > 65535 || more * per_z > INT32_MAX) return false;
+    vals = ValuesJob<T>{*values, Vc, B, (int)heads, (int)per_head};
+    grid.z += (unsigned)more;
+    return true;
+}
+
 // 512 tokens per work-group.  With 2048 (one R_r fragment build per 2048 rows) the last work-groups decide the time of the launch,
 // most where the lengths are on the device (token lists, n_tokens_dev) and the host's bound does not say how many blocks have
 // rows, and at some distances of the caches' slabs their concurrent streams meet in the same memory channels.  Call without Values,
@@ -491,59 +572,78 @@ __global__ __launch_bounds__(256) void unpack_cache(int cap, int r, const T* __r
 // 16 x 16 x 2048 38 / 41.  r = 128, where the fragments are 64 KB: 1 x 32 x 16384 54 / 56; 16 x 16 x 2048 55 / 60; 1 x 64 x 8192 (slabs 8256
 // tokens apart) 76 / 59; 1 x 16 x 32768 (33088 apart) 64 / 59.  With 1024: 56, 58, 62, 61, but 16 x 16 x 1536 ragged 41 / 30.
 template <int R>
-static hipError_t launch_compress_mfma_r(const RowsDev& rows, int B, int Hkv, int cap, int r, const float* Rr,
-                                         bf16_t* Kp, int32_t* seq_len_out, int n_cu, hipStream_t st)
+static hipError_t launch_compress_mfma_r(const RowsDev& rows, int B, int Hkv, int cap, int r, const float* Rr, bf16_t* Kp,
+                                         int32_t* seq_len_out, const RowsDev* values, bf16_t* Vc, bool join, int n_cu, hipStream_t st)
 {
     typedef CompressCfg<R> Cfg;
     int nblk = (rows.n_tokens + Cfg::TOK_PER_BLOCK - 1) / Cfg::TOK_PER_BLOCK;
     if (nblk < 1) nblk = 1;
     const bool part = nblk > 1 && rows.n_tokens % Cfg::TOK_PER_BLOCK != 0 && (int64_t)Hkv * B <= INT32_MAX / nblk;
     const int order = (int64_t)Hkv * B * nblk <= n_cu ? ORDER_FEW : part ? ORDER_PART_LAST : ORDER_MANY;
-    const auto kernel = rows.tok_idx ? compress_mfma<R, true> : compress_mfma<R, false>;
-    hipLaunchKernelGGL(kernel, dim3(nblk, Hkv, B), dim3(256), Cfg::LDS_BYTES, st, rows, Hkv, cap, r, order, Rr, Kp, seq_len_out);
-    return hipGetLastError();
+    dim3 grid(nblk, Hkv, B);
+    ValuesJob<bf16_t> vals;
+    // In the rotation's registers a compute unit holds two (R = 48, 64) or three work-groups that re-tile, eight in a launch of their own.
+    // That is enough while the rows are in the last-level cache, and with R >= 80, where the rotation itself leaves bandwidth over; beyond,
+    // the joined launch is the slower one.  Two launches / one, 32 heads, us: 6100 tokens 32, 35, 37, 41 / 26, 30, 31, 34 (r = 32, 48, 64, 96);
+    // 10000 tokens (9.9 work-groups of the Values per compute unit) 49, 53, 55, 61 / 44, 50, 51, 50; 14000: 69, 73, 76, 84 / 70, 82, 85, 82;
+    // 26000: 126, 132, 137, 152 / 125, 147, 152, 147.  1 x 8 x 1024, r = 32: 9.9 / 7.8; 1 x 4 x 32768, r = 128: 28 / 24.
+    const bool joined = add_values(join ? values : nullptr, Vc, B, Hkv, R >= 80 ? INT64_MAX : 10 * (int64_t)n_cu, grid, vals);
+    const size_t lds = joined && ValuesJob<bf16_t>::LDS_BYTES > Cfg::LDS_BYTES ? ValuesJob<bf16_t>::LDS_BYTES : Cfg::LDS_BYTES;
+    if (joined)
+        hipLaunchKernelGGL((compress_mfma<R, false, true>), grid, dim3(256), lds, st, rows, Hkv, cap, r, order, Rr, Kp, seq_len_out, vals);
+    else
+        hipLaunchKernelGGL((rows.tok_idx ? compress_mfma<R, true, false> : compress_mfma<R, false, false>), grid, dim3(256), lds, st, rows, Hkv,
+                           cap, r, order, Rr, Kp, seq_len_out, NoValues{});
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess && values && !joined ? launch_v_retile(*values, B, Hkv, cap, Vc, st) : e;
 }
 
 template <int R>
 static hipError_t launch_compress_f32_r(const RowsDev& rows, int B, int Hkv, int cap, int r, const float* Rr, float* Kp,
-                                        int32_t* seq_len_out, hipStream_t st)
+                                        int32_t* seq_len_out, const RowsDev* values, float* Vc, bool join, hipStream_t st)
 {
-    constexpr size_t lds = (size_t)(R / 16) * 8 * 64 * 16;
-    const hipError_t e = allow_dynamic_lds((const void*)compress_f32<R>, lds);
+    constexpr size_t own = (size_t)(R / 16) * 8 * 64 * 16;
+    dim3 grid(rows.n_tokens > 0 ? (rows.n_tokens + 127) / 128 : 1, Hkv, B);
+    ValuesJob<float> vals;
+    // (two launches / one, r = 64: 32 heads x 2944 tokens 46 / 37 us, x 16000 206 / 189)
+    const bool joined = add_values(join ? values : nullptr, Vc, B, Hkv, INT64_MAX, grid, vals);
+    const size_t lds = joined && ValuesJob<float>::LDS_BYTES > own ? ValuesJob<float>::LDS_BYTES : own;
+    hipError_t e = allow_dynamic_lds(joined ? (const void*)compress_f32<R, true> : (const void*)compress_f32<R, false>, lds);
     if (e != hipSuccess) return e;
-    const int nblk = rows.n_tokens > 0 ? (rows.n_tokens + 127) / 128 : 1;
-    hipLaunchKernelGGL(compress_f32<R>, dim3(nblk, Hkv, B), dim3(256), lds, st, rows, Hkv, cap, r, Rr, Kp, seq_len_out);
-    return hipGetLastError();
+    if (joined) hipLaunchKernelGGL((compress_f32<R, true>), grid, dim3(256), lds, st, rows, Hkv, cap, r, Rr, Kp, seq_len_out, vals);
+    else hipLaunchKernelGGL((compress_f32<R, false>), grid, dim3(256), lds, st, rows, Hkv, cap, r, Rr, Kp, seq_len_out, NoValues{});
+    e = hipGetLastError();
+    return e == hipSuccess && values && !joined ? launch_v_retile(*values, B, Hkv, cap, Vc, st) : e;
 }
 
-hipError_t launch_compress(int dtype, bool mfma, const RowsDev& rows, int B, int Hkv, int cap, int r,
-                           const float* Rr, void* Kp, int32_t* seq_len_out, int n_cu, hipStream_t st)
+hipError_t launch_compress(int dtype, bool mfma, const RowsDev& rows, int B, int Hkv, int cap, int r, const float* Rr, void* Kp,
+                           int32_t* seq_len_out, const RowsDev* values, void* Vc, bool join, int n_cu, hipStream_t st)
 {
     if (mfma && dtype == 1) {
-        bf16_t* kp = (bf16_t*)Kp;
+        bf16_t *kp = (bf16_t*)Kp, *vc = (bf16_t*)Vc;
         switch (keep_padded(r)) {
-            case 16: return launch_compress_mfma_r<16>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, n_cu, st);
-            case 32: return launch_compress_mfma_r<32>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, n_cu, st);
-            case 48: return launch_compress_mfma_r<48>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, n_cu, st);
-            case 64: return launch_compress_mfma_r<64>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, n_cu, st);
-            case 80: return launch_compress_mfma_r<80>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, n_cu, st);
-            case 96: return launch_compress_mfma_r<96>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, n_cu, st);
-            case 112: return launch_compress_mfma_r<112>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, n_cu, st);
-            case 128: return launch_compress_mfma_r<128>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, n_cu, st);
+            case 16: return launch_compress_mfma_r<16>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, values, vc, join, n_cu, st);
+            case 32: return launch_compress_mfma_r<32>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, values, vc, join, n_cu, st);
+            case 48: return launch_compress_mfma_r<48>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, values, vc, join, n_cu, st);
+            case 64: return launch_compress_mfma_r<64>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, values, vc, join, n_cu, st);
+            case 80: return launch_compress_mfma_r<80>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, values, vc, join, n_cu, st);
+            case 96: return launch_compress_mfma_r<96>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, values, vc, join, n_cu, st);
+            case 112: return launch_compress_mfma_r<112>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, values, vc, join, n_cu, st);
+            case 128: return launch_compress_mfma_r<128>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, values, vc, join, n_cu, st);
             default: break;
         }
     }
     if (mfma && dtype == 0) {
-        float* kp = (float*)Kp;
+        float *kp = (float*)Kp, *vc = (float*)Vc;
         switch (keep_padded(r)) {
-            case 16: return launch_compress_f32_r<16>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, st);
-            case 32: return launch_compress_f32_r<32>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, st);
-            case 48: return launch_compress_f32_r<48>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, st);
-            case 64: return launch_compress_f32_r<64>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, st);
-            case 80: return launch_compress_f32_r<80>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, st);
-            case 96: return launch_compress_f32_r<96>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, st);
-            case 112: return launch_compress_f32_r<112>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, st);
-            case 128: return launch_compress_f32_r<128>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, st);
+            case 16: return launch_compress_f32_r<16>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, values, vc, join, st);
+            case 32: return launch_compress_f32_r<32>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, values, vc, join, st);
+            case 48: return launch_compress_f32_r<48>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, values, vc, join, st);
+            case 64: return launch_compress_f32_r<64>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, values, vc, join, st);
+            case 80: return launch_compress_f32_r<80>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, values, vc, join, st);
+            case 96: return launch_compress_f32_r<96>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, values, vc, join, st);
+            case 112: return launch_compress_f32_r<112>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, values, vc, join, st);
+            case 128: return launch_compress_f32_r<128>(rows, B, Hkv, cap, r, Rr, kp, seq_len_out, values, vc, join, st);
             default: break;
         }
     }
@@ -556,17 +656,9 @@ hipError_t launch_compress(int dtype, bool mfma, const RowsDev& rows, int B, int
     else
         hipLaunchKernelGGL(compress_generic<bf16_t>, grid, dim3(256), 0, st, rows, Hkv, cap, r, Rr, (bf16_t*)Kp,
                            seq_len_out);
-    return hipGetLastError();
-}
-
-hipError_t launch_v_retile(int dtype, const RowsDev& rows, int B, int Hkv, int cap, void* dst, hipStream_t st)
-{
-    int nblk = (rows.n_tokens + 31) / 32;
-    if (nblk < 1) nblk = 1;
-    dim3 grid(nblk, Hkv, B);
-    if (dtype == 0) hipLaunchKernelGGL(v_retile<float>, grid, dim3(256), 0, st, rows, Hkv, cap, (float*)dst);
-    else hipLaunchKernelGGL(v_retile<bf16_t>, grid, dim3(256), 0, st, rows, Hkv, cap, (bf16_t*)dst);
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !values) return e;
+    return dtype == 0 ? launch_v_retile(*values, B, Hkv, cap, (float*)Vc, st) : launch_v_retile(*values, B, Hkv, cap, (bf16_t*)Vc, st);
 }
 
 hipError_t launch_append(int dtype, int B, int Hkv, int cap, int r, const void* k_new, const void* v_new,

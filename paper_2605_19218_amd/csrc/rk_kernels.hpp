@@ -41,9 +41,9 @@ hipError_t launch_gather_rotation(int U, int r, const float* R, const int32_t* k
                                   hipStream_t st);
 
 // ---- rk_compress.hip -------------------------------------------------------
-hipError_t launch_compress(int dtype, bool mfma, const RowsDev& rows, int B, int Hkv, int cap, int r,
-                           const float* Rr, void* Kp, int32_t* seq_len_out, int n_cu, hipStream_t st);
-hipError_t launch_v_retile(int dtype, const RowsDev& rows, int B, int Hkv, int cap, void* dst, hipStream_t st);
+// values: null, or the Values to lay out in Vc; join: by the launch that rotates the Keys, where there is such a kernel
+hipError_t launch_compress(int dtype, bool mfma, const RowsDev& rows, int B, int Hkv, int cap, int r, const float* Rr, void* Kp,
+                           int32_t* seq_len_out, const RowsDev* values, void* Vc, bool join, int n_cu, hipStream_t st);
 // tickets: B zero-initialised ints, left at zero on completion
 hipError_t launch_append(int dtype, int B, int Hkv, int cap, int r, const void* k_new, const void* v_new,
                          const float* Rr, void* Kp, void* Vc, int32_t* seq_len, int32_t* tickets, hipStream_t st);
