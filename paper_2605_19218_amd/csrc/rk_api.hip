@@ -172,10 +172,8 @@ int plan_splits(const rk_ctx* ctx, long units, int tiles, int tiles_min)
             }
         }
         if (S > 64) S = 64;
-        // a split shorter than 512 tokens (four 32-token tiles per wave) no longer amortises its
-        // prologue and its partial: measured optimum on short caches and small batches.  Very short
-        // caches (under 2K tokens) still gain from up to four splits of 256 tokens or more
-        // (32 heads x 1024 tokens: 9.4 us with two splits, 8.2 us with four).
+        // 512 tokens to a split (256 in fp32), and under 2K tokens up to four splits of 256: what a split's prologue and partial were worth
+        // when they cost 3 us more.  more_splits() goes on from here where compute units are idle.
         const int cap_long = tiles / tiles_min, cap_short = tiles / 2 < 4 ? tiles / 2 : 4;
         const int cap = cap_long > cap_short ? cap_long : cap_short;
         if (S > cap) S = cap;

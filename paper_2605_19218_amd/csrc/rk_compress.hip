@@ -582,12 +582,12 @@ static hipError_t launch_compress_mfma_r(const RowsDev& rows, int B, int Hkv, in
     const int order = (int64_t)Hkv * B * nblk <= n_cu ? ORDER_FEW : part ? ORDER_PART_LAST : ORDER_MANY;
     dim3 grid(nblk, Hkv, B);
     ValuesJob<bf16_t> vals;
-    // In the rotation's registers a compute unit holds two (R = 48, 64) or three work-groups that re-tile, eight in a launch of their own.
-    // That is enough while the rows are in the last-level cache, and with R >= 80, where the rotation itself leaves bandwidth over; beyond,
-    // the joined launch is the slower one.  Two launches / one, 32 heads, us: 6100 tokens 32, 35, 37, 41 / 26, 30, 31, 34 (r = 32, 48, 64, 96);
-    // 10000 tokens (9.9 work-groups of the Values per compute unit) 49, 53, 55, 61 / 44, 50, 51, 50; 14000: 69, 73, 76, 84 / 70, 82, 85, 82;
-    // 26000: 126, 132, 137, 152 / 125, 147, 152, 147.  1 x 8 x 1024, r = 32: 9.9 / 7.8; 1 x 4 x 32768, r = 128: 28 / 24.
-    const bool joined = add_values(join ? values : nullptr, Vc, B, Hkv, R >= 80 ? INT64_MAX : 10 * (int64_t)n_cu, grid, vals);
+    // In the rotation's registers a compute unit holds two (R = 48, 64; by LDS from 112 on) or three work-groups that re-tile, eight in a launch
+    // of their own.  That is enough while the rows are in the last-level cache; beyond, the joined launch is the slower one.  Two launches / one,
+    // 32 heads, us: 6100 tokens 32, 35, 37, 41 / 26, 30, 31, 34 (r = 32, 48, 64, 96); 10000 tokens (9.9 work-groups of the Values per compute unit)
+    // 49, 53, 55, 61 / 44, 50, 51, 50; 14000: 69, 73, 76, 84 / 70, 82, 85, 82; 16384, r = 80, 96, 112, 128: 92, 95, 100, 105 / 91, 94, 110, 113.
+    // 1 x 8 x 1024, r = 32: 9.9 / 7.8; 1 x 4 x 32768, r = 128: 28 / 24.
+    const bool joined = add_values(join ? values : nullptr, Vc, B, Hkv, 10 * (int64_t)n_cu, grid, vals);
     const size_t lds = joined && ValuesJob<bf16_t>::LDS_BYTES > Cfg::LDS_BYTES ? ValuesJob<bf16_t>::LDS_BYTES : Cfg::LDS_BYTES;
     if (joined)
         hipLaunchKernelGGL((compress_mfma<R, false, true>), grid, dim3(256), lds, st, rows, Hkv, cap, r, order, Rr, Kp, seq_len_out, vals);
