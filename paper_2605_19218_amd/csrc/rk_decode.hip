@@ -1602,13 +1602,27 @@ static bool fold_pays(int nunit, int S, int tiles_all, int r, int n_cu)
     const int64_t more = fold_rounds(nunit, S, n_cu);
     return more <= 0 || (double)more * 128.0 * tiles_all / S * (keep_padded(r) + D) * 2 < 90e3;
 }
+// The busiest XCD's share of the cache's bytes, ceil(nunit / 8) * 8 / nunit times the fair one: microseconds more at the chip's streaming rate.
+static double fold_excess_us(int nunit, int tiles_all, int r, int elem)
+{
+    const double cache_bytes = (double)nunit * tiles_all * 128.0 * (keep_padded(r) + D) * elem;
+    return ((double)((nunit + 7) / 8 * 8) / nunit - 1.0) * cache_bytes / 6.5e6;
+}
+// bf16 beside splits of text (Sv of the S are the cache's): a split of text runs next to one of the cache on a compute unit, so rounds of all S
+// together say little.  Folded where either count of rounds has it so or the busiest XCD's bytes cost less than 3 us (folded / two launches, us: 100
+// units x 6000 tokens, S = 2 + 3, 500 rows 40.8 / 56.0, with no round more by Sv; 44 x 16384, 5 + 6, 1200 rows 47.6 / 60.8; ragged 84 x 8000, 3 + 3, 200
+// rows, 2.0 us of bytes, 34.9 / 44.3, of equal lengths 59.1 / 59.3.  By bytes and rounds 28 x 16384, 9 + 8, 1200 rows 41.5 / 38.6; 36 x
+// 16384, 7 + 7, 51.1 / 48.9).
+static bool fold_pays_text(int nunit, int S, int Sv, int tiles_all, int r, int n_cu)
+{
+    return fold_pays(nunit, S, tiles_all, r, n_cu) || fold_pays(nunit, Sv, tiles_all, r, n_cu) || fold_excess_us(nunit, tiles_all, r, 2) < 3.0;
+}
 // fp32: not where there are such rounds (r = 64, folded / two launches: 7 units x 24000 tokens, S = 36, 48.0 / 36.2 us; 20 x 3000, S = 12, 23.2 / 17.8;
-// with as many rounds 12 x 3000, S = 12, 15.8 / 16.1; 7 x 6000, S = 23, 19.0 / 19.7), nor where the busiest XCD's share of the bytes, ceil(nunit / 8) * 8 /
-// nunit times the fair one, is 3 us more at the chip's streaming rate (68 x 8000, 3.8 us, 89.8 / 89.7; x 4000, 1.9 us, 48.7 / 49.5).
+// with as many rounds 12 x 3000, S = 12, 15.8 / 16.1; 7 x 6000, S = 23, 19.0 / 19.7), nor where the busiest XCD's bytes cost 3 us more (68 x 8000, 3.8
+// us, 89.8 / 89.7; x 4000, 1.9 us, 48.7 / 49.5).
 static bool fold_pays_f32(int nunit, int S, int tiles_all, int r, int n_cu)
 {
-    const double cache_bytes = (double)nunit * tiles_all * 128.0 * (keep_padded(r) + D) * 4;
-    return fold_rounds(nunit, S, n_cu) <= 0 && ((double)((nunit + 7) / 8 * 8) / nunit - 1.0) * cache_bytes / 6.5e6 < 3.0;
+    return fold_rounds(nunit, S, n_cu) <= 0 && fold_excess_us(nunit, tiles_all, r, 4) < 3.0;
 }
 
 bool decode_mfma_supported(int dtype, int r) { return dtype == 1 && r >= 1 && r <= 128; }
@@ -1665,7 +1679,7 @@ hipError_t launch_decode(int dtype, bool mfma, int B, int Hq, int Hkv, int cap, 
         const int nunit = B * Hkv * ngrp;
         dim3 grid(S, Hkv * ngrp, B);                    // (split, (h_kv, head group), b)
         const bool fused_merge = ((!app && !tapp) || batch_tickets) && (S >= 2 || tapp) && counters && nunit <= n_counters &&
-                                 fold_pays(nunit, S, tiles_all, r, n_cu);
+                                 (text && Sv < S ? fold_pays_text(nunit, S, Sv, tiles_all, r, n_cu) : fold_pays(nunit, S, tiles_all, r, n_cu));
         if (fused_merge) grid = dim3((unsigned)(8 * ((nunit + 7) / 8)), (unsigned)S);
         const int nv = text && Sv < S ? Sv : S;
         const DecodeShape sh{Hkv, cap, S, Sv, tiles_all / nv, nv - tiles_all % nv, (int)slab_tokens(cap), sl2};

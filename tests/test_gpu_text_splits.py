@@ -12,6 +12,7 @@ import oracle
 import paper_2605_19218_amd as rk
 
 from gpu_util import D, DEV, Pipeline, to_dev, to_host
+from test_gpu_f32 import launches
 from test_gpu_parity import check_out, layer, run_prefill
 
 pytestmark = pytest.mark.gpu
@@ -208,3 +209,35 @@ def test_large_bias_beside_text(ctx, splits):
     finally:
         rk.rk_set_option(ctx, rk.RK_OPT_DECODE_SPLITS, 0)
     assert np.array_equal(to_host(p.out), plain)
+
+
+# Whether the merge rides in the split launch where some splits are text's: more work-groups than a round of the compute units, but splits of text
+# beside those of the cache (the first three), and an XCD with too many bytes of the cache (the last two).  Against the plain kernels.
+@pytest.mark.parametrize("units,L,rows,kernels", [(100, 6000, 500, 1), (84, 8000, 200, 1), (44, 16384, 1200, 1), (28, 16384, 1200, 2), (36, 16384, 1200, 2)])
+def test_where_the_merge_rides_along_with_text(ctx, units, L, rows, kernels):
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the table is for 256 compute units")
+    r = 64
+    lay = rk.Layout(units, 1, 1, r, rk.RK_BF16, (L + 31) // 32 * 32, L, seq_len=torch.full((units,), L, device=DEV, dtype=torch.int32))
+    kb, vb = rk.rk_cache_bytes(lay)
+    g = torch.Generator(DEV).manual_seed(2)
+    K, V, q = (torch.randn(n, device=DEV, generator=g).bfloat16() for n in (kb // 2, vb // 2, units * D))
+    q, Rr = q.view(units, 1, D), torch.randn(units, 1, D, r, device=DEV, generator=g) / 11.3
+    kt, vt = (torch.randn(units, 1, rows, D, device=DEV, generator=g).bfloat16() for _ in range(2))
+    ws, outs = torch.empty(rk.rk_decode_workspace_size(ctx, lay), device=DEV, dtype=torch.uint8), []
+    try:
+        for plain in (0, 1):
+            out = torch.full((units, 1, D), float("nan"), device=DEV, dtype=torch.bfloat16)
+
+            def call(stream=None):
+                rk.rk_decode_attn_dual(ctx, lay, q, K, V, Rr, None, rk.Text(kt, vt, rows), 0.0, out, ws, stream=stream)
+
+            if not plain:
+                assert launches(call) == kernels
+            rk.rk_set_option(ctx, rk.RK_OPT_FORCE_GENERIC, plain)
+            call()
+            torch.cuda.synchronize()
+            outs.append(to_host(out))
+    finally:
+        rk.rk_set_option(ctx, rk.RK_OPT_FORCE_GENERIC, 0)
+    check_out(outs[0], outs[1], "bf16")
