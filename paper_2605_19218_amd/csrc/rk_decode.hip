@@ -626,6 +626,15 @@ __device__ __forceinline__ void fold_unit(int unit, int S, int b, int u, size_t 
     }
 }
 
+// A split without a row: no weight, and accumulators that may be multiplied by it.
+__device__ __forceinline__ void empty_partial(float* __restrict__ ws_m, float* __restrict__ ws_l, float* __restrict__ ws_acc, size_t row0,
+                                              int Gc, int S, int split, int tid)
+{
+    for (int i = tid; i < Gc * D; i += 256) ws_acc[((row0 + (i >> 7)) * S + split) * D + (i & 127)] = 0.f;
+    if (tid < Gc) { ws_m[(row0 + tid) * S + split] = NEG_INF; ws_l[(row0 + tid) * S + split] = 0.f; }
+}
+constexpr uint32_t ASK_FIRST = 0x80000000u;       // see ask_first(); in the argument that carries r and the head groups
+
 // The sizes of a matrix-core decode launch.
 struct DecodeShape {
     int Hkv, cap, S;
@@ -1063,7 +1072,7 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
     // folds the partials: the merge kernel, which then also bumps the length, or with FUSED the
     // unit's last work-group (the length is bumped by the batch item's last work-group, see below).
     const bool app = STEP && k_new != nullptr;
-    const int r = r_ngrp & 255, ngrp = r_ngrp >> 8, S = sh.S, cap = sh.cap, Hkv = sh.Hkv;
+    const int r = r_ngrp & 255, ngrp = (r_ngrp & ~ASK_FIRST) >> 8, S = sh.S, cap = sh.cap, Hkv = sh.Hkv;
     const float scale_log2 = sh.scale_log2;
     int split, u, grp, b, unit = 0, G;
     if constexpr (FUSED) {
@@ -1114,6 +1123,16 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
     auto store_row = [&]() {
         if (tr.add && r0 == 0 && r1 > 0 && grp == 0 && tid < 16) text_store_row(tr, ta, b, u - b * Hkv, tid);
     };
+    // A split behind the end of its sequence, where the launch asks for the length first: its empty partial is all that it leaves.
+    bool none = false;
+    if (__builtin_expect(r_ngrp & ASK_FIRST, 0) && (TEXT != TEXT_APART || split < sh.Sv)) {
+        none = 128 * (split * sh.tiles_each + max(split - sh.first_long, 0)) >= min(seq_len[b], cap) && !(app && split == 0);
+        if constexpr (SHARED) {
+            text_share(text.len ? text.len[b] : text.max_len, split, S);
+            none = none && r0 >= r1;
+        }
+        if (none) empty_partial(ws_m, ws_l, ws_acc, row0, Gc, S, split, tid);
+    }
     if constexpr (TEXT == TEXT_APART) {
         // no part of the cache: nothing of what follows is needed (marked unlikely, so that the cache's code stays in line)
         if (__builtin_expect(split >= sh.Sv, 0)) {
@@ -1123,7 +1142,7 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
             store_row();
         }
     }
-    if (TEXT != TEXT_APART || __builtin_expect(split < sh.Sv, 1)) {
+    if ((TEXT != TEXT_APART || __builtin_expect(split < sh.Sv, 1)) && __builtin_expect(!none, 1)) {
         // ---- everything that does not need seq_len goes out first -----------------------------
         // The sequence length costs a cold round trip to memory; the prologue operands (q, this
         // thread's R_r pieces, delta_mu) and the first tile of every wave are requested before
@@ -1306,7 +1325,9 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
                 store_row();
             }
             if constexpr (V_LATE) load_tile_v<R>(TA, Vu, okA ? tokA : 0, okA ? lane : 0);
-            load_tile<R>(TB, Ku, Vu, okB ? tokB : 0, okB ? lane : 0);
+            // (not of an empty split: with the length at hand its rows need not be read)
+            const bool getB = okB && tokB < t1;
+            load_tile<R>(TB, Ku, Vu, getB ? tokB : 0, getB ? lane : 0);
 
             // B operands of the score MFMAs: q~ of head n, split into bf16 head + remainder
             bf16x8 qh[NFA], ql[NFA];
@@ -1458,7 +1479,7 @@ __global__ __launch_bounds__(256, 2) void decode_split_f32(
     __shared__ __attribute__((aligned(16))) float qt[16][R + 4];
     __shared__ __attribute__((aligned(16))) float sbias[4][16], sm_m[4][16], sm_l[4][16];
     __shared__ int sm_last;
-    const int r = r_ngrp & 255, ngrp = r_ngrp >> 8, S = sh.S, cap = sh.cap;
+    const int r = r_ngrp & 255, ngrp = (r_ngrp & ~ASK_FIRST) >> 8, S = sh.S, cap = sh.cap;
     const float scale_log2 = sh.scale_log2;
     int split, u, grp, b, unit = 0, G;
     if constexpr (FUSED) {                         // all splits of a unit on one XCD, as in decode_split_mfma
@@ -1482,6 +1503,16 @@ __global__ __launch_bounds__(256, 2) void decode_split_f32(
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, n = lane & 15;
     __builtin_assume(wave >= 0 && wave < 4);
     if (!FUSED && ta.k && split == 0 && blockIdx.y == 0 && wave == 1) text_append_rows<float>(ta, b, sh.Hkv, lane);
+    auto fold = [&]() {
+        if constexpr (FUSED)
+            fold_unit<false>(unit, S, b, u, row0, Gc, ws_m, ws_l, ws_acc, out, done, false, nullptr, 0, nullptr, 0, nullptr,
+                             nullptr, &sm_last);
+    };
+    if (__builtin_expect(r_ngrp & ASK_FIRST, 0) &&
+        128 * (split * sh.tiles_each + max(split - sh.first_long, 0)) >= min(seq_len[b], cap)) {
+        empty_partial(ws_m, ws_l, ws_acc, row0, Gc, S, split, tid);
+        return fold();
+    }
 
     // q~ = q R_r: D[j][h] = sum_c R_r[c][j] q[h][c]; all loads unconditional with clamped indices, see decode_split_mfma (heads that
     // do not exist repeat the last one)
@@ -1579,9 +1610,7 @@ __global__ __launch_bounds__(256, 2) void decode_split_f32(
     if (k + 2 < nk) compute_tile_f32<R>(TA, m_run, l_run, O, qs, tokA + 64 * (k + 2), t1, g);
     park_and_merge<false>(big, sm_m, sm_l, sbias, O, m_run, l_run, Gc, !FUSED && out, t0 >= t1, out, ws_m, ws_l, ws_acc, row0, S,
                           split, tid);
-    if constexpr (FUSED)
-        fold_unit<false>(unit, S, b, u, row0, Gc, ws_m, ws_l, ws_acc, out, done, false, nullptr, 0, nullptr, 0, nullptr,
-                         nullptr, &sm_last);
+    fold();
 }
 
 // ---------------------------------------------------------------------------
@@ -1596,7 +1625,8 @@ static int64_t fold_rounds(int nunit, int S, int n_cu)
 // bf16: folded unless there are such rounds (folded / two launches in us: 12 units x 12000 tokens, S = 21, 16.0 / 14.3; 28 x 6000, S = 9, 22.5 / 18.5;
 // 36 x 24000, S = 7, 72 / 56; with as many rounds 4 x 12000, S = 23, 10.3 / 11.6; 44 x 24000, S = 5, 64.8 / 65.6; 258 x 2000, S = 4, 32.1 / 34.7; none of 70
 // such shapes lost more than 2 % by it), or where they are so short that one more costs less than the second launch (84 x 700, S = 3, 75 KB a
-// split: 9.0 / 9.4; x 2000, 213 KB: 16.4 / 14.1).
+// split: 9.0 / 9.4; x 2000, 213 KB: 16.4 / 14.1).  The host does not see lengths below the bound, which can turn it round: 84 x 2000, G = 4, 18.2 / 15.3
+// with full sequences, ragged batches 13.9 / 12.7 and 12.1 / 12.6.
 static bool fold_pays(int nunit, int S, int tiles_all, int r, int n_cu)
 {
     const int64_t more = fold_rounds(nunit, S, n_cu);
@@ -1623,6 +1653,16 @@ static bool fold_pays_text(int nunit, int S, int Sv, int tiles_all, int r, int n
 static bool fold_pays_f32(int nunit, int S, int tiles_all, int r, int n_cu)
 {
     return fold_rounds(nunit, S, n_cu) <= 0 && fold_excess_us(nunit, tiles_all, r, 4) < 3.0;
+}
+
+// Whether a work-group asks for the length of its sequence before anything else, so that one behind the end leaves at once.  The round trip
+// costs the others 0.1 to 0.3 us; without it such a split goes through the whole prologue and an empty merge, and reads a tile a wave
+// that it does not need.  Asked with more splits of the cache than compute units (r = 64, bf16, asked / not, us: 320 units x 1000 tokens, S = 4, full 25.9 /
+// 25.4, half 14.7 / 25.2, a twentieth 8.5 / 25.0; 300 x 3000, a twentieth 9.4 / 25.3), and with splits so long that the round trip is
+// nothing (128 x 8000, S = 2: full 70.4 / 70.0, a twentieth 9.4 / 12.0).  One round of shorter splits: 32 x 16000, S = 8, 31.1 / 31.0, 20.7 / 21.4 half.
+static bool ask_first(int nunit, int S, int tiles_all, int n_cu)
+{
+    return S > 1 && ((int64_t)nunit * S > n_cu || tiles_all >= 24 * S);
 }
 
 bool decode_mfma_supported(int dtype, int r) { return dtype == 1 && r >= 1 && r <= 128; }
@@ -1683,7 +1723,8 @@ hipError_t launch_decode(int dtype, bool mfma, int B, int Hq, int Hkv, int cap, 
         if (fused_merge) grid = dim3((unsigned)(8 * ((nunit + 7) / 8)), (unsigned)S);
         const int nv = text && Sv < S ? Sv : S;
         const DecodeShape sh{Hkv, cap, S, Sv, tiles_all / nv, nv - tiles_all % nv, (int)slab_tokens(cap), sl2};
-        const uint32_t r_ngrp = (uint32_t)r | (uint32_t)ngrp << 8, g_units = (uint32_t)G | (fused_merge ? (uint32_t)(nunit - 1) << 16 : 0u);
+        const uint32_t r_ngrp = (uint32_t)r | (uint32_t)ngrp << 8 | (ask_first(nunit, nv, tiles_all, n_cu) ? ASK_FIRST : 0u);
+        const uint32_t g_units = (uint32_t)G | (fused_merge ? (uint32_t)(nunit - 1) << 16 : 0u);
         const bf16_t* q_ = (const bf16_t*)q;
         // the caches are written only by a fused append, whose caller handed them over writable
         bf16_t *k_ = const_cast<bf16_t*>((const bf16_t*)Kp), *v_ = const_cast<bf16_t*>((const bf16_t*)Vc);
@@ -1711,7 +1752,8 @@ hipError_t launch_decode(int dtype, bool mfma, int B, int Hq, int Hkv, int cap, 
         const dim3 grid = fused_merge ? dim3((unsigned)(8 * ((nunit + 7) / 8)), (unsigned)S) : dim3(S, gy, B);
         const int G = Hq / Hkv, ngrp = (G + 15) / 16;
         const DecodeShape sh{Hkv, cap, S, S, tiles_all / S, S - tiles_all % S, (int)slab_tokens(cap), sl2};
-        const uint32_t r_ngrp = (uint32_t)r | (uint32_t)ngrp << 8, g_units = (uint32_t)G | (fused_merge ? (uint32_t)(nunit - 1) << 16 : 0u);
+        const uint32_t r_ngrp = (uint32_t)r | (uint32_t)ngrp << 8 | (ask_first(nunit, S, tiles_all, n_cu) ? ASK_FIRST : 0u);
+        const uint32_t g_units = (uint32_t)G | (fused_merge ? (uint32_t)(nunit - 1) << 16 : 0u);
         float* o = fused_merge || direct ? (float*)out : nullptr;
 #define RK_FORM(RV, FUSED)                                                                                       \
     hipLaunchKernelGGL((decode_split_f32<RV, FUSED>), grid, dim3(256), 0, st, (const float*)q, Rr, dmu, seq_len, r_ngrp, g_units, \
