@@ -48,3 +48,29 @@ def test_value_cache_over_the_keys(dtype):
     want = run(dtype, B, Hkv, L, r, K, V)
     got = run(dtype, B, Hkv, L, r, K.clone(), V, over_keys=True)
     assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]) and torch.equal(got[1], V)
+
+
+def test_a_short_batch_is_fast():
+    """128 sequences of 2000 tokens at most, with 100 in each: 16 work-groups of Values a sequence, one of them with rows, which have to spread over
+    all XCDs.  Measured 0.20 of the full batch's time, 0.45 with all of them on one XCD."""
+    B, L, r, ctx = 128, 2000, 64, rk.rk_create(0)
+    lay = rk.Layout(B, 1, 1, r, rk.RK_BF16, (L + 31) // 32 * 32, L)
+    n = torch.empty(B, dtype=torch.int32, device=DEV)
+    K, V = (torch.randn(B, 1, L, 128, device=DEV).bfloat16() for _ in range(2))
+    Rr, (kb, vb), times = torch.randn(B, 1, 128, r, device=DEV), rk.rk_cache_bytes(lay), []
+    Kp, Vc = torch.zeros(kb, dtype=torch.uint8, device=DEV), torch.zeros(vb, dtype=torch.uint8, device=DEV)
+    for tokens in (L, 100):
+        n.fill_(tokens)
+        best = float("inf")
+        for _ in range(6):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            torch.cuda._sleep(1000000)                        # the calls queue up behind it
+            a.record()
+            for _ in range(30):
+                rk.rk_compress(ctx, lay, rk.Rows(K, L, n_tokens_dev=n), Rr, Kp, rk.Rows(V, L, n_tokens_dev=n), Vc)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        times.append(best)
+    rk.rk_destroy(ctx)
+    assert times[1] <= 0.32 * times[0], times
