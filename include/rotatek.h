@@ -173,7 +173,8 @@ rk_status rk_cache_bytes(const rk_layout* L, size_t* k_packed_bytes, size_t* v_c
  * most 512 / (B H_kv). */
 size_t rk_fit_workspace_size(const rk_layout* L, int32_t max_tokens);
 /* Bytes of workspace rk_decode_attn needs (depends on batch, heads, max_seq_len);
- * what serves one max_seq_len serves every shorter one.                       */
+ * what serves one max_seq_len serves every shorter one, and the splits that are added
+ * on short caches have to fit.  rk_append_decode_attn needs that of max_seq_len + 1. */
 size_t rk_decode_workspace_size(const rk_ctx* ctx, const rk_layout* L);
 /* The split-K plan rk_decode_attn will use: N_s and the tokens of the largest split
  * (the 128-token tiles are shared out evenly, split sizes differ by at most one

@@ -255,8 +255,8 @@ int more_splits(const rk_ctx* ctx, const rk_layout* L, long units, int tiles, in
 }
 
 // N_s, the number of 128-token tiles they share (split s gets floor(tiles / N_s) tiles, the last tiles % N_s splits one
-// more) and the partials the workspace holds per (b, h_q): never fewer than a shorter max_seq_len needs
-struct DecodePlan { int S, tiles, slots; };
+// more) and the bytes of workspace that the call asks for
+struct DecodePlan { int S, tiles; size_t bytes; };
 DecodePlan decode_plan(const rk_ctx* ctx, const rk_layout* L, int text_rows = 0)
 {
     const int G = L->n_q_heads / L->n_kv_heads;
@@ -266,24 +266,29 @@ DecodePlan decode_plan(const rk_ctx* ctx, const rk_layout* L, int text_rows = 0)
     p.tiles = ((L->max_seq_len > 0 ? L->max_seq_len : 1) + 127) / 128;
     // (fp32 rows are twice as long: splits of 256 tokens there)
     p.S = plan_splits(ctx, mfma ? groups : rows, p.tiles, f32 ? 2 : 4);
-    int bound = p.S;                                            // of the splits for this max_seq_len and any shorter one
-    const int n_cu = ctx ? ctx->n_cu : 256;
-    if (mfma && !(ctx && ctx->decode_splits > 0) && groups <= n_cu) {
-        const int most = n_cu / groups < 64 ? (int)(n_cu / groups) : 64, here = most < p.tiles ? most : p.tiles;
-        // (no shape may leave the built-in scratch by it: such a one keeps to the fewer splits at every length)
-        if (here > bound && (f32 || partial_bytes(L, most + DECODE_TEXT_SPLITS_MAX) <= RK_STATIC_SCRATCH_BYTES)) bound = here;
-    }
-    p.slots = bound + DECODE_TEXT_SPLITS_MAX;
+    int slots = p.S + DECODE_TEXT_SPLITS_MAX;
     if (f32) {
         // The size of an fp32 workspace is that of the plain kernel's plan (a split count per query head), by which
         // rk_decode_attn_static takes or refuses a shape: splits per KV head, up to 16 times as many, may not take it over
         // the built-in scratch.  The text takes no splits here, so all slots are the cache's.
-        p.slots = plan_splits(ctx, rows, p.tiles, 4) + DECODE_TEXT_SPLITS_MAX;
-        while (bound > p.slots && partial_bytes(L, bound) > RK_STATIC_SCRATCH_BYTES) --bound;
-        if (p.S > bound) p.S = bound;
-        if (p.slots < bound) p.slots = bound;
+        slots = plan_splits(ctx, rows, p.tiles, 4) + DECODE_TEXT_SPLITS_MAX;
+        while (p.S > slots && partial_bytes(L, p.S) > RK_STATIC_SCRATCH_BYTES) --p.S;
+        if (slots < p.S) slots = p.S;
     }
-    if (bound > p.S) p.S = more_splits(ctx, L, groups, p.tiles, p.S, bound, f32, text_rows);
+    // The splits that more_splits() adds have to fit into twice what these few need, and into the built-in scratch if these do.  A size by
+    // the finer plan itself grows with every 128 tokens, so that a caller who sized once would soon hold too little (1 x 32 query heads on 8 KV heads:
+    // 266 KB at 1000 tokens, 283 at 1030, 666 at 4000).  What is asked rises and falls with the coarse plan's size, whatever the shapes: a
+    // workspace that serves one call by the coarse plan serves it by this one.
+    p.bytes = partial_bytes(L, slots);
+    if (p.bytes < RK_STATIC_SCRATCH_BYTES) p.bytes = 2 * p.bytes < RK_STATIC_SCRATCH_BYTES ? 2 * p.bytes : RK_STATIC_SCRATCH_BYTES;
+    const int n_cu = ctx ? ctx->n_cu : 256;
+    if (mfma && !(ctx && ctx->decode_splits > 0) && groups <= n_cu) {
+        long most = ((long)(p.bytes / (sizeof(float) * rows)) - 1) / (D + 2) - (f32 ? 0 : DECODE_TEXT_SPLITS_MAX);
+        if (most > n_cu / groups) most = n_cu / groups;
+        if (most > 64) most = 64;
+        if (most > p.tiles) most = p.tiles;
+        if (most > p.S) p.S = more_splits(ctx, L, groups, p.tiles, p.S, (int)most, f32, text_rows);
+    }
     return p;
 }
 
@@ -407,7 +412,7 @@ size_t rk_fit_workspace_size(const rk_layout* L, int32_t max_tokens)
 size_t rk_decode_workspace_size(const rk_ctx* ctx, const rk_layout* L)
 {
     if (check_layout(nullptr, L) != RK_OK) return 0;
-    return partial_bytes(L, decode_plan(ctx, L).slots);
+    return decode_plan(ctx, L).bytes;
 }
 
 rk_status rk_decode_plan(const rk_ctx* ctx, const rk_layout* L, int32_t* n_splits, int32_t* tokens_per_split)
@@ -685,7 +690,7 @@ static rk_status decode_common(rk_ctx* ctx, const rk_layout* L, const void* q, c
         }
     }
     const DecodePlan p = decode_plan(ctx, L, text ? td.max_len : 0);
-    const size_t need = partial_bytes(L, p.slots);
+    const size_t need = p.bytes;
     if (use_static) {
         if (need > (size_t)RK_STATIC_SCRATCH_BYTES)
             return fail(ctx, RK_ERR_WORKSPACE, "decode (static scratch): this shape needs %zu bytes of partials, the "
@@ -772,7 +777,7 @@ rk_status rk_append_decode_attn(rk_ctx* ctx, const rk_layout* L, const void* k_n
     La.max_seq_len = L->max_seq_len + 1;
     La.seq_len = seq_len;
     const DecodePlan p = decode_plan(ctx, &La);
-    const size_t need = partial_bytes(&La, p.slots);
+    const size_t need = p.bytes;
     if (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 15))
         return fail(ctx, RK_ERR_WORKSPACE, "append_decode workspace: need %zu bytes, 16-byte aligned", need);
     if (ctx->device == RK_DEVICE_NONE) return fail(ctx, RK_ERR_NO_DEVICE, "valid arguments, but the context has no device");

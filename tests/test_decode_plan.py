@@ -48,3 +48,51 @@ def test_plan_and_workspace(dtype):
         assert finer > 100
     finally:
         rk.rk_destroy(ctx)
+
+
+def coarse_size(dtype, B, Hq, Hkv, L):
+    """What the plan without the finer splits asks for."""
+    rows, units, tiles = B * Hq, B * Hkv * -(-(Hq // Hkv) // 16), max(1, -(-L // 128))
+    if dtype == rk.RK_BF16:
+        return scratch(rows, coarse(units, tiles, 4) + 8)
+    slots, S = coarse(rows, tiles, 4) + 8, coarse(units, tiles, 2)
+    while S > slots and scratch(rows, S) > rk.RK_STATIC_SCRATCH_BYTES:
+        S -= 1
+    return scratch(rows, max(slots, S))
+
+
+@pytest.mark.parametrize("dtype", [rk.RK_F32, rk.RK_BF16])
+def test_a_workspace_serves_what_the_coarse_plan_lets_it(dtype):
+    """A program that sizes its workspace once, for some length, batch and heads, may come with others: a call is refused for its workspace only
+    where the coarse plan, whose size hardly moves on short caches, refuses it too."""
+    ctx, P, shapes = rk.rk_create(rk.RK_DEVICE_NONE), 4096, []
+
+    def layout(B, Hq, Hkv, L):
+        return rk.Layout(B, Hq, Hkv, 64, dtype, (L + 63) // 32 * 32, L, seq_len=P)
+
+    def refused(size, *shape):
+        statuses = []
+        for call in (lambda: rk.rk_decode_attn(ctx, layout(*shape), P, P, P, P, P, 0.0, P, P, workspace_bytes=size),
+                     lambda: rk.rk_append_decode_attn(ctx, layout(*shape[:3], shape[3] - 1), P, P, P, P, P, P, P, P, 0.0, P, P, workspace_bytes=size)):
+            with pytest.raises(rk.RotateKError) as e:
+                call()
+            statuses.append(e.value.status)
+        assert statuses[0] == statuses[1] and statuses[0] in (rk.RK_ERR_NO_DEVICE, rk.RK_ERR_WORKSPACE)
+        return statuses[0] == rk.RK_ERR_WORKSPACE
+
+    try:
+        size = rk.rk_decode_workspace_size(ctx, layout(1, 32, 8, 1000))
+        assert not any(refused(size, 1, 32, 8, L) for L in (1025, 1030, 1200, 2000, 2400))
+        for B in (1, 2, 3, 5, 8, 20, 21, 22, 40, 128, 300):
+            for Hq, Hkv in ((1, 1), (8, 8), (32, 8), (28, 4), (64, 4), (40, 1)):
+                for L in LENGTHS[1:]:
+                    shapes.append((coarse_size(dtype, B, Hq, Hkv, L), rk.rk_decode_workspace_size(ctx, layout(B, Hq, Hkv, L)), (B, Hq, Hkv, L)))
+        shapes.sort()
+        most = 0                                        # of the sizes asked for so far: the coarse plan's grow along the list
+        for few, size, shape in shapes:
+            assert size >= most and few <= size <= max(few, min(2 * few, rk.RK_STATIC_SCRATCH_BYTES)), shape
+            most = size
+        for (few, size, a), (_, _, b) in zip(shapes[7::11], shapes[0::11]):
+            assert not refused(size, *b), (a, b)
+    finally:
+        rk.rk_destroy(ctx)
