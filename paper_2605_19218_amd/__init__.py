@@ -11,6 +11,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import warnings
 from dataclasses import dataclass
 from typing import Any, Optional
 
@@ -114,8 +115,8 @@ def lib():
                 getattr(L, name).restype = C.c_int
         try:
             from . import _rkbind
-        except ImportError:          # not built, or for another interpreter: every call marshals its arguments through ctypes
-            pass
+        except ImportError as e:     # not built for this interpreter: every call marshals its arguments through ctypes
+            warnings.warn(f"the per-token calls go through ctypes, some 5 us more each: {e}", RuntimeWarning, stacklevel=2)
         else:
             _rkbind.bind(Layout, Text, *[C.cast(f, C.c_void_p).value for f in
                                          (L.rk_decode_attn, L.rk_append_decode_attn, L.rk_decode_attn_dual,

@@ -1,6 +1,7 @@
 """Compile the HIP kernels and the C ABI into paper_2605_19218_amd/librotatek.so (gfx950)."""
 from __future__ import annotations
 
+import glob
 import os
 import re
 import subprocess
@@ -11,7 +12,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librotatek.so")
-BIND = os.path.join(HERE, "_rkbind.so")
+BIND = os.path.join(HERE, "_rkbind" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))      # (another interpreter does not find it)
 SOURCES = ["rk_api.hip", "rk_fit.hip", "rk_eig.hip", "rk_subspace.hip", "rk_compress.hip", "rk_decode.hip"]
 
 
@@ -52,16 +53,22 @@ def _run(cmd, verbose):
     return remarks
 
 
-def build_bind(verbose: bool = False) -> str:
-    """The C marshalling of the per-token calls, a plain CPython extension (host code only)."""
-    _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-Wall", "-shared", "-fPIC", "-fvisibility=hidden",
-          "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "rk_bind.cpp"), "-o", BIND], verbose)
+def build_bind(verbose: bool = False):
+    """The C marshalling of the per-token calls, a plain CPython extension (host code only); its path.  The library works without it, through
+    ctypes: where there is no host compiler or no Python.h, a warning and None.  What an earlier build left is removed first."""
+    for old in glob.glob(os.path.join(HERE, "_rkbind*.so")):
+        os.remove(old)
+    try:
+        _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-Wall", "-shared", "-fPIC", "-fvisibility=hidden",
+              "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "rk_bind.cpp"), "-o", BIND], verbose)
+    except (OSError, RuntimeError) as e:
+        print(f"WARNING: {os.path.basename(BIND)} is not built, the per-token calls go through ctypes (some 5 us more each): {e}")
+        return None
     return BIND
 
 
 def build(verbose: bool = False) -> str:
     """Compile every source to an object (in parallel) and link librotatek.so."""
-    build_bind(verbose)
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
     common = [hipcc(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -75,6 +82,7 @@ def build(verbose: bool = False) -> str:
         jobs = [ex.submit(_run, common + ["-c", os.path.join(CSRC, s), "-o", o], verbose) for s, o in zip(SOURCES, objs)]
         remarks = [r for j in jobs for r in j.result()]
     _run([hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs, verbose)
+    build_bind(verbose)
     _report_scratch(remarks)
     return LIB
 

@@ -1,6 +1,9 @@
 """The per-token calls marshalled in C (csrc/rk_bind.cpp) hand the library the arguments that the ctypes path hands it, or leave the call to
 that path: both are pointed at entry points that write down what arrives."""
 import ctypes as C
+import os
+import subprocess
+import sys
 import types
 
 import numpy as np
@@ -10,6 +13,7 @@ import torch
 import paper_2605_19218_amd as rk
 
 B, HQ, HKV, CAP = 2, 8, 2, 64
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 vp, f32, sz, i32 = C.c_void_p, C.c_float, C.c_size_t, C.c_int
 PL, PT = C.POINTER(rk.rk_layout), C.POINTER(rk.rk_text)
 SIGNATURES = {
@@ -171,3 +175,35 @@ def test_statuses():
             assert texts[0] == texts[1]
     finally:
         rk.rk_destroy(ctx)
+
+
+def python(code, **env):
+    res = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=300, cwd=ROOT, env={**os.environ, **env})
+    assert res.returncode == 0, res.stderr
+    return res.stdout, res.stderr
+
+
+def test_without_the_extension():
+    """Where it cannot be imported the calls work through ctypes, and the first use says so."""
+    out, err = python("import sys; sys.modules['paper_2605_19218_amd._rkbind'] = None\n"
+                      "import paper_2605_19218_amd as rk\n"
+                      "c = rk.rk_create(rk.RK_DEVICE_NONE); assert rk._bind is None\n"
+                      "lay = rk.Layout(1, 4, 4, 16, rk.RK_BF16, 64, 40, seq_len=4096)\n"
+                      "try: rk.rk_decode_attn(c, lay, 4096, 4096, 4096, 4096, 4096, 0.0, 4096, 4096, workspace_bytes=1 << 30)\n"
+                      "except rk.RotateKError as e: print(e.status)")
+    assert out.strip() == str(rk.RK_ERR_NO_DEVICE) and "RuntimeWarning" in err and "ctypes" in err
+
+
+def test_build_without_a_host_compiler(tmp_path):
+    """A missing compiler costs the extension, not the build; nothing of an earlier build is left to be loaded, and the file's name is
+    for this interpreter alone."""
+    stale = tmp_path / "_rkbind.so"
+    stale.write_bytes(b"x")
+    out, _ = python("from paper_2605_19218_amd import build\nimport os, sys\n"
+                    "name = os.path.basename(build.BIND)\n"
+                    f"build.HERE, build.BIND = {str(tmp_path)!r}, os.path.join({str(tmp_path)!r}, name)\n"
+                    "print(build.build_bind(), os.listdir(build.HERE))\n"
+                    "os.environ.pop('CXX')\n"
+                    "print(build.build_bind() == build.BIND, os.listdir(build.HERE) == [name], name.split('.', 1)[1] != 'so')",
+                    CXX=str(tmp_path / "no-such-compiler"))
+    assert "WARNING" in out and "None []" in out and "True True True" in out
