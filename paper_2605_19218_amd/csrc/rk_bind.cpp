@@ -161,8 +161,10 @@ bool tail(PyObject* const* a, Tail* t)
     t->bytes = (size_t)(n * e);
     return n >= 0 && e >= 0;
 }
+// To ctypes, which meets what an argument raised here again, and says it.  An interrupt or an exit comes once: it goes on.
 PyObject* other_path()
 {
+    if (PyErr_Occurred() && !PyErr_ExceptionMatches(PyExc_Exception)) return nullptr;
     PyErr_Clear();
     Py_RETURN_NONE;
 }

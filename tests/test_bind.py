@@ -153,6 +153,25 @@ def test_other_forms_go_to_ctypes(paths, name):
         assert fast(*args, None, None) is None
 
 
+class Interrupted:
+    def __init__(self):
+        self.asked = 0
+
+    def data_ptr(self):
+        self.asked += 1
+        if self.asked == 1:
+            raise KeyboardInterrupt
+        return 4096
+
+
+@pytest.mark.parametrize("name", list(SIGNATURES))
+def test_an_interrupt_is_not_swallowed(paths, name):
+    """What comes once, out of an argument's own code, ends the call as it does on the ctypes path."""
+    record, _ = paths
+    with pytest.raises(KeyboardInterrupt):
+        record(name, call(name, layout(), text(), torch.empty(10), kv=Interrupted()), {}, True)
+
+
 def test_statuses():
     """Errors come out as from the ctypes path, with the library's text."""
     ctx = rk.rk_create(rk.RK_DEVICE_NONE)
