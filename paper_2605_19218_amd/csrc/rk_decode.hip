@@ -1624,8 +1624,9 @@ static int64_t fold_rounds(int nunit, int S, int n_cu)
 }
 // bf16: folded unless there are such rounds (folded / two launches in us: 12 units x 12000 tokens, S = 21, 16.0 / 14.3; 28 x 6000, S = 9, 22.5 / 18.5;
 // 36 x 24000, S = 7, 72 / 56; with as many rounds 4 x 12000, S = 23, 10.3 / 11.6; 44 x 24000, S = 5, 64.8 / 65.6; 258 x 2000, S = 4, 32.1 / 34.7; none of 70
-// such shapes lost more than 2 % by it), or where they are so short that one more costs less than the second launch (84 x 700, S = 3, 75 KB a
-// split: 9.0 / 9.4; x 2000, 213 KB: 16.4 / 14.1).  The host does not see lengths below the bound, which can turn it round: 84 x 2000, G = 4, 18.2 / 15.3
+// such shapes lost more than 2 % by it), or where they are so short that one more costs less than the second launch (S = 3, KB a split: 84 x 700,
+// r = 32, 82 KB 8.4 / 9.0; r = 64, 98 9.4 / 9.3; 82 x 1000, r = 32, 109 9.6 / 9.9; 84 x 1100, r = 32, 123 10.8 / 10.1; 84 x 1100, r = 64, 147 12.2 / 11.1; more splits
+// turn earlier: 20 x 6000, r = 32, S = 12, 160 13.0 / 10.4).  The host does not see lengths below the bound, which can turn it round: 84 x 2000, G = 4, 18.2 / 15.3
 // with full sequences, ragged batches 13.9 / 12.7 and 12.1 / 12.6.
 static bool fold_pays(int nunit, int S, int tiles_all, int r, int n_cu)
 {
