@@ -622,9 +622,11 @@ rk_status rk_compress(rk_ctx* ctx, const rk_layout* L, const rk_rows* keys, cons
     bool join = false;
     if (values) {
         vals = to_dev(values);
-        // One launch for Keys and Values, except through token lists (every row's address then comes from a load, and the few work-groups that
-        // fit beside the rotation's registers do not hide two round trips: a prefill of 4 x 32 heads, 8192 rows, half of them listed, r = 32,
-        // took 187 us instead of 178) and where the Value cache lies over the Keys or R_r, which must have been read by then.
+        // One launch for Keys and Values, except where the Value cache lies over the Keys or R_r, which must have been read by then, and
+        // through token lists, for which there is no such kernel.  (Every row's address comes from a load there, and the few work-groups that fit
+        // beside the rotation's registers do not hide two round trips where they are many: a prefill of 4 x 32 heads, 4128 listed rows, r = 32, took 187 us
+        // instead of 178; that is beyond the line at which bf16 is joined at all.  Within it lists would gain as well: two launches / one, us, 1 x 8 x 2410
+        // listed rows, r = 64, 11.7 / 9.4; 1 x 32 x 3000 18.6 / 16.8; 4 x 32 x 1000 ragged 20.8 / 21.4, r = 128 27.0 / 25.4.)
         const size_t es = elem_size(L->dtype), units = (size_t)L->batch * L->n_kv_heads;
         const size_t kb = (size_t)((L->batch - 1) * keys->stride_b + (L->n_kv_heads - 1) * keys->stride_h +
                                    (int64_t)(keys->n_tokens > 0 ? keys->n_tokens - 1 : 0) * keys->stride_t + D) * es;

@@ -196,8 +196,9 @@ __global__ __launch_bounds__(256, 2) void compress_mfma(RowsDev rows, int Hkv, i
     // Work-groups go to the 8 XCDs round-robin by linear index.  The block number is rotated by head and batch item, so that
     // an XCD does not end up with "block 7 of every sequence" (which only the longest sequences have); an odd count of blocks walks
     // over the XCDs by itself, and rotated like that 9, 17, .. blocks would stand still.  ORDER_FEW: a compute unit for
-    // every work-group; rotated as the covariance kernel rotates its chunks, of 512 tokens as well for so few, the rows are
-    // in the L2 of the XCD that read them there (1 x 8 heads, 2410 kept of 4756 rows, fit and rotation 160.9 us, 169.9 otherwise).
+    // every work-group; always rotated, as the covariance kernel rotates its chunks (whose rows start elsewhere but for lengths that fill
+    // them): fit by eigenvectors and rotation, r = 32, us, so / in the other orders: 1 x 8 heads x 1100 tokens 148.3 / 148.7; 1 x 16 x 3000 152.3 / 153.1; 2 x 8,
+    // 1700 listed rows, with Values 157.0 / 158.4; 1 x 8, 4500 listed rows, 157.4 / 158.9; 1 x 8, 2410 listed 149.8 / 150.0.
     if (rotate && (order == ORDER_FEW || !(nx & 1))) bx = (int)((unsigned)(bx + h + b) % (unsigned)nx);
     const int u = b * Hkv + h;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;

@@ -1402,7 +1402,7 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
 // segment, by decode_text_merge.
 // Bound: HBM; the matrix work (R / 4 + 32 MFMA of 32 cycles per tile) takes a third of that time at one query head per
 // KV head.  (32 heads x 2944 tokens, r = 64: 59 us through the plain kernel, which reads a cache line per lane and score
-// channel; 22.3 here with a merge launch behind it, 19.9 with the merge folded in.)
+// channel; 22.3 here with a merge launch behind it, 19.9 with the merge folded in, 17.6 with the prologue and merges of decode_split_mfma.)
 template <int R>
 struct DecTileF32 {
     f32x4 k[R / 16], v[8];

@@ -680,9 +680,11 @@ int cov_chunk_tokens(int dtype, bool mfma, int64_t units, int max_tokens, int n_
     double least = 1e30;
     if (dtype == 1) {
         // A full chunk of 2048 tokens takes about 21 us of streaming when all units stream, and a work-group about 5 us beside it
-        // (dispatch, end of chunk); a shorter chunk is taken where it is at least 15 % cheaper so priced (a last chunk that is
-        // partly filled makes the long ones cheaper than this).  32 heads x 2944 tokens: 64 work-groups of 2048 tokens 16.6 us,
-        // 192 of 512 tokens 11.8 us; 8 heads x 1024 tokens 14.6 / 8.5 us; 128 heads x 5000 tokens 39 us (2048) / 42 us (1024).
+        // (dispatch, end of chunk); a shorter chunk is taken where it is at least 15 % cheaper so priced.  (Rows are dealt evenly to as few
+        // chunks as hold them, so a chunk is seldom full; the price is that of the longest one, and the reduction's partials go with the
+        // count.)  Covariance, reduction and one subspace round, us, chunks of 512 / 1024 / 2048: 32 heads x 2944 tokens 32.4 / 33.0 / 34.2; 8 x
+        // 1024 26.6 / 28.5 / 28.5; 64 x 3000 43.2 / 37.6 / 39.4, ragged 42.8 / 37.7 / 39.5; 128 x 5000 81.9 / 69.0 / 63.4; 128 ragged lists, up to 4128
+        // rows, 67.8 / 53.9 / 46.7; 32 x 9000 ragged 42.3 / 43.4 / 37.3.  Of 28 shapes one is off by more than 0.6 us (8 x 16384: 512 tokens, 35.1 / 32.3 / 34.8).
         for (int ct = COVM_CHUNK; ct >= COV_CHUNK; ct /= 2) {
             const double wgs = (double)units * ((max_tokens + ct - 1) / ct), rounds = (double)((int64_t)(wgs + n_cu - 1) / n_cu);
             const double t = rounds * (21.0 * ct / COVM_CHUNK + 5.0);
