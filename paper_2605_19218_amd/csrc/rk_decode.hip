@@ -647,6 +647,14 @@ struct DecodeShape {
 static uint32_t rcp_of(int d) { return d == 1 ? 0u : (uint32_t)((0x100000000ull + d - 1) / d); }
 __device__ __forceinline__ int div_by(uint32_t x, uint32_t rcp) { return (int)(__umulhi(x, rcp) + (rcp ? 0u : x)); }
 
+// Whether split `split` lies behind `len` tokens.  (Its first token is wanted again later: found here from a copy of the number, or else the
+// compiler finds it once for both, and every work-group waits for the shape's arguments in front of its first loads.)
+__device__ __forceinline__ bool split_behind(int split, const DecodeShape& sh, int len)
+{
+    asm volatile("" : "+s"(split));
+    return 128 * (split * sh.tiles_each + max(split - sh.first_long, 0)) >= min(len, sh.cap);
+}
+
 template <int R>
 struct DecState {
     float m_run, l_run;
@@ -1123,16 +1131,6 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
     auto store_row = [&]() {
         if (tr.add && r0 == 0 && r1 > 0 && grp == 0 && tid < 16) text_store_row(tr, ta, b, u - b * Hkv, tid);
     };
-    // A split behind the end of its sequence, where the launch asks for the length first: its empty partial is all that it leaves.
-    bool none = false;
-    if (__builtin_expect(r_ngrp & ASK_FIRST, 0) && (TEXT != TEXT_APART || split < sh.Sv)) {
-        none = 128 * (split * sh.tiles_each + max(split - sh.first_long, 0)) >= min(seq_len[b], cap) && !(app && split == 0);
-        if constexpr (SHARED) {
-            text_share(text.len ? text.len[b] : text.max_len, split, S);
-            none = none && r0 >= r1;
-        }
-        if (none) empty_partial(ws_m, ws_l, ws_acc, row0, Gc, S, split, tid);
-    }
     if constexpr (TEXT == TEXT_APART) {
         // no part of the cache: nothing of what follows is needed (marked unlikely, so that the cache's code stays in line)
         if (__builtin_expect(split >= sh.Sv, 0)) {
@@ -1142,7 +1140,23 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
             store_row();
         }
     }
-    if ((TEXT != TEXT_APART || __builtin_expect(split < sh.Sv, 1)) && __builtin_expect(!none, 1)) {
+    // A split behind the end of its sequence, where the launch asks for the length first: its empty partial is all that it leaves.
+    auto leaves = [&]() {
+        bool none = split_behind(split, sh, seq_len[b]) && !(app && split == 0);
+        if constexpr (SHARED) {              // (the rows of text_share(), from a number that is only known here)
+            int zero = 0;
+            asm volatile("" : "+s"(zero));
+            const int most = text.max_len + zero;
+            const int raw = text.len ? text.len[b] : most;
+            const int rows = min(max(raw, 0), most) + (ta.k && raw >= 0 && raw < min(ta.capacity, most) ? 1 : 0);
+            none = none && split * (((rows + 31) / 32 + S - 1) / S * 32) >= rows;
+        }
+        return none;
+    };
+    const bool cached = TEXT != TEXT_APART || __builtin_expect(split < sh.Sv, 1);
+    if (cached && __builtin_expect(r_ngrp & ASK_FIRST, 0) && leaves()) {
+        empty_partial(ws_m, ws_l, ws_acc, row0, Gc, S, split, tid);
+    } else if (cached) {
         // ---- everything that does not need seq_len goes out first -----------------------------
         // The sequence length costs a cold round trip to memory; the prologue operands (q, this
         // thread's R_r pieces, delta_mu) and the first tile of every wave are requested before
@@ -1508,8 +1522,7 @@ __global__ __launch_bounds__(256, 2) void decode_split_f32(
             fold_unit<false>(unit, S, b, u, row0, Gc, ws_m, ws_l, ws_acc, out, done, false, nullptr, 0, nullptr, 0, nullptr,
                              nullptr, &sm_last);
     };
-    if (__builtin_expect(r_ngrp & ASK_FIRST, 0) &&
-        128 * (split * sh.tiles_each + max(split - sh.first_long, 0)) >= min(seq_len[b], cap)) {
+    if (__builtin_expect(r_ngrp & ASK_FIRST, 0) && split_behind(split, sh, seq_len[b])) {
         empty_partial(ws_m, ws_l, ws_acc, row0, Gc, S, split, tid);
         return fold();
     }
