@@ -1640,7 +1640,8 @@ static int64_t fold_rounds(int nunit, int S, int n_cu)
 // such shapes lost more than 2 % by it), or where they are so short that one more costs less than the second launch (S = 3, KB a split: 84 x 700,
 // r = 32, 82 KB 8.4 / 9.0; r = 64, 98 9.4 / 9.3; 82 x 1000, r = 32, 109 9.6 / 9.9; 84 x 1100, r = 32, 123 10.8 / 10.1; 84 x 1100, r = 64, 147 12.2 / 11.1; more splits
 // turn earlier: 20 x 6000, r = 32, S = 12, 160 13.0 / 10.4).  The host does not see lengths below the bound, which can turn it round: 84 x 2000, G = 4, 18.2 / 15.3
-// with full sequences, ragged batches 13.9 / 12.7 and 12.1 / 12.6.
+// with full sequences, ragged batches 13.9 / 12.7 and 12.1 / 12.6,
+// all a tenth full 8.5 / 9.0.
 static bool fold_pays(int nunit, int S, int tiles_all, int r, int n_cu)
 {
     const int64_t more = fold_rounds(nunit, S, n_cu);
@@ -1673,10 +1674,11 @@ static bool fold_pays_f32(int nunit, int S, int tiles_all, int r, int n_cu)
 // costs the others 0.1 to 0.3 us; without it such a split goes through the whole prologue and an empty merge, and reads a tile a wave
 // that it does not need.  Asked with more splits of the cache than compute units (r = 64, bf16, asked / not, us: 320 units x 1000 tokens, S = 4, full 25.9 /
 // 25.4, half 14.7 / 25.2, a twentieth 8.5 / 25.0; 300 x 3000, a twentieth 9.4 / 25.3), and with splits so long that the round trip is
-// nothing (128 x 8000, S = 2: full 70.4 / 70.0, a twentieth 9.4 / 12.0).  One round of shorter splits: 32 x 16000, S = 8, 31.1 / 31.0, 20.7 / 21.4 half.
+// nothing (128 x 8000, S = 2: full 70.4 / 70.0, a twentieth 9.4 / 12.0;
+// 84 x 8000, S = 3, a tenth 13.8 / 15.1).  One round of shorter splits: 32 x 16000, S = 8, 31.1 / 31.0, 20.7 / 21.4 half.
 static bool ask_first(int nunit, int S, int tiles_all, int n_cu)
 {
-    return S > 1 && ((int64_t)nunit * S > n_cu || tiles_all >= 24 * S);
+    return S > 1 && ((int64_t)nunit * S > n_cu || tiles_all >= 20 * S);
 }
 
 bool decode_mfma_supported(int dtype, int r) { return dtype == 1 && r >= 1 && r <= 128; }

@@ -1,4 +1,4 @@
-"""Decodes whose work-groups ask for the length of their sequence first (more splits than compute units, or splits of 3072 tokens and more):
+"""Decodes whose work-groups ask for the length of their sequence first (more splits than compute units, or splits of 2560 tokens and more):
 splits that are full, partly filled or behind the end, whole sequences that are empty, an appended row that opens one, text beside them.
 Against the oracle, with a workspace of NaN patterns; and a batch far below its bound takes far less time than a full one."""
 import numpy as np
