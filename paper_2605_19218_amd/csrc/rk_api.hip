@@ -275,12 +275,12 @@ DecodePlan decode_plan(const rk_ctx* ctx, const rk_layout* L, int text_rows = 0)
         while (p.S > slots && partial_bytes(L, p.S) > RK_STATIC_SCRATCH_BYTES) --p.S;
         if (slots < p.S) slots = p.S;
     }
-    // The splits that more_splits() adds have to fit into twice what these few need, and into the built-in scratch if these do.  A size by
+    // The splits that more_splits() adds have to fit into four times what these few need, and into the built-in scratch if these do.  A size by
     // the finer plan itself grows with every 128 tokens, so that a caller who sized once would soon hold too little (1 x 32 query heads on 8 KV heads:
     // 266 KB at 1000 tokens, 283 at 1030, 666 at 4000).  What is asked rises and falls with the coarse plan's size, whatever the shapes: a
     // workspace that serves one call by the coarse plan serves it by this one.
     p.bytes = partial_bytes(L, slots);
-    if (p.bytes < RK_STATIC_SCRATCH_BYTES) p.bytes = 2 * p.bytes < RK_STATIC_SCRATCH_BYTES ? 2 * p.bytes : RK_STATIC_SCRATCH_BYTES;
+    if (p.bytes < RK_STATIC_SCRATCH_BYTES) p.bytes = 4 * p.bytes < RK_STATIC_SCRATCH_BYTES ? 4 * p.bytes : RK_STATIC_SCRATCH_BYTES;
     const int n_cu = ctx ? ctx->n_cu : 256;
     if (mfma && !(ctx && ctx->decode_splits > 0) && groups <= n_cu) {
         long most = ((long)(p.bytes / (sizeof(float) * rows)) - 1) / (D + 2) - (f32 ? 0 : DECODE_TEXT_SPLITS_MAX);
