@@ -647,11 +647,18 @@ struct DecodeShape {
 static uint32_t rcp_of(int d) { return d == 1 ? 0u : (uint32_t)((0x100000000ull + d - 1) / d); }
 __device__ __forceinline__ int div_by(uint32_t x, uint32_t rcp) { return (int)(__umulhi(x, rcp) + (rcp ? 0u : x)); }
 
-// Whether split `split` lies behind `len` tokens.  (Its first token is wanted again later: found here from a copy of the number, or else the
-// compiler finds it once for both, and every work-group waits for the shape's arguments in front of its first loads.)
+// Zero, but not to the compiler: what is made with it is found where it stands, and not once, far ahead, for all that want it.
+__device__ __forceinline__ int zero_here()
+{
+    int zero;
+    asm volatile("s_mov_b32 %0, 0" : "=s"(zero));
+    return zero;
+}
+// Whether split `split` lies behind `len` tokens.  (Its first token is wanted again later; found once for both, every work-group would wait for
+// the shape's arguments in front of its first loads.)
 __device__ __forceinline__ bool split_behind(int split, const DecodeShape& sh, int len)
 {
-    asm volatile("" : "+s"(split));
+    split += zero_here();
     return 128 * (split * sh.tiles_each + max(split - sh.first_long, 0)) >= min(len, sh.cap);
 }
 
@@ -1143,10 +1150,8 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma(
     // A split behind the end of its sequence, where the launch asks for the length first: its empty partial is all that it leaves.
     auto leaves = [&]() {
         bool none = split_behind(split, sh, seq_len[b]) && !(app && split == 0);
-        if constexpr (SHARED) {              // (the rows of text_share(), from a number that is only known here)
-            int zero = 0;
-            asm volatile("" : "+s"(zero));
-            const int most = text.max_len + zero;
+        if constexpr (SHARED) {              // (the rows of text_share(), likewise)
+            const int most = text.max_len + zero_here();
             const int raw = text.len ? text.len[b] : most;
             const int rows = min(max(raw, 0), most) + (ta.k && raw >= 0 && raw < min(ta.capacity, most) ? 1 : 0);
             none = none && split * (((rows + 31) / 32 + S - 1) / S * 32) >= rows;
