@@ -728,6 +728,7 @@ hipError_t launch_cov_partial(int dtype, bool mfma, const RowsDev& rows, int B, 
 hipError_t launch_cov_finalize(int dtype, bool mfma, const RowsDev& rows, int B, int Hkv, int n_chunks, int chunk_tokens, bool center,
                                const float* part_S, const float* part_sum, float* cov, float* mu, int n_cu, hipStream_t st)
 {
+    // (n_chunks: what the host's bound takes; of shorter sequences fewer are live, and both forms read only those.)
     // By rows from two work-groups a compute unit on, and not for long sequences of few units: four chunks are in flight in place of
     // eight, and off-diagonal tiles are read twice.  By rows / by positions: 32 units x 2 chunks 7.4 / 6.2 us; 128 x 2 10.2 / 11.7, x 12 18.7 /
     // 20.2, x 14 21.1 / 20.8, x 16 25.4 / 22.0; 256 x 12 33.5 / 37.2, x 16 45.4 / 42.3; 384 x 14 57 / 61, x 16 65 / 66; 512 x 14 72 / 81; fp32 128 x 6
